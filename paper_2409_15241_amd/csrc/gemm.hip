@@ -1,7 +1,7 @@
 // bf16 MFMA GEMM for gfx950 with fused epilogues: the products of Eq. 1-4 (X*A, (XA)*B_j) and the
 // two products of every "grad matmul" (Sec. 4.1.2: input gradient and weight gradient).
 //
-//   C[m][n] = epilogue( sum_k Aop(m,k) * Bop(k,n) ),  fp32 accumulation in MFMA 32x32x16.
+//   C[m][n] = epilogue( sum_k Aop(m,k) * Bop(k,n) ),  fp32 accumulation in MFMA 16x16x32.
 //
 // Each operand is either contraction-contiguous in memory (KC: [row][k]) or contraction-strided
 // (KS: [k][row]); see lds_dma.h.  The three products of a linear layer map to
@@ -9,11 +9,15 @@
 //   dgrad     dY[M,N'] * W[K',N']^T        : A KC, B KC   (contraction over N')
 //   wgrad     X[M',K']^T * dY[M',N]        : A KS, B KS   (contraction over the tokens M')
 //
-// Work decomposition: one workgroup per BM x BN tile of C, (BM/WM)*(BN/WN) waves, each owning a
-// WM x WN sub-tile as (WN/32) x (WM/32) MFMA accumulators.  Operand tiles of 32 contraction elements
-// travel HBM/L2 -> LDS with buffer_load ... lds through a ring of NST stages: while the MFMAs consume
-// stage kt, the loads of tiles kt+1 .. kt+NST-1 are in flight.  One s_waitcnt vmcnt + one barrier per
-// tile; no VGPR staging, no ds_write.
+// Work decomposition: one workgroup of four waves (one per SIMD) per BM x BN tile of C, each wave owning a
+// WM x WN sub-tile as (WN/16) x (WM/16) MFMA accumulators.  Operand tiles of BK = 64 contraction elements (whole
+// 128-byte lines of a contraction-contiguous operand) travel HBM/L2 -> LDS with buffer_load ... lds into two rings
+// (three tiles of A, two of B); no VGPR staging, no ds_write.
+// What bounds it at large sizes is power: a 16x16x32 MFMA reads and writes half as many accumulator bytes per flop as
+// a 32x32x16 one and sustains 2.04 against 1.79 PFLOP/s on N(0,1) x N(0,0.02) fragments with nothing else running, so
+// every product here is made of those; a wave tile of 128x128 reads 64 bytes of fragments per clock and compute unit at
+// full rate where 128x64 reads 96.  Every product sums its contraction in the same order (32 elements per MFMA), so the
+// bits do not depend on the tile shape.
 // The MFMA is issued with the roles swapped (first operand = B fragment) so that a lane ends up
 // with 4 consecutive n for one m: 8-byte bf16 / 16-byte fp32 stores.
 #include "gemm.h"
@@ -24,15 +28,68 @@
 
 namespace {
 
-constexpr int NST = 4;   // LDS ring depth
+constexpr int BK = 64;      // contraction elements per operand tile
+constexpr int RING_A = 3, RING_B = 2;
+
+// Loads of one operand tile: R rows (columns of C for B), NW waves, IPW one-KiB pieces per wave.
+//   KC tile [R rows][64 k]: 16-byte chunk (r, c) at slot 8 r + (c ^ (r & 7)): the 8 lanes that one LDS clock serves in a
+//       fragment read (8 rows, one chunk index) touch all banks once, and 8 lanes of a load cover a whole 128-byte line.
+//   KS tile [64 k][R rows]: the layout of lds_dma.h.
+// The tile is advanced along the contraction in the buffer resource (base and extent, scalar registers): a load costs
+// the vector ALU nothing but the contraction-tail select of a KC operand.
+template <int R, int NW, bool KS>
+struct TileLoader {
+  static_assert(R % (8 * NW) == 0, "tile pieces must divide over the waves");
+  static constexpr int IPW = R / 8 / NW;
+  uint32_t base[IPW];   // byte offset of the lane's chunk in tile 0, or BUF_OOB
+  int kofs;             // KC: contraction offset of the lane's chunk inside the tile
+  const char* ptr;      // start of the next tile to be loaded
+  int left, step;       // bytes from there to the operand's end; bytes from tile to tile
+  int kleft;            // contraction elements from there on
+
+  template <class ColMap>
+  DEV void init(const void* p, long bytes, int ld, int K, const ColMap& cols, int row0, int row_end, int wave, int lane) {
+    ptr = static_cast<const char*>(p);
+    left = (int)bytes;
+    step = KS ? BK * ld * 2 : BK * 2;
+    kleft = K;
+    kofs = ((lane & 7) ^ (lane >> 3)) * 8;
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      if constexpr (KS) {
+        const int P = (wave * IPW + i) * 1024 + lane * 16;
+        const int k = P / (R * 2), w = P % (R * 2);
+        const int c = cols((((w >> 6) ^ (k & 3)) << 5) + ((w >> 4) & 3) * 8);
+        base[i] = c >= 0 ? (uint32_t)(k * ld + c) * 2u : BUF_OOB;
+      } else {
+        const int r = row0 + 8 * (wave * IPW + i) + (lane >> 3);
+        base[i] = r < row_end ? (uint32_t)(r * ld + kofs) * 2u : BUF_OOB;
+      }
+    }
+  }
+  DEV buf_rsrc rsrc() const { return make_rsrc(ptr, left); }
+  DEV bool inside() const { return KS || kofs < kleft; }     // contraction tail: chunks past K load zeros
+  DEV void advance() { ptr += step; left = left > step ? left - step : 0; kleft -= BK; }
+  DEV void issue(int i, buf_rsrc rs, bool in, uint8_t* tile, int wave) const {
+    const uint32_t off = KS || in ? base[i] : BUF_OOB;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(tile + (wave * IPW + i) * 1024), 16, off, 0, 0, 0);
+  }
+};
+
+template <int I, int N, class F>
+DEV void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
 
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, BM * BN > 128 * 128 ? 1 : 2)
 void gemm_kernel(const GemmArgs p) {
   constexpr int NW = (BM / WM) * (BN / WN);
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int A_BYTES = BM * DMA_BK * 2, B_BYTES = BN * DMA_BK * 2;
-  constexpr int STAGE = A_BYTES + B_BYTES;
+  constexpr int TM = WM / 16, TN = WN / 16;
+  constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   extern __shared__ __align__(1024) uint8_t smem[];
 
   const int tid = threadIdx.x;
@@ -58,9 +115,6 @@ void gemm_kernel(const GemmArgs p) {
   }
   const int m0 = tm * BM, n0 = tn * BN;
 
-  const buf_rsrc A = make_rsrc(p.A, p.a_bytes);
-  const buf_rsrc B = make_rsrc(p.B, p.b_bytes);
-
   // SwiGLU forward: the tile's even 32-column groups are gate columns, the odd ones the matching
   // up columns, so one lane sees gate and up of the same ffn column.
   struct GluCols {
@@ -73,7 +127,7 @@ void gemm_kernel(const GemmArgs p) {
   };
 
   // Rotary embedding: the partner columns (i, i + d/2) of a head must meet in one lane of the epilogue, which pairs
-  // tile columns 32 apart inside a wave's 64 columns (as for SwiGLU).  Heads of 64 columns already lie that way; for
+  // tile columns 32 apart inside every 64 (as for SwiGLU).  Heads of 64 columns already lie that way; for
   // heads of 128 the tile's second and third group of 32 inside every 128 trade places.
   struct RopeCols {
     int n0, n_end, d;
@@ -83,130 +137,165 @@ void gemm_kernel(const GemmArgs p) {
     DEV int operator()(int r) const { const int g = n0 + perm(r); return g < n_end ? g : -1; }
   };
 
-  DmaLoader<BM, NW, AKS> ldA;
-  DmaLoader<BN, NW, BKS> ldB;
-  if constexpr (AKS) ldA.init_ks((int)p.lda, IdentityCols{m0, p.M}, wave, lane);
-  else ldA.init_kc((int)p.lda, m0, p.M, wave, lane);
-  if constexpr (BKS) {
-    if constexpr (EPI == EPI_SWIGLU) ldB.init_ks((int)p.ldb, GluCols{tn * (BN / 2), p.n_split}, wave, lane);
-    else if constexpr (EPI == EPI_ROPE) ldB.init_ks((int)p.ldb, RopeCols{n0, p.N, p.rope_d}, wave, lane);
-    else ldB.init_ks((int)p.ldb, IdentityCols{n0, p.N}, wave, lane);
-  } else {
-    ldB.init_kc((int)p.ldb, n0, p.N, wave, lane);
-  }
-  auto issue_tile = [&](int t) {          // tiles past the end read out of bounds and store zeros
-    uint8_t* st = smem + (t % NST) * STAGE;
-    ldA.issue(A, st, t * DMA_BK, p.K, wave);
-    ldB.issue(B, st + A_BYTES, t * DMA_BK, p.K, wave);
-  };
-  constexpr int LOADS_PER_TILE = DmaLoader<BM, NW, AKS>::IPW + DmaLoader<BN, NW, BKS>::IPW;
+  TileLoader<BM, NW, AKS> ldA;
+  TileLoader<BN, NW, BKS> ldB;
+  constexpr int IPA = TileLoader<BM, NW, AKS>::IPW, IPB = TileLoader<BN, NW, BKS>::IPW;
+  ldA.init(p.A, p.a_bytes, (int)p.lda, p.K, IdentityCols{m0, p.M}, m0, p.M, wave, lane);
+  if constexpr (EPI == EPI_SWIGLU) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, GluCols{tn * (BN / 2), p.n_split}, n0, p.N, wave, lane);
+  else if constexpr (EPI == EPI_ROPE) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, RopeCols{n0, p.N, p.rope_d}, n0, p.N, wave, lane);
+  else ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, IdentityCols{n0, p.N}, n0, p.N, wave, lane);
+  uint8_t* const ringB = smem + RING_A * A_BYTES;
 
-  f32x16 acc[TN][TM];
+  f32x4 acc[TN][TM];
 #pragma unroll
   for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // per-lane LDS byte offsets of the fragments inside a stage, for the two 16-deep MFMA steps of a tile
-  uint32_t offA[2][AKS ? TM : 1], offB[2][BKS ? TN : 1];
+  // per-lane LDS byte offsets of the fragments inside a tile.  A fragment is 16 rows x 32 contraction elements: lane
+  // holds row lane%16, elements 8 (lane/16) ..; the tile's second 32 elements are reached by XOR 64 (KC) or 32 rows on (KS)
+  const int fr = lane & 15, fh = lane >> 4;
+  const uint32_t kc_off = (uint32_t)(fr * 128 + ((fh ^ (fr & 7)) << 4));
+  auto ks_off = [&](int row_bytes, int n16) {       // first of the two transposing reads; the second is 4 k rows on
+    const int k = 8 * fh + (fr >> 2);
+    return (uint32_t)(k * row_bytes + (((n16 >> 1) ^ (k & 3)) << 6) + (n16 & 1) * 32 + 8 * (fr & 3));
+  };
+  uint32_t offA[AKS ? TM : 1], offB[BKS ? TN : 1];
+  if constexpr (AKS) {
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    if constexpr (AKS) {
+    for (int j = 0; j < TM; ++j) offA[j] = ks_off(BM * 2, (wm0 >> 4) + j);
+  } else {
+    offA[0] = kc_off + wm0 * 128;
+  }
+  if constexpr (BKS) {
 #pragma unroll
-      for (int j = 0; j < TM; ++j) offA[ks][j] = ks_frag_off<BM>(lane, ks, (wm0 >> 5) + j);
-    } else {
-      offA[ks][0] = kc_frag_off(lane, ks) + wm0 * 64;
-    }
-    if constexpr (BKS) {
-#pragma unroll
-      for (int i = 0; i < TN; ++i) offB[ks][i] = ks_frag_off<BN>(lane, ks, (wn0 >> 5) + i) + A_BYTES;
-    } else {
-      offB[ks][0] = kc_frag_off(lane, ks) + wn0 * 64 + A_BYTES;
-    }
+    for (int i = 0; i < TN; ++i) offB[i] = ks_off(BN * 2, (wn0 >> 4) + i);
+  } else {
+    offB[0] = kc_off + wn0 * 128;
   }
 
-  const int nk = (p.K + DMA_BK - 1) / DMA_BK;
-#pragma unroll
-  for (int t = 0; t < NST - 1; ++t) issue_tile(t);
-
-  const uint32_t smem_base = lds_addr(smem);
-  const int fr = lane & 31, fh = lane >> 5;
-  constexpr int STEP_READS = (AKS ? 2 * TM : TM) + (BKS ? 2 * TN : TN);
-  static_assert(STEP_READS <= 15, "lgkmcnt is a 4-bit counter");
-  u32x4 fa[2][TM], fb[2][TN];
-  // fragments of MFMA step ks (16 contraction elements) of the stage at LDS address st
-  auto read_step = [&](auto ks_c, uint32_t st) {
-    constexpr int ks = decltype(ks_c)::value;
+  // Fragments of the two 32-deep MFMA steps of a tile.  The two halves of a transposed fragment stay apart until the
+  // wait has passed: joining them earlier could copy a register whose read is still in flight.
+  u32x4 fa[2][AKS ? 1 : TM], fb[2][BKS ? 1 : TN];
+  u32x2 ha[2][AKS ? TM : 1][2], hb[2][BKS ? TN : 1][2];
+  constexpr int RA = AKS ? 2 * TM : TM, RB = BKS ? 2 * TN : TN, READS = RA + RB;
+  auto read_one = [&](auto step, auto which, uint32_t ta, uint32_t tb) {
+    constexpr int s = decltype(step)::value, r = decltype(which)::value;
+    if constexpr (r < RA) {
+      if constexpr (AKS) ha[s][r >> 1][r & 1] = ds_read_tr_at<(s * 32 + (r & 1) * 4) * BM * 2>(ta + offA[r >> 1]);
+      else fa[s][r] = ds_read_b128_at<r * 2048>(ta + (offA[0] ^ (s << 6)));
+    } else {
+      constexpr int q = r - RA;
+      if constexpr (BKS) hb[s][q >> 1][q & 1] = ds_read_tr_at<(s * 32 + (q & 1) * 4) * BN * 2>(tb + offB[q >> 1]);
+      else fb[s][q] = ds_read_b128_at<q * 2048>(tb + (offB[0] ^ (s << 6)));
+    }
+  };
+  // a wait on the LDS counter followed by "uses and redefinitions" of the fragments: no MFMA can move above it
+  auto tie_step = [&](auto step) {
+    constexpr int s = decltype(step)::value;
+    lds_wait<0>();
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
-      if constexpr (AKS) {
-        const u32x2 lo = ds_read_tr_at<0>(st + offA[ks][j]), hi = ds_read_tr_at<8 * BM>(st + offA[ks][j]);
-        fa[ks][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-      } else {
-        fa[ks][j] = (j == 0) ? ds_read_b128_at<0>(st + offA[ks][0]) : (j == 1) ? ds_read_b128_at<2048>(st + offA[ks][0])
-                  : (j == 2) ? ds_read_b128_at<4096>(st + offA[ks][0]) : ds_read_b128_at<6144>(st + offA[ks][0]);
-      }
+      if constexpr (AKS) { tie(ha[s][j][0]); tie(ha[s][j][1]); } else tie(fa[s][j]);
     }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
-      if constexpr (BKS) {
-        const u32x2 lo = ds_read_tr_at<0>(st + offB[ks][i]), hi = ds_read_tr_at<8 * BN>(st + offB[ks][i]);
-        fb[ks][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-      } else {
-        fb[ks][i] = (i == 0) ? ds_read_b128_at<0>(st + offB[ks][0]) : (i == 1) ? ds_read_b128_at<2048>(st + offB[ks][0])
-                  : (i == 2) ? ds_read_b128_at<4096>(st + offB[ks][0]) : ds_read_b128_at<6144>(st + offB[ks][0]);
-      }
+      if constexpr (BKS) { tie(hb[s][i][0]); tie(hb[s][i][1]); } else tie(fb[s][i]);
     }
   };
-  // The MFMAs of step ks.  LDS returns in order, so after lgkmcnt(STEP_READS) only the younger step's
-  // reads may be outstanding.  The empty asm statements "use and define" the fragments so that no MFMA
-  // can be scheduled above the wait.
-  auto mma_step = [&](auto ks_c) {
-    constexpr int ks = decltype(ks_c)::value;
-    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(STEP_READS) : "memory");
-#pragma unroll
-    for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(fa[ks][j]));
-#pragma unroll
-    for (int i = 0; i < TN; ++i) asm volatile("" : "+v"(fb[ks][i]));
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[ks][i]),
-                                                            __builtin_bit_cast(bf16x8, fa[ks][j]), acc[i][j], 0, 0, 0);
+  auto frag_a = [&](int s, int j) {
+    if constexpr (AKS) return __builtin_bit_cast(bf16x8, u32x4{ha[s][j][0][0], ha[s][j][0][1], ha[s][j][1][0], ha[s][j][1][1]});
+    else return __builtin_bit_cast(bf16x8, fa[s][j]);
+  };
+  auto frag_b = [&](int s, int i) {
+    if constexpr (BKS) return __builtin_bit_cast(bf16x8, u32x4{hb[s][i][0][0], hb[s][i][0][1], hb[s][i][1][0], hb[s][i][1][1]});
+    else return __builtin_bit_cast(bf16x8, fb[s][i]);
   };
   using step0 = std::integral_constant<int, 0>;
   using step1 = std::integral_constant<int, 1>;
 
-  // Software pipeline over the 16-deep MFMA steps: the LDS reads of a step are in flight while the
-  // MFMAs of the step before run, across the tile boundary too (tile kt+1 must therefore have landed
-  // by the middle of tile kt: one tile less of HBM/L2 prefetch distance than the ring depth).
-  wait_vmcnt<(NST - 2) * LOADS_PER_TILE>();
+  // Software pipeline.  Tile kt's two MFMA steps: during step 0 the fragments of step 1 are read, during step 1 those
+  // of tile kt+1's step 0.  The one barrier of a tile stands between the steps: by then every wave has read all of tile
+  // kt, whose two ring places are refilled from there on: with B of tile kt+2 during step 1, with A of tile kt+3 during
+  // the next tile's step 0.  So loads are spread over the whole tile, one every 8 MFMAs (a load occupies the address
+  // path for 16 clocks; bunched up behind the barrier they stall the MFMAs issued between them), each has at least a
+  // step to land, and the third place of the A ring keeps a tile in flight across the barrier.
+  // (8192^3, fp32 sums of N(0,1) x N(0,0.02): 1.48 / 1.45 / 1.43 PFLOP/s NT / NN / TN, with a ring of four 32-deep
+  // tiles, eight waves and 32x32x16 MFMAs 1.20 / 1.26 / 1.21; two rings of two: 1.42 / 1.39 / 1.40.)
+  const int nk = (p.K + BK - 1) / BK;
+  auto fill_a = [&](int slot) {
+    const buf_rsrc rs = ldA.rsrc();
+    const bool in = ldA.inside();
+#pragma unroll
+    for (int i = 0; i < IPA; ++i) ldA.issue(i, rs, in, smem + slot * A_BYTES, wave);
+    ldA.advance();
+  };
+  auto fill_b = [&](int slot) {
+    const buf_rsrc rs = ldB.rsrc();
+    const bool in = ldB.inside();
+#pragma unroll
+    for (int i = 0; i < IPB; ++i) ldB.issue(i, rs, in, ringB + slot * B_BYTES, wave);
+    ldB.advance();
+  };
+  fill_a(0); fill_b(0); fill_a(1); fill_b(1); fill_a(2);
+  wait_vmcnt<2 * IPA + IPB>();
   __builtin_amdgcn_s_barrier();
-  read_step(step0{}, smem_base);
+  const uint32_t lds_a = lds_addr(smem), lds_b = lds_addr(ringB);
+  static_for<0, READS>([&](auto r) { read_one(step0{}, r, lds_a, lds_b); });
+
+  constexpr int NM = TM * TN;                          // MFMAs per step
+  constexpr int EVERY = NM * 3 / 4 / READS > 0 ? NM * 3 / 4 / READS : 1;      // MFMAs per LDS read
+  int sa = 0, sb = 0;                                  // ring places of tile kt
+  int free_a = 0;                                      // ring place that tile kt-1 left to the A tile loaded in step 0
   for (int kt = 0; kt < nk; ++kt) {
-    read_step(step1{}, smem_base + (kt % NST) * STAGE);
-    mma_step(step0{});
-    wait_vmcnt<(NST - 3) * LOADS_PER_TILE>();      // tile kt+1 has landed (this wave's share)
-    __builtin_amdgcn_s_barrier();                  // ... everybody's; and nobody reads stage (kt-1)%NST any more
-    issue_tile(kt + NST - 1);
-    read_step(step0{}, smem_base + ((kt + 1) % NST) * STAGE);
-    mma_step(step1{});
+    const uint32_t ta = lds_a + sa * A_BYTES, tb = lds_b + sb * B_BYTES;
+    const int sa_next = sa == RING_A - 1 ? 0 : sa + 1, sb_next = sb ^ 1;
+    const uint32_t ta_next = lds_a + sa_next * A_BYTES, tb_next = lds_b + sb_next * B_BYTES;
+    tie_step(step0{});
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const buf_rsrc rs = ldA.rsrc();
+      const bool in = ldA.inside();
+      uint8_t* dst = smem + free_a * A_BYTES;
+      static_for<0, NM>([&](auto mc) {
+        constexpr int m = decltype(mc)::value, i = m / TM, j = m % TM;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_b(0, i), frag_a(0, j), acc[i][j], 0, 0, 0);
+        if constexpr (m % EVERY == 0 && m / EVERY < READS) read_one(step1{}, std::integral_constant<int, m / EVERY>{}, ta, tb);
+        constexpr int LE = NM / IPA;
+        if constexpr (m % LE == LE / 2 && m / LE < IPA) { if (kt > 0) ldA.issue(m / LE, rs, in, dst, wave); }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if (kt > 0) ldA.advance();
+    }
+    wait_vmcnt<IPA>();                                 // tile kt+1 has landed (this wave's share); A of kt+2 may be in flight
+    tie_step(step1{});                                 // ... and this wave has read all of tile kt
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const buf_rsrc rs = ldB.rsrc();
+      const bool in = ldB.inside();
+      uint8_t* dst = ringB + sb * B_BYTES;
+      static_for<0, NM>([&](auto mc) {
+        constexpr int m = decltype(mc)::value, i = m / TM, j = m % TM;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_b(1, i), frag_a(1, j), acc[i][j], 0, 0, 0);
+        if constexpr (m % EVERY == 0 && m / EVERY < READS) read_one(step0{}, std::integral_constant<int, m / EVERY>{}, ta_next, tb_next);
+        constexpr int LE = NM / IPB;
+        if constexpr (m % LE == LE / 2 && m / LE < IPB) ldB.issue(m / LE, rs, in, dst, wave);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      ldB.advance();
+    }
+    free_a = sa;
+    sa = sa_next; sb = sb_next;
   }
   wait_vmcnt<0>();     // the zero-fill loads issued past the last tile must land before the LDS is released
   // The last iteration's look-ahead reads are still in flight: they must land in their registers
   // before the epilogue may reuse those registers.
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-  for (int j = 0; j < TM; ++j) asm volatile("" : "+v"(fa[0][j]));
-#pragma unroll
-  for (int i = 0; i < TN; ++i) asm volatile("" : "+v"(fb[0][i]));
+  tie_step(step0{});
 
   // ---- epilogue.  Accumulator (i, j) value v of a lane is C[m][n] with
-  //      m = m0 + wm0 + 32 j + lane%32,  n = n0 + wn0 + 32 i + 8 (v/4) + 4 (lane/32) + v%4,
-  // i.e. a lane owns one row: stored from there, every instruction would touch 32 rows with 16 bytes
+  //      m = m0 + wm0 + 16 j + lane%16,  n = n0 + wn0 + 16 i + 4 (lane/16) + v,
+  // stored from there, every instruction would touch 16 rows with 32 or 64 bytes
   // each.  Each wave therefore turns its 32 x WN blocks through its own piece of the (now free) LDS:
   // written by row owner, read back with WN/4 consecutive lanes along a row, so that loads of the side
   // tensors and all stores cover whole 128-byte lines.
@@ -216,8 +305,8 @@ void gemm_kernel(const GemmArgs p) {
   constexpr int RPI = 64 / LPR;                  // rows per read instruction
   uint8_t* wbuf = smem + wave * (32 * ROWB);
   const int rrow = lane / LPR, rcol = (lane % LPR) * 4;
-  const bool tanh_form = p.gelu_tanh != 0;
   constexpr int NT_ROWS = 32 / RPI;              // read-back instructions per 32-row block
+  constexpr int CH = NT_ROWS < 8 ? NT_ROWS : 8;
 
   // what depends on the lane's 4 columns only
   const int nl = wn0 + rcol;                     // tile-local column of the first of this lane's 4
@@ -228,7 +317,7 @@ void gemm_kernel(const GemmArgs p) {
     n = col;
     n_ok = !((nl >> 5) & 1) && col < p.n_split;  // up groups are handled by the lane holding their gate group
   } else if constexpr (EPI == EPI_ROPE) {
-    static_assert(EPI != EPI_ROPE || WN == 64, "the rotary epilogue pairs columns inside 64-column wave blocks");
+    static_assert(EPI != EPI_ROPE || WN % 64 == 0, "the rotary epilogue pairs columns inside 64-column groups");
     n = n0 + RopeCols{n0, p.N, p.rope_d}.perm(nl);            // memory column of the first element of the pair
     n_ok = !((nl >> 5) & 1) && n < p.N;                        // the partner groups are handled by the lane holding i
   } else {
@@ -251,115 +340,124 @@ void gemm_kernel(const GemmArgs p) {
     }
   }
 
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
+  static_for<0, TM / 2>([&](auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
 #pragma unroll
     for (int i = 0; i < TN; ++i)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-        *reinterpret_cast<f32x4*>(wbuf + fr * ROWB + (i * 32 + g * 8 + fh * 4) * 4) = v;
-      }
-    // phase 1: every load of the block (LDS read-back and side tensors) is issued before any is used; rows or
-    // columns outside the matrix read a safe address instead of branching, their results are never stored
-    f32x4 v[NT_ROWS], u[(EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? NT_ROWS : 1], old[EPI == EPI_ACC_F32 ? NT_ROWS : 1];
-    u32x2 sa[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? NT_ROWS : 1], sb[EPI == EPI_DSWIGLU ? NT_ROWS : 1];
-    bool ok[NT_ROWS];
-    long mrow[NT_ROWS];
+      for (int g = 0; g < 2; ++g)
+        *reinterpret_cast<f32x4*>(wbuf + (16 * g + fr) * ROWB + (i * 16 + fh * 4) * 4) = acc[i][2 * j + g];
+    // 8 row groups at a time.  Phase 1: every load of the group (LDS read-back and side tensors) is issued before any is
+    // used; rows or columns outside the matrix read a safe address instead of branching, their results are never stored
+#pragma unroll 1
+    for (int t0 = 0; t0 < NT_ROWS; t0 += CH) {
+      f32x4 v[CH], u[(EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? CH : 1], old[EPI == EPI_ACC_F32 ? CH : 1];
+      u32x2 sa[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? CH : 1], sb[EPI == EPI_DSWIGLU ? CH : 1];
+      bool ok[CH];
+      long mrow[CH];
 #pragma unroll
-    for (int t = 0; t < NT_ROWS; ++t) {
-      const int row = t * RPI + rrow;
-      const int m = m0 + wm0 + j * 32 + row;
-      ok[t] = n_ok && m < p.M;
-      mrow[t] = ok[t] ? (long)m : 0L;
-      v[t] = *reinterpret_cast<const f32x4*>(wbuf + row * ROWB + rcol * 4);
-      if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) u[t] = *reinterpret_cast<const f32x4*>(wbuf + row * ROWB + ((rcol + 32) % WN) * 4);
-      const int ns = ok[t] ? n : 0;
-      if constexpr (EPI == EPI_ACC_F32) {
-        if (p.beta) old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + mrow[t] * p.ldc + ns);
-      } else if constexpr (EPI == EPI_DGELU) {
-        sa[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux + ns);
-      } else if constexpr (EPI == EPI_DSWIGLU) {
-        const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux;
-        sa[t] = *reinterpret_cast<const u32x2*>(aux + ns);
-        sb[t] = *reinterpret_cast<const u32x2*>(aux + p.n_split + ns);
-      }
-    }
-    // phase 2: arithmetic and stores
-#pragma unroll
-    for (int t = 0; t < NT_ROWS; ++t) {
-      f32x4 w = v[t];
-      if constexpr (EPI == EPI_SWIGLU) {
-        if (ok[t]) {
-          bf16_t* aux = static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux;
-          const u32x2 pg = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-          const u32x2 pu = {pack_bf16(u[t][0], u[t][1]), pack_bf16(u[t][2], u[t][3])};
-          *reinterpret_cast<u32x2*>(aux + col) = pg;
-          *reinterpret_cast<u32x2*>(aux + p.n_split + col) = pu;
-          f32x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = w[e] * sigmoid_f(w[e]) * u[t][e];
-          const u32x2 po = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
-          *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + col) = po;
-        }
-      } else if constexpr (EPI == EPI_ACC_F32) {
-        if (p.beta) w += old[t];
-        if (ok[t]) *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + mrow[t] * p.ldc + n) = w;
-      } else if constexpr (EPI == EPI_ROPE) {
-        f32x4 hi = u[t];
-        if (rot) {
-          const float pos = (float)(int)(mrow[t] % p.rope_seq);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float sn, cs;
-            rope_sincos(pos, rfreq[e], &sn, &cs);
-            const float a = w[e], b = hi[e];
-            w[e] = a * cs - b * sn;
-            hi[e] = b * cs + a * sn;
-          }
-        }
-        if (ok[t]) {
-          bf16_t* crow = static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n;
-          const u32x2 plo = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-          const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
-          *reinterpret_cast<u32x2*>(crow) = plo;
-          *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
-        }
-      } else {
-        w += bias4;
-        if constexpr (EPI == EPI_BIAS_GELU) {
-          const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-          if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux + n) = pp;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = gelu_f(w[e], tanh_form);
+      for (int t = 0; t < CH; ++t) {
+        const int row = (t0 + t) * RPI + rrow;
+        const int m = m0 + wm0 + j * 32 + row;
+        ok[t] = n_ok && m < p.M;
+        mrow[t] = ok[t] ? (long)m : 0L;
+        v[t] = *reinterpret_cast<const f32x4*>(wbuf + row * ROWB + rcol * 4);
+        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) u[t] = *reinterpret_cast<const f32x4*>(wbuf + row * ROWB + (rcol ^ 32) * 4);
+        const int ns = ok[t] ? n : 0;
+        if constexpr (EPI == EPI_ACC_F32) {
+          if (p.beta) old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + mrow[t] * p.ldc + ns);
         } else if constexpr (EPI == EPI_DGELU) {
-          w[0] *= gelu_grad_f(bf16_lo(sa[t][0]), tanh_form); w[1] *= gelu_grad_f(bf16_hi(sa[t][0]), tanh_form);
-          w[2] *= gelu_grad_f(bf16_lo(sa[t][1]), tanh_form); w[3] *= gelu_grad_f(bf16_hi(sa[t][1]), tanh_form);
+          sa[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux + ns);
         } else if constexpr (EPI == EPI_DSWIGLU) {
-          const float gv[4] = {bf16_lo(sa[t][0]), bf16_hi(sa[t][0]), bf16_lo(sa[t][1]), bf16_hi(sa[t][1])};
-          const float uv[4] = {bf16_lo(sb[t][0]), bf16_hi(sb[t][0]), bf16_lo(sb[t][1]), bf16_hi(sb[t][1])};
-          f32x4 du;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float sg = sigmoid_f(gv[e]);
-            du[e] = w[e] * gv[e] * sg;                                   // d_act * silu(g)
-            w[e] = w[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));     // d_act * u * silu'(g)
-          }
-          const u32x2 pdu = {pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
-          if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + p.n_split + n) = pdu;
+          const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux;
+          sa[t] = *reinterpret_cast<const u32x2*>(aux + ns);
+          sb[t] = *reinterpret_cast<const u32x2*>(aux + p.n_split + ns);
         }
-        const u32x2 po = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-        if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n) = po;
+      }
+      // Phase 2: arithmetic and stores
+      auto finish = [&](auto tanh_c) __attribute__((always_inline)) {
+        [[maybe_unused]] constexpr bool tanh_form = decltype(tanh_c)::value;
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+          f32x4 w = v[t];
+          if constexpr (EPI == EPI_SWIGLU) {
+            if (ok[t]) {
+              bf16_t* aux = static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux;
+              const u32x2 pg = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+              const u32x2 pu = {pack_bf16(u[t][0], u[t][1]), pack_bf16(u[t][2], u[t][3])};
+              *reinterpret_cast<u32x2*>(aux + col) = pg;
+              *reinterpret_cast<u32x2*>(aux + p.n_split + col) = pu;
+              f32x4 o;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[e] = w[e] * sigmoid_f(w[e]) * u[t][e];
+              const u32x2 po = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+              *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + col) = po;
+            }
+          } else if constexpr (EPI == EPI_ACC_F32) {
+            if (p.beta) w += old[t];
+            if (ok[t]) *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + mrow[t] * p.ldc + n) = w;
+          } else if constexpr (EPI == EPI_ROPE) {
+            f32x4 hi = u[t];
+            if (rot) {
+              const float pos = (float)(int)(mrow[t] % p.rope_seq);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                float sn, cs;
+                rope_sincos(pos, rfreq[e], &sn, &cs);
+                const float a = w[e], b = hi[e];
+                w[e] = a * cs - b * sn;
+                hi[e] = b * cs + a * sn;
+              }
+            }
+            if (ok[t]) {
+              bf16_t* crow = static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n;
+              const u32x2 plo = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+              const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
+              *reinterpret_cast<u32x2*>(crow) = plo;
+              *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
+            }
+          } else {
+            w += bias4;
+            if constexpr (EPI == EPI_BIAS_GELU) {
+              const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+              if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux + n) = pp;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) w[e] = gelu_f(w[e], tanh_form);
+            } else if constexpr (EPI == EPI_DGELU) {
+              w[0] *= gelu_grad_f(bf16_lo(sa[t][0]), tanh_form); w[1] *= gelu_grad_f(bf16_hi(sa[t][0]), tanh_form);
+              w[2] *= gelu_grad_f(bf16_lo(sa[t][1]), tanh_form); w[3] *= gelu_grad_f(bf16_hi(sa[t][1]), tanh_form);
+            } else if constexpr (EPI == EPI_DSWIGLU) {
+              const float gv[4] = {bf16_lo(sa[t][0]), bf16_hi(sa[t][0]), bf16_lo(sa[t][1]), bf16_hi(sa[t][1])};
+              const float uv[4] = {bf16_lo(sb[t][0]), bf16_hi(sb[t][0]), bf16_lo(sb[t][1]), bf16_hi(sb[t][1])};
+              f32x4 du;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float sg = sigmoid_f(gv[e]);
+                du[e] = w[e] * gv[e] * sg;                                   // d_act * silu(g)
+                w[e] = w[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));     // d_act * u * silu'(g)
+              }
+              const u32x2 pdu = {pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
+              if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + p.n_split + n) = pdu;
+            }
+            const u32x2 po = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+            if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n) = po;
+          }
+        }
+      };
+      if constexpr (EPI == EPI_BIAS_GELU || EPI == EPI_DGELU) {
+        if (p.gelu_tanh) finish(std::true_type{}); else finish(std::false_type{});
+      } else {
+        finish(std::true_type{});
       }
     }
-  }
+  });
 }
 
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 hipError_t launch_cfg(const GemmArgs& a0, hipStream_t stream) {
   GemmArgs a = a0;
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  constexpr int LDS = NST * (BM + BN) * DMA_BK * 2;
+  constexpr int LDS = (RING_A * BM + RING_B * BN) * BK * 2;
   const int n_logical = (EPI == EPI_SWIGLU) ? 2 * a.n_split : a.N;
   a.tiles_m = (a.M + BM - 1) / BM;
   a.a_bytes = AKS ? ((long)(a.K - 1) * a.lda + a.M) * 2 : ((long)(a.M - 1) * a.lda + a.K) * 2;
@@ -370,68 +468,50 @@ hipError_t launch_cfg(const GemmArgs& a0, hipStream_t stream) {
   static LdsLimitOnce lds_limit;      // one per instantiation
   if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
   const int T = a.tiles_m * a.tiles_n;
-  a.group_m = (T >= 16 && a.tiles_m >= 2) ? 2 : 0;    // measured: a third fewer L2 misses, 1-2 % on the layer
+  a.group_m = (T >= 16 && a.tiles_m >= 2) ? 4 : 0;
   hipLaunchKernelGGL(kern, dim3(a.group_m ? 8 * ((T + 7) / 8) : T), dim3(NT), LDS, stream, a);
   return hipGetLastError();
 }
 
 template <bool AKS, bool BKS, int EPI>
 hipError_t launch_layout(const GemmArgs& a, int tile_cfg, hipStream_t stream) {
-  if constexpr (EPI == EPI_ROPE) {          // needs 64-column wave blocks: the 128x256 tile has 128
-    if (tile_cfg == GEMM_TILE_128x256) tile_cfg = GEMM_TILE_256x256;
-    switch (tile_cfg) {
-      case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 64, AKS, BKS, EPI>(a, stream);
-      case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, stream);
-      default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, stream);
-    }
-  } else {
-    switch (tile_cfg) {
-      case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 64, AKS, BKS, EPI>(a, stream);
-      case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, stream);
-      case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, stream);
-      default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, stream);
-    }
+  switch (tile_cfg) {
+    case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, stream);
+    case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, stream);
+    case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, stream);
+    default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, stream);
   }
 }
 
 }  // namespace
 
 int gemm_pick_tile(int M, int N, int concurrency) {
-  // The main loop is bound by the operand stream into LDS, so a workgroup's rate grows with the flops
-  // per operand byte of its tile, BM*BN/(BM+BN); the relative per-CU rates below are measured.
-  // Against that, one launch only fills the 256 CUs if it has enough tiles.  With three or more
-  // launches of this size in flight on other streams the chip is kept full dynamically and only the
-  // rate and the padding of ragged edges count; alone, whole rounds of tiles count.  128x128 tiles run
-  // two to a CU (sharing its feed) and balance dynamically.
+  // Time of a launch = rounds of tiles on 256 compute units x time of a tile.  A compute unit's rate on each tile
+  // shape (TFLOP/s, measured on the products of the 13B shard: 5120 deep, 160 to 640 tiles) grows with the flops per
+  // operand byte; 128x128 tiles run two to a unit (4.9 between them, 3.8 when one is alone), the others alone.
+  // A launch with nothing beside it pays for its last round in full; beside three or more others of its size only the
+  // work and the padding of ragged edges count, the other launches fill the rest; beside one other, half way between.
   if (concurrency < 1) concurrency = 1;
   struct Cand { int id, bm, bn; double rate; };
-  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 6.3}, {GEMM_TILE_128x256, 128, 256, 4.5},
-                               {GEMM_TILE_256x128, 256, 128, 4.5}, {GEMM_TILE_128x128, 128, 128, 3.4}};
+  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 6.0}, {GEMM_TILE_256x128, 256, 128, 5.5},
+                               {GEMM_TILE_128x256, 128, 256, 5.3}, {GEMM_TILE_128x128, 128, 128, 4.9}};
   int best = GEMM_TILE_128x128;
   double best_cost = 1e30;
   for (const Cand& c : cands) {
     const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    double rounds, rate = c.rate;
-    if (concurrency >= 3) {
-      // a launch of few tiles is a long serial kernel on its stream's critical path, and the other
-      // launches in flight do not always fill the chip beside it: charge a tile shape for leaving more
-      // than three eighths of its fair share of the chip (256 / concurrency CUs) unused.  Measured on
-      // the 640-column input gradient of the 13B shard, four such launches side by side: 24 tiles of
-      // 256x256 take 103 us, 40 tiles of 256x128 79 us (0.5 % of the step).  (While the slices' weight
-      // gradients still ran between their input gradients, charging against a quarter of the share was
-      // the better rule; charging against the whole share was 0.7 % slower then.)
-      const double share = 160.0 / concurrency;
-      rounds = tiles / 256.0 * (tiles < share ? share / tiles : 1.0);
-    } else if (c.id == GEMM_TILE_128x128) {
-      const double t = tiles * concurrency;
-      if (t > 256) { rate = 2.1; rounds = t / 512 > 1.0 ? t / 512 : 1.0; }
-      else rounds = 1.0;
+    const double unit = (double)c.bm * c.bn / c.rate;
+    double alone;
+    if (c.id == GEMM_TILE_128x128) {
+      const double lone = (double)c.bm * c.bn / 3.8, full = floor(tiles / 512), rest = tiles - 512 * full;
+      alone = full * 2 * unit + (rest == 0 ? 0.0 : rest <= 256 ? lone : 2 * unit);
     } else {
-      const double t = tiles * concurrency;
-      rounds = ceil(t / 256.0);
-      if (rounds > 2) rounds = t / 256.0 + 0.5;
+      alone = ceil(tiles / 256) * unit;
     }
-    const double cost = rounds * c.bm * c.bn / rate;
+    // a launch of few tiles is a long serial kernel on its stream, and the other launches in flight do not always fill
+    // the chip beside it: it is charged for leaving more than three eighths of its share of the chip unused
+    const double share = 160.0 / concurrency;
+    const double shared = (tiles < share ? share : tiles) / 256 * unit;
+    const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.5 * (alone + shared) : shared;
     if (cost < best_cost * 0.999) { best_cost = cost; best = c.id; }
   }
   return best;
