@@ -47,22 +47,22 @@ std::mutex g_warn_mutex;
 char g_warn[512] = "";
 bool g_warned_queues = false;
 
-// The pool's streams overlap only if each sits on a hardware queue of its own.  The HIP runtime reads
-// GPU_MAX_HW_QUEUES once, when it starts (default 4, one of which serves the null stream), so all the library can do
-// is look at the environment the process was started with and say what it sees.
-void note_hw_queues(int nslice) {
-  if (nslice < 4) return;
+// Streams that share a hardware queue run one after the other.  The HIP runtime reads GPU_MAX_HW_QUEUES once, when it
+// starts (default 4, one of which serves the null stream), so all the library can do is look at the environment the
+// process was started with and say what it sees.  A call puts launches on at most three streams of its pool.
+void note_hw_queues(int pool) {
+  if (pool < 4) return;
   std::lock_guard<std::mutex> lock(g_warn_mutex);
   if (g_warned_queues) return;
   const char* env = getenv("GPU_MAX_HW_QUEUES");
   const int have = env ? atoi(env) : 0;
-  if (have >= nslice + 1) return;
+  if (have >= pool + 1) return;
   g_warned_queues = true;
   snprintf(g_warn, sizeof(g_warn),
-           "%d row slices run on %d streams but GPU_MAX_HW_QUEUES is %s%s: with fewer hardware queues than streams + 1 "
-           "two pool streams share a queue and their slices run one after the other (measured 3.7-4.0 ms instead of "
-           "2.6 ms per step on the 13B shard); set GPU_MAX_HW_QUEUES >= %d before the HIP runtime starts",
-           nslice, nslice, env ? "" : "unset (runtime default 4)", env ? env : "", nslice + 1);
+           "a pool of %d streams for as many row slices, but GPU_MAX_HW_QUEUES is %s%s: with fewer hardware queues than streams + 1 "
+           "some streams of the process share a queue and run one after the other; the library itself uses at most three of "
+           "the pool's streams; to give each a queue of its own set GPU_MAX_HW_QUEUES >= %d before the HIP runtime starts",
+           pool, env ? "" : "unset (runtime default 4)", env ? env : "", pool + 1);
 }
 
 constexpr size_t ALIGN = 256;
@@ -74,17 +74,31 @@ struct Layout {
   int h, n, t, r, p, q, b, s, f, d, nl, hl, fl, upc, M, Ms, hq;
   bool llama;
   bool merged;       // weight and vector gradients of a block in one launch each over all slices (see merged_wgrads)
+  int groups;        // row groups: consecutive slices whose launches are one launch each (see row_groups)
   // saved block (bytes)
   size_t ln1, qkv, ctx, lse, x1, ln2, pre, act, mean1, rstd1, mean2, rstd2, saved_total;
   // workspace block (bytes)
   size_t d_pre, dx1, dctx, dqkv, dot, red, ws_total;
-  // per-slice block of partial column sums: area k starts area_off[k] floats in and holds area_rows[k]
-  // rows of area_n[k] floats; red_floats = size of one slice's block
+  // partial column sums: area k starts area_off[k] floats in and holds, for every slice (the norms') or row group (the
+  // column sums'), area_rows[k] rows of area_n[k] floats; red_floats = size of all areas
   size_t red_floats, area_off[8];
   int area_rows[8], area_n[8];
+
+  size_t area(int k, int i) const { return area_off[k] + (size_t)i * area_rows[k] * area_n[k]; }     // of slice or group i
+  int first_slice(int g) const { return (int)((long)p * g / groups); }      // group g = slices [first_slice(g), first_slice(g + 1))
 };
 
 enum { AREA_G1 = 0, AREA_B1, AREA_G2, AREA_B2, AREA_BQKV, AREA_BO, AREA_BUP, AREA_BDOWN, NAREAS };
+
+// Row slices cut the batch so that a program can reduce one slice's partial sums over the ranks while the next slice
+// computes.  Inside one library call nothing waits for a single slice, so consecutive slices are launched together, as
+// one launch over the rows of all of them: larger launches fill 256 compute units better, and a step of many small
+// launches pays for the launches.  What the slices' streams used to buy, two chains of dependent launches side by side
+// so that one fills the chip while the other drains, needs two groups and no more: four streams share the four hardware
+// queues that a process gets by default, and slices that meet on a queue run one after the other.  With one or two
+// slices the second chain is the weight gradients' (the backward's side stream), and a group is all rows.
+// The rule looks at the slicing alone, so neither the arithmetic nor a bit of any result depends on the stream pool.
+int row_groups(int p) { return p > 2 ? 2 : 1; }
 
 int validate(const domino_cfg* c, Layout* L) {
   if (!c) return fail(DOMINO_ERR_NULL_POINTER, "cfg is NULL");
@@ -107,6 +121,7 @@ int validate(const domino_cfg* c, Layout* L) {
   l.llama = c->arch == DOMINO_ARCH_LLAMA;
   if (c->wgrad_per_slice != 0 && c->wgrad_per_slice != 1) return fail(DOMINO_ERR_INVALID_ARG, "wgrad_per_slice must be 0 or 1");
   l.merged = c->p > 2 && !c->wgrad_per_slice;
+  l.groups = row_groups(c->p);
   l.d = l.h / l.n; l.nl = l.n / l.t; l.hl = l.nl * l.d; l.fl = l.f / l.t;
   l.upc = l.fl * (l.llama ? 2 : 1);
   l.hq = l.h / l.q;
@@ -151,11 +166,11 @@ int validate(const domino_cfg* c, Layout* L) {
     size_t fo = 0;
     for (int k = 0; k < NAREAS; ++k) {
       l.area_off[k] = fo; l.area_rows[k] = rows[k]; l.area_n[k] = width[k];
-      fo += (size_t)rows[k] * width[k];
+      fo += (size_t)rows[k] * width[k] * (k == AREA_BQKV || k == AREA_BUP ? l.groups : l.p);
     }
     l.red_floats = (fo + 63) / 64 * 64;
   }
-  l.red = take((size_t)l.p * l.red_floats * 4);
+  l.red = take(l.red_floats * 4);
   l.ws_total = o;
   if (L) *L = l;
   return DOMINO_OK;
@@ -180,7 +195,7 @@ bool capture_pool_ok(int nstreams, int p) {
 
 thread_local bool g_capturing = false;     // streams[0] of the call being enqueued is under HIP graph capture
 
-int begin_call(void* const* streams, int nstreams, int p, bool backward = false) {
+int begin_call(void* const* streams, int nstreams, int p) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
   g_pool = &g_pools[dev];
@@ -196,8 +211,7 @@ int begin_call(void* const* streams, int nstreams, int p, bool backward = false)
   } else {
     g_pool->used = 0;
   }
-  const int nslice = p < nstreams ? p : nstreams;
-  note_hw_queues((backward && !g_capturing && nslice <= 2 && nstreams >= 2 * nslice) ? 2 * nslice : nslice);     // streams with launches in flight
+  note_hw_queues(p < nstreams ? p : nstreams);
   return DOMINO_OK;
 }
 
@@ -248,7 +262,7 @@ struct ProfScope {
   }
 };
 
-// row slices in flight at once in the layer call being enqueued (tile choice of its GEMMs); 1 outside
+// launches in flight at once in the layer call being enqueued (tile choice of its GEMMs); 1 outside
 thread_local int g_concurrency = 1;
 struct ConcurrencyScope {
   explicit ConcurrencyScope(int c) { g_concurrency = c < 1 ? 1 : c; }
@@ -321,50 +335,37 @@ struct BwdLayer {
   const domino_grads* G;
   const void *saved, *x, *dy, *dln2_others, *dln1_others;
   void *dln2_partial, *dln1_partial, *dx;
-  float* red;        // this block's partial column sums: p slices of red_floats floats
+  float* red;        // this block's partial column sums: red_floats floats
   int accumulate;
 };
 
-// which stream of the pool carries which piece (Sec. 4.3.1: a fixed pool, picked by index)
-// Row slice i runs on streams[i % nslice] with all its column pieces: on one GPU there is no all-reduce for a
-// piece to overlap, and pieces on streams of their own were measured slower (the slices already fill the chip).
-// With one or two slices in flight and at least twice as many streams in the pool, the backward puts a slice's weight
-// gradients on a second stream of its own, streams[nslice + i % nslice]: the weight gradient of a product then runs
-// beside the input gradients that follow it on the slice's stream (Sec. 4.1.2 runs it beside the all-reduce of the
-// input gradient).  One or two launches have too few tiles for 256 compute units (11-12 % faster steps on the
-// shards configured with p = 2); from four launches in flight on the chip is full and more only slow each other
-// down (the 13B shard with 4 slices and 4 such extra streams: 630 instead of 790 TFLOP/s).
+// Which stream of the pool carries what (Sec. 4.3.1: a fixed pool, picked by index): row group g runs on streams[g], the
+// backward's weight gradients on a stream of their own behind the groups' when the pool has one, where they fill the
+// compute units that the chain of input gradients, attention and norms leaves idle (Sec. 4.1.2 runs a weight gradient
+// beside the all-reduce of its input gradient).  Not under graph capture: instantiating a graph in which one stream
+// waits for events of two others has crashed inside the runtime, so a captured call keeps to the groups' streams.
 struct StreamPlan {
   void* const* streams;
-  int ns, p, nslice;
-  bool side;             // weight gradients on streams of their own
-  // (not under graph capture: instantiating a graph captured with the weight gradients on streams of their own has
-  // crashed inside the runtime, so a captured call keeps them on the slices' streams)
-  StreamPlan(void* const* s, int n, int p_)
-      : streams(s), ns(n), p(p_), nslice(p_ < n ? p_ : n), side(!g_capturing && (p_ < n ? p_ : n) <= 2 && n >= 2 * (p_ < n ? p_ : n)) {}
-  hipStream_t slice(int i) const { return as_stream(streams[i % nslice]); }
-  hipStream_t second(int i) const { return as_stream(streams[(side ? nslice : 0) + i % nslice]); }
-  int in_flight(bool backward) const { return (backward && side) ? 2 * nslice : nslice; }
-  // streams that a call touches: the first nslice, in the backward also the weight-gradient streams
-  std::vector<char> used(bool backward = false) const {
-    std::vector<char> u(ns, 0);
-    for (int k = 0; k < in_flight(backward); ++k) u[k] = 1;
-    return u;
-  }
+  int ns, lanes;
+  bool side;
+  StreamPlan(void* const* s, int n, const Layout& L, bool backward)
+      : streams(s), ns(n), lanes(L.groups < n ? L.groups : n), side(backward && !g_capturing && n > lanes) {}
+  hipStream_t lane(int g) const { return as_stream(streams[g % lanes]); }
+  hipStream_t side_stream() const { return as_stream(streams[lanes]); }
+  int used() const { return lanes + (side ? 1 : 0); }
 };
 
-// fork: one event on streams[0]; every other stream marked in `used` waits for it
-int fork_streams(const StreamPlan& S, const std::vector<char>& used) {
+// fork: one event on streams[0]; every other stream that the call uses waits for it
+int fork_streams(const StreamPlan& S, int n) {
+  if (n < 2) return DOMINO_OK;
   hipEvent_t fork;
   TRY(next_sync_event(&fork));
   HIP_TRY(hipEventRecord(fork, as_stream(S.streams[0])), "hipEventRecord");
-  for (int k = 1; k < S.ns; ++k)
-    if (used[k]) HIP_TRY(hipStreamWaitEvent(as_stream(S.streams[k]), fork, 0), "hipStreamWaitEvent");
+  for (int k = 1; k < n; ++k) HIP_TRY(hipStreamWaitEvent(as_stream(S.streams[k]), fork, 0), "hipStreamWaitEvent");
   return DOMINO_OK;
 }
-int join_streams(const StreamPlan& S, const std::vector<char>& used) {
-  for (int k = 1; k < S.ns; ++k)
-    if (used[k]) TRY(edge(as_stream(S.streams[k]), as_stream(S.streams[0])));
+int join_streams(const StreamPlan& S, int n) {
+  for (int k = 1; k < n; ++k) TRY(edge(as_stream(S.streams[k]), as_stream(S.streams[0])));
   return DOMINO_OK;
 }
 
@@ -397,432 +398,402 @@ int check_bwd_layer(const Layout& L, const BwdLayer& B, int parts = DOMINO_BWD_A
   return DOMINO_OK;
 }
 
-// Forward of row slice i of one block (Sec. 3.2, Eq. 3): every kernel of the slice on its own stream, the q
-// column pieces of the two row-cut products (Sec. 3.3, Eq. 4) written in place into the full-width buffers.
-// `norm1_done`: the block's Norm1 of this slice has already been written (by the block below, see `next`).
-// `next`: the block above in a stack; its Norm1 is then taken in the same pass that forms this block's output.
-int enqueue_fwd_slice(const Layout& L, const domino_cfg* cfg, const StreamPlan& S, const FwdLayer& B, int i,
-                      int parts = DOMINO_FWD_ALL, bool norm1_done = false, const FwdLayer* next = nullptr) {
-  const domino_params* P = B.P;
-  const int Ms = L.Ms;
-  const bool rms = L.llama;
-  hipStream_t st = S.slice(i);
-  const size_t r0 = (size_t)i * Ms;                       // first token row of the slice
-  const size_t rh = r0 * L.h * 2;                         // byte offset into [M, h] bf16 tensors
-  const char* xi = at(B.x, rh);
-  void* saved = B.saved;
-  char* ln1 = at(saved, L.ln1 + rh);
-  char* qkv = at(saved, L.qkv + r0 * 3 * L.hl * 2);
-  char* ctx = at(saved, L.ctx + r0 * L.hl * 2);
-  float* lse = reinterpret_cast<float*>(at(saved, L.lse)) + (size_t)i * (L.b / L.p) * L.nl * L.s;
-  char* x1 = at(saved, L.x1 + rh);
-  char* ln2 = at(saved, L.ln2 + rh);
-  char* pre = at(saved, L.pre + r0 * L.upc * 2);
-  char* act = at(saved, L.act + r0 * L.fl * 2);
-  float* mean1 = reinterpret_cast<float*>(at(saved, L.mean1)) + r0;
-  float* rstd1 = reinterpret_cast<float*>(at(saved, L.rstd1)) + r0;
-  float* mean2 = reinterpret_cast<float*>(at(saved, L.mean2)) + r0;
-  float* rstd2 = reinterpret_cast<float*>(at(saved, L.rstd2)) + r0;
-
-  if (parts & DOMINO_FWD_ATTN) {
-  if (!norm1_done) {  // F1: Norm1
-    ProfScope ps(PC_NORM_FWD, st);
-    NormFwdArgs a{};
-    a.x = xi; a.gamma = P->norm1_g; a.beta = P->norm1_b; a.y = ln1; a.mean = rms ? nullptr : mean1; a.rstd = rstd1;
-    a.rows = Ms; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
-    LAUNCH(norm_fwd_launch(a, st), "norm1 forward");
-  }
-  {  // F2: X * A (attention), column-parallel, never column-sliced
-    ProfScope ps(PC_GEMM_QKV, st);
-    GemmArgs a = gemm_args(ln1, L.h, P->w_qkv, 3 * L.hl, qkv, 3 * L.hl, Ms, 3 * L.hl, L.h);
-    a.bias = P->b_qkv;
-    if (rope_fused(L)) {     // q and k leave the product already rotated (the rotary embedding of Sec. 5.4)
-      a.rope_d = L.d; a.rope_seq = L.s; a.rope_cols = 2 * L.hl; a.rope_log2_base = log2f(cfg->rope_base);
-      LAUNCH(gemm_launch(GEMM_NN, EPI_ROPE, a, -1, st), "qkv product");
-    } else {
-      LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "qkv product");
-    }
-  }
-  if (L.llama && !rope_fused(L)) {
-    ProfScope ps(PC_ROPE, st);
-    LAUNCH(rope_launch(qkv, 3 * L.hl, Ms, L.s, 0, 2, L.nl, L.d, cfg->rope_base, 0, st), "rotary embedding");
-  }
-  {  // F3
-    ProfScope ps(PC_ATTN_FWD, st);
-    AttnArgs a{};
-    a.qkv = qkv; a.ld = 3 * L.hl; a.ctx = ctx; a.ld_ctx = L.hl; a.lse = lse;
-    a.batch = L.b / L.p; a.seq = L.s; a.heads = L.nl; a.head_dim = L.d; a.scale = 1.0f / sqrtf((float)L.d);
-    LAUNCH(attention_fwd_launch(a, st), "attention forward");
-  }
-  // F4: (XA) * B_j, one piece per column slice, written in place into the full-width buffer
-  for (int j = 0; j < L.q; ++j) {
-    ProfScope ps(PC_GEMM_OUT, st);
-    const size_t cj = (size_t)j * L.hq * 2;
-    GemmArgs a = gemm_args(ctx, L.hl, at(P->w_o, cj), L.h, at(B.attn_partial, rh + cj), L.h, Ms, L.hq, L.hl);
-    LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "out-projection piece");
-  }                                                       // column synchronisation before Norm2: stream order
-  }
-  if (!(parts & DOMINO_FWD_MLP)) return DOMINO_OK;
-  {  // F5: residual + reduced attention output + Norm2
-    ProfScope ps(PC_NORM_FWD, st);
-    NormFwdArgs a{};
-    a.x = xi; a.add1 = at(B.attn_partial, rh); a.add2 = B.attn_others ? at(B.attn_others, rh) : nullptr; a.vec = P->b_o;
-    a.gamma = P->norm2_g; a.beta = P->norm2_b; a.xsum = x1; a.y = ln2; a.mean = rms ? nullptr : mean2; a.rstd = rstd2;
-    a.rows = Ms; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
-    LAUNCH(norm_fwd_launch(a, st), "norm2 forward");
-  }
-  {  // F6: X * A (MLP) with the activation fused
-    ProfScope ps(PC_GEMM_UP, st);
-    GemmArgs a = gemm_args(ln2, L.h, P->w_up, L.upc, act, L.fl, Ms, L.fl, L.h);
-    a.aux = pre; a.ldaux = L.upc; a.gelu_tanh = cfg->gelu_tanh;
-    if (L.llama) { a.n_split = L.fl; LAUNCH(gemm_launch(GEMM_NN, EPI_SWIGLU, a, -1, st), "mlp-up product"); }
-    else { a.bias = P->b_up; LAUNCH(gemm_launch(GEMM_NN, EPI_BIAS_GELU, a, -1, st), "mlp-up product"); }
-  }
-  for (int j = 0; j < L.q; ++j) {  // F7
-    ProfScope ps(PC_GEMM_DOWN, st);
-    const size_t cj = (size_t)j * L.hq * 2;
-    GemmArgs a = gemm_args(act, L.fl, at(P->w_down, cj), L.h, at(B.mlp_partial, rh + cj), L.h, Ms, L.hq, L.fl);
-    LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "mlp-down piece");
-  }
-  if (next) {  // F8 of this block and F1 of the next in one pass over the rows: y is written and normalised at once
-    ProfScope ps(PC_NORM_FWD, st);
-    NormFwdArgs a{};
-    a.x = x1; a.add1 = at(B.mlp_partial, rh); a.add2 = B.mlp_others ? at(B.mlp_others, rh) : nullptr; a.vec = P->b_down;
-    a.gamma = next->P->norm1_g; a.beta = next->P->norm1_b; a.xsum = at(B.y, rh); a.y = at(next->saved, L.ln1 + rh);
-    a.mean = rms ? nullptr : reinterpret_cast<float*>(at(next->saved, L.mean1)) + r0;
-    a.rstd = reinterpret_cast<float*>(at(next->saved, L.rstd1)) + r0;
-    a.rows = Ms; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
-    LAUNCH(norm_fwd_launch(a, st), "block output + next norm1");
-  } else if (B.y) {  // F8
-    ProfScope ps(PC_RESID_OUT, st);
-    LAUNCH(residual_out_launch(x1, at(B.mlp_partial, rh), B.mlp_others ? at(B.mlp_others, rh) : nullptr, P->b_down,
-                               at(B.y, rh), (long)Ms * L.h, L.h, st), "block output");
-  }
-  return DOMINO_OK;
+// The token rows that group g's launches cover.
+struct Rows {
+  size_t r0, rh;         // first row; byte offset of its hidden-wide bf16 row
+  int n, batch, slice;   // rows, batch elements, first slice
+};
+Rows rows_of(const Layout& L, int g) {
+  const int i0 = L.first_slice(g), i1 = L.first_slice(g + 1);
+  const size_t r0 = (size_t)i0 * L.Ms;
+  return {r0, r0 * L.h * 2, (i1 - i0) * L.Ms, (i1 - i0) * (L.b / L.p), i0};
 }
 
-// With one or two row slices (see merged_wgrads for more) the weight gradients are summed over the slices in slice
-// order: slice i's product into a matrix waits for slice i-1's product into the same matrix (one event per matrix; the
-// fifth is for the vector gradients).
-struct WgChain {
-  hipStream_t prev = nullptr, prev_w = nullptr;      // the previous slice's stream and weight-gradient stream
-  hipEvent_t done[5] = {}, cur[5] = {};
-  // the next slice of the block runs on other streams and will wait for this slice's sums: only then are the events
-  // behind them recorded (a record between two kernels costs a few microseconds on the stream)
-  bool feeds_next = true;
-  void next_is(const StreamPlan& S, int i, int p) {
-    feeds_next = i + 1 < p && (S.slice(i + 1) != S.slice(i) || S.second(i + 1) != S.second(i));
-  }
-};
+// Forward of one block (Sec. 3.2, Eq. 3): each step of the block for one row group after the other, every group on its
+// own stream.  Of the two row-cut products (Sec. 3.3, Eq. 4), whose column pieces are written in place into the
+// full-width buffers, the MLP's pieces are one launch, and the out-projection's too when one group holds all rows: a
+// piece is a unit of reduction, and inside a call none is handed out.
+// `norm1_done`: the block's Norm1 has already been written (by the block below, see `next`).
+// `next`: the block above in a stack; its Norm1 is then taken in the same pass that forms this block's output.
+int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& S, const FwdLayer& B,
+                      int parts = DOMINO_FWD_ALL, bool norm1_done = false, const FwdLayer* next = nullptr) {
+  const domino_params* P = B.P;
+  const bool rms = L.llama;
+  void* saved = B.saved;
+  auto rowf = [&](size_t off, const Rows& R) { return reinterpret_cast<float*>(at(saved, off)) + R.r0; };
+  auto ln1 = [&](const Rows& R) { return at(saved, L.ln1 + R.rh); };
+  auto qkv = [&](const Rows& R) { return at(saved, L.qkv + R.r0 * 3 * L.hl * 2); };
+  auto ctx = [&](const Rows& R) { return at(saved, L.ctx + R.r0 * L.hl * 2); };
+  auto x1 = [&](const Rows& R) { return at(saved, L.x1 + R.rh); };
+  auto ln2 = [&](const Rows& R) { return at(saved, L.ln2 + R.rh); };
+  auto act = [&](const Rows& R) { return at(saved, L.act + R.r0 * L.fl * 2); };
+  auto each_group = [&](auto step) -> int {
+    for (int g = 0; g < L.groups; ++g) TRY(step(rows_of(L, g), S.lane(g)));
+    return DOMINO_OK;
+  };
 
-// Backward of row slice i of one block; within the slice each input gradient is enqueued before the weight
-// gradient of the same product (Sec. 4.1.2).
+  if (parts & DOMINO_FWD_ATTN) {
+    if (!norm1_done)
+      TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F1: Norm1
+        ProfScope ps(PC_NORM_FWD, st);
+        NormFwdArgs a{};
+        a.x = at(B.x, R.rh); a.gamma = P->norm1_g; a.beta = P->norm1_b; a.y = ln1(R);
+        a.mean = rms ? nullptr : rowf(L.mean1, R); a.rstd = rowf(L.rstd1, R);
+        a.rows = R.n; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
+        LAUNCH(norm_fwd_launch(a, st), "norm1 forward");
+        return DOMINO_OK;
+      }));
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F2: X * A (attention), column-parallel, never column-sliced
+      ProfScope ps(PC_GEMM_QKV, st);
+      GemmArgs a = gemm_args(ln1(R), L.h, P->w_qkv, 3 * L.hl, qkv(R), 3 * L.hl, R.n, 3 * L.hl, L.h);
+      a.bias = P->b_qkv;
+      if (rope_fused(L)) {     // q and k leave the product already rotated (the rotary embedding of Sec. 5.4)
+        a.rope_d = L.d; a.rope_seq = L.s; a.rope_cols = 2 * L.hl; a.rope_log2_base = log2f(cfg->rope_base);
+        LAUNCH(gemm_launch(GEMM_NN, EPI_ROPE, a, -1, st), "qkv product");
+      } else {
+        LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "qkv product");
+      }
+      return DOMINO_OK;
+    }));
+    if (L.llama && !rope_fused(L))
+      TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
+        ProfScope ps(PC_ROPE, st);
+        LAUNCH(rope_launch(qkv(R), 3 * L.hl, R.n, L.s, 0, 2, L.nl, L.d, cfg->rope_base, 0, st), "rotary embedding");
+        return DOMINO_OK;
+      }));
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F3
+      ProfScope ps(PC_ATTN_FWD, st);
+      AttnArgs a{};
+      a.qkv = qkv(R); a.ld = 3 * L.hl; a.ctx = ctx(R); a.ld_ctx = L.hl;
+      a.lse = reinterpret_cast<float*>(at(saved, L.lse)) + R.r0 * L.nl;
+      a.batch = R.batch; a.seq = L.s; a.heads = L.nl; a.head_dim = L.d; a.scale = 1.0f / sqrtf((float)L.d);
+      LAUNCH(attention_fwd_launch(a, st), "attention forward");
+      return DOMINO_OK;
+    }));
+    const int pieces = L.groups > 1 ? L.q : 1;
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F4: (XA) * B_j
+      for (int j = 0; j < pieces; ++j) {
+        ProfScope ps(PC_GEMM_OUT, st);
+        const int n = L.h / pieces;
+        const size_t cj = (size_t)j * n * 2;
+        GemmArgs a = gemm_args(ctx(R), L.hl, at(P->w_o, cj), L.h, at(B.attn_partial, R.rh + cj), L.h, R.n, n, L.hl);
+        LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "out-projection");
+      }
+      return DOMINO_OK;
+    }));                                                    // column synchronisation before Norm2: stream order
+  }
+  if (!(parts & DOMINO_FWD_MLP)) return DOMINO_OK;
+  TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F5: residual + reduced attention output + Norm2
+    ProfScope ps(PC_NORM_FWD, st);
+    NormFwdArgs a{};
+    a.x = at(B.x, R.rh); a.add1 = at(B.attn_partial, R.rh); a.add2 = B.attn_others ? at(B.attn_others, R.rh) : nullptr; a.vec = P->b_o;
+    a.gamma = P->norm2_g; a.beta = P->norm2_b; a.xsum = x1(R); a.y = ln2(R);
+    a.mean = rms ? nullptr : rowf(L.mean2, R); a.rstd = rowf(L.rstd2, R);
+    a.rows = R.n; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
+    LAUNCH(norm_fwd_launch(a, st), "norm2 forward");
+    return DOMINO_OK;
+  }));
+  TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F6: X * A (MLP) with the activation fused
+    ProfScope ps(PC_GEMM_UP, st);
+    GemmArgs a = gemm_args(ln2(R), L.h, P->w_up, L.upc, act(R), L.fl, R.n, L.fl, L.h);
+    a.aux = at(saved, L.pre + R.r0 * L.upc * 2); a.ldaux = L.upc; a.gelu_tanh = cfg->gelu_tanh;
+    if (L.llama) { a.n_split = L.fl; LAUNCH(gemm_launch(GEMM_NN, EPI_SWIGLU, a, -1, st), "mlp-up product"); }
+    else { a.bias = P->b_up; LAUNCH(gemm_launch(GEMM_NN, EPI_BIAS_GELU, a, -1, st), "mlp-up product"); }
+    return DOMINO_OK;
+  }));
+  TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F7
+    ProfScope ps(PC_GEMM_DOWN, st);
+    GemmArgs a = gemm_args(act(R), L.fl, P->w_down, L.h, at(B.mlp_partial, R.rh), L.h, R.n, L.h, L.fl);
+    LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "mlp-down product");
+    return DOMINO_OK;
+  }));
+  return each_group([&](const Rows& R, hipStream_t st) -> int {
+    const void* others = B.mlp_others ? at(B.mlp_others, R.rh) : nullptr;
+    if (next) {  // F8 of this block and F1 of the next in one pass over the rows: y is written and normalised at once
+      ProfScope ps(PC_NORM_FWD, st);
+      NormFwdArgs a{};
+      a.x = x1(R); a.add1 = at(B.mlp_partial, R.rh); a.add2 = others; a.vec = P->b_down;
+      a.gamma = next->P->norm1_g; a.beta = next->P->norm1_b; a.xsum = at(B.y, R.rh); a.y = at(next->saved, L.ln1 + R.rh);
+      a.mean = rms ? nullptr : reinterpret_cast<float*>(at(next->saved, L.mean1)) + R.r0;
+      a.rstd = reinterpret_cast<float*>(at(next->saved, L.rstd1)) + R.r0;
+      a.rows = R.n; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
+      LAUNCH(norm_fwd_launch(a, st), "block output + next norm1");
+    } else if (B.y) {  // F8
+      ProfScope ps(PC_RESID_OUT, st);
+      LAUNCH(residual_out_launch(x1(R), at(B.mlp_partial, R.rh), others, P->b_down, at(B.y, R.rh), (long)R.n * L.h, L.h, st), "block output");
+    }
+    return DOMINO_OK;
+  });
+}
+
 // The gradients of a block's intermediate activations that its weight gradients read (whole tensors, all row slices).
 struct GradBufs { char *d_pre, *dx1, *dqkv; };
 GradBufs grad_bufs(const Layout& L, void* ws) { return {at(ws, L.d_pre), at(ws, L.dx1), at(ws, L.dqkv)}; }
 
 // With more than two row slices the weight gradients are not formed slice by slice: one launch per matrix contracts
-// over all rows of the block after the last slice's input gradients (enqueue_block_end).  Slice by slice, every
-// slice after the first reads and rewrites the whole fp32 gradient (for the 13B shard 0.94 GB of 9.4 GB per step at
-// p = 4) in launches a quarter as deep; the step sits on the board's power cap, so the saved traffic is saved time
-// (3.5-4.5 % of the step).  With one or two slices the slice-by-slice launches on second streams are faster (they fill
-// a chip that two slices leave half empty), so the rule follows p alone and the arithmetic does not depend on the pool.
-// cfg->wgrad_per_slice keeps the slice-by-slice order of Sec. 4.1.2 for any p.
+// over all rows of the block.  Slice by slice, every slice after the first reads and rewrites the whole fp32 gradient
+// (for the 13B shard 0.94 GB of 9.4 GB per step at p = 4) in launches a quarter as deep.  With one or two slices they
+// are summed over the slices in slice order.  cfg->wgrad_per_slice keeps the slice-by-slice order of Sec. 4.1.2 for any p.
 inline bool merged_wgrads(const Layout& L) { return L.merged; }
 
-// out (+)= the partial rows that `nslices` consecutive slices, the first one's block of partial sums at `red`, left for
-// the eight vector gradients (norm gains and shifts, biases): one launch, slices and rows summed in index order
-int vector_grads(const Layout& L, const BwdLayer& B, const float* red, int nslices, int accumulate, hipStream_t st) {
+enum { WG_DOWN = 0, WG_UP, WG_OUT, WG_QKV, NWGRADS };
+
+// the weight gradient of one matrix (and the column sums behind the bias of the same product), on `st`: one launch over
+// all rows or one per slice, in slice order
+int weight_gradient(const Layout& L, const GradBufs& gb, const BwdLayer& B, int which, hipStream_t st) {
+  const char* sv = static_cast<const char*>(B.saved);
   const domino_grads* G = B.G;
-  ProfScope ps(PC_COLSUM, st);
-  struct { int k; float* out; } vec[NAREAS] = {
-    {AREA_G1, G->norm1_g}, {AREA_B1, G->norm1_b}, {AREA_G2, G->norm2_g}, {AREA_B2, G->norm2_b},
-    {AREA_BQKV, G->b_qkv}, {AREA_BO, G->b_o}, {AREA_BUP, G->b_up}, {AREA_BDOWN, G->b_down}};
-  ColsumJobs jobs{};
-  int njobs = 0;
-  for (auto& v : vec) {
-    if (!v.out) continue;
-    if (L.llama && v.k != AREA_G1 && v.k != AREA_G2) continue;
-    jobs.job[njobs++] = {red + L.area_off[v.k], v.out, L.area_rows[v.k], L.area_n[v.k], (long)L.area_n[v.k], nslices, (long)L.red_floats};
+  struct { int cls; const void* A; long lda; const void* Bm; long ldb; float* C; int M, N; int bias; } const tab[NWGRADS] = {
+    {PC_WGRAD_DOWN, sv + L.act, L.fl, B.dy, L.h, G->w_down, L.fl, L.h, -1},
+    {PC_WGRAD_UP, sv + L.ln2, L.h, gb.d_pre, L.upc, G->w_up, L.h, L.upc, AREA_BUP},
+    {PC_WGRAD_OUT, sv + L.ctx, L.hl, gb.dx1, L.h, G->w_o, L.hl, L.h, -1},
+    {PC_WGRAD_QKV, sv + L.ln1, L.h, gb.dqkv, 3 * L.hl, G->w_qkv, L.h, 3 * L.hl, AREA_BQKV}};
+  const auto& w = tab[which];
+  const int launches = merged_wgrads(L) ? 1 : L.p, K = L.M / launches;
+  for (int i = 0; i < launches; ++i) {
+    ProfScope ps(w.cls, st);
+    const size_t r0 = (size_t)i * K;
+    GemmArgs a = gemm_args(at(w.A, r0 * w.lda * 2), w.lda, at(w.Bm, r0 * w.ldb * 2), w.ldb, w.C, w.N, w.M, w.N, K);
+    a.beta = (i > 0 || B.accumulate) ? 1 : 0;
+    LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
   }
-  LAUNCH(colsum_finish_jobs_launch(jobs, njobs, accumulate, st), "vector gradient reduction");
+  if (!L.llama && w.bias >= 0)
+    for (int g = 0; g < L.groups; ++g) {
+      const Rows R = rows_of(L, g);
+      ProfScope ps(PC_COLSUM, st);
+      LAUNCH(colsum_partial_launch(at(w.Bm, R.r0 * w.ldb * 2), w.ldb, R.n, w.N, B.red + L.area(w.bias, g), st), "bias gradient");
+    }
   return DOMINO_OK;
 }
 
-// Points on a slice's stream after which the merged launches at the end of the block, on other streams, may read what
-// the slice has written: `ready` behind the last kernel of the call that writes an operand of a weight gradient (the
-// attention backward, which leaves the gradient of q, k, v; in a call of the MLP part alone the down-projection's input
-// gradient), `dx` behind the Norm1 backward.  One record each: a record between two kernels costs a few microseconds.
-struct SliceEvents {
-  hipStream_t on = nullptr;
-  hipEvent_t ready = nullptr, dx = nullptr;
+// The eight vector gradients (norm gains and shifts, biases) from the partial rows that the slices' norm backwards and
+// the groups' column sums left: summed in index order, in one launch over all slices or in one per slice (the groups'
+// column sums then belong to the first).
+int vector_gradients(const Layout& L, const BwdLayer& B, hipStream_t st) {
+  const domino_grads* G = B.G;
+  const int launches = merged_wgrads(L) ? 1 : L.p, slices = L.p / launches;
+  for (int i = 0; i < launches; ++i) {
+    ProfScope ps(PC_COLSUM, st);
+    struct { int k; float* out; } const vec[NAREAS] = {
+      {AREA_G1, G->norm1_g}, {AREA_B1, G->norm1_b}, {AREA_G2, G->norm2_g}, {AREA_B2, G->norm2_b},
+      {AREA_BQKV, G->b_qkv}, {AREA_BO, G->b_o}, {AREA_BUP, G->b_up}, {AREA_BDOWN, G->b_down}};
+    ColsumJobs jobs{};
+    int njobs = 0;
+    for (auto& v : vec) {
+      if (!v.out) continue;
+      if (L.llama && v.k != AREA_G1 && v.k != AREA_G2) continue;
+      const bool by_group = v.k == AREA_BQKV || v.k == AREA_BUP;
+      if (by_group && i > 0) continue;
+      jobs.job[njobs++] = {B.red + L.area(v.k, by_group ? 0 : i * slices), v.out, L.area_rows[v.k], L.area_n[v.k], (long)L.area_n[v.k],
+                           by_group ? L.groups : slices, (long)L.area_rows[v.k] * L.area_n[v.k]};
+    }
+    LAUNCH(colsum_finish_jobs_launch(jobs, njobs, (i > 0 || B.accumulate) ? 1 : 0, st), "vector gradient reduction");
+  }
+  return DOMINO_OK;
+}
+
+// What the blocks of a stack hand on to each other: events behind the weight gradients of a block and the stream each ran
+// on (the tensors they read are written again two blocks later), and behind its Norm1 backward, per group (it writes the
+// dy of the block below).
+struct BlockEvents {
+  hipEvent_t wgrad[NWGRADS] = {};
+  hipStream_t on[NWGRADS] = {};
+  std::vector<hipEvent_t> dx;
 };
 
-int enqueue_bwd_slice(const Layout& L, const domino_cfg* cfg, void* ws, const GradBufs& gb, hipStream_t st, hipStream_t wst,
-                      const BwdLayer& B, int i, WgChain& wg, int parts = DOMINO_BWD_ALL, hipEvent_t before_dx = nullptr,
-                      SliceEvents* marks = nullptr) {
-  const domino_params* P = B.P;
-  const domino_grads* G = B.G;
-  const void* saved = B.saved;
-  const int Ms = L.Ms;
-  const bool rms = L.llama;
-  const size_t r0 = (size_t)i * Ms;
-  const size_t rh = r0 * L.h * 2;
-  const char* xi = B.x ? at(B.x, rh) : nullptr;
-  const char* dyi = B.dy ? at(B.dy, rh) : nullptr;
-  const char* ln1 = at(saved, L.ln1 + rh);
-  const char* qkv = at(saved, L.qkv + r0 * 3 * L.hl * 2);
-  const char* ctx = at(saved, L.ctx + r0 * L.hl * 2);
-  const float* lse = reinterpret_cast<const float*>(at(saved, L.lse)) + (size_t)i * (L.b / L.p) * L.nl * L.s;
-  const char* x1 = at(saved, L.x1 + rh);
-  const char* ln2 = at(saved, L.ln2 + rh);
-  const char* pre = at(saved, L.pre + r0 * L.upc * 2);
-  const char* act = at(saved, L.act + r0 * L.fl * 2);
-  const float* mean1 = reinterpret_cast<const float*>(at(saved, L.mean1)) + r0;
-  const float* rstd1 = reinterpret_cast<const float*>(at(saved, L.rstd1)) + r0;
-  const float* mean2 = reinterpret_cast<const float*>(at(saved, L.mean2)) + r0;
-  const float* rstd2 = reinterpret_cast<const float*>(at(saved, L.rstd2)) + r0;
-  char* d_pre = gb.d_pre + r0 * L.upc * 2;
-  char* dx1 = gb.dx1 + rh;
-  char* dctx = at(ws, L.dctx + r0 * L.hl * 2);
-  char* dqkv = gb.dqkv + r0 * 3 * L.hl * 2;
-  float* dot = reinterpret_cast<float*>(at(ws, L.dot)) + (size_t)i * (L.b / L.p) * L.nl * L.s;
-  float* red = B.red + (size_t)i * L.red_floats;
-  auto area = [&](int k) { return red + L.area_off[k]; };
-  const int beta = (i > 0 || B.accumulate) ? 1 : 0;
-  const bool chain = wg.prev && wg.prev != st;
-  const bool chain_w = wg.prev_w && wg.prev_w != wst;
-  const bool side = wst != st;
-  const bool merged = merged_wgrads(L);
-  for (hipEvent_t& e : wg.cur) e = nullptr;
+int record(hipEvent_t* ev, hipStream_t st) {
+  TRY(next_sync_event(ev));
+  HIP_TRY(hipEventRecord(*ev, st), "hipEventRecord");
+  return DOMINO_OK;
+}
+int wait(hipStream_t st, hipEvent_t ev) {
+  if (ev) HIP_TRY(hipStreamWaitEvent(st, ev, 0), "hipStreamWaitEvent");
+  return DOMINO_OK;
+}
 
-  // the point on the slice's stream after which an operand of a weight gradient exists (only needed when the weight
-  // gradients run on a stream of their own)
-  if (marks) marks->on = st;
-  auto produced = [&](hipEvent_t* ev) -> int {
-    *ev = nullptr;
-    if (!side) return DOMINO_OK;
-    TRY(next_sync_event(ev));
-    HIP_TRY(hipEventRecord(*ev, st), "hipEventRecord");
+// Backward of one block: each step of the chain of input gradients for one row group after the other, every group on
+// its own stream; each input gradient is enqueued before the weight gradient of the same product (Sec. 4.1.2).  With a
+// side stream the weight and vector gradients run there, each behind an event of every group; without one they follow
+// on the groups' streams: one group forms them where their operands are complete, several first meet on streams[0] and
+// part again (the same join and fork that end one call and begin the next) and take the matrices in turn.
+// In a stack: `own` receives this block's events, `above` are those of the block above, `two_above` of the block that
+// used the same set of gradient tensors (NULL outside a stack or where there is no such block); `turn` deals the matrices
+// to the streams differently from block to block.
+int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& S, void* ws, const GradBufs& gb, const BwdLayer& B,
+                      int parts, int turn = 0, BlockEvents* own = nullptr, const BlockEvents* above = nullptr,
+                      const BlockEvents* two_above = nullptr) {
+  const domino_params* P = B.P;
+  const void* saved = B.saved;
+  const bool rms = L.llama;
+  auto rowf = [&](size_t off, const Rows& R) { return reinterpret_cast<const float*>(at(saved, off)) + R.r0; };
+  auto d_pre = [&](const Rows& R) { return gb.d_pre + R.r0 * L.upc * 2; };
+  auto dx1 = [&](const Rows& R) { return gb.dx1 + R.rh; };
+  auto dqkv = [&](const Rows& R) { return gb.dqkv + R.r0 * 3 * L.hl * 2; };
+  auto dctx = [&](const Rows& R) { return at(ws, L.dctx + R.r0 * L.hl * 2); };
+  auto each_group = [&](auto step) -> int {
+    for (int g = 0; g < L.groups; ++g) TRY(step(rows_of(L, g), S.lane(g)));
     return DOMINO_OK;
   };
-  auto wgrad = [&](int which, int cls, hipEvent_t dep, const void* A, long lda, const void* Bm, long ldb, float* C, long ldc,
-                   int M, int N) -> int {
-    if (merged) return DOMINO_OK;      // formed over all slices at once, after the last slice
-    if (dep) HIP_TRY(hipStreamWaitEvent(wst, dep, 0), "hipStreamWaitEvent");
-    if (chain_w) HIP_TRY(hipStreamWaitEvent(wst, wg.done[which], 0), "hipStreamWaitEvent");
-    {
-      ProfScope ps(cls, wst);
-      GemmArgs a = gemm_args(A, lda, Bm, ldb, C, ldc, M, N, Ms);
-      a.beta = beta;
-      LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, wst), "weight gradient");
+  // an event on every stream that carries groups: `to` then waits for what the groups have enqueued so far
+  auto behind_groups = [&](hipStream_t to, std::vector<hipEvent_t>* keep = nullptr) -> int {
+    for (int k = 0; k < S.lanes; ++k) {
+      hipEvent_t ev;
+      TRY(record(&ev, as_stream(S.streams[k])));
+      if (keep) keep->push_back(ev);
+      if (to != as_stream(S.streams[k])) TRY(wait(to, ev));
     }
-    if (wg.feeds_next || (side && which == 0)) {       // (the second stream's reader of dy is waited for below)
-      TRY(next_sync_event(&wg.cur[which]));
-      HIP_TRY(hipEventRecord(wg.cur[which], wst), "hipEventRecord");
+    return DOMINO_OK;
+  };
+  auto form = [&](int which, hipStream_t st) -> int {
+    TRY(weight_gradient(L, gb, B, which, st));
+    if (own) {
+      own->on[which] = st;
+      TRY(record(&own->wgrad[which], st));
     }
     return DOMINO_OK;
   };
-  auto colsum = [&](const void* g, long ld, int n, int k) -> int {
-    ProfScope ps(PC_COLSUM, st);
-    LAUNCH(colsum_partial_launch(g, ld, Ms, n, area(k), st), "bias gradient");
-    return DOMINO_OK;
-  };
-  auto norm_bwd = [&](const void* ga, const void* gb, const void* xin, const void* gamma, const float* mean,
-                      const float* rstd, const void* dres, void* out, int kg, int kb, int kres = -1, int kdx = -1) -> int {
+  const bool in_place = !S.side && S.lanes == 1;
+  hipStream_t side = S.side ? S.side_stream() : nullptr;
+
+  // the set of gradient tensors that this block writes was read by the weight gradients of the block two above, enqueued
+  // a whole block ago: these waits order without stalling (on the side stream the last of them is behind the others)
+  if (two_above)
+    for (int k = 0; k < S.lanes; ++k)
+      for (int m = S.side ? WG_QKV : WG_UP; m < NWGRADS; ++m)
+        if (two_above->on[m] != as_stream(S.streams[k])) TRY(wait(as_stream(S.streams[k]), two_above->wgrad[m]));
+
+  auto norm_bwd = [&](const Rows& R, hipStream_t st, const void* ga, const void* gb2, const void* xin, const void* gamma, size_t mean,
+                      size_t rstd, const void* dres, void* out, int kg, int kb, int kres, int kdx) -> int {
     ProfScope ps(PC_NORM_BWD, st);
     NormBwdArgs a{};
-    a.ga = ga; a.gb = gb; a.x = xin; a.gamma = gamma; a.mean = mean; a.rstd = rstd; a.dres = dres; a.dx = out;
-    a.part_g = area(kg); a.part_b = area(kb); a.rows = Ms; a.h = L.h; a.rms = rms;
-    if (kres >= 0) { a.part_dres = area(kres); a.part_dx = area(kdx); }   // bias gradients of the two row-cut products
+    a.ga = ga; a.gb = gb2; a.x = xin; a.gamma = gamma; a.mean = rowf(mean, R); a.rstd = rowf(rstd, R); a.dres = dres; a.dx = out;
+    a.part_g = B.red + L.area(kg, R.slice); a.part_b = B.red + L.area(kb, R.slice); a.rows = R.n; a.h = L.h; a.rms = rms;
+    a.slice_rows = L.Ms;
+    if (kres >= 0) { a.part_dres = B.red + L.area(kres, R.slice); a.part_dx = B.red + L.area(kdx, R.slice); }   // bias gradients of the two row-cut products
     LAUNCH(norm_bwd_launch(a, st), "norm backward");
     return DOMINO_OK;
   };
 
-  hipEvent_t read_dy = nullptr;   // set once the down-projection's weight gradient, a reader of dy on the second stream, is enqueued
   if (parts & DOMINO_BWD_MLP) {
-  hipEvent_t have_dy;          // in a stack dy is what the block above has just written on this stream
-  TRY(produced(&have_dy));
-  {  // B1 + B3: input gradient of the down-projection (all q column slices inside the K loop), activation backward fused
-    ProfScope ps(PC_DGRAD_DOWN, st);
-    GemmArgs a = gemm_args(dyi, L.h, P->w_down, L.h, d_pre, L.upc, Ms, L.fl, L.h);
-    a.aux = const_cast<char*>(pre); a.ldaux = L.upc; a.gelu_tanh = cfg->gelu_tanh;
-    if (L.llama) { a.n_split = L.fl; LAUNCH(gemm_launch(GEMM_NT, EPI_DSWIGLU, a, -1, st), "mlp-down input gradient"); }
-    else LAUNCH(gemm_launch(GEMM_NT, EPI_DGELU, a, -1, st), "mlp-down input gradient");
-  }
-  TRY(wgrad(0, PC_WGRAD_DOWN, have_dy, act, L.fl, dyi, L.h, G->w_down, L.h, L.fl, L.h));        // B2
-  if (side) read_dy = wg.cur[0];
-  hipEvent_t have_dpre;
-  TRY(produced(&have_dpre));
-  if (marks && !(parts & DOMINO_BWD_ATTN)) {
-    TRY(next_sync_event(&marks->ready));
-    HIP_TRY(hipEventRecord(marks->ready, st), "hipEventRecord");
-  }
-  {  // B4: input gradient of MLP-up: the tensor the third all-reduce would sum
-    ProfScope ps(PC_DGRAD_UP, st);
-    GemmArgs a = gemm_args(d_pre, L.upc, P->w_up, L.upc, at(B.dln2_partial, rh), L.h, Ms, L.h, L.upc);
-    LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "mlp-up input gradient");
-  }
-  TRY(wgrad(1, PC_WGRAD_UP, have_dpre, ln2, L.h, d_pre, L.upc, G->w_up, L.upc, L.h, L.upc));
-  if (!L.llama) TRY(colsum(d_pre, L.upc, L.fl, AREA_BUP));
+    if (S.side) {        // operands: the forward's, and dy, which in a stack the block above has just written
+      if (above) for (hipEvent_t ev : above->dx) TRY(wait(side, ev));
+      TRY(form(WG_DOWN, side));                             // B2
+    }
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
+      // B1 + B3: input gradient of the down-projection (all q column slices inside the K loop), activation backward fused
+      ProfScope ps(PC_DGRAD_DOWN, st);
+      GemmArgs a = gemm_args(at(B.dy, R.rh), L.h, P->w_down, L.h, d_pre(R), L.upc, R.n, L.fl, L.h);
+      a.aux = const_cast<char*>(at(saved, L.pre + R.r0 * L.upc * 2)); a.ldaux = L.upc; a.gelu_tanh = cfg->gelu_tanh;
+      if (L.llama) { a.n_split = L.fl; LAUNCH(gemm_launch(GEMM_NT, EPI_DSWIGLU, a, -1, st), "mlp-down input gradient"); }
+      else LAUNCH(gemm_launch(GEMM_NT, EPI_DGELU, a, -1, st), "mlp-down input gradient");
+      return DOMINO_OK;
+    }));
+    if (S.side) {
+      TRY(behind_groups(side));
+      TRY(form(WG_UP, side));
+    } else if (in_place) {
+      TRY(form(WG_DOWN, S.lane(0)));
+    }
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
+      // B4: input gradient of MLP-up: the tensor the third all-reduce would sum
+      ProfScope ps(PC_DGRAD_UP, st);
+      GemmArgs a = gemm_args(d_pre(R), L.upc, P->w_up, L.upc, at(B.dln2_partial, R.rh), L.h, R.n, L.h, L.upc);
+      LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "mlp-up input gradient");
+      return DOMINO_OK;
+    }));
+    if (in_place) TRY(form(WG_UP, S.lane(0)));
   }
   if (parts & DOMINO_BWD_ATTN) {
-  // B5
-  TRY(norm_bwd(at(B.dln2_partial, rh), B.dln2_others ? at(B.dln2_others, rh) : nullptr, x1, P->norm2_g, mean2, rstd2,
-               dyi, dx1, AREA_G2, AREA_B2, L.llama ? -1 : AREA_BDOWN, L.llama ? -1 : AREA_BO));
-  hipEvent_t have_dx1;
-  TRY(produced(&have_dx1));
-  {  // B6
-    ProfScope ps(PC_DGRAD_OUT, st);
-    GemmArgs a = gemm_args(dx1, L.h, P->w_o, L.h, dctx, L.hl, Ms, L.hl, L.h);
-    LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "out-projection input gradient");
-  }
-  TRY(wgrad(2, PC_WGRAD_OUT, have_dx1, ctx, L.hl, dx1, L.h, G->w_o, L.h, L.hl, L.h));
-  {  // B7
-    ProfScope ps(PC_ATTN_BWD, st);
-    AttnArgs a{};
-    a.qkv = qkv; a.ld = 3 * L.hl; a.ctx = const_cast<char*>(ctx); a.ld_ctx = L.hl; a.dctx = dctx;
-    a.lse = const_cast<float*>(lse); a.dot = dot; a.dqkv = dqkv;
-    a.batch = L.b / L.p; a.seq = L.s; a.heads = L.nl; a.head_dim = L.d; a.scale = 1.0f / sqrtf((float)L.d);
-    a.rope = L.llama ? 1 : 0; a.rope_log2_base = log2f(cfg->rope_base);   // dq, dk are turned back where they are stored
-    LAUNCH(attention_bwd_launch(a, st), "attention backward");
-  }
-  hipEvent_t have_dqkv;
-  TRY(produced(&have_dqkv));
-  if (marks) {
-    TRY(next_sync_event(&marks->ready));
-    HIP_TRY(hipEventRecord(marks->ready, st), "hipEventRecord");
-  }
-  {  // B8: input gradient of QKV: the tensor the fourth all-reduce would sum
-    ProfScope ps(PC_DGRAD_QKV, st);
-    GemmArgs a = gemm_args(dqkv, 3 * L.hl, P->w_qkv, 3 * L.hl, at(B.dln1_partial, rh), L.h, Ms, L.h, 3 * L.hl);
-    LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "qkv input gradient");
-  }
-  TRY(wgrad(3, PC_WGRAD_QKV, have_dqkv, ln1, L.h, dqkv, 3 * L.hl, G->w_qkv, 3 * L.hl, L.h, 3 * L.hl));
-  if (!L.llama) TRY(colsum(dqkv, 3 * L.hl, 3 * L.hl, AREA_BQKV));
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B5
+      return norm_bwd(R, st, at(B.dln2_partial, R.rh), B.dln2_others ? at(B.dln2_others, R.rh) : nullptr, at(saved, L.x1 + R.rh),
+                      P->norm2_g, L.mean2, L.rstd2, at(B.dy, R.rh), dx1(R), AREA_G2, AREA_B2, L.llama ? -1 : AREA_BDOWN, L.llama ? -1 : AREA_BO);
+    }));
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B6
+      ProfScope ps(PC_DGRAD_OUT, st);
+      GemmArgs a = gemm_args(dx1(R), L.h, P->w_o, L.h, dctx(R), L.hl, R.n, L.hl, L.h);
+      LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "out-projection input gradient");
+      return DOMINO_OK;
+    }));
+    if (in_place) TRY(form(WG_OUT, S.lane(0)));
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B7
+      ProfScope ps(PC_ATTN_BWD, st);
+      AttnArgs a{};
+      a.qkv = at(saved, L.qkv + R.r0 * 3 * L.hl * 2); a.ld = 3 * L.hl;
+      a.ctx = const_cast<char*>(at(saved, L.ctx + R.r0 * L.hl * 2)); a.ld_ctx = L.hl; a.dctx = dctx(R);
+      a.lse = const_cast<float*>(reinterpret_cast<const float*>(at(saved, L.lse))) + R.r0 * L.nl;
+      a.dot = reinterpret_cast<float*>(at(ws, L.dot)) + R.r0 * L.nl; a.dqkv = dqkv(R);
+      a.batch = R.batch; a.seq = L.s; a.heads = L.nl; a.head_dim = L.d; a.scale = 1.0f / sqrtf((float)L.d);
+      a.rope = L.llama ? 1 : 0; a.rope_log2_base = log2f(cfg->rope_base);   // dq, dk are turned back where they are stored
+      LAUNCH(attention_bwd_launch(a, st), "attention backward");
+      return DOMINO_OK;
+    }));
+    if (S.side) {
+      TRY(behind_groups(side));
+      TRY(form(WG_OUT, side));
+      TRY(form(WG_QKV, side));
+    }
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
+      // B8: input gradient of QKV: the tensor the fourth all-reduce would sum
+      ProfScope ps(PC_DGRAD_QKV, st);
+      GemmArgs a = gemm_args(dqkv(R), 3 * L.hl, P->w_qkv, 3 * L.hl, at(B.dln1_partial, R.rh), L.h, R.n, L.h, 3 * L.hl);
+      LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "qkv input gradient");
+      return DOMINO_OK;
+    }));
+    if (in_place) TRY(form(WG_QKV, S.lane(0)));
   }
   if (parts & DOMINO_BWD_NORM1) {
-    // dx may be the tensor dy came in (a stack hands one tensor from block to block): its rows are overwritten only
-    // after the second stream's reader of dy is through (long since, in practice: it was the first thing enqueued there)
-    if (read_dy) HIP_TRY(hipStreamWaitEvent(st, read_dy, 0), "hipStreamWaitEvent");
-    // in a stack with merged weight gradients dx goes into the tensor that the block above took its dy from, and that
-    // block's down-projection weight gradient (on another stream, enqueued a whole block ago) reads all of it
-    if (before_dx) HIP_TRY(hipStreamWaitEvent(st, before_dx, 0), "hipStreamWaitEvent");
-    TRY(norm_bwd(at(B.dln1_partial, rh), B.dln1_others ? at(B.dln1_others, rh) : nullptr, xi, P->norm1_g, mean1, rstd1,
-                 dx1, at(B.dx, rh), AREA_G1, AREA_B1));
-    if (merged) {
-      // the vector gradients are summed over all slices in one launch at the end of the block (enqueue_block_end)
-      if (marks) {
-        TRY(next_sync_event(&marks->dx));
-        HIP_TRY(hipEventRecord(marks->dx, st), "hipEventRecord");
+    // in a stack dx goes into the tensor that the block above took its dy from, and that block's down-projection weight
+    // gradient, enqueued a whole block ago, reads all of it
+    if (above && above->wgrad[WG_DOWN])
+      for (int k = 0; k < S.lanes; ++k)
+        if (above->on[WG_DOWN] != as_stream(S.streams[k])) TRY(wait(as_stream(S.streams[k]), above->wgrad[WG_DOWN]));
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
+      return norm_bwd(R, st, at(B.dln1_partial, R.rh), B.dln1_others ? at(B.dln1_others, R.rh) : nullptr, at(B.x, R.rh), P->norm1_g,
+                      L.mean1, L.rstd1, dx1(R), at(B.dx, R.rh), AREA_G1, AREA_B1, -1, -1);
+    }));
+  }
+  if (S.side) {
+    if (parts & DOMINO_BWD_NORM1) {
+      TRY(behind_groups(side, own ? &own->dx : nullptr));
+      TRY(vector_gradients(L, B, side));
+    }
+  } else if (in_place) {
+    if (parts & DOMINO_BWD_NORM1) TRY(vector_gradients(L, B, S.lane(0)));
+  } else {
+    TRY(join_streams(S, S.lanes));
+    TRY(fork_streams(S, S.lanes));
+    int slot = turn;
+    const int order[NWGRADS] = {WG_DOWN, WG_UP, WG_QKV, WG_OUT};
+    for (int which : order)
+      if (parts & (which <= WG_UP ? DOMINO_BWD_MLP : DOMINO_BWD_ATTN)) TRY(form(which, as_stream(S.streams[slot++ % S.lanes])));
+    if (parts & DOMINO_BWD_NORM1) {
+      // behind the column sums, which come with the matrices, on whichever stream they ran
+      if (!L.llama && (parts & (DOMINO_BWD_MLP | DOMINO_BWD_ATTN))) {
+        TRY(join_streams(S, S.lanes));
+        TRY(fork_streams(S, S.lanes));
       }
-    } else {
-      // Vector gradients (norm gains and shifts, biases): the partial rows of all three parts of this slice lie in
-      // its block of the workspace now; one launch adds them to the gradients, after slice i-1's launch did
-      // (fixed order), so only the last slice's small sum is left at the end of the block.
-      if (chain) HIP_TRY(hipStreamWaitEvent(st, wg.done[4], 0), "hipStreamWaitEvent");
-      TRY(vector_grads(L, B, red, 1, beta, st));
-      if (wg.feeds_next) {
-        TRY(next_sync_event(&wg.cur[4]));
-        HIP_TRY(hipEventRecord(wg.cur[4], st), "hipEventRecord");
-      }
+      TRY(vector_gradients(L, B, as_stream(S.streams[slot % S.lanes])));
     }
-  }
-
-  // the slice's stream ends after the slice's weight gradients: whatever follows on it (the same slice of the block
-  // below in a stack, a later part, the join) may overwrite what they read
-  if (side) TRY(edge(wst, st));
-  wg.prev = st;
-  wg.prev_w = wst;
-  for (int k = 0; k < 5; ++k) wg.done[k] = wg.cur[k];
-  return DOMINO_OK;
-}
-
-// The end of a block whose weight gradients are merged (see merged_wgrads): the weight gradients of the matrices that
-// `parts` owns, each in one launch over all rows of the block, and (with the Norm1 part) one launch that sums the
-// vector gradients over all slices.  Enqueued after the slices of the block, the launches spread over the slices' streams starting at
-// streams[turn % nslice] (largest first; a stack turns the assignment from block to block so that no stream always
-// gets the big ones).  The sum over the rows runs inside the kernel in a fixed order, so results are run-to-run
-// identical.
-//   marks (one entry per slice, or NULL): with them a launch waits only for the events that the slices on other
-//   streams recorded behind the last kernel that writes an operand of a weight gradient (long past when a stream
-//   has finished its own slice, so the launches start without a stall and fill the time in which the slowest slice
-//   finishes);
-//   `above`: the marks of the block above in a stack, whose slices wrote this block's dy.  Without marks the
-//   streams meet on streams[0] and part again first, the same join and fork that end one call and begin the next:
-//   the form for a call under HIP graph capture (a graph captured with direct waits of every stream for every
-//   other one crashed the runtime when it was instantiated).
-//   done / done_on (4 entries, by matrix: down, up, qkv, out; or NULL): an event recorded after each launch and the
-//   stream it ran on.
-int enqueue_block_end(const Layout& L, const StreamPlan& S, const GradBufs& gb, const BwdLayer& B, int parts, int turn,
-                          const std::vector<SliceEvents>* marks, const std::vector<SliceEvents>* above = nullptr,
-                          hipEvent_t* done = nullptr, hipStream_t* done_on = nullptr) {
-  const char* sv = static_cast<const char*>(B.saved);
-  const domino_grads* G = B.G;
-  // second operand: dy (written by the block above, or the caller's) for the down-projection, else a tensor of this block's slices
-  struct { int part, cls; bool reads_dy; const void* A; long lda; const void* Bm; long ldb; float* C; long ldc; int M, N; } w[4] = {
-    {DOMINO_BWD_MLP, PC_WGRAD_DOWN, true, sv + L.act, L.fl, B.dy, L.h, G->w_down, L.h, L.fl, L.h},
-    {DOMINO_BWD_MLP, PC_WGRAD_UP, false, sv + L.ln2, L.h, gb.d_pre, L.upc, G->w_up, L.upc, L.h, L.upc},
-    {DOMINO_BWD_ATTN, PC_WGRAD_QKV, false, sv + L.ln1, L.h, gb.dqkv, 3 * L.hl, G->w_qkv, 3 * L.hl, L.h, 3 * L.hl},
-    {DOMINO_BWD_ATTN, PC_WGRAD_OUT, false, sv + L.ctx, L.hl, gb.dx1, L.h, G->w_o, L.h, L.hl, L.h}};
-  if (!marks && S.nslice > 1) {
-    const std::vector<char> slices = S.used(false);
-    TRY(join_streams(S, slices));
-    TRY(fork_streams(S, slices));
-  }
-  int slot = 0;
-  for (int m = 0; m < 4; ++m) {
-    if (!(parts & w[m].part)) continue;
-    hipStream_t st = S.slice((slot++ + turn) % S.nslice);
-    if (marks) {
-      const std::vector<SliceEvents>* from = w[m].reads_dy ? above : marks;     // dy of a single block is the caller's
-      if (from)
-        for (const SliceEvents& e : *from) {
-          hipEvent_t ev = w[m].reads_dy ? e.dx : e.ready;
-          if (ev && e.on != st) HIP_TRY(hipStreamWaitEvent(st, ev, 0), "hipStreamWaitEvent");
-        }
-    }
-    {
-      ProfScope ps(w[m].cls, st);
-      GemmArgs a = gemm_args(w[m].A, w[m].lda, w[m].Bm, w[m].ldb, w[m].C, w[m].ldc, w[m].M, w[m].N, L.M);
-      a.beta = B.accumulate ? 1 : 0;
-      LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
-    }
-    if (done) {
-      TRY(next_sync_event(&done[m]));
-      HIP_TRY(hipEventRecord(done[m], st), "hipEventRecord");
-      done_on[m] = st;
-    }
-  }
-  if (parts & DOMINO_BWD_NORM1) {
-    // the eight vector gradients from the partial rows of all slices, behind the smallest weight gradient: by the
-    // time that stream gets here the last slice's Norm1 backward, whose partial rows it needs, is through
-    hipStream_t st = S.slice((3 + turn) % S.nslice);
-    if (marks)
-      for (const SliceEvents& e : *marks)
-        if (e.dx && e.on != st) HIP_TRY(hipStreamWaitEvent(st, e.dx, 0), "hipStreamWaitEvent");
-    TRY(vector_grads(L, B, B.red, L.p, B.accumulate ? 1 : 0, st));
   }
   return DOMINO_OK;
 }
 
 // workspace of a stack: one block's workspace, the partial-sum areas of the other blocks, two gradient tensors
-// handed from block to block in turn (a block reads its dy from one and writes its dx into the other) and, when the
-// weight gradients are merged, a second set of the tensors they read, so that the block below can run on while
-// they are formed
+// handed from block to block in turn (a block reads its dy from one and writes its dx into the other) and a second set of
+// the tensors the weight gradients read, so that the block below can run on while they are formed
 struct StackLayout {
   size_t red_bytes, extra_red, dmid[2], d_pre2, dx1_2, dqkv2, total;
 };
 StackLayout stack_layout(const Layout& L, int nlayers) {
   StackLayout s{};
   const size_t Mz = (size_t)L.M;
-  s.red_bytes = align_up((size_t)L.p * L.red_floats * 4);
+  s.red_bytes = align_up(L.red_floats * 4);
   s.extra_red = L.ws_total;
   size_t o = s.extra_red + (size_t)(nlayers - 1) * s.red_bytes;
   auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
   s.dmid[0] = take(Mz * L.h * 2);
   s.dmid[1] = take(Mz * L.h * 2);
-  if (merged_wgrads(L) && nlayers > 1) {
+  if (nlayers > 1) {
     s.d_pre2 = take(Mz * L.upc * 2);
     s.dx1_2 = take(Mz * L.h * 2);
     s.dqkv2 = take(Mz * 3 * L.hl * 2);
@@ -896,13 +867,11 @@ int domino_layer_fwd_parts(const domino_cfg* cfg, const domino_params* P,
   if (workspace_bytes < L.ws_total) return fail(DOMINO_ERR_WORKSPACE_TOO_SMALL, "workspace holds %zu bytes, %zu needed", workspace_bytes, L.ws_total);
   std::lock_guard<std::mutex> lock(g_mutex);
   TRY(begin_call(streams, nstreams, L.p));
-  ConcurrencyScope conc(nstreams < L.p ? nstreams : L.p);
-
-  const StreamPlan S(streams, nstreams, L.p);
-  const std::vector<char> used = S.used();
-  TRY(fork_streams(S, used));
-  for (int i = 0; i < L.p; ++i) TRY(enqueue_fwd_slice(L, cfg, S, B, i, parts));
-  TRY(join_streams(S, used));
+  const StreamPlan S(streams, nstreams, L, false);
+  ConcurrencyScope conc(S.used());
+  TRY(fork_streams(S, S.used()));
+  TRY(enqueue_fwd_block(L, cfg, S, B, parts));
+  TRY(join_streams(S, S.used()));
   return DOMINO_OK;
 }
 
@@ -933,23 +902,13 @@ int domino_layer_bwd_parts(const domino_cfg* cfg, const domino_params* P, const 
   if (!workspace) return fail(DOMINO_ERR_NULL_POINTER, "workspace is NULL");
   if (workspace_bytes < L.ws_total) return fail(DOMINO_ERR_WORKSPACE_TOO_SMALL, "workspace holds %zu bytes, %zu needed", workspace_bytes, L.ws_total);
   std::lock_guard<std::mutex> lock(g_mutex);
-  TRY(begin_call(streams, nstreams, L.p, true));
-  ConcurrencyScope conc(StreamPlan(streams, nstreams, L.p).in_flight(true));
-
+  TRY(begin_call(streams, nstreams, L.p));
   B.red = reinterpret_cast<float*>(at(workspace, L.red));
-  const StreamPlan S(streams, nstreams, L.p);
-  const std::vector<char> used = S.used(true);
-  TRY(fork_streams(S, used));
-  WgChain wg;
-  const GradBufs gb = grad_bufs(L, workspace);
-  const bool merged = merged_wgrads(L);
-  std::vector<SliceEvents> marks(merged && !g_capturing && S.nslice > 1 ? L.p : 0);     // (one stream orders itself)
-  for (int i = 0; i < L.p; ++i) {
-    wg.next_is(S, i, L.p);
-    TRY(enqueue_bwd_slice(L, cfg, workspace, gb, S.slice(i), S.second(i), B, i, wg, parts, nullptr, marks.empty() ? nullptr : &marks[i]));
-  }
-  if (merged) TRY(enqueue_block_end(L, S, gb, B, parts, 0, marks.empty() ? nullptr : &marks));
-  TRY(join_streams(S, used));
+  const StreamPlan S(streams, nstreams, L, true);
+  ConcurrencyScope conc(S.used());
+  TRY(fork_streams(S, S.used()));
+  TRY(enqueue_bwd_block(L, cfg, S, workspace, grad_bufs(L, workspace), B, parts));
+  TRY(join_streams(S, S.used()));
   return DOMINO_OK;
 }
 
@@ -981,17 +940,14 @@ int domino_stack_fwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   if (workspace_bytes < need) return fail(DOMINO_ERR_WORKSPACE_TOO_SMALL, "workspace holds %zu bytes, %zu needed", workspace_bytes, need);
   std::lock_guard<std::mutex> lock(g_mutex);
   TRY(begin_call(streams, nstreams, L.p));
-  ConcurrencyScope conc(nstreams < L.p ? nstreams : L.p);
-
-  // a row slice of block l+1 needs only the same row slice of block l (Sec. 3.2): the slices run through the
+  // a row slice of block l+1 needs only the same row slice of block l (Sec. 3.2): the groups run through the
   // whole stack on their own streams and meet only at the end
-  const StreamPlan S(streams, nstreams, L.p);
-  const std::vector<char> used = S.used();
-  TRY(fork_streams(S, used));
+  const StreamPlan S(streams, nstreams, L, false);
+  ConcurrencyScope conc(S.used());
+  TRY(fork_streams(S, S.used()));
   for (int l = 0; l < nlayers; ++l)
-    for (int i = 0; i < L.p; ++i)
-      TRY(enqueue_fwd_slice(L, cfg, S, layers[l], i, DOMINO_FWD_ALL, l > 0, l + 1 < nlayers ? &layers[l + 1] : nullptr));
-  TRY(join_streams(S, used));
+    TRY(enqueue_fwd_block(L, cfg, S, layers[l], DOMINO_FWD_ALL, l > 0, l + 1 < nlayers ? &layers[l + 1] : nullptr));
+  TRY(join_streams(S, S.used()));
   return DOMINO_OK;
 }
 
@@ -1018,9 +974,7 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   }
   TRY(check_streams(streams, nstreams));
   std::lock_guard<std::mutex> lock(g_mutex);
-  TRY(begin_call(streams, nstreams, L.p, true));
-  ConcurrencyScope conc(StreamPlan(streams, nstreams, L.p).in_flight(true));
-
+  TRY(begin_call(streams, nstreams, L.p));
   const bool merged = merged_wgrads(L);
   // A graph captured from this call with merged weight gradients and more than one block crashed the runtime when
   // it was instantiated (the single-block call, whose capture is a chain of plain forks and joins, replays fine):
@@ -1028,39 +982,21 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   if (g_capturing && merged && nlayers > 1)
     return fail(DOMINO_ERR_UNSUPPORTED, "streams[0] is being captured into a HIP graph: the backward of a stack of %d blocks with "
                 "p = %d > 2 row slices cannot be captured; capture one domino_layer_bwd call per block instead", nlayers, L.p);
-  const StreamPlan S(streams, nstreams, L.p);
-  const std::vector<char> used = S.used(true);
-  TRY(fork_streams(S, used));
+  const StreamPlan S(streams, nstreams, L, true);
+  ConcurrencyScope conc(S.used());
+  TRY(fork_streams(S, S.used()));
   GradBufs gb[2] = {grad_bufs(L, workspace), grad_bufs(L, workspace)};
-  if (merged && nlayers > 1) gb[1] = GradBufs{at(workspace, SL.d_pre2), at(workspace, SL.dx1_2), at(workspace, SL.dqkv2)};
-  // merged weight gradients of the last block that used each set of gradient tensors: by matrix (down, up, qkv, out)
-  hipEvent_t wdone[2][4] = {};
-  hipStream_t won[2][4] = {};
-  std::vector<SliceEvents> marks[2];       // of the current block and of the block above
-  for (int l = nlayers - 1; l >= 0; --l) {
-    const int turn = (nlayers - 1 - l) & 1;
-    if (merged) {
-      // this block overwrites the set of tensors that the merged weight gradients of the block two above read: they
-      // were enqueued a whole block ago, so these waits order without stalling
-      for (int k = 0; k < S.nslice; ++k)
-        for (int m = 1; m < 4; ++m)
-          if (wdone[turn][m] && won[turn][m] != S.slice(k)) HIP_TRY(hipStreamWaitEvent(S.slice(k), wdone[turn][m], 0), "hipStreamWaitEvent");
-    }
-    WgChain wg;
-    // dx of this block goes where the block above read its dy: its down-projection weight gradient must be through
-    hipEvent_t before_dx = merged ? wdone[turn ^ 1][0] : nullptr;
-    std::vector<SliceEvents>& mk = marks[turn];
-    mk.assign(merged && !g_capturing && S.nslice > 1 ? L.p : 0, SliceEvents{});
-    for (int i = 0; i < L.p; ++i) {
-      wg.next_is(S, i, L.p);
-      TRY(enqueue_bwd_slice(L, cfg, workspace, gb[turn], S.slice(i), S.second(i), layers[l], i, wg, DOMINO_BWD_ALL, before_dx,
-                            mk.empty() ? nullptr : &mk[i]));
-    }
-    if (merged)
-      TRY(enqueue_block_end(L, S, gb[turn], layers[l], DOMINO_BWD_ALL, nlayers - 1 - l, mk.empty() ? nullptr : &mk,
-                                l + 1 < nlayers && !marks[turn ^ 1].empty() ? &marks[turn ^ 1] : nullptr, wdone[turn], won[turn]));
+  if (nlayers > 1) gb[1] = GradBufs{at(workspace, SL.d_pre2), at(workspace, SL.dx1_2), at(workspace, SL.dqkv2)};
+  // by set of gradient tensors: what the last block that used it left for the others to wait for
+  BlockEvents ev[2];
+  const bool several = S.used() > 1;       // one stream orders itself
+  for (int l = nlayers - 1, k = 0; l >= 0; --l, ++k) {
+    BlockEvents own;
+    TRY(enqueue_bwd_block(L, cfg, S, workspace, gb[k & 1], layers[l], DOMINO_BWD_ALL, k, several ? &own : nullptr,
+                          several && k > 0 ? &ev[(k & 1) ^ 1] : nullptr, several && k > 1 ? &ev[k & 1] : nullptr));
+    ev[k & 1] = own;
   }
-  TRY(join_streams(S, used));
+  TRY(join_streams(S, S.used()));
   return DOMINO_OK;
 }
 

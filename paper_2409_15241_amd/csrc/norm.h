@@ -30,11 +30,13 @@ struct NormBwdArgs {
   const float* rstd;      // fp32 [rows]
   const void* dres;       // bf16 [rows, h] or null: gradient arriving over the residual branch
   void* dx;               // bf16 [rows, h] = dres + NormBwd(ga + gb)
-  float* part_g;          // fp32 [norm_bwd_blocks(rows), h]
-  float* part_b;          // fp32 [norm_bwd_blocks(rows), h] (LayerNorm only)
-  float* part_dres;       // fp32 [norm_bwd_blocks(rows), h] or null: partial column sums of dres (a bias gradient)
-  float* part_dx;         // fp32 [norm_bwd_blocks(rows), h] or null: partial column sums of dx (a bias gradient)
+  // partial column sums: [norm_bwd_blocks(slice_rows), h] for each slice of slice_rows rows, one slice after the other
+  float* part_g;          // fp32
+  float* part_b;          // fp32 (LayerNorm only)
+  float* part_dres;       // fp32 or null: of dres (a bias gradient)
+  float* part_dx;         // fp32 or null: of dx (a bias gradient)
   int rows, h, rms;
+  int slice_rows;         // divides rows; 0: one slice of all rows
 };
 
 int norm_bwd_blocks(int rows);

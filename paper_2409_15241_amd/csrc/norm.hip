@@ -148,7 +148,7 @@ void norm_fwd_kernel(const NormFwdArgs p) {
 // iteration, added in wave order (fixed summation order).
 template <int NT, int R, bool RMS, bool SUMS>
 __global__ __launch_bounds__(NT)
-void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block) {
+void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block, int blocks_per_slice) {
   constexpr int NW = NT / 64;
   constexpr int RW = 2 * R < 4 ? 4 : 2 * R;     // row sums per wave and iteration, padded to whole 16-byte reads
   __shared__ __align__(16) float red[2][NW][RW];
@@ -165,7 +165,10 @@ void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) { dg[e] = 0.0f; db[e] = 0.0f; sres[e] = 0.0f; sdx[e] = 0.0f; }
 
-  const int r0 = blockIdx.x * rows_per_block, r1 = min(p.rows, r0 + rows_per_block);
+  // the rows of a workgroup lie in one slice, so the partial sums do not depend on how many slices a launch covers
+  const int slice = blockIdx.x / blocks_per_slice, block = blockIdx.x % blocks_per_slice;
+  const int s0 = slice * p.slice_rows, r0 = s0 + block * rows_per_block, r1 = min(s0 + p.slice_rows, r0 + rows_per_block);
+  const long part_at = (long)blockIdx.x * p.h + tid * 8;
   // the rows of iteration k+1 are requested before iteration k is worked on, so the memory pipeline stays
   // busy across the barrier and the arithmetic of an iteration
   struct Rows { u32x4 xs[R], gs[R], bs[R], ds[R]; float mean[R], rstd[R]; };
@@ -247,19 +250,19 @@ void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block) {
     cur = nxt;
   }
   if (live) {
-    f32x4* pg = reinterpret_cast<f32x4*>(p.part_g + (long)blockIdx.x * p.h + tid * 8);
+    f32x4* pg = reinterpret_cast<f32x4*>(p.part_g + part_at);
     pg[0] = f32x4{dg[0], dg[1], dg[2], dg[3]};
     pg[1] = f32x4{dg[4], dg[5], dg[6], dg[7]};
     if (!RMS) {
-      f32x4* pb = reinterpret_cast<f32x4*>(p.part_b + (long)blockIdx.x * p.h + tid * 8);
+      f32x4* pb = reinterpret_cast<f32x4*>(p.part_b + part_at);
       pb[0] = f32x4{db[0], db[1], db[2], db[3]};
       pb[1] = f32x4{db[4], db[5], db[6], db[7]};
     }
     if (SUMS) {
-      f32x4* pr = reinterpret_cast<f32x4*>(p.part_dres + (long)blockIdx.x * p.h + tid * 8);
+      f32x4* pr = reinterpret_cast<f32x4*>(p.part_dres + part_at);
       pr[0] = f32x4{sres[0], sres[1], sres[2], sres[3]};
       pr[1] = f32x4{sres[4], sres[5], sres[6], sres[7]};
-      f32x4* px = reinterpret_cast<f32x4*>(p.part_dx + (long)blockIdx.x * p.h + tid * 8);
+      f32x4* px = reinterpret_cast<f32x4*>(p.part_dx + part_at);
       px[0] = f32x4{sdx[0], sdx[1], sdx[2], sdx[3]};
       px[1] = f32x4{sdx[4], sdx[5], sdx[6], sdx[7]};
     }
@@ -327,16 +330,16 @@ hipError_t fwd_dispatch(const NormFwdArgs& a, hipStream_t st) {
 }
 
 template <bool RMS, bool SUMS>
-hipError_t bwd_dispatch(const NormBwdArgs& a, int nblocks, hipStream_t st) {
+hipError_t bwd_dispatch(const NormBwdArgs& a, hipStream_t st) {
   const int nt = (((a.h >> 3) + 63) / 64) * 64;           // one thread per 16-byte chunk of a row
-  const int rpb = (a.rows + nblocks - 1) / nblocks;
-  const dim3 grid(nblocks), block(nt);
+  const int nb = norm_bwd_blocks(a.slice_rows), rpb = (a.slice_rows + nb - 1) / nb;
+  const dim3 grid(nb * (a.rows / a.slice_rows)), block(nt);
   // rows per iteration: two iterations' loads are held at once, within the registers the block size leaves
   constexpr int RS = SUMS ? 2 : 4;
-  if (nt <= 256) hipLaunchKernelGGL((norm_bwd_kernel<256, RS, RMS, SUMS>), grid, block, 0, st, a, rpb);
-  else if (nt <= 512) hipLaunchKernelGGL((norm_bwd_kernel<512, RS, RMS, SUMS>), grid, block, 0, st, a, rpb);
-  else if (nt <= 768) hipLaunchKernelGGL((norm_bwd_kernel<768, 2, RMS, SUMS>), grid, block, 0, st, a, rpb);
-  else hipLaunchKernelGGL((norm_bwd_kernel<1024, 1, RMS, SUMS>), grid, block, 0, st, a, rpb);
+  if (nt <= 256) hipLaunchKernelGGL((norm_bwd_kernel<256, RS, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
+  else if (nt <= 512) hipLaunchKernelGGL((norm_bwd_kernel<512, RS, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
+  else if (nt <= 768) hipLaunchKernelGGL((norm_bwd_kernel<768, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
+  else hipLaunchKernelGGL((norm_bwd_kernel<1024, 1, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
   return hipGetLastError();
 }
 
@@ -351,11 +354,13 @@ hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st) {
   return a.rms ? fwd_dispatch<true>(a, st) : fwd_dispatch<false>(a, st);
 }
 
-hipError_t norm_bwd_launch(const NormBwdArgs& a, hipStream_t st) {
-  const int nb = norm_bwd_blocks(a.rows);
+hipError_t norm_bwd_launch(const NormBwdArgs& a0, hipStream_t st) {
+  NormBwdArgs a = a0;
+  if (a.slice_rows <= 0) a.slice_rows = a.rows;
+  if (a.rows % a.slice_rows) return hipErrorInvalidValue;
   const bool sums = a.part_dres && a.part_dx && a.dres;
-  if (a.rms) return sums ? bwd_dispatch<true, true>(a, nb, st) : bwd_dispatch<true, false>(a, nb, st);
-  return sums ? bwd_dispatch<false, true>(a, nb, st) : bwd_dispatch<false, false>(a, nb, st);
+  if (a.rms) return sums ? bwd_dispatch<true, true>(a, st) : bwd_dispatch<true, false>(a, st);
+  return sums ? bwd_dispatch<false, true>(a, st) : bwd_dispatch<false, false>(a, st);
 }
 
 hipError_t colsum_finish_launch(const float* part, int nparts, int n, float* out, int accumulate, hipStream_t st) {
