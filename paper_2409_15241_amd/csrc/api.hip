@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <vector>
@@ -74,6 +75,8 @@ struct Layout {
   int h, n, t, r, p, q, b, s, f, d, nl, hl, fl, upc, M, Ms, hq;
   bool llama;
   bool merged;       // weight and vector gradients of a block in one launch each over all slices (see merged_wgrads)
+  bool per_slice;    // cfg->wgrad_per_slice
+  bool beside;       // the backward's weight gradients run on a stream of their own (see side_pays)
   int groups;        // row groups: consecutive slices whose launches are one launch each (see row_groups)
   // saved block (bytes)
   size_t ln1, qkv, ctx, lse, x1, ln2, pre, act, mean1, rstd1, mean2, rstd2, saved_total;
@@ -100,6 +103,14 @@ enum { AREA_G1 = 0, AREA_B1, AREA_G2, AREA_B2, AREA_BQKV, AREA_BO, AREA_BUP, ARE
 // The rule looks at the slicing alone, so neither the arithmetic nor a bit of any result depends on the stream pool.
 int row_groups(int p) { return p > 2 ? 2 : 1; }
 
+// A second stream costs a call about 100 us of host time (event records and waits) and 5 to 10 us at each of its edges
+// on the GPU, whatever the size of the block: below this many multiplications and additions of a block's four weight
+// gradients, they follow on the one stream, grouped into one launch.
+constexpr double SIDE_MIN_FLOPS = 40e9;
+bool side_pays(const Layout& l) {
+  return 2.0 * l.M * l.h * (4.0 * l.hl + l.upc + l.fl) >= SIDE_MIN_FLOPS;
+}
+
 int validate(const domino_cfg* c, Layout* L) {
   if (!c) return fail(DOMINO_ERR_NULL_POINTER, "cfg is NULL");
   if (c->hidden <= 0 || c->heads <= 0 || c->tp <= 0 || c->p <= 0 || c->q <= 0 || c->batch <= 0 ||
@@ -121,6 +132,7 @@ int validate(const domino_cfg* c, Layout* L) {
   l.llama = c->arch == DOMINO_ARCH_LLAMA;
   if (c->wgrad_per_slice != 0 && c->wgrad_per_slice != 1) return fail(DOMINO_ERR_INVALID_ARG, "wgrad_per_slice must be 0 or 1");
   l.merged = c->p > 2 && !c->wgrad_per_slice;
+  l.per_slice = c->wgrad_per_slice;
   l.groups = row_groups(c->p);
   l.d = l.h / l.n; l.nl = l.n / l.t; l.hl = l.nl * l.d; l.fl = l.f / l.t;
   l.upc = l.fl * (l.llama ? 2 : 1);
@@ -137,6 +149,7 @@ int validate(const domino_cfg* c, Layout* L) {
   if ((long)l.h * widest * 4 >= TWO_GIB) return fail(DOMINO_ERR_UNSUPPORTED, "a weight-gradient tensor would reach 2 GiB");
   l.M = (int)M;
   l.Ms = l.M / l.p;
+  l.beside = side_pays(l);
 
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
@@ -349,7 +362,7 @@ struct StreamPlan {
   int ns, lanes;
   bool side;
   StreamPlan(void* const* s, int n, const Layout& L, bool backward)
-      : streams(s), ns(n), lanes(L.groups < n ? L.groups : n), side(backward && !g_capturing && n > lanes) {}
+      : streams(s), ns(n), lanes(L.groups < n ? L.groups : n), side(backward && L.beside && !g_capturing && n > lanes) {}
   hipStream_t lane(int g) const { return as_stream(streams[g % lanes]); }
   hipStream_t side_stream() const { return as_stream(streams[lanes]); }
   int used() const { return lanes + (side ? 1 : 0); }
@@ -538,9 +551,9 @@ inline bool merged_wgrads(const Layout& L) { return L.merged; }
 
 enum { WG_DOWN = 0, WG_UP, WG_OUT, WG_QKV, NWGRADS };
 
-// the weight gradient of one matrix (and the column sums behind the bias of the same product), on `st`: one launch over
-// all rows or one per slice, in slice order
-int weight_gradient(const Layout& L, const GradBufs& gb, const BwdLayer& B, int which, hipStream_t st) {
+// the weight gradients of the n matrices in `which` (and before them the column sums behind the biases of the same
+// products), on `st`: one launch for all of them; with cfg->wgrad_per_slice one per matrix and slice, in slice order
+int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, const int* which, int n, hipStream_t st) {
   const char* sv = static_cast<const char*>(B.saved);
   const domino_grads* G = B.G;
   struct { int cls; const void* A; long lda; const void* Bm; long ldb; float* C; int M, N; int bias; } const tab[NWGRADS] = {
@@ -548,21 +561,27 @@ int weight_gradient(const Layout& L, const GradBufs& gb, const BwdLayer& B, int 
     {PC_WGRAD_UP, sv + L.ln2, L.h, gb.d_pre, L.upc, G->w_up, L.h, L.upc, AREA_BUP},
     {PC_WGRAD_OUT, sv + L.ctx, L.hl, gb.dx1, L.h, G->w_o, L.hl, L.h, -1},
     {PC_WGRAD_QKV, sv + L.ln1, L.h, gb.dqkv, 3 * L.hl, G->w_qkv, L.h, 3 * L.hl, AREA_BQKV}};
-  const auto& w = tab[which];
-  const int launches = merged_wgrads(L) ? 1 : L.p, K = L.M / launches;
-  for (int i = 0; i < launches; ++i) {
-    ProfScope ps(w.cls, st);
-    const size_t r0 = (size_t)i * K;
-    GemmArgs a = gemm_args(at(w.A, r0 * w.lda * 2), w.lda, at(w.Bm, r0 * w.ldb * 2), w.ldb, w.C, w.N, w.M, w.N, K);
-    a.beta = (i > 0 || B.accumulate) ? 1 : 0;
-    LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
+  for (int m = 0; m < n; ++m) {
+    const auto& w = tab[which[m]];
+    if (!L.llama && w.bias >= 0)
+      for (int g = 0; g < L.groups; ++g) {
+        const Rows R = rows_of(L, g);
+        ProfScope ps(PC_COLSUM, st);
+        LAUNCH(colsum_partial_launch(at(w.Bm, R.r0 * w.ldb * 2), w.ldb, R.n, w.N, B.red + L.area(w.bias, g), st), "bias gradient");
+      }
   }
-  if (!L.llama && w.bias >= 0)
-    for (int g = 0; g < L.groups; ++g) {
-      const Rows R = rows_of(L, g);
-      ProfScope ps(PC_COLSUM, st);
-      LAUNCH(colsum_partial_launch(at(w.Bm, R.r0 * w.ldb * 2), w.ldb, R.n, w.N, B.red + L.area(w.bias, g), st), "bias gradient");
+  const int slices = merged_wgrads(L) ? 1 : L.p, K = L.M / slices;
+  for (int m = 0; m < n; ++m) {
+    const auto& w = tab[which[m]];
+    for (int i = 0; i < slices; ++i) {
+      ProfScope ps(w.cls, st);
+      const size_t r0 = (size_t)i * K;
+      GemmArgs a = gemm_args(at(w.A, r0 * w.lda * 2), w.lda, at(w.Bm, r0 * w.ldb * 2), w.ldb, w.C, w.N, w.M, w.N, K);
+      a.beta = (i > 0 || B.accumulate) ? 1 : 0;
+      a.join = !L.per_slice && (m < n - 1 || i < slices - 1) ? 1 : 0;
+      LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
     }
+  }
   return DOMINO_OK;
 }
 
@@ -644,11 +663,12 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }
     return DOMINO_OK;
   };
-  auto form = [&](int which, hipStream_t st) -> int {
-    TRY(weight_gradient(L, gb, B, which, st));
+  auto form = [&](std::initializer_list<int> which, hipStream_t st) -> int {
+    TRY(weight_gradients(L, gb, B, which.begin(), (int)which.size(), st));
     if (own) {
-      own->on[which] = st;
-      TRY(record(&own->wgrad[which], st));
+      hipEvent_t ev;
+      TRY(record(&ev, st));
+      for (int m : which) { own->on[m] = st; own->wgrad[m] = ev; }
     }
     return DOMINO_OK;
   };
@@ -677,7 +697,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
   if (parts & DOMINO_BWD_MLP) {
     if (S.side) {        // operands: the forward's, and dy, which in a stack the block above has just written
       if (above) for (hipEvent_t ev : above->dx) TRY(wait(side, ev));
-      TRY(form(WG_DOWN, side));                             // B2
+      TRY(form({WG_DOWN}, side));                           // B2
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
       // B1 + B3: input gradient of the down-projection (all q column slices inside the K loop), activation backward fused
@@ -690,9 +710,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }));
     if (S.side) {
       TRY(behind_groups(side));
-      TRY(form(WG_UP, side));
-    } else if (in_place) {
-      TRY(form(WG_DOWN, S.lane(0)));
+      TRY(form({WG_UP}, side));
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
       // B4: input gradient of MLP-up: the tensor the third all-reduce would sum
@@ -701,20 +719,23 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "mlp-up input gradient");
       return DOMINO_OK;
     }));
-    if (in_place) TRY(form(WG_UP, S.lane(0)));
+    if (in_place && !(parts & DOMINO_BWD_ATTN)) TRY(form({WG_DOWN, WG_UP}, S.lane(0)));
   }
   if (parts & DOMINO_BWD_ATTN) {
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B5
       return norm_bwd(R, st, at(B.dln2_partial, R.rh), B.dln2_others ? at(B.dln2_others, R.rh) : nullptr, at(saved, L.x1 + R.rh),
                       P->norm2_g, L.mean2, L.rstd2, at(B.dy, R.rh), dx1(R), AREA_G2, AREA_B2, L.llama ? -1 : AREA_BDOWN, L.llama ? -1 : AREA_BO);
     }));
+    if (S.side) {        // beside the attention backward, which leaves the matrix cores idle most of the time
+      TRY(behind_groups(side));
+      TRY(form({WG_OUT}, side));
+    }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B6
       ProfScope ps(PC_DGRAD_OUT, st);
       GemmArgs a = gemm_args(dx1(R), L.h, P->w_o, L.h, dctx(R), L.hl, R.n, L.hl, L.h);
       LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "out-projection input gradient");
       return DOMINO_OK;
     }));
-    if (in_place) TRY(form(WG_OUT, S.lane(0)));
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B7
       ProfScope ps(PC_ATTN_BWD, st);
       AttnArgs a{};
@@ -729,8 +750,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }));
     if (S.side) {
       TRY(behind_groups(side));
-      TRY(form(WG_OUT, side));
-      TRY(form(WG_QKV, side));
+      TRY(form({WG_QKV}, side));
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
       // B8: input gradient of QKV: the tensor the fourth all-reduce would sum
@@ -739,7 +759,10 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       LAUNCH(gemm_launch(GEMM_NT, EPI_STORE, a, -1, st), "qkv input gradient");
       return DOMINO_OK;
     }));
-    if (in_place) TRY(form(WG_QKV, S.lane(0)));
+    if (in_place) {      // all of the call's weight gradients in one launch
+      if (parts & DOMINO_BWD_MLP) TRY(form({WG_DOWN, WG_UP, WG_OUT, WG_QKV}, S.lane(0)));
+      else TRY(form({WG_OUT, WG_QKV}, S.lane(0)));
+    }
   }
   if (parts & DOMINO_BWD_NORM1) {
     // in a stack dx goes into the tensor that the block above took its dy from, and that block's down-projection weight
@@ -765,7 +788,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     int slot = turn;
     const int order[NWGRADS] = {WG_DOWN, WG_UP, WG_QKV, WG_OUT};
     for (int which : order)
-      if (parts & (which <= WG_UP ? DOMINO_BWD_MLP : DOMINO_BWD_ATTN)) TRY(form(which, as_stream(S.streams[slot++ % S.lanes])));
+      if (parts & (which <= WG_UP ? DOMINO_BWD_MLP : DOMINO_BWD_ATTN)) TRY(form({which}, as_stream(S.streams[slot++ % S.lanes])));
     if (parts & DOMINO_BWD_NORM1) {
       // behind the column sums, which come with the matrices, on whichever stream they ran
       if (!L.llama && (parts & (DOMINO_BWD_MLP | DOMINO_BWD_ATTN))) {

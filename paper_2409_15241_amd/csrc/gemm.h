@@ -27,11 +27,16 @@ struct GemmArgs {
   float rope_log2_base;
   int gelu_tanh;
   int concurrency;       // launches of similar size expected in flight at once (other streams); 0 = 1
+  int join;              // EPI_ACC_F32: 1 = hold this product back, it is launched together with the next call's (see gemm_launch)
   int tiles_m, tiles_n;  // filled by the launcher
-  int group_m;           // filled by the launcher: tile rows per band of the XCD-blocked order, 0 = linear
+  int group_m;           // filled by the launcher: tile rows per band of the tile order
   long a_bytes, b_bytes; // extent of the A / B views in bytes, filled by the launcher
 };
 
 int gemm_pick_tile(int M, int N, int concurrency);
 // tile_cfg < 0: pick by shape.  Enqueues on `stream`; returns the launch status.
+// Products with `join` set are held back (per thread) until the next call without it, which must follow on the same
+// stream: at most GEMM_GROUP weight gradients then go out as one launch.  A product into the matrix of the one before it,
+// over the rows that follow it (the next slice of the batch), continues that product's contraction.
+constexpr int GEMM_GROUP = 4;
 hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int tile_cfg, hipStream_t stream);

@@ -84,9 +84,11 @@ DEV void static_for(F&& f) {
   }
 }
 
+// The products of one launch: one, or several weight gradients with tiles first[i] .. first[i + 1] - 1 of the launch each.
+struct GemmGroup { GemmArgs g[GEMM_GROUP]; int first[GEMM_GROUP + 1]; };
+
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, BM * BN > 128 * 128 ? 1 : 2)
-void gemm_kernel(const GemmArgs p) {
+DEV void gemm_body(const GemmArgs& p, const int lin) {
   constexpr int NW = (BM / WM) * (BN / WN);
   constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
@@ -97,22 +99,10 @@ void gemm_kernel(const GemmArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave % (BM / WM)) * WM, wn0 = (wave / (BM / WM)) * WN;
 
-  // Consecutive workgroup ids land on different XCDs (each with its own L2): with m fastest, the
-  // tiles of one XCD share few A panels and walk the B panels in step.
-  int tm, tn;
-  if (p.group_m == 0) {
-    const int tile = blockIdx.x;
-    tm = tile % p.tiles_m; tn = tile / p.tiles_m;
-  } else {
-    // workgroup ids go round-robin over the 8 XCDs: give each XCD one contiguous chunk of a tile order
-    // that walks bands of group_m tile rows, so the tiles sharing an L2 share operand panels
-    const int T = p.tiles_m * p.tiles_n, chunk = (T + 7) >> 3;
-    const int lin = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
-    if (lin >= T) return;
-    const int band = lin / (p.group_m * p.tiles_n), r = lin % (p.group_m * p.tiles_n);
-    const int gm = min(p.group_m, p.tiles_m - band * p.group_m);
-    tm = band * p.group_m + r % gm; tn = r / gm;
-  }
+  // bands of group_m tile rows, walked column by column
+  const int band = lin / (p.group_m * p.tiles_n), inband = lin % (p.group_m * p.tiles_n);
+  const int gm = min(p.group_m, p.tiles_m - band * p.group_m);
+  const int tm = band * p.group_m + inband % gm, tn = inband / gm;
   const int m0 = tm * BM, n0 = tn * BN;
 
   // SwiGLU forward: the tile's even 32-column groups are gate columns, the odd ones the matching
@@ -453,39 +443,98 @@ void gemm_kernel(const GemmArgs p) {
   });
 }
 
+// Workgroup ids go round-robin over the 8 XCDs (each with its own L2): every XCD gets one contiguous chunk of the tile
+// order, so that the tiles sharing an L2 share operand panels.  Launches of a few tiles keep the plain order, which
+// spreads them over all XCDs.
+DEV int tile_of_block(int T) {
+  if (T < 16) return blockIdx.x;
+  return (blockIdx.x & 7) * ((T + 7) >> 3) + (blockIdx.x >> 3);
+}
+
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-hipError_t launch_cfg(const GemmArgs& a0, hipStream_t stream) {
-  GemmArgs a = a0;
-  constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  constexpr int LDS = (RING_A * BM + RING_B * BN) * BK * 2;
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, BM * BN > 128 * 128 ? 1 : 2)
+void gemm_kernel(const GemmArgs p) {
+  const int T = p.tiles_m * p.tiles_n, lin = tile_of_block(T);
+  if (lin < T) gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p, lin);
+}
+
+// Several weight gradients of one block in one launch: alone, each leaves part of the chip idle (the 13B shard's are 200,
+// 200, 60 and 160 tiles of 256x256 on 256 compute units), and a small block pays mostly for the launches.
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, BM * BN > 128 * 128 ? 1 : 2)
+void gemm_group_kernel(const GemmGroup p) {
+  const int T = p.first[GEMM_GROUP], lin = tile_of_block(T);
+  if (lin >= T) return;
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < GEMM_GROUP; ++k)
+    if (lin >= p.first[k]) i = k;
+  gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p.g[i], lin - p.first[i]);
+}
+
+// fills what the kernel needs to know about the tiles; false: an operand reaches 2 GiB
+template <int BM, int BN, bool AKS, bool BKS, int EPI>
+bool plan_tiles(GemmArgs& a) {
   const int n_logical = (EPI == EPI_SWIGLU) ? 2 * a.n_split : a.N;
-  a.tiles_m = (a.M + BM - 1) / BM;
   a.a_bytes = AKS ? ((long)(a.K - 1) * a.lda + a.M) * 2 : ((long)(a.M - 1) * a.lda + a.K) * 2;
   a.b_bytes = BKS ? ((long)(a.K - 1) * a.ldb + n_logical) * 2 : ((long)(a.N - 1) * a.ldb + a.K) * 2;
-  if (a.a_bytes >= (1L << 31) || a.b_bytes >= (1L << 31)) return hipErrorInvalidValue;
+  a.tiles_m = (a.M + BM - 1) / BM;
   a.tiles_n = (n_logical + BN - 1) / BN;
+  a.group_m = a.tiles_m * a.tiles_n >= 16 ? 4 : a.tiles_m;
+  return a.a_bytes < (1L << 31) && a.b_bytes < (1L << 31);
+}
+
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
+  constexpr int NT = (BM / WM) * (BN / WN) * 64;
+  constexpr int LDS = (RING_A * BM + RING_B * BN) * BK * 2;
+  auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
+  if (n > 1) {
+    if constexpr (EPI == EPI_ACC_F32) {
+      auto kern = gemm_group_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
+      static LdsLimitOnce lds_limit;      // one per instantiation
+      if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
+      GemmGroup grp{};
+      int T = 0;
+      for (int i = 0; i < GEMM_GROUP; ++i) {
+        grp.first[i] = T;
+        if (i >= n) continue;
+        grp.g[i] = products[i];
+        if (!plan_tiles<BM, BN, AKS, BKS, EPI>(grp.g[i])) return hipErrorInvalidValue;
+        T += grp.g[i].tiles_m * grp.g[i].tiles_n;
+      }
+      for (int i = n; i <= GEMM_GROUP; ++i) grp.first[i] = T;
+      hipLaunchKernelGGL(kern, grid(T), dim3(NT), LDS, stream, grp);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  }
+  GemmArgs a = products[0];
+  if (!plan_tiles<BM, BN, AKS, BKS, EPI>(a)) return hipErrorInvalidValue;
   auto kern = gemm_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
   static LdsLimitOnce lds_limit;      // one per instantiation
   if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
-  const int T = a.tiles_m * a.tiles_n;
-  a.group_m = (T >= 16 && a.tiles_m >= 2) ? 4 : 0;
-  hipLaunchKernelGGL(kern, dim3(a.group_m ? 8 * ((T + 7) / 8) : T), dim3(NT), LDS, stream, a);
+  hipLaunchKernelGGL(kern, grid(a.tiles_m * a.tiles_n), dim3(NT), LDS, stream, a);
   return hipGetLastError();
 }
 
 template <bool AKS, bool BKS, int EPI>
-hipError_t launch_layout(const GemmArgs& a, int tile_cfg, hipStream_t stream) {
+hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t stream) {
   switch (tile_cfg) {
-    case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, stream);
-    case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, stream);
-    case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, stream);
-    default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, stream);
+    case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream);
+    default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, n, stream);
   }
 }
 
+// products held back for the next launch (GemmArgs::join)
+thread_local GemmArgs g_held[GEMM_GROUP];
+thread_local int g_nheld = 0;
+
 }  // namespace
 
-int gemm_pick_tile(int M, int N, int concurrency) {
+static int pick_tile(const GemmArgs* products, int n, bool swiglu, int concurrency) {
   // Time of a launch = rounds of tiles on 256 compute units x time of a tile.  A compute unit's rate on each tile
   // shape (TFLOP/s, measured on the products of the 13B shard: 5120 deep, 160 to 640 tiles) grows with the flops per
   // operand byte; 128x128 tiles run two to a unit (4.9 between them, 3.8 when one is alone), the others alone.
@@ -498,7 +547,11 @@ int gemm_pick_tile(int M, int N, int concurrency) {
   int best = GEMM_TILE_128x128;
   double best_cost = 1e30;
   for (const Cand& c : cands) {
-    const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    double tiles = 0;
+    for (int i = 0; i < n; ++i) {
+      const int N = swiglu ? 2 * products[i].n_split : products[i].N;
+      tiles += (double)((products[i].M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    }
     const double unit = (double)c.bm * c.bn / c.rate;
     double alone;
     if (c.id == GEMM_TILE_128x128) {
@@ -517,25 +570,47 @@ int gemm_pick_tile(int M, int N, int concurrency) {
   return best;
 }
 
-hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int tile_cfg, hipStream_t stream) {
-  if (tile_cfg < 0) tile_cfg = gemm_pick_tile(a.M, epi == EPI_SWIGLU ? 2 * a.n_split : a.N, a.concurrency);
+int gemm_pick_tile(int M, int N, int concurrency) {
+  GemmArgs a{};
+  a.M = M; a.N = N;
+  return pick_tile(&a, 1, false, concurrency);
+}
+
+hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hipStream_t stream) {
+  const GemmArgs* a = &a0;
+  int n = 1;
+  if (a0.join || g_nheld) {
+    if (layout != GEMM_TN || epi != EPI_ACC_F32) { g_nheld = 0; return hipErrorInvalidValue; }
+    GemmArgs* last = g_nheld ? &g_held[g_nheld - 1] : nullptr;
+    if (last && last->C == a0.C) {      // the next rows of the same product
+      if (static_cast<const char*>(last->A) + (long)last->K * last->lda * 2 != a0.A ||
+          static_cast<const char*>(last->B) + (long)last->K * last->ldb * 2 != a0.B || !a0.beta) { g_nheld = 0; return hipErrorInvalidValue; }
+      last->K += a0.K;
+    } else {
+      if (g_nheld == GEMM_GROUP) { g_nheld = 0; return hipErrorInvalidValue; }
+      g_held[g_nheld++] = a0;
+    }
+    if (a0.join) return hipSuccess;
+    a = g_held; n = g_nheld; g_nheld = 0;
+  }
+  if (tile_cfg < 0) tile_cfg = pick_tile(a, n, epi == EPI_SWIGLU, a->concurrency);
   if (layout == GEMM_NN) {
     switch (epi) {
-      case EPI_STORE:     return launch_layout<false, true, EPI_STORE>(a, tile_cfg, stream);
-      case EPI_BIAS_GELU: return launch_layout<false, true, EPI_BIAS_GELU>(a, tile_cfg, stream);
-      case EPI_SWIGLU:    return launch_layout<false, true, EPI_SWIGLU>(a, tile_cfg, stream);
-      case EPI_ROPE:      return launch_layout<false, true, EPI_ROPE>(a, tile_cfg, stream);
+      case EPI_STORE:     return launch_layout<false, true, EPI_STORE>(a, n, tile_cfg, stream);
+      case EPI_BIAS_GELU: return launch_layout<false, true, EPI_BIAS_GELU>(a, n, tile_cfg, stream);
+      case EPI_SWIGLU:    return launch_layout<false, true, EPI_SWIGLU>(a, n, tile_cfg, stream);
+      case EPI_ROPE:      return launch_layout<false, true, EPI_ROPE>(a, n, tile_cfg, stream);
       default: return hipErrorInvalidValue;
     }
   } else if (layout == GEMM_NT) {
     switch (epi) {
-      case EPI_STORE:   return launch_layout<false, false, EPI_STORE>(a, tile_cfg, stream);
-      case EPI_DGELU:   return launch_layout<false, false, EPI_DGELU>(a, tile_cfg, stream);
-      case EPI_DSWIGLU: return launch_layout<false, false, EPI_DSWIGLU>(a, tile_cfg, stream);
+      case EPI_STORE:   return launch_layout<false, false, EPI_STORE>(a, n, tile_cfg, stream);
+      case EPI_DGELU:   return launch_layout<false, false, EPI_DGELU>(a, n, tile_cfg, stream);
+      case EPI_DSWIGLU: return launch_layout<false, false, EPI_DSWIGLU>(a, n, tile_cfg, stream);
       default: return hipErrorInvalidValue;
     }
   } else if (layout == GEMM_TN) {
-    if (epi == EPI_ACC_F32) return launch_layout<true, true, EPI_ACC_F32>(a, tile_cfg, stream);
+    if (epi == EPI_ACC_F32) return launch_layout<true, true, EPI_ACC_F32>(a, n, tile_cfg, stream);
     return hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;
