@@ -76,7 +76,7 @@ struct Layout {
   bool llama;
   bool merged;       // weight and vector gradients of a block in one launch each over all slices (see merged_wgrads)
   bool per_slice;    // cfg->wgrad_per_slice
-  bool beside;       // the backward's weight gradients run on a stream of their own (see side_pays)
+  bool beside;       // the backward's weight gradients run on a stream of their own (see wgrads_beside)
   int groups;        // row groups: consecutive slices whose launches are one launch each (see row_groups)
   // saved block (bytes)
   size_t ln1, qkv, ctx, lse, x1, ln2, pre, act, mean1, rstd1, mean2, rstd2, saved_total;
@@ -93,23 +93,31 @@ struct Layout {
 
 enum { AREA_G1 = 0, AREA_B1, AREA_G2, AREA_B2, AREA_BQKV, AREA_BO, AREA_BUP, AREA_BDOWN, NAREAS };
 
+// Two rules say how a call spreads over its streams.  Both look at the block alone, so neither the arithmetic nor a bit
+// of any result depends on the stream pool.  In 256x256 tiles of the four weight gradients and of a product as wide as
+// the block:
+int tiles256(long m, long n) { return (int)((m + 255) / 256 * ((n + 255) / 256)); }
+int wgrad_tiles(const Layout& l) { return tiles256(l.fl, l.h) + tiles256(l.h, l.upc) + tiles256(l.hl, l.h) + tiles256(l.h, 3 * l.hl); }
+
+// The backward's weight gradients run on a stream of their own where their tiles fill the 256 compute units more than
+// once: then they fill what the chain of input gradients, attention and norms leaves idle.  Below that they follow on the
+// chain's stream as one launch, which has the chip to itself (24000 tokens of a 1536-wide shard, 63 tiles: 1231 against
+// 1666 us; GPT-3 2.7B, 160 tiles: 1646 against 1710; 13B, 620 tiles: 2283 against 2202).  The second stream also costs a
+// call about 100 us of host time (event records and waits) and 5 to 10 us at each of its edges on the GPU, whatever the
+// block's size: blocks under 40 GFLOP of weight gradients (half of 13B's at 512 tokens) keep to one.
+bool wgrads_beside(const Layout& l) {
+  return wgrad_tiles(l) > 256 && 2.0 * l.M * l.h * (4.0 * l.hl + l.upc + l.fl) >= 40e9;
+}
+
 // Row slices cut the batch so that a program can reduce one slice's partial sums over the ranks while the next slice
 // computes.  Inside one library call nothing waits for a single slice, so consecutive slices are launched together, as
 // one launch over the rows of all of them: larger launches fill 256 compute units better, and a step of many small
 // launches pays for the launches.  What the slices' streams used to buy, two chains of dependent launches side by side
-// so that one fills the chip while the other drains, needs two groups and no more: four streams share the four hardware
-// queues that a process gets by default, and slices that meet on a queue run one after the other.  With one or two
-// slices the second chain is the weight gradients' (the backward's side stream), and a group is all rows.
-// The rule looks at the slicing alone, so neither the arithmetic nor a bit of any result depends on the stream pool.
-int row_groups(int p) { return p > 2 ? 2 : 1; }
-
-// A second stream costs a call about 100 us of host time (event records and waits) and 5 to 10 us at each of its edges
-// on the GPU, whatever the size of the block: below this many multiplications and additions of a block's four weight
-// gradients, they follow on the one stream, grouped into one launch.
-constexpr double SIDE_MIN_FLOPS = 40e9;
-bool side_pays(const Layout& l) {
-  return 2.0 * l.M * l.h * (4.0 * l.hl + l.upc + l.fl) >= SIDE_MIN_FLOPS;
-}
+// so that one fills the chip while the other drains, needs two groups and no more (four streams share the four hardware
+// queues that a process gets by default, and slices that meet on a queue run one after the other), and only pays in
+// wide blocks where a group's launches fill the chip on their own: 13B with 8192 tokens, 640 tiles: 2202 us with two
+// groups, 2376 with one; with 2048 tokens, 160 tiles: 752 and 723; 2.7B with 32768 tokens: 3728 and 3391.
+int row_groups(const Layout& l) { return l.p > 2 && wgrads_beside(l) && tiles256(l.M, l.h) >= 512 ? 2 : 1; }
 
 int validate(const domino_cfg* c, Layout* L) {
   if (!c) return fail(DOMINO_ERR_NULL_POINTER, "cfg is NULL");
@@ -133,7 +141,6 @@ int validate(const domino_cfg* c, Layout* L) {
   if (c->wgrad_per_slice != 0 && c->wgrad_per_slice != 1) return fail(DOMINO_ERR_INVALID_ARG, "wgrad_per_slice must be 0 or 1");
   l.merged = c->p > 2 && !c->wgrad_per_slice;
   l.per_slice = c->wgrad_per_slice;
-  l.groups = row_groups(c->p);
   l.d = l.h / l.n; l.nl = l.n / l.t; l.hl = l.nl * l.d; l.fl = l.f / l.t;
   l.upc = l.fl * (l.llama ? 2 : 1);
   l.hq = l.h / l.q;
@@ -149,7 +156,8 @@ int validate(const domino_cfg* c, Layout* L) {
   if ((long)l.h * widest * 4 >= TWO_GIB) return fail(DOMINO_ERR_UNSUPPORTED, "a weight-gradient tensor would reach 2 GiB");
   l.M = (int)M;
   l.Ms = l.M / l.p;
-  l.beside = side_pays(l);
+  l.beside = wgrads_beside(l);
+  l.groups = row_groups(l);
 
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };

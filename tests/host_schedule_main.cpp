@@ -316,11 +316,15 @@ struct Buffers {                                    // addresses only: one arena
   }
 };
 
+// a block wide enough that row groups run side by side and the weight gradients beside them (the small one keeps to one stream)
+static bool g_wide = false;
+
 static domino_cfg make_cfg(int arch, int p, int q, bool per_slice) {
   domino_cfg c{};
   c.wgrad_per_slice = per_slice ? 1 : 0;
   c.hidden = 256; c.heads = 4; c.tp = 2; c.rank = 1; c.p = p; c.q = q; c.batch = 8; c.seq = 64;
   c.ffn = arch == DOMINO_ARCH_LLAMA ? 704 : 1024;
+  if (g_wide) { c.hidden = 4096; c.heads = 32; c.tp = 4; c.seq = 1024; c.ffn = 16384; }
   c.arch = arch; c.gelu_tanh = 1; c.norm_eps = 1e-5f; c.rope_base = 10000.0f;
   return c;
 }
@@ -355,14 +359,14 @@ static Layer make_layer(Buffers& B, const domino_cfg& c) {
 
 static void run_case(int arch, int p, int q, int nstreams, bool capturing, int nlayers, bool parts, bool per_slice = false) {
   char name[160];
-  std::snprintf(name, sizeof(name), "%s p=%d q=%d streams=%d%s layers=%d%s", arch ? "llama" : "gpt", p, q, nstreams,
+  std::snprintf(name, sizeof(name), "%s%s p=%d q=%d streams=%d%s layers=%d%s", g_wide ? "wide " : "", arch ? "llama" : "gpt", p, q, nstreams,
                 capturing ? " capturing" : "", nlayers, parts ? (per_slice ? " parts per-slice" : " parts") : (per_slice ? " per-slice" : ""));
   g_case = name;
   const domino_cfg c = make_cfg(arch, p, q, per_slice);
   g_merged = p > 2 && !per_slice;
   g_rows = (long)c.batch * c.seq;
   if (domino_validate_cfg(&c) != DOMINO_OK) { EXPECT(false, "configuration rejected: %s", domino_last_error()); return; }
-  Buffers B((size_t)96 << 20);
+  Buffers B((size_t)12 << 30);
   std::vector<Layer> layers;
   for (int l = 0; l < nlayers; ++l) layers.push_back(make_layer(B, c));
   const size_t act = (size_t)c.batch * c.seq * c.hidden * 2;
@@ -441,10 +445,12 @@ static void run_case(int arch, int p, int q, int nstreams, bool capturing, int n
 
 int main() {
   int cases = 0;
+  for (bool wide : {false, true})
   for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})
     for (int p : {1, 2, 4, 8})
       for (int q : {1, 2})
         for (int ns = 1; ns <= 8; ++ns) {
+          g_wide = wide;
           run_case(arch, p, q, ns, false, 1, false); ++cases;
           run_case(arch, p, q, ns, true, 1, false); ++cases;
           // four blocks: the tensors handed from block to block, taken in turn, come round again
