@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -93,6 +94,8 @@ struct Layout {
 
 enum { AREA_G1 = 0, AREA_B1, AREA_G2, AREA_B2, AREA_BQKV, AREA_BO, AREA_BUP, AREA_BDOWN, NAREAS };
 
+std::atomic<bool> g_prof_on{false};      // per-launch timing (domino_profile_enable)
+
 // Two rules say how a call spreads over its streams.  Both look at the block alone, so neither the arithmetic nor a bit
 // of any result depends on the stream pool.  In 256x256 tiles of the four weight gradients and of a product as wide as
 // the block:
@@ -117,7 +120,11 @@ bool wgrads_beside(const Layout& l) {
 // queues that a process gets by default, and slices that meet on a queue run one after the other), and only pays in
 // wide blocks where a group's launches fill the chip on their own: 13B with 8192 tokens, 640 tiles: 2202 us with two
 // groups, 2376 with one; with 2048 tokens, 160 tiles: 752 and 723; 2.7B with 32768 tokens: 3728 and 3391.
-int row_groups(const Layout& l) { return l.p > 2 && wgrads_beside(l) && tiles256(l.M, l.h) >= 512 ? 2 : 1; }
+// With per-launch timing on, p > 2 slices are always two groups, so that a timeline has launches to tell slices by.
+int most_groups(const Layout& l) { return l.p > 2 ? 2 : 1; }
+int row_groups(const Layout& l) {
+  return g_prof_on || (wgrads_beside(l) && tiles256(l.M, l.h) >= 512) ? most_groups(l) : 1;
+}
 
 int validate(const domino_cfg* c, Layout* L) {
   if (!c) return fail(DOMINO_ERR_NULL_POINTER, "cfg is NULL");
@@ -187,7 +194,7 @@ int validate(const domino_cfg* c, Layout* L) {
     size_t fo = 0;
     for (int k = 0; k < NAREAS; ++k) {
       l.area_off[k] = fo; l.area_rows[k] = rows[k]; l.area_n[k] = width[k];
-      fo += (size_t)rows[k] * width[k] * (k == AREA_BQKV || k == AREA_BUP ? l.groups : l.p);
+      fo += (size_t)rows[k] * width[k] * (k == AREA_BQKV || k == AREA_BUP ? most_groups(l) : l.p);
     }
     l.red_floats = (fo + 63) / 64 * 64;
   }
@@ -257,7 +264,6 @@ const char* const PROF_NAMES[PC_COUNT] = {
   "attn_bwd", "dgrad_qkv", "wgrad_qkv", "colsum"};
 
 struct ProfRec { int cls; hipStream_t stream; hipEvent_t start, stop; };
-bool g_prof_on = false;
 std::vector<ProfRec> g_prof_recs;
 std::vector<hipEvent_t> g_prof_free;
 
@@ -593,27 +599,30 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
   return DOMINO_OK;
 }
 
-// The eight vector gradients (norm gains and shifts, biases) from the partial rows that the slices' norm backwards and
-// the groups' column sums left: summed in index order, in one launch over all slices or in one per slice (the groups'
-// column sums then belong to the first).
-int vector_gradients(const Layout& L, const BwdLayer& B, hipStream_t st) {
+// The vector gradients (norm gains and shifts, biases) from the partial rows that the slices' norm backwards and the
+// groups' column sums left: summed in index order, all slices in one launch (with cfg->wgrad_per_slice one per slice; the
+// groups' column sums then belong to the first).  Those of the MLP half are complete behind the Norm2 backward, the
+// others behind Norm1's.
+enum { VEC_MLP = 1, VEC_ATTN = 2, VEC_ALL = 3 };
+int vector_gradients(const Layout& L, const BwdLayer& B, int which, hipStream_t st) {
   const domino_grads* G = B.G;
   const int launches = merged_wgrads(L) ? 1 : L.p, slices = L.p / launches;
   for (int i = 0; i < launches; ++i) {
     ProfScope ps(PC_COLSUM, st);
-    struct { int k; float* out; } const vec[NAREAS] = {
-      {AREA_G1, G->norm1_g}, {AREA_B1, G->norm1_b}, {AREA_G2, G->norm2_g}, {AREA_B2, G->norm2_b},
-      {AREA_BQKV, G->b_qkv}, {AREA_BO, G->b_o}, {AREA_BUP, G->b_up}, {AREA_BDOWN, G->b_down}};
+    struct { int k; float* out; int set; } const vec[NAREAS] = {
+      {AREA_G1, G->norm1_g, VEC_ATTN}, {AREA_B1, G->norm1_b, VEC_ATTN}, {AREA_G2, G->norm2_g, VEC_MLP}, {AREA_B2, G->norm2_b, VEC_MLP},
+      {AREA_BQKV, G->b_qkv, VEC_ATTN}, {AREA_BO, G->b_o, VEC_MLP}, {AREA_BUP, G->b_up, VEC_MLP}, {AREA_BDOWN, G->b_down, VEC_MLP}};
     ColsumJobs jobs{};
     int njobs = 0;
     for (auto& v : vec) {
-      if (!v.out) continue;
+      if (!v.out || !(v.set & which)) continue;
       if (L.llama && v.k != AREA_G1 && v.k != AREA_G2) continue;
       const bool by_group = v.k == AREA_BQKV || v.k == AREA_BUP;
       if (by_group && i > 0) continue;
       jobs.job[njobs++] = {B.red + L.area(v.k, by_group ? 0 : i * slices), v.out, L.area_rows[v.k], L.area_n[v.k], (long)L.area_n[v.k],
                            by_group ? L.groups : slices, (long)L.area_rows[v.k] * L.area_n[v.k]};
     }
+    jobs.join = !L.per_slice && i < launches - 1 ? 1 : 0;
     LAUNCH(colsum_finish_jobs_launch(jobs, njobs, (i > 0 || B.accumulate) ? 1 : 0, st), "vector gradient reduction");
   }
   return DOMINO_OK;
@@ -737,6 +746,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     if (S.side) {        // beside the attention backward, which leaves the matrix cores idle most of the time
       TRY(behind_groups(side));
       TRY(form({WG_OUT}, side));
+      TRY(vector_gradients(L, B, VEC_MLP, side));
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B6
       ProfScope ps(PC_DGRAD_OUT, st);
@@ -786,10 +796,10 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
   if (S.side) {
     if (parts & DOMINO_BWD_NORM1) {
       TRY(behind_groups(side, own ? &own->dx : nullptr));
-      TRY(vector_gradients(L, B, side));
+      TRY(vector_gradients(L, B, VEC_ATTN, side));
     }
   } else if (in_place) {
-    if (parts & DOMINO_BWD_NORM1) TRY(vector_gradients(L, B, S.lane(0)));
+    if (parts & DOMINO_BWD_NORM1) TRY(vector_gradients(L, B, VEC_ALL, S.lane(0)));
   } else {
     TRY(join_streams(S, S.lanes));
     TRY(fork_streams(S, S.lanes));
@@ -803,7 +813,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
         TRY(join_streams(S, S.lanes));
         TRY(fork_streams(S, S.lanes));
       }
-      TRY(vector_gradients(L, B, as_stream(S.streams[slot % S.lanes])));
+      TRY(vector_gradients(L, B, VEC_ALL, as_stream(S.streams[slot % S.lanes])));
     }
   }
   return DOMINO_OK;

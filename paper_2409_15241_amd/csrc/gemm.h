@@ -13,7 +13,8 @@ enum GemmEpilogue {
   EPI_ACC_F32 = 5,    // C(fp32) = acc (+ C if beta)
   EPI_ROPE = 6,       // C = bf16(acc) with the rotary embedding applied to columns below rope_cols (heads of rope_d columns)
 };
-enum GemmTile { GEMM_TILE_128x128 = 0, GEMM_TILE_256x128 = 1, GEMM_TILE_256x256 = 2, GEMM_TILE_128x256 = 3 };
+enum GemmTile { GEMM_TILE_128x128 = 0, GEMM_TILE_256x128 = 1, GEMM_TILE_256x256 = 2, GEMM_TILE_128x256 = 3,
+                GEMM_TILE_64x64 = 4 };
 
 struct GemmArgs {
   const void* A; const void* B; void* C;
@@ -33,7 +34,6 @@ struct GemmArgs {
   long a_bytes, b_bytes; // extent of the A / B views in bytes, filled by the launcher
 };
 
-int gemm_pick_tile(int M, int N, int concurrency);
 // tile_cfg < 0: pick by shape.  Enqueues on `stream`; returns the launch status.
 // Products with `join` set are held back (per thread) until the next call without it, which must follow on the same
 // stream: at most GEMM_GROUP weight gradients then go out as one launch.  A product into the matrix of the one before it,

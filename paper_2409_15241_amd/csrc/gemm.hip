@@ -31,10 +31,19 @@ namespace {
 constexpr int BK = 64;      // contraction elements per operand tile
 constexpr int RING_A = 3, RING_B = 2;
 
+// KS tile [64 k][R rows]: element (k, n) at byte 2 R k + 64 ((n >> 5) ^ ks_swz(k)) + 2 (n & 31).  A transposing read
+// covers 4 consecutive k x 16 n: the XOR, together with the row pitch, puts the 4 rows in 4 different 64-byte quarters of
+// the banks.
+template <int R>
+DEV int ks_swz(int k) {
+  static_assert(R % 64 == 0, "rows of a contraction-strided tile");
+  return R % 128 == 0 ? (k & 3) : ((k >> 1) & 1);
+}
+
 // Loads of one operand tile: R rows (columns of C for B), NW waves, IPW one-KiB pieces per wave.
 //   KC tile [R rows][64 k]: 16-byte chunk (r, c) at slot 8 r + (c ^ (r & 7)): the 8 lanes that one LDS clock serves in a
 //       fragment read (8 rows, one chunk index) touch all banks once, and 8 lanes of a load cover a whole 128-byte line.
-//   KS tile [64 k][R rows]: the layout of lds_dma.h.
+//   KS tile [64 k][R rows]: see ks_swz.
 // The tile is advanced along the contraction in the buffer resource (base and extent, scalar registers): a load costs
 // the vector ALU nothing but the contraction-tail select of a KC operand.
 template <int R, int NW, bool KS>
@@ -59,7 +68,7 @@ struct TileLoader {
       if constexpr (KS) {
         const int P = (wave * IPW + i) * 1024 + lane * 16;
         const int k = P / (R * 2), w = P % (R * 2);
-        const int c = cols((((w >> 6) ^ (k & 3)) << 5) + ((w >> 4) & 3) * 8);
+        const int c = cols((((w >> 6) ^ ks_swz<R>(k)) << 5) + ((w >> 4) & 3) * 8);
         base[i] = c >= 0 ? (uint32_t)(k * ld + c) * 2u : BUF_OOB;
       } else {
         const int r = row0 + 8 * (wave * IPW + i) + (lane >> 3);
@@ -69,7 +78,7 @@ struct TileLoader {
   }
   DEV buf_rsrc rsrc() const { return make_rsrc(ptr, left); }
   DEV bool inside() const { return KS || kofs < kleft; }     // contraction tail: chunks past K load zeros
-  DEV void advance() { ptr += step; left = left > step ? left - step : 0; kleft -= BK; }
+  DEV void advance(int n = 1) { ptr += (long)n * step; left = left > n * step ? left - n * step : 0; kleft -= n * BK; }
   DEV void issue(int i, buf_rsrc rs, bool in, uint8_t* tile, int wave) const {
     const uint32_t off = KS || in ? base[i] : BUF_OOB;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(tile + (wave * IPW + i) * 1024), 16, off, 0, 0, 0);
@@ -81,6 +90,202 @@ DEV void static_for(F&& f) {
   if constexpr (I < N) {
     f(std::integral_constant<int, I>{});
     static_for<I + 1, N>(f);
+  }
+}
+
+// Per-lane byte offsets of a 16-row fragment's reads inside a tile: lane holds row lane%16, elements 8 (lane/16) .. of 32.
+DEV uint32_t kc_frag_off16(int lane) { const int fr = lane & 15, fh = lane >> 4; return (uint32_t)(fr * 128 + ((fh ^ (fr & 7)) << 4)); }
+template <int R>
+DEV uint32_t ks_frag_off16(int lane, int n16) {       // first of the two transposing reads; the second is 4 k rows on
+  const int fr = lane & 15, fh = lane >> 4, k = 8 * fh + (fr >> 2);
+  return (uint32_t)(k * R * 2 + (((n16 >> 1) ^ ks_swz<R>(k)) << 6) + (n16 & 1) * 32 + 8 * (fr & 3));
+}
+
+// SwiGLU forward: the tile's even 32-column groups are gate columns, the odd ones the matching
+// up columns, so one lane sees gate and up of the same ffn column.
+struct GluCols {
+  int c0, n_split;
+  DEV int operator()(int r) const {
+    int col = c0 + ((r >> 6) << 5) + (r & 31);
+    if (col >= n_split) return -1;
+    return col + ((r >> 5) & 1) * n_split;
+  }
+};
+
+// Rotary embedding: the partner columns (i, i + d/2) of a head must meet in one lane of the epilogue, which pairs
+// tile columns 32 apart inside every 64 (as for SwiGLU).  Heads of 64 columns already lie that way; for
+// heads of 128 the second and third group of 32 inside every 128 trade places.
+struct RopeCols {
+  int n0, n_end, d;
+  DEV int at(int r) const {
+    const int g = n0 + r;
+    return d == 128 ? ((g & ~96) | (((g >> 5) & 1) << 6) | (((g >> 6) & 1) << 5)) : g;
+  }
+  DEV int operator()(int r) const { const int g = at(r); return g < n_end ? g : -1; }
+};
+
+// Epilogue.  Stored from the accumulators, every instruction would touch 16 rows with 32 or 64 bytes each.  Blocks of
+// fp32 sums go through LDS instead: written by row owner, read back with WN/4 consecutive lanes along a row, so that
+// loads of the side tensors and all stores cover whole 128-byte lines.
+constexpr int epi_row_bytes(int WN) { return WN * 4 + 16; }      // padded row: the 16 rows of a write phase hit distinct banks
+
+// what depends on a lane's 4 columns only: lane (row lane / (WN/4) of an instruction) has the 4 from rcol on
+template <int BN, int WN, int EPI>
+struct EpiCols {
+  int rcol, rrow;
+  int n, col;                                    // global column; SwiGLU: ffn column of the gate / up pair
+  bool n_ok;
+  float rfreq[EPI == EPI_ROPE ? 4 : 1];          // rotary embedding: the frequencies of the lane's 4 pair indices
+  bool rot;
+  f32x4 bias4;
+
+  DEV EpiCols(const GemmArgs& p, int tn, int n0, int wn0, int lane) {
+    rrow = lane / (WN / 4);
+    rcol = (lane % (WN / 4)) * 4;
+    const int nl = wn0 + rcol;                   // tile-local column of the first of this lane's 4
+    col = 0; rot = false;
+    if constexpr (EPI == EPI_SWIGLU) {
+      col = tn * (BN / 2) + ((nl >> 6) << 5) + (nl & 31);
+      n = col;
+      n_ok = !((nl >> 5) & 1) && col < p.n_split;  // up groups are handled by the lane holding their gate group
+    } else if constexpr (EPI == EPI_ROPE) {
+      static_assert(EPI != EPI_ROPE || WN % 64 == 0, "the rotary epilogue pairs columns inside 64-column groups");
+      n = RopeCols{n0, p.N, p.rope_d}.at(nl);                    // memory column of the first element of the pair
+      n_ok = !((nl >> 5) & 1) && n < p.N;                        // the partner groups are handled by the lane holding i
+      rot = n_ok && n < p.rope_cols;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rfreq[e] = rot ? rope_freq(n % p.rope_d + e, p.rope_d, p.rope_log2_base) : 0.0f;
+    } else {
+      n = n0 + nl;
+      n_ok = n < p.N;
+    }
+    bias4 = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (EPI == EPI_STORE || EPI == EPI_BIAS_GELU) {
+      if (p.bias && n_ok) {
+        const u32x2 bb = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.bias) + n);
+        bias4 = f32x4{bf16_lo(bb[0]), bf16_hi(bb[0]), bf16_lo(bb[1]), bf16_hi(bb[1])};
+      }
+    }
+  }
+};
+
+// Stores ROWS rows of sums from LDS, buffer row 0 = row m_first of C: the sums of `parts` buffers part_bytes apart,
+// added in their order.
+template <int BN, int WN, int EPI, int ROWS, bool PARTS>
+DEV void store_rows(const GemmArgs& p, const EpiCols<BN, WN, EPI>& ec, const uint8_t* buf, int m_first, int parts = 1, int part_bytes = 0) {
+  constexpr int ROWB = epi_row_bytes(WN);
+  constexpr int RPI = 64 / (WN / 4);             // rows per read instruction
+  constexpr int NT_ROWS = ROWS / RPI;            // read-back instructions
+  constexpr int CH = NT_ROWS < 8 ? NT_ROWS : 8;
+  const int n = ec.n, col = ec.col, rcol = ec.rcol;
+  auto read = [&](int at) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(buf + at);
+    if constexpr (PARTS)
+      for (int k = 1; k < parts; ++k) v += *reinterpret_cast<const f32x4*>(buf + k * part_bytes + at);
+    return v;
+  };
+  // 8 row groups at a time.  Phase 1: every load of the group (LDS read-back and side tensors) is issued before any is
+  // used; rows or columns outside the matrix read a safe address instead of branching, their results are never stored
+#pragma unroll 1
+  for (int t0 = 0; t0 < NT_ROWS; t0 += CH) {
+    f32x4 v[CH], u[(EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? CH : 1], old[EPI == EPI_ACC_F32 ? CH : 1];
+    u32x2 sa[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? CH : 1], sb[EPI == EPI_DSWIGLU ? CH : 1];
+    bool ok[CH];
+    long mrow[CH];
+#pragma unroll
+    for (int t = 0; t < CH; ++t) {
+      const int row = (t0 + t) * RPI + ec.rrow;
+      const int m = m_first + row;
+      ok[t] = ec.n_ok && m < p.M;
+      mrow[t] = ok[t] ? (long)m : 0L;
+      v[t] = read(row * ROWB + rcol * 4);
+      if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) u[t] = read(row * ROWB + (rcol ^ 32) * 4);
+      const int ns = ok[t] ? n : 0;
+      if constexpr (EPI == EPI_ACC_F32) {
+        if (p.beta) old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + mrow[t] * p.ldc + ns);
+      } else if constexpr (EPI == EPI_DGELU) {
+        sa[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux + ns);
+      } else if constexpr (EPI == EPI_DSWIGLU) {
+        const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux;
+        sa[t] = *reinterpret_cast<const u32x2*>(aux + ns);
+        sb[t] = *reinterpret_cast<const u32x2*>(aux + p.n_split + ns);
+      }
+    }
+    // Phase 2: arithmetic and stores
+    auto finish = [&](auto tanh_c) __attribute__((always_inline)) {
+      [[maybe_unused]] constexpr bool tanh_form = decltype(tanh_c)::value;
+#pragma unroll
+      for (int t = 0; t < CH; ++t) {
+        f32x4 w = v[t];
+        if constexpr (EPI == EPI_SWIGLU) {
+          if (ok[t]) {
+            bf16_t* aux = static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux;
+            const u32x2 pg = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+            const u32x2 pu = {pack_bf16(u[t][0], u[t][1]), pack_bf16(u[t][2], u[t][3])};
+            *reinterpret_cast<u32x2*>(aux + col) = pg;
+            *reinterpret_cast<u32x2*>(aux + p.n_split + col) = pu;
+            f32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = w[e] * sigmoid_f(w[e]) * u[t][e];
+            const u32x2 po = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+            *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + col) = po;
+          }
+        } else if constexpr (EPI == EPI_ACC_F32) {
+          if (p.beta) w += old[t];
+          if (ok[t]) *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + mrow[t] * p.ldc + n) = w;
+        } else if constexpr (EPI == EPI_ROPE) {
+          f32x4 hi = u[t];
+          if (ec.rot) {
+            const float pos = (float)(int)(mrow[t] % p.rope_seq);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              float sn, cs;
+              rope_sincos(pos, ec.rfreq[e], &sn, &cs);
+              const float a = w[e], b = hi[e];
+              w[e] = a * cs - b * sn;
+              hi[e] = b * cs + a * sn;
+            }
+          }
+          if (ok[t]) {
+            bf16_t* crow = static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n;
+            const u32x2 plo = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+            const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
+            *reinterpret_cast<u32x2*>(crow) = plo;
+            *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
+          }
+        } else {
+          w += ec.bias4;
+          if constexpr (EPI == EPI_BIAS_GELU) {
+            const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+            if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux + n) = pp;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = gelu_f(w[e], tanh_form);
+          } else if constexpr (EPI == EPI_DGELU) {
+            w[0] *= gelu_grad_f(bf16_lo(sa[t][0]), tanh_form); w[1] *= gelu_grad_f(bf16_hi(sa[t][0]), tanh_form);
+            w[2] *= gelu_grad_f(bf16_lo(sa[t][1]), tanh_form); w[3] *= gelu_grad_f(bf16_hi(sa[t][1]), tanh_form);
+          } else if constexpr (EPI == EPI_DSWIGLU) {
+            const float gv[4] = {bf16_lo(sa[t][0]), bf16_hi(sa[t][0]), bf16_lo(sa[t][1]), bf16_hi(sa[t][1])};
+            const float uv[4] = {bf16_lo(sb[t][0]), bf16_hi(sb[t][0]), bf16_lo(sb[t][1]), bf16_hi(sb[t][1])};
+            f32x4 du;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float sg = sigmoid_f(gv[e]);
+              du[e] = w[e] * gv[e] * sg;                                   // d_act * silu(g)
+              w[e] = w[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));     // d_act * u * silu'(g)
+            }
+            const u32x2 pdu = {pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
+            if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + p.n_split + n) = pdu;
+          }
+          const u32x2 po = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+          if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n) = po;
+        }
+      }
+    };
+    if constexpr (EPI == EPI_BIAS_GELU || EPI == EPI_DGELU) {
+      if (p.gelu_tanh) finish(std::true_type{}); else finish(std::false_type{});
+    } else {
+      finish(std::true_type{});
+    }
   }
 }
 
@@ -105,28 +310,6 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   const int tm = band * p.group_m + inband % gm, tn = inband / gm;
   const int m0 = tm * BM, n0 = tn * BN;
 
-  // SwiGLU forward: the tile's even 32-column groups are gate columns, the odd ones the matching
-  // up columns, so one lane sees gate and up of the same ffn column.
-  struct GluCols {
-    int c0, n_split;
-    DEV int operator()(int r) const {
-      int col = c0 + ((r >> 6) << 5) + (r & 31);
-      if (col >= n_split) return -1;
-      return col + ((r >> 5) & 1) * n_split;
-    }
-  };
-
-  // Rotary embedding: the partner columns (i, i + d/2) of a head must meet in one lane of the epilogue, which pairs
-  // tile columns 32 apart inside every 64 (as for SwiGLU).  Heads of 64 columns already lie that way; for
-  // heads of 128 the tile's second and third group of 32 inside every 128 trade places.
-  struct RopeCols {
-    int n0, n_end, d;
-    DEV int perm(int r) const {
-      return d == 128 ? ((r & ~96) | (((r >> 5) & 1) << 6) | (((r >> 6) & 1) << 5)) : r;
-    }
-    DEV int operator()(int r) const { const int g = n0 + perm(r); return g < n_end ? g : -1; }
-  };
-
   TileLoader<BM, NW, AKS> ldA;
   TileLoader<BN, NW, BKS> ldB;
   constexpr int IPA = TileLoader<BM, NW, AKS>::IPW, IPB = TileLoader<BN, NW, BKS>::IPW;
@@ -145,21 +328,17 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   // per-lane LDS byte offsets of the fragments inside a tile.  A fragment is 16 rows x 32 contraction elements: lane
   // holds row lane%16, elements 8 (lane/16) ..; the tile's second 32 elements are reached by XOR 64 (KC) or 32 rows on (KS)
   const int fr = lane & 15, fh = lane >> 4;
-  const uint32_t kc_off = (uint32_t)(fr * 128 + ((fh ^ (fr & 7)) << 4));
-  auto ks_off = [&](int row_bytes, int n16) {       // first of the two transposing reads; the second is 4 k rows on
-    const int k = 8 * fh + (fr >> 2);
-    return (uint32_t)(k * row_bytes + (((n16 >> 1) ^ (k & 3)) << 6) + (n16 & 1) * 32 + 8 * (fr & 3));
-  };
+  const uint32_t kc_off = kc_frag_off16(lane);
   uint32_t offA[AKS ? TM : 1], offB[BKS ? TN : 1];
   if constexpr (AKS) {
 #pragma unroll
-    for (int j = 0; j < TM; ++j) offA[j] = ks_off(BM * 2, (wm0 >> 4) + j);
+    for (int j = 0; j < TM; ++j) offA[j] = ks_frag_off16<BM>(lane, (wm0 >> 4) + j);
   } else {
     offA[0] = kc_off + wm0 * 128;
   }
   if constexpr (BKS) {
 #pragma unroll
-    for (int i = 0; i < TN; ++i) offB[i] = ks_off(BN * 2, (wn0 >> 4) + i);
+    for (int i = 0; i < TN; ++i) offB[i] = ks_frag_off16<BN>(lane, (wn0 >> 4) + i);
   } else {
     offB[0] = kc_off + wn0 * 128;
   }
@@ -284,52 +463,12 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   tie_step(step0{});
 
   // ---- epilogue.  Accumulator (i, j) value v of a lane is C[m][n] with
-  //      m = m0 + wm0 + 16 j + lane%16,  n = n0 + wn0 + 16 i + 4 (lane/16) + v,
-  // stored from there, every instruction would touch 16 rows with 32 or 64 bytes
-  // each.  Each wave therefore turns its 32 x WN blocks through its own piece of the (now free) LDS:
-  // written by row owner, read back with WN/4 consecutive lanes along a row, so that loads of the side
-  // tensors and all stores cover whole 128-byte lines.
+  //      m = m0 + wm0 + 16 j + lane%16,  n = n0 + wn0 + 16 i + 4 (lane/16) + v:
+  // each wave turns its 32 x WN blocks through its own piece of the (now free) LDS
   __builtin_amdgcn_s_barrier();                  // every wave has finished reading the operand stages
-  constexpr int ROWB = WN * 4 + 16;              // padded row: the 16 rows of a write phase hit distinct banks
-  constexpr int LPR = WN / 4;                    // lanes per row when reading back
-  constexpr int RPI = 64 / LPR;                  // rows per read instruction
+  constexpr int ROWB = epi_row_bytes(WN);
   uint8_t* wbuf = smem + wave * (32 * ROWB);
-  const int rrow = lane / LPR, rcol = (lane % LPR) * 4;
-  constexpr int NT_ROWS = 32 / RPI;              // read-back instructions per 32-row block
-  constexpr int CH = NT_ROWS < 8 ? NT_ROWS : 8;
-
-  // what depends on the lane's 4 columns only
-  const int nl = wn0 + rcol;                     // tile-local column of the first of this lane's 4
-  int n, col = 0;                                // global column; SwiGLU: ffn column of the gate / up pair
-  bool n_ok;
-  if constexpr (EPI == EPI_SWIGLU) {
-    col = tn * (BN / 2) + ((nl >> 6) << 5) + (nl & 31);
-    n = col;
-    n_ok = !((nl >> 5) & 1) && col < p.n_split;  // up groups are handled by the lane holding their gate group
-  } else if constexpr (EPI == EPI_ROPE) {
-    static_assert(EPI != EPI_ROPE || WN % 64 == 0, "the rotary epilogue pairs columns inside 64-column groups");
-    n = n0 + RopeCols{n0, p.N, p.rope_d}.perm(nl);            // memory column of the first element of the pair
-    n_ok = !((nl >> 5) & 1) && n < p.N;                        // the partner groups are handled by the lane holding i
-  } else {
-    n = n0 + nl;
-    n_ok = n < p.N;
-  }
-  // rotary embedding: the frequencies of this lane's 4 pair indices
-  [[maybe_unused]] float rfreq[4];
-  [[maybe_unused]] bool rot = false;
-  if constexpr (EPI == EPI_ROPE) {
-    rot = n_ok && n < p.rope_cols;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) rfreq[e] = rot ? rope_freq(n % p.rope_d + e, p.rope_d, p.rope_log2_base) : 0.0f;
-  }
-  f32x4 bias4 = {0.0f, 0.0f, 0.0f, 0.0f};
-  if constexpr (EPI == EPI_STORE || EPI == EPI_BIAS_GELU) {
-    if (p.bias && n_ok) {
-      const u32x2 bb = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.bias) + n);
-      bias4 = f32x4{bf16_lo(bb[0]), bf16_hi(bb[0]), bf16_lo(bb[1]), bf16_hi(bb[1])};
-    }
-  }
-
+  const EpiCols<BN, WN, EPI> ec(p, tn, n0, wn0, lane);
   static_for<0, TM / 2>([&](auto jc) __attribute__((always_inline)) {
     constexpr int j = decltype(jc)::value;
 #pragma unroll
@@ -337,110 +476,118 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
 #pragma unroll
       for (int g = 0; g < 2; ++g)
         *reinterpret_cast<f32x4*>(wbuf + (16 * g + fr) * ROWB + (i * 16 + fh * 4) * 4) = acc[i][2 * j + g];
-    // 8 row groups at a time.  Phase 1: every load of the group (LDS read-back and side tensors) is issued before any is
-    // used; rows or columns outside the matrix read a safe address instead of branching, their results are never stored
-#pragma unroll 1
-    for (int t0 = 0; t0 < NT_ROWS; t0 += CH) {
-      f32x4 v[CH], u[(EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? CH : 1], old[EPI == EPI_ACC_F32 ? CH : 1];
-      u32x2 sa[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? CH : 1], sb[EPI == EPI_DSWIGLU ? CH : 1];
-      bool ok[CH];
-      long mrow[CH];
-#pragma unroll
-      for (int t = 0; t < CH; ++t) {
-        const int row = (t0 + t) * RPI + rrow;
-        const int m = m0 + wm0 + j * 32 + row;
-        ok[t] = n_ok && m < p.M;
-        mrow[t] = ok[t] ? (long)m : 0L;
-        v[t] = *reinterpret_cast<const f32x4*>(wbuf + row * ROWB + rcol * 4);
-        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) u[t] = *reinterpret_cast<const f32x4*>(wbuf + row * ROWB + (rcol ^ 32) * 4);
-        const int ns = ok[t] ? n : 0;
-        if constexpr (EPI == EPI_ACC_F32) {
-          if (p.beta) old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + mrow[t] * p.ldc + ns);
-        } else if constexpr (EPI == EPI_DGELU) {
-          sa[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux + ns);
-        } else if constexpr (EPI == EPI_DSWIGLU) {
-          const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux;
-          sa[t] = *reinterpret_cast<const u32x2*>(aux + ns);
-          sb[t] = *reinterpret_cast<const u32x2*>(aux + p.n_split + ns);
-        }
-      }
-      // Phase 2: arithmetic and stores
-      auto finish = [&](auto tanh_c) __attribute__((always_inline)) {
-        [[maybe_unused]] constexpr bool tanh_form = decltype(tanh_c)::value;
-#pragma unroll
-        for (int t = 0; t < CH; ++t) {
-          f32x4 w = v[t];
-          if constexpr (EPI == EPI_SWIGLU) {
-            if (ok[t]) {
-              bf16_t* aux = static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux;
-              const u32x2 pg = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-              const u32x2 pu = {pack_bf16(u[t][0], u[t][1]), pack_bf16(u[t][2], u[t][3])};
-              *reinterpret_cast<u32x2*>(aux + col) = pg;
-              *reinterpret_cast<u32x2*>(aux + p.n_split + col) = pu;
-              f32x4 o;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o[e] = w[e] * sigmoid_f(w[e]) * u[t][e];
-              const u32x2 po = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
-              *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + col) = po;
-            }
-          } else if constexpr (EPI == EPI_ACC_F32) {
-            if (p.beta) w += old[t];
-            if (ok[t]) *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + mrow[t] * p.ldc + n) = w;
-          } else if constexpr (EPI == EPI_ROPE) {
-            f32x4 hi = u[t];
-            if (rot) {
-              const float pos = (float)(int)(mrow[t] % p.rope_seq);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                float sn, cs;
-                rope_sincos(pos, rfreq[e], &sn, &cs);
-                const float a = w[e], b = hi[e];
-                w[e] = a * cs - b * sn;
-                hi[e] = b * cs + a * sn;
-              }
-            }
-            if (ok[t]) {
-              bf16_t* crow = static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n;
-              const u32x2 plo = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-              const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
-              *reinterpret_cast<u32x2*>(crow) = plo;
-              *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
-            }
-          } else {
-            w += bias4;
-            if constexpr (EPI == EPI_BIAS_GELU) {
-              const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-              if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux + n) = pp;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) w[e] = gelu_f(w[e], tanh_form);
-            } else if constexpr (EPI == EPI_DGELU) {
-              w[0] *= gelu_grad_f(bf16_lo(sa[t][0]), tanh_form); w[1] *= gelu_grad_f(bf16_hi(sa[t][0]), tanh_form);
-              w[2] *= gelu_grad_f(bf16_lo(sa[t][1]), tanh_form); w[3] *= gelu_grad_f(bf16_hi(sa[t][1]), tanh_form);
-            } else if constexpr (EPI == EPI_DSWIGLU) {
-              const float gv[4] = {bf16_lo(sa[t][0]), bf16_hi(sa[t][0]), bf16_lo(sa[t][1]), bf16_hi(sa[t][1])};
-              const float uv[4] = {bf16_lo(sb[t][0]), bf16_hi(sb[t][0]), bf16_lo(sb[t][1]), bf16_hi(sb[t][1])};
-              f32x4 du;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float sg = sigmoid_f(gv[e]);
-                du[e] = w[e] * gv[e] * sg;                                   // d_act * silu(g)
-                w[e] = w[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));     // d_act * u * silu'(g)
-              }
-              const u32x2 pdu = {pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
-              if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + p.n_split + n) = pdu;
-            }
-            const u32x2 po = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-            if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n) = po;
-          }
-        }
-      };
-      if constexpr (EPI == EPI_BIAS_GELU || EPI == EPI_DGELU) {
-        if (p.gelu_tanh) finish(std::true_type{}); else finish(std::false_type{});
-      } else {
-        finish(std::true_type{});
-      }
-    }
+    store_rows<BN, WN, EPI, 32, false>(p, ec, wbuf, m0 + wm0 + j * 32);
   });
+}
+
+// Products of few tiles: one workgroup of eight waves per 64x64 tile, the contraction dealt over the waves (wave w takes
+// the 64-deep operand tiles w, w + 8, ...), their sums added in wave order through LDS.  Such launches are bound by the
+// serial chain of loads along the contraction, not by any unit's rate: eight chains run side by side here, each wave
+// stages its own operand tiles (no barrier in the loop), and a tile's loads are in flight while the wave's MFMAs on the
+// one before run.  A wave's fragments of both steps sit in registers, so its one stage is free as soon as they are read.
+constexpr int SPLIT_WAVES = 8;
+constexpr int SPLIT_STAGE = 64 * epi_row_bytes(64);      // a wave's LDS: two operand tiles of 8 KiB, its 64x64 sums afterwards
+template <bool AKS, bool BKS, int EPI>
+DEV void gemm_split_body(const GemmArgs& p, const int lin) {
+  constexpr int T4 = 4, TILE = 64 * BK * 2;
+  static_assert(SPLIT_STAGE >= 2 * TILE && SPLIT_STAGE % 1024 == 0, "stage");
+  extern __shared__ __align__(1024) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int band = lin / (p.group_m * p.tiles_n), inband = lin % (p.group_m * p.tiles_n);
+  const int gm = min(p.group_m, p.tiles_m - band * p.group_m);
+  const int tm = band * p.group_m + inband % gm, tn = inband / gm;
+  const int m0 = tm * 64, n0 = tn * 64;
+
+  TileLoader<64, 1, AKS> ldA;
+  TileLoader<64, 1, BKS> ldB;
+  ldA.init(p.A, p.a_bytes, (int)p.lda, p.K, IdentityCols{m0, p.M}, m0, p.M, 0, lane);
+  if constexpr (EPI == EPI_SWIGLU) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, GluCols{tn * 32, p.n_split}, n0, p.N, 0, lane);
+  else if constexpr (EPI == EPI_ROPE) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, RopeCols{n0, p.N, p.rope_d}, n0, p.N, 0, lane);
+  else ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, IdentityCols{n0, p.N}, n0, p.N, 0, lane);
+  ldA.advance(wave);
+  ldB.advance(wave);
+  uint8_t* const stage = smem + wave * SPLIT_STAGE;
+  auto fill = [&] {
+    const buf_rsrc ra = ldA.rsrc(), rb = ldB.rsrc();
+    const bool ia = ldA.inside(), ib = ldB.inside();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ldA.issue(i, ra, ia, stage, 0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ldB.issue(i, rb, ib, stage + TILE, 0);
+    ldA.advance(SPLIT_WAVES);
+    ldB.advance(SPLIT_WAVES);
+  };
+
+  f32x4 acc[T4][T4];
+#pragma unroll
+  for (int i = 0; i < T4; ++i)
+#pragma unroll
+    for (int j = 0; j < T4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t offA[AKS ? T4 : 1], offB[BKS ? T4 : 1];
+  const uint32_t lds_a = lds_addr(stage), lds_b = lds_a + TILE;
+#pragma unroll
+  for (int j = 0; j < (AKS ? T4 : 1); ++j) offA[j] = lds_a + (AKS ? ks_frag_off16<64>(lane, j) : kc_frag_off16(lane));
+#pragma unroll
+  for (int i = 0; i < (BKS ? T4 : 1); ++i) offB[i] = lds_b + (BKS ? ks_frag_off16<64>(lane, i) : kc_frag_off16(lane));
+
+  const int nk = (p.K + BK - 1) / BK;
+  if (wave < nk) fill();
+  for (int kt = wave; kt < nk; kt += SPLIT_WAVES) {
+    u32x4 fa[2][AKS ? 1 : T4], fb[2][BKS ? 1 : T4];
+    u32x2 ha[2][AKS ? T4 : 1][2], hb[2][BKS ? T4 : 1][2];
+    wait_vmcnt<0>();
+    static_for<0, 2>([&](auto sc) {
+      constexpr int s = decltype(sc)::value;
+      static_for<0, T4>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        if constexpr (AKS) {
+          ha[s][r][0] = ds_read_tr_at<s * 32 * 128>(offA[r]);
+          ha[s][r][1] = ds_read_tr_at<(s * 32 + 4) * 128>(offA[r]);
+        } else {
+          fa[s][r] = ds_read_b128_at<r * 2048>(lds_a + ((offA[0] - lds_a) ^ (s << 6)));
+        }
+        if constexpr (BKS) {
+          hb[s][r][0] = ds_read_tr_at<s * 32 * 128>(offB[r]);
+          hb[s][r][1] = ds_read_tr_at<(s * 32 + 4) * 128>(offB[r]);
+        } else {
+          fb[s][r] = ds_read_b128_at<r * 2048>(lds_b + ((offB[0] - lds_b) ^ (s << 6)));
+        }
+      });
+    });
+    lds_wait<0>();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int r = 0; r < T4; ++r) {
+        if constexpr (AKS) { tie(ha[s][r][0]); tie(ha[s][r][1]); } else tie(fa[s][r]);
+        if constexpr (BKS) { tie(hb[s][r][0]); tie(hb[s][r][1]); } else tie(fb[s][r]);
+      }
+    if (kt + SPLIT_WAVES < nk) fill();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < T4; ++i)
+#pragma unroll
+        for (int j = 0; j < T4; ++j) {
+          u32x4 a, b;
+          if constexpr (AKS) a = u32x4{ha[s][j][0][0], ha[s][j][0][1], ha[s][j][1][0], ha[s][j][1][1]}; else a = fa[s][j];
+          if constexpr (BKS) b = u32x4{hb[s][i][0][0], hb[s][i][0][1], hb[s][i][1][0], hb[s][i][1][1]}; else b = fb[s][i];
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), acc[i][j], 0, 0, 0);
+        }
+  }
+  // the sums replace the wave's own operand tiles; then every wave stores 8 rows of the tile
+  constexpr int ROWB = epi_row_bytes(64);
+  if (wave < nk) {
+#pragma unroll
+    for (int i = 0; i < T4; ++i)
+#pragma unroll
+      for (int j = 0; j < T4; ++j)
+        *reinterpret_cast<f32x4*>(stage + (16 * j + (lane & 15)) * ROWB + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][j];
+  }
+  __syncthreads();
+  const EpiCols<64, 64, EPI> ec(p, tn, n0, 0, lane);
+  store_rows<64, 64, EPI, 8, true>(p, ec, smem + wave * 8 * ROWB, m0 + wave * 8, min(nk, SPLIT_WAVES), SPLIT_STAGE);
 }
 
 // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): every XCD gets one contiguous chunk of the tile
@@ -451,17 +598,21 @@ DEV int tile_of_block(int T) {
   return (blockIdx.x & 7) * ((T + 7) >> 3) + (blockIdx.x >> 3);
 }
 
+constexpr int gemm_threads(int BM, int BN, int WM, int WN) { return BM == 64 ? SPLIT_WAVES * 64 : (BM / WM) * (BN / WN) * 64; }
+
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, BM * BN > 128 * 128 ? 1 : 2)
+__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 ? 2 : 1)
 void gemm_kernel(const GemmArgs p) {
   const int T = p.tiles_m * p.tiles_n, lin = tile_of_block(T);
-  if (lin < T) gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p, lin);
+  if (lin >= T) return;
+  if constexpr (BM == 64) gemm_split_body<AKS, BKS, EPI>(p, lin);
+  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p, lin);
 }
 
 // Several weight gradients of one block in one launch: alone, each leaves part of the chip idle (the 13B shard's are 200,
 // 200, 60 and 160 tiles of 256x256 on 256 compute units), and a small block pays mostly for the launches.
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, BM * BN > 128 * 128 ? 1 : 2)
+__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 ? 2 : 1)
 void gemm_group_kernel(const GemmGroup p) {
   const int T = p.first[GEMM_GROUP], lin = tile_of_block(T);
   if (lin >= T) return;
@@ -469,7 +620,8 @@ void gemm_group_kernel(const GemmGroup p) {
 #pragma unroll
   for (int k = 1; k < GEMM_GROUP; ++k)
     if (lin >= p.first[k]) i = k;
-  gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p.g[i], lin - p.first[i]);
+  if constexpr (BM == 64) gemm_split_body<AKS, BKS, EPI>(p.g[i], lin - p.first[i]);
+  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p.g[i], lin - p.first[i]);
 }
 
 // fills what the kernel needs to know about the tiles; false: an operand reaches 2 GiB
@@ -486,8 +638,8 @@ bool plan_tiles(GemmArgs& a) {
 
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
-  constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  constexpr int LDS = (RING_A * BM + RING_B * BN) * BK * 2;
+  constexpr int NT = gemm_threads(BM, BN, WM, WN);
+  constexpr int LDS = BM == 64 ? SPLIT_WAVES * SPLIT_STAGE : (RING_A * BM + RING_B * BN) * BK * 2;
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
   if (n > 1) {
     if constexpr (EPI == EPI_ACC_F32) {
@@ -524,6 +676,7 @@ hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t str
     case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_64x64:   return launch_cfg<64, 64, 64, 64, AKS, BKS, EPI>(a, n, stream);
     default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, n, stream);
   }
 }
@@ -534,32 +687,44 @@ thread_local int g_nheld = 0;
 
 }  // namespace
 
-static int pick_tile(const GemmArgs* products, int n, bool swiglu, int concurrency) {
-  // Time of a launch = rounds of tiles on 256 compute units x time of a tile.  A compute unit's rate on each tile
-  // shape (TFLOP/s, measured on the products of the 13B shard: 5120 deep, 160 to 640 tiles) grows with the flops per
-  // operand byte; 128x128 tiles run two to a unit (4.9 between them, 3.8 when one is alone), the others alone.
-  // A launch with nothing beside it pays for its last round in full; beside three or more others of its size only the
-  // work and the padding of ragged edges count, the other launches fill the rest; beside one other, half way between.
+// Time of a launch that has the chip to itself = 3 us + rounds of tiles on 256 compute units x time of a tile; time of a
+// tile = what its start and its epilogue take + what 64 elements of the contraction take (us; fitted to 77 shapes of 128 to
+// 4096 rows, 640 to 7168 columns, 256 to 16384 deep).  128x128 tiles run two to a unit; one that is alone is faster.
+// A launch beside three or more others of its size pays for the work and the padding of ragged edges only, the other
+// launches fill the rest of its last round; beside one other, half way between.
+// 64x64 tiles deal the contraction over eight waves and sum in another order than the rest: whether they are taken
+// is decided as if nothing ran beside the launch, so that no bit of a result depends on the stream pool.  They win where
+// the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep 41 -> 19 us, 240 x 2688 x 7168
+// 55 -> 24, 256 x 1024 x 1024 10.0 -> 6.5; at 1024 x 2560 x 5120 the two forms meet.
+static int pick_tile(const GemmArgs* products, int n, int layout, int epi, int concurrency) {
   if (concurrency < 1) concurrency = 1;
-  struct Cand { int id, bm, bn; double rate; };
-  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 6.0}, {GEMM_TILE_256x128, 256, 128, 5.5},
-                               {GEMM_TILE_128x256, 128, 256, 5.3}, {GEMM_TILE_128x128, 128, 128, 4.9}};
-  int best = GEMM_TILE_128x128;
-  double best_cost = 1e30;
-  for (const Cand& c : cands) {
-    double tiles = 0;
+  const bool swiglu = epi == EPI_SWIGLU;
+  // fixed: without / with fp32 sums to store
+  struct Cand { int id, bm, bn; double fixed[2], per64; };
+  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, {8.0, 16.0}, 1.06}, {GEMM_TILE_256x128, 256, 128, {4.0, 8.0}, 0.67},
+                               {GEMM_TILE_128x256, 128, 256, {4.0, 8.0}, 0.70}, {GEMM_TILE_128x128, 128, 128, {1.5, 2.9}, 0.40}};
+  const int f32 = layout == GEMM_TN;
+  auto tiles_of = [&](int bm, int bn) {
+    double t = 0;
     for (int i = 0; i < n; ++i) {
       const int N = swiglu ? 2 * products[i].n_split : products[i].N;
-      tiles += (double)((products[i].M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+      t += (double)((products[i].M + bm - 1) / bm) * ((N + bn - 1) / bn);
     }
-    const double unit = (double)c.bm * c.bn / c.rate;
+    return t;
+  };
+  const int it = (products[0].K + BK - 1) / BK;      // a group's products share the contraction
+  int best = GEMM_TILE_128x128;
+  double best_cost = 1e30, best_alone = 1e30;
+  for (const Cand& c : cands) {
+    const double tiles = tiles_of(c.bm, c.bn), unit = c.fixed[f32] + c.per64 * it;
     double alone;
     if (c.id == GEMM_TILE_128x128) {
-      const double lone = (double)c.bm * c.bn / 3.8, full = floor(tiles / 512), rest = tiles - 512 * full;
+      const double lone = c.fixed[f32] + 0.5 + 0.47 * it, full = floor(tiles / 512), rest = tiles - 512 * full;
       alone = full * 2 * unit + (rest == 0 ? 0.0 : rest <= 256 ? lone : 2 * unit);
     } else {
       alone = ceil(tiles / 256) * unit;
     }
+    best_alone = alone < best_alone ? alone : best_alone;
     // a launch of few tiles is a long serial kernel on its stream, and the other launches in flight do not always fill
     // the chip beside it: it is charged for leaving more than three eighths of its share of the chip unused
     const double share = 160.0 / concurrency;
@@ -567,13 +732,8 @@ static int pick_tile(const GemmArgs* products, int n, bool swiglu, int concurren
     const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.5 * (alone + shared) : shared;
     if (cost < best_cost * 0.999) { best_cost = cost; best = c.id; }
   }
-  return best;
-}
-
-int gemm_pick_tile(int M, int N, int concurrency) {
-  GemmArgs a{};
-  a.M = M; a.N = N;
-  return pick_tile(&a, 1, false, concurrency);
+  const double split = ceil(tiles_of(64, 64) / 256) * (1.8 + 1.4 * ((it + SPLIT_WAVES - 1) / SPLIT_WAVES));
+  return 3 + split < 0.95 * (3 + best_alone) ? GEMM_TILE_64x64 : best;
 }
 
 hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hipStream_t stream) {
@@ -593,7 +753,7 @@ hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hi
     if (a0.join) return hipSuccess;
     a = g_held; n = g_nheld; g_nheld = 0;
   }
-  if (tile_cfg < 0) tile_cfg = pick_tile(a, n, epi == EPI_SWIGLU, a->concurrency);
+  if (tile_cfg < 0) tile_cfg = pick_tile(a, n, layout, epi, a->concurrency);
   if (layout == GEMM_NN) {
     switch (epi) {
       case EPI_STORE:     return launch_layout<false, true, EPI_STORE>(a, n, tile_cfg, stream);

@@ -3,7 +3,8 @@
 #include <hip/hip_runtime.h>
 
 constexpr int NORM_BWD_MAX_BLOCKS = 256;   // one partial row of d gamma / d beta per workgroup
-constexpr int NORM_BWD_ROWS = 16;          // rows per workgroup until the block limit is reached
+constexpr int NORM_BWD_ROWS = 16;          // rows per workgroup until the block limit is reached ...
+constexpr int NORM_BWD_FEW = 64;           // ... but down to 4 each while that makes no more than this many workgroups
 constexpr int COLSUM_PARTS = 64;           // row ranges of the first column-sum stage
 
 struct NormFwdArgs {
@@ -48,7 +49,10 @@ hipError_t colsum_finish_launch(const float* part, int nparts, int n, float* out
 // partial rows (stride floats apart), group by group
 constexpr int COLSUM_MAX_JOBS = 8;
 struct ColsumJob { const float* part; float* out; int nparts, n; long stride; int nouter; long ostride; };
-struct ColsumJobs { ColsumJob job[COLSUM_MAX_JOBS]; };
+struct ColsumJobs {
+  ColsumJob job[COLSUM_MAX_JOBS];
+  int join;      // 1: hold these jobs back until the next call (same stream), which continues them with the groups behind theirs
+};
 hipError_t colsum_finish_jobs_launch(const ColsumJobs& jobs, int njobs, int accumulate, hipStream_t st);
 // part[COLSUM_PARTS][n] = partial column sums of the bf16 matrix g[rows][ld]
 hipError_t colsum_partial_launch(const void* g, long ld, int rows, int n, float* part, hipStream_t st);

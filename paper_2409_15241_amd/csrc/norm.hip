@@ -298,24 +298,51 @@ void colsum_finish_kernel(const ColsumJobs jobs, int accumulate) {
   }
 }
 
-// part[blockIdx.y][col] = sum over this block's row range of g[row][col] (bf16 in, fp32 out).
-__global__ __launch_bounds__(64)
+// part[blockIdx.y][col] = sum over this block's row range of g[row][col] (bf16 in, fp32 out).  HBM-bound: a workgroup owns
+// 512 columns, its four waves take every fourth row of the range with eight 1-KiB loads in flight each, and the wave sums
+// are added in wave order through LDS.  (One wave per workgroup and four loads in flight read 16384 x 1280 at 1.4 TB/s.)
+__global__ __launch_bounds__(256)
 void colsum_partial_kernel(const bf16_t* __restrict__ g, long ld, int rows, int n, float* __restrict__ part) {
-  const int chunk = blockIdx.x * 64 + threadIdx.x;      // 8 columns
-  if (chunk * 8 >= n) return;
+  __shared__ __align__(16) float red[3][512];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int chunk = blockIdx.x * 64 + lane;             // 8 columns
+  const bool live = chunk * 8 < n;
+  const bf16_t* at = g + (live ? chunk : 0) * 8;
   const int per = (rows + gridDim.y - 1) / gridDim.y;
   const int r0 = blockIdx.y * per, r1 = min(rows, r0 + per);
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll 4
-  for (int r = r0; r < r1; ++r) {
+  int r = r0 + wave;
+  for (; r + 28 < r1; r += 32) {
+    u32x4 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const u32x4*>(at + (long)(r + 4 * k) * ld);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      float f[8];
+      unpack8(v[k], f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += f[e];
+    }
+  }
+  for (; r < r1; r += 4) {
     float f[8];
-    unpack8(*reinterpret_cast<const u32x4*>(g + (long)r * ld + chunk * 8), f);
+    unpack8(*reinterpret_cast<const u32x4*>(at + (long)r * ld), f);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += f[e];
   }
-  float* o = part + (long)blockIdx.y * n + chunk * 8;
+  if (wave) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = acc[e];
+    for (int e = 0; e < 8; e += 4) *reinterpret_cast<f32x4*>(&red[wave - 1][lane * 8 + e]) = f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+  }
+  __syncthreads();
+  if (wave || !live) return;
+#pragma unroll
+  for (int w = 0; w < 3; ++w)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += red[w][lane * 8 + e];
+  f32x4* o = reinterpret_cast<f32x4*>(part + (long)blockIdx.y * n + chunk * 8);
+  o[0] = f32x4{acc[0], acc[1], acc[2], acc[3]};
+  o[1] = f32x4{acc[4], acc[5], acc[6], acc[7]};
 }
 
 template <bool RMS>
@@ -345,8 +372,13 @@ hipError_t bwd_dispatch(const NormBwdArgs& a, hipStream_t st) {
 
 }  // namespace
 
+// Each workgroup walks its rows one after the other and leaves a partial row per gradient vector: 16 rows keep that
+// traffic below a tenth of the kernel's, and a few hundred rows are spread further while the chip has room (400 rows of
+// 1024: 25 workgroups took 10.9 us, nearly all of it the serial walk).
 int norm_bwd_blocks(int rows) {
-  const int want = (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
+  int want = (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
+  const int fine = (rows + 3) / 4;
+  if (want < NORM_BWD_FEW) want = fine < NORM_BWD_FEW ? fine : NORM_BWD_FEW;
   return want < NORM_BWD_MAX_BLOCKS ? want : NORM_BWD_MAX_BLOCKS;
 }
 
@@ -369,9 +401,36 @@ hipError_t colsum_finish_launch(const float* part, int nparts, int n, float* out
   return colsum_finish_jobs_launch(jobs, 1, accumulate, st);
 }
 
-hipError_t colsum_finish_jobs_launch(const ColsumJobs& jobs, int njobs, int accumulate, hipStream_t st) {
+namespace {
+// jobs held back for the next call (ColsumJobs::join)
+thread_local ColsumJobs t_held;
+thread_local int t_nheld = 0, t_accumulate = 0;
+}  // namespace
+
+hipError_t colsum_finish_jobs_launch(const ColsumJobs& jobs0, int njobs, int accumulate, hipStream_t st) {
   if (njobs <= 0) return hipSuccess;
   if (njobs > COLSUM_MAX_JOBS) return hipErrorInvalidValue;
+  ColsumJobs jobs = jobs0;
+  if (t_nheld) {
+    ColsumJobs held = t_held;
+    const int nheld = t_nheld;
+    t_nheld = 0;
+    for (int k = 0; k < njobs; ++k) {           // every job must lengthen a held one
+      int h = 0;
+      while (h < nheld && held.job[h].out != jobs.job[k].out) ++h;
+      if (h == nheld || !accumulate) return hipErrorInvalidValue;
+      ColsumJob& j = held.job[h];
+      const ColsumJob& more = jobs.job[k];
+      if (j.n != more.n || j.nparts != more.nparts || j.stride != more.stride || j.ostride != more.ostride ||
+          j.part + j.nouter * j.ostride != more.part) return hipErrorInvalidValue;
+      j.nouter += more.nouter;
+    }
+    jobs = held; njobs = nheld; accumulate = t_accumulate;
+  }
+  if (jobs0.join) {
+    t_held = jobs; t_nheld = njobs; t_accumulate = accumulate;
+    return hipSuccess;
+  }
   int widest = 0;
   for (int k = 0; k < njobs; ++k) widest = jobs.job[k].n > widest ? jobs.job[k].n : widest;
   hipLaunchKernelGGL(colsum_finish_kernel, dim3((widest + 31) / 32, njobs), dim3(256), 0, st, jobs, accumulate);
@@ -379,7 +438,7 @@ hipError_t colsum_finish_jobs_launch(const ColsumJobs& jobs, int njobs, int accu
 }
 
 hipError_t colsum_partial_launch(const void* g, long ld, int rows, int n, float* part, hipStream_t st) {
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((n / 8 + 63) / 64, COLSUM_PARTS), dim3(64), 0, st,
+  hipLaunchKernelGGL(colsum_partial_kernel, dim3((n / 8 + 63) / 64, COLSUM_PARTS), dim3(256), 0, st,
                      static_cast<const bf16_t*>(g), ld, rows, n, part);
   return hipGetLastError();
 }

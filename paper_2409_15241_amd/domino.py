@@ -143,11 +143,10 @@ def _check(rc: int) -> None:
 
 
 def _ptr(t) -> Optional[int]:
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
-    assert t.is_contiguous() or t.dim() == 2, "tensors must be contiguous (or 2-D row-strided views)"
+    if not t.is_contiguous():
+        assert t.dim() == 2, "tensors must be contiguous (or 2-D row-strided views)"
     return t.data_ptr()
 
 
@@ -158,8 +157,8 @@ def _stream(s) -> Optional[int]:
 
 
 def _streams(streams: Sequence):
-    arr = (C.c_void_p * len(streams))(*[_stream(s) for s in streams])
-    return arr, len(streams)
+    n = len(streams)
+    return (C.c_void_p * n)(*[_stream(s) for s in streams]), n
 
 
 def make_cfg(sc=None, **kw) -> domino_cfg:
@@ -179,7 +178,8 @@ def make_cfg(sc=None, **kw) -> domino_cfg:
 
 
 def _params_struct(cls, tensors: Dict[str, object]):
-    return cls(**{n: _ptr(tensors.get(n)) for n in PARAM_NAMES})
+    get = tensors.get
+    return cls(*[_ptr(get(n)) for n in PARAM_NAMES])
 
 
 # --------------------------------------------------------------------------- layout queries
@@ -226,7 +226,7 @@ def domino_layer_fwd(cfg, params, x, attn_others, mlp_others, attn_partial, mlp_
                      saved, workspace, streams) -> None:
     arr, n = _streams(streams)
     ps = _params_struct(domino_params, params)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().domino_layer_fwd(C.byref(cfg), C.byref(ps), _ptr(x), _ptr(attn_others), _ptr(mlp_others),
                                    _ptr(attn_partial), _ptr(mlp_partial), _ptr(y), _ptr(saved), _ptr(workspace),
                                    ws_bytes, arr, n))
@@ -237,7 +237,7 @@ def domino_layer_bwd(cfg, params, saved, x, dy, dln2_others, dln1_others, dln2_p
     arr, n = _streams(streams)
     ps = _params_struct(domino_params, params)
     gs = _params_struct(domino_grads, grads)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().domino_layer_bwd(C.byref(cfg), C.byref(ps), _ptr(saved), _ptr(x), _ptr(dy), _ptr(dln2_others),
                                    _ptr(dln1_others), _ptr(dln2_partial), _ptr(dln1_partial), _ptr(dx),
                                    C.byref(gs), int(accumulate), _ptr(workspace), ws_bytes, arr, n))
@@ -247,7 +247,7 @@ def domino_layer_fwd_parts(cfg, params, x, attn_others, mlp_others, attn_partial
                            saved, workspace, streams, parts) -> None:
     arr, n = _streams(streams)
     ps = _params_struct(domino_params, params)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().domino_layer_fwd_parts(C.byref(cfg), C.byref(ps), _ptr(x), _ptr(attn_others), _ptr(mlp_others),
                                          _ptr(attn_partial), _ptr(mlp_partial), _ptr(y), _ptr(saved),
                                          _ptr(workspace), ws_bytes, arr, n, int(parts)))
@@ -258,7 +258,7 @@ def domino_layer_bwd_parts(cfg, params, saved, x, dy, dln2_others, dln1_others, 
     arr, n = _streams(streams)
     ps = _params_struct(domino_params, params)
     gs = _params_struct(domino_grads, grads)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().domino_layer_bwd_parts(C.byref(cfg), C.byref(ps), _ptr(saved), _ptr(x), _ptr(dy),
                                          _ptr(dln2_others), _ptr(dln1_others), _ptr(dln2_partial),
                                          _ptr(dln1_partial), _ptr(dx), C.byref(gs), int(accumulate),
@@ -271,7 +271,7 @@ def domino_stack_workspace_bytes(cfg: domino_cfg, nlayers: int) -> int:
 
 
 def _struct_array(cls, fields, dicts):
-    return (cls * len(dicts))(*[cls(**{n: _ptr(d.get(n)) for n in fields}) for d in dicts])
+    return (cls * len(dicts))(*[cls(*[_ptr(d.get(n)) for n in fields]) for d in dicts])
 
 
 def _params_array(cls, dicts):
@@ -281,7 +281,7 @@ def _params_array(cls, dicts):
 def domino_stack_fwd(cfg, params, x, io, workspace, streams) -> None:
     """params: one dict of the twelve tensors per block; io: one dict per block keyed by STACK_FWD_FIELDS."""
     arr, n = _streams(streams)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().domino_stack_fwd(C.byref(cfg), len(params), _params_array(domino_params, params), _ptr(x),
                                    _struct_array(domino_stack_fwd_io, STACK_FWD_FIELDS, io), _ptr(workspace),
                                    ws_bytes, arr, n))
@@ -290,7 +290,7 @@ def domino_stack_fwd(cfg, params, x, io, workspace, streams) -> None:
 def domino_stack_bwd(cfg, params, dy, io, dx, grads, accumulate, workspace, streams) -> None:
     """io: one dict per block keyed by STACK_BWD_FIELDS; grads: one dict of fp32 tensors per block."""
     arr, n = _streams(streams)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(load().domino_stack_bwd(C.byref(cfg), len(params), _params_array(domino_params, params), _ptr(dy),
                                    _struct_array(domino_stack_bwd_io, STACK_BWD_FIELDS, io), _ptr(dx),
                                    _params_array(domino_grads, grads), int(accumulate), _ptr(workspace), ws_bytes,
