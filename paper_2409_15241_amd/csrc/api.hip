@@ -102,14 +102,15 @@ std::atomic<bool> g_prof_on{false};      // per-launch timing (domino_profile_en
 int tiles256(long m, long n) { return (int)((m + 255) / 256 * ((n + 255) / 256)); }
 int wgrad_tiles(const Layout& l) { return tiles256(l.fl, l.h) + tiles256(l.h, l.upc) + tiles256(l.hl, l.h) + tiles256(l.h, 3 * l.hl); }
 
-// The backward's weight gradients run on a stream of their own where their tiles fill the 256 compute units more than
-// once: then they fill what the chain of input gradients, attention and norms leaves idle.  Below that they follow on the
+// The backward's weight gradients run on a stream of their own where their tiles fill most of the 256 compute units or
+// more: then they fill what the chain of input gradients, attention and norms leaves idle.  Below that they follow on the
 // chain's stream as one launch, which has the chip to itself (24000 tokens of a 1536-wide shard, 63 tiles: 1231 against
-// 1666 us; GPT-3 2.7B, 160 tiles: 1646 against 1710; 13B, 620 tiles: 2283 against 2202).  The second stream also costs a
+// 1666 us; GPT-3 2.7B, 160 tiles: 1646 against 1710; a 3072-wide
+// Llama shard, 228 tiles: 828 against 801; 13B, 620 tiles: 2283 against 2202).  The second stream also costs a
 // call about 100 us of host time (event records and waits) and 5 to 10 us at each of its edges on the GPU, whatever the
 // block's size: blocks under 40 GFLOP of weight gradients (half of 13B's at 512 tokens) keep to one.
 bool wgrads_beside(const Layout& l) {
-  return wgrad_tiles(l) > 256 && 2.0 * l.M * l.h * (4.0 * l.hl + l.upc + l.fl) >= 40e9;
+  return wgrad_tiles(l) > 200 && 2.0 * l.M * l.h * (4.0 * l.hl + l.upc + l.fl) >= 40e9;
 }
 
 // Row slices cut the batch so that a program can reduce one slice's partial sums over the ranks while the next slice
@@ -592,6 +593,7 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
       const size_t r0 = (size_t)i * K;
       GemmArgs a = gemm_args(at(w.A, r0 * w.lda * 2), w.lda, at(w.Bm, r0 * w.ldb * 2), w.ldb, w.C, w.N, w.M, w.N, K);
       a.beta = (i > 0 || B.accumulate) ? 1 : 0;
+      a.beside = L.beside;
       a.join = !L.per_slice && (m < n - 1 || i < slices - 1) ? 1 : 0;
       LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
     }
@@ -743,9 +745,12 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       return norm_bwd(R, st, at(B.dln2_partial, R.rh), B.dln2_others ? at(B.dln2_others, R.rh) : nullptr, at(saved, L.x1 + R.rh),
                       P->norm2_g, L.mean2, L.rstd2, at(B.dy, R.rh), dx1(R), AREA_G2, AREA_B2, L.llama ? -1 : AREA_BDOWN, L.llama ? -1 : AREA_BO);
     }));
-    if (S.side) {        // beside the attention backward, which leaves the matrix cores idle most of the time
+    if (S.side) {
+      // one group: beside the attention backward, which leaves the matrix cores idle most of the time; two groups leave
+      // little idle there, and the few tiles of the out-projection then share a launch with QKV's (2826 -> 2694 us for
+      // 16384 tokens of Llama-2 7B; 13B equal; 2048 tokens of 13B in one group 701 -> 708)
       TRY(behind_groups(side));
-      TRY(form({WG_OUT}, side));
+      if (L.groups == 1) TRY(form({WG_OUT}, side));
       TRY(vector_gradients(L, B, VEC_MLP, side));
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B6
@@ -768,7 +773,8 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }));
     if (S.side) {
       TRY(behind_groups(side));
-      TRY(form({WG_QKV}, side));
+      if (L.groups == 1) TRY(form({WG_QKV}, side));
+      else TRY(form({WG_OUT, WG_QKV}, side));
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
       // B8: input gradient of QKV: the tensor the fourth all-reduce would sum

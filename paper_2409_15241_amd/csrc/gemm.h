@@ -28,6 +28,7 @@ struct GemmArgs {
   float rope_log2_base;
   int gelu_tanh;
   int concurrency;       // launches of similar size expected in flight at once (other streams); 0 = 1
+  int beside;            // 1: meant to fill what other launches leave idle, so not with 64x64 tiles, which take the whole chip
   int join;              // EPI_ACC_F32: 1 = hold this product back, it is launched together with the next call's (see gemm_launch)
   int tiles_m, tiles_n;  // filled by the launcher
   int group_m;           // filled by the launcher: tile rows per band of the tile order

@@ -732,6 +732,7 @@ static int pick_tile(const GemmArgs* products, int n, int layout, int epi, int c
     const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.5 * (alone + shared) : shared;
     if (cost < best_cost * 0.999) { best_cost = cost; best = c.id; }
   }
+  if (products[0].beside) return best;
   const double split = ceil(tiles_of(64, 64) / 256) * (1.8 + 1.4 * ((it + SPLIT_WAVES - 1) / SPLIT_WAVES));
   return 3 + split < 0.95 * (3 + best_alone) ? GEMM_TILE_64x64 : best;
 }
