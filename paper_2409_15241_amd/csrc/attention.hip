@@ -377,40 +377,38 @@ DEV uint32_t rm_trans_off(int lane) {
   return (uint32_t)(posl * 256 + (h << 4) + 8 * (sl & 1));
 }
 
-// acc[t] += Tile[32 t + lane%32, d] * frag[d, lane] over all d, batches of 4 steps with the next batch's
-// reads in flight.  tile_addr = LDS byte address of the row-major tile, off = rm_plain_off(lane).
-template <int D>
-DEV void rm_mma_rows(uint32_t tile_addr, uint32_t off, const bf16x8 (&f)[Dims<D>::KSTEPS], f32x16 (&acc)[2]) {
+// Both row products of 32 tile positions: accA += TileA[32 t + lane%32, d] * fa[d, lane] and accB likewise, over all d, in
+// batches of a few steps with the next batch's reads in flight; the two chains of MFMAs alternate.  off = rm_plain_off(lane).
+template <int D, int T>
+DEV void rm_mma_rows(uint32_t tile_a, uint32_t tile_b, uint32_t off, const bf16x8 (&fa)[Dims<D>::KSTEPS], const bf16x8 (&fb)[Dims<D>::KSTEPS],
+                     f32x16& acc_a, f32x16& acc_b) {
   using X = Dims<D>;
-  constexpr int NB = (X::KSTEPS + 3) / 4;
-  u32x4 fr[2][4][2];
+  constexpr int BS = D == 128 ? 4 : 2, NB = (X::KSTEPS + BS - 1) / BS;
+  u32x4 fr[2][BS][2];
   auto read_batch = [&](auto bb) {
     constexpr int B = decltype(bb)::value;
-    static_for<0, 4>([&](auto kk) {
-      constexpr int KS = B * 4 + decltype(kk)::value;
+    static_for<0, BS>([&](auto kk) {
+      constexpr int KS = B * BS + decltype(kk)::value;
       if constexpr (KS < X::KSTEPS) {
-        const uint32_t a = tile_addr + (off ^ (KS << 5));
-        fr[B & 1][decltype(kk)::value][0] = ds_read_b128_at<0>(a);
-        fr[B & 1][decltype(kk)::value][1] = ds_read_b128_at<8192>(a);
+        fr[B & 1][decltype(kk)::value][0] = ds_read_b128_at<T * 8192>(tile_a + (off ^ (KS << 5)));
+        fr[B & 1][decltype(kk)::value][1] = ds_read_b128_at<T * 8192>(tile_b + (off ^ (KS << 5)));
       }
     });
   };
   read_batch(std::integral_constant<int, 0>{});
   static_for<0, NB>([&](auto bb) {
     constexpr int B = decltype(bb)::value;
-    constexpr int LEFT = X::KSTEPS - 4 * (B + 1);
-    constexpr int NEXT = (B + 1 < NB) ? (LEFT < 4 ? LEFT : 4) * 2 : 0;
+    constexpr int LEFT = X::KSTEPS - BS * (B + 1);
+    constexpr int NEXT = (B + 1 < NB) ? (LEFT < BS ? LEFT : BS) * 2 : 0;
     if constexpr (B + 1 < NB) read_batch(std::integral_constant<int, B + 1>{});
     lds_wait<NEXT>();
-    static_for<0, 4>([&](auto kk) {
-      constexpr int KS = B * 4 + decltype(kk)::value;
+    static_for<0, BS>([&](auto kk) {
+      constexpr int K = decltype(kk)::value, KS = B * BS + K;
       if constexpr (KS < X::KSTEPS) {
-        tie(fr[B & 1][decltype(kk)::value][0]);
-        tie(fr[B & 1][decltype(kk)::value][1]);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[B & 1][decltype(kk)::value][t]),
-                                                          f[KS], acc[t], 0, 0, 0);
+        tie(fr[B & 1][K][0]);
+        tie(fr[B & 1][K][1]);
+        acc_a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[B & 1][K][0]), fa[KS], acc_a, 0, 0, 0);
+        acc_b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[B & 1][K][1]), fb[KS], acc_b, 0, 0, 0);
       }
     });
   });
@@ -425,49 +423,70 @@ DEV void pin_acc(f32x16 (&acc)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+a"(acc[i]));
 }
 
-// Two accumulators covering a tile's 64 positions, rounded to bf16 as the second operand of rm_mma_cols:
-// fragment s4 = 2 t + u holds accumulator t's values 8 u .. 8 u + 7.
-DEV void pack_acc_pair(const f32x16 (&vals)[2], bf16x8 (&pf)[4]) {
+// 16 accumulator values (32 tile positions), rounded to bf16 as the second operand of rm_mma_cols
+DEV void pack_acc(const f32x16& vals, bf16x8 (&pf)[2]) {
 #pragma unroll
-  for (int s4 = 0; s4 < 4; ++s4) {
-    const int t = s4 >> 1, u = s4 & 1;
-    u32x4 w = {pack_bf16(vals[t][8 * u + 0], vals[t][8 * u + 1]), pack_bf16(vals[t][8 * u + 2], vals[t][8 * u + 3]),
-               pack_bf16(vals[t][8 * u + 4], vals[t][8 * u + 5]), pack_bf16(vals[t][8 * u + 6], vals[t][8 * u + 7])};
-    pf[s4] = __builtin_bit_cast(bf16x8, w);
+  for (int u = 0; u < 2; ++u) {
+    const u32x4 w = {pack_bf16(vals[8 * u + 0], vals[8 * u + 1]), pack_bf16(vals[8 * u + 2], vals[8 * u + 3]),
+                     pack_bf16(vals[8 * u + 4], vals[8 * u + 5]), pack_bf16(vals[8 * u + 6], vals[8 * u + 7])};
+    pf[u] = __builtin_bit_cast(bf16x8, w);
   }
 }
 
-// out[dt] += TileT[32 dt + lane%32, pos] * pf[pos, lane]: pf = packed values covering the tile's 64
-// positions (see pack_acc_pair); off = rm_trans_off(lane).
-template <int D>
-DEV void rm_mma_cols(uint32_t tile_addr, uint32_t off, const bf16x8 (&pf)[4], f32x16 (&out)[Dims<D>::DT]) {
+// out[dt] += TileT[32 dt + lane%32, pos] * pf[pos, lane] over the 32 positions 32 T ..; off = rm_trans_off(lane).
+template <int D, int T>
+DEV void rm_mma_cols(uint32_t tile_addr, uint32_t off, const bf16x8 (&pf)[2], f32x16 (&out)[Dims<D>::DT]) {
   using X = Dims<D>;
-  u32x2 vf[2][4][2];
+  u32x2 vf[2][2][2];
   auto read_v = [&](auto dd) {
     constexpr int DTI = decltype(dd)::value;
-    static_for<0, 4>([&](auto ss) {
-      constexpr int S4 = decltype(ss)::value;
-      constexpr int OFF = (S4 >> 1) * 8192 + (S4 & 1) * 4096;
-      vf[DTI & 1][S4][0] = ds_read_tr_at<OFF>(tile_addr + (off ^ ((4 * DTI) << 4)));
-      vf[DTI & 1][S4][1] = ds_read_tr_at<OFF + 2048>(tile_addr + (off ^ (((4 * DTI) ^ 2) << 4)));
+    static_for<0, 2>([&](auto uu) {
+      constexpr int U = decltype(uu)::value, OFF = T * 8192 + U * 4096;
+      vf[DTI & 1][U][0] = ds_read_tr_at<OFF>(tile_addr + (off ^ ((4 * DTI) << 4)));
+      vf[DTI & 1][U][1] = ds_read_tr_at<OFF + 2048>(tile_addr + (off ^ (((4 * DTI) ^ 2) << 4)));
     });
   };
   read_v(std::integral_constant<int, 0>{});
   static_for<0, X::DT>([&](auto dd) {
     constexpr int DTI = decltype(dd)::value;
     if constexpr (DTI + 1 < X::DT) read_v(std::integral_constant<int, DTI + 1>{});
-    lds_wait<(DTI + 1 < X::DT) ? 8 : 0>();
+    lds_wait<(DTI + 1 < X::DT) ? 4 : 0>();
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      tie(vf[DTI & 1][s4][0]);
-      tie(vf[DTI & 1][s4][1]);
-      const u32x4 a = {vf[DTI & 1][s4][0][0], vf[DTI & 1][s4][0][1], vf[DTI & 1][s4][1][0], vf[DTI & 1][s4][1][1]};
-      out[DTI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pf[s4], out[DTI], 0, 0, 0);
+    for (int u = 0; u < 2; ++u) {
+      tie(vf[DTI & 1][u][0]);
+      tie(vf[DTI & 1][u][1]);
+      const u32x4 a = {vf[DTI & 1][u][0][0], vf[DTI & 1][u][0][1], vf[DTI & 1][u][1][0], vf[DTI & 1][u][1][1]};
+      out[DTI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pf[u], out[DTI], 0, 0, 0);
     }
   });
 }
 
 constexpr int RM_TILE = 16384;
+
+// Start of a score product over 32 tile positions: -inf where the causal mask hides the position from the lane's query or
+// key (last: the largest tile row that stays, first: the smallest), so that the product itself carries the mask.  Set here
+// and not behind the product: where a branch stood between an MFMA and the first use of its result, some results were read
+// too early.
+DEV void start_scores(f32x16& acc, bool masked, int first, int last, int fh) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  if (masked) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = acc_row(v, fh) > last || acc_row(v, fh) < first ? -INFINITY : 0.0f;
+  }
+}
+// part(masked, t) for both halves of a tile.  Heads of 128 (one wave per SIMD) keep a body without a mask; the narrower ones
+// have no registers for two bodies.
+template <int D, class Part>
+DEV void both_halves(bool diagonal, Part&& part) {
+  static_for<0, 2>([&](auto tc) {
+    if constexpr (D == 128) {
+      if (diagonal) part(std::true_type{}, tc); else part(std::false_type{}, tc);
+    } else {
+      part(diagonal, tc);
+    }
+  });
+}
 
 // ------------------------------------------------------------------------------------- dQ pass
 template <int D>
@@ -515,34 +534,32 @@ DEV void attn_bwd_dq_body(const AttnArgs& p, uint8_t* smem, int qb, int hh, int 
 
   issue_tile(0);
   for (int j = 0; j < ntiles; ++j) {
-    pin_acc(dq);
+    if constexpr (D == 128) pin_acc(dq);
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     if (j + 1 < ntiles) issue_tile(j + 1);
     const int kv0 = j * 64;
     if (kv0 > qw0 + 31) continue;
     const uint32_t st = smem_base + (j & 1) * STAGE;
-    f32x16 sT[2], dpT[2];
+    const bool diagonal = kv0 + 63 > qw0;                   // the tile meets the diagonal
+    auto part = [&](auto mc, auto tc) {                   // 32 keys at a time
+      constexpr int T = decltype(tc)::value;
+      const bool masked = mc;
+      f32x16 sT, dpT;
+      start_scores(sT, masked, 0, qpos - kv0 - 32 * T, fh);
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int v = 0; v < 16; ++v) dpT[v] = 0.0f;
+      rm_mma_rows<D, T>(st, st + RM_TILE, offP, qf, dof, sT, dpT);      // S^T = K Q^T, dP^T = V dO^T
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { sT[t][v] = 0.0f; dpT[t][v] = 0.0f; }
-    rm_mma_rows<D>(st, offP, qf, sT);                    // S^T  = K Q^T
-    rm_mma_rows<D>(st + RM_TILE, offP, dof, dpT);        // dP^T = V dO^T
-    auto probs = [&](auto masked) {                       // the mask arithmetic only where the tile meets the diagonal
+      for (int v = 0; v < 16; ++v) sT[v] = exp2_raw(sT[v] * sc - lse2);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float pr = exp2_raw(sT[t][v] * sc - lse2);
-          if (decltype(masked)::value && kv0 + 32 * t + acc_row(v, fh) > qpos) pr = 0.0f;
-          sT[t][v] = pr * (dpT[t][v] - dq_dot);
-        }
+      for (int v = 0; v < 16; ++v) sT[v] *= dpT[v] - dq_dot;
+      bf16x8 dsf[2];
+      pack_acc(sT, dsf);
+      rm_mma_cols<D, T>(st, offT, dsf, dq);               // dQ^T += K^T dS^T
+      __builtin_amdgcn_sched_barrier(0);
     };
-    if (kv0 + 63 > qw0) probs(std::true_type{}); else probs(std::false_type{});
-    bf16x8 dsf[4];
-    pack_acc_pair(sT, dsf);
-    rm_mma_cols<D>(st, offT, dsf, dq);                   // dQ^T += K^T dS^T
+    both_halves<D>(diagonal, part);
   }
   if (qpos < s) {
     bf16_t* out = static_cast<bf16_t*>(p.dqkv) + ((long)bi * s + qpos) * ld + hh * D;
@@ -552,6 +569,31 @@ DEV void attn_bwd_dq_body(const AttnArgs& p, uint8_t* smem, int qb, int hh, int 
 }
 
 // ------------------------------------------------------------------------------------- dK / dV pass
+// P = exp(S - lse) into sm and dS = P (dP - D) into dpm for 32 queries: a lane's lse and D (256 bytes on) of group g of
+// its rows lie in LDS at `stats` + 32 g bytes.
+DEV void dkv_probs(uint32_t stats, float sc, f32x16& sm, f32x16& dpm) {
+  u32x4 l4[4], d4[4];
+  static_for<0, 4>([&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    l4[G] = ds_read_b128_at<32 * G>(stats);
+    d4[G] = ds_read_b128_at<32 * G + 256>(stats);
+  });
+  lds_wait<0>();
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    tie(l4[g]);
+    tie(d4[g]);
+    const f32x4 lf = __builtin_bit_cast(f32x4, l4[g]), df = __builtin_bit_cast(f32x4, d4[g]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sm[4 * g + e] = exp2_raw(sm[4 * g + e] * sc - lf[e] * LOG2E);
+      dpm[4 * g + e] -= df[e];
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) dpm[v] *= sm[v];
+}
+
 template <int D>
 DEV void attn_bwd_dkv_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int bi) {
   using X = Dims<D>;
@@ -599,8 +641,7 @@ DEV void attn_bwd_dkv_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int
 
   issue_tile(j0, 0);
   for (int j = j0; j < nq; ++j) {
-    pin_acc(dk);
-    pin_acc(dv);
+    if constexpr (D == 128) { pin_acc(dk); pin_acc(dv); }
     const int slot = (j - j0) & 1;
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
@@ -608,52 +649,24 @@ DEV void attn_bwd_dkv_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int
     const int q0 = j * 64;
     if (q0 + 63 < kw0) continue;                          // no query of the tile sees this wave's keys
     const uint32_t st = smem_base + slot * STAGE;
-    f32x16 sm[2], dpm[2];
+    const bool diagonal = q0 < kw0 + 31;                    // the tile meets the diagonal
+    auto part = [&](auto mc, auto tc) {                   // 32 queries at a time
+      constexpr int T = decltype(tc)::value;
+      const bool masked = mc;
+      f32x16 sm, dpm;
+      start_scores(sm, masked, kpos - q0 - 32 * T, 31, fh);
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { sm[t][v] = 0.0f; dpm[t][v] = 0.0f; }
-    rm_mma_rows<D>(st, offP, kf, sm);                     // S[q, kv]  = Q K^T
-    rm_mma_rows<D>(st + RM_TILE, offP, vf, dpm);          // dP[q, kv] = dO V^T
-    u32x4 pw[4], dw[4];                                   // P and dS rounded to bf16 as they are formed
-    auto probs = [&](auto masked) {                       // the mask arithmetic only where the tile meets the diagonal
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      u32x4 l4[4], d4[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {                       // 4 consecutive query rows 32 t + 8 g + 4 fh ..
-        const uint32_t a = st + 2 * RM_TILE + (uint32_t)(32 * t + 8 * g + 4 * fh) * 4u;
-        l4[g] = ds_read_b128_at<0>(a);
-        d4[g] = ds_read_b128_at<256>(a);
-      }
-      lds_wait<0>();
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        tie(l4[g]);
-        tie(d4[g]);
-        const f32x4 lf = __builtin_bit_cast(f32x4, l4[g]), df = __builtin_bit_cast(f32x4, d4[g]);
-        float pr[4], ds[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v = 4 * g + e;
-          pr[e] = exp2_raw(sm[t][v] * sc - lf[e] * LOG2E);
-          if (decltype(masked)::value && q0 + 32 * t + 8 * g + 4 * fh + e < kpos) pr[e] = 0.0f;
-          ds[e] = pr[e] * (dpm[t][v] - df[e]);
-        }
-        // values 4 g .. 4 g + 3 of accumulator t are words 2 (g & 1), 2 (g & 1) + 1 of fragment 2 t + (g >> 1)
-        pw[2 * t + (g >> 1)][2 * (g & 1)] = pack_bf16(pr[0], pr[1]);
-        pw[2 * t + (g >> 1)][2 * (g & 1) + 1] = pack_bf16(pr[2], pr[3]);
-        dw[2 * t + (g >> 1)][2 * (g & 1)] = pack_bf16(ds[0], ds[1]);
-        dw[2 * t + (g >> 1)][2 * (g & 1) + 1] = pack_bf16(ds[2], ds[3]);
-      }
-    }
+      for (int v = 0; v < 16; ++v) dpm[v] = 0.0f;
+      rm_mma_rows<D, T>(st, st + RM_TILE, offP, kf, vf, sm, dpm);       // S[q, kv] = Q K^T, dP[q, kv] = dO V^T
+      dkv_probs(st + 2 * RM_TILE + (uint32_t)(32 * T + 4 * fh) * 4u, sc, sm, dpm);
+      bf16x8 pf[2], dsf[2];
+      pack_acc(sm, pf);
+      pack_acc(dpm, dsf);
+      rm_mma_cols<D, T>(st + RM_TILE, offT, pf, dv);      // dV^T += dO^T P
+      rm_mma_cols<D, T>(st, offT, dsf, dk);               // dK^T += Q^T dS
+      __builtin_amdgcn_sched_barrier(0);
     };
-    if (q0 < kw0 + 31) probs(std::true_type{}); else probs(std::false_type{});
-    bf16x8 pf[4], dsf[4];
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) { pf[s4] = __builtin_bit_cast(bf16x8, pw[s4]); dsf[s4] = __builtin_bit_cast(bf16x8, dw[s4]); }
-    rm_mma_cols<D>(st + RM_TILE, offT, pf, dv);           // dV^T += dO^T P
-    rm_mma_cols<D>(st, offT, dsf, dk);                    // dK^T += Q^T dS
+    both_halves<D>(diagonal, part);
   }
   if (kpos < s) {
     bf16_t* out = static_cast<bf16_t*>(p.dqkv) + ((long)bi * s + kpos) * ld + hh * D;
@@ -669,7 +682,7 @@ DEV void attn_bwd_dkv_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int
 // (batch, head) group the items alternate, longest first: dK/dV pass of key block 0, dQ pass of the last query
 // block, dK/dV pass of key block 1, ...
 template <int D>
-__global__ __launch_bounds__(256)
+__global__ __launch_bounds__(256, D == 128 ? 1 : 2)
 void attn_bwd_kernel(const AttnArgs p) {
   extern __shared__ __align__(1024) uint8_t smem[];
   const int nxb = (p.seq + 127) / 128;
@@ -681,8 +694,348 @@ void attn_bwd_kernel(const AttnArgs p) {
 }
 
 
+// ------------------------------------------------------------------------------------- few workgroups
+// With few (batch element, head) pairs or short sequences the passes above are one serial chain per workgroup (64 keys
+// or queries a step, 1.4 us forward and 2.9 us backward) on a chip that is mostly idle.  Here a workgroup owns 32 queries
+// (keys), and its four waves deal the other side's 32-row tiles among themselves: four times the workgroups, a quarter of
+// the chain.  Every wave stages its own tiles (no barrier inside the loop), and the waves' sums meet in LDS at the end,
+// added in wave order.
+constexpr int SP_TILE = 8192;                    // 32 positions of a row-major tile
+constexpr int SP_STAGE = 2 * SP_TILE + 512;      // two tiles, and lse[64], dot[64] where a pass needs them
+constexpr int SP_WAVE = 2 * SP_STAGE;            // a wave's LDS: two stages, its sums afterwards
+
+struct SplitLoader {         // one wave, 8 one-KiB pieces (4 rows each) of a 32-row tile
+  uint32_t base[8];
+  DEV void init(int ld, int d_valid, int lane) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = 4 * i + (lane >> 4);
+      const int d = ((lane & 15) ^ rm_swz(row)) * 8;
+      base[i] = d < d_valid ? (uint32_t)(row * ld + d) * 2u : BUF_OOB;
+    }
+  }
+  DEV void issue(buf_rsrc rs, uint8_t* tile, uint32_t row_byte_off) const {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(tile + i * 1024), 16, base[i] + row_byte_off, 0, 0, 0);
+  }
+};
+
+// Accumulators to LDS and back, 16 bytes a lane: value group (dt, g) of lane l at ((4 dt + g) * 64 + l) * 16.
+template <int N>
+DEV void put_acc(uint8_t* at, const f32x16 (&o)[N], int lane) {
+#pragma unroll
+  for (int dt = 0; dt < N; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4*>(at + ((4 * dt + g) * 64 + lane) * 16) = f32x4{o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+}
+template <int N>
+DEV void sum_acc(const uint8_t* at, f32x16 (&o)[N], int lane) {      // over the four waves, in wave order
+#pragma unroll
+  for (int dt = 0; dt < N; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 v = *reinterpret_cast<const f32x4*>(at + ((4 * dt + g) * 64 + lane) * 16);
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const f32x4*>(at + w * SP_WAVE + ((4 * dt + g) * 64 + lane) * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[dt][4 * g + e] = v[e];
+    }
+}
+template <int D>
+DEV void zero_acc(f32x16 (&o)[Dims<D>::DT]) {
+#pragma unroll
+  for (int dt = 0; dt < Dims<D>::DT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[dt][v] = 0.0f;
+}
+
+template <int D>
+__global__ __launch_bounds__(256)
+void attn_fwd_split_kernel(const AttnArgs p) {
+  using X = Dims<D>;
+  extern __shared__ __align__(1024) uint8_t smem[];
+  __shared__ float stat_m[4][64], stat_l[4][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 31, fh = lane >> 5;
+  const int s = p.seq, nqb = (s + 31) / 32;
+  int pos, group;
+  if (!ranked_item(nqb, p.heads * p.batch, pos, group)) return;
+  const int qb = nqb - 1 - pos, hh = group % p.heads, bi = group / p.heads;
+  const int qpos = qb * 32 + fr;
+  const long ld = p.ld;
+  const bf16_t* tok0 = static_cast<const bf16_t*>(p.qkv) + (long)bi * s * ld;
+  const int hl = p.heads * D;
+  const long view_bytes = ((long)(s - 1) * ld + D) * 2;
+  const buf_rsrc rsK = make_rsrc(tok0 + hl + hh * D, view_bytes);
+  const buf_rsrc rsV = make_rsrc(tok0 + 2 * hl + hh * D, view_bytes);
+  uint8_t* const mine = smem + wave * SP_WAVE;
+  SplitLoader ldr;
+  ldr.init((int)ld, D, lane);
+  auto issue = [&](int j, int stage) {
+    const uint32_t ro = (uint32_t)(j * 32) * (uint32_t)ld * 2u;
+    ldr.issue(rsK, mine + stage * SP_STAGE, ro);
+    ldr.issue(rsV, mine + stage * SP_STAGE + SP_TILE, ro);
+  };
+  if (wave <= qb) issue(wave, 0);
+  bf16x8 qf[X::KSTEPS];
+  load_row_frags<D>(tok0 + hh * D, ld, qpos, s, fh, qf);
+  const uint32_t offP = rm_plain_off(lane), offT = rm_trans_off(lane);
+  f32x16 o[X::DT];
+  zero_acc<D>(o);
+  float m = -INFINITY, l = 0.0f;
+  const float sc = p.scale * LOG2E;
+  int stage = 0;
+  for (int j = wave; j <= qb; j += 4, stage ^= 1) {
+    if (j + 4 <= qb) { issue(j + 4, stage ^ 1); wait_vmcnt<16>(); } else { wait_vmcnt<0>(); }
+    const uint32_t st = lds_addr(mine) + stage * SP_STAGE;
+    f32x16 sT;
+    start_scores(sT, j == qb, 0, qpos - j * 32, fh);
+    u32x4 kf[X::KSTEPS];
+    static_for<0, X::KSTEPS>([&](auto kc) { constexpr int K = decltype(kc)::value; kf[K] = ds_read_b128_at<0>(st + (offP ^ (K << 5))); });
+    u32x2 vf[2][2][2];
+    auto read_v = [&](auto dd) {
+      constexpr int DTI = decltype(dd)::value;
+      static_for<0, 2>([&](auto uu) {
+        constexpr int U = decltype(uu)::value;
+        vf[DTI & 1][U][0] = ds_read_tr_at<SP_TILE + U * 4096>(st + (offT ^ ((4 * DTI) << 4)));
+        vf[DTI & 1][U][1] = ds_read_tr_at<SP_TILE + U * 4096 + 2048>(st + (offT ^ (((4 * DTI) ^ 2) << 4)));
+      });
+    };
+    lds_wait<0>();
+#pragma unroll
+    for (int k = 0; k < X::KSTEPS; ++k) {
+      tie(kf[k]);
+      sT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[k]), qf[k], sT, 0, 0, 0);     // S^T[kv, q] = K Q^T
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[v]);
+    mx = fmaxf(mx, other_half(mx)) * sc;
+    const float m_new = fmaxf(m, mx);                    // finite: the first key of any tile up to the diagonal is visible
+    if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {
+      const float alpha = exp2_raw(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < X::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
+      m = m_new;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      sT[v] = exp2_raw(sT[v] * sc - m);
+      l += sT[v];
+    }
+    bf16x8 pf[2];
+    pack_acc(sT, pf);
+    read_v(std::integral_constant<int, 0>{});
+    static_for<0, X::DT>([&](auto dd) {                  // O^T[d, q] += V^T P^T
+      constexpr int DTI = decltype(dd)::value;
+      if constexpr (DTI + 1 < X::DT) read_v(std::integral_constant<int, DTI + 1>{});
+      lds_wait<(DTI + 1 < X::DT) ? 4 : 0>();
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        tie(vf[DTI & 1][u][0]);
+        tie(vf[DTI & 1][u][1]);
+        const u32x4 a = {vf[DTI & 1][u][0][0], vf[DTI & 1][u][0][1], vf[DTI & 1][u][1][0], vf[DTI & 1][u][1][1]};
+        o[DTI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pf[u], o[DTI], 0, 0, 0);
+      }
+    });
+  }
+  l += other_half(l);
+  stat_m[wave][lane] = m;
+  stat_l[wave][lane] = l;
+  __syncthreads();
+  float m_all = -INFINITY, l_all = 0.0f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, stat_m[w][lane]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) l_all += stat_l[w][lane] * exp2_raw(stat_m[w][lane] - m_all);     // a wave without a tile: 2^-inf = 0
+  const float mine_scale = exp2_raw(m - m_all);
+#pragma unroll
+  for (int dt = 0; dt < X::DT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[dt][v] *= mine_scale;
+  put_acc(mine, o, lane);
+  __syncthreads();
+  if (wave == 0) {
+    sum_acc(smem, o, lane);
+    if (qpos < s) {
+      bf16_t* out = static_cast<bf16_t*>(p.ctx) + ((long)bi * s + qpos) * p.ld_ctx + hh * D;
+      store_transposed<D>(o, 1.0f / l_all, out, fh);
+      if (fh == 0) p.lse[((long)bi * p.heads + hh) * s + qpos] = (m_all + log2f(l_all)) * LN2;
+    }
+  }
+}
+
+template <int D>
+DEV void attn_bwd_dq_split_body(const AttnArgs& p, uint8_t* smem, int qb, int hh, int bi) {
+  using X = Dims<D>;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 31, fh = lane >> 5;
+  const int s = p.seq, qpos = qb * 32 + fr;
+  const long ld = p.ld;
+  const bf16_t* tok0 = static_cast<const bf16_t*>(p.qkv) + (long)bi * s * ld;
+  const int hl = p.heads * D;
+  const long view_bytes = ((long)(s - 1) * ld + D) * 2;
+  const buf_rsrc rsK = make_rsrc(tok0 + hl + hh * D, view_bytes);
+  const buf_rsrc rsV = make_rsrc(tok0 + 2 * hl + hh * D, view_bytes);
+  uint8_t* const mine = smem + wave * SP_WAVE;
+  SplitLoader ldr;
+  ldr.init((int)ld, D, lane);
+  auto issue = [&](int j, int stage) {
+    const uint32_t ro = (uint32_t)(j * 32) * (uint32_t)ld * 2u;
+    ldr.issue(rsK, mine + stage * SP_STAGE, ro);
+    ldr.issue(rsV, mine + stage * SP_STAGE + SP_TILE, ro);
+  };
+  if (wave <= qb) issue(wave, 0);
+  bf16x8 qf[X::KSTEPS], dof[X::KSTEPS];
+  load_row_frags<D>(tok0 + hh * D, ld, qpos, s, fh, qf);
+  load_row_frags<D>(static_cast<const bf16_t*>(p.dctx) + (long)bi * s * p.ld_ctx + hh * D, p.ld_ctx, qpos, s, fh, dof);
+  const long stat = ((long)bi * p.heads + hh) * s + qpos;
+  const float lse2 = qpos < s ? p.lse[stat] * LOG2E : INFINITY;
+  const float dq_dot = qpos < s ? p.dot[stat] : 0.0f;
+  const uint32_t offP = rm_plain_off(lane), offT = rm_trans_off(lane);
+  const float sc = p.scale * LOG2E;
+  f32x16 dq[X::DT];
+  zero_acc<D>(dq);
+  int stage = 0;
+  for (int j = wave; j <= qb; j += 4, stage ^= 1) {
+    if (j + 4 <= qb) { issue(j + 4, stage ^ 1); wait_vmcnt<16>(); } else { wait_vmcnt<0>(); }
+    const uint32_t st = lds_addr(mine) + stage * SP_STAGE;
+    {
+      f32x16 sT, dpT;
+      start_scores(sT, j == qb, 0, qpos - j * 32, fh);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dpT[v] = 0.0f;
+      rm_mma_rows<D, 0>(st, st + SP_TILE, offP, qf, dof, sT, dpT);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sT[v] = exp2_raw(sT[v] * sc - lse2);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sT[v] *= dpT[v] - dq_dot;
+      bf16x8 dsf[2];
+      pack_acc(sT, dsf);
+      rm_mma_cols<D, 0>(st, offT, dsf, dq);
+    }
+  }
+  put_acc(mine, dq, lane);
+  __syncthreads();
+  if (wave == 0 && qpos < s) {
+    sum_acc(smem, dq, lane);
+    bf16_t* out = static_cast<bf16_t*>(p.dqkv) + ((long)bi * s + qpos) * ld + hh * D;
+    if (p.rope) rope_back<D>(dq, qpos, fh, p.rope_log2_base);
+    store_transposed<D>(dq, p.scale, out, fh);
+  }
+}
+
+template <int D>
+DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int bi) {
+  using X = Dims<D>;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 31, fh = lane >> 5;
+  const int s = p.seq, kpos = kb * 32 + fr, nq = (s + 31) / 32;
+  const long ld = p.ld, ldc = p.ld_ctx;
+  const bf16_t* tok0 = static_cast<const bf16_t*>(p.qkv) + (long)bi * s * ld;
+  const bf16_t* do0 = static_cast<const bf16_t*>(p.dctx) + (long)bi * s * ldc + hh * D;
+  const int hl = p.heads * D;
+  const buf_rsrc rsQ = make_rsrc(tok0 + hh * D, ((long)(s - 1) * ld + D) * 2);
+  const buf_rsrc rsO = make_rsrc(do0, ((long)(s - 1) * ldc + D) * 2);
+  const long stat0 = ((long)bi * p.heads + hh) * s;
+  const buf_rsrc rsL = make_rsrc(p.lse + stat0, (long)s * 4);
+  const buf_rsrc rsD = make_rsrc(p.dot + stat0, (long)s * 4);
+  uint8_t* const mine = smem + wave * SP_WAVE;
+  SplitLoader ldq, ldo;
+  ldq.init((int)ld, D, lane);
+  ldo.init((int)ldc, D, lane);
+  auto issue = [&](int j, int stage) {
+    uint8_t* st = mine + stage * SP_STAGE;
+    ldq.issue(rsQ, st, (uint32_t)(j * 32) * (uint32_t)ld * 2u);
+    ldo.issue(rsO, st + SP_TILE, (uint32_t)(j * 32) * (uint32_t)ldc * 2u);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, LDS_PTR(st + 2 * SP_TILE), 4, (uint32_t)(j * 32 + lane) * 4u, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsD, LDS_PTR(st + 2 * SP_TILE + 256), 4, (uint32_t)(j * 32 + lane) * 4u, 0, 0, 0);
+  };
+  if (kb + wave < nq) issue(kb + wave, 0);
+  bf16x8 kf[X::KSTEPS], vf[X::KSTEPS];
+  load_row_frags<D>(tok0 + hl + hh * D, ld, kpos, s, fh, kf);
+  load_row_frags<D>(tok0 + 2 * hl + hh * D, ld, kpos, s, fh, vf);
+  const uint32_t offP = rm_plain_off(lane), offT = rm_trans_off(lane);
+  const float sc = p.scale * LOG2E;
+  f32x16 dk[X::DT], dv[X::DT];
+  zero_acc<D>(dk);
+  zero_acc<D>(dv);
+  int stage = 0;
+  for (int j = kb + wave; j < nq; j += 4, stage ^= 1) {
+    if (j + 4 < nq) { issue(j + 4, stage ^ 1); wait_vmcnt<18>(); } else { wait_vmcnt<0>(); }
+    const uint32_t st = lds_addr(mine) + stage * SP_STAGE;
+    {
+      f32x16 sm, dpm;
+      start_scores(sm, j == kb, kpos - j * 32, 31, fh);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dpm[v] = 0.0f;
+      rm_mma_rows<D, 0>(st, st + SP_TILE, offP, kf, vf, sm, dpm);
+      dkv_probs(st + 2 * SP_TILE + (uint32_t)fh * 16u, sc, sm, dpm);
+      bf16x8 pf[2], dsf[2];
+      pack_acc(sm, pf);
+      pack_acc(dpm, dsf);
+      rm_mma_cols<D, 0>(st + SP_TILE, offT, pf, dv);
+      rm_mma_cols<D, 0>(st, offT, dsf, dk);
+    }
+  }
+  put_acc(mine, dk, lane);
+  put_acc(mine + X::DT * 4096, dv, lane);
+  __syncthreads();
+  if (kpos >= s) return;
+  bf16_t* out = static_cast<bf16_t*>(p.dqkv) + ((long)bi * s + kpos) * ld + hh * D;
+  if (wave == 0) {
+    sum_acc(smem, dk, lane);
+    if (p.rope) rope_back<D>(dk, kpos, fh, p.rope_log2_base);
+    store_transposed<D>(dk, p.scale, out + hl, fh);
+  } else if (wave == 1) {
+    sum_acc(smem + X::DT * 4096, dv, lane);
+    store_transposed<D>(dv, 1.0f, out + 2 * hl, fh);
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(256)
+void attn_bwd_split_kernel(const AttnArgs p) {
+  static_assert(SP_WAVE >= 2 * Dims<D>::DT * 4096, "a wave's dK and dV sums fit its stages");
+  extern __shared__ __align__(1024) uint8_t smem[];
+  const int nb = (p.seq + 31) / 32;
+  int pos, group;
+  if (!ranked_item(2 * nb, p.heads * p.batch, pos, group)) return;
+  const int hh = group % p.heads, bi = group / p.heads;
+  if (pos & 1) attn_bwd_dq_split_body<D>(p, smem, nb - 1 - (pos >> 1), hh, bi);
+  else attn_bwd_dkv_split_body<D>(p, smem, pos >> 1, hh, bi);
+}
+
+// Whether the split form is the faster one, from the time of either on an otherwise idle chip (us, fitted to 21 shapes):
+// the longest workgroup's chain against the split form's start, end and rounds of workgroups.  Forward / backward, heads
+// of 128: 4 x 704 positions, one head 16.5 -> 11.8 / 37 -> 20; 812, seven heads 18.9 -> 13.9 / 44 -> 27; 4096, two heads
+// 80 -> 40 / 150 -> 65; the two forms meet at 4 x 512, five heads.
+static bool split_pays(const AttnArgs& a, bool backward) {
+  const int wgs = (a.seq + 127) / 128 * a.heads * a.batch, steps = (a.seq + 63) / 64;
+  if (wgs > 128) return false;
+  const double at_once = backward ? wgs / 32.0 : wgs / 96.0, rounds = at_once > 1.0 ? at_once : 1.0;
+  if (backward) return 11 + rounds * (5 + 1.45 * a.seq / 256) < 0.95 * (14 + 2.15 * steps);
+  return 4.5 + rounds * (1.5 + 1.1 * a.seq / 128) < 0.95 * (5 + 1.17 * steps);
+}
+
 template <int D>
 hipError_t fwd_launch(const AttnArgs& a, hipStream_t st) {
+  if (split_pays(a, false)) {
+    constexpr int LDS = 4 * SP_WAVE;
+    static LdsLimitOnce lds_limit;
+    hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_split_kernel<D>), LDS);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_fwd_split_kernel<D>, dim3(ranked_grid((a.seq + 31) / 32, a.heads * a.batch)), dim3(256), LDS, st, a);
+    return hipGetLastError();
+  }
   constexpr int LDS = 2 * (((D + 31) / 32) * 4096 + 2 * 8192);
   static LdsLimitOnce lds_limit;
   hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_kernel<D>), LDS);
@@ -699,6 +1052,13 @@ hipError_t bwd_launch(const AttnArgs& a, hipStream_t st) {
                      a.heads, D, a.dot);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (split_pays(a, true)) {
+    constexpr int LDS = 4 * SP_WAVE;
+    static LdsLimitOnce lds_limit;
+    if ((e = lds_limit.ensure(reinterpret_cast<const void*>(attn_bwd_split_kernel<D>), LDS)) != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_bwd_split_kernel<D>, dim3(ranked_grid(2 * ((a.seq + 31) / 32), a.heads * a.batch)), dim3(256), LDS, st, a);
+    return hipGetLastError();
+  }
   constexpr int LDS = 2 * (2 * RM_TILE + 512);             // the larger of the two passes' needs
   static LdsLimitOnce lds_limit;
   if ((e = lds_limit.ensure(reinterpret_cast<const void*>(attn_bwd_kernel<D>), LDS)) != hipSuccess) return e;
