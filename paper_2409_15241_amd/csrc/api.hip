@@ -82,7 +82,8 @@ struct Layout {
   // saved block (bytes)
   size_t ln1, qkv, ctx, lse, x1, ln2, pre, act, mean1, rstd1, mean2, rstd2, saved_total;
   // workspace block (bytes)
-  size_t d_pre, dx1, dctx, dqkv, dot, red, ws_total;
+  size_t d_pre, dx1, dctx, dqkv, dot, red, wpart, ws_total;
+  int wsplits;       // contraction ranges of the weight gradients' one launch, whose sums meet in wpart
   // partial column sums: area k starts area_off[k] floats in and holds, for every slice (the norms') or row group (the
   // column sums'), area_rows[k] rows of area_n[k] floats; red_floats = size of all areas
   size_t red_floats, area_off[8];
@@ -200,6 +201,9 @@ int validate(const domino_cfg* c, Layout* L) {
     l.red_floats = (fo + 63) / 64 * 64;
   }
   l.red = take(l.red_floats * 4);
+  const long wfloats = (long)l.h * (4L * l.hl + l.upc + l.fl);
+  l.wsplits = l.beside || l.per_slice ? 1 : gemm_wgrad_splits(wgrad_tiles(l), l.M, wfloats);
+  l.wpart = take(l.wsplits > 1 ? (size_t)wfloats * 4 * l.wsplits : 0);
   l.ws_total = o;
   if (L) *L = l;
   return DOMINO_OK;
@@ -567,8 +571,9 @@ inline bool merged_wgrads(const Layout& L) { return L.merged; }
 enum { WG_DOWN = 0, WG_UP, WG_OUT, WG_QKV, NWGRADS };
 
 // the weight gradients of the n matrices in `which` (and before them the column sums behind the biases of the same
-// products), on `st`: one launch for all of them; with cfg->wgrad_per_slice one per matrix and slice, in slice order
-int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, const int* which, int n, hipStream_t st) {
+// products), on `st`: one launch for all of them (`parts`: memory for the sums of L.wsplits contraction ranges, or NULL
+// for one range); with cfg->wgrad_per_slice one per matrix and slice, in slice order
+int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, const int* which, int n, hipStream_t st, float* parts) {
   const char* sv = static_cast<const char*>(B.saved);
   const domino_grads* G = B.G;
   struct { int cls; const void* A; long lda; const void* Bm; long ldb; float* C; int M, N; int bias; } const tab[NWGRADS] = {
@@ -594,6 +599,7 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
       GemmArgs a = gemm_args(at(w.A, r0 * w.lda * 2), w.lda, at(w.Bm, r0 * w.ldb * 2), w.ldb, w.C, w.N, w.M, w.N, K);
       a.beta = (i > 0 || B.accumulate) ? 1 : 0;
       a.beside = L.beside;
+      if (parts) { a.splits = L.wsplits; a.split_ws = parts; }
       a.join = !L.per_slice && (m < n - 1 || i < slices - 1) ? 1 : 0;
       LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
     }
@@ -682,8 +688,11 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }
     return DOMINO_OK;
   };
+  const bool in_place = !S.side && S.lanes == 1;
+  // several contraction ranges where the launch follows the chain on its one stream: nothing else then uses their sums' memory
+  float* const parts_ws = in_place && L.wsplits > 1 ? reinterpret_cast<float*>(at(ws, L.wpart)) : nullptr;
   auto form = [&](std::initializer_list<int> which, hipStream_t st) -> int {
-    TRY(weight_gradients(L, gb, B, which.begin(), (int)which.size(), st));
+    TRY(weight_gradients(L, gb, B, which.begin(), (int)which.size(), st, parts_ws));
     if (own) {
       hipEvent_t ev;
       TRY(record(&ev, st));
@@ -691,7 +700,6 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }
     return DOMINO_OK;
   };
-  const bool in_place = !S.side && S.lanes == 1;
   hipStream_t side = S.side ? S.side_stream() : nullptr;
 
   // the set of gradient tensors that this block writes was read by the weight gradients of the block two above, enqueued

@@ -29,6 +29,8 @@ struct GemmArgs {
   int gelu_tanh;
   int concurrency;       // launches of similar size expected in flight at once (other streams); 0 = 1
   int beside;            // 1: meant to fill what other launches leave idle, so not with 64x64 tiles, which take the whole chip
+  int splits;            // joined weight gradients: contraction ranges, each summed into its own part of split_ws (0 or 1: one)
+  float* split_ws;       // splits * (sum of M * N of the joined products) floats
   int join;              // EPI_ACC_F32: 1 = hold this product back, it is launched together with the next call's (see gemm_launch)
   int tiles_m, tiles_n;  // filled by the launcher
   int group_m;           // filled by the launcher: tile rows per band of the tile order
@@ -40,4 +42,24 @@ struct GemmArgs {
 // stream: at most GEMM_GROUP weight gradients then go out as one launch.  A product into the matrix of the one before it,
 // over the rows that follow it (the next slice of the batch), continues that product's contraction.
 constexpr int GEMM_GROUP = 4;
+
+// Contraction ranges for weight gradients that are launched together and have the chip to themselves: `tiles` tiles of
+// 256x256, `depth` deep, `floats` values in all.  A launch of 160 such tiles leaves 96 of 256 compute units idle for as
+// long as its contraction is deep; cut into ranges it is rounds of shorter tiles, for partial sums that are written and
+// read once each.  (us per tile and per byte as in the tile choice of gemm.hip.)
+constexpr int GEMM_MAX_SPLITS = 6;
+inline int gemm_wgrad_splits(int tiles, int depth, long floats) {
+  const int it = (depth + 63) / 64;
+  auto rounds = [&](int s) { return (tiles * s + 255) / 256 * (13.0 + 1.2 * ((it + s - 1) / s)); };
+  double cost = rounds(1);
+  if (const double t64 = (tiles + 15) / 16 * (1.8 + 1.4 * ((it + 7) / 8)); t64 < cost) cost = t64;              // in 64x64 tiles
+  if (const double t128 = (tiles / 128) * (6 + 0.8 * it) + 3.4 + 0.47 * it; t128 < cost) cost = t128;           // in 128x128 tiles
+  cost *= 0.9;
+  int best = 1;
+  for (int s = 2; s <= GEMM_MAX_SPLITS; ++s) {
+    const double c = rounds(s) + 4.0 + 2.0 * s * floats * 4 / 5e6;
+    if (c < cost) { cost = c; best = s; }
+  }
+  return best;
+}
 hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int tile_cfg, hipStream_t stream);

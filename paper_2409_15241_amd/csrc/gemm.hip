@@ -169,128 +169,145 @@ struct EpiCols {
   }
 };
 
-// Stores ROWS rows of sums from LDS, buffer row 0 = row m_first of C: the sums of `parts` buffers part_bytes apart,
-// added in their order.
+// Stores ROWS rows of sums from LDS.  side() requests what the epilogue needs of the side tensors for the rows from m on
+// and is called one block of rows ahead of finish(), which reads the sums and stores: loads of global memory (1 to 2 us)
+// are in flight while the block before them is worked on.  Rows or columns outside the matrix read a safe address instead
+// of branching, their results are never stored.  PARTS: the sums of `parts` buffers part_bytes apart, added in their order.
 template <int BN, int WN, int EPI, int ROWS, bool PARTS>
-DEV void store_rows(const GemmArgs& p, const EpiCols<BN, WN, EPI>& ec, const uint8_t* buf, int m_first, int parts = 1, int part_bytes = 0) {
-  constexpr int ROWB = epi_row_bytes(WN);
-  constexpr int RPI = 64 / (WN / 4);             // rows per read instruction
-  constexpr int NT_ROWS = ROWS / RPI;            // read-back instructions
-  constexpr int CH = NT_ROWS < 8 ? NT_ROWS : 8;
-  const int n = ec.n, col = ec.col, rcol = ec.rcol;
-  auto read = [&](int at) {
+struct RowStore {
+  static constexpr int ROWB = epi_row_bytes(WN);
+  static constexpr int RPI = 64 / (WN / 4);      // rows per read instruction
+  static constexpr int NR = ROWS / RPI;          // read-back instructions
+  static constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_ROPE;
+  struct Side {
+    u32x2 a[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? NR : 1], b[EPI == EPI_DSWIGLU ? NR : 1];
+    f32x4 old[EPI == EPI_ACC_F32 ? NR : 1];
+  };
+  const GemmArgs& p;
+  const EpiCols<BN, WN, EPI>& ec;
+  int parts, part_bytes;
+
+  DEV bool inside(int m, int t, long& row) const {
+    const int mr = m + t * RPI + ec.rrow;
+    const bool ok = ec.n_ok && mr < p.M;
+    row = ok ? (long)mr : 0L;
+    return ok;
+  }
+  DEV void side(Side& s, int m) const {
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+      long row;
+      const int ns = inside(m, t, row) ? ec.n : 0;
+      if constexpr (EPI == EPI_ACC_F32) {
+        if (p.beta) s.old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + row * p.ldc + ns);
+      } else if constexpr (EPI == EPI_DGELU) {
+        s.a[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + row * p.ldaux + ns);
+      } else if constexpr (EPI == EPI_DSWIGLU) {
+        const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + row * p.ldaux;
+        s.a[t] = *reinterpret_cast<const u32x2*>(aux + ns);
+        s.b[t] = *reinterpret_cast<const u32x2*>(aux + p.n_split + ns);
+      }
+    }
+  }
+  DEV f32x4 read(const uint8_t* buf, int at) const {
     f32x4 v = *reinterpret_cast<const f32x4*>(buf + at);
     if constexpr (PARTS)
       for (int k = 1; k < parts; ++k) v += *reinterpret_cast<const f32x4*>(buf + k * part_bytes + at);
     return v;
-  };
-  // 8 row groups at a time.  Phase 1: every load of the group (LDS read-back and side tensors) is issued before any is
-  // used; rows or columns outside the matrix read a safe address instead of branching, their results are never stored
-#pragma unroll 1
-  for (int t0 = 0; t0 < NT_ROWS; t0 += CH) {
-    f32x4 v[CH], u[(EPI == EPI_SWIGLU || EPI == EPI_ROPE) ? CH : 1], old[EPI == EPI_ACC_F32 ? CH : 1];
-    u32x2 sa[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? CH : 1], sb[EPI == EPI_DSWIGLU ? CH : 1];
-    bool ok[CH];
-    long mrow[CH];
-#pragma unroll
-    for (int t = 0; t < CH; ++t) {
-      const int row = (t0 + t) * RPI + ec.rrow;
-      const int m = m_first + row;
-      ok[t] = ec.n_ok && m < p.M;
-      mrow[t] = ok[t] ? (long)m : 0L;
-      v[t] = read(row * ROWB + rcol * 4);
-      if constexpr (EPI == EPI_SWIGLU || EPI == EPI_ROPE) u[t] = read(row * ROWB + (rcol ^ 32) * 4);
-      const int ns = ok[t] ? n : 0;
-      if constexpr (EPI == EPI_ACC_F32) {
-        if (p.beta) old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + mrow[t] * p.ldc + ns);
-      } else if constexpr (EPI == EPI_DGELU) {
-        sa[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux + ns);
-      } else if constexpr (EPI == EPI_DSWIGLU) {
-        const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + mrow[t] * p.ldaux;
-        sa[t] = *reinterpret_cast<const u32x2*>(aux + ns);
-        sb[t] = *reinterpret_cast<const u32x2*>(aux + p.n_split + ns);
-      }
-    }
-    // Phase 2: arithmetic and stores
-    auto finish = [&](auto tanh_c) __attribute__((always_inline)) {
-      [[maybe_unused]] constexpr bool tanh_form = decltype(tanh_c)::value;
-#pragma unroll
-      for (int t = 0; t < CH; ++t) {
-        f32x4 w = v[t];
-        if constexpr (EPI == EPI_SWIGLU) {
-          if (ok[t]) {
-            bf16_t* aux = static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux;
-            const u32x2 pg = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-            const u32x2 pu = {pack_bf16(u[t][0], u[t][1]), pack_bf16(u[t][2], u[t][3])};
-            *reinterpret_cast<u32x2*>(aux + col) = pg;
-            *reinterpret_cast<u32x2*>(aux + p.n_split + col) = pu;
-            f32x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = w[e] * sigmoid_f(w[e]) * u[t][e];
-            const u32x2 po = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
-            *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + col) = po;
-          }
-        } else if constexpr (EPI == EPI_ACC_F32) {
-          if (p.beta) w += old[t];
-          if (ok[t]) *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + mrow[t] * p.ldc + n) = w;
-        } else if constexpr (EPI == EPI_ROPE) {
-          f32x4 hi = u[t];
-          if (ec.rot) {
-            const float pos = (float)(int)(mrow[t] % p.rope_seq);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              float sn, cs;
-              rope_sincos(pos, ec.rfreq[e], &sn, &cs);
-              const float a = w[e], b = hi[e];
-              w[e] = a * cs - b * sn;
-              hi[e] = b * cs + a * sn;
-            }
-          }
-          if (ok[t]) {
-            bf16_t* crow = static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n;
-            const u32x2 plo = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-            const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
-            *reinterpret_cast<u32x2*>(crow) = plo;
-            *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
-          }
-        } else {
-          w += ec.bias4;
-          if constexpr (EPI == EPI_BIAS_GELU) {
-            const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-            if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.aux) + mrow[t] * p.ldaux + n) = pp;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = gelu_f(w[e], tanh_form);
-          } else if constexpr (EPI == EPI_DGELU) {
-            w[0] *= gelu_grad_f(bf16_lo(sa[t][0]), tanh_form); w[1] *= gelu_grad_f(bf16_hi(sa[t][0]), tanh_form);
-            w[2] *= gelu_grad_f(bf16_lo(sa[t][1]), tanh_form); w[3] *= gelu_grad_f(bf16_hi(sa[t][1]), tanh_form);
-          } else if constexpr (EPI == EPI_DSWIGLU) {
-            const float gv[4] = {bf16_lo(sa[t][0]), bf16_hi(sa[t][0]), bf16_lo(sa[t][1]), bf16_hi(sa[t][1])};
-            const float uv[4] = {bf16_lo(sb[t][0]), bf16_hi(sb[t][0]), bf16_lo(sb[t][1]), bf16_hi(sb[t][1])};
-            f32x4 du;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float sg = sigmoid_f(gv[e]);
-              du[e] = w[e] * gv[e] * sg;                                   // d_act * silu(g)
-              w[e] = w[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));     // d_act * u * silu'(g)
-            }
-            const u32x2 pdu = {pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
-            if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + p.n_split + n) = pdu;
-          }
-          const u32x2 po = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
-          if (ok[t]) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + mrow[t] * p.ldc + n) = po;
-        }
-      }
-    };
+  }
+  // buf: row m's sums
+  DEV void finish(const Side& s, const uint8_t* buf, int m) const {
     if constexpr (EPI == EPI_BIAS_GELU || EPI == EPI_DGELU) {
-      if (p.gelu_tanh) finish(std::true_type{}); else finish(std::false_type{});
+      if (p.gelu_tanh) finish_form<true>(s, buf, m); else finish_form<false>(s, buf, m);
     } else {
-      finish(std::true_type{});
+      finish_form<true>(s, buf, m);
     }
   }
-}
+  template <bool TANH>
+  DEV void finish_form(const Side& s, const uint8_t* buf, int m) const {
+    const int n = ec.n, col = ec.col;
+    f32x4 v[NR], u[PAIR ? NR : 1];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+      const int at = (t * RPI + ec.rrow) * ROWB;
+      v[t] = read(buf, at + ec.rcol * 4);
+      if constexpr (PAIR) u[t] = read(buf, at + (ec.rcol ^ 32) * 4);
+    }
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+      long row;
+      const bool ok = inside(m, t, row);
+      f32x4 w = v[t];
+      if constexpr (EPI == EPI_SWIGLU) {
+        if (ok) {
+          bf16_t* aux = static_cast<bf16_t*>(p.aux) + row * p.ldaux;
+          const u32x2 pg = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+          const u32x2 pu = {pack_bf16(u[t][0], u[t][1]), pack_bf16(u[t][2], u[t][3])};
+          *reinterpret_cast<u32x2*>(aux + col) = pg;
+          *reinterpret_cast<u32x2*>(aux + p.n_split + col) = pu;
+          f32x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = w[e] * sigmoid_f(w[e]) * u[t][e];
+          const u32x2 po = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+          *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + row * p.ldc + col) = po;
+        }
+      } else if constexpr (EPI == EPI_ACC_F32) {
+        if (p.beta) w += s.old[t];
+        if (ok) *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + row * p.ldc + n) = w;
+      } else if constexpr (EPI == EPI_ROPE) {
+        f32x4 hi = u[t];
+        if (ec.rot) {
+          const float pos = (float)(int)(row % p.rope_seq);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float sn, cs;
+            rope_sincos(pos, ec.rfreq[e], &sn, &cs);
+            const float a = w[e], b = hi[e];
+            w[e] = a * cs - b * sn;
+            hi[e] = b * cs + a * sn;
+          }
+        }
+        if (ok) {
+          bf16_t* crow = static_cast<bf16_t*>(p.C) + row * p.ldc + n;
+          const u32x2 plo = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+          const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
+          *reinterpret_cast<u32x2*>(crow) = plo;
+          *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
+        }
+      } else {
+        w += ec.bias4;
+        if constexpr (EPI == EPI_BIAS_GELU) {
+          const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+          if (ok) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.aux) + row * p.ldaux + n) = pp;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = gelu_f<TANH>(w[e]);
+        } else if constexpr (EPI == EPI_DGELU) {
+          w[0] *= gelu_grad_f<TANH>(bf16_lo(s.a[t][0])); w[1] *= gelu_grad_f<TANH>(bf16_hi(s.a[t][0]));
+          w[2] *= gelu_grad_f<TANH>(bf16_lo(s.a[t][1])); w[3] *= gelu_grad_f<TANH>(bf16_hi(s.a[t][1]));
+        } else if constexpr (EPI == EPI_DSWIGLU) {
+          const float gv[4] = {bf16_lo(s.a[t][0]), bf16_hi(s.a[t][0]), bf16_lo(s.a[t][1]), bf16_hi(s.a[t][1])};
+          const float uv[4] = {bf16_lo(s.b[t][0]), bf16_hi(s.b[t][0]), bf16_lo(s.b[t][1]), bf16_hi(s.b[t][1])};
+          f32x4 du;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float sg = sigmoid_f(gv[e]);
+            du[e] = w[e] * gv[e] * sg;                                   // d_act * silu(g)
+            w[e] = w[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));     // d_act * u * silu'(g)
+          }
+          const u32x2 pdu = {pack_bf16(du[0], du[1]), pack_bf16(du[2], du[3])};
+          if (ok) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + row * p.ldc + p.n_split + n) = pdu;
+        }
+        const u32x2 po = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+        if (ok) *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + row * p.ldc + n) = po;
+      }
+    }
+  }
+};
 
 // The products of one launch: one, or several weight gradients with tiles first[i] .. first[i + 1] - 1 of the launch each.
-struct GemmGroup { GemmArgs g[GEMM_GROUP]; int first[GEMM_GROUP + 1]; };
+// With several contraction ranges (splits) the tiles of range s follow those of range s - 1, it starts s * k_per elements
+// down the contraction and its sums go part_stride floats behind the range's before it.
+struct GemmGroup { GemmArgs g[GEMM_GROUP]; int first[GEMM_GROUP + 1]; int splits, k_per; long part_stride; };
 
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 DEV void gemm_body(const GemmArgs& p, const int lin) {
@@ -469,6 +486,10 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   constexpr int ROWB = epi_row_bytes(WN);
   uint8_t* wbuf = smem + wave * (32 * ROWB);
   const EpiCols<BN, WN, EPI> ec(p, tn, n0, wn0, lane);
+  constexpr int RPI = 64 / (WN / 4), ROWS = 8 * RPI < 32 ? 8 * RPI : 32, NB = 32 / ROWS;     // rows per block, blocks per 32 rows
+  const RowStore<BN, WN, EPI, ROWS, false> rs{p, ec, 1, 0};
+  typename RowStore<BN, WN, EPI, ROWS, false>::Side cur, nxt;
+  rs.side(cur, m0 + wm0);
   static_for<0, TM / 2>([&](auto jc) __attribute__((always_inline)) {
     constexpr int j = decltype(jc)::value;
 #pragma unroll
@@ -476,7 +497,13 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
 #pragma unroll
       for (int g = 0; g < 2; ++g)
         *reinterpret_cast<f32x4*>(wbuf + (16 * g + fr) * ROWB + (i * 16 + fh * 4) * 4) = acc[i][2 * j + g];
-    store_rows<BN, WN, EPI, 32, false>(p, ec, wbuf, m0 + wm0 + j * 32);
+#pragma unroll 1
+    for (int b = 0; b < NB; ++b) {
+      const int m = m0 + wm0 + j * 32 + b * ROWS;
+      if (j < TM / 2 - 1 || b < NB - 1) rs.side(nxt, m + ROWS);
+      rs.finish(cur, wbuf + b * ROWS * ROWB, m);
+      cur = nxt;
+    }
   });
 }
 
@@ -578,6 +605,10 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
   }
   // the sums replace the wave's own operand tiles; then every wave stores 8 rows of the tile
   constexpr int ROWB = epi_row_bytes(64);
+  const EpiCols<64, 64, EPI> ec(p, tn, n0, 0, lane);
+  const RowStore<64, 64, EPI, 8, true> rs{p, ec, min(nk, SPLIT_WAVES), SPLIT_STAGE};
+  typename RowStore<64, 64, EPI, 8, true>::Side side;
+  rs.side(side, m0 + wave * 8);
   if (wave < nk) {
 #pragma unroll
     for (int i = 0; i < T4; ++i)
@@ -586,8 +617,7 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
         *reinterpret_cast<f32x4*>(stage + (16 * j + (lane & 15)) * ROWB + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][j];
   }
   __syncthreads();
-  const EpiCols<64, 64, EPI> ec(p, tn, n0, 0, lane);
-  store_rows<64, 64, EPI, 8, true>(p, ec, smem + wave * 8 * ROWB, m0 + wave * 8, min(nk, SPLIT_WAVES), SPLIT_STAGE);
+  rs.finish(side, smem + wave * 8 * ROWB, m0 + wave * 8);
 }
 
 // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): every XCD gets one contiguous chunk of the tile
@@ -614,14 +644,47 @@ void gemm_kernel(const GemmArgs p) {
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 __global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 ? 2 : 1)
 void gemm_group_kernel(const GemmGroup p) {
-  const int T = p.first[GEMM_GROUP], lin = tile_of_block(T);
+  const int T1 = p.first[GEMM_GROUP], T = T1 * p.splits;
+  int lin = tile_of_block(T);
   if (lin >= T) return;
+  const int range = lin / T1;
+  lin -= range * T1;
   int i = 0;
 #pragma unroll
   for (int k = 1; k < GEMM_GROUP; ++k)
     if (lin >= p.first[k]) i = k;
-  if constexpr (BM == 64) gemm_split_body<AKS, BKS, EPI>(p.g[i], lin - p.first[i]);
-  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p.g[i], lin - p.first[i]);
+  GemmArgs a = p.g[i];
+  const long k0 = (long)range * p.k_per;
+  a.A = static_cast<const bf16_t*>(a.A) + k0 * a.lda;
+  a.B = static_cast<const bf16_t*>(a.B) + k0 * a.ldb;
+  a.a_bytes -= k0 * a.lda * 2;
+  a.b_bytes -= k0 * a.ldb * 2;
+  a.K = min(a.K - (int)k0, p.k_per);
+  a.C = static_cast<float*>(a.C) + range * p.part_stride;
+  if constexpr (BM == 64) gemm_split_body<AKS, BKS, EPI>(a, lin - p.first[i]);
+  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(a, lin - p.first[i]);
+}
+
+// The ranges' sums added in order (and to what the gradient held): HBM-bound, one 16-byte chunk of every range per thread.
+struct SplitSum { float* out[GEMM_GROUP]; long end[GEMM_GROUP]; const float* part; long part_stride; int splits, beta; };
+__global__ __launch_bounds__(256)
+void split_sum_kernel(const SplitSum p) {
+  const long at = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (at >= p.part_stride) return;
+  float* out = p.out[0] + at;
+#pragma unroll
+  for (int k = 1; k < GEMM_GROUP; ++k)
+    if (at >= p.end[k - 1]) out = p.out[k] + (at - p.end[k - 1]);
+  f32x4 v[GEMM_MAX_SPLITS];
+#pragma unroll
+  for (int s = 0; s < GEMM_MAX_SPLITS; ++s)
+    if (s < p.splits) v[s] = *reinterpret_cast<const f32x4*>(p.part + s * p.part_stride + at);
+  f32x4 sum = v[0];
+#pragma unroll
+  for (int s = 1; s < GEMM_MAX_SPLITS; ++s)
+    if (s < p.splits) sum += v[s];
+  if (p.beta) sum += *reinterpret_cast<const f32x4*>(out);
+  *reinterpret_cast<f32x4*>(out) = sum;
 }
 
 // fills what the kernel needs to know about the tiles; false: an operand reaches 2 GiB
@@ -641,22 +704,41 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int NT = gemm_threads(BM, BN, WM, WN);
   constexpr int LDS = BM == 64 ? SPLIT_WAVES * SPLIT_STAGE : (RING_A * BM + RING_B * BN) * BK * 2;
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
-  if (n > 1) {
+  if (n > 1 || products[0].splits > 1) {
     if constexpr (EPI == EPI_ACC_F32) {
       auto kern = gemm_group_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
       static LdsLimitOnce lds_limit;      // one per instantiation
       if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
       GemmGroup grp{};
+      SplitSum sum{};
+      grp.splits = products[0].splits > 1 ? products[0].splits : 1;
+      grp.k_per = ((products[0].K + BK - 1) / BK + grp.splits - 1) / grp.splits * BK;
+      grp.splits = (products[0].K + grp.k_per - 1) / grp.k_per;      // no range is empty
+      sum.part = products[0].split_ws; sum.splits = grp.splits; sum.beta = products[0].beta;
       int T = 0;
+      long at = 0;
       for (int i = 0; i < GEMM_GROUP; ++i) {
         grp.first[i] = T;
+        sum.end[i] = at;
         if (i >= n) continue;
-        grp.g[i] = products[i];
-        if (!plan_tiles<BM, BN, AKS, BKS, EPI>(grp.g[i])) return hipErrorInvalidValue;
-        T += grp.g[i].tiles_m * grp.g[i].tiles_n;
+        GemmArgs& g = grp.g[i];
+        g = products[i];
+        if (!plan_tiles<BM, BN, AKS, BKS, EPI>(g) || g.K != products[0].K) return hipErrorInvalidValue;
+        T += g.tiles_m * g.tiles_n;
+        if (grp.splits > 1) {
+          if (g.ldc != g.N || g.beta != sum.beta || !g.split_ws) return hipErrorInvalidValue;
+          sum.out[i] = static_cast<float*>(g.C);
+          g.C = g.split_ws + at;
+          g.beta = 0;
+          at += (long)g.M * g.N;
+          sum.end[i] = at;
+        }
       }
       for (int i = n; i <= GEMM_GROUP; ++i) grp.first[i] = T;
-      hipLaunchKernelGGL(kern, grid(T), dim3(NT), LDS, stream, grp);
+      grp.part_stride = sum.part_stride = at;
+      hipLaunchKernelGGL(kern, grid(T * grp.splits), dim3(NT), LDS, stream, grp);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess || grp.splits == 1) return e;
+      hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((at / 4 + 255) / 256)), dim3(256), 0, stream, sum);
       return hipGetLastError();
     }
     return hipErrorInvalidValue;
@@ -696,30 +778,32 @@ thread_local int g_nheld = 0;
 // is decided as if nothing ran beside the launch, so that no bit of a result depends on the stream pool.  They win where
 // the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep 41 -> 19 us, 240 x 2688 x 7168
 // 55 -> 24, 256 x 1024 x 1024 10.0 -> 6.5; at 1024 x 2560 x 5120 the two forms meet.
-static int pick_tile(const GemmArgs* products, int n, int layout, int epi, int concurrency) {
+static int pick_tile(const GemmArgs* products, int n, int epi, int concurrency) {
   if (concurrency < 1) concurrency = 1;
   const bool swiglu = epi == EPI_SWIGLU;
-  // fixed: without / with fp32 sums to store
-  struct Cand { int id, bm, bn; double fixed[2], per64; };
-  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, {8.0, 16.0}, 1.06}, {GEMM_TILE_256x128, 256, 128, {4.0, 8.0}, 0.67},
-                               {GEMM_TILE_128x256, 128, 256, {4.0, 8.0}, 0.70}, {GEMM_TILE_128x128, 128, 128, {1.5, 2.9}, 0.40}};
-  const int f32 = layout == GEMM_TN;
+  struct Cand { int id, bm, bn; double fixed, per64; };
+  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 8.0, 1.06}, {GEMM_TILE_256x128, 256, 128, 4.0, 0.67},
+                               {GEMM_TILE_128x256, 128, 256, 4.0, 0.70}, {GEMM_TILE_128x128, 128, 128, 1.5, 0.40}};
+  // what the epilogue takes beyond storing bf16 sums, for 256x256 values: activations (vector ALUs), wider results
+  const double extra = epi == EPI_BIAS_GELU ? 6.0 : epi == EPI_SWIGLU ? 5.0 : epi == EPI_DGELU ? 8.0 : epi == EPI_DSWIGLU ? 12.0 :
+                       epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : 0.0;
+  const int splits = products[0].splits > 1 ? products[0].splits : 1;
   auto tiles_of = [&](int bm, int bn) {
     double t = 0;
     for (int i = 0; i < n; ++i) {
       const int N = swiglu ? 2 * products[i].n_split : products[i].N;
       t += (double)((products[i].M + bm - 1) / bm) * ((N + bn - 1) / bn);
     }
-    return t;
+    return t * splits;
   };
-  const int it = (products[0].K + BK - 1) / BK;      // a group's products share the contraction
+  const int it = ((products[0].K + BK - 1) / BK + splits - 1) / splits;      // a group's products share the contraction
   int best = GEMM_TILE_128x128;
   double best_cost = 1e30, best_alone = 1e30;
   for (const Cand& c : cands) {
-    const double tiles = tiles_of(c.bm, c.bn), unit = c.fixed[f32] + c.per64 * it;
+    const double tiles = tiles_of(c.bm, c.bn), fixed = c.fixed + extra * c.bm * c.bn / 65536, unit = fixed + c.per64 * it;
     double alone;
     if (c.id == GEMM_TILE_128x128) {
-      const double lone = c.fixed[f32] + 0.5 + 0.47 * it, full = floor(tiles / 512), rest = tiles - 512 * full;
+      const double lone = fixed + 0.5 + 0.47 * it, full = floor(tiles / 512), rest = tiles - 512 * full;
       alone = full * 2 * unit + (rest == 0 ? 0.0 : rest <= 256 ? lone : 2 * unit);
     } else {
       alone = ceil(tiles / 256) * unit;
@@ -732,8 +816,8 @@ static int pick_tile(const GemmArgs* products, int n, int layout, int epi, int c
     const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.5 * (alone + shared) : shared;
     if (cost < best_cost * 0.999) { best_cost = cost; best = c.id; }
   }
-  if (products[0].beside) return best;
-  const double split = ceil(tiles_of(64, 64) / 256) * (1.8 + 1.4 * ((it + SPLIT_WAVES - 1) / SPLIT_WAVES));
+  if (products[0].beside || splits > 1) return best;
+  const double split = ceil(tiles_of(64, 64) / 256) * (1.8 + (epi == EPI_SWIGLU ? 0.4 : 0.15) * extra + 1.4 * ((it + SPLIT_WAVES - 1) / SPLIT_WAVES));
   return 3 + split < 0.95 * (3 + best_alone) ? GEMM_TILE_64x64 : best;
 }
 
@@ -754,7 +838,7 @@ hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hi
     if (a0.join) return hipSuccess;
     a = g_held; n = g_nheld; g_nheld = 0;
   }
-  if (tile_cfg < 0) tile_cfg = pick_tile(a, n, layout, epi, a->concurrency);
+  if (tile_cfg < 0) tile_cfg = pick_tile(a, n, epi, a->concurrency);
   if (layout == GEMM_NN) {
     switch (epi) {
       case EPI_STORE:     return launch_layout<false, true, EPI_STORE>(a, n, tile_cfg, stream);
