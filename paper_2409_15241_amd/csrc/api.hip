@@ -296,9 +296,10 @@ struct ProfScope {
 
 // launches in flight at once in the layer call being enqueued (tile choice of its GEMMs); 1 outside
 thread_local int g_concurrency = 1;
+thread_local int g_beside = 0;           // 1: the call's row groups run side by side (see GemmArgs::beside)
 struct ConcurrencyScope {
-  explicit ConcurrencyScope(int c) { g_concurrency = c < 1 ? 1 : c; }
-  ~ConcurrencyScope() { g_concurrency = 1; }
+  ConcurrencyScope(int c, const Layout& L) { g_concurrency = c < 1 ? 1 : c; g_beside = L.groups > 1; }
+  ~ConcurrencyScope() { g_concurrency = 1; g_beside = 0; }
 };
 
 inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
@@ -310,6 +311,7 @@ GemmArgs gemm_args(const void* A, long lda, const void* B, long ldb, void* C, lo
   a.A = A; a.B = B; a.C = C; a.lda = lda; a.ldb = ldb; a.ldc = ldc; a.M = M; a.N = N; a.K = K;
   a.gelu_tanh = 1;
   a.concurrency = g_concurrency;
+  a.beside = g_beside;
   return a;
 }
 
@@ -923,7 +925,7 @@ int domino_layer_fwd_parts(const domino_cfg* cfg, const domino_params* P,
   std::lock_guard<std::mutex> lock(g_mutex);
   TRY(begin_call(streams, nstreams, L.p));
   const StreamPlan S(streams, nstreams, L, false);
-  ConcurrencyScope conc(S.used());
+  ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   TRY(enqueue_fwd_block(L, cfg, S, B, parts));
   TRY(join_streams(S, S.used()));
@@ -960,7 +962,7 @@ int domino_layer_bwd_parts(const domino_cfg* cfg, const domino_params* P, const 
   TRY(begin_call(streams, nstreams, L.p));
   B.red = reinterpret_cast<float*>(at(workspace, L.red));
   const StreamPlan S(streams, nstreams, L, true);
-  ConcurrencyScope conc(S.used());
+  ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   TRY(enqueue_bwd_block(L, cfg, S, workspace, grad_bufs(L, workspace), B, parts));
   TRY(join_streams(S, S.used()));
@@ -998,7 +1000,7 @@ int domino_stack_fwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   // a row slice of block l+1 needs only the same row slice of block l (Sec. 3.2): the groups run through the
   // whole stack on their own streams and meet only at the end
   const StreamPlan S(streams, nstreams, L, false);
-  ConcurrencyScope conc(S.used());
+  ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   for (int l = 0; l < nlayers; ++l)
     TRY(enqueue_fwd_block(L, cfg, S, layers[l], DOMINO_FWD_ALL, l > 0, l + 1 < nlayers ? &layers[l + 1] : nullptr));
@@ -1038,7 +1040,7 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
     return fail(DOMINO_ERR_UNSUPPORTED, "streams[0] is being captured into a HIP graph: the backward of a stack of %d blocks with "
                 "p = %d > 2 row slices cannot be captured; capture one domino_layer_bwd call per block instead", nlayers, L.p);
   const StreamPlan S(streams, nstreams, L, true);
-  ConcurrencyScope conc(S.used());
+  ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   GradBufs gb[2] = {grad_bufs(L, workspace), grad_bufs(L, workspace)};
   if (nlayers > 1) gb[1] = GradBufs{at(workspace, SL.d_pre2), at(workspace, SL.dx1_2), at(workspace, SL.dqkv2)};

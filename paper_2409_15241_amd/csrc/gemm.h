@@ -14,7 +14,7 @@ enum GemmEpilogue {
   EPI_ROPE = 6,       // C = bf16(acc) with the rotary embedding applied to columns below rope_cols (heads of rope_d columns)
 };
 enum GemmTile { GEMM_TILE_128x128 = 0, GEMM_TILE_256x128 = 1, GEMM_TILE_256x256 = 2, GEMM_TILE_128x256 = 3,
-                GEMM_TILE_64x64 = 4 };
+                GEMM_TILE_64x64 = 4, GEMM_TILE_128x128_DEALT = 5 };
 
 struct GemmArgs {
   const void* A; const void* B; void* C;
@@ -28,7 +28,7 @@ struct GemmArgs {
   float rope_log2_base;
   int gelu_tanh;
   int concurrency;       // launches of similar size expected in flight at once (other streams); 0 = 1
-  int beside;            // 1: meant to fill what other launches leave idle, so not with 64x64 tiles, which take the whole chip
+  int beside;            // 1: meant to share the chip with other launches, so not in a dealt form, which takes all of it
   int splits;            // joined weight gradients: contraction ranges, each summed into its own part of split_ws (0 or 1: one)
   float* split_ws;       // splits * (sum of M * N of the joined products) floats
   int join;              // EPI_ACC_F32: 1 = hold this product back, it is launched together with the next call's (see gemm_launch)

@@ -507,76 +507,83 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   });
 }
 
-// Products of few tiles: one workgroup of eight waves per 64x64 tile, the contraction dealt over the waves (wave w takes
-// the 64-deep operand tiles w, w + 8, ...), their sums added in wave order through LDS.  Such launches are bound by the
-// serial chain of loads along the contraction, not by any unit's rate: eight chains run side by side here, each wave
-// stages its own operand tiles (no barrier in the loop), and a tile's loads are in flight while the wave's MFMAs on the
-// one before run.  A wave's fragments of both steps sit in registers, so its one stage is free as soon as they are read.
-constexpr int SPLIT_WAVES = 8;
-constexpr int SPLIT_STAGE = 64 * epi_row_bytes(64);      // a wave's LDS: two operand tiles of 8 KiB, its 64x64 sums afterwards
-template <bool AKS, bool BKS, int EPI>
+// Products of few tiles: one workgroup per tile of R x R, the contraction dealt over its waves (wave w of W takes the
+// 64-deep operand tiles w, w + W, ...), their sums added in wave order through LDS.  Such launches are bound by the serial
+// chain along the contraction, not by any unit's rate: W chains run side by side here, each wave stages its own operand
+// tiles (no barrier in the loop), and a tile's loads are in flight while the wave's MFMAs on the one before run.  A wave's
+// fragments of both steps sit in registers, so its one stage is free as soon as they are read.
+//   64x64, eight waves: for the fewest tiles
+//   128x128, four waves: reads half the LDS bytes per MFMA of four waves of 64x64 each
+template <int R> struct Split {
+  static constexpr int W = R == 64 ? 8 : 4;
+  static constexpr int ROWS = 64;                                   // rows of sums that meet in LDS at once
+  static constexpr int TILE = R * BK * 2, SUMS = ROWS * epi_row_bytes(R);
+  static constexpr int STAGE = SUMS > 2 * TILE ? SUMS : 2 * TILE;   // a wave's LDS: two operand tiles, sums afterwards
+  static_assert(STAGE % 1024 == 0 && W * STAGE <= 160 * 1024, "LDS");
+};
+template <int R, bool AKS, bool BKS, int EPI>
 DEV void gemm_split_body(const GemmArgs& p, const int lin) {
-  constexpr int T4 = 4, TILE = 64 * BK * 2;
-  static_assert(SPLIT_STAGE >= 2 * TILE && SPLIT_STAGE % 1024 == 0, "stage");
+  using S = Split<R>;
+  constexpr int T = R / 16, NL = R / 8;                             // fragments of a tile; loads of an operand tile
   extern __shared__ __align__(1024) uint8_t smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int band = lin / (p.group_m * p.tiles_n), inband = lin % (p.group_m * p.tiles_n);
   const int gm = min(p.group_m, p.tiles_m - band * p.group_m);
   const int tm = band * p.group_m + inband % gm, tn = inband / gm;
-  const int m0 = tm * 64, n0 = tn * 64;
+  const int m0 = tm * R, n0 = tn * R;
 
-  TileLoader<64, 1, AKS> ldA;
-  TileLoader<64, 1, BKS> ldB;
+  TileLoader<R, 1, AKS> ldA;
+  TileLoader<R, 1, BKS> ldB;
   ldA.init(p.A, p.a_bytes, (int)p.lda, p.K, IdentityCols{m0, p.M}, m0, p.M, 0, lane);
-  if constexpr (EPI == EPI_SWIGLU) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, GluCols{tn * 32, p.n_split}, n0, p.N, 0, lane);
+  if constexpr (EPI == EPI_SWIGLU) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, GluCols{tn * (R / 2), p.n_split}, n0, p.N, 0, lane);
   else if constexpr (EPI == EPI_ROPE) ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, RopeCols{n0, p.N, p.rope_d}, n0, p.N, 0, lane);
   else ldB.init(p.B, p.b_bytes, (int)p.ldb, p.K, IdentityCols{n0, p.N}, n0, p.N, 0, lane);
   ldA.advance(wave);
   ldB.advance(wave);
-  uint8_t* const stage = smem + wave * SPLIT_STAGE;
+  uint8_t* const stage = smem + wave * S::STAGE;
   auto fill = [&] {
     const buf_rsrc ra = ldA.rsrc(), rb = ldB.rsrc();
     const bool ia = ldA.inside(), ib = ldB.inside();
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ldA.issue(i, ra, ia, stage, 0);
+    for (int i = 0; i < NL; ++i) ldA.issue(i, ra, ia, stage, 0);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ldB.issue(i, rb, ib, stage + TILE, 0);
-    ldA.advance(SPLIT_WAVES);
-    ldB.advance(SPLIT_WAVES);
+    for (int i = 0; i < NL; ++i) ldB.issue(i, rb, ib, stage + S::TILE, 0);
+    ldA.advance(S::W);
+    ldB.advance(S::W);
   };
 
-  f32x4 acc[T4][T4];
+  f32x4 acc[T][T];
 #pragma unroll
-  for (int i = 0; i < T4; ++i)
+  for (int i = 0; i < T; ++i)
 #pragma unroll
-    for (int j = 0; j < T4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  uint32_t offA[AKS ? T4 : 1], offB[BKS ? T4 : 1];
-  const uint32_t lds_a = lds_addr(stage), lds_b = lds_a + TILE;
+    for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t offA[AKS ? T : 1], offB[BKS ? T : 1];
+  const uint32_t lds_a = lds_addr(stage), lds_b = lds_a + S::TILE;
 #pragma unroll
-  for (int j = 0; j < (AKS ? T4 : 1); ++j) offA[j] = lds_a + (AKS ? ks_frag_off16<64>(lane, j) : kc_frag_off16(lane));
+  for (int j = 0; j < (AKS ? T : 1); ++j) offA[j] = lds_a + (AKS ? ks_frag_off16<R>(lane, j) : kc_frag_off16(lane));
 #pragma unroll
-  for (int i = 0; i < (BKS ? T4 : 1); ++i) offB[i] = lds_b + (BKS ? ks_frag_off16<64>(lane, i) : kc_frag_off16(lane));
+  for (int i = 0; i < (BKS ? T : 1); ++i) offB[i] = lds_b + (BKS ? ks_frag_off16<R>(lane, i) : kc_frag_off16(lane));
 
   const int nk = (p.K + BK - 1) / BK;
   if (wave < nk) fill();
-  for (int kt = wave; kt < nk; kt += SPLIT_WAVES) {
-    u32x4 fa[2][AKS ? 1 : T4], fb[2][BKS ? 1 : T4];
-    u32x2 ha[2][AKS ? T4 : 1][2], hb[2][BKS ? T4 : 1][2];
+  for (int kt = wave; kt < nk; kt += S::W) {
+    u32x4 fa[2][AKS ? 1 : T], fb[2][BKS ? 1 : T];
+    u32x2 ha[2][AKS ? T : 1][2], hb[2][BKS ? T : 1][2];
     wait_vmcnt<0>();
     static_for<0, 2>([&](auto sc) {
       constexpr int s = decltype(sc)::value;
-      static_for<0, T4>([&](auto rc) {
+      static_for<0, T>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
         if constexpr (AKS) {
-          ha[s][r][0] = ds_read_tr_at<s * 32 * 128>(offA[r]);
-          ha[s][r][1] = ds_read_tr_at<(s * 32 + 4) * 128>(offA[r]);
+          ha[s][r][0] = ds_read_tr_at<s * 32 * R * 2>(offA[r]);
+          ha[s][r][1] = ds_read_tr_at<(s * 32 + 4) * R * 2>(offA[r]);
         } else {
           fa[s][r] = ds_read_b128_at<r * 2048>(lds_a + ((offA[0] - lds_a) ^ (s << 6)));
         }
         if constexpr (BKS) {
-          hb[s][r][0] = ds_read_tr_at<s * 32 * 128>(offB[r]);
-          hb[s][r][1] = ds_read_tr_at<(s * 32 + 4) * 128>(offB[r]);
+          hb[s][r][0] = ds_read_tr_at<s * 32 * R * 2>(offB[r]);
+          hb[s][r][1] = ds_read_tr_at<(s * 32 + 4) * R * 2>(offB[r]);
         } else {
           fb[s][r] = ds_read_b128_at<r * 2048>(lds_b + ((offB[0] - lds_b) ^ (s << 6)));
         }
@@ -586,38 +593,43 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int r = 0; r < T4; ++r) {
+      for (int r = 0; r < T; ++r) {
         if constexpr (AKS) { tie(ha[s][r][0]); tie(ha[s][r][1]); } else tie(fa[s][r]);
         if constexpr (BKS) { tie(hb[s][r][0]); tie(hb[s][r][1]); } else tie(fb[s][r]);
       }
-    if (kt + SPLIT_WAVES < nk) fill();
+    if (kt + S::W < nk) fill();
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int i = 0; i < T4; ++i)
+      for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < T4; ++j) {
+        for (int j = 0; j < T; ++j) {
           u32x4 a, b;
           if constexpr (AKS) a = u32x4{ha[s][j][0][0], ha[s][j][0][1], ha[s][j][1][0], ha[s][j][1][1]}; else a = fa[s][j];
           if constexpr (BKS) b = u32x4{hb[s][i][0][0], hb[s][i][0][1], hb[s][i][1][0], hb[s][i][1][1]}; else b = fb[s][i];
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), acc[i][j], 0, 0, 0);
         }
   }
-  // the sums replace the wave's own operand tiles; then every wave stores 8 rows of the tile
-  constexpr int ROWB = epi_row_bytes(64);
-  const EpiCols<64, 64, EPI> ec(p, tn, n0, 0, lane);
-  const RowStore<64, 64, EPI, 8, true> rs{p, ec, min(nk, SPLIT_WAVES), SPLIT_STAGE};
-  typename RowStore<64, 64, EPI, 8, true>::Side side;
-  rs.side(side, m0 + wave * 8);
-  if (wave < nk) {
+  // the sums replace the wave's own operand tiles, 64 rows at a time; then every wave stores its share of these rows
+  constexpr int ROWB = epi_row_bytes(R), MINE = S::ROWS / S::W;
+  const EpiCols<R, R, EPI> ec(p, tn, n0, 0, lane);
+  const RowStore<R, R, EPI, MINE, true> rs{p, ec, min(nk, S::W), S::STAGE};
+  static_for<0, R / S::ROWS>([&](auto bc) {
+    constexpr int B = decltype(bc)::value;
+    const int m = m0 + B * S::ROWS + wave * MINE;
+    typename RowStore<R, R, EPI, MINE, true>::Side side;
+    rs.side(side, m);
+    if constexpr (B > 0) __syncthreads();                           // everybody has read the rows before
+    if (wave < nk) {
 #pragma unroll
-    for (int i = 0; i < T4; ++i)
+      for (int i = 0; i < T; ++i)
 #pragma unroll
-      for (int j = 0; j < T4; ++j)
-        *reinterpret_cast<f32x4*>(stage + (16 * j + (lane & 15)) * ROWB + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][j];
-  }
-  __syncthreads();
-  rs.finish(side, smem + wave * 8 * ROWB, m0 + wave * 8);
+        for (int j = 0; j < S::ROWS / 16; ++j)
+          *reinterpret_cast<f32x4*>(stage + (16 * j + (lane & 15)) * ROWB + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][B * (S::ROWS / 16) + j];
+    }
+    __syncthreads();
+    rs.finish(side, smem + wave * MINE * ROWB, m);
+  });
 }
 
 // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): every XCD gets one contiguous chunk of the tile
@@ -628,21 +640,22 @@ DEV int tile_of_block(int T) {
   return (blockIdx.x & 7) * ((T + 7) >> 3) + (blockIdx.x >> 3);
 }
 
-constexpr int gemm_threads(int BM, int BN, int WM, int WN) { return BM == 64 ? SPLIT_WAVES * 64 : (BM / WM) * (BN / WN) * 64; }
+// wave tile = tile: the contraction is dealt over the waves (gemm_split_body)
+constexpr int gemm_threads(int BM, int BN, int WM, int WN) { return BM == WM && BN == WN ? (BM == 64 ? Split<64>::W : Split<128>::W) * 64 : (BM / WM) * (BN / WN) * 64; }
 
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 ? 2 : 1)
+__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
 void gemm_kernel(const GemmArgs p) {
   const int T = p.tiles_m * p.tiles_n, lin = tile_of_block(T);
   if (lin >= T) return;
-  if constexpr (BM == 64) gemm_split_body<AKS, BKS, EPI>(p, lin);
+  if constexpr (BM == WM && BN == WN) gemm_split_body<BM, AKS, BKS, EPI>(p, lin);
   else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p, lin);
 }
 
 // Several weight gradients of one block in one launch: alone, each leaves part of the chip idle (the 13B shard's are 200,
 // 200, 60 and 160 tiles of 256x256 on 256 compute units), and a small block pays mostly for the launches.
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 ? 2 : 1)
+__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
 void gemm_group_kernel(const GemmGroup p) {
   const int T1 = p.first[GEMM_GROUP], T = T1 * p.splits;
   int lin = tile_of_block(T);
@@ -661,7 +674,7 @@ void gemm_group_kernel(const GemmGroup p) {
   a.b_bytes -= k0 * a.ldb * 2;
   a.K = min(a.K - (int)k0, p.k_per);
   a.C = static_cast<float*>(a.C) + range * p.part_stride;
-  if constexpr (BM == 64) gemm_split_body<AKS, BKS, EPI>(a, lin - p.first[i]);
+  if constexpr (BM == WM && BN == WN) gemm_split_body<BM, AKS, BKS, EPI>(a, lin - p.first[i]);
   else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(a, lin - p.first[i]);
 }
 
@@ -702,7 +715,7 @@ bool plan_tiles(GemmArgs& a) {
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int NT = gemm_threads(BM, BN, WM, WN);
-  constexpr int LDS = BM == 64 ? SPLIT_WAVES * SPLIT_STAGE : (RING_A * BM + RING_B * BN) * BK * 2;
+  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : (RING_A * BM + RING_B * BN) * BK * 2;
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
   if (n > 1 || products[0].splits > 1) {
     if constexpr (EPI == EPI_ACC_F32) {
@@ -759,6 +772,7 @@ hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t str
     case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_64x64:   return launch_cfg<64, 64, 64, 64, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_128x128_DEALT: return launch_cfg<128, 128, 128, 128, AKS, BKS, EPI>(a, n, stream);
     default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, n, stream);
   }
 }
@@ -771,13 +785,15 @@ thread_local int g_nheld = 0;
 
 // Time of a launch that has the chip to itself = 3 us + rounds of tiles on 256 compute units x time of a tile; time of a
 // tile = what its start and its epilogue take + what 64 elements of the contraction take (us; fitted to 77 shapes of 128 to
-// 4096 rows, 640 to 7168 columns, 256 to 16384 deep).  128x128 tiles run two to a unit; one that is alone is faster.
+// 4096 rows, 640 to 7168 columns, 256 to 16384 deep).  128x128 tiles run two to a unit; one that is alone is faster, less
+// so on long rows, whose loads come from further away.
 // A launch beside three or more others of its size pays for the work and the padding of ragged edges only, the other
 // launches fill the rest of its last round; beside one other, half way between.
-// 64x64 tiles deal the contraction over eight waves and sum in another order than the rest: whether they are taken
-// is decided as if nothing ran beside the launch, so that no bit of a result depends on the stream pool.  They win where
-// the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep 41 -> 19 us, 240 x 2688 x 7168
-// 55 -> 24, 256 x 1024 x 1024 10.0 -> 6.5; at 1024 x 2560 x 5120 the two forms meet.
+// The dealt forms (gemm_split_body) sum in another order than the rest: whether they are taken is decided as if nothing
+// ran beside the launch, so that no bit of a result depends on the stream pool, and products meant to run beside others
+// never take them.  They win where the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep
+// 41 -> 19 us, 240 x 2688 x 7168 82 -> 31, 1024 x 2688 x 7168 79 -> 57, 2048 x 1920 x 5120 55 -> 46, 256 x 1024 x 1024
+// 10.0 -> 6.5; about 3000 deep the plain 128x128 tile meets the dealt one.
 static int pick_tile(const GemmArgs* products, int n, int epi, int concurrency) {
   if (concurrency < 1) concurrency = 1;
   const bool swiglu = epi == EPI_SWIGLU;
@@ -803,7 +819,7 @@ static int pick_tile(const GemmArgs* products, int n, int epi, int concurrency) 
     const double tiles = tiles_of(c.bm, c.bn), fixed = c.fixed + extra * c.bm * c.bn / 65536, unit = fixed + c.per64 * it;
     double alone;
     if (c.id == GEMM_TILE_128x128) {
-      const double lone = fixed + 0.5 + 0.47 * it, full = floor(tiles / 512), rest = tiles - 512 * full;
+      const double lone = fixed + 0.5 + 0.47 * (it < 40 ? it : 40) + 0.66 * (it < 40 ? 0 : it - 40), full = floor(tiles / 512), rest = tiles - 512 * full;
       alone = full * 2 * unit + (rest == 0 ? 0.0 : rest <= 256 ? lone : 2 * unit);
     } else {
       alone = ceil(tiles / 256) * unit;
@@ -817,8 +833,10 @@ static int pick_tile(const GemmArgs* products, int n, int epi, int concurrency) 
     if (cost < best_cost * 0.999) { best_cost = cost; best = c.id; }
   }
   if (products[0].beside || splits > 1) return best;
-  const double split = ceil(tiles_of(64, 64) / 256) * (1.8 + (epi == EPI_SWIGLU ? 0.4 : 0.15) * extra + 1.4 * ((it + SPLIT_WAVES - 1) / SPLIT_WAVES));
-  return 3 + split < 0.95 * (3 + best_alone) ? GEMM_TILE_64x64 : best;
+  const double dealt64 = ceil(tiles_of(64, 64) / 256) * (1.8 + (epi == EPI_SWIGLU ? 0.4 : 0.15) * extra + 1.4 * ((it + 7) / 8));
+  const double dealt128 = ceil(tiles_of(128, 128) / 256) * (7.0 + 0.3 * extra + 0.40 * it);
+  if (3 + (dealt64 < dealt128 ? dealt64 : dealt128) >= 0.95 * (3 + best_alone)) return best;
+  return dealt64 < dealt128 ? GEMM_TILE_64x64 : GEMM_TILE_128x128_DEALT;
 }
 
 hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hipStream_t stream) {
