@@ -189,7 +189,7 @@ int validate(const domino_cfg* c, Layout* L) {
   l.dqkv = take(Mz * 3 * l.hl * 2);
   l.dot = take((size_t)l.b * l.nl * l.s * 4);
   {
-    const int nb = norm_bwd_blocks(l.Ms);
+    const int nb = norm_bwd_slice_blocks(l.M, l.Ms);
     // b_o and b_down come out of the Norm2 backward kernel (one partial row per workgroup), the others from column-sum passes
     const int rows[NAREAS] = {nb, nb, nb, nb, COLSUM_PARTS, nb, COLSUM_PARTS, nb};
     const int width[NAREAS] = {l.h, l.h, l.h, l.h, 3 * l.hl, l.h, l.fl, l.h};
@@ -718,6 +718,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     a.ga = ga; a.gb = gb2; a.x = xin; a.gamma = gamma; a.mean = rowf(mean, R); a.rstd = rowf(rstd, R); a.dres = dres; a.dx = out;
     a.part_g = B.red + L.area(kg, R.slice); a.part_b = B.red + L.area(kb, R.slice); a.rows = R.n; a.h = L.h; a.rms = rms;
     a.slice_rows = L.Ms;
+    a.slice_blocks = L.area_rows[kg];
     if (kres >= 0) { a.part_dres = B.red + L.area(kres, R.slice); a.part_dx = B.red + L.area(kdx, R.slice); }   // bias gradients of the two row-cut products
     LAUNCH(norm_bwd_launch(a, st), "norm backward");
     return DOMINO_OK;

@@ -798,8 +798,8 @@ static int pick_tile(const GemmArgs* products, int n, int epi, int concurrency) 
   if (concurrency < 1) concurrency = 1;
   const bool swiglu = epi == EPI_SWIGLU;
   struct Cand { int id, bm, bn; double fixed, per64; };
-  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 8.0, 1.06}, {GEMM_TILE_256x128, 256, 128, 4.0, 0.67},
-                               {GEMM_TILE_128x256, 128, 256, 4.0, 0.70}, {GEMM_TILE_128x128, 128, 128, 1.5, 0.40}};
+  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 8.0, 1.06}, {GEMM_TILE_256x128, 256, 128, 4.0, 0.70},
+                               {GEMM_TILE_128x256, 128, 256, 4.0, 0.73}, {GEMM_TILE_128x128, 128, 128, 1.5, 0.40}};
   // what the epilogue takes beyond storing bf16 sums, for 256x256 values: activations (vector ALUs), wider results
   const double extra = epi == EPI_BIAS_GELU ? 6.0 : epi == EPI_SWIGLU ? 5.0 : epi == EPI_DGELU ? 8.0 : epi == EPI_DSWIGLU ? 12.0 :
                        epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : 0.0;

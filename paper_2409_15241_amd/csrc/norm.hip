@@ -359,12 +359,11 @@ hipError_t fwd_dispatch(const NormFwdArgs& a, hipStream_t st) {
 template <bool RMS, bool SUMS>
 hipError_t bwd_dispatch(const NormBwdArgs& a, hipStream_t st) {
   const int nt = (((a.h >> 3) + 63) / 64) * 64;           // one thread per 16-byte chunk of a row
-  const int nb = norm_bwd_blocks(a.slice_rows), rpb = (a.slice_rows + nb - 1) / nb;
+  const int nb = a.slice_blocks, rpb = (a.slice_rows + nb - 1) / nb;
   const dim3 grid(nb * (a.rows / a.slice_rows)), block(nt);
-  // rows per iteration: two iterations' loads are held at once, within the registers the block size leaves
-  constexpr int RS = SUMS ? 2 : 4;
-  if (nt <= 256) hipLaunchKernelGGL((norm_bwd_kernel<256, RS, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
-  else if (nt <= 512) hipLaunchKernelGGL((norm_bwd_kernel<512, RS, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
+  // two rows per iteration (four took 245 registers and left one workgroup per compute unit), one where the block has 16 waves
+  if (nt <= 256) hipLaunchKernelGGL((norm_bwd_kernel<256, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
+  else if (nt <= 512) hipLaunchKernelGGL((norm_bwd_kernel<512, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
   else if (nt <= 768) hipLaunchKernelGGL((norm_bwd_kernel<768, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
   else hipLaunchKernelGGL((norm_bwd_kernel<1024, 1, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
   return hipGetLastError();
@@ -372,13 +371,8 @@ hipError_t bwd_dispatch(const NormBwdArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// Each workgroup walks its rows one after the other and leaves a partial row per gradient vector: 16 rows keep that
-// traffic below a tenth of the kernel's, and a few hundred rows are spread further while the chip has room (400 rows of
-// 1024: 25 workgroups took 10.9 us, nearly all of it the serial walk).
 int norm_bwd_blocks(int rows) {
-  int want = (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
-  const int fine = (rows + 3) / 4;
-  if (want < NORM_BWD_FEW) want = fine < NORM_BWD_FEW ? fine : NORM_BWD_FEW;
+  const int want = (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
   return want < NORM_BWD_MAX_BLOCKS ? want : NORM_BWD_MAX_BLOCKS;
 }
 
@@ -389,6 +383,7 @@ hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st) {
 hipError_t norm_bwd_launch(const NormBwdArgs& a0, hipStream_t st) {
   NormBwdArgs a = a0;
   if (a.slice_rows <= 0) a.slice_rows = a.rows;
+  if (a.slice_blocks <= 0) a.slice_blocks = norm_bwd_blocks(a.slice_rows);
   if (a.rows % a.slice_rows) return hipErrorInvalidValue;
   const bool sums = a.part_dres && a.part_dx && a.dres;
   if (a.rms) return sums ? bwd_dispatch<true, true>(a, st) : bwd_dispatch<true, false>(a, st);
