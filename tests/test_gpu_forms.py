@@ -1,0 +1,134 @@
+"""The forms that the launchers pick by size: products whose contraction is dealt over the waves of a workgroup, attention
+with few and with many workgroups, weight gradients over several contraction ranges.  Shapes at the edges of tiles and of
+the ranges in which a form is picked."""
+import numpy as np
+import pytest
+
+from oracle import domino_oracle as O
+from paper_2409_15241_amd import synth
+from test_gpu_kernels import BF16_OUT, _attn_inputs, dev, dom, host, relerr, rnd      # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# 64x64 tiles, eight waves: fewer operand tiles than waves, one more than waves, a tail of the contraction, ragged edges
+FEW = [(72, 136, 520), (200, 264, 72), (64, 64, 512), (400, 1032, 584)]
+# 128x128 tiles, four waves: deep products of more than two rounds of 64x64 tiles
+DEEP = [(1032, 2568, 4104), (1024, 2688, 4096)]
+
+
+def gpu(a, scale=1.0):
+    return torch.randn(a, device="cuda").mul_(scale).to(torch.bfloat16)
+
+
+def close(got, ref, bar=BF16_OUT):
+    return float((got.float() - ref).abs().max() / ref.abs().max()) < bar
+
+
+@pytest.mark.parametrize("M,N,K", FEW + DEEP)
+def test_products_with_a_dealt_contraction(dom, M, N, K):
+    torch.manual_seed(M + N + K)
+    A, W, bias = gpu((M, K)), gpu((K, N), 0.05), gpu(N, 0.5)
+    ref = A.float() @ W.float()
+    C, aux = torch.zeros((M, N), device="cuda", dtype=torch.bfloat16), torch.zeros((M, N), device="cuda", dtype=torch.bfloat16)
+    dom.domino_gemm(dom.GEMM_NN, dom.EPI_STORE, -1, A, K, W, N, C, N, M, N, K, bias=bias)
+    torch.cuda.synchronize()
+    assert close(C, ref + bias.float())
+    for tanh in (1, 0):
+        dom.domino_gemm(dom.GEMM_NN, dom.EPI_BIAS_GELU, -1, A, K, W, N, C, N, M, N, K, bias=bias, aux=aux, ldaux=N, gelu_tanh=tanh)
+        torch.cuda.synchronize()
+        pre = ref + bias.float()
+        assert close(aux, pre)
+        assert close(C, torch.nn.functional.gelu(pre, approximate="tanh" if tanh else "none"))
+    Wt = W.t().contiguous()                                        # [N][K]: the input-gradient layout
+    dom.domino_gemm(dom.GEMM_NT, dom.EPI_STORE, -1, A, K, Wt, K, C, N, M, N, K)
+    torch.cuda.synchronize()
+    assert close(C, ref)
+    pre = gpu((M, N), 1.5)
+    x = pre.float().requires_grad_()
+    for tanh in (1, 0):
+        g, = torch.autograd.grad(torch.nn.functional.gelu(x, approximate="tanh" if tanh else "none").sum(), x)
+        dom.domino_gemm(dom.GEMM_NT, dom.EPI_DGELU, -1, A, K, Wt, K, C, N, M, N, K, aux=pre, ldaux=N, gelu_tanh=tanh)
+        torch.cuda.synchronize()
+        assert close(C, ref * g)
+    At = A.t().contiguous()                                        # [K][M]: the weight-gradient layout, summed onto what is there
+    F = torch.ones((M, N), device="cuda")
+    dom.domino_gemm(dom.GEMM_TN, dom.EPI_ACC_F32, -1, At, M, W, N, F, N, M, N, K, beta=1)
+    torch.cuda.synchronize()
+    assert close(F, ref + 1.0, 1e-4)
+
+
+@pytest.mark.parametrize("M,fl,K", [(72, 96, 520), (400, 352, 584), (1032, 1376, 4104)])
+def test_gated_and_rotary_products_with_a_dealt_contraction(dom, M, fl, K):
+    torch.manual_seed(M + fl)
+    A, W = gpu((M, K)), gpu((K, 2 * fl), 0.05)
+    ref = A.float() @ W.float()
+    act, gu = torch.zeros((M, fl), device="cuda", dtype=torch.bfloat16), torch.zeros((M, 2 * fl), device="cuda", dtype=torch.bfloat16)
+    dom.domino_gemm(dom.GEMM_NN, dom.EPI_SWIGLU, -1, A, K, W, 2 * fl, act, fl, M, fl, K, aux=gu, ldaux=2 * fl, n_split=fl)
+    torch.cuda.synchronize()
+    assert close(gu, ref) and close(act, torch.nn.functional.silu(ref[:, :fl]) * ref[:, fl:])
+    dact, Wd = gpu((M, K)), gpu((fl, K), 0.05)
+    x = gu.float().requires_grad_()
+    d = dact.float() @ Wd.float().t()
+    g, = torch.autograd.grad((torch.nn.functional.silu(x[:, :fl]) * x[:, fl:] * d).sum(), x)
+    out = torch.zeros_like(gu)
+    dom.domino_gemm(dom.GEMM_NT, dom.EPI_DSWIGLU, -1, dact, K, Wd, K, out, 2 * fl, M, fl, K, aux=gu, ldaux=2 * fl, n_split=fl)
+    torch.cuda.synchronize()
+    assert close(out, g)
+    for d_head in (64, 128):
+        N = fl // 128 * 128 + 128
+        Wr = gpu((K, N), 0.05)
+        plain, turned = torch.zeros((M, N), device="cuda", dtype=torch.bfloat16), torch.zeros((M, N), device="cuda", dtype=torch.bfloat16)
+        dom.domino_gemm(dom.GEMM_NN, dom.EPI_STORE, -1, A, K, Wr, N, plain, N, M, N, K)
+        dom.domino_rope(plain, N, M, M, 0, 1, N // d_head, d_head, 10000.0, 0)
+        dom.domino_gemm_rope(-1, A, K, Wr, N, turned, N, M, N, K, M, d_head, N, 10000.0)
+        torch.cuda.synchronize()
+        assert close(turned, plain.float(), 1.5e-2)
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("b,s,nh", [(1, 129, 1), (2, 161, 3), (1, 1000, 2),                 # few workgroups: 32 positions each
+                                    (40, 200, 4), (35, 257, 2), (24, 63, 6)])               # many: 128 positions each
+def test_attention_with_few_and_with_many_workgroups(dom, d, b, s, nh):
+    rng = np.random.default_rng(d + s + nh)
+    hl = nh * d
+    qkv, q, k, v = _attn_inputs(rng, b, s, nh, d)
+    dctx = rnd(rng, (b * s, hl))
+    ctx = torch.zeros((b * s, hl), dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros((b, nh, s), dtype=torch.float32, device="cuda")
+    dqkv = torch.zeros((b * s, 3 * hl), dtype=torch.bfloat16, device="cuda")
+    dot = torch.zeros((b, nh, s), dtype=torch.float32, device="cuda")
+    qd = dev(qkv)
+    dom.domino_attention_fwd(qd, 3 * hl, b, s, nh, d, ctx, lse)
+    dom.domino_attention_bwd(qd, 3 * hl, ctx, dev(dctx), lse, dqkv, dot, b, s, nh, d)
+    torch.cuda.synchronize()
+    back = lambda m: m.transpose(0, 2, 1, 3).reshape(b * s, hl)
+    rctx, rlse = O.attention_fwd(q, k, v)
+    assert relerr(host(ctx), back(rctx)) < 1e-2
+    assert np.max(np.abs(lse.cpu().numpy() - rlse)) < 2e-3
+    refs = O.attention_bwd(dctx.reshape(b, s, nh, d).transpose(0, 2, 1, 3).astype(np.float64), q, k, v)
+    got = host(dqkv)
+    for i, ref in enumerate(refs):
+        assert relerr(got[:, i * hl:(i + 1) * hl], back(ref)) < 1.5e-2
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("seq", [1024, 1000])
+def test_weight_gradients_over_contraction_ranges(dom, seq, accumulate):
+    """A narrow block with many tokens: one launch over all rows in ranges, against one launch per matrix without."""
+    from paper_2409_15241_amd import harness as H
+    base = synth.ShardConfig(name="narrow", hidden=512, heads=8, tp=1, rank=0, ffn=2048, batch=16, seq=seq, p=1, q=1)
+    params = synth.make_rank_params(base, random_affine=True)
+    x, dy = synth.make_activations(base)
+    grads = []
+    for per_slice in (0, 1):
+        buf = H.LayerBuffers(base.replace(wgrad_per_slice=per_slice), params, x, dy, None, nstreams=2)
+        buf.forward()
+        buf.backward(accumulate=False)
+        if accumulate:
+            buf.backward(accumulate=True)
+        buf.sync()
+        grads.append({k: g.clone() for k, g in buf.grads.items() if g is not None})
+    for k, g in grads[0].items():
+        assert float((g - grads[1][k]).norm() / grads[1][k].norm()) < 1e-5, k
