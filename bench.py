@@ -28,9 +28,9 @@ DEFAULT_WORKLOAD = "gpt3-13b"      # the shard the throughput target is quoted o
 
 
 def gemm_flops_per_launch(sc):
-    """Algorithmic flops of one launch of each GEMM step class (one row slice; one column piece for
-    the two row-parallel products; the weight gradients contract over one slice's rows for p <= 2 and over all rows
-    of the block, in one launch per matrix, beyond that)."""
+    """Algorithmic flops of one product of each GEMM step class (one row slice; one column piece for
+    the two row-parallel products; the weight gradients contract over all rows of the block, or over one slice's with
+    --wgrad-per-slice)."""
     Ms = sc.tokens // sc.p
     Mw = wgrad_rows(sc)
     h, hl, fl, upc, hq = sc.hidden, sc.h_local, sc.f_local, sc.up_cols, sc.hidden // sc.q
@@ -43,8 +43,8 @@ def gemm_flops_per_launch(sc):
 
 
 def wgrad_rows(sc):
-    """Rows one weight-gradient launch contracts over (the library's rule: merged over the slices when p > 2)."""
-    return sc.tokens if sc.p > 2 and not sc.wgrad_per_slice else sc.tokens // sc.p
+    """Rows one weight-gradient launch contracts over (the library's rule: all of the block's)."""
+    return sc.tokens // sc.p if sc.wgrad_per_slice else sc.tokens
 
 
 def algorithmic_flops(sc):
@@ -196,7 +196,7 @@ def main():
     ap.add_argument("--p", type=int, default=None)
     ap.add_argument("--q", type=int, default=None)
     ap.add_argument("--wgrad-per-slice", action="store_true",
-                    help="weight gradients slice by slice behind each input gradient (the order of Sec. 4.1.2) also for p > 2")
+                    help="weight gradients slice by slice behind each input gradient (the order of Sec. 4.1.2)")
     ap.add_argument("--stack-layers", type=int, default=4,
                     help="with --layers 1: also time a stack of this many blocks (0 = skip) and report it under 'stack'")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -411,7 +411,7 @@ def main():
         "config": {"workload": sc.name, "hidden": sc.hidden, "heads": sc.heads, "tp": sc.tp, "rank": sc.rank,
                    "batch": sc.batch, "seq": sc.seq, "ffn": sc.ffn, "p": sc.p, "q": sc.q,
                    "arch": "llama" if sc.arch else "gpt", "streams": args.streams, "layers": args.layers,
-                   "weight_gradients": "slice by slice" if sc.p <= 2 or sc.wgrad_per_slice else "once per block over all rows"},
+                   "weight_gradients": "slice by slice" if sc.wgrad_per_slice else "once per block over all rows"},
         "pct_of_bf16_mfma_peak": 100.0 * value / BF16_MFMA_PEAK_TFLOPS,
         "algorithmic_gflop_per_step": flops / 1e9, "ms_per_step_median": ms_median, "ms_per_step_min": ms_min,
         "ms_per_step_max": ms_max, "fwd_ms": fwd_ms, "bwd_ms": bwd_ms,

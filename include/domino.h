@@ -54,8 +54,8 @@ typedef struct domino_cfg {
   int32_t gelu_tanh;                   /* 1 = tanh form (default), 0 = erf form */
   float norm_eps;                      /* inside the square root; 1e-5 */
   float rope_base;                     /* 10000 */
-  int32_t wgrad_per_slice;             /* 0 (default): with p > 2 the weight gradients of a block are formed once over all
-                                          rows after the last slice's input gradients (see domino_layer_bwd);
+  int32_t wgrad_per_slice;             /* 0 (default): the weight gradients of a block are formed once over all its rows
+                                          (see domino_layer_bwd);
                                           1: always slice by slice behind each input gradient, as Sec. 4.1.2 orders them */
 } domino_cfg;
 
@@ -122,10 +122,9 @@ int domino_layer_fwd(const domino_cfg* cfg, const domino_params* params,
  *   dln2_others, dln1_others: [b,s,h] or NULL: the other ranks' sums of the two backward all-reduces.
  *   dln2_partial, dln1_partial: out [b,s,h]: this rank's input gradients of MLP-up and QKV.
  *   dx: out [b,s,h]; must not overlap dy.   grads: fp32; accumulate != 0 adds to their contents, else overwrites.
- * Weight gradients: with p <= 2 (or cfg->wgrad_per_slice) each slice adds its share right behind its input gradient, in
- * slice order; with p > 2 one launch per matrix contracts over all rows of the block after the last slice's input gradients (every
- * further slice would otherwise read and rewrite the whole fp32 gradient; on one GPU that traffic is time), the four
- * launches spread over the slices' streams.  Either way the order of the sums is fixed: results are run-to-run
+ * Weight gradients: each matrix's is formed once over all rows of the block, after the input gradient of the same
+ * product (slice by slice, every further slice would read and rewrite the whole fp32 gradient; on one GPU that traffic is
+ * time).  With cfg->wgrad_per_slice each slice adds its share in a launch of its own, in slice order.  Either way the order of the sums is fixed: results are run-to-run
  * identical and do not depend on the stream pool. */
 int domino_layer_bwd(const domino_cfg* cfg, const domino_params* params, const void* saved,
                      const void* x, const void* dy,
@@ -185,8 +184,8 @@ typedef struct domino_stack_bwd_io {
 } domino_stack_bwd_io;
 
 /* Workspace bytes of a stack of nlayers blocks (1..1024): one block's workspace, one area of partial
- * vector-gradient sums per further block, two [b,s,h] gradients handed from block to block in turn and, for
- * p > 2, a second set of the activation gradients that the weight gradients read.  0 on error. */
+ * vector-gradient sums per further block, two [b,s,h] gradients handed from block to block in turn and,
+ * with more than one block, a second set of the activation gradients that the weight gradients read.  0 on error. */
 size_t domino_stack_workspace_bytes(const domino_cfg* cfg, int nlayers);
 
 /* Forward of nlayers blocks of the same configuration, params[l] and io[l] being block l's (host arrays of
@@ -202,9 +201,8 @@ int domino_stack_fwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
 /* Backward of the stack for L = sum(y_last * dy): blocks nlayers-1 .. 0, dx of one being dy of the one below
  * (kept in the workspace).  grads[l] are block l's gradients (host array of nlayers structs); accumulate as
  * in domino_layer_bwd.  Within a block the weight and vector gradients are summed as domino_layer_bwd sums them.
- * For p <= 2 a slice goes on from block to block without waiting for the others; for p > 2 the slices of a block
- * meet before its weight gradients (one launch per matrix over all rows), after which each stream goes on with
- * its slice of the block below while the other streams' launches still run (the tensors those read are kept
+ * The chain of input gradients goes on from block to block while the weight gradients of the block above still run on a
+ * stream of their own, where the pool has one to spare and the block is large enough (the tensors those read are kept
  * twice and used in turn).  Results are bitwise those of nlayers calls of domino_layer_bwd.
  * Under HIP graph capture (see domino_layer_fwd) a stack backward of more than one block with p > 2 returns
  * DOMINO_ERR_UNSUPPORTED before anything is enqueued: capture one domino_layer_bwd call per block instead. */

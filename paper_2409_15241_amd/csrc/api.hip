@@ -564,10 +564,10 @@ int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
 struct GradBufs { char *d_pre, *dx1, *dqkv; };
 GradBufs grad_bufs(const Layout& L, void* ws) { return {at(ws, L.d_pre), at(ws, L.dx1), at(ws, L.dqkv)}; }
 
-// With more than two row slices the weight gradients are not formed slice by slice: one launch per matrix contracts
-// over all rows of the block.  Slice by slice, every slice after the first reads and rewrites the whole fp32 gradient
-// (for the 13B shard 0.94 GB of 9.4 GB per step at p = 4) in launches a quarter as deep.  With one or two slices they
-// are summed over the slices in slice order.  cfg->wgrad_per_slice keeps the slice-by-slice order of Sec. 4.1.2 for any p.
+// The weight gradients are not formed slice by slice: every slice after the first would read and rewrite the whole fp32
+// gradient (for the 13B shard 0.94 GB of 9.4 GB per step at p = 4) in launches a p-th as deep.  With more than two slices
+// a product is handed over once, over all rows; with one or two slice by slice and joined there (GemmArgs::join), to the
+// same end.  cfg->wgrad_per_slice keeps the slice-by-slice launches of Sec. 4.1.2 for any p.
 inline bool merged_wgrads(const Layout& L) { return L.merged; }
 
 enum { WG_DOWN = 0, WG_UP, WG_OUT, WG_QKV, NWGRADS };
