@@ -612,7 +612,9 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
 // The vector gradients (norm gains and shifts, biases) from the partial rows that the slices' norm backwards and the
 // groups' column sums left: summed in index order, all slices in one launch (with cfg->wgrad_per_slice one per slice; the
 // groups' column sums then belong to the first).  Those of the MLP half are complete behind the Norm2 backward, the
-// others behind Norm1's.
+// others behind Norm1's.  All of them belong to the call that runs DOMINO_BWD_NORM1: only where that call holds the Norm2
+// backward too may it reduce the MLP half's early.  The calls of one backward need not agree on their streams (another
+// pool, one captured and the next not), so what an earlier part reduced could not be told from here.
 enum { VEC_MLP = 1, VEC_ATTN = 2, VEC_ALL = 3 };
 int vector_gradients(const Layout& L, const BwdLayer& B, int which, hipStream_t st) {
   const domino_grads* G = B.G;
@@ -703,6 +705,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     return DOMINO_OK;
   };
   hipStream_t side = S.side ? S.side_stream() : nullptr;
+  const bool mlp_vectors_early = S.side && (parts & DOMINO_BWD_ATTN) && (parts & DOMINO_BWD_NORM1);
 
   // the set of gradient tensors that this block writes was read by the weight gradients of the block two above, enqueued
   // a whole block ago: these waits order without stalling (on the side stream the last of them is behind the others)
@@ -762,7 +765,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       // 16384 tokens of Llama-2 7B; 13B equal; 2048 tokens of 13B in one group 701 -> 708)
       TRY(behind_groups(side));
       if (L.groups == 1) TRY(form({WG_OUT}, side));
-      TRY(vector_gradients(L, B, VEC_MLP, side));
+      if (mlp_vectors_early) TRY(vector_gradients(L, B, VEC_MLP, side));
     }
     TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // B6
       ProfScope ps(PC_DGRAD_OUT, st);
@@ -813,7 +816,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
   if (S.side) {
     if (parts & DOMINO_BWD_NORM1) {
       TRY(behind_groups(side, own ? &own->dx : nullptr));
-      TRY(vector_gradients(L, B, VEC_ATTN, side));
+      TRY(vector_gradients(L, B, mlp_vectors_early ? VEC_ATTN : VEC_ALL, side));
     }
   } else if (in_place) {
     if (parts & DOMINO_BWD_NORM1) TRY(vector_gradients(L, B, VEC_ALL, S.lane(0)));

@@ -8,6 +8,8 @@
 //     a chain of events (the race check), over the buffers the launchers are handed;
 //   - the weight gradients of a matrix, and the reductions of the vector gradients, are enqueued in slice order and
 //     ordered one after the other (the fixed accumulation order);
+//   - over the parts of one backward every gradient is formed exactly once, whatever pool each part is handed and whichever
+//     of them are captured;
 //   - a captured call uses no event twice, and pools outside domino_capture_supported() are refused while capturing.
 // Nothing here touches a GPU.  Exit status 0 = every expectation held.
 #include <algorithm>
@@ -443,6 +445,68 @@ static void run_case(int arch, int p, int q, int nstreams, bool capturing, int n
   g_capturing = false;
 }
 
+// One backward in its three parts, each call in a stream situation of its own (the pool it is handed, and whether it is
+// captured): whatever the situations, over the whole backward every gradient is formed exactly once.
+struct Situation { int nstreams; bool capturing; };
+static int run_mixed_parts(int arch, int p, int accumulate) {
+  const Situation some[] = {{1, false}, {4, false}, {4, true}};
+  const int bparts[3] = {DOMINO_BWD_MLP, DOMINO_BWD_ATTN, DOMINO_BWD_NORM1};
+  const domino_cfg c = make_cfg(arch, p, 1, false);
+  g_merged = p > 2;
+  g_rows = (long)c.batch * c.seq;
+  Buffers B((size_t)12 << 30);
+  Layer L = make_layer(B, c);
+  const size_t act = (size_t)c.batch * c.seq * c.hidden * 2, wsb = domino_workspace_bytes(&c);
+  void *x = B.take(act), *dy = B.take(act), *dx = B.take(act), *ws = B.take(wsb);
+  void* streams[4];
+  for (int k = 0; k < 4; ++k) streams[k] = reinterpret_cast<void*>((uintptr_t)0x1000 * (k + 1));
+  int cases = 0;
+  for (int sit = 0; sit < 27; ++sit, ++cases) {
+    const Situation at[3] = {some[sit / 9], some[sit / 3 % 3], some[sit % 3]};
+    char name[160];
+    std::snprintf(name, sizeof(name), "%s%s p=%d parts on %d%s, %d%s, %d%s streams", g_wide ? "wide " : "", arch ? "llama" : "gpt", p,
+                  at[0].nstreams, at[0].capturing ? " captured" : "", at[1].nstreams, at[1].capturing ? " captured" : "",
+                  at[2].nstreams, at[2].capturing ? " captured" : "");
+    g_case = name;
+    g_ops.clear();
+    for (int k = 0; k < 3; ++k) {
+      const int first = (int)g_ops.size();
+      g_capturing = at[k].capturing;
+      const int rc = domino_layer_bwd_parts(&c, &L.P, L.saved, x, dy, L.dln2_others, L.dln1_others, L.dln2_partial, L.dln1_partial, dx,
+                                            &L.G, accumulate, ws, wsb, streams, at[k].nstreams, bparts[k]);
+      g_capturing = false;
+      EXPECT(rc == DOMINO_OK, "part %d returned %d: %s", bparts[k], rc, domino_last_error());
+      check_call(first, static_cast<hipStream_t>(streams[0]), p, at[k].capturing);
+    }
+    const float* const vecs[] = {L.G.norm1_g, L.G.norm1_b, L.G.norm2_g, L.G.norm2_b, L.G.b_qkv, L.G.b_o, L.G.b_up, L.G.b_down};
+    const char* const names[] = {"norm1_g", "norm1_b", "norm2_g", "norm2_b", "b_qkv", "b_o", "b_up", "b_down"};
+    for (int v = 0; v < 8; ++v) {
+      if (!vecs[v]) continue;
+      long summed = 0;               // sets of partial rows that the vector's reductions take in
+      for (const Op& o : g_ops)
+        for (size_t r = 0; o.vec_reduce && r < o.regions.size(); ++r)
+          if (o.regions[r].write && o.regions[r].base == reinterpret_cast<const char*>(vecs[v]))
+            for (size_t k = r + 1; k < o.regions.size() && !o.regions[k].write; ++k) ++summed;
+      const bool by_group = v == 4 || v == 6;          // column sums: as many sets as launches that made them
+      long want = p;
+      if (by_group) {
+        want = 0;
+        for (const Op& o : g_ops)
+          if (o.what == "colsum_partial" && o.regions[0].cols == (v == 4 ? 3L * c.hidden / c.tp : (long)c.ffn / c.tp)) ++want;
+      }
+      EXPECT(summed == want, "%s takes in %ld sets of partial rows of %ld over the three parts", names[v], summed, want);
+    }
+    const float* const mats[] = {L.G.w_qkv, L.G.w_o, L.G.w_up, L.G.w_down};
+    for (const float* m : mats) {
+      long rows = 0;
+      for (const Op& o : g_ops)
+        if (o.wgrad_c == m) rows += o.regions[0].rows;
+      EXPECT(rows == g_rows, "a matrix' weight gradient contracts over %ld rows of %ld over the three parts", rows, g_rows);
+    }
+  }
+  return cases;
+}
+
 int main() {
   int cases = 0;
   for (bool wide : {false, true})
@@ -462,6 +526,13 @@ int main() {
             cases += 4;
           }
           if (p == 4 && q == 1) { run_case(arch, p, q, ns, false, 1, true, true); ++cases; }
+        }
+  for (bool wide : {false, true})
+    for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})
+      for (int p : {1, 2, 4})
+        for (int accumulate : {0, 1}) {
+          g_wide = wide;
+          cases += run_mixed_parts(arch, p, accumulate);
         }
   // the check must be able to fail: two launches on different fake streams that write one buffer, no event between them
   {
