@@ -95,10 +95,8 @@ struct Layout {
 
 enum { AREA_G1 = 0, AREA_B1, AREA_G2, AREA_B2, AREA_BQKV, AREA_BO, AREA_BUP, AREA_BDOWN, NAREAS };
 
-std::atomic<bool> g_prof_on{false};      // per-launch timing (domino_profile_enable)
-
 // Two rules say how a call spreads over its streams.  Both look at the block alone, so neither the arithmetic nor a bit
-// of any result depends on the stream pool.  In 256x256 tiles of the four weight gradients and of a product as wide as
+// of any result depends on the stream pool, and the parts of one backward agree on the layout of what they hand on.  In 256x256 tiles of the four weight gradients and of a product as wide as
 // the block:
 int tiles256(long m, long n) { return (int)((m + 255) / 256 * ((n + 255) / 256)); }
 int wgrad_tiles(const Layout& l) { return tiles256(l.fl, l.h) + tiles256(l.h, l.upc) + tiles256(l.hl, l.h) + tiles256(l.h, 3 * l.hl); }
@@ -122,11 +120,7 @@ bool wgrads_beside(const Layout& l) {
 // queues that a process gets by default, and slices that meet on a queue run one after the other), and only pays in
 // wide blocks where a group's launches fill the chip on their own: 13B with 8192 tokens, 640 tiles: 2202 us with two
 // groups, 2376 with one; with 2048 tokens, 160 tiles: 752 and 723; 2.7B with 32768 tokens: 3728 and 3391.
-// With per-launch timing on, p > 2 slices are always two groups, so that a timeline has launches to tell slices by.
-int most_groups(const Layout& l) { return l.p > 2 ? 2 : 1; }
-int row_groups(const Layout& l) {
-  return g_prof_on || (wgrads_beside(l) && tiles256(l.M, l.h) >= 512) ? most_groups(l) : 1;
-}
+int row_groups(const Layout& l) { return l.p > 2 && wgrads_beside(l) && tiles256(l.M, l.h) >= 512 ? 2 : 1; }
 
 int validate(const domino_cfg* c, Layout* L) {
   if (!c) return fail(DOMINO_ERR_NULL_POINTER, "cfg is NULL");
@@ -196,7 +190,7 @@ int validate(const domino_cfg* c, Layout* L) {
     size_t fo = 0;
     for (int k = 0; k < NAREAS; ++k) {
       l.area_off[k] = fo; l.area_rows[k] = rows[k]; l.area_n[k] = width[k];
-      fo += (size_t)rows[k] * width[k] * (k == AREA_BQKV || k == AREA_BUP ? most_groups(l) : l.p);
+      fo += (size_t)rows[k] * width[k] * (k == AREA_BQKV || k == AREA_BUP ? l.groups : l.p);
     }
     l.red_floats = (fo + 63) / 64 * 64;
   }
@@ -268,6 +262,7 @@ const char* const PROF_NAMES[PC_COUNT] = {
   "dgrad_down", "wgrad_down", "dgrad_up", "wgrad_up", "norm_bwd", "dgrad_out", "wgrad_out",
   "attn_bwd", "dgrad_qkv", "wgrad_qkv", "colsum"};
 
+std::atomic<bool> g_prof_on{false};      // per-launch timing (domino_profile_enable): adds event records to a call, changes none of its launches
 struct ProfRec { int cls; hipStream_t stream; hipEvent_t start, stop; };
 std::vector<ProfRec> g_prof_recs;
 std::vector<hipEvent_t> g_prof_free;

@@ -9,7 +9,8 @@
 //   - the weight gradients of a matrix, and the reductions of the vector gradients, are enqueued in slice order and
 //     ordered one after the other (the fixed accumulation order);
 //   - over the parts of one backward every gradient is formed exactly once, whatever pool each part is handed and whichever
-//     of them are captured;
+//     of them are captured or timed launch by launch;
+//   - timing a step launch by launch changes none of its launches;
 //   - a captured call uses no event twice, and pools outside domino_capture_supported() are refused while capturing.
 // Nothing here touches a GPU.  Exit status 0 = every expectation held.
 #include <algorithm>
@@ -445,11 +446,11 @@ static void run_case(int arch, int p, int q, int nstreams, bool capturing, int n
   g_capturing = false;
 }
 
-// One backward in its three parts, each call in a stream situation of its own (the pool it is handed, and whether it is
-// captured): whatever the situations, over the whole backward every gradient is formed exactly once.
-struct Situation { int nstreams; bool capturing; };
+// One backward in its three parts, each call in a situation of its own (the pool it is handed, whether it is captured,
+// whether per-launch timing is on): whatever the situations, over the whole backward every gradient is formed exactly once.
+struct Situation { int nstreams; bool capturing, timed; };
 static int run_mixed_parts(int arch, int p, int accumulate) {
-  const Situation some[] = {{1, false}, {4, false}, {4, true}};
+  const Situation some[] = {{1, false, false}, {4, false, false}, {4, true, false}, {4, false, true}};
   const int bparts[3] = {DOMINO_BWD_MLP, DOMINO_BWD_ATTN, DOMINO_BWD_NORM1};
   const domino_cfg c = make_cfg(arch, p, 1, false);
   g_merged = p > 2;
@@ -461,20 +462,22 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
   void* streams[4];
   for (int k = 0; k < 4; ++k) streams[k] = reinterpret_cast<void*>((uintptr_t)0x1000 * (k + 1));
   int cases = 0;
-  for (int sit = 0; sit < 27; ++sit, ++cases) {
-    const Situation at[3] = {some[sit / 9], some[sit / 3 % 3], some[sit % 3]};
+  for (int sit = 0; sit < 64; ++sit, ++cases) {
+    const Situation at[3] = {some[sit / 16], some[sit / 4 % 4], some[sit % 4]};
+    auto kind = [](const Situation& s) { return s.capturing ? " captured" : s.timed ? " timed" : ""; };
     char name[160];
     std::snprintf(name, sizeof(name), "%s%s p=%d parts on %d%s, %d%s, %d%s streams", g_wide ? "wide " : "", arch ? "llama" : "gpt", p,
-                  at[0].nstreams, at[0].capturing ? " captured" : "", at[1].nstreams, at[1].capturing ? " captured" : "",
-                  at[2].nstreams, at[2].capturing ? " captured" : "");
+                  at[0].nstreams, kind(at[0]), at[1].nstreams, kind(at[1]), at[2].nstreams, kind(at[2]));
     g_case = name;
     g_ops.clear();
     for (int k = 0; k < 3; ++k) {
       const int first = (int)g_ops.size();
       g_capturing = at[k].capturing;
+      domino_profile_enable(at[k].timed);
       const int rc = domino_layer_bwd_parts(&c, &L.P, L.saved, x, dy, L.dln2_others, L.dln1_others, L.dln2_partial, L.dln1_partial, dx,
                                             &L.G, accumulate, ws, wsb, streams, at[k].nstreams, bparts[k]);
       g_capturing = false;
+      domino_profile_enable(0);
       EXPECT(rc == DOMINO_OK, "part %d returned %d: %s", bparts[k], rc, domino_last_error());
       check_call(first, static_cast<hipStream_t>(streams[0]), p, at[k].capturing);
     }
@@ -507,6 +510,44 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
   return cases;
 }
 
+// Per-launch timing adds event records and nothing else: the launches of a timed step are those of an untimed one.
+static void run_timed(int arch, int p, int nstreams) {
+  char name[160];
+  std::snprintf(name, sizeof(name), "%s%s p=%d streams=%d timed", g_wide ? "wide " : "", arch ? "llama" : "gpt", p, nstreams);
+  g_case = name;
+  const domino_cfg c = make_cfg(arch, p, 2, false);
+  Buffers B((size_t)12 << 30);
+  Layer L = make_layer(B, c);
+  const size_t act = (size_t)c.batch * c.seq * c.hidden * 2, wsb = domino_workspace_bytes(&c);
+  void *x = B.take(act), *dy = B.take(act), *dx = B.take(act), *ws = B.take(wsb);
+  void* streams[8];
+  for (int k = 0; k < 8; ++k) streams[k] = reinterpret_cast<void*>((uintptr_t)0x1000 * (k + 1));
+  std::vector<Op> seen[2];
+  domino_profile_reset();
+  for (int timed = 0; timed < 2; ++timed) {
+    g_ops.clear();
+    domino_profile_enable(timed);
+    int rc = domino_layer_fwd(&c, &L.P, x, L.attn_others, L.mlp_others, L.attn_partial, L.mlp_partial, L.y, L.saved, ws, wsb, streams, nstreams);
+    EXPECT(rc == DOMINO_OK, "domino_layer_fwd returned %d: %s", rc, domino_last_error());
+    rc = domino_layer_bwd(&c, &L.P, L.saved, x, dy, L.dln2_others, L.dln1_others, L.dln2_partial, L.dln1_partial, dx, &L.G, 0, ws, wsb,
+                          streams, nstreams);
+    EXPECT(rc == DOMINO_OK, "domino_layer_bwd returned %d: %s", rc, domino_last_error());
+    domino_profile_enable(0);
+    EXPECT((domino_profile_records() > 0) == (timed == 1), "%d launches were timed", domino_profile_records());
+    for (const Op& o : g_ops)
+      if (o.kind == Op::LAUNCH) seen[timed].push_back(o);
+  }
+  domino_profile_reset();
+  EXPECT(seen[0].size() == seen[1].size(), "%zu launches with timing, %zu without", seen[1].size(), seen[0].size());
+  for (size_t i = 0; i < seen[0].size() && i < seen[1].size(); ++i) {
+    const Op &a = seen[0][i], &b = seen[1][i];
+    bool same = a.what == b.what && a.stream == b.stream && a.regions.size() == b.regions.size();
+    for (size_t r = 0; same && r < a.regions.size(); ++r)
+      same = a.regions[r].base == b.regions[r].base && a.regions[r].rows == b.regions[r].rows && a.regions[r].cols == b.regions[r].cols;
+    EXPECT(same, "launch %zu differs with timing (%s, %s)", i, a.what.c_str(), b.what.c_str());
+  }
+}
+
 int main() {
   int cases = 0;
   for (bool wide : {false, true})
@@ -534,6 +575,10 @@ int main() {
           g_wide = wide;
           cases += run_mixed_parts(arch, p, accumulate);
         }
+  for (bool wide : {false, true})
+    for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})
+      for (int p : {1, 2, 4, 8})
+        for (int ns : {1, 2, 4}) { g_wide = wide; run_timed(arch, p, ns); ++cases; }
   // the check must be able to fail: two launches on different fake streams that write one buffer, no event between them
   {
     g_case = "planted race";

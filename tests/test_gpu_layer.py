@@ -317,7 +317,10 @@ def test_profile_records_give_the_timeline_of_a_step(H):
         D.domino_profile_enable(False)
     n = D.domino_profile_records()
     recs = [D.domino_profile_record(i) for i in range(n)]
-    assert n == sum(D.domino_profile_read(c)[1] for c in range(D.domino_profile_classes())) > 40
+    assert n == sum(D.domino_profile_read(c)[1] for c in range(D.domino_profile_classes()))
+    # timing does not cut the block into more launches than it has: every step of the path is there, all slices in one launch
+    steps = {D.domino_profile_name(c) for c in range(D.domino_profile_classes())}
+    assert {r[0] for r in recs} == {s for s in steps if s != "rope"} and n >= len(steps) - 1
     handles = {s.cuda_stream for s in buf.streams}
     last = {}
     for name, st, a, b in recs:
