@@ -6,8 +6,9 @@
 //     capture this is how a stream joins the capture), and no wait refers to an event not yet recorded in the call;
 //   - any two launches that touch overlapping memory, at least one of them writing, are ordered by stream order or by
 //     a chain of events (the race check), over the buffers the launchers are handed;
-//   - the weight gradients of a matrix, and the reductions of the vector gradients, are enqueued in slice order and
-//     ordered one after the other (the fixed accumulation order);
+//   - the weight gradients of a matrix, and the reductions of the vector gradients, are one launch over all rows, or
+//     enqueued in slice order and ordered one after the other (the fixed accumulation order);
+//   - the vector gradients sum partial rows that were written in this backward, and no launch writes over another's;
 //   - over the parts of one backward every gradient is formed exactly once, whatever pool each part is handed and whichever
 //     of them are captured or timed launch by launch;
 //   - timing a step launch by launch changes none of its launches;
@@ -42,11 +43,14 @@ struct Op {
   void* event;                       // RECORD / WAIT
   std::string what;                  // LAUNCH: step name
   std::vector<Region> regions;
-  float* wgrad_c = nullptr;          // LAUNCH of a weight gradient: the matrix it accumulates into
+  struct Product { float* c; const char* a; long rows; int beta; };
+  std::vector<Product> products;     // LAUNCH of weight gradients: the matrices they go into, the rows they contract over
   bool vec_reduce = false;           // LAUNCH of the vector-gradient reduction
 };
 static std::vector<Op> g_ops;
-static bool g_merged = false;         // the configuration under test forms its weight gradients once per block
+static bool g_per_slice = false;      // the configuration under test forms its weight gradients slice by slice
+static bool g_merged = false;         // ... hands them over once per block (refused in a captured stack of several blocks)
+static bool g_accumulate = false;
 static long g_rows = 0;              // rows (batch x sequence) of the configuration under test
 static bool g_capturing = false;
 static int g_failures = 0;
@@ -65,9 +69,9 @@ static std::string g_case;
 static Region reg(const void* p, long ld, long rows, long cols, int esz, bool write) {
   return Region{static_cast<const char*>(p), ld, rows, cols, esz, write};
 }
-static void launch(hipStream_t st, const char* what, std::vector<Region> r, float* wgrad_c = nullptr, bool vec = false) {
+static void launch(hipStream_t st, const char* what, std::vector<Region> r, std::vector<Op::Product> products = {}, bool vec = false) {
   Op o;
-  o.kind = Op::LAUNCH; o.stream = st; o.event = nullptr; o.what = what; o.wgrad_c = wgrad_c; o.vec_reduce = vec;
+  o.kind = Op::LAUNCH; o.stream = st; o.event = nullptr; o.what = what; o.products = std::move(products); o.vec_reduce = vec;
   for (auto& x : r)
     if (x.base) o.regions.push_back(x);
   g_ops.push_back(std::move(o));
@@ -100,23 +104,65 @@ void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) 
 
 // ------------------------------------------------------------------------------------------- launcher stand-ins
 static const char* gemm_name(int layout, int epi) {
-  if (layout == GEMM_TN) return "wgrad";
   if (layout == GEMM_NT) return epi == EPI_STORE ? "dgrad" : "dgrad+act'";
   return epi == EPI_STORE ? "gemm" : epi == EPI_ROPE ? "gemm+rope" : "gemm+act";
 }
-hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int, hipStream_t st) {
-  std::vector<Region> r;
-  const bool glu = epi == EPI_SWIGLU || epi == EPI_DSWIGLU;
-  if (layout == GEMM_TN) r.push_back(reg(a.A, a.lda, a.K, a.M, 2, false)); else r.push_back(reg(a.A, a.lda, a.M, a.K, 2, false));
-  if (layout == GEMM_NT) r.push_back(reg(a.B, a.ldb, a.N, a.K, 2, false));
-  else r.push_back(reg(a.B, a.ldb, a.K, epi == EPI_SWIGLU ? 2L * a.n_split : a.N, 2, false));
-  r.push_back(reg(a.C, a.ldc, a.M, epi == EPI_DSWIGLU ? 2L * a.n_split : a.N, layout == GEMM_TN ? 4 : 2, true));
-  if (a.bias) r.push_back(reg(a.bias, a.N, 1, a.N, 2, false));
-  if (a.aux) r.push_back(reg(a.aux, a.ldaux, a.M, glu ? 2L * a.n_split : a.N, 2, epi == EPI_BIAS_GELU || epi == EPI_SWIGLU));
-  launch(st, gemm_name(layout, epi), r, layout == GEMM_TN ? static_cast<float*>(a.C) : nullptr);
+// products held back by GemmArgs::join, and the stream of the first
+static std::vector<GemmArgs> g_held;
+static hipStream_t g_held_on;
+static long g_range_launches = 0;     // launches over several contraction ranges, in all cases
+static hipError_t launch_weight_gradients(const std::vector<GemmArgs>& held, hipStream_t st) {
+  std::vector<Region> r, sums;
+  std::vector<Op::Product> products;
+  const int splits = held[0].splits > 1 ? held[0].splits : 1;
+  long floats = 0;
+  for (const GemmArgs& a : held) floats += (long)a.M * a.N;
+  for (const GemmArgs& a : held) {
+    r.push_back(reg(a.A, a.lda, a.K, a.M, 2, false));
+    r.push_back(reg(a.B, a.ldb, a.K, a.N, 2, false));
+    (splits > 1 ? sums : r).push_back(reg(a.C, a.ldc, a.M, a.N, 4, true));
+    products.push_back({static_cast<float*>(a.C), static_cast<const char*>(a.A), a.K, a.beta});
+    EXPECT(a.K == held[0].K && a.beta == held[0].beta && a.splits == held[0].splits, "products of one launch differ in depth, ranges or accumulation");
+  }
+  if (splits == 1) { launch(st, "wgrad", r, products); return hipSuccess; }
+  ++g_range_launches;
+  EXPECT(held[0].split_ws != nullptr, "%d contraction ranges without memory for their sums", splits);
+  r.push_back(reg(held[0].split_ws, floats, splits, floats, 4, true));
+  launch(st, "wgrad ranges", r, products);
+  sums.push_back(reg(held[0].split_ws, floats, splits, floats, 4, false));
+  launch(st, "wgrad sum of ranges", sums);
   return hipSuccess;
 }
-int gemm_pick_tile(int, int, int) { return 0; }
+hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int, hipStream_t st) {
+  if (layout == GEMM_TN) {
+    if (g_held.empty()) g_held_on = st;
+    EXPECT(g_held_on == st, "products of one launch are handed over on two streams");
+    if (!g_held.empty() && g_held.back().C == a.C) {       // the next rows of the same product
+      GemmArgs& h = g_held.back();
+      EXPECT(a.beta && static_cast<const char*>(h.A) + h.K * h.lda * 2 == a.A && static_cast<const char*>(h.B) + h.K * h.ldb * 2 == a.B,
+             "a product into the same matrix does not continue the one before it");
+      h.K += a.K;
+    } else {
+      EXPECT((int)g_held.size() < GEMM_GROUP, "more than %d products held back", GEMM_GROUP);
+      g_held.push_back(a);
+    }
+    if (a.join) return hipSuccess;
+    const std::vector<GemmArgs> held = std::move(g_held);
+    g_held.clear();
+    return launch_weight_gradients(held, st);
+  }
+  EXPECT(g_held.empty(), "a product is launched while weight gradients are held back");
+  std::vector<Region> r;
+  const bool glu = epi == EPI_SWIGLU || epi == EPI_DSWIGLU;
+  r.push_back(reg(a.A, a.lda, a.M, a.K, 2, false));
+  if (layout == GEMM_NT) r.push_back(reg(a.B, a.ldb, a.N, a.K, 2, false));
+  else r.push_back(reg(a.B, a.ldb, a.K, epi == EPI_SWIGLU ? 2L * a.n_split : a.N, 2, false));
+  r.push_back(reg(a.C, a.ldc, a.M, epi == EPI_DSWIGLU ? 2L * a.n_split : a.N, 2, true));
+  if (a.bias) r.push_back(reg(a.bias, a.N, 1, a.N, 2, false));
+  if (a.aux) r.push_back(reg(a.aux, a.ldaux, a.M, glu ? 2L * a.n_split : a.N, 2, epi == EPI_BIAS_GELU || epi == EPI_SWIGLU));
+  launch(st, gemm_name(layout, epi), r);
+  return hipSuccess;
+}
 hipError_t rope_launch(void* m, long ld, int rows, int, int col0, int nblocks, int heads, int d, float, int, hipStream_t st) {
   launch(st, "rope", {reg(static_cast<char*>(m) + 2L * col0, ld, rows, (long)nblocks * heads * d, 2, true)});
   return hipSuccess;
@@ -133,7 +179,9 @@ hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st) {
   return hipSuccess;
 }
 hipError_t norm_bwd_launch(const NormBwdArgs& a, hipStream_t st) {
-  const long nb = norm_bwd_blocks(a.rows);
+  // one partial row per workgroup: slice_blocks of them for each slice
+  const int slice_rows = a.slice_rows > 0 ? a.slice_rows : a.rows;
+  const long nb = (long)(a.slice_blocks > 0 ? a.slice_blocks : norm_bwd_blocks(slice_rows)) * (a.rows / slice_rows);
   launch(st, "norm_bwd", {reg(a.ga, a.h, a.rows, a.h, 2, false), reg(a.gb, a.h, a.rows, a.h, 2, false),
                           reg(a.x, a.h, a.rows, a.h, 2, false), reg(a.dres, a.h, a.rows, a.h, 2, false),
                           reg(a.mean, a.rows, 1, a.rows, 4, false), reg(a.rstd, a.rows, 1, a.rows, 4, false),
@@ -163,14 +211,33 @@ hipError_t colsum_partial_launch(const void* g, long ld, int rows, int n, float*
   launch(st, "colsum_partial", {reg(g, ld, rows, n, 2, false), reg(part, n, COLSUM_PARTS, n, 4, true)});
   return hipSuccess;
 }
-hipError_t colsum_finish_jobs_launch(const ColsumJobs& jobs, int njobs, int, hipStream_t st) {
-  std::vector<Region> r;
-  for (int k = 0; k < njobs; ++k) {
-    r.push_back(reg(jobs.job[k].out, jobs.job[k].n, 1, jobs.job[k].n, 4, true));
-    for (int g = 0; g < jobs.job[k].nouter; ++g)
-      r.push_back(reg(jobs.job[k].part + g * jobs.job[k].ostride, jobs.job[k].stride, jobs.job[k].nparts, jobs.job[k].n, 4, false));
+// jobs held back by ColsumJobs::join, and their stream
+static std::vector<ColsumJob> g_jobs;
+static hipStream_t g_jobs_on;
+hipError_t colsum_finish_jobs_launch(const ColsumJobs& jobs, int njobs, int accumulate, hipStream_t st) {
+  if (g_jobs.empty()) {
+    g_jobs.assign(jobs.job, jobs.job + njobs);
+    g_jobs_on = st;
+  } else {
+    EXPECT(g_jobs_on == st && accumulate, "a continued reduction is on another stream, or does not accumulate");
+    for (int k = 0; k < njobs; ++k) {
+      bool found = false;
+      for (ColsumJob& h : g_jobs)
+        if (h.out == jobs.job[k].out) {
+          found = h.part + h.nouter * h.ostride == jobs.job[k].part && h.nparts == jobs.job[k].nparts && h.ostride == jobs.job[k].ostride;
+          h.nouter += jobs.job[k].nouter;
+        }
+      EXPECT(found, "a reduction does not continue one that is held back");
+    }
   }
-  launch(st, "vector_gradients", r, nullptr, true);
+  if (jobs.join) return hipSuccess;
+  std::vector<Region> r;
+  for (const ColsumJob& j : g_jobs) {
+    r.push_back(reg(j.out, j.n, 1, j.n, 4, true));
+    for (int g = 0; g < j.nouter; ++g) r.push_back(reg(j.part + g * j.ostride, j.stride, j.nparts, j.n, 4, false));
+  }
+  g_jobs.clear();
+  launch(st, "vector_gradients", r, {}, true);
   return hipSuccess;
 }
 hipError_t colsum_finish_launch(const float* part, int nparts, int n, float* out, int, hipStream_t st) {
@@ -228,6 +295,36 @@ static Analysis analyse(const std::vector<Op>& ops, int first) {
   return A;
 }
 
+// What the vector gradients take in, over operations [first, end) of g_ops that hold a whole backward: rows of partial sums
+// written earlier, each by one launch only (two launches whose partial rows overlap would have outgrown their area).
+static void check_partial_rows(int first) {
+  std::vector<std::pair<const char*, const char*>> written;
+  auto range = [](const Region& r) { return std::make_pair(r.base, r.base + ((r.rows - 1) * r.ld + r.cols) * r.esz); };
+  for (int i = first; i < (int)g_ops.size(); ++i) {
+    const Op& o = g_ops[i];
+    if (o.kind != Op::LAUNCH) continue;
+    if (o.what == "norm_bwd" || o.what == "colsum_partial")
+      for (const Region& r : o.regions)
+        if (r.write && r.esz == 4) {
+          const auto w = range(r);
+          for (const auto& v : written)
+            EXPECT(w.second <= v.first || v.second <= w.first, "launch %d (%s) writes over partial rows of another launch", i, o.what.c_str());
+          written.push_back(w);
+        }
+    if (!o.vec_reduce) continue;
+    for (const Region& r : o.regions) {
+      if (r.write) continue;
+      auto want = range(r);
+      for (bool more = true; more && want.first < want.second;) {
+        more = false;
+        for (const auto& v : written)
+          if (v.first <= want.first && want.first < v.second) { want.first = v.second; more = true; }
+      }
+      EXPECT(want.first >= want.second, "launch %d sums partial rows that nothing has written", i);
+    }
+  }
+}
+
 // one library call = operations [first, end) of g_ops
 static void check_call(int first, hipStream_t s0, int p, bool capturing) {
   const int n = (int)g_ops.size();
@@ -273,25 +370,33 @@ static void check_call(int first, hipStream_t s0, int p, bool capturing) {
   // fixed accumulation order: per matrix, and for the vector gradients, enqueue order = slice order, each ordered after the one before
   std::map<const void*, std::vector<int>> per_matrix, per_vector;     // keyed by the gradient tensor (one set per block of a stack)
   for (int i : L) {
-    if (g_ops[i].wgrad_c) per_matrix[g_ops[i].wgrad_c].push_back(i);
+    for (const Op::Product& w : g_ops[i].products) per_matrix[w.c].push_back(i);
     if (g_ops[i].vec_reduce)
       for (const Region& r : g_ops[i].regions)
         if (r.write) { per_vector[r.base].push_back(i); break; }
   }
   for (auto& kv : per_matrix) {
-    // slice by slice for one or two slices, one launch over all rows beyond that; either way every row exactly once
-    EXPECT((int)kv.second.size() == (g_merged ? 1 : p), "%zu weight-gradient launches into one matrix for %d slices", kv.second.size(), p);
+    // one launch over all rows, or slice by slice where the configuration asks for it; either way every row exactly once
+    EXPECT((int)kv.second.size() == (g_per_slice ? p : 1), "%zu weight-gradient launches into one matrix for %d slices", kv.second.size(), p);
+    auto product = [&](int i) {
+      for (const Op::Product& w : g_ops[i].products)
+        if (w.c == kv.first) return w;
+      return Op::Product{};
+    };
     long rows = 0;
-    for (int i : kv.second) rows += g_ops[i].regions[0].rows;
+    for (int i : kv.second) rows += product(i).rows;
     EXPECT(rows == g_rows, "the weight-gradient launches into one matrix contract over %ld rows of %ld", rows, g_rows);
-    for (size_t k = 1; k < kv.second.size(); ++k)
+    for (size_t k = 0; k < kv.second.size(); ++k)
+      EXPECT(product(kv.second[k]).beta == (k > 0 || g_accumulate ? 1 : 0), "launch %zu into a matrix %s what it holds", k,
+             product(kv.second[k]).beta ? "adds to" : "overwrites");
+    // slice by slice: rows of slice k start k * Ms rows into the activation operand, so the k-th launch must be slice k's
+    for (size_t k = 1; k < kv.second.size(); ++k) {
       EXPECT(A.hb(kv.second[k - 1], kv.second[k]), "weight gradients %d and %d into one matrix are not ordered", kv.second[k - 1], kv.second[k]);
-    // rows of slice k start k * Ms rows into the activation operand: the k-th launch must be slice k's
-    for (size_t k = 1; k < kv.second.size(); ++k)
-      EXPECT(g_ops[kv.second[k]].regions[0].base > g_ops[kv.second[k - 1]].regions[0].base, "weight gradients into one matrix are not enqueued in slice order");
+      EXPECT(product(kv.second[k]).a > product(kv.second[k - 1]).a, "weight gradients into one matrix are not enqueued in slice order");
+    }
   }
   for (auto& kv : per_vector) {
-    EXPECT((int)kv.second.size() == (g_merged ? 1 : p) || kv.second.empty(), "%zu vector-gradient reductions for %d slices", kv.second.size(), p);
+    EXPECT((int)kv.second.size() == (g_per_slice ? p : 1), "%zu vector-gradient reductions for %d slices", kv.second.size(), p);
     long groups = 0;                 // every slice's partial rows exactly once (read off the launch's first vector, a norm gain)
     for (int i : kv.second) {
       const std::vector<Region>& r = g_ops[i].regions;
@@ -319,15 +424,21 @@ struct Buffers {                                    // addresses only: one arena
   }
 };
 
-// a block wide enough that row groups run side by side and the weight gradients beside them (the small one keeps to one stream)
-static bool g_wide = false;
+// Blocks of three sizes: a small one, which keeps to one stream; one of few weight-gradient tiles and many rows, whose
+// gradients are formed over several contraction ranges; one so wide that row groups run side by side and the weight
+// gradients beside them.
+enum { SMALL, DEEP, WIDE };
+static const int SIZES[] = {SMALL, DEEP, WIDE};
+static const char* const SIZE_NAMES[] = {"", "deep ", "wide "};
+static int g_size = SMALL;
 
 static domino_cfg make_cfg(int arch, int p, int q, bool per_slice) {
   domino_cfg c{};
   c.wgrad_per_slice = per_slice ? 1 : 0;
   c.hidden = 256; c.heads = 4; c.tp = 2; c.rank = 1; c.p = p; c.q = q; c.batch = 8; c.seq = 64;
   c.ffn = arch == DOMINO_ARCH_LLAMA ? 704 : 1024;
-  if (g_wide) { c.hidden = 4096; c.heads = 32; c.tp = 4; c.seq = 1024; c.ffn = 16384; }
+  if (g_size == DEEP) { c.hidden = 2560; c.heads = 32; c.tp = 8; c.seq = 2048; c.ffn = 10240; }
+  if (g_size == WIDE) { c.hidden = 4096; c.heads = 32; c.tp = 4; c.seq = 1024; c.ffn = 16384; }
   c.arch = arch; c.gelu_tanh = 1; c.norm_eps = 1e-5f; c.rope_base = 10000.0f;
   return c;
 }
@@ -362,11 +473,13 @@ static Layer make_layer(Buffers& B, const domino_cfg& c) {
 
 static void run_case(int arch, int p, int q, int nstreams, bool capturing, int nlayers, bool parts, bool per_slice = false) {
   char name[160];
-  std::snprintf(name, sizeof(name), "%s%s p=%d q=%d streams=%d%s layers=%d%s", g_wide ? "wide " : "", arch ? "llama" : "gpt", p, q, nstreams,
+  std::snprintf(name, sizeof(name), "%s%s p=%d q=%d streams=%d%s layers=%d%s", SIZE_NAMES[g_size], arch ? "llama" : "gpt", p, q, nstreams,
                 capturing ? " capturing" : "", nlayers, parts ? (per_slice ? " parts per-slice" : " parts") : (per_slice ? " per-slice" : ""));
   g_case = name;
   const domino_cfg c = make_cfg(arch, p, q, per_slice);
   g_merged = p > 2 && !per_slice;
+  g_per_slice = per_slice;
+  g_accumulate = false;
   g_rows = (long)c.batch * c.seq;
   if (domino_validate_cfg(&c) != DOMINO_OK) { EXPECT(false, "configuration rejected: %s", domino_last_error()); return; }
   Buffers B((size_t)12 << 30);
@@ -401,6 +514,7 @@ static void run_case(int arch, int p, int q, int nstreams, bool capturing, int n
                             ws, wsb, streams.data(), nstreams), "domino_layer_bwd");
       // a capture holds the forward and the backward: checked as one unit (events must not repeat across the two calls)
       check_call(capturing ? first : mid, s0, p, capturing);
+      check_partial_rows(mid);
     } else {
       const int fparts[2] = {DOMINO_FWD_ATTN, DOMINO_FWD_MLP};
       for (int k = 0; k < 2; ++k) {
@@ -416,6 +530,7 @@ static void run_case(int arch, int p, int q, int nstreams, bool capturing, int n
                                     0, ws, wsb, streams.data(), nstreams, bparts[k]), "domino_layer_bwd_parts");
         check_call(first, s0, p, false);
       }
+      check_partial_rows(0);
     }
   } else {
     std::vector<domino_params> P;
@@ -441,6 +556,7 @@ static void run_case(int arch, int p, int q, int nstreams, bool capturing, int n
     } else {
       call(rc, "domino_stack_bwd");
       check_call(capturing ? first : mid, s0, p, capturing);
+      check_partial_rows(mid);
     }
   }
   g_capturing = false;
@@ -454,6 +570,8 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
   const int bparts[3] = {DOMINO_BWD_MLP, DOMINO_BWD_ATTN, DOMINO_BWD_NORM1};
   const domino_cfg c = make_cfg(arch, p, 1, false);
   g_merged = p > 2;
+  g_per_slice = false;
+  g_accumulate = accumulate != 0;
   g_rows = (long)c.batch * c.seq;
   Buffers B((size_t)12 << 30);
   Layer L = make_layer(B, c);
@@ -466,7 +584,7 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
     const Situation at[3] = {some[sit / 16], some[sit / 4 % 4], some[sit % 4]};
     auto kind = [](const Situation& s) { return s.capturing ? " captured" : s.timed ? " timed" : ""; };
     char name[160];
-    std::snprintf(name, sizeof(name), "%s%s p=%d parts on %d%s, %d%s, %d%s streams", g_wide ? "wide " : "", arch ? "llama" : "gpt", p,
+    std::snprintf(name, sizeof(name), "%s%s p=%d parts on %d%s, %d%s, %d%s streams", SIZE_NAMES[g_size], arch ? "llama" : "gpt", p,
                   at[0].nstreams, kind(at[0]), at[1].nstreams, kind(at[1]), at[2].nstreams, kind(at[2]));
     g_case = name;
     g_ops.clear();
@@ -499,11 +617,13 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
       }
       EXPECT(summed == want, "%s takes in %ld sets of partial rows of %ld over the three parts", names[v], summed, want);
     }
+    check_partial_rows(0);
     const float* const mats[] = {L.G.w_qkv, L.G.w_o, L.G.w_up, L.G.w_down};
     for (const float* m : mats) {
       long rows = 0;
       for (const Op& o : g_ops)
-        if (o.wgrad_c == m) rows += o.regions[0].rows;
+        for (const Op::Product& w : o.products)
+          if (w.c == m) rows += w.rows;
       EXPECT(rows == g_rows, "a matrix' weight gradient contracts over %ld rows of %ld over the three parts", rows, g_rows);
     }
   }
@@ -513,7 +633,7 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
 // Per-launch timing adds event records and nothing else: the launches of a timed step are those of an untimed one.
 static void run_timed(int arch, int p, int nstreams) {
   char name[160];
-  std::snprintf(name, sizeof(name), "%s%s p=%d streams=%d timed", g_wide ? "wide " : "", arch ? "llama" : "gpt", p, nstreams);
+  std::snprintf(name, sizeof(name), "%s%s p=%d streams=%d timed", SIZE_NAMES[g_size], arch ? "llama" : "gpt", p, nstreams);
   g_case = name;
   const domino_cfg c = make_cfg(arch, p, 2, false);
   Buffers B((size_t)12 << 30);
@@ -550,12 +670,12 @@ static void run_timed(int arch, int p, int nstreams) {
 
 int main() {
   int cases = 0;
-  for (bool wide : {false, true})
+  for (int size : SIZES)
   for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})
     for (int p : {1, 2, 4, 8})
       for (int q : {1, 2})
         for (int ns = 1; ns <= 8; ++ns) {
-          g_wide = wide;
+          g_size = size;
           run_case(arch, p, q, ns, false, 1, false); ++cases;
           run_case(arch, p, q, ns, true, 1, false); ++cases;
           // four blocks: the tensors handed from block to block, taken in turn, come round again
@@ -568,17 +688,18 @@ int main() {
           }
           if (p == 4 && q == 1) { run_case(arch, p, q, ns, false, 1, true, true); ++cases; }
         }
-  for (bool wide : {false, true})
+  for (int size : SIZES)
     for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})
       for (int p : {1, 2, 4})
         for (int accumulate : {0, 1}) {
-          g_wide = wide;
+          g_size = size;
           cases += run_mixed_parts(arch, p, accumulate);
         }
-  for (bool wide : {false, true})
+  for (int size : SIZES)
     for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})
       for (int p : {1, 2, 4, 8})
-        for (int ns : {1, 2, 4}) { g_wide = wide; run_timed(arch, p, ns); ++cases; }
+        for (int ns : {1, 2, 4}) { g_size = size; run_timed(arch, p, ns); ++cases; }
+  EXPECT(g_range_launches > 0, "no case formed its weight gradients over several contraction ranges");
   // the check must be able to fail: two launches on different fake streams that write one buffer, no event between them
   {
     g_case = "planted race";
@@ -607,6 +728,15 @@ int main() {
     (void)hipEventRecord(e, b);
     (void)hipStreamWaitEvent(a, e, 0);
     check_call(0, a, 1, false);
+    // the check of partial rows must be able to fail, too: a reduction of four rows where three were written
+    g_ops.clear();
+    const int had = g_failures;
+    launch(a, "colsum_partial", {reg(buf, 16, 3, 16, 4, true)});
+    launch(a, "vector_gradients", {reg(buf + 2048, 16, 1, 16, 4, true), reg(buf, 16, 4, 16, 4, false)}, {}, true);
+    std::printf("(the next FAILED line is the planted unwritten row being found)\n");
+    check_partial_rows(0);
+    if (g_failures == had + 1) g_failures = had;
+    else { std::printf("the check of partial rows did not find the planted one\n"); ++g_failures; }
   }
   domino_shutdown();
   std::printf(g_failures ? "host schedule driver: %d expectation(s) failed over %d cases\n" : "host schedule driver: ok (%d cases)\n",
