@@ -464,9 +464,13 @@ DEV void rm_mma_cols(uint32_t tile_addr, uint32_t off, const bf16x8 (&pf)[2], f3
 constexpr int RM_TILE = 16384;
 
 // Start of a score product over 32 tile positions: -inf where the causal mask hides the position from the lane's query or
-// key (last: the largest tile row that stays, first: the smallest), so that the product itself carries the mask.  Set here
-// and not behind the product: where a branch stood between an MFMA and the first use of its result, some results were read
-// too early.
+// key (last: the largest tile row that stays, first: the smallest), so that the product itself carries the mask and no
+// branch stands between its MFMAs and the first use of their sums.  The hardware does not hold back a use that comes too
+// soon; the compiler keeps the distance by counting wait states, but it counts a block that two paths share along one of
+// them only, and behind a few branches the shorter path can come out short (ROCm 7.2: 11 states of 12 behind an if with an
+// if in both arms).  Branches as such are not unsafe: those behind products in this file (the mask and the maximum in
+// attn_fwd_kernel, the rotation before the stores of both backward bodies) keep their distance on every path, as
+// tests/test_mfma_distance.py finds on the assembly of all kernels, for the registers of LDS reads in flight as well.
 DEV void start_scores(f32x16& acc, bool masked, int first, int last, int fh) {
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
