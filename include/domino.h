@@ -324,11 +324,10 @@ int domino_profile_record(int index, int* cls, void** stream, double* start_ms, 
 const char* domino_last_error(void);   /* thread-local, static storage */
 
 /* A note about a condition that costs time without changing results, or "" if there is none (process-wide,
- * static storage, written at most once per condition).  Today: a layer or stack call that puts 4 or more row
- * slices on streams of their own while GPU_MAX_HW_QUEUES, as found in the environment, is unset or below the
- * number of those streams + 1 (Sec. 4.3.1 keeps a fixed pool of streams; on this runtime two streams that share a
- * hardware queue run their slices one after the other: 3.7-4.0 ms instead of 2.6 ms per step on the 13B shard).
- * The runtime reads the variable when it starts, so the library can only report it. */
+ * static storage, written at most once per condition).  Today: a layer or stack call whose launches go to two or three
+ * streams while GPU_MAX_HW_QUEUES, as found in the environment, is below that number + 1 (one queue serves the null
+ * stream; unset, the runtime's default is 4, which is enough).  Streams that share a hardware queue run one after the
+ * other.  The runtime reads the variable when it starts, so the library can only report it. */
 const char* domino_last_warning(void);
 
 /* Whether layer and stack calls may be recorded into a HIP graph (Sec. 4.3.2) with a pool of nstreams streams

@@ -51,20 +51,18 @@ bool g_warned_queues = false;
 
 // Streams that share a hardware queue run one after the other.  The HIP runtime reads GPU_MAX_HW_QUEUES once, when it
 // starts (default 4, one of which serves the null stream), so all the library can do is look at the environment the
-// process was started with and say what it sees.  A call puts launches on at most three streams of its pool.
-void note_hw_queues(int pool) {
-  if (pool < 4) return;
+// process was started with and say what it sees.  `used`: the streams that a call puts launches on, at most three of its pool.
+void note_hw_queues(int used) {
+  if (used < 2) return;
   std::lock_guard<std::mutex> lock(g_warn_mutex);
   if (g_warned_queues) return;
   const char* env = getenv("GPU_MAX_HW_QUEUES");
-  const int have = env ? atoi(env) : 0;
-  if (have >= pool + 1) return;
+  if ((env ? atoi(env) : 4) >= used + 1) return;
   g_warned_queues = true;
   snprintf(g_warn, sizeof(g_warn),
-           "a pool of %d streams for as many row slices, but GPU_MAX_HW_QUEUES is %s%s: with fewer hardware queues than streams + 1 "
-           "some streams of the process share a queue and run one after the other; the library itself uses at most three of "
-           "the pool's streams; to give each a queue of its own set GPU_MAX_HW_QUEUES >= %d before the HIP runtime starts",
-           pool, env ? "" : "unset (runtime default 4)", env ? env : "", pool + 1);
+           "a call uses %d streams of its pool side by side, but GPU_MAX_HW_QUEUES is %s: with fewer hardware queues than these "
+           "streams and the null stream some of them share a queue and run one after the other; set GPU_MAX_HW_QUEUES >= %d "
+           "before the HIP runtime starts", used, env ? env : "unset (runtime default 4)", used + 1);
 }
 
 constexpr size_t ALIGN = 256;
@@ -238,7 +236,6 @@ int begin_call(void* const* streams, int nstreams, int p) {
   } else {
     g_pool->used = 0;
   }
-  note_hw_queues(p < nstreams ? p : nstreams);
   return DOMINO_OK;
 }
 
@@ -924,6 +921,7 @@ int domino_layer_fwd_parts(const domino_cfg* cfg, const domino_params* P,
   std::lock_guard<std::mutex> lock(g_mutex);
   TRY(begin_call(streams, nstreams, L.p));
   const StreamPlan S(streams, nstreams, L, false);
+  note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   TRY(enqueue_fwd_block(L, cfg, S, B, parts));
@@ -961,6 +959,7 @@ int domino_layer_bwd_parts(const domino_cfg* cfg, const domino_params* P, const 
   TRY(begin_call(streams, nstreams, L.p));
   B.red = reinterpret_cast<float*>(at(workspace, L.red));
   const StreamPlan S(streams, nstreams, L, true);
+  note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   TRY(enqueue_bwd_block(L, cfg, S, workspace, grad_bufs(L, workspace), B, parts));
@@ -999,6 +998,7 @@ int domino_stack_fwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   // a row slice of block l+1 needs only the same row slice of block l (Sec. 3.2): the groups run through the
   // whole stack on their own streams and meet only at the end
   const StreamPlan S(streams, nstreams, L, false);
+  note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   for (int l = 0; l < nlayers; ++l)
@@ -1039,6 +1039,7 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
     return fail(DOMINO_ERR_UNSUPPORTED, "streams[0] is being captured into a HIP graph: the backward of a stack of %d blocks with "
                 "p = %d > 2 row slices cannot be captured; capture one domino_layer_bwd call per block instead", nlayers, L.p);
   const StreamPlan S(streams, nstreams, L, true);
+  note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   GradBufs gb[2] = {grad_bufs(L, workspace), grad_bufs(L, workspace)};

@@ -668,7 +668,38 @@ static void run_timed(int arch, int p, int nstreams) {
   }
 }
 
+// The note about hardware queues speaks of the streams that a call uses, not of the pool's size: a small block uses one,
+// whatever the pool; a wide block's backward three, two groups' and the weight gradients', which the runtime's default of
+// four queues serves beside the null stream.
+static void run_queue_note() {
+  g_case = "hardware-queue note";
+  auto note_after = [](int size, const char* queues) -> std::string {
+    g_size = size;
+    const domino_cfg c = make_cfg(DOMINO_ARCH_GPT, 4, 1, false);
+    Buffers B((size_t)12 << 30);
+    Layer L = make_layer(B, c);
+    const size_t act = (size_t)c.batch * c.seq * c.hidden * 2, wsb = domino_workspace_bytes(&c);
+    void *x = B.take(act), *dy = B.take(act), *dx = B.take(act), *ws = B.take(wsb);
+    void* streams[8];
+    for (int k = 0; k < 8; ++k) streams[k] = reinterpret_cast<void*>((uintptr_t)0x1000 * (k + 1));
+    if (queues) setenv("GPU_MAX_HW_QUEUES", queues, 1); else unsetenv("GPU_MAX_HW_QUEUES");
+    EXPECT(domino_layer_bwd(&c, &L.P, L.saved, x, dy, L.dln2_others, L.dln1_others, L.dln2_partial, L.dln1_partial, dx, &L.G, 0, ws, wsb,
+                            streams, 8) == DOMINO_OK, "domino_layer_bwd: %s", domino_last_error());
+    unsetenv("GPU_MAX_HW_QUEUES");
+    return domino_last_warning();
+  };
+  std::string note = note_after(SMALL, "2");
+  EXPECT(note.empty(), "a block on one stream gets the note: %s", note.c_str());
+  for (const char* enough : {(const char*)nullptr, "4", "8"}) {
+    note = note_after(WIDE, enough);
+    EXPECT(note.empty(), "three streams with enough queues get the note: %s", note.c_str());
+  }
+  note = note_after(WIDE, "3");
+  EXPECT(note.find("GPU_MAX_HW_QUEUES") != std::string::npos && note.find(">= 4") != std::string::npos, "three streams on three queues: '%s'", note.c_str());
+}
+
 int main() {
+  run_queue_note();          // before any other call: the note is made once in a process
   int cases = 0;
   for (int size : SIZES)
   for (int arch : {DOMINO_ARCH_GPT, DOMINO_ARCH_LLAMA})

@@ -482,16 +482,13 @@ def test_graph_replay_with_other_pools(H, nstreams):
 
 
 def test_hardware_queue_note(H, hw_queues_at_start):
-    """Four slices on four streams with fewer hardware queues than streams + 1 configured: the library says so
-    once; with enough queues it stays silent."""
+    """The note is about the streams that a call uses, not about the pool: four slices of a small block run on one of the
+    pool's four streams, and at most three are ever used, for which the runtime's default of four queues is enough."""
     from paper_2409_15241_amd import domino as D
     sc = TINY.replace(batch=4, p=4, q=2)
     params = synth.make_rank_params(sc, random_affine=True)
     x, dy = synth.make_activations(sc)
     buf = H.LayerBuffers(sc, params, x, dy, synth.make_others(sc), nstreams=4)
-    buf.forward(); buf.sync()
-    note = D.domino_last_warning()
-    if hw_queues_at_start >= 5:
-        assert note == ""
-    else:
-        assert "GPU_MAX_HW_QUEUES" in note and ">= 5" in note
+    buf.forward(); buf.backward(); buf.sync()
+    if hw_queues_at_start == 0 or hw_queues_at_start >= 4:
+        assert D.domino_last_warning() == ""
