@@ -832,8 +832,8 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
 }
 
 // workspace of a stack: one block's workspace, the partial-sum areas of the other blocks, two gradient tensors
-// handed from block to block in turn (a block reads its dy from one and writes its dx into the other) and a second set of
-// the tensors the weight gradients read, so that the block below can run on while they are formed
+// handed from block to block in turn (a block reads its dy from one and writes its dx into the other) and, where weight
+// gradients run beside the chain, a second set of the tensors they read, so that the block below can run on meanwhile
 struct StackLayout {
   size_t red_bytes, extra_red, dmid[2], d_pre2, dx1_2, dqkv2, total;
 };
@@ -846,7 +846,7 @@ StackLayout stack_layout(const Layout& L, int nlayers) {
   auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
   s.dmid[0] = take(Mz * L.h * 2);
   s.dmid[1] = take(Mz * L.h * 2);
-  if (nlayers > 1) {
+  if (nlayers > 1 && L.beside) {
     s.d_pre2 = take(Mz * L.upc * 2);
     s.dx1_2 = take(Mz * L.h * 2);
     s.dqkv2 = take(Mz * 3 * L.hl * 2);
@@ -1043,7 +1043,7 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
   GradBufs gb[2] = {grad_bufs(L, workspace), grad_bufs(L, workspace)};
-  if (nlayers > 1) gb[1] = GradBufs{at(workspace, SL.d_pre2), at(workspace, SL.dx1_2), at(workspace, SL.dqkv2)};
+  if (nlayers > 1 && L.beside) gb[1] = GradBufs{at(workspace, SL.d_pre2), at(workspace, SL.dx1_2), at(workspace, SL.dqkv2)};
   // by set of gradient tensors: what the last block that used it left for the others to wait for
   BlockEvents ev[2];
   const bool several = S.used() > 1;       // one stream orders itself

@@ -82,6 +82,19 @@ def test_every_workload_validates_and_sizes_are_consistent():
         domino.domino_saved_slot(domino.make_cfg(synth.WORKLOADS["tiny"]), "nope")
 
 
+@pytest.mark.parametrize("name,twice", [("tiny", False), ("gpt3-2.7b", False), ("gpt3-13b", True), ("llama2-7b", True)])
+def test_stacks_keep_a_second_set_of_gradient_tensors_only_where_a_block_runs_beside_the_one_above(name, twice):
+    """Blocks whose weight gradients follow on the chain's own stream finish with a set of tensors before the block below
+    writes it; only where they run on a stream of their own does a stack hold two sets (d_pre, dx1, dqkv in bf16)."""
+    sc = synth.WORKLOADS[name]
+    c = domino.make_cfg(sc)
+    size = [domino.domino_stack_workspace_bytes(c, n) for n in (1, 2, 3)]
+    second = (size[1] - size[0]) - (size[2] - size[1])
+    hl, fl = sc.hidden // sc.tp, sc.ffn // sc.tp
+    tensors = 2 * sc.batch * sc.seq * (fl * (2 if c.arch == domino.ARCH_LLAMA else 1) + sc.hidden + 3 * hl)
+    assert tensors <= second <= tensors + 3 * 256 if twice else second == 0
+
+
 def _call_fwd(c, params_ptrs, x=1, ap=1, mp=1, saved=1, ws=1, ws_bytes=1 << 40, streams=None, n=1):
     lib = domino.load()
     ps = domino.domino_params(**params_ptrs)
