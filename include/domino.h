@@ -3,7 +3,8 @@
  * One tensor-parallel rank's share of a pre-norm transformer block, forward and backward, run the
  * Domino way: the batch is cut into p independent row slices (paper Sec. 3.2 / 4.1, Eq. 3) and the
  * second weight matrix of each sub-layer (attention out-projection, MLP down-projection) into q
- * column slices (Sec. 3.3 / 4.2, Eq. 4); the p x q pieces (Sec. 3.4) are enqueued on a fixed pool of
+ * column slices (Sec. 3.3 / 4.2, Eq. 4).  The p x q pieces (Sec. 3.4) are what a program reduces over the ranks one
+ * by one; inside a call consecutive row slices share launches, as one or two row groups on a fixed pool of
  * caller-provided HIP streams (Sec. 4.3.1).  The four all-reduces of a block (Sec. 2.3) are not
  * performed: the tensors they would sum are outputs ("*_partial"), and what they would add from
  * the other ranks are optional inputs ("*_others").
@@ -83,7 +84,10 @@ int domino_validate_cfg(const domino_cfg* cfg);
 /* Bytes of the activation block carried from forward to backward, and of the scratch workspace
  * either call needs (0 on an invalid cfg).  Both are caller-allocated, 256-byte aligned: like the
  * pre-allocated full-width output buffer of Sec. 4.2 into which the column pieces are written, every
- * buffer of the path exists before the call and the library allocates none. */
+ * buffer of the path exists before the call and the library allocates none.
+ * The workspace holds the gradients of the activations inside a block, the partial sums of the vector gradients and,
+ * for blocks whose weight gradients alone would leave much of the chip idle, two to six fp32 copies of these, one for
+ * each range of rows that they are summed over. */
 size_t domino_saved_bytes(const domino_cfg* cfg);
 size_t domino_workspace_bytes(const domino_cfg* cfg);
 
@@ -93,22 +97,23 @@ size_t domino_workspace_bytes(const domino_cfg* cfg);
 int domino_saved_slot(const domino_cfg* cfg, const char* name, size_t* offset, size_t* bytes);
 
 /* Forward of the rank's block on x [b, s, h] (Sec. 3.1-3.4; schedule of Sec. 4.1.1 / 4.2).
- * For each row slice i: Norm1, QKV product (never column-sliced, Sec. 3.1), causal attention, then per
- * column slice j the out-projection piece written in place into attn_partial[rows_i, cols_j] (the
- * concatenation of Sec. 4.2 without a copy); after all q pieces of slice i (the column
- * synchronisation of Sec. 3.3): x1 = x + attn_partial + attn_others + b_o, Norm2, MLP-up with fused
- * activation, per column slice j the down-projection piece into mlp_partial[rows_i, cols_j]; finally
+ * For each row slice: Norm1, QKV product (never column-sliced, Sec. 3.1), causal attention, then the out-projection's q
+ * column pieces written in place into attn_partial (the concatenation of Sec. 4.2 without a copy); after all q
+ * pieces of the slice (the column synchronisation of Sec. 3.3): x1 = x + attn_partial + attn_others + b_o, Norm2,
+ * MLP-up with fused activation, the down-projection's pieces into mlp_partial; finally
  * y = x1 + mlp_partial + mlp_others + b_down.
+ * A call hands out no single piece, so pieces share launches: all row slices are one row group, or two where p > 2 and
+ * the block is wide enough that a half's launches fill the chip, and the column pieces of a product are one launch
+ * (those of the out-projection one each where there are two groups).
  *   attn_others, mlp_others: [b,s,h] or NULL (= zeros): sum of the other ranks' partials.
  *   attn_partial, mlp_partial: out [b,s,h]: what the two forward all-reduces would consume.
  *   y: out [b,s,h] or NULL.   saved: out, domino_saved_bytes().   workspace: scratch.
- *   streams[0..nstreams-1]: row slice i, with its q column pieces in index order, runs on
- *   streams[i % m], m = min(nstreams, p); the forward uses no other stream.  (The backward, when m <= 2 and
- *   nstreams >= 2 m and streams[0] is not being captured, puts slice i's weight gradients on streams[m + i % m],
- *   beside the input gradients that follow them: few slices alone do not fill the chip.)
- *   Slices overlap only if their streams sit on distinct hardware queues: create
- *   the pool once, and let the process have more hardware queues than the pool has streams (HIP's
- *   GPU_MAX_HW_QUEUES, read when the runtime starts; domino_last_warning() tells when it looks too small).
+ *   streams[0..nstreams-1]: row group g runs on streams[g % m], m = min(nstreams, groups).  The backward puts weight and
+ *   vector gradients on streams[m], beside the chain of input gradients, attention and norms, where the pool has that
+ *   stream, streams[0] is not being captured and the block is large enough for it to pay; otherwise they follow on the
+ *   groups' streams.  No other stream is used: three at most.  Which block gets what follows from cfg alone.
+ *   Streams overlap only on distinct hardware queues: create the pool once; HIP's default of four queues
+ *   (GPU_MAX_HW_QUEUES, read when the runtime starts) is enough (domino_last_warning() tells when it is set too low).
  *   streams[0] may be under HIP graph capture (the other streams join the capture through the call's own
  *   fork and leave it at its join) for the pools domino_capture_supported() accepts. */
 int domino_layer_fwd(const domino_cfg* cfg, const domino_params* params,
@@ -122,10 +127,11 @@ int domino_layer_fwd(const domino_cfg* cfg, const domino_params* params,
  *   dln2_others, dln1_others: [b,s,h] or NULL: the other ranks' sums of the two backward all-reduces.
  *   dln2_partial, dln1_partial: out [b,s,h]: this rank's input gradients of MLP-up and QKV.
  *   dx: out [b,s,h]; must not overlap dy.   grads: fp32; accumulate != 0 adds to their contents, else overwrites.
- * Weight gradients: each matrix's is formed once over all rows of the block, after the input gradient of the same
- * product (slice by slice, every further slice would read and rewrite the whole fp32 gradient; on one GPU that traffic is
- * time).  With cfg->wgrad_per_slice each slice adds its share in a launch of its own, in slice order.  Either way the order of the sums is fixed: results are run-to-run
- * identical and do not depend on the stream pool. */
+ * Weight gradients: each matrix's is formed once over all rows of the block (slice by slice, every further slice would
+ * read and rewrite the whole fp32 gradient; on one GPU that traffic is time), several matrices in one launch where they
+ * share a stream.  With cfg->wgrad_per_slice each slice adds its share in a launch of its own, in slice order.
+ * Either way the order of the sums is fixed by cfg and by the parts a call runs: results are run-to-run identical and
+ * do not depend on the stream pool, on capture or on per-launch timing. */
 int domino_layer_bwd(const domino_cfg* cfg, const domino_params* params, const void* saved,
                      const void* x, const void* dy,
                      const void* dln2_others, const void* dln1_others,
@@ -154,8 +160,10 @@ int domino_layer_fwd_parts(const domino_cfg* cfg, const domino_params* params,
                            void* saved, void* workspace, size_t workspace_bytes,
                            void* const* streams, int nstreams, int parts);
 /* The gradient tensors of every matrix are complete after the part that owns the matrix; the eight vector
- * gradients (gains, shifts, biases) are written by DOMINO_BWD_NORM1, from partial sums that the earlier
- * parts left in the workspace.  accumulate must be the same in all parts of one backward. */
+ * gradients (gains, shifts, biases) are written by the call that runs DOMINO_BWD_NORM1, from partial sums that the earlier
+ * parts left in the workspace.  accumulate must be the same in all parts of one backward; the streams need not be, nor
+ * whether a part is captured.  Small blocks may sum a weight gradient in another fp32 order in parts than in one call
+ * (other matrices share its launch, and the form of the launch follows from all of them). */
 int domino_layer_bwd_parts(const domino_cfg* cfg, const domino_params* params, const void* saved,
                            const void* x, const void* dy,
                            const void* dln2_others, const void* dln1_others,
@@ -165,7 +173,7 @@ int domino_layer_bwd_parts(const domino_cfg* cfg, const domino_params* params, c
                            void* const* streams, int nstreams, int parts);
 
 /* ---- a stack of blocks (Sec. 2.3: N blocks one after the other; Sec. 3.2 and 4.1.1: the row slices stay
- * independent from block to block, so slice 0 of block l+1 starts while the other slices of block l still run) --- */
+ * independent from block to block, so one row group of block l+1 starts while the other of block l still runs) --- */
 
 /* Buffers of one block of a stack in the forward: meanings as in domino_layer_fwd.  y is required (it is the
  * next block's input; the last block's y is the stack's output). */
@@ -184,15 +192,15 @@ typedef struct domino_stack_bwd_io {
 } domino_stack_bwd_io;
 
 /* Workspace bytes of a stack of nlayers blocks (1..1024): one block's workspace, one area of partial
- * vector-gradient sums per further block, two [b,s,h] gradients handed from block to block in turn and,
- * with more than one block, a second set of the activation gradients that the weight gradients read.  0 on error. */
+ * vector-gradient sums per further block, two [b,s,h] gradients handed from block to block in turn and, with more than
+ * one block whose weight gradients run on a stream of their own, a second set of the activation gradients that these
+ * read.  0 on error. */
 size_t domino_stack_workspace_bytes(const domino_cfg* cfg, int nlayers);
 
 /* Forward of nlayers blocks of the same configuration, params[l] and io[l] being block l's (host arrays of
- * nlayers structs).  Row slice i of every block runs on the stream domino_layer_fwd would give it, and the
- * only joins are the column synchronisations inside a block and one join onto streams[0] after the last
- * block: no stream waits for another between blocks.  Between two blocks one pass over a slice's rows forms
- * the lower block's y and the upper block's Norm1 of it.  Results are bitwise those of nlayers calls of
+ * nlayers structs).  Row group g of every block runs on the stream domino_layer_fwd would give it, and the only join is
+ * one onto streams[0] after the last block: no group waits for another between blocks.  Between two blocks one pass
+ * over a group's rows forms the lower block's y and the upper block's Norm1 of it.  Results are bitwise those of nlayers calls of
  * domino_layer_fwd with y of one as x of the next. */
 int domino_stack_fwd(const domino_cfg* cfg, int nlayers, const domino_params* params, const void* x,
                      const domino_stack_fwd_io* io, void* workspace, size_t workspace_bytes,
@@ -225,7 +233,9 @@ enum { DOMINO_EPI_STORE = 0,      /* C = bf16(acc + bias)                       
        DOMINO_EPI_ACC_F32 = 5 };  /* C(fp32) = acc, or += acc if beta                        TN     */
 
 /* bf16 MFMA product with fp32 accumulation.  M, N, K and all leading dimensions (in elements) must be
- * multiples of 8.  tile: -1 = choose by shape, 0 = 128x128, 1 = 256x128, 2 = 256x256, 3 = 128x256 workgroup tile.
+ * multiples of 8.  tile: -1 = choose by shape, 0 = 128x128, 1 = 256x128, 2 = 256x256, 3 = 128x256 workgroup tile (all of
+ * these sum in the same order).  The choice by shape includes two forms for few tiles, in which a workgroup's waves deal
+ * the contraction among themselves and their sums are added at the end.
  * bias: bf16 [N] or NULL.  Invalid layout/epilogue pairs return DOMINO_ERR_INVALID_ARG. */
 int domino_gemm(int layout, int epilogue, int tile,
                 const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
