@@ -313,11 +313,12 @@ int domino_mfma_probe(const void* a, const void* b, float* out, int blocks, int 
 
 /* ---- instrumentation -------------------------------------------------------------------------- */
 
-/* While enabled, every kernel launched by domino_layer_fwd/bwd is bracketed by a pair of timing
- * events on its own stream.  domino_profile_read() synchronises those events and returns, for step
- * class `cls` (0 .. domino_profile_classes()-1), the summed elapsed milliseconds and the launch count
- * since the last domino_profile_reset().  Costs two event records per launch: keep it off when
- * timing the whole layer. */
+/* While enabled, every step of a layer or stack call is bracketed by a pair of timing events on its own stream where it
+ * is launched; nothing else about the call changes.  A step launched together with others is timed with them: the weight
+ * gradients of several matrices in one launch are the class "wgrad_joined", those of one matrix their own class.
+ * domino_profile_read() synchronises the events and returns, for step class `cls` (0 .. domino_profile_classes()-1), the
+ * summed elapsed milliseconds and the launch count since the last domino_profile_reset().  Costs two event records per
+ * launch: keep it off when timing the whole layer. */
 int domino_profile_enable(int on);
 int domino_profile_classes(void);
 const char* domino_profile_name(int cls);

@@ -252,12 +252,12 @@ int next_sync_event(hipEvent_t* ev) {
 enum ProfClass {
   PC_NORM_FWD = 0, PC_GEMM_QKV, PC_ROPE, PC_ATTN_FWD, PC_GEMM_OUT, PC_GEMM_UP, PC_GEMM_DOWN, PC_RESID_OUT,
   PC_DGRAD_DOWN, PC_WGRAD_DOWN, PC_DGRAD_UP, PC_WGRAD_UP, PC_NORM_BWD, PC_DGRAD_OUT, PC_WGRAD_OUT,
-  PC_ATTN_BWD, PC_DGRAD_QKV, PC_WGRAD_QKV, PC_COLSUM, PC_COUNT
+  PC_ATTN_BWD, PC_DGRAD_QKV, PC_WGRAD_QKV, PC_COLSUM, PC_WGRAD_JOINED, PC_COUNT
 };
 const char* const PROF_NAMES[PC_COUNT] = {
   "norm_fwd", "gemm_qkv", "rope", "attn_fwd", "gemm_out", "gemm_up", "gemm_down", "residual_out",
   "dgrad_down", "wgrad_down", "dgrad_up", "wgrad_up", "norm_bwd", "dgrad_out", "wgrad_out",
-  "attn_bwd", "dgrad_qkv", "wgrad_qkv", "colsum"};
+  "attn_bwd", "dgrad_qkv", "wgrad_qkv", "colsum", "wgrad_joined"};
 
 std::atomic<bool> g_prof_on{false};      // per-launch timing (domino_profile_enable): adds event records to a call, changes none of its launches
 struct ProfRec { int cls; hipStream_t stream; hipEvent_t start, stop; };
@@ -270,11 +270,12 @@ int prof_event(hipEvent_t* ev) {
   return DOMINO_OK;
 }
 
-// RAII bracket around the launches of one step on one stream
+// RAII bracket around the launches of one step on one stream; launches = false: the step only hands work over to a later
+// launch (GemmArgs::join, ColsumJobs::join), which has the bracket
 struct ProfScope {
   int cls; hipStream_t st; hipEvent_t start{}, stop{}; bool live = false;
-  ProfScope(int c, hipStream_t s) : cls(c), st(s) {
-    if (!g_prof_on) return;
+  ProfScope(int c, hipStream_t s, bool launches = true) : cls(c), st(s) {
+    if (!g_prof_on || !launches) return;
     if (prof_event(&start) != DOMINO_OK || prof_event(&stop) != DOMINO_OK) return;
     if (hipEventRecord(start, st) != hipSuccess) return;
     live = true;
@@ -588,13 +589,14 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
   for (int m = 0; m < n; ++m) {
     const auto& w = tab[which[m]];
     for (int i = 0; i < slices; ++i) {
-      ProfScope ps(w.cls, st);
+      const bool join = !L.per_slice && (m < n - 1 || i < slices - 1);
+      ProfScope ps(n > 1 && !L.per_slice ? (int)PC_WGRAD_JOINED : w.cls, st, !join);
       const size_t r0 = (size_t)i * K;
       GemmArgs a = gemm_args(at(w.A, r0 * w.lda * 2), w.lda, at(w.Bm, r0 * w.ldb * 2), w.ldb, w.C, w.N, w.M, w.N, K);
       a.beta = (i > 0 || B.accumulate) ? 1 : 0;
       a.beside = L.beside;
       if (parts) { a.splits = L.wsplits; a.split_ws = parts; }
-      a.join = !L.per_slice && (m < n - 1 || i < slices - 1) ? 1 : 0;
+      a.join = join ? 1 : 0;
       LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
     }
   }
@@ -612,7 +614,8 @@ int vector_gradients(const Layout& L, const BwdLayer& B, int which, hipStream_t 
   const domino_grads* G = B.G;
   const int launches = merged_wgrads(L) ? 1 : L.p, slices = L.p / launches;
   for (int i = 0; i < launches; ++i) {
-    ProfScope ps(PC_COLSUM, st);
+    const bool join = !L.per_slice && i < launches - 1;
+    ProfScope ps(PC_COLSUM, st, !join);
     struct { int k; float* out; int set; } const vec[NAREAS] = {
       {AREA_G1, G->norm1_g, VEC_ATTN}, {AREA_B1, G->norm1_b, VEC_ATTN}, {AREA_G2, G->norm2_g, VEC_MLP}, {AREA_B2, G->norm2_b, VEC_MLP},
       {AREA_BQKV, G->b_qkv, VEC_ATTN}, {AREA_BO, G->b_o, VEC_MLP}, {AREA_BUP, G->b_up, VEC_MLP}, {AREA_BDOWN, G->b_down, VEC_MLP}};
@@ -626,7 +629,7 @@ int vector_gradients(const Layout& L, const BwdLayer& B, int which, hipStream_t 
       jobs.job[njobs++] = {B.red + L.area(v.k, by_group ? 0 : i * slices), v.out, L.area_rows[v.k], L.area_n[v.k], (long)L.area_n[v.k],
                            by_group ? L.groups : slices, (long)L.area_rows[v.k] * L.area_n[v.k]};
     }
-    jobs.join = !L.per_slice && i < launches - 1 ? 1 : 0;
+    jobs.join = join ? 1 : 0;
     LAUNCH(colsum_finish_jobs_launch(jobs, njobs, (i > 0 || B.accumulate) ? 1 : 0, st), "vector gradient reduction");
   }
   return DOMINO_OK;

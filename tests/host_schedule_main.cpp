@@ -81,7 +81,7 @@ static void launch(hipStream_t st, const char* what, std::vector<Region> r, std:
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "stub"; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(new int(1)); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(new int(1)); /* 1: it can time */ return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = reinterpret_cast<hipEvent_t>(new int(0)); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<int*>(e); return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
@@ -656,6 +656,16 @@ static void run_timed(int arch, int p, int nstreams) {
     EXPECT((domino_profile_records() > 0) == (timed == 1), "%d launches were timed", domino_profile_records());
     for (const Op& o : g_ops)
       if (o.kind == Op::LAUNCH) seen[timed].push_back(o);
+    // the timing events of a stream come in pairs, and every pair brackets launches
+    std::map<hipStream_t, int> open;           // launches since the start event, or -1 outside a pair
+    for (const Op& o : g_ops) {
+      int& n = open.emplace(o.stream, -1).first->second;
+      if (o.kind == Op::LAUNCH && n >= 0) ++n;
+      if (o.kind == Op::LAUNCH && timed) EXPECT(n > 0, "a launch (%s) is not timed", o.what.c_str());
+      if (o.kind != Op::RECORD || *static_cast<int*>(o.event) != 1) continue;
+      EXPECT(n != 0, "two timing events with nothing between them");
+      n = n < 0 ? 0 : -1;
+    }
   }
   domino_profile_reset();
   EXPECT(seen[0].size() == seen[1].size(), "%zu launches with timing, %zu without", seen[1].size(), seen[0].size());
