@@ -17,9 +17,9 @@ import os
 import sys
 import time
 
-# The pool's streams only overlap if each has a hardware queue of its own; the HIP runtime's default of 4
-# queues per process leaves one of them to the null stream, and two pool streams then share a queue and
-# run their row slices one after the other.  Must be set before the runtime initialises (import torch).
+# Streams only overlap if each has a hardware queue of its own.  The library uses at most three of the pool's streams, for
+# which the HIP runtime's default of 4 queues per process is enough beside the null stream; 8 leave room for whatever
+# else a process runs.  Must be set before the runtime initialises (import torch).
 if int(os.environ.get("GPU_MAX_HW_QUEUES", "0") or 0) < 8:
     os.environ["GPU_MAX_HW_QUEUES"] = "8"
 
@@ -27,24 +27,27 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 matrix peak
 DEFAULT_WORKLOAD = "gpt3-13b"      # the shard the throughput target is quoted on
 
 
-def gemm_flops_per_launch(sc):
-    """Algorithmic flops of one product of each GEMM step class (one row slice; one column piece for
-    the two row-parallel products; the weight gradients contract over all rows of the block, or over one slice's with
-    --wgrad-per-slice)."""
-    Ms = sc.tokens // sc.p
-    Mw = wgrad_rows(sc)
-    h, hl, fl, upc, hq = sc.hidden, sc.h_local, sc.f_local, sc.up_cols, sc.hidden // sc.q
-    return {
-        "gemm_qkv": 2.0 * Ms * h * 3 * hl, "gemm_out": 2.0 * Ms * hl * hq, "gemm_up": 2.0 * Ms * h * upc,
-        "gemm_down": 2.0 * Ms * fl * hq, "dgrad_down": 2.0 * Ms * h * fl, "wgrad_down": 2.0 * Mw * fl * h,
-        "dgrad_up": 2.0 * Ms * upc * h, "wgrad_up": 2.0 * Mw * h * upc, "dgrad_out": 2.0 * Ms * h * hl,
-        "wgrad_out": 2.0 * Mw * hl * h, "dgrad_qkv": 2.0 * Ms * 3 * hl * h, "wgrad_qkv": 2.0 * Mw * h * 3 * hl,
-    }
+WGRADS = ("wgrad_down", "wgrad_up", "wgrad_out", "wgrad_qkv")
 
 
-def wgrad_rows(sc):
-    """Rows one weight-gradient launch contracts over (the library's rule: all of the block's)."""
-    return sc.tokens // sc.p if sc.wgrad_per_slice else sc.tokens
+def gemm_flops_per_step(sc):
+    """Algorithmic flops of each GEMM step class over a whole step, whatever launches it goes out in: a launch covers one
+    or all row slices and column pieces, and several weight gradients can share one."""
+    M, h, hl, fl, upc = sc.tokens, sc.hidden, sc.h_local, sc.f_local, sc.up_cols
+    qkv, out, up, down = 2.0 * M * h * 3 * hl, 2.0 * M * hl * h, 2.0 * M * h * upc, 2.0 * M * fl * h
+    return {"gemm_qkv": qkv, "gemm_out": out, "gemm_up": up, "gemm_down": down,
+            "dgrad_down": down, "dgrad_up": up, "dgrad_out": out, "dgrad_qkv": qkv,
+            "wgrad_down": down, "wgrad_up": up, "wgrad_out": out, "wgrad_qkv": qkv}
+
+
+def class_flops_per_step(sc, classes):
+    """Flops per step of each GEMM step class in `classes`, the ones that left launch records: weight gradients without
+    records of their own went out in the joined launches."""
+    per = gemm_flops_per_step(sc)
+    out = {c: per[c] for c in classes if c in per}
+    if "wgrad_joined" in classes:
+        out["wgrad_joined"] = sum(per[c] for c in WGRADS if c not in classes)
+    return out
 
 
 def algorithmic_flops(sc):
@@ -117,7 +120,7 @@ def time_other_workloads(names, nstreams, pool, steps=10, warmup=3):
 
 
 def measured_mfma_ceiling(stream, seconds=0.06):
-    """TFLOP/s of back-to-back bf16 MFMAs (the library's MFMA-only probe) on operands drawn like the layer's
+    """TFLOP/s of back-to-back bf16 MFMAs of the shape the products are made of (the library's MFMA-only probe) on operands drawn like the layer's
     (activations ~ N(0,1) against weights ~ N(0, 0.02^2)), sustained for about `seconds` so that the clock has
     settled where the power limit puts it."""
     import torch
@@ -129,10 +132,10 @@ def measured_mfma_ceiling(stream, seconds=0.06):
     out = torch.empty(blocks * 256, device="cuda", dtype=torch.float32)
     torch.cuda.synchronize()
     iters = 2000
-    domino.domino_mfma_probe(a, b, out, blocks, iters, stream)          # warm-up and a first rate
+    domino.domino_mfma_probe_shape(domino.MFMA_16x16x32, a, b, out, blocks, iters, stream)          # warm-up and a first rate
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record(stream)
-    fl = domino.domino_mfma_probe(a, b, out, blocks, iters, stream)
+    fl = domino.domino_mfma_probe_shape(domino.MFMA_16x16x32, a, b, out, blocks, iters, stream)
     e1.record(stream)
     torch.cuda.synchronize()
     per_iter_ms = e0.elapsed_time(e1) / iters
@@ -143,7 +146,7 @@ def measured_mfma_ceiling(stream, seconds=0.06):
         if k == 2:
             e0.record(stream)                                           # the first two launches let the clock settle
             tot_fl = 0.0
-        tot_fl += domino.domino_mfma_probe(a, b, out, blocks, n, stream)
+        tot_fl += domino.domino_mfma_probe_shape(domino.MFMA_16x16x32, a, b, out, blocks, n, stream)
     e1.record(stream)
     torch.cuda.synchronize()
     return tot_fl / (e0.elapsed_time(e1) * 1e-3) / 1e12
@@ -191,7 +194,7 @@ def main():
     ap.add_argument("--streams", type=int, default=4)
     ap.add_argument("--layers", type=int, default=1,
                     help="blocks per step: above 1 the step is domino_stack_fwd + domino_stack_bwd over that many "
-                         "blocks (row slices run on from block to block without joining)")
+                         "blocks (row groups run on from block to block without joining)")
     ap.add_argument("--graph", action="store_true", help="capture the step in a HIP graph and replay it")
     ap.add_argument("--p", type=int, default=None)
     ap.add_argument("--q", type=int, default=None)
@@ -301,13 +304,14 @@ def main():
         torch.cuda.synchronize()
         inst_ms = (time.perf_counter() - t0) * 1e3 / args.steps
         domino.domino_profile_enable(False)
-        per = gemm_flops_per_launch(sc)
         table = {}
         for c in range(domino.domino_profile_classes()):
             tot, n = domino.domino_profile_read(c)
             if n:
                 table[domino.domino_profile_name(c)] = (tot, n)
         domino.domino_profile_reset()
+        # flops per step of one block; a stack's records are those of all its blocks
+        per = {c: f * args.layers for c, f in class_flops_per_step(sc, table).items()}
         # step classes that run the same kernel instantiation (= one line of a rocprofv3 kernel summary)
         llama = bool(sc.arch)
         instances = {
@@ -315,13 +319,13 @@ def main():
             ("gemm_kernel<NN, swiglu> (mlp-up product)" if llama else "gemm_kernel<NN, bias+gelu> (mlp-up product)"): ["gemm_up"],
             "gemm_kernel<NT, store> (input gradients of mlp-up, out-proj, qkv)": ["dgrad_up", "dgrad_out", "dgrad_qkv"],
             ("gemm_kernel<NT, dswiglu> (input gradient of mlp-down)" if llama else "gemm_kernel<NT, dgelu> (input gradient of mlp-down)"): ["dgrad_down"],
-            "gemm_kernel<TN, fp32 accumulate> (the four weight gradients)": ["wgrad_down", "wgrad_up", "wgrad_out", "wgrad_qkv"],
+            "gemm_kernel and gemm_group_kernel<TN, fp32 accumulate> (the four weight gradients)": [*WGRADS, "wgrad_joined"],
         }
         agg = {}
         for name, classes in instances.items():
             t = sum(table[c][0] for c in classes if c in table)
             n = sum(table[c][1] for c in classes if c in table)
-            f = sum(per[c] * table[c][1] for c in classes if c in table)
+            f = sum(per[c] for c in classes if c in table) * args.steps
             if n:
                 agg[name] = (t, n, f)
         # the dominant kernel: most time on its streams; of those within 10 % of the longest (two instantiations can
@@ -342,7 +346,7 @@ def main():
         if args.breakdown:
             print(f"{'class':14s} {'launch/step':>11s} {'us/launch':>10s} {'ms/step':>8s} {'TFLOP/s':>8s}", file=sys.stderr)
             for k, (t, m) in sorted(table.items(), key=lambda kv: -kv[1][0]):
-                tf = per[k] / (t / m * 1e-3) / 1e12 if k in per else float("nan")
+                tf = per[k] * args.steps / (t * 1e-3) / 1e12 if k in per else float("nan")
                 print(f"{k:14s} {m // args.steps:11d} {t / m * 1e3:10.1f} {t / args.steps:8.3f} {tf:8.1f}", file=sys.stderr)
 
     if args.copy_check:
@@ -352,18 +356,17 @@ def main():
             dst.copy_(src)
         torch.cuda.synchronize()
 
-    if roofline is not None and roofline["kernel"].startswith("gemm_kernel<TN"):
-        # context for `achieved`: the same launches with the chip to themselves (one stream, nothing else running)
-        Ms = wgrad_rows(sc)
+    if roofline is not None and "<TN" in roofline["kernel"]:
+        # context for `achieved`: the four products one by one with the chip to themselves (one stream, nothing else running)
+        Ms = sc.tokens // sc.p if sc.wgrad_per_slice else sc.tokens
         shapes = [(sc.f_local, sc.hidden), (sc.hidden, sc.up_cols), (sc.h_local, sc.hidden), (sc.hidden, 3 * sc.h_local)]
-        tile = 2 if min(args.streams, sc.p) >= 3 else -1       # the tile the layer call picks
         tot_ms, tot_fl = 0.0, 0.0
         for (Mw, Nw) in shapes:
             A = torch.randn(Ms, Mw, device="cuda").to(torch.bfloat16)
             B = torch.randn(Ms, Nw, device="cuda").to(torch.bfloat16)
             Cw = torch.zeros(Mw, Nw, device="cuda", dtype=torch.float32)
             torch.cuda.synchronize()
-            run = lambda: domino.domino_gemm(domino.GEMM_TN, domino.EPI_ACC_F32, tile, A, Mw, B, Nw, Cw, Nw, Mw, Nw, Ms,
+            run = lambda: domino.domino_gemm(domino.GEMM_TN, domino.EPI_ACC_F32, -1, A, Mw, B, Nw, Cw, Nw, Mw, Nw, Ms,
                                              beta=0 if Ms == sc.tokens else 1, stream=s0)
             run()
             tot_ms += timed(run, 10)
@@ -417,7 +420,7 @@ def main():
         "ms_per_step_max": ms_max, "fwd_ms": fwd_ms, "bwd_ms": bwd_ms,
         "measured_mfma_ceiling": None if ceiling is None else {
             "value": ceiling, "unit": "TFLOP/s",
-            "what": "back-to-back 32x32x16 bf16 MFMAs on N(0,1) x N(0,0.02) fragments, nothing else running (domino_mfma_probe)"},
+            "what": "back-to-back 16x16x32 bf16 MFMAs on N(0,1) x N(0,0.02) fragments, nothing else running (domino_mfma_probe_shape)"},
         "pct_of_measured_mfma_ceiling": None if ceiling is None else 100.0 * value / ceiling,
         "other_workloads": others_wl,
         "stack": stack, "roofline": roofline, "cpu_baseline": cpu,

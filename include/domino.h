@@ -306,9 +306,13 @@ int domino_colsum_noalloc(const void* g, int64_t ld, int rows, int n, float* out
 
 /* MFMA-only probe for the "share of the measured matrix ceiling" figure that goes beside the share of the nominal
  * peak (the paper's metric is throughput, Sec. 5.2; a roofline needs the ceiling the chip really sustains): `blocks`
- * workgroups of 4 waves, every wave issuing iters x 8 independent 32x32x16 bf16 MFMAs back to back on one A and
- * one B fragment per lane taken from a and b (bf16 [2048] each, caller-filled with the data distribution to
- * probe).  out: fp32 [blocks * 256], receives accumulator sums.  *flops (may be NULL) = flops of the launch. */
+ * workgroups of 4 waves, every wave issuing iters x 8 x 16384 multiply-adds as bf16 MFMAs of the given shape back to
+ * back (8 or 16 independent accumulators) on one A and one B fragment per lane taken from a and b (bf16 [2048] each,
+ * caller-filled with the data distribution to probe).  out: fp32 [blocks * 256], receives accumulator sums.  *flops
+ * (may be NULL) = flops of the launch.  The products of this library are made of 16x16x32 MFMAs, the attention of
+ * 32x32x16.  domino_mfma_probe is the probe with 32x32x16. */
+enum { DOMINO_MFMA_32x32x16 = 0, DOMINO_MFMA_16x16x32 = 1 };
+int domino_mfma_probe_shape(int shape, const void* a, const void* b, float* out, int blocks, int iters, double* flops, void* stream);
 int domino_mfma_probe(const void* a, const void* b, float* out, int blocks, int iters, double* flops, void* stream);
 
 /* ---- instrumentation -------------------------------------------------------------------------- */

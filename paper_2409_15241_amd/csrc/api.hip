@@ -1257,11 +1257,15 @@ int domino_colsum_noalloc(const void* g, int64_t ld, int rows, int n, float* out
 }
 
 int domino_mfma_probe(const void* a, const void* b, float* out, int blocks, int iters, double* flops, void* stream) {
+  return domino_mfma_probe_shape(DOMINO_MFMA_32x32x16, a, b, out, blocks, iters, flops, stream);
+}
+int domino_mfma_probe_shape(int shape, const void* a, const void* b, float* out, int blocks, int iters, double* flops, void* stream) {
+  if (shape != DOMINO_MFMA_32x32x16 && shape != DOMINO_MFMA_16x16x32) return fail(DOMINO_ERR_INVALID_ARG, "MFMA shape %d is neither 32x32x16 (0) nor 16x16x32 (1)", shape);
   if (!a || !b || !out) return fail(DOMINO_ERR_NULL_POINTER, "a, b or out is NULL");
   if (blocks < 1 || blocks > 65536 || iters < 1 || iters > (1 << 24))
     return fail(DOMINO_ERR_INVALID_ARG, "blocks must lie in [1, 65536] and iters in [1, 2^24]");
   if (flops) *flops = (double)blocks * 4.0 * iters * MFMA_PROBE_FLOPS_PER_WAVE_ITER;
-  HIP_TRY(mfma_probe_launch(a, b, out, blocks, iters, as_stream(stream)), "mfma probe launch");
+  HIP_TRY(mfma_probe_launch(shape, a, b, out, blocks, iters, as_stream(stream)), "mfma probe launch");
   return DOMINO_OK;
 }
 

@@ -22,6 +22,7 @@ GEMM_NN, GEMM_NT, GEMM_TN = 0, 1, 2
 EPI_STORE, EPI_BIAS_GELU, EPI_SWIGLU, EPI_DGELU, EPI_DSWIGLU, EPI_ACC_F32 = range(6)
 FWD_ATTN, FWD_MLP, FWD_ALL = 1, 2, 3
 BWD_MLP, BWD_ATTN, BWD_NORM1, BWD_ALL = 1, 2, 4, 7
+MFMA_32x32x16, MFMA_16x16x32 = 0, 1
 
 PARAM_NAMES = ("norm1_g", "norm1_b", "w_qkv", "b_qkv", "w_o", "b_o",
                "norm2_g", "norm2_b", "w_up", "b_up", "w_down", "b_down")
@@ -31,7 +32,7 @@ EXPORTS = (
     "domino_stack_workspace_bytes", "domino_stack_fwd", "domino_stack_bwd",
     "domino_gemm", "domino_gemm_rope", "domino_attention_bwd_rope", "domino_norm_fwd",
     "domino_norm_bwd_scratch_floats", "domino_norm_bwd", "domino_attention_fwd", "domino_attention_bwd",
-    "domino_rope", "domino_colsum", "domino_colsum_noalloc", "domino_mfma_probe", "domino_profile_enable", "domino_profile_classes",
+    "domino_rope", "domino_colsum", "domino_colsum_noalloc", "domino_mfma_probe", "domino_mfma_probe_shape", "domino_profile_enable", "domino_profile_classes",
     "domino_profile_name", "domino_profile_read", "domino_profile_reset", "domino_profile_records",
     "domino_profile_record", "domino_last_error", "domino_last_warning", "domino_capture_supported",
     "domino_version", "domino_shutdown",
@@ -117,6 +118,7 @@ def load() -> C.CDLL:
         "domino_colsum": (i32, [vp, i64, i32, i32, vp, i32, vp, vp]),
         "domino_colsum_noalloc": (i32, [vp, i64, i32, i32, vp, i32, vp]),
         "domino_mfma_probe": (i32, [vp, vp, vp, i32, i32, C.POINTER(C.c_double), vp]),
+        "domino_mfma_probe_shape": (i32, [i32, vp, vp, vp, i32, i32, C.POINTER(C.c_double), vp]),
         "domino_profile_enable": (i32, [i32]),
         "domino_profile_classes": (i32, []),
         "domino_profile_name": (C.c_char_p, [i32]),
@@ -356,6 +358,13 @@ def domino_mfma_probe(a, b, out, blocks, iters, stream=None) -> float:
     """Enqueues the probe; returns the flops of the launch."""
     fl = C.c_double()
     _check(load().domino_mfma_probe(_ptr(a), _ptr(b), _ptr(out), blocks, iters, C.byref(fl), _stream(stream)))
+    return fl.value
+
+
+def domino_mfma_probe_shape(shape, a, b, out, blocks, iters, stream=None) -> float:
+    """Enqueues the probe with MFMAs of the given shape; returns the flops of the launch."""
+    fl = C.c_double()
+    _check(load().domino_mfma_probe_shape(shape, _ptr(a), _ptr(b), _ptr(out), blocks, iters, C.byref(fl), _stream(stream)))
     return fl.value
 
 

@@ -1,7 +1,7 @@
 """Board power while the path runs: `python -m paper_2409_15241_amd.power [--workload gpt3-13b] [--seconds 3]`.
 
 Samples the GPU's power sensor (hwmon `power1_input`, the same figure `rocm-smi --showpower` prints) while, one
-after the other, each of these runs back to back for a few seconds: nothing (idle), the MFMA-only probe, the
+after the other, each of these runs back to back for a few seconds: nothing (idle), the MFMA-only probe in both shapes, the
 library's GEMM at 8192^3 in its three operand layouts, a plain device copy of known size, and forward + backward of
 the workload's block as bench.py times it.  Prints time per launch, mean power, energy per launch and what that is
 per flop or per byte above the idle power.  Under sustained matrix load an MI355X sits at its power cap, so that
@@ -115,8 +115,10 @@ def main():
     st = torch.cuda.current_stream()
     iters = 4000
     fl = 512 * 4.0 * iters * 8 * 2 * 32 * 32 * 16
-    run("MFMA only, N(0,1) x N(0,0.02) fragments", lambda: domino.domino_mfma_probe(a, b, out, 512, iters, st), flops=fl, batch=5)
-    run("MFMA only, all-zero fragments", lambda: domino.domino_mfma_probe(z, z, out, 512, iters, st), flops=fl, batch=5)
+    for name, shape in (("16x16x32", domino.MFMA_16x16x32), ("32x32x16", domino.MFMA_32x32x16)):
+        probe = lambda x, y, shape=shape: (lambda: domino.domino_mfma_probe_shape(shape, x, y, out, 512, iters, st))
+        run(f"MFMA {name} only, N(0,1) x N(0,0.02) fragments", probe(a, b), flops=fl, batch=5)
+        run(f"MFMA {name} only, all-zero fragments", probe(z, z), flops=fl, batch=5)
     n = 8192
     A = torch.randn(n, n, device="cuda", generator=g).to(torch.bfloat16)
     B = (0.02 * torch.randn(n, n, device="cuda", generator=g)).to(torch.bfloat16)

@@ -249,7 +249,7 @@ hipError_t residual_out_launch(const void* x1, const void* a, const void* b, con
                               reg(y, h, n / h, h, 2, true)});
   return hipSuccess;
 }
-hipError_t mfma_probe_launch(const void*, const void*, float*, int, int, hipStream_t) { return hipSuccess; }
+hipError_t mfma_probe_launch(int, const void*, const void*, float*, int, int, hipStream_t) { return hipSuccess; }
 
 // ------------------------------------------------------------------------------------------- the checks
 static bool overlap(const Region& a, const Region& b) {

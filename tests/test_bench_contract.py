@@ -28,6 +28,20 @@ def test_algorithmic_flops_of_the_benchmarked_shard():
     assert abs(want / 1e9 - 1997.16) < 0.01
 
 
+def test_launch_records_are_charged_the_flops_of_the_whole_step_once():
+    """However a step's products are cut into launches, the classes that left records carry all of its GEMM flops."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2409_15241_amd import synth
+    sc = synth.WORKLOADS["llama2-7b"]
+    attention = 3 * 2.0 * sc.batch * sc.local_heads * sc.seq * sc.seq * sc.head_dim
+    chain = ["norm_fwd", "gemm_qkv", "gemm_out", "gemm_up", "gemm_down", "dgrad_down", "dgrad_up", "dgrad_out", "dgrad_qkv"]
+    for wgrads in (["wgrad_joined"], ["wgrad_down", "wgrad_up", "wgrad_joined"], list(bench.WGRADS)):
+        per = bench.class_flops_per_step(sc, chain + wgrads)
+        assert set(per) == set(chain[1:] + wgrads)
+        assert abs(sum(per.values()) + attention - bench.algorithmic_flops(sc)) <= 1e-9 * bench.algorithmic_flops(sc)
+
+
 @pytest.mark.gpu
 def test_bench_prints_one_json_line_with_the_contract_keys():
     torch = pytest.importorskip("torch")

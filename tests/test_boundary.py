@@ -168,6 +168,7 @@ def test_no_warning_before_any_layer_call_and_probe_validates():
     assert lib.domino_mfma_probe(None, 1, 1, 1, 1, None, None) == domino.ERR_NULL_POINTER
     assert lib.domino_mfma_probe(1, 1, 1, 0, 1, None, None) == domino.ERR_INVALID_ARG
     assert lib.domino_mfma_probe(1, 1, 1, 1, 0, None, None) == domino.ERR_INVALID_ARG
+    assert lib.domino_mfma_probe_shape(2, 1, 1, 1, 1, 1, None, None) == domino.ERR_INVALID_ARG
 
 
 def test_tuner_candidates_cut_exactly():
