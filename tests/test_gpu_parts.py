@@ -36,9 +36,9 @@ def fwd_part(D, b, parts):
                              b.saved, b.workspace, b.streams, parts)
 
 
-def bwd_part(D, b, parts):
+def bwd_part(D, b, parts, accumulate=False, nstreams=None):
     D.domino_layer_bwd_parts(b.cfg, b.params, b.saved, b.x, b.dy, b.dln2_others, b.dln1_others, b.dln2_partial,
-                             b.dln1_partial, b.dx, b.grads, False, b.workspace, b.streams, parts)
+                             b.dln1_partial, b.dx, b.grads, accumulate, b.workspace, b.streams[:nstreams], parts)
 
 
 def others_of(bufs, name):
@@ -145,3 +145,79 @@ def test_parts_reject_bad_masks_and_missing_buffers(H):
     assert e.value.code == D.ERR_NULL_POINTER
     b.mlp_partial = keep
     b.sync()
+
+
+# The smallest block of two row groups with weight gradients on a stream of their own: two or three streams side by side
+# in one call, where the small blocks above keep to one.
+WIDE = synth.ShardConfig(name="wide", hidden=4096, heads=32, tp=4, rank=0, ffn=16384, batch=8, seq=1024, p=4, q=2)
+OUTPUTS = ("dln2_partial", "dln1_partial", "dx")
+
+
+@pytest.fixture(scope="module")
+def wide(H):
+    params = synth.make_rank_params(WIDE, random_affine=True)
+    x, dy = synth.make_activations(WIDE)
+    others = dict(synth.make_others(WIDE))
+    b = H.LayerBuffers(WIDE, params, x, dy, others)
+    b.forward()
+    ref = {}
+    for accumulate in (False, True):
+        start(b, accumulate)
+        b.backward(accumulate=accumulate)
+        b.sync()
+        ref[accumulate] = {k: t.clone() for k, t in results(b).items()}
+    return b, ref
+
+
+def results(b):
+    return dict({k: getattr(b, k) for k in OUTPUTS}, **{k: g for k, g in b.grads.items() if g is not None})
+
+
+def start(b, accumulate):
+    """Outputs that must be overwritten hold NaN, gradients that are added to hold one."""
+    for k, t in results(b).items():
+        t.fill_(1.0 if accumulate and k not in OUTPUTS else float("nan"))
+    torch.cuda.synchronize()
+
+
+def check(b, ref):
+    for k, t in results(b).items():
+        assert torch.equal(t, ref[k]), k
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("pools", [(4, 4, 4), (1, 1, 4), (4, 4, 1), (4, 1, 2), (1, 4, 1)], ids=str)
+def test_parts_of_a_wide_block_on_changing_streams_are_bitwise_the_whole_call(wide, pools, accumulate):
+    """Each part on a pool of its own size, per-launch timing switched on for the middle one."""
+    from paper_2409_15241_amd import domino as D
+    b, ref = wide
+    start(b, accumulate)
+    for part, n in zip((D.BWD_MLP, D.BWD_ATTN, D.BWD_NORM1), pools):
+        D.domino_profile_enable(part == D.BWD_ATTN)
+        try:
+            bwd_part(D, b, part, accumulate, n)
+        finally:
+            D.domino_profile_enable(False)
+    b.sync()
+    D.domino_profile_reset()
+    check(b, ref[accumulate])
+
+
+def test_captured_parts_of_a_wide_block_beside_an_eager_one(wide):
+    """The first two parts replayed from a graph, the last one eager on the full pool."""
+    from paper_2409_15241_amd import domino as D
+    b, ref = wide
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=b.streams[0]):
+        bwd_part(D, b, D.BWD_MLP)
+        bwd_part(D, b, D.BWD_ATTN)
+    for _ in range(3):
+        start(b, False)
+        with torch.cuda.stream(b.streams[0]):
+            graph.replay()
+        bwd_part(D, b, D.BWD_NORM1)
+        b.sync()
+        check(b, ref[False])
+        b.forward()                                 # eager work of the same pool between the replays
+        b.backward()
+        b.sync()
