@@ -17,5 +17,17 @@ struct AttnArgs {
   float rope_log2_base;
 };
 
+// Whether the form for few workgroups (32 positions each, see attention.hip) is the faster one, from the time of either on
+// an otherwise idle chip (us, fitted to 21 shapes): the longest workgroup's chain against the split form's start, end and
+// rounds of workgroups.  Forward / backward, heads of 128: 4 x 704 positions, one head 16.5 -> 11.8 / 37 -> 20; 812, seven
+// heads 18.9 -> 13.9 / 44 -> 27; 4096, two heads 80 -> 40 / 150 -> 65; the two forms meet at 4 x 512, five heads.
+inline bool attention_split_pays(const AttnArgs& a, bool backward) {
+  const int wgs = (a.seq + 127) / 128 * a.heads * a.batch, steps = (a.seq + 63) / 64;
+  if (wgs > 128) return false;
+  const double at_once = backward ? wgs / 32.0 : wgs / 96.0, rounds = at_once > 1.0 ? at_once : 1.0;
+  if (backward) return 11 + rounds * (5 + 1.45 * a.seq / 256) < 0.95 * (14 + 2.15 * steps);
+  return 4.5 + rounds * (1.5 + 1.1 * a.seq / 128) < 0.95 * (5 + 1.17 * steps);
+}
+
 hipError_t attention_fwd_launch(const AttnArgs& a, hipStream_t st);
 hipError_t attention_bwd_launch(const AttnArgs& a, hipStream_t st);

@@ -1,0 +1,32 @@
+// Which form the launchers pick for given sizes, from the rules in csrc/gemm.h and csrc/attention.h alone (no GPU, no
+// library).  Reads one question per line and answers each with one number:
+//   gemm <epilogue> <M> <N> <K> <concurrency> <beside>   GemmTile of one product (SwiGLU: N gate columns)
+//   attention <backward> <batch> <seq> <heads>            1: 32 positions per workgroup, 0: 128
+//   ranges <tiles> <depth> <floats>                       contraction ranges of joined weight gradients
+#include <cstdio>
+#include <cstring>
+
+#include "../paper_2409_15241_amd/csrc/attention.h"
+#include "../paper_2409_15241_amd/csrc/gemm.h"
+
+int main() {
+  char line[256], what[32];
+  long v[6];
+  while (std::fgets(line, sizeof(line), stdin)) {
+    const int n = std::sscanf(line, "%31s %ld %ld %ld %ld %ld %ld", what, v, v + 1, v + 2, v + 3, v + 4, v + 5);
+    if (n == 7 && !std::strcmp(what, "gemm")) {
+      GemmArgs a{};
+      a.M = (int)v[1]; a.N = a.n_split = (int)v[2]; a.K = (int)v[3]; a.beside = (int)v[5];
+      std::printf("%d\n", gemm_pick_form(&a, 1, (int)v[0], (int)v[4]));
+    } else if (n == 5 && !std::strcmp(what, "attention")) {
+      AttnArgs a{};
+      a.batch = (int)v[1]; a.seq = (int)v[2]; a.heads = (int)v[3];
+      std::printf("%d\n", attention_split_pays(a, v[0] != 0) ? 1 : 0);
+    } else if (n == 4 && !std::strcmp(what, "ranges")) {
+      std::printf("%d\n", gemm_wgrad_splits((int)v[0], (int)v[1], v[2]));
+    } else {
+      return 1;
+    }
+  }
+  return 0;
+}

@@ -1,0 +1,76 @@
+"""The rules that pick a kernel's form by size, on the CPU: the shapes of the GPU tests take the forms that those tests are
+about, and what decides the order of a sum does not look at the streams."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+import test_gpu_forms as F
+from paper_2409_15241_amd import domino as D
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+pytestmark = pytest.mark.skipif(not os.path.exists(CLANG) and not shutil.which("g++"), reason="needs a C++ compiler")
+TILE_64_DEALT, TILE_128_DEALT = 4, 5
+EPI_ROPE = 6
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("forms") / "host_forms")
+    cc = CLANG if os.path.exists(CLANG) else "g++"
+    subprocess.run([cc, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "host_forms_main.cpp"), "-o", exe], check=True, capture_output=True)
+
+    def ask(questions):
+        text = "\n".join(" ".join(str(int(x)) if not isinstance(x, str) else x for x in q) for q in questions) + "\n"
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, check=True)
+        out = [int(x) for x in r.stdout.split()]
+        assert len(out) == len(questions)
+        return out
+    return ask
+
+
+def test_shapes_of_the_gpu_tests_take_the_dealt_forms(ask):
+    epis = (D.EPI_STORE, D.EPI_BIAS_GELU, D.EPI_DGELU, D.EPI_ACC_F32)
+    for shapes, form in ((F.FEW, TILE_64_DEALT), (F.DEEP, TILE_128_DEALT)):
+        for M, N, K in shapes:
+            assert ask([("gemm", e, M, N, K, 1, 0) for e in epis]) == [form] * len(epis), (M, N, K)
+    for M, N, K in F.SHALLOW:
+        assert ask([("gemm", D.EPI_DGELU, M, N, K, 1, 0), ("gemm", D.EPI_STORE, M, N, K, 1, 0)]) == [TILE_64_DEALT, 0], (M, N, K)
+    for M, fl, K in F.GATED:
+        n = fl // 128 * 128 + 128
+        forms = ask([("gemm", D.EPI_SWIGLU, M, fl, K, 1, 0), ("gemm", D.EPI_DSWIGLU, M, fl, K, 1, 0), ("gemm", EPI_ROPE, M, n, K, 1, 0)])
+        assert all(f in (TILE_64_DEALT, TILE_128_DEALT) for f in forms), (M, fl, K, forms)
+
+
+def test_attention_shapes_of_the_gpu_tests_take_both_forms(ask):
+    for shapes, form in ((F.ATTN_FEW, 1), (F.ATTN_MANY, 0)):
+        for b, s, nh in shapes:
+            assert ask([("attention", 0, b, s, nh), ("attention", 1, b, s, nh)]) == [form, form], (b, s, nh)
+
+
+def test_ranges_of_the_gpu_test(ask):
+    for seq in F.RANGE_SEQS:                                   # the narrow block of test_weight_gradients_over_contraction_ranges
+        h, f = 512, 2048
+        tiles = sum(-(-a // 256) * -(-b // 256) for a, b in ((f, h), (h, f), (h, h), (h, 3 * h)))
+        assert ask([("ranges", tiles, 16 * seq, h * (4 * h + 2 * f))])[0] > 1
+
+
+def test_whether_a_contraction_is_dealt_does_not_depend_on_the_streams(ask):
+    """The dealt forms sum in another order than the rest, which all sum alike: only whether one is taken may matter, and
+    products that share the chip with others never take one."""
+    rng = random.Random(2409)
+    dealt = lambda f: f in (TILE_64_DEALT, TILE_128_DEALT)
+    log = lambda lo, hi: int(lo * (hi / lo) ** rng.random()) // 8 * 8
+    taken = 0
+    for _ in range(300):
+        e, M, N, K = rng.choice((0, 1, 2, 3, 4, 5, 6)), log(64, 32768), log(64, 32768), log(64, 32768)
+        forms = ask([("gemm", e, M, N, K, c, 0) for c in (1, 2, 3, 4, 8)])
+        assert len({dealt(f) for f in forms}) == 1, (e, M, N, K, forms)
+        assert len({f for f in forms if dealt(f)}) <= 1, (e, M, N, K, forms)
+        assert not dealt(ask([("gemm", e, M, N, K, 1, 1)])[0])
+        taken += dealt(forms[0])
+    assert 30 < taken < 270

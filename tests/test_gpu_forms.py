@@ -13,9 +13,17 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # 64x64 tiles, eight waves: fewer operand tiles than waves, one more than waves, a tail of the contraction, ragged edges
-FEW = [(72, 136, 520), (200, 264, 72), (64, 64, 512), (400, 1032, 584)]
+FEW = [(72, 136, 520), (200, 264, 200), (64, 64, 512), (400, 1032, 584)]
+SHALLOW = [(200, 264, 72)]         # two operand tiles: dealt under GeLU', plain 128x128 tiles otherwise
 # 128x128 tiles, four waves: deep products of more than two rounds of 64x64 tiles
 DEEP = [(1032, 2568, 4104), (1024, 2688, 4096)]
+# (M, ffn columns, K) of the gated and rotary products: dealt forms too
+GATED = [(72, 96, 520), (400, 352, 584), (1032, 1376, 4104)]
+# (batch, seq, heads): few workgroups, 32 positions each, and many, 128 positions each
+ATTN_FEW = [(1, 129, 1), (2, 161, 3), (1, 1000, 2)]
+ATTN_MANY = [(40, 200, 4), (35, 257, 2), (24, 63, 6)]
+RANGE_SEQS = [1024, 1000]
+# test_forms.py checks on the CPU that these shapes take these forms
 
 
 def gpu(a, scale=1.0):
@@ -26,7 +34,7 @@ def close(got, ref, bar=BF16_OUT):
     return float((got.float() - ref).abs().max() / ref.abs().max()) < bar
 
 
-@pytest.mark.parametrize("M,N,K", FEW + DEEP)
+@pytest.mark.parametrize("M,N,K", FEW + SHALLOW + DEEP)
 def test_products_with_a_dealt_contraction(dom, M, N, K):
     torch.manual_seed(M + N + K)
     A, W, bias = gpu((M, K)), gpu((K, N), 0.05), gpu(N, 0.5)
@@ -59,7 +67,7 @@ def test_products_with_a_dealt_contraction(dom, M, N, K):
     assert close(F, ref + 1.0, 1e-4)
 
 
-@pytest.mark.parametrize("M,fl,K", [(72, 96, 520), (400, 352, 584), (1032, 1376, 4104)])
+@pytest.mark.parametrize("M,fl,K", GATED)
 def test_gated_and_rotary_products_with_a_dealt_contraction(dom, M, fl, K):
     torch.manual_seed(M + fl)
     A, W = gpu((M, K)), gpu((K, 2 * fl), 0.05)
@@ -88,8 +96,7 @@ def test_gated_and_rotary_products_with_a_dealt_contraction(dom, M, fl, K):
 
 
 @pytest.mark.parametrize("d", [64, 80, 128])
-@pytest.mark.parametrize("b,s,nh", [(1, 129, 1), (2, 161, 3), (1, 1000, 2),                 # few workgroups: 32 positions each
-                                    (40, 200, 4), (35, 257, 2), (24, 63, 6)])               # many: 128 positions each
+@pytest.mark.parametrize("b,s,nh", ATTN_FEW + ATTN_MANY)
 def test_attention_with_few_and_with_many_workgroups(dom, d, b, s, nh):
     rng = np.random.default_rng(d + s + nh)
     hl = nh * d
@@ -114,7 +121,7 @@ def test_attention_with_few_and_with_many_workgroups(dom, d, b, s, nh):
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
-@pytest.mark.parametrize("seq", [1024, 1000])
+@pytest.mark.parametrize("seq", RANGE_SEQS)
 def test_weight_gradients_over_contraction_ranges(dom, seq, accumulate):
     """A narrow block with many tokens: one launch over all rows in ranges, against one launch per matrix without."""
     from paper_2409_15241_amd import harness as H
