@@ -74,10 +74,12 @@ def tune(sc, pairs: Optional[List[Tuple[int, int]]] = None, streams: Iterable[in
     table = []
     data = make_data(sc)
     for (p, q) in (pairs if pairs is not None else candidates(sc)):
+        # the library uses at most three streams, two where there is one row group, so a pool with as many is the last to time
+        most, timed = (3 if p > 2 else 2), []
         for ns in streams:
-            if ns > 1 and ns > (2 * p if p <= 2 else p):
-                continue          # streams the library would not use: one per row slice, and with one or two slices
-                                  # a second one per slice for the backward's weight gradients
+            if timed and max(timed) >= most:
+                continue
+            timed.append(ns)
             ms = measure(sc.replace(p=p, q=q), ns, steps, warmup, data)
             table.append((p, q, ns, ms))
             if report:
