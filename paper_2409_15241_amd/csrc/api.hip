@@ -1,6 +1,6 @@
 // Host side of the C ABI declared in include/domino.h: argument validation, memory layout of the
 // saved / workspace blocks, the p x q piece schedule over the caller's stream pool (one block, one
-// block cut at its all-reduce points, or a stack of blocks whose row slices run on without joining),
+// block cut at its all-reduce points, or a stack of blocks whose row groups run on without joining),
 // and the single-kernel entry points.  No device memory is allocated here and no host synchronisation
 // is performed by the layer calls.
 #include "../../include/domino.h"
@@ -94,18 +94,19 @@ struct Layout {
 enum { AREA_G1 = 0, AREA_B1, AREA_G2, AREA_B2, AREA_BQKV, AREA_BO, AREA_BUP, AREA_BDOWN, NAREAS };
 
 // Two rules say how a call spreads over its streams.  Both look at the block alone, so neither the arithmetic nor a bit
-// of any result depends on the stream pool, and the parts of one backward agree on the layout of what they hand on.  In 256x256 tiles of the four weight gradients and of a product as wide as
-// the block:
+// of any result depends on the stream pool, and the parts of one backward agree on the layout of what they hand on.
+// In 256x256 tiles of the four weight gradients and of a product as wide as the block:
 int tiles256(long m, long n) { return (int)((m + 255) / 256 * ((n + 255) / 256)); }
 int wgrad_tiles(const Layout& l) { return tiles256(l.fl, l.h) + tiles256(l.h, l.upc) + tiles256(l.hl, l.h) + tiles256(l.h, 3 * l.hl); }
 
 // The backward's weight gradients run on a stream of their own where their tiles fill most of the 256 compute units or
 // more: then they fill what the chain of input gradients, attention and norms leaves idle.  Below that they follow on the
-// chain's stream as one launch, which has the chip to itself (24000 tokens of a 1536-wide shard, 63 tiles: 1231 against
-// 1666 us; GPT-3 2.7B, 160 tiles: 1646 against 1710; a 3072-wide
-// Llama shard, 228 tiles: 828 against 801; 13B, 620 tiles: 2283 against 2202).  The second stream also costs a
+// chain's stream as one launch, which has the chip to itself (forward + backward without and with the side stream, us:
+// 24000 tokens of a 1536-wide shard, 114 tiles, 1654 and 2000; GPT-3 2.7B, 160 tiles, 1548 and 1611; a 3072-wide Llama
+// shard of 4096 tokens, 228 tiles, 576 and 610; Llama-2 7B, 400 tiles, 8192 tokens, 1570 and 1565, 16384 tokens, 2879 and
+// 2642; 13B, 620 tiles, 2048 tokens, 755 and 701, 8192 tokens, 2325 and 2095).  The second stream also costs a
 // call about 100 us of host time (event records and waits) and 5 to 10 us at each of its edges on the GPU, whatever the
-// block's size: blocks under 40 GFLOP of weight gradients (half of 13B's at 512 tokens) keep to one.
+// block's size: blocks under 40 GFLOP of weight gradients (13B's at 512 tokens) keep to one.
 bool wgrads_beside(const Layout& l) {
   return wgrad_tiles(l) > 200 && 2.0 * l.M * l.h * (4.0 * l.hl + l.upc + l.fl) >= 40e9;
 }
@@ -116,8 +117,9 @@ bool wgrads_beside(const Layout& l) {
 // launches pays for the launches.  What the slices' streams used to buy, two chains of dependent launches side by side
 // so that one fills the chip while the other drains, needs two groups and no more (four streams share the four hardware
 // queues that a process gets by default, and slices that meet on a queue run one after the other), and only pays in
-// wide blocks where a group's launches fill the chip on their own: 13B with 8192 tokens, 640 tiles: 2202 us with two
-// groups, 2376 with one; with 2048 tokens, 160 tiles: 752 and 723; 2.7B with 32768 tokens: 3728 and 3391.
+// wide blocks where a group's launches fill the chip on their own (two groups and one beside a side stream, us: 13B with
+// 8192 tokens, 640 tiles, 2095 and 2128; with 4096 tokens, 320 tiles, 1202 and 1169; with 2048, 754 and 701; Llama-2 7B
+// with 8192 tokens, 512 tiles, 1509 and 1565; with 16384, 2642 and 2900).
 int row_groups(const Layout& l) { return l.p > 2 && wgrads_beside(l) && tiles256(l.M, l.h) >= 512 ? 2 : 1; }
 
 int validate(const domino_cfg* c, Layout* L) {

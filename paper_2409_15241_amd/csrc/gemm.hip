@@ -14,10 +14,11 @@
 // 128-byte lines of a contraction-contiguous operand) travel HBM/L2 -> LDS with buffer_load ... lds into two rings
 // (three tiles of A, two of B); no VGPR staging, no ds_write.
 // What bounds it at large sizes is power: a 16x16x32 MFMA reads and writes half as many accumulator bytes per flop as
-// a 32x32x16 one and sustains 2.04 against 1.79 PFLOP/s on N(0,1) x N(0,0.02) fragments with nothing else running, so
-// every product here is made of those; a wave tile of 128x128 reads 64 bytes of fragments per clock and compute unit at
-// full rate where 128x64 reads 96.  Every product sums its contraction in the same order (32 elements per MFMA), so the
-// bits do not depend on the tile shape.
+// a 32x32x16 one (1.91 against 1.86 PFLOP/s at 0.53 against 0.54 pJ/flop above idle on N(0,1) x N(0,0.02) fragments with
+// nothing else running, which domino_mfma_probe_shape measures), so every product here is made of those; a wave tile of
+// 128x128 reads 64 bytes of fragments per clock and compute unit at full rate where 128x64 reads 96.  All whole-tile forms
+// sum the contraction in the same order (32 elements per MFMA), so the bits do not depend on the tile shape; the dealt
+// forms (gemm_split_body) sum it per wave.
 // The MFMA is issued with the roles swapped (first operand = B fragment) so that a lane ends up
 // with 4 consecutive n for one m: 8-byte bf16 / 16-byte fp32 stores.
 #include "gemm.h"
@@ -406,7 +407,8 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   // path for 16 clocks; bunched up behind the barrier they stall the MFMAs issued between them), each has at least a
   // step to land, and the third place of the A ring keeps a tile in flight across the barrier.
   // (8192^3, fp32 sums of N(0,1) x N(0,0.02): 1.48 / 1.45 / 1.43 PFLOP/s NT / NN / TN, with a ring of four 32-deep
-  // tiles, eight waves and 32x32x16 MFMAs 1.20 / 1.26 / 1.21; two rings of two: 1.42 / 1.39 / 1.40.)
+  // tiles, eight waves and 32x32x16 MFMAs 1.20 / 1.26 / 1.21; two rings of two: 1.42 / 1.39 / 1.40.  Sustained for two
+  // seconds on another board: 1.54 / 1.51, and 1.36 TN adding to what C holds.)
   const int nk = (p.K + BK - 1) / BK;
   auto fill_a = [&](int slot) {
     const buf_rsrc rs = ldA.rsrc();

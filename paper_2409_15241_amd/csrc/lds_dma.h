@@ -1,11 +1,11 @@
-// Direct-to-LDS operand tiles for the GEMM: buffer_load ... lds writes global data straight into LDS
-// (no VGPR staging, no ds_write), several tiles deep, and MFMA fragments are read back with
-// ds_read_b128 (contraction-contiguous operands) or ds_read_b64_tr_b16 (contraction-strided operands:
-// the transposing read of gfx950 delivers 4 consecutive contraction values per lane from a
-// row-major [k][n] tile).
+// Direct-to-LDS operand tiles: buffer_load ... lds writes global data straight into LDS (no VGPR staging, no ds_write), and
+// MFMA fragments are read back with ds_read_b128 (contraction-contiguous operands) or ds_read_b64_tr_b16
+// (contraction-strided operands: the transposing read of gfx950 delivers 4 consecutive contraction values
+// per lane from a row-major [k][n] tile).
 //
-// A tile holds DMA_BK = 32 contraction elements.  One buffer_load_dwordx4 ... lds of a wave fills
-// 1 KiB of LDS linearly (lane l writes bytes [16 l, 16 l + 16) from the LDS base in M0), so the
+// The tiles described here are the attention forward's, of DMA_BK = 32 contraction elements (the products'
+// are 64 deep and have their own loader in gemm.hip, the attention backward's are row-major).  One
+// buffer_load_dwordx4 ... lds of a wave fills 1 KiB of LDS linearly (lane l writes bytes [16 l, 16 l + 16) from the LDS base in M0), so the
 // swizzles below are applied on the GLOBAL side: each lane fetches the chunk that belongs at its
 // fixed LDS position.  Lanes whose chunk lies outside the operand read at BUF_OOB and store zeros.
 //
