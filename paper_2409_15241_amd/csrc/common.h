@@ -7,7 +7,6 @@ typedef __bf16 bf16_t;
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -24,7 +23,6 @@ DEV uint32_t pack_bf16(float lo, float hi) {
 }
 DEV float bf16_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
 DEV float bf16_hi(uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
-DEV float bf16_to_f32(bf16_t v) { return (float)v; }
 
 // Logistic function on the hardware's 2^x and reciprocal units (1 ulp each; the results are rounded to bf16).
 // 2^x overflowing to +inf gives 1/inf = 0 and underflowing to 0 gives 1: the correct limits.
@@ -110,9 +108,4 @@ DEV float other_half(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // r[0] = [lo, lo], r[1] = [hi, hi]
   return __builtin_bit_cast(float, (threadIdx.x & 32) ? r[0] : r[1]);
-}
-DEV float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
 }

@@ -49,17 +49,6 @@ DEV uint32_t kc_frag_off(int lane, int ks) {
   const int fr = lane & 31, kc = 2 * ks + (lane >> 5);
   return (uint32_t)((fr * 4 + (kc ^ ((fr >> 2) & 3))) << 4);
 }
-// per-lane byte offset (inside a KS tile of R rows) of the first of the two transposing reads of the
-// fragment (rows n0 .. n0+31, n0 % 32 == 0, contraction 16 ks + 8 (lane/32) ..); the second read is
-// 4 k rows (8 R bytes) further.  tile_n32 = n0 / 32.
-template <int R>
-DEV uint32_t ks_frag_off(int lane, int ks, int tile_n32) {
-  const int s = lane & 15, nh = (lane >> 4) & 1, kh = lane >> 5;
-  const int n = 16 * nh + 4 * (s & 3);
-  const int k = 16 * ks + 8 * kh + (s >> 2);
-  return (uint32_t)(k * (R * 2) + ((tile_n32 ^ (k & 3)) << 6) + n * 2);
-}
-
 struct IdentityCols {
   int row0, row_end;
   DEV int operator()(int r) const { int g = row0 + r; return g < row_end ? g : -1; }
