@@ -14,7 +14,8 @@ enum GemmEpilogue {
   EPI_ROPE = 6,       // C = bf16(acc) with the rotary embedding applied to columns below rope_cols (heads of rope_d columns)
 };
 enum GemmTile { GEMM_TILE_128x128 = 0, GEMM_TILE_256x128 = 1, GEMM_TILE_256x256 = 2, GEMM_TILE_128x256 = 3,
-                GEMM_TILE_64x64 = 4, GEMM_TILE_128x128_DEALT = 5 };
+                GEMM_TILE_64x64 = 4, GEMM_TILE_128x128_DEALT = 5,
+                GEMM_TILE_256x192 = 6, GEMM_TILE_192x256 = 7, GEMM_TILE_256x320 = 8, GEMM_TILE_320x256 = 9 };
 
 constexpr int GEMM_BK = 64;      // contraction elements per operand tile
 
@@ -45,10 +46,41 @@ struct GemmArgs {
 // over the rows that follow it (the next slice of the batch), continues that product's contraction.
 constexpr int GEMM_GROUP = 4;
 
+// Time of a launch that has the chip to itself = 3 us + rounds of tiles on 256 compute units x time of a tile; time of a tile
+// = what its start and its epilogue take (fixed) + what 64 elements of the contraction take: `full` where the round fills the
+// chip, whose clocks then fall to what its power allows, `lone` where few compute units are at work, in proportion between
+// (us; fitted to 8000 timings of 921 products of shards like the library's, 128 to 32768 rows, 64 to 28672 columns, 80 to 8192
+// deep, operands out of the caches; the form picked is the fastest at the median, within 5 % of it for nine tenths; 128x256
+// was the fastest for one of them and is not looked at).
+// Forms of 192 and 320 rows or columns are there for the last round: 16384 x 1280 x 2560 is 320 tiles of 256x256, the second
+// round a quarter full, or 256 of 256x320 (108 -> 79 us; 8192 x 2560 x 5120 206 -> 147; 8192 x 2688 x 7168, 352 tiles or 448 of
+// 256x192, 274 -> 227).  A pair of columns that must meet in a lane rules out those with wave tiles of 96 or 160 columns.
+struct GemmForm { int id, bm, bn; double fixed, lone, full; };
+constexpr GemmForm GEMM_FORMS[] = {
+  {GEMM_TILE_256x256, 256, 256, 6.1, 1.17, 1.335}, {GEMM_TILE_256x320, 256, 320, 9.5, 1.46, 1.85}, {GEMM_TILE_320x256, 320, 256, 7.6, 1.49, 2.00},
+  {GEMM_TILE_256x192, 256, 192, 4.8, 0.86, 1.19}, {GEMM_TILE_192x256, 192, 256, 4.3, 0.89, 1.27}, {GEMM_TILE_256x128, 256, 128, 3.4, 0.57, 0.90},
+  {GEMM_TILE_128x128, 128, 128, 2.1, 0.39, 0.47}};
+// what the epilogue takes beyond storing bf16 sums, for 256x256 values: activations (vector ALUs), wider results
+inline double gemm_epilogue_time(int epi) {
+  return epi == EPI_BIAS_GELU ? 5.9 : epi == EPI_SWIGLU ? 8.2 : epi == EPI_DGELU ? 8.9 : epi == EPI_DSWIGLU ? 10.6 :
+         epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : 0.0;
+}
+inline bool gemm_form_takes(const GemmForm& f, int epi) { return (epi != EPI_SWIGLU && epi != EPI_ROPE) || (f.bn != 192 && f.bn != 320); }
+// tiles of contraction `it` x 64 deep; 128x128 tiles run two to a compute unit
+inline double gemm_form_time(const GemmForm& f, double tiles, int it, int epi) {
+  const double fixed = f.fixed + gemm_epilogue_time(epi) * f.bm * f.bn / 65536;
+  if (f.id == GEMM_TILE_128x128) {
+    const double rounds = floor(tiles / 512), rest = tiles - 512 * rounds, share = f.full * rest / 512;
+    return 3 + rounds * 2 * (fixed + f.full * it) + (rest == 0 ? 0.0 : rest <= 256 ? fixed - 1.1 + 0.503 * (it < 40 ? it : 40) + (it < 40 ? 0.0 : 0.80 * (it - 40)) : 2 * (fixed + (f.lone > share ? f.lone : share) * it));
+  }
+  const double rounds = floor(tiles / 256), rest = tiles - 256 * rounds, share = f.full * rest / 256;
+  return 3 + rounds * (fixed + f.full * it) + (rest == 0 ? 0.0 : fixed + (f.lone > share ? f.lone : share) * it);
+}
+
 // Contraction ranges for weight gradients that are launched together and have the chip to themselves: `tiles` tiles of
 // 256x256, `depth` deep, `floats` values in all.  A launch of 160 such tiles leaves 96 of 256 compute units idle for as
 // long as its contraction is deep; cut into ranges it is rounds of shorter tiles, for partial sums that are written and
-// read once each.  (us per tile and per byte as in the tile choice of gemm.hip.)
+// read once each.  (13 + 1.2 us per 64 deep and tile, 5 TB/s for the sums.)
 constexpr int GEMM_MAX_SPLITS = 6;
 inline int gemm_wgrad_splits(int tiles, int depth, long floats) {
   const int it = (depth + 63) / 64;
@@ -64,12 +96,9 @@ inline int gemm_wgrad_splits(int tiles, int depth, long floats) {
   }
   return best;
 }
-// Time of a launch that has the chip to itself = 3 us + rounds of tiles on 256 compute units x time of a tile; time of a
-// tile = what its start and its epilogue take + what 64 elements of the contraction take (us; fitted to 77 shapes of 128 to
-// 4096 rows, 640 to 7168 columns, 256 to 16384 deep).  128x128 tiles run two to a unit; one that is alone is faster, less
-// so on long rows, whose loads come from further away.
-// A launch beside three or more others of its size pays for the work and the padding of ragged edges only, the other
-// launches fill the rest of its last round; beside one other, half way between.
+
+// The form of a launch of n products.  A launch beside three or more others of its size pays for the work and the padding of
+// ragged edges only, the other launches fill the rest of its last round; beside one other, a third of the way from there to a launch alone.
 // The dealt forms (gemm_split_body of gemm.hip) sum in another order than the rest: whether they are taken is decided as if nothing
 // ran beside the launch, so that no bit of a result depends on the stream pool, and products meant to run beside others
 // never take them.  They win where the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep
@@ -77,46 +106,34 @@ inline int gemm_wgrad_splits(int tiles, int depth, long floats) {
 // 10.0 -> 6.5; about 3000 deep the plain 128x128 tile meets the dealt one.
 inline int gemm_pick_form(const GemmArgs* products, int n, int epi, int concurrency) {
   if (concurrency < 1) concurrency = 1;
-  const bool swiglu = epi == EPI_SWIGLU;
-  struct Cand { int id, bm, bn; double fixed, per64; };
-  static const Cand cands[] = {{GEMM_TILE_256x256, 256, 256, 8.0, 1.06}, {GEMM_TILE_256x128, 256, 128, 4.0, 0.70},
-                               {GEMM_TILE_128x256, 128, 256, 4.0, 0.73}, {GEMM_TILE_128x128, 128, 128, 1.5, 0.40}};
-  // what the epilogue takes beyond storing bf16 sums, for 256x256 values: activations (vector ALUs), wider results
-  const double extra = epi == EPI_BIAS_GELU ? 6.0 : epi == EPI_SWIGLU ? 5.0 : epi == EPI_DGELU ? 8.0 : epi == EPI_DSWIGLU ? 12.0 :
-                       epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : 0.0;
   const int splits = products[0].splits > 1 ? products[0].splits : 1;
   auto tiles_of = [&](int bm, int bn) {
     double t = 0;
     for (int i = 0; i < n; ++i) {
-      const int N = swiglu ? 2 * products[i].n_split : products[i].N;
+      const int N = epi == EPI_SWIGLU ? 2 * products[i].n_split : products[i].N;
       t += (double)((products[i].M + bm - 1) / bm) * ((N + bn - 1) / bn);
     }
     return t * splits;
   };
   const int it = ((products[0].K + GEMM_BK - 1) / GEMM_BK + splits - 1) / splits;      // a group's products share the contraction
+  const double extra = gemm_epilogue_time(epi);
   int best = GEMM_TILE_128x128;
   double best_cost = 1e30, best_alone = 1e30;
-  for (const Cand& c : cands) {
-    const double tiles = tiles_of(c.bm, c.bn), fixed = c.fixed + extra * c.bm * c.bn / 65536, unit = fixed + c.per64 * it;
-    double alone;
-    if (c.id == GEMM_TILE_128x128) {
-      const double lone = fixed + 0.5 + 0.47 * (it < 40 ? it : 40) + 0.66 * (it < 40 ? 0 : it - 40), full = floor(tiles / 512), rest = tiles - 512 * full;
-      alone = full * 2 * unit + (rest == 0 ? 0.0 : rest <= 256 ? lone : 2 * unit);
-    } else {
-      alone = ceil(tiles / 256) * unit;
-    }
+  for (const GemmForm& f : GEMM_FORMS) {
+    if (!gemm_form_takes(f, epi)) continue;
+    const double tiles = tiles_of(f.bm, f.bn), alone = gemm_form_time(f, tiles, it, epi);
     best_alone = alone < best_alone ? alone : best_alone;
     // a launch of few tiles is a long serial kernel on its stream, and the other launches in flight do not always fill
     // the chip beside it: it is charged for leaving more than three eighths of its share of the chip unused
     const double share = 160.0 / concurrency;
-    const double shared = (tiles < share ? share : tiles) / 256 * unit;
-    const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.5 * (alone + shared) : shared;
-    if (cost < best_cost * 0.999) { best_cost = cost; best = c.id; }
+    const double shared = 3 + (tiles < share ? share : tiles) / 256 * (f.fixed + extra * f.bm * f.bn / 65536 + f.full * it);
+    const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.35 * alone + 0.65 * shared : shared;
+    if (cost < best_cost * 0.999) { best_cost = cost; best = f.id; }
   }
   if (products[0].beside || splits > 1) return best;
-  const double dealt64 = ceil(tiles_of(64, 64) / 256) * (1.8 + (epi == EPI_SWIGLU ? 0.4 : 0.15) * extra + 1.4 * ((it + 7) / 8));
-  const double dealt128 = ceil(tiles_of(128, 128) / 256) * (7.0 + 0.3 * extra + 0.40 * it);
-  if (3 + (dealt64 < dealt128 ? dealt64 : dealt128) >= 0.95 * (3 + best_alone)) return best;
+  const double dealt64 = 1.7 + ceil(tiles_of(64, 64) / 256) * (1.9 + (epi == EPI_SWIGLU ? 0.23 : 0.07) * extra + 1.68 * ((it + 7) / 8));
+  const double dealt128 = 3 + ceil(tiles_of(128, 128) / 256) * (7.0 + 0.36 * extra + 0.403 * it);
+  if ((dealt64 < dealt128 ? dealt64 : dealt128) >= best_alone) return best;
   return dealt64 < dealt128 ? GEMM_TILE_64x64 : GEMM_TILE_128x128_DEALT;
 }
 

@@ -12,7 +12,7 @@
 // Work decomposition: one workgroup of four waves (one per SIMD) per BM x BN tile of C, each wave owning a
 // WM x WN sub-tile as (WN/16) x (WM/16) MFMA accumulators.  Operand tiles of BK = 64 contraction elements (whole
 // 128-byte lines of a contraction-contiguous operand) travel HBM/L2 -> LDS with buffer_load ... lds into two rings
-// (three tiles of A, two of B); no VGPR staging, no ds_write.
+// (three tiles of A, two of B; two of each where a tile is 320 wide); no VGPR staging, no ds_write.
 // What bounds it at large sizes is power: a 16x16x32 MFMA reads and writes half as many accumulator bytes per flop as
 // a 32x32x16 one (1.91 against 1.86 PFLOP/s at 0.53 against 0.54 pJ/flop above idle on N(0,1) x N(0,0.02) fragments with
 // nothing else running, which domino_mfma_probe_shape measures), so every product here is made of those; a wave tile of
@@ -29,11 +29,14 @@
 namespace {
 
 constexpr int BK = GEMM_BK;
-constexpr int RING_A = 3, RING_B = 2;
+constexpr int RING_B = 2;
+constexpr int ring_a(int BM, int BN) { return (3 * BM + RING_B * BN) * BK * 2 <= 160 * 1024 ? 3 : 2; }      // tiles of A in flight
 
 // KS tile [64 k][R rows]: element (k, n) at byte 2 R k + 64 ((n >> 5) ^ ks_swz(k)) + 2 (n & 31).  A transposing read
 // covers 4 consecutive k x 16 n: the XOR, together with the row pitch, puts the 4 rows in 4 different 64-byte quarters of
-// the banks.
+// the banks.  Two such groups of 16 lanes share a clock of the LDS, and their rows, 8 apart, share quarters: 4.0 clocks a read
+// with eight waves reading.  An XOR of 32-byte pieces that parts them too makes it 2.4, but its addresses cost the vector
+// ALU more than the LDS gains: products of 256x256 and 256x320 tiles came out level to 2 % slower.
 template <int R>
 DEV int ks_swz(int k) {
   static_assert(R % 64 == 0, "rows of a contraction-strided tile");
@@ -96,9 +99,9 @@ DEV void static_for(F&& f) {
 // Per-lane byte offsets of a 16-row fragment's reads inside a tile: lane holds row lane%16, elements 8 (lane/16) .. of 32.
 DEV uint32_t kc_frag_off16(int lane) { const int fr = lane & 15, fh = lane >> 4; return (uint32_t)(fr * 128 + ((fh ^ (fr & 7)) << 4)); }
 template <int R>
-DEV uint32_t ks_frag_off16(int lane, int n16) {       // first of the two transposing reads; the second is 4 k rows on
+DEV uint32_t ks_frag_off16(int lane, int n32) {       // of columns 32 n32 .. + 15, first of the two transposing reads; the second is 4 k rows on
   const int fr = lane & 15, fh = lane >> 4, k = 8 * fh + (fr >> 2);
-  return (uint32_t)(k * R * 2 + (((n16 >> 1) ^ ks_swz<R>(k)) << 6) + (n16 & 1) * 32 + 8 * (fr & 3));
+  return (uint32_t)(k * R * 2 + ((n32 ^ ks_swz<R>(k)) << 6) + 8 * (fr & 3));
 }
 
 // SwiGLU forward: the tile's even 32-column groups are gate columns, the odd ones the matching
@@ -173,9 +176,9 @@ struct EpiCols {
 // and is called one block of rows ahead of finish(), which reads the sums and stores: loads of global memory (1 to 2 us)
 // are in flight while the block before them is worked on.  Rows or columns outside the matrix read a safe address instead
 // of branching, their results are never stored.  PARTS: the sums of `parts` buffers part_bytes apart, added in their order.
-template <int BN, int WN, int EPI, int ROWS, bool PARTS>
+template <int BN, int WN, int EPI, int ROWS, bool PARTS, int ROW_BYTES = epi_row_bytes(WN)>
 struct RowStore {
-  static constexpr int ROWB = epi_row_bytes(WN);
+  static constexpr int ROWB = ROW_BYTES, NROWS = ROWS;
   static constexpr int RPI = 64 / (WN / 4);      // rows per read instruction
   static constexpr int NR = ROWS / RPI;          // read-back instructions
   static constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_ROPE;
@@ -304,15 +307,37 @@ struct RowStore {
   }
 };
 
+// 32 rows of sums in blocks of rows, the side tensors one block ahead; `more`: rows follow.
+template <class Store>
+DEV void store_rows32(const Store& rs, typename Store::Side& cur, const uint8_t* buf, int m, bool more) {
+  typename Store::Side nxt;
+#pragma unroll 1
+  for (int b = 0; b < 32 / Store::NROWS; ++b) {
+    const int mb = m + b * Store::NROWS;
+    if (more || b < 32 / Store::NROWS - 1) rs.side(nxt, mb + Store::NROWS);
+    rs.finish(cur, buf + b * Store::NROWS * Store::ROWB, mb);
+    cur = nxt;
+  }
+}
+constexpr int epi_block_rows(int C) { return 8 * (256 / C) < 32 ? 8 * (256 / C) : 32; }       // eight read instructions, at most 32 rows
+
 // The products of one launch: one, or several weight gradients with tiles first[i] .. first[i + 1] - 1 of the launch each.
 // With several contraction ranges (splits) the tiles of range s follow those of range s - 1, it starts s * k_per elements
 // down the contraction and its sums go part_stride floats behind the range's before it.
 struct GemmGroup { GemmArgs g[GEMM_GROUP]; int first[GEMM_GROUP + 1]; int splits, k_per; long part_stride; };
 
+// The MFMAs of the large tiles are inline assembly, which says where their sums live: 64 accumulators in the 256 accumulation
+// registers, what a tile has beyond that in vector registers.  Left to itself the compiler takes the accumulation registers for
+// all of them and copies in and out around the loop's ends (24 sums a tile of 256x256) or, beyond 256 registers, around
+// every use.  It does not see these instructions' latency: the epilogue keeps its own distance.
+constexpr int IN_AGPRS = 64;
+DEV void mfma_agpr(bf16x8 a, bf16x8 b, f32x4& c) { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
+DEV void mfma_vgpr(bf16x8 a, bf16x8 b, f32x4& c) { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b)); }
+
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 DEV void gemm_body(const GemmArgs& p, const int lin) {
   constexpr int NW = (BM / WM) * (BN / WN);
-  constexpr int TM = WM / 16, TN = WN / 16;
+  constexpr int TM = WM / 16, TN = WN / 16, RING_A = ring_a(BM, BN);
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   extern __shared__ __align__(1024) uint8_t smem[];
 
@@ -346,34 +371,59 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   // holds row lane%16, elements 8 (lane/16) ..; the tile's second 32 elements are reached by XOR 64 (KC) or 32 rows on (KS)
   const int fr = lane & 15, fh = lane >> 4;
   const uint32_t kc_off = kc_frag_off16(lane);
-  uint32_t offA[AKS ? TM : 1], offB[BKS ? TN : 1];
+  // (KS: groups of 32 columns up to the XOR's period apart have offsets of their own, a multiple of it apart a constant)
+  constexpr int GA = BM % 128 == 0 && WM > 64 ? 4 : 2, GB = BN % 128 == 0 && WN > 64 ? 4 : 2;
+  uint32_t offA[AKS ? GA : 1], offB[BKS ? GB : 1];
   if constexpr (AKS) {
 #pragma unroll
-    for (int j = 0; j < TM; ++j) offA[j] = ks_frag_off16<BM>(lane, (wm0 >> 4) + j);
+    for (int j = 0; j < GA; ++j) offA[j] = ks_frag_off16<BM>(lane, (wm0 >> 5) + j);
   } else {
     offA[0] = kc_off + wm0 * 128;
   }
   if constexpr (BKS) {
 #pragma unroll
-    for (int i = 0; i < TN; ++i) offB[i] = ks_frag_off16<BN>(lane, (wn0 >> 4) + i);
+    for (int i = 0; i < GB; ++i) offB[i] = ks_frag_off16<BN>(lane, (wn0 >> 5) + i);
   } else {
     offB[0] = kc_off + wn0 * 128;
   }
 
-  // Fragments of the two 32-deep MFMA steps of a tile.  The two halves of a transposed fragment stay apart until the
+  // Fragments of the two 32-deep MFMA steps of a tile: those of one step are read while the MFMAs of the other run.  A tile of
+  // up to 64 accumulators holds both sets.  The larger ones walk the operand of more fragments in the outer loop of a step
+  // and refill a fragment of it in place behind its last MFMA; its last SPARE fragments have a second place each, so that the
+  // last reads of a step are some 16 MFMAs ahead of the wait.  The two halves of a transposed fragment stay apart until the
   // wait has passed: joining them earlier could copy a register whose read is still in flight.
-  u32x4 fa[2][AKS ? 1 : TM], fb[2][BKS ? 1 : TN];
-  u32x2 ha[2][AKS ? TM : 1][2], hb[2][BKS ? TN : 1][2];
-  constexpr int RA = AKS ? 2 * TM : TM, RB = BKS ? 2 * TN : TN, READS = RA + RB;
+  constexpr bool IN_PLACE = TM * TN > 64, OUTER_A = IN_PLACE && TM > TN;
+  constexpr int SPARE = 2, NO = OUTER_A ? TM : TN, NI = OUTER_A ? TN : TM;      // fragments of the outer and the inner operand
+  constexpr int HA = AKS ? 2 : 1, HB = BKS ? 2 : 1, HO = OUTER_A ? HA : HB, HI = OUTER_A ? HB : HA;      // reads of a fragment
+  constexpr int FA = OUTER_A ? TM + SPARE : 2 * TM, FB = IN_PLACE && !OUTER_A ? TN + SPARE : 2 * TN;
+  u32x4 fa[AKS ? 1 : FA], fb[BKS ? 1 : FB];
+  u32x2 ha[AKS ? FA : 1][2], hb[BKS ? FB : 1][2];
+  auto at_a = [](int s, int j) constexpr { return !OUTER_A ? s * TM + j : j < TM - SPARE ? j : j + s * SPARE; };
+  auto at_b = [](int s, int i) constexpr { return !IN_PLACE || OUTER_A ? s * TN + i : i < TN - SPARE ? i : i + s * SPARE; };
+  auto read_a = [&](auto step, auto frag, auto half, uint32_t ta) {
+    constexpr int s = decltype(step)::value, j = decltype(frag)::value, h = decltype(half)::value, at = at_a(s, j);
+    if constexpr (AKS) ha[at][h] = ds_read_tr_at<(s * 32 + h * 4) * BM * 2 + (j & 1) * 32 + j / 2 / GA * GA * 64>(ta + offA[j / 2 % GA]);
+    else fa[at] = ds_read_b128_at<j * 2048>(ta + (offA[0] ^ (s << 6)));
+  };
+  auto read_b = [&](auto step, auto frag, auto half, uint32_t tb) {
+    constexpr int s = decltype(step)::value, i = decltype(frag)::value, h = decltype(half)::value, at = at_b(s, i);
+    if constexpr (BKS) hb[at][h] = ds_read_tr_at<(s * 32 + h * 4) * BN * 2 + (i & 1) * 32 + i / 2 / GB * GB * 64>(tb + offB[i / 2 % GB]);
+    else fb[at] = ds_read_b128_at<i * 2048>(tb + (offB[0] ^ (s << 6)));
+  };
+  auto read_outer = [&](auto step, auto frag, auto half, uint32_t ta, uint32_t tb) {
+    if constexpr (OUTER_A) read_a(step, frag, half, ta); else read_b(step, frag, half, tb);
+  };
+  // reads that no MFMA of the step before holds up: the inner operand, then of the outer one all, or the SPARE in two places
+  constexpr int READS = NI * HI + (IN_PLACE ? SPARE : NO) * HO;
   auto read_one = [&](auto step, auto which, uint32_t ta, uint32_t tb) {
-    constexpr int s = decltype(step)::value, r = decltype(which)::value;
-    if constexpr (r < RA) {
-      if constexpr (AKS) ha[s][r >> 1][r & 1] = ds_read_tr_at<(s * 32 + (r & 1) * 4) * BM * 2>(ta + offA[r >> 1]);
-      else fa[s][r] = ds_read_b128_at<r * 2048>(ta + (offA[0] ^ (s << 6)));
+    constexpr int r = decltype(which)::value;
+    if constexpr (r < NI * HI) {
+      using frag = std::integral_constant<int, r / HI>;
+      using half = std::integral_constant<int, r % HI>;
+      if constexpr (OUTER_A) read_b(step, frag{}, half{}, tb); else read_a(step, frag{}, half{}, ta);
     } else {
-      constexpr int q = r - RA;
-      if constexpr (BKS) hb[s][q >> 1][q & 1] = ds_read_tr_at<(s * 32 + (q & 1) * 4) * BN * 2>(tb + offB[q >> 1]);
-      else fb[s][q] = ds_read_b128_at<q * 2048>(tb + (offB[0] ^ (s << 6)));
+      constexpr int q = r - NI * HI;
+      read_outer(step, std::integral_constant<int, q / HO + (IN_PLACE ? NO - SPARE : 0)>{}, std::integral_constant<int, q % HO>{}, ta, tb);
     }
   };
   // a wait on the LDS counter followed by "uses and redefinitions" of the fragments: no MFMA can move above it
@@ -382,20 +432,33 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
     lds_wait<0>();
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
-      if constexpr (AKS) { tie(ha[s][j][0]); tie(ha[s][j][1]); } else tie(fa[s][j]);
+      if constexpr (AKS) { tie(ha[at_a(s, j)][0]); tie(ha[at_a(s, j)][1]); } else tie(fa[at_a(s, j)]);
     }
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
-      if constexpr (BKS) { tie(hb[s][i][0]); tie(hb[s][i][1]); } else tie(fb[s][i]);
+      if constexpr (BKS) { tie(hb[at_b(s, i)][0]); tie(hb[at_b(s, i)][1]); } else tie(fb[at_b(s, i)]);
     }
   };
   auto frag_a = [&](int s, int j) {
-    if constexpr (AKS) return __builtin_bit_cast(bf16x8, u32x4{ha[s][j][0][0], ha[s][j][0][1], ha[s][j][1][0], ha[s][j][1][1]});
-    else return __builtin_bit_cast(bf16x8, fa[s][j]);
+    const int k = at_a(s, j);
+    if constexpr (AKS) return __builtin_bit_cast(bf16x8, u32x4{ha[k][0][0], ha[k][0][1], ha[k][1][0], ha[k][1][1]});
+    else return __builtin_bit_cast(bf16x8, fa[k]);
   };
   auto frag_b = [&](int s, int i) {
-    if constexpr (BKS) return __builtin_bit_cast(bf16x8, u32x4{hb[s][i][0][0], hb[s][i][0][1], hb[s][i][1][0], hb[s][i][1][1]});
-    else return __builtin_bit_cast(bf16x8, fb[s][i]);
+    const int k = at_b(s, i);
+    if constexpr (BKS) return __builtin_bit_cast(bf16x8, u32x4{hb[k][0][0], hb[k][0][1], hb[k][1][0], hb[k][1][1]});
+    else return __builtin_bit_cast(bf16x8, fb[k]);
+  };
+  // MFMA m of step s, and the reads for the other step that follow it
+  auto mfma_and_reads = [&](auto step, auto next, auto mc, uint32_t ta, uint32_t tb) {
+    constexpr int s = decltype(step)::value, m = decltype(mc)::value, o = m / NI, i = OUTER_A ? m % NI : o, j = OUTER_A ? o : m % NI;
+    constexpr int EVERY = TM * TN * 3 / 4 / READS > 0 ? TM * TN * 3 / 4 / READS : 1;      // MFMAs per LDS read
+    if constexpr (m >= IN_AGPRS) mfma_vgpr(frag_b(s, i), frag_a(s, j), acc[i][j]);
+    else if constexpr (TM * TN > 16) mfma_agpr(frag_b(s, i), frag_a(s, j), acc[i][j]);
+    else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_b(s, i), frag_a(s, j), acc[i][j], 0, 0, 0);
+    if constexpr (m % EVERY == 0 && m / EVERY < READS) read_one(next, std::integral_constant<int, m / EVERY>{}, ta, tb);
+    if constexpr (IN_PLACE && o > 0 && o <= NO - SPARE && (m % NI == 1 || (HO == 2 && m % NI == 3)))
+      read_outer(next, std::integral_constant<int, o - 1>{}, std::integral_constant<int, m % NI / 2>{}, ta, tb);
   };
   using step0 = std::integral_constant<int, 0>;
   using step1 = std::integral_constant<int, 1>;
@@ -405,10 +468,12 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   // kt, whose two ring places are refilled from there on: with B of tile kt+2 during step 1, with A of tile kt+3 during
   // the next tile's step 0.  So loads are spread over the whole tile, one every 8 MFMAs (a load occupies the address
   // path for 16 clocks; bunched up behind the barrier they stall the MFMAs issued between them), each has at least a
-  // step to land, and the third place of the A ring keeps a tile in flight across the barrier.
-  // (8192^3, fp32 sums of N(0,1) x N(0,0.02): 1.48 / 1.45 / 1.43 PFLOP/s NT / NN / TN, with a ring of four 32-deep
-  // tiles, eight waves and 32x32x16 MFMAs 1.20 / 1.26 / 1.21; two rings of two: 1.42 / 1.39 / 1.40.  Sustained for two
-  // seconds on another board: 1.54 / 1.51, and 1.36 TN adding to what C holds.)
+  // step to land, and the third place of the A ring keeps a tile in flight across the barrier.  Where the LDS has no third
+  // place (tiles of 320), both are loaded during step 1, A first, which comes from further away: one every 3 MFMAs (every 2
+  // measured 3 to 4 % slower); a step of such a tile is a quarter longer, which is what its loads have less to land in.
+  // (8192^3, N(0,1) x N(0,0.02), NT / NN / TN: 1.52 / 1.53 / 1.48 PFLOP/s; with compiler-placed sums 1.51 / 1.49 / 1.43, and on
+  // another board 1.48 / 1.45 / 1.43, where a ring of four 32-deep tiles, eight waves and 32x32x16 MFMAs made 1.20 / 1.26 /
+  // 1.21 and two rings of two 1.42 / 1.39 / 1.40.)
   const int nk = (p.K + BK - 1) / BK;
   auto fill_a = [&](int slot) {
     const buf_rsrc rs = ldA.rsrc();
@@ -424,16 +489,20 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
     for (int i = 0; i < IPB; ++i) ldB.issue(i, rs, in, ringB + slot * B_BYTES, wave);
     ldB.advance();
   };
-  fill_a(0); fill_b(0); fill_a(1); fill_b(1); fill_a(2);
-  wait_vmcnt<2 * IPA + IPB>();
+  fill_a(0); fill_b(0); fill_a(1); fill_b(1);
+  wait_vmcnt<IPA + IPB>();
   __builtin_amdgcn_s_barrier();
   const uint32_t lds_a = lds_addr(smem), lds_b = lds_addr(ringB);
   static_for<0, READS>([&](auto r) { read_one(step0{}, r, lds_a, lds_b); });
+  if constexpr (IN_PLACE) {
+    static_for<0, (NO - SPARE) * HO>([&](auto r) {
+      read_outer(step0{}, std::integral_constant<int, decltype(r)::value / HO>{}, std::integral_constant<int, decltype(r)::value % HO>{}, lds_a, lds_b);
+    });
+  }
 
   constexpr int NM = TM * TN;                          // MFMAs per step
-  constexpr int EVERY = NM * 3 / 4 / READS > 0 ? NM * 3 / 4 / READS : 1;      // MFMAs per LDS read
   int sa = 0, sb = 0;                                  // ring places of tile kt
-  int free_a = 0;                                      // ring place that tile kt-1 left to the A tile loaded in step 0
+  int free_a = RING_A - 1;                             // ring place that tile kt-1 left to the A tile loaded in step 0
   for (int kt = 0; kt < nk; ++kt) {
     const uint32_t ta = lds_a + sa * A_BYTES, tb = lds_b + sb * B_BYTES;
     const int sa_next = sa == RING_A - 1 ? 0 : sa + 1, sb_next = sb ^ 1;
@@ -445,32 +514,35 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
       const bool in = ldA.inside();
       uint8_t* dst = smem + free_a * A_BYTES;
       static_for<0, NM>([&](auto mc) {
-        constexpr int m = decltype(mc)::value, i = m / TM, j = m % TM;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_b(0, i), frag_a(0, j), acc[i][j], 0, 0, 0);
-        if constexpr (m % EVERY == 0 && m / EVERY < READS) read_one(step1{}, std::integral_constant<int, m / EVERY>{}, ta, tb);
+        constexpr int m = decltype(mc)::value;
+        mfma_and_reads(step0{}, step1{}, mc, ta, tb);
         constexpr int LE = NM / IPA;
-        if constexpr (m % LE == LE / 2 && m / LE < IPA) { if (kt > 0) ldA.issue(m / LE, rs, in, dst, wave); }
+        if constexpr (RING_A == 3 && m % LE == LE / 2 && m / LE < IPA) ldA.issue(m / LE, rs, in, dst, wave);
         __builtin_amdgcn_sched_barrier(0);
       });
-      if (kt > 0) ldA.advance();
+      if (RING_A == 3) ldA.advance();
     }
-    wait_vmcnt<IPA>();                                 // tile kt+1 has landed (this wave's share); A of kt+2 may be in flight
+    wait_vmcnt<RING_A == 3 ? IPA : 0>();               // tile kt+1 has landed (this wave's share); A of kt+2 may be in flight
     tie_step(step1{});                                 // ... and this wave has read all of tile kt
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     {
-      const buf_rsrc rs = ldB.rsrc();
-      const bool in = ldB.inside();
-      uint8_t* dst = ringB + sb * B_BYTES;
+      const buf_rsrc rs = ldB.rsrc(), rsa = ldA.rsrc();
+      const bool in = ldB.inside(), ina = ldA.inside();
+      uint8_t *dst = ringB + sb * B_BYTES, *dsta = smem + sa * A_BYTES;
       static_for<0, NM>([&](auto mc) {
-        constexpr int m = decltype(mc)::value, i = m / TM, j = m % TM;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_b(1, i), frag_a(1, j), acc[i][j], 0, 0, 0);
-        if constexpr (m % EVERY == 0 && m / EVERY < READS) read_one(step0{}, std::integral_constant<int, m / EVERY>{}, ta_next, tb_next);
-        constexpr int LE = NM / IPB;
-        if constexpr (m % LE == LE / 2 && m / LE < IPB) ldB.issue(m / LE, rs, in, dst, wave);
+        constexpr int m = decltype(mc)::value;
+        mfma_and_reads(step1{}, step0{}, mc, ta_next, tb_next);
+        constexpr int LOADS = RING_A == 3 ? IPB : IPA + IPB, LE = RING_A == 3 ? NM / LOADS : NM * 3 / 4 / LOADS;
+        if constexpr (m % LE == LE / 2 && m / LE < LOADS) {
+          constexpr int l = m / LE, a = RING_A == 3 ? 0 : IPA;
+          if constexpr (l < a) ldA.issue(l, rsa, ina, dsta, wave);
+          else ldB.issue(l - a, rs, in, dst, wave);
+        }
         __builtin_amdgcn_sched_barrier(0);
       });
       ldB.advance();
+      if (RING_A == 2) ldA.advance();
     }
     free_a = sa;
     sa = sa_next; sb = sb_next;
@@ -479,6 +551,9 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   // The last iteration's look-ahead reads are still in flight: they must land in their registers
   // before the epilogue may reuse those registers.
   tie_step(step0{});
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (TM * TN > 16) asm volatile("s_nop 7\n\ts_nop 7");      // the last sums are 8 wait states away from their MFMA
+  __builtin_amdgcn_sched_barrier(0);
 
   // ---- epilogue.  Accumulator (i, j) value v of a lane is C[m][n] with
   //      m = m0 + wm0 + 16 j + lane%16,  n = n0 + wn0 + 16 i + 4 (lane/16) + v:
@@ -486,11 +561,18 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   __builtin_amdgcn_s_barrier();                  // every wave has finished reading the operand stages
   constexpr int ROWB = epi_row_bytes(WN);
   uint8_t* wbuf = smem + wave * (32 * ROWB);
-  const EpiCols<BN, WN, EPI> ec(p, tn, n0, wn0, lane);
-  constexpr int RPI = 64 / (WN / 4), ROWS = 8 * RPI < 32 ? 8 * RPI : 32, NB = 32 / ROWS;     // rows per block, blocks per 32 rows
-  const RowStore<BN, WN, EPI, ROWS, false> rs{p, ec, 1, 0};
-  typename RowStore<BN, WN, EPI, ROWS, false>::Side cur, nxt;
-  rs.side(cur, m0 + wm0);
+  // columns in parts whose lanes divide a wave: 128 or 64, and 32 behind them where the wave tile is 160 or 96 wide
+  constexpr int CA = WN >= 128 ? 128 : 64, CB = WN - CA;
+  const EpiCols<BN, CA, EPI> ec_a(p, tn, n0, wn0, lane);
+  const EpiCols<BN, CB ? CB : CA, EPI> ec_b(p, tn, n0, wn0 + (CB ? CA : 0), lane);
+  using StoreA = RowStore<BN, CA, EPI, epi_block_rows(CA), false, ROWB>;
+  using StoreB = RowStore<BN, CB ? CB : CA, EPI, epi_block_rows(CB ? CB : CA), false, ROWB>;
+  const StoreA rs_a{p, ec_a, 1, 0};
+  const StoreB rs_b{p, ec_b, 1, 0};
+  typename StoreA::Side side_a;
+  typename StoreB::Side side_b;
+  rs_a.side(side_a, m0 + wm0);
+  if constexpr (CB > 0) rs_b.side(side_b, m0 + wm0);
   static_for<0, TM / 2>([&](auto jc) __attribute__((always_inline)) {
     constexpr int j = decltype(jc)::value;
 #pragma unroll
@@ -498,13 +580,8 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
 #pragma unroll
       for (int g = 0; g < 2; ++g)
         *reinterpret_cast<f32x4*>(wbuf + (16 * g + fr) * ROWB + (i * 16 + fh * 4) * 4) = acc[i][2 * j + g];
-#pragma unroll 1
-    for (int b = 0; b < NB; ++b) {
-      const int m = m0 + wm0 + j * 32 + b * ROWS;
-      if (j < TM / 2 - 1 || b < NB - 1) rs.side(nxt, m + ROWS);
-      rs.finish(cur, wbuf + b * ROWS * ROWB, m);
-      cur = nxt;
-    }
+    store_rows32(rs_a, side_a, wbuf, m0 + wm0 + j * 32, j < TM / 2 - 1);
+    if constexpr (CB > 0) store_rows32(rs_b, side_b, wbuf + CA * 4, m0 + wm0 + j * 32, j < TM / 2 - 1);
   });
 }
 
@@ -559,12 +636,12 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
   for (int i = 0; i < T; ++i)
 #pragma unroll
     for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  uint32_t offA[AKS ? T : 1], offB[BKS ? T : 1];
+  uint32_t offA[AKS ? T / 2 : 1], offB[BKS ? T / 2 : 1];
   const uint32_t lds_a = lds_addr(stage), lds_b = lds_a + S::TILE;
 #pragma unroll
-  for (int j = 0; j < (AKS ? T : 1); ++j) offA[j] = lds_a + (AKS ? ks_frag_off16<R>(lane, j) : kc_frag_off16(lane));
+  for (int j = 0; j < (AKS ? T / 2 : 1); ++j) offA[j] = lds_a + (AKS ? ks_frag_off16<R>(lane, j) : kc_frag_off16(lane));
 #pragma unroll
-  for (int i = 0; i < (BKS ? T : 1); ++i) offB[i] = lds_b + (BKS ? ks_frag_off16<R>(lane, i) : kc_frag_off16(lane));
+  for (int i = 0; i < (BKS ? T / 2 : 1); ++i) offB[i] = lds_b + (BKS ? ks_frag_off16<R>(lane, i) : kc_frag_off16(lane));
 
   const int nk = (p.K + BK - 1) / BK;
   if (wave < nk) fill();
@@ -577,14 +654,14 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
       static_for<0, T>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
         if constexpr (AKS) {
-          ha[s][r][0] = ds_read_tr_at<s * 32 * R * 2>(offA[r]);
-          ha[s][r][1] = ds_read_tr_at<(s * 32 + 4) * R * 2>(offA[r]);
+          ha[s][r][0] = ds_read_tr_at<s * 32 * R * 2 + (r & 1) * 32>(offA[r / 2]);
+          ha[s][r][1] = ds_read_tr_at<(s * 32 + 4) * R * 2 + (r & 1) * 32>(offA[r / 2]);
         } else {
           fa[s][r] = ds_read_b128_at<r * 2048>(lds_a + ((offA[0] - lds_a) ^ (s << 6)));
         }
         if constexpr (BKS) {
-          hb[s][r][0] = ds_read_tr_at<s * 32 * R * 2>(offB[r]);
-          hb[s][r][1] = ds_read_tr_at<(s * 32 + 4) * R * 2>(offB[r]);
+          hb[s][r][0] = ds_read_tr_at<s * 32 * R * 2 + (r & 1) * 32>(offB[r / 2]);
+          hb[s][r][1] = ds_read_tr_at<(s * 32 + 4) * R * 2 + (r & 1) * 32>(offB[r / 2]);
         } else {
           fb[s][r] = ds_read_b128_at<r * 2048>(lds_b + ((offB[0] - lds_b) ^ (s << 6)));
         }
@@ -716,7 +793,7 @@ bool plan_tiles(GemmArgs& a) {
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int NT = gemm_threads(BM, BN, WM, WN);
-  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : (RING_A * BM + RING_B * BN) * BK * 2;
+  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : (ring_a(BM, BN) * BM + RING_B * BN) * BK * 2;
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
   if (n > 1 || products[0].splits > 1) {
     if constexpr (EPI == EPI_ACC_F32) {
@@ -768,10 +845,15 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
 
 template <bool AKS, bool BKS, int EPI>
 hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t stream) {
+  constexpr bool PAIRED = EPI == EPI_SWIGLU || EPI == EPI_ROPE;      // column pairs 32 apart inside every 64 of a wave tile
   switch (tile_cfg) {
     case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_256x192: if constexpr (!PAIRED) return launch_cfg<256, 192, 128, 96, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
+    case GEMM_TILE_256x320: if constexpr (!PAIRED) return launch_cfg<256, 320, 128, 160, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
+    case GEMM_TILE_192x256: return launch_cfg<192, 256, 96, 128, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_320x256: return launch_cfg<320, 256, 160, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_64x64:   return launch_cfg<64, 64, 64, 64, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_128x128_DEALT: return launch_cfg<128, 128, 128, 128, AKS, BKS, EPI>(a, n, stream);
     default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, n, stream);

@@ -46,6 +46,14 @@ def test_shapes_of_the_gpu_tests_take_the_dealt_forms(ask):
         assert all(f in (TILE_64_DEALT, TILE_128_DEALT) for f in forms), (M, fl, K, forms)
 
 
+def test_shapes_of_the_gpu_tests_take_every_tile_of_192_and_320(ask):
+    wide = {6: "256x192", 7: "192x256", 8: "256x320", 9: "320x256"}
+    for e in (D.EPI_STORE, D.EPI_BIAS_GELU, D.EPI_DGELU, D.EPI_ACC_F32):
+        assert set(ask([("gemm", e, M, N, K, 1, 0) for M, N, K in F.WIDE])) >= set(wide), e
+    gated = ask([("gemm", D.EPI_SWIGLU, M, N, K, 1, 0) for M, N, K in F.WIDE_GATED])
+    assert set(gated) == {7, 9}                   # pairs of columns 32 apart inside every 64 of a wave tile
+
+
 def test_attention_shapes_of_the_gpu_tests_take_both_forms(ask):
     for shapes, form in ((F.ATTN_FEW, 1), (F.ATTN_MANY, 0)):
         for b, s, nh in shapes:

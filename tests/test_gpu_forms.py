@@ -19,6 +19,9 @@ SHALLOW = [(200, 264, 72)]         # two operand tiles: dealt under GeLU', plain
 DEEP = [(1032, 2568, 4104), (1024, 2688, 4096)]
 # (M, ffn columns, K) of the gated and rotary products: dealt forms too
 GATED = [(72, 96, 520), (400, 352, 584), (1032, 1376, 4104)]
+# tiles of 192 and 320 rows or columns, products and (M, ffn columns, K): two operand tiles and more, ragged edges
+WIDE = [(1976, 5944, 72), (3408, 2352, 328), (8104, 2552, 136), (4048, 5112, 264), (4776, 3376, 72), (2888, 5784, 264)]
+WIDE_GATED = [(1160, 3392, 72), (2072, 3936, 200)]
 # (batch, seq, heads): few workgroups, 32 positions each, and many, 128 positions each
 ATTN_FEW = [(1, 129, 1), (2, 161, 3), (1, 1000, 2)]
 ATTN_MANY = [(40, 200, 4), (35, 257, 2), (24, 63, 6)]
@@ -93,6 +96,16 @@ def test_gated_and_rotary_products_with_a_dealt_contraction(dom, M, fl, K):
         dom.domino_gemm_rope(-1, A, K, Wr, N, turned, N, M, N, K, M, d_head, N, 10000.0)
         torch.cuda.synchronize()
         assert close(turned, plain.float(), 1.5e-2)
+
+
+@pytest.mark.parametrize("M,N,K", WIDE)
+def test_products_in_tiles_of_192_and_320(dom, M, N, K):
+    test_products_with_a_dealt_contraction(dom, M, N, K)
+
+
+@pytest.mark.parametrize("M,fl,K", WIDE_GATED)
+def test_gated_and_rotary_products_in_tiles_of_192_and_320(dom, M, fl, K):
+    test_gated_and_rotary_products_with_a_dealt_contraction(dom, M, fl, K)
 
 
 @pytest.mark.parametrize("d", [64, 80, 128])
