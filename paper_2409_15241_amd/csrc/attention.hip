@@ -318,23 +318,27 @@ void attn_fwd_kernel(const AttnArgs p) {
 }
 
 // ------------------------------------------------------------------------------------- D = rowsum(dO * O)
-__global__ __launch_bounds__(256)
+// One thread per (row, head), all its loads in flight at once; a workgroup of one wave, so that few rows still spread over
+// the chip.  The sum runs along d as it always has: for a sequence of one position it equals the product that it is
+// subtracted from bit for bit.
+template <int D>
+__global__ __launch_bounds__(64)
 void attn_dot_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dO, long ld, int rows, int seq,
-                     int heads, int d, float* __restrict__ dot) {
-  // one thread per (row, head): heads*d contiguous bf16 per row, d/8 16-byte chunks per head
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long)rows * heads) return;
-  const int row = (int)(idx / heads), hh = (int)(idx % heads);
-  const u32x4* a = reinterpret_cast<const u32x4*>(o + (long)row * ld + hh * d);
-  const u32x4* b = reinterpret_cast<const u32x4*>(dO + (long)row * ld + hh * d);
-  float acc = 0.0f;
-  for (int c = 0; c < d / 8; ++c) {
-    const u32x4 x = a[c], y = b[c];
+                     int heads, float* __restrict__ dot) {
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (i >= rows * heads) return;
+  const int row = i / heads, hh = i % heads;
+  const u32x4* a = reinterpret_cast<const u32x4*>(o + (long)row * ld + hh * D);
+  const u32x4* b = reinterpret_cast<const u32x4*>(dO + (long)row * ld + hh * D);
+  u32x4 x[D / 8], y[D / 8];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc += bf16_lo(x[e]) * bf16_lo(y[e]) + bf16_hi(x[e]) * bf16_hi(y[e]);
-  }
-  const int bi = row / seq, pos = row % seq;
-  dot[((long)bi * heads + hh) * seq + pos] = acc;
+  for (int c = 0; c < D / 8; ++c) { x[c] = a[c]; y[c] = b[c]; }
+  float acc = 0.0f;
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc += bf16_lo(x[c][e]) * bf16_lo(y[c][e]) + bf16_hi(x[c][e]) * bf16_hi(y[c][e]);
+  dot[((long)(row / seq) * heads + hh) * seq + row % seq] = acc;
 }
 
 // ------------------------------------------------------------------------------------- backward tiles
@@ -1038,10 +1042,9 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t st) {
 
 template <int D>
 hipError_t bwd_launch(const AttnArgs& a, hipStream_t st) {
-  const long rows = (long)a.batch * a.seq;
-  hipLaunchKernelGGL(attn_dot_kernel, dim3((unsigned)((rows * a.heads + 255) / 256)), dim3(256), 0, st,
-                     static_cast<const bf16_t*>(a.ctx), static_cast<const bf16_t*>(a.dctx), a.ld_ctx, (int)rows, a.seq,
-                     a.heads, D, a.dot);
+  const int rows = a.batch * a.seq;
+  hipLaunchKernelGGL(attn_dot_kernel<D>, dim3((unsigned)(((long)rows * a.heads + 63) / 64)), dim3(64), 0, st,
+                     static_cast<const bf16_t*>(a.ctx), static_cast<const bf16_t*>(a.dctx), a.ld_ctx, rows, a.seq, a.heads, a.dot);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (attention_split_pays(a, true)) {

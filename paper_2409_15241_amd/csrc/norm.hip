@@ -284,8 +284,13 @@ void colsum_finish_kernel(const ColsumJobs jobs, int accumulate) {
   if (col < job.n) {
     for (int g = 0; g < job.nouter; ++g) {
       const float* part = job.part + (long)g * job.ostride + col;
-#pragma unroll 4
-      for (int k = kg; k < job.nparts; k += 8) s += part[(long)k * job.stride];
+      for (int k = kg; k < job.nparts; k += 128) {       // 16 rows in flight (four: 13 us where there are 2048 rows of 2560, 10 so)
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = k + 8 * j < job.nparts ? part[(long)(k + 8 * j) * job.stride] : 0.0f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s += v[j];
+      }
     }
   }
   red[kg][c] = s;
