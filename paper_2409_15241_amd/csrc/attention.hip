@@ -360,10 +360,12 @@ struct RmLoader {            // 4 waves x 4 one-KiB pieces (4 rows each)
       base[i] = d < d_valid ? (uint32_t)(row * ld + d) * 2u : BUF_OOB;
     }
   }
+  DEV void issue_one(int i, buf_rsrc rs, uint8_t* tile, uint32_t row_byte_off, int wave) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(tile + (wave * 4 + i) * 1024), 16, base[i] + row_byte_off, 0, 0, 0);
+  }
   DEV void issue(buf_rsrc rs, uint8_t* tile, uint32_t row_byte_off, int wave) const {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(tile + (wave * 4 + i) * 1024), 16, base[i] + row_byte_off, 0, 0, 0);
+    for (int i = 0; i < 4; ++i) issue_one(i, rs, tile, row_byte_off, wave);
   }
 };
 // per-lane byte offset of the plain fragment (row lane%32, chunk lane/32) at contraction step 0; step ks
@@ -419,8 +421,8 @@ DEV void rm_mma_rows(uint32_t tile_a, uint32_t tile_b, uint32_t off, const bf16x
 }
 
 // States that the running sums sit in the accumulation registers at this point.  Placed at the top of a pass's
-// loop it keeps them there across the back edge; without it the register allocator carried all of them in
-// vector registers at the loop head and copied them to the accumulation registers and back around every tile.
+// loop it keeps them there across the back edge; without it the register allocator carried them in vector registers at
+// the loop head and copied them to the accumulation registers and back around every tile.
 template <int N>
 DEV void pin_acc(f32x16 (&acc)[N]) {
 #pragma unroll
@@ -466,6 +468,8 @@ DEV void rm_mma_cols(uint32_t tile_addr, uint32_t off, const bf16x8 (&pf)[2], f3
 }
 
 constexpr int RM_TILE = 16384;
+using half0 = std::integral_constant<int, 0>;      // the halves of a tile of 64 positions
+using half1 = std::integral_constant<int, 1>;
 
 // Start of a score product over 32 tile positions: -inf where the causal mask hides the position from the lane's query or
 // key (last: the largest tile row that stays, first: the smallest), so that the product itself carries the mask and no
@@ -483,16 +487,145 @@ DEV void start_scores(f32x16& acc, bool masked, int first, int last, int fh) {
     for (int v = 0; v < 16; ++v) acc[v] = acc_row(v, fh) > last || acc_row(v, fh) < first ? -INFINITY : 0.0f;
   }
 }
-// part(masked, t) for both halves of a tile.  Heads of 128 (one wave per SIMD) keep a body without a mask; the narrower ones
-// have no registers for two bodies.
-template <int D, class Part>
-DEV void both_halves(bool diagonal, Part&& part) {
-  static_for<0, 2>([&](auto tc) {
-    if constexpr (D == 128) {
-      if (diagonal) part(std::true_type{}, tc); else part(std::false_type{}, tc);
+// ---- heads of 128, one wave per SIMD.  A tile of 64 positions is a chain of steps of two MFMAs: the row products of both
+// halves (32 positions each), then the column products.  With one wave nothing else covers a wait, so the wave does it: the vector
+// work of one half stands between the MFMAs of the other's, and fragments are read 3 or 4 steps before they are used.
+// (4 x 4096 positions, 5 heads: 394 us with fragments read one batch ahead and the softmax between the products, 330 so; 2 x
+// 4096, 4 heads 162 -> 146; 2 x 2048, 5 heads 76 -> 65.  A tile takes 4400 clocks, 2048 of them MFMAs.)
+// The MFMAs are inline assembly, which says where their operands live: the running sums and the wave's own rows (its keys
+// and values, or queries and gradients) in accumulation registers, scores in vector registers, where the softmax takes
+// them from.  Left to the compiler all results go to accumulation registers and every score is copied.  It does not see
+// these instructions' latency: results are used behind the reads and the MFMAs of the next step (checked on the
+// assembly), running sums behind idle clocks of their own, and an operand that the vector ALU has just written gets two.
+// The matrix pipe holds one MFMA beside the one at work: a pair of them, then other work, takes 82 clocks for the pair and 8
+// multiply-adds, one MFMA and 4 of them twice takes 67.  So a step's other work is dealt out behind each of its MFMAs.
+template <bool FIRST>
+DEV void score_mfma(bf16x8 a, bf16x8 own, f32x16& sums) {        // FIRST: the sums' start has just been written
+  if constexpr (FIRST) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(sums) : "v"(a), "a"(own));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(sums) : "v"(a), "a"(own));
+}
+DEV void score_mfma_zero(bf16x8 a, bf16x8 own, f32x16& sums) { asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(sums) : "v"(a), "a"(own)); }
+template <bool FIRST>
+DEV void sums_mfma(bf16x8 a, bf16x8 p, f32x16& sums) {           // FIRST: the operand p has just been written
+  if constexpr (FIRST) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(sums) : "v"(a), "v"(p));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(sums) : "v"(a), "v"(p));
+}
+template <int N>
+DEV void wait_for(u32x4& a, u32x4& b) { asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N) : "memory"); }
+template <int N>
+DEV void wait_for(u32x2& a, u32x2& b, u32x2& c, u32x2& d) { asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N) : "memory"); }
+
+// The steps of a tile: 0 .. 7 and 8 .. 15 the row products of half 0 and 1 (one contraction step over d each), then four steps
+// (d tiles) a column product.  A step's fragments are 2 reads (rows) or 4 (columns), issued behind the MFMAs of an earlier one;
+// the dK/dV pass also reads the lse and D of 16 queries a lane, two reads for 4 queries, in front of them.
+template <bool DKV>
+struct BwdSteps {
+  static constexpr int ROWS = 16, N = DKV ? 32 : 24;
+  static constexpr int issued_at(int g) { return g < ROWS ? g - 4 : g - 3; }            // the step behind which g's reads stand; < 0: before the first
+  static constexpr int group_of(int t) { for (int g = 0; g < N; ++g) if (issued_at(g) == t) return g; return -1; }
+  static constexpr int stats_at(int t) { return !DKV ? -1 : t >= 0 && t < 4 ? t : t >= 11 && t <= 17 && t % 2 == 1 ? 4 + (t - 11) / 2 : -1; }
+  static constexpr int reads(int g) { return g < ROWS ? 2 : 4; }
+  static constexpr int stats_through(int t) { int n = 0; for (int u = 0; u <= t; ++u) n += stats_at(u) >= 0 ? 2 : 0; return n; }
+  static constexpr int through_step(int t) { int n = stats_through(t); for (int g = 0; g < N; ++g) n += issued_at(g) <= t ? reads(g) : 0; return n; }
+  static constexpr int through_group(int g) { int n = stats_through(issued_at(g)); for (int h = 0; h <= g; ++h) n += reads(h); return n; }
+  static constexpr int behind(int g) { return through_step(g - 1) - through_group(g); } // reads that may still be in flight at step g
+};
+
+// an operand that stays in accumulation registers from here on
+DEV void keep_in_acc(bf16x8 (&f)[8]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+a"(f[i]));
+}
+// behind the loop: the last sums are as many clocks away from their MFMA as a use needs, and no copy of them is made before
+template <int N>
+DEV void settle(f32x16 (&acc)[N]) {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 7\n\ts_nop 7");
+  pin_acc(acc);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The vector work of a half in steps of PER pairs of scores: the powers of the pairs to come, then what needs the powers taken a
+// step before, so that neither waits for the other.
+template <int K, int PER, class Half, class Powers>
+DEV void powers_step(Half half, Powers&& powers) {
+  constexpr int a0 = K == 0 ? 0 : (K + 1) * PER, a1 = (K + 2) * PER < 8 ? (K + 2) * PER : 8;
+  static_for<(a0 < 8 ? a0 : 8), a1>([&](auto wc) { powers(half, wc); });
+}
+template <int K, int PER, class Half, class Grads>
+DEV void grads_step(Half half, Grads&& grads) {
+  constexpr int b0 = K == 0 ? 0 : (K - 1) * PER, b1 = K == 0 ? 0 : (K + 1) * PER == 8 ? 8 : K * PER;
+  static_for<b0, b1>([&](auto wc) { grads(half, wc); });
+}
+
+// One tile.  rows_a, rows_b: LDS addresses of the tiles of the row products (with the own rows fa, fb; their sums are the two
+// score accumulators sa, sb of each half); cols(c) gives the address, the operand and the sums of column product c (four steps).
+// start() gives sa their start; powers(T, W) and grads(T, W) turn pair W of half T's scores into operands; stats(i) reads what
+// they need for 4 queries; load(i) asks for piece i of the next tile, which costs 48 clocks where nothing stands beside it.
+template <bool DKV, class Start, class Load, class Stats, class Powers, class Grads, class Cols>
+DEV void bwd_tile(uint32_t rows_a, uint32_t rows_b, uint32_t off_rows, uint32_t off_cols, const bf16x8 (&fa)[8], const bf16x8 (&fb)[8],
+                  f32x16 (&sa)[2], f32x16 (&sb)[2], Start&& start, Load&& load, Stats&& stats, Powers&& powers, Grads&& grads, Cols&& cols) {
+  using S = BwdSteps<DKV>;
+  u32x4 fr[5][2];
+  u32x2 vf[4][2][2];
+  auto read_group = [&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    if constexpr (G < S::ROWS) {
+      constexpr int T = G / 8, KS = G % 8;
+      fr[G % 5][0] = ds_read_b128_at<T * 8192>(rows_a + (off_rows ^ (KS << 5)));
+      fr[G % 5][1] = ds_read_b128_at<T * 8192>(rows_b + (off_rows ^ (KS << 5)));
     } else {
-      part(diagonal, tc);
+      constexpr int C = (G - S::ROWS) / 4, DTI = (G - S::ROWS) % 4, T = DKV ? C / 2 : C;
+      const uint32_t tile = cols(std::integral_constant<int, C>{}, nullptr);
+      static_for<0, 2>([&](auto uu) {
+        constexpr int U = decltype(uu)::value, OFF = T * 8192 + U * 4096;
+        vf[G % 4][U][0] = ds_read_tr_at<OFF>(tile + (off_cols ^ ((4 * DTI) << 4)));
+        vf[G % 4][U][1] = ds_read_tr_at<OFF + 2048>(tile + (off_cols ^ (((4 * DTI) ^ 2) << 4)));
+      });
     }
+  };
+  static_for<0, 4>([&](auto g) { read_group(g); });
+  start();
+  static_for<0, S::N>([&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    static_assert(S::behind(G) <= 15, "the LDS counter has four bits");
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int STEP = G >= 16 ? G - 16 : G - 8, PER = G >= 16 && !DKV ? 2 : 1;      // the softmax's step of a half
+    constexpr bool SOFTMAX = G >= 8 && G < (DKV ? 24 : 20);
+    using half = std::integral_constant<int, G >= 16 ? 1 : 0>;
+    auto beside = [&] {
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (S::stats_at(G) >= 0) stats(std::integral_constant<int, S::stats_at(G)>{});
+      if constexpr (S::group_of(G) >= 0) read_group(std::integral_constant<int, S::group_of(G)>{});
+      if constexpr (G < 8) load(gc);
+      if constexpr (G == 8 || G == 16) {          // a half's scores: the distance to their first use
+        asm volatile("s_nop 7");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (SOFTMAX) powers_step<STEP, PER>(half{}, powers);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (G < S::ROWS) {
+      constexpr int T = G / 8, KS = G % 8;
+      wait_for<S::behind(G)>(fr[G % 5][0], fr[G % 5][1]);
+      score_mfma<KS == 0>(__builtin_bit_cast(bf16x8, fr[G % 5][0]), fa[KS], sa[T]);
+      beside();
+      if constexpr (KS == 0) score_mfma_zero(__builtin_bit_cast(bf16x8, fr[G % 5][1]), fb[KS], sb[T]);
+      else score_mfma<false>(__builtin_bit_cast(bf16x8, fr[G % 5][1]), fb[KS], sb[T]);
+    } else {
+      constexpr int C = (G - S::ROWS) / 4, DTI = (G - S::ROWS) % 4;
+      u32x2 (&v)[2][2] = vf[G % 4];
+      wait_for<S::behind(G)>(v[0][0], v[0][1], v[1][0], v[1][1]);
+      cols(std::integral_constant<int, C>{}, [&](const uint32_t (&w)[8], auto& sums) {
+        const u32x4 a0 = {v[0][0][0], v[0][0][1], v[0][1][0], v[0][1][1]}, a1 = {v[1][0][0], v[1][0][1], v[1][1][0], v[1][1][1]};
+        sums_mfma<DTI == 0>(__builtin_bit_cast(bf16x8, a0), __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]}), sums[DTI]);
+        beside();
+        sums_mfma<DTI == 0>(__builtin_bit_cast(bf16x8, a1), __builtin_bit_cast(bf16x8, u32x4{w[4], w[5], w[6], w[7]}), sums[DTI]);
+      });
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SOFTMAX) grads_step<STEP, PER>(half{}, grads);
+    __builtin_amdgcn_sched_barrier(0);
   });
 }
 
@@ -516,6 +649,7 @@ DEV void attn_bwd_dq_body(const AttnArgs& p, uint8_t* smem, int qb, int hh, int 
   bf16x8 qf[X::KSTEPS], dof[X::KSTEPS];
   load_row_frags<D>(tok0 + hh * D, ld, qpos, s, fh, qf);
   load_row_frags<D>(static_cast<const bf16_t*>(p.dctx) + (long)bi * s * p.ld_ctx + hh * D, p.ld_ctx, qpos, s, fh, dof);
+  if constexpr (D == 128) { keep_in_acc(qf); keep_in_acc(dof); }
   const long stat = ((long)bi * p.heads + hh) * s + qpos;
   const float lse2 = qpos < s ? p.lse[stat] * LOG2E : INFINITY;
   const float dq_dot = qpos < s ? p.dot[stat] : 0.0f;
@@ -545,30 +679,61 @@ DEV void attn_bwd_dq_body(const AttnArgs& p, uint8_t* smem, int qb, int hh, int 
     if constexpr (D == 128) pin_acc(dq);
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
-    if (j + 1 < ntiles) issue_tile(j + 1);
     const int kv0 = j * 64;
-    if (kv0 > qw0 + 31) continue;
+    const bool hidden = kv0 > qw0 + 31;                       // every key of the tile is masked for this wave
+    if constexpr (D == 128) {      // the other heads' tiles are asked for here, these between the tile's products: past the last one as well
+      if (hidden) issue_tile(j + 1);
+    } else {
+      if (j + 1 < ntiles) issue_tile(j + 1);
+    }
+    if (hidden) continue;
     const uint32_t st = smem_base + (j & 1) * STAGE;
     const bool diagonal = kv0 + 63 > qw0;                   // the tile meets the diagonal
-    auto part = [&](auto mc, auto tc) {                   // 32 keys at a time
-      constexpr int T = decltype(tc)::value;
-      const bool masked = mc;
-      f32x16 sT, dpT;
-      start_scores(sT, masked, 0, qpos - kv0 - 32 * T, fh);
+    if constexpr (D == 128) {
+      f32x16 sT[2], dpT[2];
+      uint32_t ds[2][8];
+      auto powers = [&](auto tc, auto wc) {             // P^T of two keys of half T, in the place of their scores
+        constexpr int T = decltype(tc)::value, W = decltype(wc)::value;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) dpT[v] = 0.0f;
-      rm_mma_rows<D, T>(st, st + RM_TILE, offP, qf, dof, sT, dpT);      // S^T = K Q^T, dP^T = V dO^T
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sT[v] = exp2_raw(sT[v] * sc - lse2);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sT[v] *= dpT[v] - dq_dot;
-      bf16x8 dsf[2];
-      pack_acc(sT, dsf);
-      rm_mma_cols<D, T>(st, offT, dsf, dq);               // dQ^T += K^T dS^T
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    both_halves<D>(diagonal, part);
+        for (int v = 2 * W; v < 2 * W + 2; ++v) sT[T][v] = exp2_raw(sT[T][v] * sc - lse2);
+      };
+      auto grads = [&](auto tc, auto wc) {              // dS^T, packed
+        constexpr int T = decltype(tc)::value, W = decltype(wc)::value;
+        ds[T][W] = pack_bf16(sT[T][2 * W] * (dpT[T][2 * W] - dq_dot), sT[T][2 * W + 1] * (dpT[T][2 * W + 1] - dq_dot));
+      };
+      // S^T = K Q^T and dP^T = V dO^T, then dQ^T += K^T dS^T
+      bwd_tile<false>(st, st + RM_TILE, offP, offT, qf, dof, sT, dpT, [&] { start_scores(sT[0], diagonal, 0, qpos - kv0, fh); start_scores(sT[1], diagonal, 0, qpos - kv0 - 32, fh); },
+                      [&](auto ic) {
+                        constexpr int I = decltype(ic)::value;
+                        ldr.issue_one(I % 4, I < 4 ? rsK : rsV, smem + ((j + 1) & 1) * STAGE + I / 4 * RM_TILE, (uint32_t)((j + 1) * 64) * (uint32_t)ld * 2u, wave);
+                      },
+                      [](auto) {}, powers, grads, [&](auto cc, auto&& use) {
+                        constexpr int C = decltype(cc)::value;
+                        if constexpr (std::is_same_v<std::decay_t<decltype(use)>, std::nullptr_t>) return st;
+                        else use(ds[C], dq);
+                      });
+    } else {
+      auto part = [&](bool masked, auto tc) {               // 32 keys at a time
+        constexpr int T = decltype(tc)::value;
+        f32x16 sT, dpT;
+        start_scores(sT, masked, 0, qpos - kv0 - 32 * T, fh);
+  #pragma unroll
+        for (int v = 0; v < 16; ++v) dpT[v] = 0.0f;
+        rm_mma_rows<D, T>(st, st + RM_TILE, offP, qf, dof, sT, dpT);      // S^T = K Q^T, dP^T = V dO^T
+  #pragma unroll
+        for (int v = 0; v < 16; ++v) sT[v] = exp2_raw(sT[v] * sc - lse2);
+  #pragma unroll
+        for (int v = 0; v < 16; ++v) sT[v] *= dpT[v] - dq_dot;
+        bf16x8 dsf[2];
+        pack_acc(sT, dsf);
+        rm_mma_cols<D, T>(st, offT, dsf, dq);               // dQ^T += K^T dS^T
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      part(diagonal, half0{});
+      part(diagonal, half1{});
+    }
   }
+  if constexpr (D == 128) { settle(dq); wait_vmcnt<0>(); }       // no load may land in the LDS once it is another workgroup's
   if (qpos < s) {
     bf16_t* out = static_cast<bf16_t*>(p.dqkv) + ((long)bi * s + qpos) * ld + hh * D;
     if (p.rope) rope_back<D>(dq, qpos, fh, p.rope_log2_base);
@@ -624,16 +789,20 @@ DEV void attn_bwd_dkv_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int
   bf16x8 kf[X::KSTEPS], vf[X::KSTEPS];
   load_row_frags<D>(tok0 + hl + hh * D, ld, kpos, s, fh, kf);
   load_row_frags<D>(tok0 + 2 * hl + hh * D, ld, kpos, s, fh, vf);
+  if constexpr (D == 128) { keep_in_acc(kf); keep_in_acc(vf); }
 
   RmLoader ldq, ldo;
   ldq.init((int)ld, D, wave, lane);
   ldo.init((int)ldc, D, wave, lane);
+  auto issue_stats = [&](int j, uint8_t* st) {
+    if (wave == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, LDS_PTR(st + 2 * RM_TILE), 4, (uint32_t)(j * 64 + lane) * 4u, 0, 0, 0);
+    if (wave == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsD, LDS_PTR(st + 2 * RM_TILE + 256), 4, (uint32_t)(j * 64 + lane) * 4u, 0, 0, 0);
+  };
   auto issue_tile = [&](int j, int slot) {
     uint8_t* st = smem + slot * STAGE;
     ldq.issue(rsQ, st, (uint32_t)(j * 64) * (uint32_t)ld * 2u, wave);
     ldo.issue(rsO, st + RM_TILE, (uint32_t)(j * 64) * (uint32_t)ldc * 2u, wave);
-    if (wave == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, LDS_PTR(st + 2 * RM_TILE), 4, (uint32_t)(j * 64 + lane) * 4u, 0, 0, 0);
-    if (wave == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsD, LDS_PTR(st + 2 * RM_TILE + 256), 4, (uint32_t)(j * 64 + lane) * 4u, 0, 0, 0);
+    issue_stats(j, st);
   };
   const uint32_t offP = rm_plain_off(lane), offT = rm_trans_off(lane);
 
@@ -653,29 +822,73 @@ DEV void attn_bwd_dkv_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int
     const int slot = (j - j0) & 1;
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
-    if (j + 1 < nq) issue_tile(j + 1, slot ^ 1);
     const int q0 = j * 64;
-    if (q0 + 63 < kw0) continue;                          // no query of the tile sees this wave's keys
+    const bool hidden = q0 + 63 < kw0;                    // no query of the tile sees this wave's keys
+    if constexpr (D == 128) {      // as in the dQ pass
+      if (hidden) issue_tile(j + 1, slot ^ 1); else issue_stats(j + 1, smem + (slot ^ 1) * STAGE);
+    } else {
+      if (j + 1 < nq) issue_tile(j + 1, slot ^ 1);
+    }
+    if (hidden) continue;
     const uint32_t st = smem_base + slot * STAGE;
     const bool diagonal = q0 < kw0 + 31;                    // the tile meets the diagonal
-    auto part = [&](auto mc, auto tc) {                   // 32 queries at a time
-      constexpr int T = decltype(tc)::value;
-      const bool masked = mc;
-      f32x16 sm, dpm;
-      start_scores(sm, masked, kpos - q0 - 32 * T, 31, fh);
+    if constexpr (D == 128) {
+      f32x16 sm[2], dpm[2];
+      uint32_t pw[2][8], ds[2][8];
+      u32x4 l4[4], d4[4];
+      auto read_stats = [&](auto ic) {                  // lse and D of four of the lane's queries (half 0, then half 1)
+        constexpr int T = decltype(ic)::value / 4, G = decltype(ic)::value % 4;
+        l4[G] = ds_read_b128_at<2 * RM_TILE + 128 * T + 32 * G>(st + 16 * fh);
+        d4[G] = ds_read_b128_at<2 * RM_TILE + 128 * T + 32 * G + 256>(st + 16 * fh);
+      };
+      auto powers = [&](auto tc, auto wc) {             // P of two queries of half T, in the place of their scores
+        constexpr int T = decltype(tc)::value, W = decltype(wc)::value, G = W / 2;
+        if constexpr (W % 2 == 0) asm volatile("" : "+v"(l4[G]), "+v"(d4[G]));       // behind the wait of this step
+        const f32x4 lf = __builtin_bit_cast(f32x4, l4[G]);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) dpm[v] = 0.0f;
-      rm_mma_rows<D, T>(st, st + RM_TILE, offP, kf, vf, sm, dpm);       // S[q, kv] = Q K^T, dP[q, kv] = dO V^T
-      dkv_probs(st + 2 * RM_TILE + (uint32_t)(32 * T + 4 * fh) * 4u, sc, sm, dpm);
-      bf16x8 pf[2], dsf[2];
-      pack_acc(sm, pf);
-      pack_acc(dpm, dsf);
-      rm_mma_cols<D, T>(st + RM_TILE, offT, pf, dv);      // dV^T += dO^T P
-      rm_mma_cols<D, T>(st, offT, dsf, dk);               // dK^T += Q^T dS
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    both_halves<D>(diagonal, part);
+        for (int v = 2 * W; v < 2 * W + 2; ++v) sm[T][v] = exp2_raw(sm[T][v] * sc - lf[v & 3] * LOG2E);
+      };
+      auto grads = [&](auto tc, auto wc) {              // P and dS, packed
+        constexpr int T = decltype(tc)::value, W = decltype(wc)::value, V = 2 * W;
+        const f32x4 df = __builtin_bit_cast(f32x4, d4[W / 2]);
+        pw[T][W] = pack_bf16(sm[T][V], sm[T][V + 1]);
+        ds[T][W] = pack_bf16(sm[T][V] * (dpm[T][V] - df[V & 3]), sm[T][V + 1] * (dpm[T][V + 1] - df[(V + 1) & 3]));
+      };
+      // S[q, kv] = Q K^T and dP[q, kv] = dO V^T, then dV^T += dO^T P and dK^T += Q^T dS
+      bwd_tile<true>(st, st + RM_TILE, offP, offT, kf, vf, sm, dpm, [&] { start_scores(sm[0], diagonal, kpos - q0, 31, fh); start_scores(sm[1], diagonal, kpos - q0 - 32, 31, fh); },
+                     [&](auto ic) {
+                       constexpr int I = decltype(ic)::value;
+                       uint8_t* next = smem + (slot ^ 1) * STAGE;
+                       if constexpr (I < 4) ldq.issue_one(I, rsQ, next, (uint32_t)((j + 1) * 64) * (uint32_t)ld * 2u, wave);
+                       else ldo.issue_one(I - 4, rsO, next + RM_TILE, (uint32_t)((j + 1) * 64) * (uint32_t)ldc * 2u, wave);
+                     },
+                     read_stats, powers, grads, [&](auto cc, auto&& use) {
+                       constexpr int C = decltype(cc)::value;
+                       if constexpr (std::is_same_v<std::decay_t<decltype(use)>, std::nullptr_t>) return C % 2 == 0 ? st + RM_TILE : st;
+                       else if constexpr (C % 2 == 0) use(pw[C / 2], dv);
+                       else use(ds[C / 2], dk);
+                     });
+    } else {
+      auto part = [&](bool masked, auto tc) {               // 32 queries at a time
+        constexpr int T = decltype(tc)::value;
+        f32x16 sm, dpm;
+        start_scores(sm, masked, kpos - q0 - 32 * T, 31, fh);
+  #pragma unroll
+        for (int v = 0; v < 16; ++v) dpm[v] = 0.0f;
+        rm_mma_rows<D, T>(st, st + RM_TILE, offP, kf, vf, sm, dpm);       // S[q, kv] = Q K^T, dP[q, kv] = dO V^T
+        dkv_probs(st + 2 * RM_TILE + (uint32_t)(32 * T + 4 * fh) * 4u, sc, sm, dpm);
+        bf16x8 pf[2], dsf[2];
+        pack_acc(sm, pf);
+        pack_acc(dpm, dsf);
+        rm_mma_cols<D, T>(st + RM_TILE, offT, pf, dv);      // dV^T += dO^T P
+        rm_mma_cols<D, T>(st, offT, dsf, dk);               // dK^T += Q^T dS
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      part(diagonal, half0{});
+      part(diagonal, half1{});
+    }
   }
+  if constexpr (D == 128) { settle(dk); settle(dv); wait_vmcnt<0>(); }
   if (kpos < s) {
     bf16_t* out = static_cast<bf16_t*>(p.dqkv) + ((long)bi * s + kpos) * ld + hh * D;
     if (p.rope) rope_back<D>(dk, kpos, fh, p.rope_log2_base);

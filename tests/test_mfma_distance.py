@@ -143,6 +143,25 @@ class Kernel:
             self.walk(i, step)
         return found
 
+    def fresh_operands(self):
+        """(vector instruction, MFMA, wait states between them) for every MFMA that reads a register less than two wait
+        states behind the vector instruction that writes it: the compiler keeps them for its own MFMAs, not in inline assembly."""
+        found = []
+        for i, (op, _, rs) in enumerate(self.code):
+            if not op.startswith("v_") or op.startswith(("v_mfma", "v_cmp")) or not rs:
+                continue
+
+            def step(k, count):
+                o, operands, r = self.code[k]
+                if count >= 2:
+                    return None
+                if o.startswith("v_mfma") and any(x & rs[0] for x in r[1:]):
+                    found.append((i, k, count))
+                return count + (int(operands[0], 0) + 1 if o == "s_nop" else 1)
+
+            self.walk(i, step)
+        return found
+
     def unwaited_reads(self):
         """(LDS read, instruction) for every instruction that touches a read's registers before a wait that covers it."""
         found = []
@@ -206,6 +225,28 @@ def test_the_walk_finds_planted_mistakes():
     assert not k.early_uses()
     (k,) = kernels(EARLY_READ)
     assert [k.code[b][1] for _, b in k.unwaited_reads()] == [["v9", "v3"]]
+
+
+FRESH_OPERAND = """
+_Z13fresh_operandv:
+\tv_cvt_pk_bf16_f32 v3, v10, v11
+\ts_nop 0
+\tv_mfma_f32_32x32x16_bf16 a[0:15], v[4:7], v[0:3], a[0:15]
+\ts_endpgm
+.Lfunc_end0:
+"""
+
+
+@needs_compiler
+@pytest.mark.parametrize("source", ["attention.hip", "gemm.hip"])
+def test_no_mfma_reads_an_operand_that_the_vector_alu_has_just_written(library, source):
+    (k,) = kernels(FRESH_OPERAND)
+    assert [n for _, _, n in k.fresh_operands()] == [1]
+    (k,) = kernels(FRESH_OPERAND.replace("s_nop 0", "s_nop 1"))
+    assert not k.fresh_operands()
+    for k in library[source]:
+        show = lambda i: " ".join([k.code[i][0], ", ".join(k.code[i][1])])
+        assert not [(show(a), show(b), n) for a, b, n in k.fresh_operands()][:5], k.name
 
 
 @needs_compiler
