@@ -252,12 +252,12 @@ int next_sync_event(hipEvent_t* ev) {
 }
 
 enum ProfClass {
-  PC_NORM_FWD = 0, PC_GEMM_QKV, PC_ROPE, PC_ATTN_FWD, PC_GEMM_OUT, PC_GEMM_UP, PC_GEMM_DOWN, PC_RESID_OUT,
+  PC_NORM_FWD = 0, PC_GEMM_QKV, PC_ROPE, PC_ATTN_FWD, PC_GEMM_OUT, PC_GEMM_UP, PC_GEMM_DOWN,
   PC_DGRAD_DOWN, PC_WGRAD_DOWN, PC_DGRAD_UP, PC_WGRAD_UP, PC_NORM_BWD, PC_DGRAD_OUT, PC_WGRAD_OUT,
   PC_ATTN_BWD, PC_DGRAD_QKV, PC_WGRAD_QKV, PC_COLSUM, PC_WGRAD_JOINED, PC_COUNT
 };
 const char* const PROF_NAMES[PC_COUNT] = {
-  "norm_fwd", "gemm_qkv", "rope", "attn_fwd", "gemm_out", "gemm_up", "gemm_down", "residual_out",
+  "norm_fwd", "gemm_qkv", "rope", "attn_fwd", "gemm_out", "gemm_up", "gemm_down",
   "dgrad_down", "wgrad_down", "dgrad_up", "wgrad_up", "norm_bwd", "dgrad_out", "wgrad_out",
   "attn_bwd", "dgrad_qkv", "wgrad_qkv", "colsum", "wgrad_joined"};
 
@@ -533,7 +533,12 @@ int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
   TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F7
     ProfScope ps(PC_GEMM_DOWN, st);
     GemmArgs a = gemm_args(act(R), L.fl, P->w_down, L.h, at(B.mlp_partial, R.rh), L.h, R.n, L.h, L.fl);
-    LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "mlp-down product");
+    if (B.y && !next) {        // F8, the block output, with the product's last tiles
+      a.aux = x1(R); a.ldaux = L.h; a.add2 = B.mlp_others ? at(B.mlp_others, R.rh) : nullptr; a.bias = P->b_down; a.out2 = at(B.y, R.rh);
+      LAUNCH(gemm_launch(GEMM_NN, EPI_RESID, a, -1, st), "mlp-down product and block output");
+    } else {
+      LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "mlp-down product");
+    }
     return DOMINO_OK;
   }));
   return each_group([&](const Rows& R, hipStream_t st) -> int {
@@ -547,9 +552,6 @@ int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       a.rstd = reinterpret_cast<float*>(at(next->saved, L.rstd1)) + R.r0;
       a.rows = R.n; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
       LAUNCH(norm_fwd_launch(a, st), "block output + next norm1");
-    } else if (B.y) {  // F8
-      ProfScope ps(PC_RESID_OUT, st);
-      LAUNCH(residual_out_launch(x1(R), at(B.mlp_partial, R.rh), others, P->b_down, at(B.y, R.rh), (long)R.n * L.h, L.h, st), "block output");
     }
     return DOMINO_OK;
   });

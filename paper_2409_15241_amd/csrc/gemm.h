@@ -12,6 +12,7 @@ enum GemmEpilogue {
   EPI_DSWIGLU = 4,    // C[:, n] = acc * up * silu'(gate); C[:, n_split + n] = acc * silu(gate)
   EPI_ACC_F32 = 5,    // C(fp32) = acc (+ C if beta)
   EPI_ROPE = 6,       // C = bf16(acc) with the rotary embedding applied to columns below rope_cols (heads of rope_d columns)
+  EPI_RESID = 7,      // C = bf16(acc); out2 = bf16(aux + C + add2 + bias)   add2, bias optional: the block output with its last partial sum
 };
 enum GemmTile { GEMM_TILE_128x128 = 0, GEMM_TILE_256x128 = 1, GEMM_TILE_256x256 = 2, GEMM_TILE_128x256 = 3,
                 GEMM_TILE_64x64 = 4, GEMM_TILE_128x128_DEALT = 5,
@@ -25,6 +26,7 @@ struct GemmArgs {
   int M, N, K;
   const void* bias;      // bf16 [N] or null
   void* aux; long ldaux; // epilogue side tensor (read or written, see GemmEpilogue)
+  const void* add2; void* out2;      // EPI_RESID: bf16, rows of ldaux
   int n_split;           // SwiGLU: number of gate (= up) columns
   int beta;              // EPI_ACC_F32: 1 = accumulate into C
   int rope_d, rope_seq, rope_cols;   // EPI_ROPE: head width (64 or 128), sequence length (position = row % seq), rotated columns
@@ -63,12 +65,14 @@ constexpr GemmForm GEMM_FORMS[] = {
 // what the epilogue takes beyond storing bf16 sums, for 256x256 values: activations (vector ALUs), wider results
 inline double gemm_epilogue_time(int epi) {
   return epi == EPI_BIAS_GELU ? 5.9 : epi == EPI_SWIGLU ? 8.2 : epi == EPI_DGELU ? 8.9 : epi == EPI_DSWIGLU ? 10.6 :
-         epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : 0.0;
+         epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : epi == EPI_RESID ? 8.0 : 0.0;
 }
 inline bool gemm_form_takes(const GemmForm& f, int epi) { return (epi != EPI_SWIGLU && epi != EPI_ROPE) || (f.bn != 192 && f.bn != 320); }
+// (The block output moves four rows of bf16 where a plain product stores one; the last 32 columns of a 160-wide wave tile
+// do so in half lines.  GPT-3 2.7B 1459 us with its down-projection in 256x320 tiles, 1452 in 256x256.)
 // tiles of contraction `it` x 64 deep; 128x128 tiles run two to a compute unit
 inline double gemm_form_time(const GemmForm& f, double tiles, int it, int epi) {
-  const double fixed = f.fixed + gemm_epilogue_time(epi) * f.bm * f.bn / 65536;
+  const double fixed = f.fixed + (epi == EPI_RESID && f.bn == 320 ? 14.0 : gemm_epilogue_time(epi)) * f.bm * f.bn / 65536;
   if (f.id == GEMM_TILE_128x128) {
     const double rounds = floor(tiles / 512), rest = tiles - 512 * rounds, share = f.full * rest / 512;
     return 3 + rounds * 2 * (fixed + f.full * it) + (rest == 0 ? 0.0 : rest <= 256 ? fixed - 1.1 + 0.503 * (it < 40 ? it : 40) + (it < 40 ? 0.0 : 0.80 * (it - 40)) : 2 * (fixed + (f.lone > share ? f.lone : share) * it));

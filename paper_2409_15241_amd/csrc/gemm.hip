@@ -163,7 +163,7 @@ struct EpiCols {
       n_ok = n < p.N;
     }
     bias4 = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (EPI == EPI_STORE || EPI == EPI_BIAS_GELU) {
+    if constexpr (EPI == EPI_STORE || EPI == EPI_BIAS_GELU || EPI == EPI_RESID) {
       if (p.bias && n_ok) {
         const u32x2 bb = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.bias) + n);
         bias4 = f32x4{bf16_lo(bb[0]), bf16_hi(bb[0]), bf16_lo(bb[1]), bf16_hi(bb[1])};
@@ -183,7 +183,7 @@ struct RowStore {
   static constexpr int NR = ROWS / RPI;          // read-back instructions
   static constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_ROPE;
   struct Side {
-    u32x2 a[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU) ? NR : 1], b[EPI == EPI_DSWIGLU ? NR : 1];
+    u32x2 a[(EPI == EPI_DGELU || EPI == EPI_DSWIGLU || EPI == EPI_RESID) ? NR : 1], b[(EPI == EPI_DSWIGLU || EPI == EPI_RESID) ? NR : 1];
     f32x4 old[EPI == EPI_ACC_F32 ? NR : 1];
   };
   const GemmArgs& p;
@@ -205,6 +205,10 @@ struct RowStore {
         if (p.beta) s.old[t] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(p.C) + row * p.ldc + ns);
       } else if constexpr (EPI == EPI_DGELU) {
         s.a[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + row * p.ldaux + ns);
+      } else if constexpr (EPI == EPI_RESID) {
+        s.a[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.aux) + row * p.ldaux + ns);
+        s.b[t] = u32x2{0u, 0u};
+        if (p.add2) s.b[t] = *reinterpret_cast<const u32x2*>(static_cast<const bf16_t*>(p.add2) + row * p.ldaux + ns);
       } else if constexpr (EPI == EPI_DSWIGLU) {
         const bf16_t* aux = static_cast<const bf16_t*>(p.aux) + row * p.ldaux;
         s.a[t] = *reinterpret_cast<const u32x2*>(aux + ns);
@@ -276,6 +280,20 @@ struct RowStore {
           const u32x2 phi = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
           *reinterpret_cast<u32x2*>(crow) = plo;
           *reinterpret_cast<u32x2*>(crow + (p.rope_d >> 1)) = phi;
+        }
+      } else if constexpr (EPI == EPI_RESID) {
+        // the sum takes the partial sum as it is stored, in the order of the norm kernel that forms it between two blocks
+        const u32x2 pp = {pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
+        const float x1[4] = {bf16_lo(s.a[t][0]), bf16_hi(s.a[t][0]), bf16_lo(s.a[t][1]), bf16_hi(s.a[t][1])};
+        const float part[4] = {bf16_lo(pp[0]), bf16_hi(pp[0]), bf16_lo(pp[1]), bf16_hi(pp[1])};
+        const float oth[4] = {bf16_lo(s.b[t][0]), bf16_hi(s.b[t][0]), bf16_lo(s.b[t][1]), bf16_hi(s.b[t][1])};
+        float y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = ((x1[e] + part[e]) + oth[e]) + ec.bias4[e];
+        const u32x2 py = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+        if (ok) {
+          *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + row * p.ldc + n) = pp;
+          *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.out2) + row * p.ldaux + n) = py;
         }
       } else {
         w += ec.bias4;
@@ -890,6 +908,7 @@ hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hi
       case EPI_BIAS_GELU: return launch_layout<false, true, EPI_BIAS_GELU>(a, n, tile_cfg, stream);
       case EPI_SWIGLU:    return launch_layout<false, true, EPI_SWIGLU>(a, n, tile_cfg, stream);
       case EPI_ROPE:      return launch_layout<false, true, EPI_ROPE>(a, n, tile_cfg, stream);
+      case EPI_RESID:     return launch_layout<false, true, EPI_RESID>(a, n, tile_cfg, stream);
       default: return hipErrorInvalidValue;
     }
   } else if (layout == GEMM_NT) {

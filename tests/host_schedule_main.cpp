@@ -160,6 +160,8 @@ hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int, hipStream_t 
   r.push_back(reg(a.C, a.ldc, a.M, epi == EPI_DSWIGLU ? 2L * a.n_split : a.N, 2, true));
   if (a.bias) r.push_back(reg(a.bias, a.N, 1, a.N, 2, false));
   if (a.aux) r.push_back(reg(a.aux, a.ldaux, a.M, glu ? 2L * a.n_split : a.N, 2, epi == EPI_BIAS_GELU || epi == EPI_SWIGLU));
+  if (a.add2) r.push_back(reg(a.add2, a.ldaux, a.M, a.N, 2, false));
+  if (a.out2) r.push_back(reg(a.out2, a.ldaux, a.M, a.N, 2, true));
   launch(st, gemm_name(layout, epi), r);
   return hipSuccess;
 }

@@ -152,3 +152,27 @@ def test_weight_gradients_over_contraction_ranges(dom, seq, accumulate):
         grads.append({k: g.clone() for k, g in buf.grads.items() if g is not None})
     for k, g in grads[0].items():
         assert float((g - grads[1][k]).norm() / grads[1][k].norm()) < 1e-5, k
+
+
+# (hidden, ffn, batch, seq, arch, other ranks' sum): dealt, 128x128, 256x256 and 256x320 tiles, ragged rows
+BLOCK_OUTPUT = [(256, 512, 2, 37, synth.ARCH_GPT, True), (512, 2048, 3, 333, synth.ARCH_GPT, False), (512, 1376, 3, 333, synth.ARCH_LLAMA, True),
+                (1280, 320, 2, 4000, synth.ARCH_GPT, True), (2560, 320, 2, 4100, synth.ARCH_GPT, True)]
+
+
+@pytest.mark.parametrize("h,f,b,s,arch,others", BLOCK_OUTPUT)
+def test_block_output_is_the_rounded_sum_of_what_the_block_stores(dom, h, f, b, s, arch, others):
+    """y = ((x1 + mlp_partial) + others) + b_down in fp32 of the stored bf16 tensors, rounded once: bit for bit."""
+    from paper_2409_15241_amd import harness as H
+    sc = synth.ShardConfig(name="out", hidden=h, heads=h // 64, tp=1, rank=0, ffn=f, batch=b, seq=s, p=1, q=1, arch=arch)
+    params = synth.make_rank_params(sc, random_affine=True)
+    x, dy = synth.make_activations(sc)
+    buf = H.LayerBuffers(sc, params, x, dy, synth.make_others(sc) if others else None, nstreams=2)
+    buf.forward()
+    buf.sync()
+    x1 = buf.saved_tensor("x1").view(b, s, h).float()
+    y = x1 + buf.mlp_partial.float()
+    if others:
+        y = y + buf.mlp_others.float()
+    if buf.params["b_down"] is not None:
+        y = y + buf.params["b_down"].float()
+    assert torch.equal(buf.y, y.to(torch.bfloat16))
