@@ -1,4 +1,4 @@
-// Rotary embedding as a pass of its own (HBM-bound).
+// Small HBM-bound element-wise kernels: rotary embedding and the block's final residual sum.
 #include "eltwise.h"
 #include "common.h"
 
@@ -40,6 +40,27 @@ void rope_kernel(bf16_t* __restrict__ m, long ld, int rows, int seq, int col0, i
   }
 }
 
+__global__ __launch_bounds__(256)
+void residual_out_kernel(const u32x4* __restrict__ x1, const u32x4* __restrict__ a, const u32x4* __restrict__ b,
+                         const u32x4* __restrict__ vec, u32x4* __restrict__ y, long nchunks, int hch) {
+  const long c = (long)blockIdx.x * 256 + threadIdx.x;
+  if (c >= nchunks) return;
+  // all four loads are issued before the first use: absent operands read x1 again and are dropped
+  const u32x4 vx = x1[c], va = a[c];
+  const u32x4 vb = (b ? b : x1)[c];
+  const u32x4 vv = (vec ? vec : x1)[vec ? c % hch : c];
+  // same association as the fused norm kernel, ((x1 + a) + b) + vec with absent operands as +0, so that a
+  // caller may fold this sum into the next block's Norm1 without changing a bit
+  float f[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f[2 * e] = ((bf16_lo(vx[e]) + bf16_lo(va[e])) + (b ? bf16_lo(vb[e]) : 0.0f)) + (vec ? bf16_lo(vv[e]) : 0.0f);
+    f[2 * e + 1] = ((bf16_hi(vx[e]) + bf16_hi(va[e])) + (b ? bf16_hi(vb[e]) : 0.0f)) + (vec ? bf16_hi(vv[e]) : 0.0f);
+  }
+  u32x4 o = {pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])};
+  y[c] = o;
+}
+
 }  // namespace
 
 hipError_t rope_launch(void* m, long ld, int rows, int seq, int col0, int nblocks, int heads, int d,
@@ -48,5 +69,14 @@ hipError_t rope_launch(void* m, long ld, int rows, int seq, int col0, int nblock
   const int all = nblocks * heads, want = (int)(65536 / n);
   hipLaunchKernelGGL(rope_kernel, dim3((unsigned)((n + 255) / 256), want < 1 ? 1 : want < all ? want : all), dim3(256), 0, st,
                      static_cast<bf16_t*>(m), ld, rows, seq, col0, nblocks, heads, d, log2f(base), inverse);
+  return hipGetLastError();
+}
+
+hipError_t residual_out_launch(const void* x1, const void* a, const void* b, const void* vec, void* y,
+                               long n_elems, int h, hipStream_t st) {
+  const long nch = n_elems / 8;
+  hipLaunchKernelGGL(residual_out_kernel, dim3((unsigned)((nch + 255) / 256)), dim3(256), 0, st,
+                     static_cast<const u32x4*>(x1), static_cast<const u32x4*>(a), static_cast<const u32x4*>(b),
+                     static_cast<const u32x4*>(vec), static_cast<u32x4*>(y), nch, h / 8);
   return hipGetLastError();
 }
