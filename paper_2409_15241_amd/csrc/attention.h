@@ -29,13 +29,5 @@ inline bool attention_split_pays(const AttnArgs& a, bool backward) {
   return 4.5 + rounds * (1.5 + 1.1 * a.seq / 128) < 0.95 * (5 + 1.17 * steps);
 }
 
-// Whether the forward's workgroups of 128 queries take two waves for each 32.  One wave against two, us: 160 workgroups of
-// 2048 tokens 44.4 / 36.7, 256 of 4096 87.4 / 71.3, of 4096 and d 64 59.1 / 47.2, of 1024 24.6 / 21.6, 320 of 1024 26.1 / 23.2,
-// 384 of 1024 26.9 / 26.9, 512 of 1024 29.4 / 31.5: past 320 two workgroups of four waves share a CU anyway.  Short chains
-// don't earn the meeting of the sums: 80 workgroups of 512 tokens 13.1 / 13.4, 64 of 128 6.7 / 8.5; 42 of 777 19.4 / 18.1.
-inline bool attention_two_waves_pay(const AttnArgs& a) {
-  return a.seq > 640 && (long)((a.seq + 127) / 128) * a.heads * a.batch <= 320;
-}
-
 hipError_t attention_fwd_launch(const AttnArgs& a, hipStream_t st);
 hipError_t attention_bwd_launch(const AttnArgs& a, hipStream_t st);

@@ -123,27 +123,12 @@ DEV bool ranked_item(int per_group, int groups, int& pos, int& group) {
 }
 inline int ranked_grid(int per_group, int groups) { return ((per_group * groups + 7) / 8) * 8; }
 
-// Accumulators to LDS and back, 16 bytes a lane: value group (dt, g) of lane l at ((4 dt + g) * 64 + l) * 16.
-template <int N>
-DEV void put_acc(uint8_t* at, const f32x16 (&o)[N], int lane) {
-#pragma unroll
-  for (int dt = 0; dt < N; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<f32x4*>(at + ((4 * dt + g) * 64 + lane) * 16) = f32x4{o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
-}
-
 // One workgroup = 128 queries of one (batch element, head): 4 waves x 32 queries.  K and V tiles of 64
 // keys travel HBM/L2 -> LDS with buffer_load ... lds (double buffered, no VGPR staging): K as
 // contraction-contiguous [kv][32 d] sub-tiles, V as row-major [32 kv][d] sub-tiles read back with the
 // transposing LDS read in accumulator-row order, so P feeds P V straight from registers.
-// H = 2: eight waves, two for each 32 queries, which take the tiles of even and of odd index; their sums meet at the end.  A
-// workgroup is a chain along its keys, and where there are few workgroups the longest one is the launch: two waves on a SIMD
-// fill each other's waits.  2 x 4096 tokens, 4 heads of 128: 87.4 us with one wave, 71.3 with two.  Half a tile of offset
-// between the two, held by a second barrier, so that the products of one meet the softmax of the other: 76.0.  Four stages
-// of tiles for the one wave: 108.
-template <int D, int H>
-__global__ __launch_bounds__(256 * H, H == 1 ? 2 : 1)
+template <int D>
+__global__ __launch_bounds__(256, 2)
 void attn_fwd_kernel(const AttnArgs p) {
   using X = Dims<D>;
   constexpr int DS = (D + 31) / 32;                 // 32-wide d sub-tiles of K
@@ -153,7 +138,7 @@ void attn_fwd_kernel(const AttnArgs p) {
   constexpr int NB = (X::KSTEPS + 3) / 4;           // batches of up to 4 contraction steps over d
   extern __shared__ __align__(1024) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3, half = H == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 31, fh = lane >> 5;
   const int s = p.seq;
   const int nqb = (s + 127) / 128;
@@ -177,7 +162,7 @@ void attn_fwd_kernel(const AttnArgs p) {
   ldK.init_kc((int)ld, 0, 1 << 30, wave, lane);       // rows past the sequence end fall outside the extent
   ldV.init_ks((int)ld, IdentityCols{0, D}, wave, lane);
   auto issue_tile = [&](int j) {
-    uint8_t* st = smem + (j % (2 * H)) * STAGE;
+    uint8_t* st = smem + (j & 1) * STAGE;
     const int kv0 = j * 64;
 #pragma unroll
     for (int c = 0; c < DS; ++c) ldK.issue(rsK, st + c * 4096, c * 32, D, wave, (uint32_t)kv0 * (uint32_t)ld * 2u);
@@ -203,20 +188,18 @@ void attn_fwd_kernel(const AttnArgs p) {
   for (int dt = 0; dt < X::DT; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[dt][v] = 0.0f;
-  // one of two waves may have no tile: its maximum stays finite, and its weight is 2^(-3.4e38 - m) = 0
-  float m = H == 1 ? -INFINITY : -3.402823466e38f, l = 0.0f;
+  float m = -INFINITY, l = 0.0f;
   const float sc = p.scale * LOG2E;
   const uint32_t smem_base = lds_addr(smem);
 
-  if (half < ntiles) issue_tile(half);
-  for (int j0 = 0; j0 < ntiles; j0 += H) {
-    const int j = j0 + half;
+  issue_tile(0);
+  for (int j = 0; j < ntiles; ++j) {
     wait_vmcnt<0>();                                  // tile j has landed (this wave's part)
     __builtin_amdgcn_s_barrier();                     // ... everybody's part; the other stage is free
-    if (j + H < ntiles) issue_tile(j + H);
+    if (j + 1 < ntiles) issue_tile(j + 1);
     const int kv0 = j * 64;
-    if (kv0 > qw0 + 31 || (H > 1 && j >= ntiles)) continue;   // every key of the tile is masked for this wave, or no tile is left
-    const uint32_t st = smem_base + (j % (2 * H)) * STAGE;
+    if (kv0 > qw0 + 31) continue;                     // every key of the tile is masked for this wave
+    const uint32_t st = smem_base + (j & 1) * STAGE;
 
     // ---- S^T[kv, q] = K Q^T: batches of 4 contraction steps, next batch's reads in flight
     f32x16 sT[2];
@@ -272,7 +255,7 @@ void attn_fwd_kernel(const AttnArgs p) {
         for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[t][v]);
     }
     mx = fmaxf(mx, other_half(mx)) * sc;       // scores scaled to the log2 domain (sc > 0)
-    const float m_new = fmaxf(m, mx);                  // finite: the tile's first key is visible to all queries of the wave
+    const float m_new = fmaxf(m, mx);                  // finite: key 0 is visible to every query
     if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {   // rescale only when some query's maximum moved
       const float alpha = exp2_raw(m - m_new);
       l *= alpha;
@@ -325,31 +308,6 @@ void attn_fwd_kernel(const AttnArgs p) {
         o[DTI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pf[s4], o[DTI], 0, 0, 0);
       }
     });
-  }
-  if constexpr (H == 2) {
-    // wave w + 4's maximum, sum and products to wave w: 16 bytes a lane, behind each other in the stages
-    static_assert(4 * (X::DT * 4096 + 512) <= 4 * STAGE, "the sums of four waves fit the stages");
-    uint8_t* const mine = smem + wave * (X::DT * 4096 + 512);
-    __builtin_amdgcn_s_barrier();                     // everybody has read the last tiles
-    if (half == 1) {
-      put_acc(mine, o, lane);
-      reinterpret_cast<float*>(mine + X::DT * 4096)[lane] = m;
-      reinterpret_cast<float*>(mine + X::DT * 4096 + 256)[lane] = l;
-    }
-    __syncthreads();
-    if (half == 1) return;
-    const float m1 = reinterpret_cast<const float*>(mine + X::DT * 4096)[lane], l1 = reinterpret_cast<const float*>(mine + X::DT * 4096 + 256)[lane];
-    const float m_all = fmaxf(m, m1), a0 = exp2_raw(m - m_all), a1 = exp2_raw(m1 - m_all);      // a wave without a tile: 2^-inf = 0
-    l = l * a0 + l1 * a1;
-    m = m_all;
-#pragma unroll
-    for (int dt = 0; dt < X::DT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(mine + ((4 * dt + g) * 64 + lane) * 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[dt][4 * g + e] = o[dt][4 * g + e] * a0 + v[e] * a1;
-      }
   }
   l += other_half(l);
   if (qpos < s) {
@@ -984,6 +942,15 @@ struct SplitLoader {         // one wave, 8 one-KiB pieces (4 rows each) of a 32
   }
 };
 
+// Accumulators to LDS and back, 16 bytes a lane: value group (dt, g) of lane l at ((4 dt + g) * 64 + l) * 16.
+template <int N>
+DEV void put_acc(uint8_t* at, const f32x16 (&o)[N], int lane) {
+#pragma unroll
+  for (int dt = 0; dt < N; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4*>(at + ((4 * dt + g) * 64 + lane) * 16) = f32x4{o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+}
 template <int N>
 DEV void sum_acc(const uint8_t* at, f32x16 (&o)[N], int lane) {      // over the four waves, in wave order
 #pragma unroll
@@ -1279,18 +1246,10 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   constexpr int LDS = 2 * (((D + 31) / 32) * 4096 + 2 * 8192);
-  const dim3 grid(ranked_grid((a.seq + 127) / 128, a.heads * a.batch));
-  if (attention_two_waves_pay(a)) {
-    static LdsLimitOnce lds_limit;
-    hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_kernel<D, 2>), 2 * LDS);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_fwd_kernel<D, 2>), grid, dim3(512), 2 * LDS, st, a);
-    return hipGetLastError();
-  }
   static LdsLimitOnce lds_limit;
-  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_kernel<D, 1>), LDS);
+  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_kernel<D>), LDS);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_fwd_kernel<D, 1>), grid, dim3(256), LDS, st, a);
+  hipLaunchKernelGGL(attn_fwd_kernel<D>, dim3(ranked_grid((a.seq + 127) / 128, a.heads * a.batch)), dim3(256), LDS, st, a);
   return hipGetLastError();
 }
 

@@ -133,17 +133,6 @@ def test_attention_with_few_and_with_many_workgroups(dom, d, b, s, nh):
         assert relerr(got[:, i * hl:(i + 1) * hl], back(ref)) < 1.5e-2
 
 
-# (batch, seq, heads): the first sequence with two waves for 32 queries, odd and even numbers of 64-key tiles, ragged last
-# ones, the last grid of workgroups (320 of 128 queries)
-ATTN_TWO_WAVES = [(1, 641, 3), (1, 704, 1), (2, 769, 2), (1, 1000, 4), (1, 1153, 1), (4, 1280, 8)]
-
-
-@pytest.mark.parametrize("d", [64, 80, 128])
-@pytest.mark.parametrize("b,s,nh", ATTN_TWO_WAVES)
-def test_attention_with_two_waves_for_32_queries(dom, d, b, s, nh):
-    test_attention_with_few_and_with_many_workgroups(dom, d, b, s, nh)
-
-
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("seq", RANGE_SEQS)
 def test_weight_gradients_over_contraction_ranges(dom, seq, accumulate):
