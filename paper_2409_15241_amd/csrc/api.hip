@@ -251,13 +251,14 @@ int next_sync_event(hipEvent_t* ev) {
   return DOMINO_OK;
 }
 
+// residual_out: the block output as a pass of its own (two row groups); in the MLP-down product's epilogue it is part of gemm_down
 enum ProfClass {
-  PC_NORM_FWD = 0, PC_GEMM_QKV, PC_ROPE, PC_ATTN_FWD, PC_GEMM_OUT, PC_GEMM_UP, PC_GEMM_DOWN,
+  PC_NORM_FWD = 0, PC_GEMM_QKV, PC_ROPE, PC_ATTN_FWD, PC_GEMM_OUT, PC_GEMM_UP, PC_GEMM_DOWN, PC_RESID_OUT,
   PC_DGRAD_DOWN, PC_WGRAD_DOWN, PC_DGRAD_UP, PC_WGRAD_UP, PC_NORM_BWD, PC_DGRAD_OUT, PC_WGRAD_OUT,
   PC_ATTN_BWD, PC_DGRAD_QKV, PC_WGRAD_QKV, PC_COLSUM, PC_WGRAD_JOINED, PC_COUNT
 };
 const char* const PROF_NAMES[PC_COUNT] = {
-  "norm_fwd", "gemm_qkv", "rope", "attn_fwd", "gemm_out", "gemm_up", "gemm_down",
+  "norm_fwd", "gemm_qkv", "rope", "attn_fwd", "gemm_out", "gemm_up", "gemm_down", "residual_out",
   "dgrad_down", "wgrad_down", "dgrad_up", "wgrad_up", "norm_bwd", "dgrad_out", "wgrad_out",
   "attn_bwd", "dgrad_qkv", "wgrad_qkv", "colsum", "wgrad_joined"};
 
@@ -557,7 +558,7 @@ int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       a.rows = R.n; a.h = L.h; a.rms = rms; a.eps = cfg->norm_eps;
       LAUNCH(norm_fwd_launch(a, st), "block output + next norm1");
     } else if (B.y && !y_in_product) {
-      ProfScope ps(PC_GEMM_DOWN, st);
+      ProfScope ps(PC_RESID_OUT, st);
       LAUNCH(residual_out_launch(x1(R), at(B.mlp_partial, R.rh), others, P->b_down, at(B.y, R.rh), (long)R.n * L.h, L.h, st), "block output");
     }
     return DOMINO_OK;

@@ -11,7 +11,7 @@
 //   - the vector gradients sum partial rows that were written in this backward, and no launch writes over another's;
 //   - over the parts of one backward every gradient is formed exactly once, whatever pool each part is handed and whichever
 //     of them are captured or timed launch by launch;
-//   - timing a step launch by launch changes none of its launches;
+//   - timing a step launch by launch changes none of its launches, and times each under its own step's name;
 //   - a captured call uses no event twice, and pools outside domino_capture_supported() are refused while capturing.
 // Nothing here touches a GPU.  Exit status 0 = every expectation held.
 #include <algorithm>
@@ -632,7 +632,18 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
   return cases;
 }
 
-// Per-launch timing adds event records and nothing else: the launches of a timed step are those of an untimed one.
+// The step class that a launch's record has to carry: products by their place in the block, the rest by what they are.
+static bool class_fits(const std::string& cls, const std::string& what) {
+  auto starts = [&](const char* s) { return cls.rfind(s, 0) == 0; };
+  if (what == "colsum_partial" || what == "vector_gradients") return cls == "colsum";
+  if (what.rfind("gemm", 0) == 0) return starts("gemm_");
+  if (what.rfind("dgrad", 0) == 0) return starts("dgrad_");
+  if (what.rfind("wgrad", 0) == 0) return starts("wgrad_");
+  return cls == what;        // norm_fwd, norm_bwd, attn_fwd, attn_bwd, rope, residual_out
+}
+
+// Per-launch timing adds event records and nothing else: the launches of a timed step are those of an untimed one, and
+// every record carries the class of the launches that it brackets.
 static void run_timed(int arch, int p, int nstreams) {
   char name[160];
   std::snprintf(name, sizeof(name), "%s%s p=%d streams=%d timed", SIZE_NAMES[g_size], arch ? "llama" : "gpt", p, nstreams);
@@ -660,12 +671,23 @@ static void run_timed(int arch, int p, int nstreams) {
       if (o.kind == Op::LAUNCH) seen[timed].push_back(o);
     // the timing events of a stream come in pairs, and every pair brackets launches
     std::map<hipStream_t, int> open;           // launches since the start event, or -1 outside a pair
+    std::map<hipStream_t, std::vector<std::string>> inside;
+    int record = 0;
     for (const Op& o : g_ops) {
       int& n = open.emplace(o.stream, -1).first->second;
-      if (o.kind == Op::LAUNCH && n >= 0) ++n;
+      if (o.kind == Op::LAUNCH && n >= 0) { ++n; inside[o.stream].push_back(o.what); }
       if (o.kind == Op::LAUNCH && timed) EXPECT(n > 0, "a launch (%s) is not timed", o.what.c_str());
       if (o.kind != Op::RECORD || *static_cast<int*>(o.event) != 1) continue;
       EXPECT(n != 0, "two timing events with nothing between them");
+      if (n > 0) {                             // the pair's second event: records are kept in the order in which pairs close
+        int cls = -1;
+        void* on = nullptr;
+        double from, to;
+        EXPECT(domino_profile_record(record++, &cls, &on, &from, &to) == DOMINO_OK && on == o.stream, "record %d is of another stream", record - 1);
+        for (const std::string& what : inside[o.stream])
+          EXPECT(class_fits(domino_profile_name(cls), what), "a launch (%s) is timed as %s", what.c_str(), domino_profile_name(cls));
+        inside[o.stream].clear();
+      }
       n = n < 0 ? 0 : -1;
     }
   }

@@ -148,6 +148,8 @@ def test_single_kernel_entry_points_validate():
     assert lib.domino_colsum(1, 64, 4, 60, 1, 0, 1, None) == domino.ERR_UNSUPPORTED
     assert lib.domino_norm_bwd_scratch_floats(2048, 5120) == 2 * 128 * 5120
     assert lib.domino_profile_classes() >= 18 and lib.domino_profile_name(1) == b"gemm_qkv"
+    # a class keeps its number: programs that read by number find the steps where they were
+    assert [lib.domino_profile_name(c) for c in (6, 7, 8, 19)] == [b"gemm_down", b"residual_out", b"dgrad_down", b"wgrad_joined"]
     assert lib.domino_profile_read(99, None, None) == domino.ERR_INVALID_ARG
     assert lib.domino_profile_records() == 0
     assert lib.domino_profile_record(0, None, None, None, None) == domino.ERR_NULL_POINTER
