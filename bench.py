@@ -50,6 +50,31 @@ def class_flops_per_step(sc, classes):
     return out
 
 
+def kernel_instances(sc, classes, layers=1):
+    """{kernel instantiation (= one line of a rocprofv3 kernel summary): the step classes whose launches run it}, for the
+    classes that left launch records.  The MLP-down product of a block whose rows are one group forms the block output in its
+    epilogue, another instantiation than the plain store (in a stack only the last block's does, the others share its class),
+    and so does a QKV product that applies the rotary embedding."""
+    llama = bool(sc.arch)
+    rotary = llama and sc.head_dim in (64, 128)               # applied in the QKV product's epilogue
+    down_alone = "residual_out" in classes                    # two row groups: the output is a pass of its own
+    stores = [("qkv", "gemm_qkv")] * (not rotary) + [("out-proj", "gemm_out")] + [("mlp-down", "gemm_down")] * down_alone
+    names = [n for n, _ in stores]
+    listed = ", ".join(names[:-1]) + " and " + names[-1] if len(names) > 1 else names[0]
+    out = {f"gemm_kernel<NN, store> ({listed} product{'s' * (len(names) > 1)})": [c for _, c in stores],
+           ("gemm_kernel<NN, swiglu> (mlp-up product)" if llama else "gemm_kernel<NN, bias+gelu> (mlp-up product)"): ["gemm_up"],
+           "gemm_kernel<NT, store> (input gradients of mlp-up, out-proj, qkv)": ["dgrad_up", "dgrad_out", "dgrad_qkv"],
+           ("gemm_kernel<NT, dswiglu> (input gradient of mlp-down)" if llama else "gemm_kernel<NT, dgelu> (input gradient of mlp-down)"): ["dgrad_down"],
+           "gemm_kernel and gemm_group_kernel<TN, fp32 accumulate> (the four weight gradients)": [*WGRADS, "wgrad_joined"]}
+    if rotary:
+        out["gemm_kernel<NN, rotary> (qkv product)"] = ["gemm_qkv"]
+    if not down_alone:
+        out["gemm_kernel<NN, block output> (mlp-down product)" if layers == 1 else
+            "gemm_kernel<NN, store> and, in the last block, <NN, block output> (mlp-down products)"] = ["gemm_down"]
+    out = {k: [c for c in v if c in classes] for k, v in out.items()}
+    return {k: v for k, v in out.items() if v}
+
+
 def algorithmic_flops(sc):
     M = sc.tokens
     gemm = 2.0 * M * (sc.hidden * 3 * sc.h_local + sc.h_local * sc.hidden + sc.hidden * sc.up_cols
@@ -312,22 +337,13 @@ def main():
         domino.domino_profile_reset()
         # flops per step of one block; a stack's records are those of all its blocks
         per = {c: f * args.layers for c, f in class_flops_per_step(sc, table).items()}
-        # step classes that run the same kernel instantiation (= one line of a rocprofv3 kernel summary)
-        llama = bool(sc.arch)
-        instances = {
-            "gemm_kernel<NN, store> (qkv, out-proj and mlp-down products)": ["gemm_qkv", "gemm_out", "gemm_down"],
-            ("gemm_kernel<NN, swiglu> (mlp-up product)" if llama else "gemm_kernel<NN, bias+gelu> (mlp-up product)"): ["gemm_up"],
-            "gemm_kernel<NT, store> (input gradients of mlp-up, out-proj, qkv)": ["dgrad_up", "dgrad_out", "dgrad_qkv"],
-            ("gemm_kernel<NT, dswiglu> (input gradient of mlp-down)" if llama else "gemm_kernel<NT, dgelu> (input gradient of mlp-down)"): ["dgrad_down"],
-            "gemm_kernel and gemm_group_kernel<TN, fp32 accumulate> (the four weight gradients)": [*WGRADS, "wgrad_joined"],
-        }
+        instances = kernel_instances(sc, table, args.layers)
         agg = {}
         for name, classes in instances.items():
-            t = sum(table[c][0] for c in classes if c in table)
-            n = sum(table[c][1] for c in classes if c in table)
-            f = sum(per[c] for c in classes if c in table) * args.steps
-            if n:
-                agg[name] = (t, n, f)
+            t = sum(table[c][0] for c in classes)
+            n = sum(table[c][1] for c in classes)
+            f = sum(per[c] for c in classes) * args.steps
+            agg[name] = (t, n, f)
         # the dominant kernel: most time on its streams; of those within 10 % of the longest (two instantiations can
         # trade places from run to run) the one that carries more of the step's flops
         longest = max(v[0] for v in agg.values())

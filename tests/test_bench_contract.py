@@ -42,6 +42,27 @@ def test_launch_records_are_charged_the_flops_of_the_whole_step_once():
         assert abs(sum(per.values()) + attention - bench.algorithmic_flops(sc)) <= 1e-9 * bench.algorithmic_flops(sc)
 
 
+def test_kernel_instances_name_the_kernel_that_a_class_runs():
+    """Each GEMM class belongs to one kernel; the pass that forms the block output of two row groups to none.  The MLP-down
+    product that forms it itself and the QKV product that applies the rotary embedding are not counted as plain stores."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2409_15241_amd import synth
+    classes = ["norm_fwd", "gemm_qkv", "gemm_out", "gemm_up", "gemm_down", "dgrad_down", "dgrad_up", "dgrad_out", "dgrad_qkv", "wgrad_joined"]
+    for name in ("gpt3-13b", "llama2-13b"):
+        sc = synth.WORKLOADS[name]
+        for extra, layers in ((["residual_out"], 1), (["residual_out"], 4), ([], 1), ([], 4)):
+            inst = bench.kernel_instances(sc, classes + extra, layers)
+            assert sorted(c for v in inst.values() for c in v) == sorted(c for c in classes if c != "norm_fwd")
+            of = {c: k for k, v in inst.items() for c in v}
+            assert "<NN, store>" in of["gemm_out"]
+            assert (of["gemm_qkv"] == of["gemm_out"]) == (name == "gpt3-13b") and ("rotary" in of["gemm_qkv"]) == (name == "llama2-13b")
+            assert (of["gemm_down"] == of["gemm_out"]) == bool(extra) and ("block output" in of["gemm_down"]) == (not extra)
+    # the names under which profiles/hbm_traffic_per_launch.md holds this shard's traffic
+    for kernel in bench.kernel_instances(synth.WORKLOADS["gpt3-13b"], classes + ["residual_out"]):
+        assert bench.measured_traffic("gpt3-13b", kernel)
+
+
 @pytest.mark.gpu
 def test_bench_prints_one_json_line_with_the_contract_keys():
     torch = pytest.importorskip("torch")
