@@ -105,11 +105,17 @@ inline int gemm_wgrad_splits(int tiles, int depth, long floats) {
 // ragged edges only, the other launches fill the rest of its last round; beside one other, a third of the way from there to a launch alone.
 // The dealt forms (gemm_split_body of gemm.hip) sum in another order than the rest: whether they are taken is decided as if nothing
 // ran beside the launch, so that no bit of a result depends on the stream pool, and products meant to run beside others
-// never take them.  They win where the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep
+// never take them.  The product that forms the block output in its epilogue takes them where the plain product does, which
+// a stack runs in its place in all blocks but the last: a block's sums are the same alone and in a stack.
+// They win where the other shapes leave most of the chip idle: 512 rows x 1920 columns x 5120 deep
 // 41 -> 19 us, 240 x 2688 x 7168 82 -> 31, 1024 x 2688 x 7168 79 -> 57, 2048 x 1920 x 5120 55 -> 46, 256 x 1024 x 1024
 // 10.0 -> 6.5; about 3000 deep the plain 128x128 tile meets the dealt one.
 inline int gemm_pick_form(const GemmArgs* products, int n, int epi, int concurrency) {
   if (concurrency < 1) concurrency = 1;
+  if (epi == EPI_RESID) {
+    const int plain = gemm_pick_form(products, n, EPI_STORE, concurrency);
+    if (plain == GEMM_TILE_64x64 || plain == GEMM_TILE_128x128_DEALT) return plain;
+  }
   const int splits = products[0].splits > 1 ? products[0].splits : 1;
   auto tiles_of = [&](int bm, int bn) {
     double t = 0;
@@ -134,7 +140,7 @@ inline int gemm_pick_form(const GemmArgs* products, int n, int epi, int concurre
     const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.35 * alone + 0.65 * shared : shared;
     if (cost < best_cost * 0.999) { best_cost = cost; best = f.id; }
   }
-  if (products[0].beside || splits > 1) return best;
+  if (products[0].beside || splits > 1 || epi == EPI_RESID) return best;
   const double dealt64 = 1.7 + ceil(tiles_of(64, 64) / 256) * (1.9 + (epi == EPI_SWIGLU ? 0.23 : 0.07) * extra + 1.68 * ((it + 7) / 8));
   const double dealt128 = 3 + ceil(tiles_of(128, 128) / 256) * (7.0 + 0.36 * extra + 0.403 * it);
   if ((dealt64 < dealt128 ? dealt64 : dealt128) >= best_alone) return best;

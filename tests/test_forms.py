@@ -14,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CLANG = "/opt/rocm/llvm/bin/clang++"
 pytestmark = pytest.mark.skipif(not os.path.exists(CLANG) and not shutil.which("g++"), reason="needs a C++ compiler")
 TILE_64_DEALT, TILE_128_DEALT = 4, 5
-EPI_ROPE = 6
+EPI_ROPE, EPI_RESID = 6, 7       # of csrc/gemm.h: not among the single-kernel entry points' epilogues
 
 
 @pytest.fixture(scope="module")
@@ -65,6 +65,23 @@ def test_ranges_of_the_gpu_test(ask):
         h, f = 512, 2048
         tiles = sum(-(-a // 256) * -(-b // 256) for a, b in ((f, h), (h, f), (h, h), (h, 3 * h)))
         assert ask([("ranges", tiles, 16 * seq, h * (4 * h + 2 * f))])[0] > 1
+
+
+# (hidden, ffn columns, batch, seq) of blocks whose MLP-down product was dealt with the block output in its epilogue and not
+# without: 4 x 66 tokens of the Llama-2 7B shard, 16 x 257 of the smallest GPT block
+ORDER_OF_BLOCK_OUTPUT = [(4096, 1376, 4, 66), (256, 512, 16, 257), (256, 48, 1, 233)]
+
+
+def test_a_block_sums_alike_alone_and_in_a_stack(ask):
+    """The last block of a stack, and a block alone, form the block output in the MLP-down product; the other blocks of a
+    stack run the plain product.  Results are bitwise the same only if both deal the contraction in the same way."""
+    rng = random.Random(5)
+    order = lambda f: f if f in (TILE_64_DEALT, TILE_128_DEALT) else "whole"
+    shapes = [(b * s, h, fl) for h, fl, b, s in ORDER_OF_BLOCK_OUTPUT]
+    shapes += [(rng.randrange(60, 9000), rng.randrange(4, 129) * 64, rng.randrange(4, 400) * 8) for _ in range(4000)]
+    for c in (1, 2, 4):
+        plain, out = (ask([("gemm", e, *x, c, 0) for x in shapes]) for e in (D.EPI_STORE, EPI_RESID))
+        assert [x for x, f, g in zip(shapes, plain, out) if order(f) != order(g)] == []
 
 
 def test_whether_a_contraction_is_dealt_does_not_depend_on_the_streams(ask):

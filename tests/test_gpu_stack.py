@@ -78,6 +78,16 @@ def test_stack_with_weight_gradients_slice_by_slice(H, base):
     stack_against_single_blocks(H, synth.WORKLOADS[base].replace(p=4, q=2, batch=4, wgrad_per_slice=1), 4, 4)
 
 
+# (hidden, ffn columns, local heads, head width, batch, seq, arch): the shapes of ORDER_OF_BLOCK_OUTPUT of test_forms.py
+@pytest.mark.parametrize("h,fl,nl,d,b,s,arch", [(4096, 1376, 4, 128, 4, 66, synth.ARCH_LLAMA), (256, 512, 2, 64, 16, 257, synth.ARCH_GPT),
+                                                (256, 48, 1, 64, 1, 233, synth.ARCH_GPT)])
+def test_stack_is_bitwise_single_blocks_where_the_block_output_comes_out_of_a_shallow_product(H, h, fl, nl, d, b, s, arch):
+    """The product of the last block forms the block output, those below it are plain: they sum in the same order."""
+    tp = h // d // nl
+    sc = synth.ShardConfig(name="order", hidden=h, heads=h // d, tp=tp, rank=0, ffn=fl * tp, batch=b, seq=s, p=1, q=1, arch=arch)
+    stack_against_single_blocks(H, sc, 2, 2)
+
+
 def stack_against_single_blocks(H, sc, nlayers, nstreams):
     from paper_2409_15241_amd import domino
     params, others = synth.make_stack(sc, nlayers, random_affine=True)
