@@ -251,7 +251,7 @@ int next_sync_event(hipEvent_t* ev) {
   return DOMINO_OK;
 }
 
-// residual_out: the block output as a pass of its own (two row groups); in the MLP-down product's epilogue it is part of gemm_down
+// residual_out: the block output as a pass of its own; in the MLP-down product's epilogue it is part of gemm_down
 enum ProfClass {
   PC_NORM_FWD = 0, PC_GEMM_QKV, PC_ROPE, PC_ATTN_FWD, PC_GEMM_OUT, PC_GEMM_UP, PC_GEMM_DOWN, PC_RESID_OUT,
   PC_DGRAD_DOWN, PC_WGRAD_DOWN, PC_DGRAD_UP, PC_WGRAD_UP, PC_NORM_BWD, PC_DGRAD_OUT, PC_WGRAD_OUT,
@@ -531,10 +531,11 @@ int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     else { a.bias = P->b_up; LAUNCH(gemm_launch(GEMM_NN, EPI_BIAS_GELU, a, -1, st), "mlp-up product"); }
     return DOMINO_OK;
   }));
-  // F8, the block output, in the product's epilogue where one row group is the chain (Llama-2 7B 1574 -> 1558 us, 6018 tokens
-  // of 2.7B 643 -> 638, 256 tokens 84.6 -> 82.5; 13B at 2048 tokens 658 -> 661); with two, one group's pass over memory runs
-  // beside the other's product (13B at 8192 tokens is 0.7 % faster with the pass)
-  const bool y_in_product = B.y && !next && L.groups == 1;
+  // F8, the block output, in the product's epilogue where one row group is the chain and gemm_forms_output says so; with two
+  // groups a pass, which runs beside the other group's product.  (Forward, us, pass and epilogue: 13B with 8192 tokens 721
+  // and 738, Llama-2 7B with 16384 952 and 941, with 8 x 1024 532 and 535, 30B 1215 and 1208, Llama-2 13B 1387 and 1373;
+  // their forward + backward is level to 1 %.)
+  const bool y_in_product = B.y && !next && L.groups == 1 && gemm_forms_output(L.M, L.h, L.fl);
   TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F7
     ProfScope ps(PC_GEMM_DOWN, st);
     GemmArgs a = gemm_args(act(R), L.fl, P->w_down, L.h, at(B.mlp_partial, R.rh), L.h, R.n, L.h, L.fl);

@@ -67,12 +67,13 @@ inline double gemm_epilogue_time(int epi) {
   return epi == EPI_BIAS_GELU ? 5.9 : epi == EPI_SWIGLU ? 8.2 : epi == EPI_DGELU ? 8.9 : epi == EPI_DSWIGLU ? 10.6 :
          epi == EPI_ACC_F32 ? 5.0 : epi == EPI_ROPE ? 4.0 : epi == EPI_RESID ? 8.0 : 0.0;
 }
-inline bool gemm_form_takes(const GemmForm& f, int epi) { return (epi != EPI_SWIGLU && epi != EPI_ROPE) || (f.bn != 192 && f.bn != 320); }
-// (The block output moves four rows of bf16 where a plain product stores one; the last 32 columns of a 160-wide wave tile
-// do so in half lines.  GPT-3 2.7B 1459 us with its down-projection in 256x320 tiles, 1452 in 256x256.)
+inline bool gemm_form_takes(const GemmForm& f, int epi) {
+  if (epi == EPI_RESID) return f.bn != 320;                    // see gemm_forms_output
+  return (epi != EPI_SWIGLU && epi != EPI_ROPE) || (f.bn != 192 && f.bn != 320);
+}
 // tiles of contraction `it` x 64 deep; 128x128 tiles run two to a compute unit
 inline double gemm_form_time(const GemmForm& f, double tiles, int it, int epi) {
-  const double fixed = f.fixed + (epi == EPI_RESID && f.bn == 320 ? 14.0 : gemm_epilogue_time(epi)) * f.bm * f.bn / 65536;
+  const double fixed = f.fixed + gemm_epilogue_time(epi) * f.bm * f.bn / 65536;
   if (f.id == GEMM_TILE_128x128) {
     const double rounds = floor(tiles / 512), rest = tiles - 512 * rounds, share = f.full * rest / 512;
     return 3 + rounds * 2 * (fixed + f.full * it) + (rest == 0 ? 0.0 : rest <= 256 ? fixed - 1.1 + 0.503 * (it < 40 ? it : 40) + (it < 40 ? 0.0 : 0.80 * (it - 40)) : 2 * (fixed + (f.lone > share ? f.lone : share) * it));
@@ -145,6 +146,21 @@ inline int gemm_pick_form(const GemmArgs* products, int n, int epi, int concurre
   const double dealt128 = 3 + ceil(tiles_of(128, 128) / 256) * (7.0 + 0.36 * extra + 0.403 * it);
   if ((dealt64 < dealt128 ? dealt64 : dealt128) >= best_alone) return best;
   return dealt64 < dealt128 ? GEMM_TILE_64x64 : GEMM_TILE_128x128_DEALT;
+}
+
+// Whether the product that completes a block's sums forms the block output in its epilogue (EPI_RESID), or a pass over memory
+// does behind the plain product.  The epilogue moves four rows of bf16 where a plain one stores one: it saves a launch and
+// the sums' way through memory, but runs at a tile's end, with the matrix cores idle.  That pays except where the plain
+// product takes 256x320 tiles: one round of those or little more has the longest epilogues, and the last 32 columns of a
+// 160-wide wave tile move in half lines.  (Forward of a block, us, pass and epilogue.  256x320: 2.7B with 8192 tokens 281
+// and 288, 13B with 4096 391 and 397, Llama-2 13B with 4096 385 and 390, 2.7B with 16384 520 and 525.  Other tiles: 2.7B
+// with 4096 160 and 156, with 6018 228 and 225, 13B with 1024 156 and 151, with 2048 237 and 235, Llama-2 7B with 2 x 4096
+// 599 and 587, a 1024-wide block with 16384 329 and 324; 6.7B with 4096 and 30B with 2048 are level, a 3072-wide one with
+// 4096 is 1 % slower.)
+inline bool gemm_forms_output(int M, int N, int K) {
+  GemmArgs a{};
+  a.M = M; a.N = N; a.K = K;
+  return gemm_pick_form(&a, 1, EPI_STORE, 1) != GEMM_TILE_256x320;
 }
 
 hipError_t gemm_launch(int layout, int epi, const GemmArgs& a, int tile_cfg, hipStream_t stream);

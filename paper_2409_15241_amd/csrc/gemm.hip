@@ -869,7 +869,7 @@ hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t str
     case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_256x192: if constexpr (!PAIRED) return launch_cfg<256, 192, 128, 96, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
-    case GEMM_TILE_256x320: if constexpr (!PAIRED) return launch_cfg<256, 320, 128, 160, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
+    case GEMM_TILE_256x320: if constexpr (!PAIRED && EPI != EPI_RESID) return launch_cfg<256, 320, 128, 160, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
     case GEMM_TILE_192x256: return launch_cfg<192, 256, 96, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_320x256: return launch_cfg<320, 256, 160, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_64x64:   return launch_cfg<64, 64, 64, 64, AKS, BKS, EPI>(a, n, stream);

@@ -1,6 +1,7 @@
 // Which form the launchers pick for given sizes, from the rules in csrc/gemm.h and csrc/attention.h alone (no GPU, no
 // library).  Reads one question per line and answers each with one number:
 //   gemm <epilogue> <M> <N> <K> <concurrency> <beside>   GemmTile of one product (SwiGLU: N gate columns)
+//   output <M> <N> <K>                                    1: the block output in the product's epilogue, 0: a pass
 //   attention <backward> <batch> <seq> <heads>            1: 32 positions per workgroup, 0: 128
 //   ranges <tiles> <depth> <floats>                       contraction ranges of joined weight gradients
 #include <cstdio>
@@ -18,6 +19,8 @@ int main() {
       GemmArgs a{};
       a.M = (int)v[1]; a.N = a.n_split = (int)v[2]; a.K = (int)v[3]; a.beside = (int)v[5];
       std::printf("%d\n", gemm_pick_form(&a, 1, (int)v[0], (int)v[4]));
+    } else if (n == 4 && !std::strcmp(what, "output")) {
+      std::printf("%d\n", gemm_forms_output((int)v[0], (int)v[1], (int)v[2]) ? 1 : 0);
     } else if (n == 5 && !std::strcmp(what, "attention")) {
       AttnArgs a{};
       a.batch = (int)v[1]; a.seq = (int)v[2]; a.heads = (int)v[3];

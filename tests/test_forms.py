@@ -54,6 +54,15 @@ def test_shapes_of_the_gpu_tests_take_every_tile_of_192_and_320(ask):
     assert set(gated) == {7, 9}                   # pairs of columns 32 apart inside every 64 of a wave tile
 
 
+def test_blocks_of_the_gpu_tests_form_their_output_in_the_tile_they_are_listed_under(ask):
+    def form(h, fl, b, s):       # (tile of the MLP-down product, whether it forms the block output)
+        output, = ask([("output", b * s, h, fl)])
+        return ask([("gemm", EPI_RESID if output else D.EPI_STORE, b * s, h, fl, 1, 0)])[0], output
+    for tile, (h, fl, b, s, _, _) in F.BLOCK_OUTPUT_BY_TILE.items():
+        assert form(h, fl, b, s) == (tile, tile != 8), (tile, h, fl, b, s)
+    assert [form(h, f, b, s) for h, f, b, s, _, _ in F.BLOCK_OUTPUT] == [(TILE_64_DEALT, 1)] * 3 + [(7, 1)] * 2
+
+
 def test_attention_shapes_of_the_gpu_tests_take_both_forms(ask):
     for shapes, form in ((F.ATTN_FEW, 1), (F.ATTN_MANY, 0)):
         for b, s, nh in shapes:

@@ -154,16 +154,29 @@ def test_weight_gradients_over_contraction_ranges(dom, seq, accumulate):
         assert float((g - grads[1][k]).norm() / grads[1][k].norm()) < 1e-5, k
 
 
-# (hidden, ffn, batch, seq, arch, other ranks' sum): dealt, 128x128, 256x256 and 256x320 tiles, ragged rows
+# (hidden, ffn, batch, seq, arch, other ranks' sum): 64x64 dealt (the first three) and 192x256 tiles, ragged rows
 BLOCK_OUTPUT = [(256, 512, 2, 37, synth.ARCH_GPT, True), (512, 2048, 3, 333, synth.ARCH_GPT, False), (512, 1376, 3, 333, synth.ARCH_LLAMA, True),
                 (1280, 320, 2, 4000, synth.ARCH_GPT, True), (2560, 320, 2, 4100, synth.ARCH_GPT, True)]
 
 
+# (hidden, ffn columns, batch, seq, arch, other ranks' sum) of a shard with one head of 64, by GemmTile of the MLP-down product;
+# ragged rows and columns.  256x320 tiles (8) leave the output to a pass of its own.
+BLOCK_OUTPUT_BY_TILE = {0: (5568, 72, 1, 139, synth.ARCH_GPT, True), 1: (320, 352, 5, 2191, synth.ARCH_LLAMA, True),
+                        2: (832, 1032, 5, 2697, synth.ARCH_GPT, False), 5: (320, 3080, 5, 1315, synth.ARCH_GPT, True),
+                        6: (832, 352, 5, 1899, synth.ARCH_LLAMA, True), 7: (704, 352, 5, 2209, synth.ARCH_GPT, True),
+                        8: (2112, 3080, 3, 2459, synth.ARCH_GPT, True), 9: (1088, 264, 5, 2921, synth.ARCH_GPT, True)}
+
+
+@pytest.mark.parametrize("h,fl,b,s,arch,others", BLOCK_OUTPUT_BY_TILE.values())
+def test_block_output_in_every_tile(dom, h, fl, b, s, arch, others):
+    test_block_output_is_the_rounded_sum_of_what_the_block_stores(dom, h, fl * (h // 64), b, s, arch, others, tp=h // 64)
+
+
 @pytest.mark.parametrize("h,f,b,s,arch,others", BLOCK_OUTPUT)
-def test_block_output_is_the_rounded_sum_of_what_the_block_stores(dom, h, f, b, s, arch, others):
+def test_block_output_is_the_rounded_sum_of_what_the_block_stores(dom, h, f, b, s, arch, others, tp=1):
     """y = ((x1 + mlp_partial) + others) + b_down in fp32 of the stored bf16 tensors, rounded once: bit for bit."""
     from paper_2409_15241_amd import harness as H
-    sc = synth.ShardConfig(name="out", hidden=h, heads=h // 64, tp=1, rank=0, ffn=f, batch=b, seq=s, p=1, q=1, arch=arch)
+    sc = synth.ShardConfig(name="out", hidden=h, heads=h // 64, tp=tp, rank=0, ffn=f, batch=b, seq=s, p=1, q=1, arch=arch)
     params = synth.make_rank_params(sc, random_affine=True)
     x, dy = synth.make_activations(sc)
     buf = H.LayerBuffers(sc, params, x, dy, synth.make_others(sc) if others else None, nstreams=2)
@@ -176,3 +189,4 @@ def test_block_output_is_the_rounded_sum_of_what_the_block_stores(dom, h, f, b, 
     if buf.params["b_down"] is not None:
         y = y + buf.params["b_down"].float()
     assert torch.equal(buf.y, y.to(torch.bfloat16))
+    assert close(buf.mlp_partial.view(b * s, h), buf.saved_tensor("act").view(b * s, -1).float() @ buf.params["w_down"].float())
