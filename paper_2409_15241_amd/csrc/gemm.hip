@@ -814,7 +814,7 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : (ring_a(BM, BN) * BM + RING_B * BN) * BK * 2;
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
   if (n > 1 || products[0].splits > 1) {
-    if constexpr (EPI == EPI_ACC_F32) {
+    if constexpr (EPI == EPI_ACC_F32 && !(BM == 128 && BN == 256)) {      // (the rule, which alone forms groups, never picks 128x256)
       auto kern = gemm_group_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
       static LdsLimitOnce lds_limit;      // one per instantiation
       if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
@@ -867,7 +867,8 @@ hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t str
   switch (tile_cfg) {
     case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, n, stream);
     case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
-    case GEMM_TILE_128x256: return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream);
+    // by number only, through the single-kernel entry points, which offer no block output
+    case GEMM_TILE_128x256: if constexpr (EPI != EPI_RESID) return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
     case GEMM_TILE_256x192: if constexpr (!PAIRED) return launch_cfg<256, 192, 128, 96, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
     case GEMM_TILE_256x320: if constexpr (!PAIRED && EPI != EPI_RESID) return launch_cfg<256, 320, 128, 160, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
     case GEMM_TILE_192x256: return launch_cfg<192, 256, 96, 128, AKS, BKS, EPI>(a, n, stream);
