@@ -54,6 +54,17 @@ def test_shapes_of_the_gpu_tests_take_every_tile_of_192_and_320(ask):
     assert set(gated) == {7, 9}                   # pairs of columns 32 apart inside every 64 of a wave tile
 
 
+def test_shapes_of_the_gpu_tests_take_the_tile_they_are_listed_under(ask):
+    epis = (D.EPI_STORE, D.EPI_BIAS_GELU, D.EPI_DGELU, D.EPI_DSWIGLU, D.EPI_ACC_F32)
+    for tile, shapes in F.BY_TILE.items():
+        for shape in shapes:
+            assert ask([("gemm", e, *shape, 1, 0) for e in epis]) == [tile] * len(epis), (tile, shape)
+    for e, table in ((D.EPI_SWIGLU, F.BY_TILE_GATED), (EPI_ROPE, F.BY_TILE_ROPE)):
+        for tile, shapes in table.items():
+            assert ask([("gemm", e, *shape, 1, 0) for shape in shapes]) == [tile] * len(shapes), (e, tile)
+    assert any(K == 64 for shapes in F.BY_TILE.values() for _, _, K in shapes)      # one operand tile
+
+
 def test_blocks_of_the_gpu_tests_form_their_output_in_the_tile_they_are_listed_under(ask):
     def form(h, fl, b, s):       # (tile of the MLP-down product, whether it forms the block output)
         output, = ask([("output", b * s, h, fl)])
@@ -61,6 +72,18 @@ def test_blocks_of_the_gpu_tests_form_their_output_in_the_tile_they_are_listed_u
     for tile, (h, fl, b, s, _, _) in F.BLOCK_OUTPUT_BY_TILE.items():
         assert form(h, fl, b, s) == (tile, tile != 8), (tile, h, fl, b, s)
     assert [form(h, f, b, s) for h, f, b, s, _, _ in F.BLOCK_OUTPUT] == [(TILE_64_DEALT, 1)] * 3 + [(7, 1)] * 2
+
+
+def test_blocks_of_the_gpu_tests_join_their_weight_gradients_in_the_tile_they_are_listed_under(ask):
+    for tile, blocks in F.JOINED.items():
+        for h, fl, nl, _, b, s in blocks:
+            hl, K = 64 * nl, b * s
+            shapes = [(fl, h), (h, fl), (hl, h), (h, 3 * hl)]
+            tiles = sum(-(-m // 256) * -(-n // 256) for m, n in shapes)
+            assert tiles <= 200                                # on the chain's stream, all four in one launch
+            assert ask([("ranges", tiles, K, h * (4 * hl + 2 * fl))]) == [1]
+            assert ask([("joined", K, 1, 0, 1, *[x for s in shapes for x in s])]) == [tile], (tile, h, fl, nl)
+            assert not {TILE_64_DEALT, TILE_128_DEALT} & set(ask([("gemm", D.EPI_ACC_F32, m, n, K, 1, 0) for m, n in shapes]))
 
 
 def test_attention_shapes_of_the_gpu_tests_take_both_forms(ask):

@@ -21,7 +21,15 @@ DEEP = [(1032, 2568, 4104), (1024, 2688, 4096)]
 GATED = [(72, 96, 520), (400, 352, 584), (1032, 1376, 4104)]
 # tiles of 192 and 320 rows or columns, products and (M, ffn columns, K): two operand tiles and more, ragged edges
 WIDE = [(1976, 5944, 72), (3408, 2352, 328), (8104, 2552, 136), (4048, 5112, 264), (4776, 3376, 72), (2888, 5784, 264)]
-WIDE_GATED = [(1160, 3392, 72), (2072, 3936, 200)]
+WIDE_GATED = [(1160, 3392, 72), (2072, 3936, 200)]       # (the derivative takes 256x128 and 192x256 here; BY_TILE has it in all four)
+# one tile of 192 or 320 each under every epilogue it can take, by GemmTile: products (also the gated derivative), (M, ffn
+# columns, K) of the gated product, rotary products; the first of each row is one operand tile deep where such a shape takes it
+BY_TILE = {6: [(7016, 1552, 64), (7352, 1056, 264)], 7: [(7208, 1032, 64), (1040, 7208, 264)],
+           8: [(2896, 6488, 136), (2944, 6432, 264)], 9: [(7192, 2208, 64), (6184, 2584, 264)]}
+BY_TILE_GATED = {7: [(648, 5568, 64), (536, 6624, 264)], 9: [(2576, 3104, 64), (1576, 4736, 264)]}
+BY_TILE_ROPE = {7: [(1184, 6784, 64), (1032, 7424, 200)], 9: [(2336, 6656, 64), (2080, 7296, 264)]}
+# (hidden, ffn columns, local heads of 64, ranks, batch, seq) of blocks whose four weight gradients share a launch of such tiles
+JOINED = {6: [(2688, 584, 7, 6, 2, 260), (3136, 376, 7, 7, 3, 67)], 7: [(3520, 464, 5, 11, 1, 130), (2560, 544, 8, 5, 3, 134)]}
 # (batch, seq, heads): few workgroups, 32 positions each, and many, 128 positions each
 ATTN_FEW = [(1, 129, 1), (2, 161, 3), (1, 1000, 2)]
 ATTN_MANY = [(40, 200, 4), (35, 257, 2), (24, 63, 6)]
@@ -108,6 +116,79 @@ def test_gated_and_rotary_products_in_tiles_of_192_and_320(dom, M, fl, K):
     test_gated_and_rotary_products_with_a_dealt_contraction(dom, M, fl, K)
 
 
+TILE_256x256 = 2
+
+
+def same_bits_by_rule_and_in_256x256(launch, *outs):
+    """launch(tile) with the form picked by size and in 256x256 tiles: all whole tiles sum in the same order."""
+    got = []
+    for tile in (-1, TILE_256x256):
+        for o in outs:
+            o.fill_(7.0)
+        launch(tile)
+        torch.cuda.synchronize()
+        got.append([o.clone() for o in outs])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("M,N,K", [x for xs in BY_TILE.values() for x in xs])
+def test_tiles_of_192_and_320_sum_as_256x256_does(dom, M, N, K):
+    torch.manual_seed(M + N + K)
+    A, W, bias = gpu((M, K)), gpu((K, N), 0.05), gpu(N, 0.5)
+    Wt, At = W.t().contiguous(), A.t().contiguous()
+    C, aux, pre = (torch.empty((M, N), device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_NN, dom.EPI_STORE, t, A, K, W, N, C, N, M, N, K, bias=bias), C)
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_NN, dom.EPI_BIAS_GELU, t, A, K, W, N, C, N, M, N, K, bias=bias, aux=aux, ldaux=N), C, aux)
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_NT, dom.EPI_STORE, t, A, K, Wt, K, C, N, M, N, K), C)
+    assert close(C, A.float() @ W.float())
+    pre.normal_(0, 1.5)
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_NT, dom.EPI_DGELU, t, A, K, Wt, K, C, N, M, N, K, aux=pre, ldaux=N), C)
+    gu, dgu = gpu((M, 2 * N)), torch.empty((M, 2 * N), device="cuda", dtype=torch.bfloat16)
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_NT, dom.EPI_DSWIGLU, t, A, K, Wt, K, dgu, 2 * N, M, N, K, aux=gu, ldaux=2 * N, n_split=N), dgu)
+    F = torch.empty((M, N), device="cuda")
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_TN, dom.EPI_ACC_F32, t, At, M, W, N, F, N, M, N, K, beta=1), F)
+
+
+@pytest.mark.parametrize("M,fl,K", [x for xs in BY_TILE_GATED.values() for x in xs])
+def test_gated_products_in_tiles_of_192_and_320_rows_sum_as_256x256_does(dom, M, fl, K):
+    torch.manual_seed(M + fl + K)
+    A, W = gpu((M, K)), gpu((K, 2 * fl), 0.05)
+    act, gu = torch.empty((M, fl), device="cuda", dtype=torch.bfloat16), torch.empty((M, 2 * fl), device="cuda", dtype=torch.bfloat16)
+    same_bits_by_rule_and_in_256x256(
+        lambda t: dom.domino_gemm(dom.GEMM_NN, dom.EPI_SWIGLU, t, A, K, W, 2 * fl, act, fl, M, fl, K, aux=gu, ldaux=2 * fl, n_split=fl), act, gu)
+    assert close(gu, A.float() @ W.float())
+
+
+@pytest.mark.parametrize("M,N,K", [x for xs in BY_TILE_ROPE.values() for x in xs])
+def test_rotary_products_in_tiles_of_192_and_320_rows_sum_as_256x256_does(dom, M, N, K):
+    torch.manual_seed(M + N + K)
+    A, W, C = gpu((M, K)), gpu((K, N), 0.05), torch.empty((M, N), device="cuda", dtype=torch.bfloat16)
+    for d in (64, 128):
+        same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm_rope(t, A, K, W, N, C, N, M, N, K, M // 2 + 1, d, N // 128 // 2 * 128, 10000.0), C)
+
+
+@pytest.mark.parametrize("h,fl,nl,tp,b,s", [x for xs in JOINED.values() for x in xs])
+def test_joined_weight_gradients_sum_as_single_ones_do(dom, h, fl, nl, tp, b, s):
+    """All four in one launch against one launch each, both in whole tiles over the whole contraction."""
+    from paper_2409_15241_amd import harness as H
+    base = synth.ShardConfig(name="joined", hidden=h, heads=nl * tp, tp=tp, rank=0, ffn=fl * tp, batch=b, seq=s, p=1, q=1)
+    params = synth.make_rank_params(base, random_affine=True)
+    x, dy = synth.make_activations(base)
+    grads = []
+    for per_slice in (0, 1):
+        buf = H.LayerBuffers(base.replace(wgrad_per_slice=per_slice), params, x, dy, None, nstreams=1)
+        buf.forward()
+        buf.backward(accumulate=False)
+        buf.sync()
+        grads.append({k: g.clone() for k, g in buf.grads.items() if k.startswith("w_")})
+        if not per_slice:
+            act, g = buf.saved_tensor("act").view(b * s, fl).float(), buf.dy.view(b * s, h).float()
+            assert close(buf.grads["w_down"], act.t() @ g, 1e-4)
+    for k in grads[0]:
+        assert torch.equal(grads[0][k], grads[1][k]), k
+
+
 @pytest.mark.parametrize("d", [64, 80, 128])
 @pytest.mark.parametrize("b,s,nh", ATTN_FEW + ATTN_MANY)
 def test_attention_with_few_and_with_many_workgroups(dom, d, b, s, nh):
@@ -157,8 +238,6 @@ def test_weight_gradients_over_contraction_ranges(dom, seq, accumulate):
 # (hidden, ffn, batch, seq, arch, other ranks' sum): 64x64 dealt (the first three) and 192x256 tiles, ragged rows
 BLOCK_OUTPUT = [(256, 512, 2, 37, synth.ARCH_GPT, True), (512, 2048, 3, 333, synth.ARCH_GPT, False), (512, 1376, 3, 333, synth.ARCH_LLAMA, True),
                 (1280, 320, 2, 4000, synth.ARCH_GPT, True), (2560, 320, 2, 4100, synth.ARCH_GPT, True)]
-
-
 # (hidden, ffn columns, batch, seq, arch, other ranks' sum) of a shard with one head of 64, by GemmTile of the MLP-down product;
 # ragged rows and columns.  256x320 tiles (8) leave the output to a pass of its own.
 BLOCK_OUTPUT_BY_TILE = {0: (5568, 72, 1, 139, synth.ARCH_GPT, True), 1: (320, 352, 5, 2191, synth.ARCH_LLAMA, True),
