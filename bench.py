@@ -52,12 +52,12 @@ def class_flops_per_step(sc, classes):
 
 def kernel_instances(sc, classes, layers=1):
     """{kernel instantiation (= one line of a rocprofv3 kernel summary): the step classes whose launches run it}, for the
-    classes that left launch records.  The MLP-down product of a block whose rows are one group forms the block output in its
+    classes that left launch records.  Where the block output is no pass of its own, the MLP-down product forms it in its
     epilogue, another instantiation than the plain store (in a stack only the last block's does, the others share its class),
-    and so does a QKV product that applies the rotary embedding."""
+    and a QKV product that applies the rotary embedding is one of its own too."""
     llama = bool(sc.arch)
     rotary = llama and sc.head_dim in (64, 128)               # applied in the QKV product's epilogue
-    down_alone = "residual_out" in classes                    # two row groups: the output is a pass of its own
+    down_alone = "residual_out" in classes                    # the block output is a pass of its own
     stores = [("qkv", "gemm_qkv")] * (not rotary) + [("out-proj", "gemm_out")] + [("mlp-down", "gemm_down")] * down_alone
     names = [n for n, _ in stores]
     listed = ", ".join(names[:-1]) + " and " + names[-1] if len(names) > 1 else names[0]

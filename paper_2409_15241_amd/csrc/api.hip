@@ -102,9 +102,9 @@ int wgrad_tiles(const Layout& l) { return tiles256(l.fl, l.h) + tiles256(l.h, l.
 // The backward's weight gradients run on a stream of their own where their tiles fill most of the 256 compute units or
 // more: then they fill what the chain of input gradients, attention and norms leaves idle.  Below that they follow on the
 // chain's stream as one launch, which has the chip to itself (forward + backward without and with the side stream, us:
-// 24000 tokens of a 1536-wide shard, 114 tiles, 1654 and 2000; GPT-3 2.7B, 160 tiles, 1548 and 1611; a 3072-wide Llama
-// shard of 4096 tokens, 228 tiles, 576 and 610; Llama-2 7B, 400 tiles, 8192 tokens, 1570 and 1565, 16384 tokens, 2879 and
-// 2642; 13B, 620 tiles, 2048 tokens, 755 and 701, 8192 tokens, 2325 and 2095).  The second stream also costs a
+// 24000 tokens of a 1536-wide shard, 114 tiles, 1656 and 1950; GPT-3 2.7B, 160 tiles, 1464 and 1703; a 3072-wide Llama
+// shard of 4096 tokens, 228 tiles, 547 and 574; Llama-2 7B, 400 tiles, 2048 tokens, 486 and 491, 8192 tokens, 1421 and 1384,
+// 16384 tokens, 2658 and 2571; 13B, 620 tiles, 2048 tokens, 703 and 652, 8192 tokens, 2129 and 2019).  The second stream also costs a
 // call about 100 us of host time (event records and waits) and 5 to 10 us at each of its edges on the GPU, whatever the
 // block's size: blocks under 40 GFLOP of weight gradients (13B's at 512 tokens) keep to one.
 bool wgrads_beside(const Layout& l) {
@@ -117,9 +117,10 @@ bool wgrads_beside(const Layout& l) {
 // launches pays for the launches.  What the slices' streams used to buy, two chains of dependent launches side by side
 // so that one fills the chip while the other drains, needs two groups and no more (four streams share the four hardware
 // queues that a process gets by default, and slices that meet on a queue run one after the other), and only pays in
-// wide blocks where a group's launches fill the chip on their own (two groups and one beside a side stream, us: 13B with
-// 8192 tokens, 640 tiles, 2095 and 2128; with 4096 tokens, 320 tiles, 1202 and 1169; with 2048, 754 and 701; Llama-2 7B
-// with 8192 tokens, 512 tiles, 1509 and 1565; with 16384, 2642 and 2900).
+// wide blocks where a group's launches fill the chip on their own (two groups and one beside a side stream, us: Llama-2 7B
+// with 16384 tokens, 1024 tiles, 2571 and 2691; with 8192, 512 tiles, 1384 and 1415; with 4096, 256 tiles, 823 and 781; 13B with
+// 4096 tokens, 320 tiles, 1134 and 1062; with 2048, 765 and 653.  Level to 1 %: 13B with 8192 tokens, 640 tiles, 2035 and 2019,
+// 30B, 896 tiles, 3521 and 3542, Llama-2 13B with 16384, 1280 tiles, 4172 and 4234.)
 int row_groups(const Layout& l) { return l.p > 2 && wgrads_beside(l) && tiles256(l.M, l.h) >= 512 ? 2 : 1; }
 
 int validate(const domino_cfg* c, Layout* L) {

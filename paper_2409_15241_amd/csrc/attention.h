@@ -18,9 +18,13 @@ struct AttnArgs {
 };
 
 // Whether the form for few workgroups (32 positions each, see attention.hip) is the faster one, from the time of either on
-// an otherwise idle chip (us, fitted to 21 shapes): the longest workgroup's chain against the split form's start, end and
-// rounds of workgroups.  Forward / backward, heads of 128: 4 x 704 positions, one head 16.5 -> 11.8 / 37 -> 20; 812, seven
-// heads 18.9 -> 13.9 / 44 -> 27; 4096, two heads 80 -> 40 / 150 -> 65; the two forms meet at 4 x 512, five heads.
+// an otherwise idle chip (us): the longest workgroup's chain against the split form's start, end and rounds of workgroups.
+// Forward / backward, heads of 128: 4 x 704 positions, one head 16.9 -> 12.3 / 30.7 -> 18.6; 812, seven heads 19.1 -> 14.4 /
+// 35.0 -> 24.4; 4096, two heads 80 -> 42 / 118 -> 67; the two forms meet at 6 x 512, four heads, forward (14.9 each) and at
+// 3 x 1024, four heads, backward (42.2 and 41.2).  Of 34 shapes with heads of 64, 80 and 128 the form taken is the slower one
+// by more than 5 % in the backward of 2 x 2048, four heads of 128 (75.5 for 70.1: the constants were fitted before the
+// 128-position backward of these heads ran its softmax under its MFMAs) and of 8 x 256, four heads of 64 and 80 (by 1 us), and
+// in the forward of 8 x 512, four heads (by 1 us) and 2 x 2048, five heads of 64 (31.7 for 29.9).
 inline bool attention_split_pays(const AttnArgs& a, bool backward) {
   const int wgs = (a.seq + 127) / 128 * a.heads * a.batch, steps = (a.seq + 63) / 64;
   if (wgs > 128) return false;

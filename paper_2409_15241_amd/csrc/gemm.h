@@ -51,9 +51,9 @@ constexpr int GEMM_GROUP = 4;
 // Time of a launch that has the chip to itself = 3 us + rounds of tiles on 256 compute units x time of a tile; time of a tile
 // = what its start and its epilogue take (fixed) + what 64 elements of the contraction take: `full` where the round fills the
 // chip, whose clocks then fall to what its power allows, `lone` where few compute units are at work, in proportion between
-// (us; fitted to 8000 timings of 921 products of shards like the library's, 128 to 32768 rows, 64 to 28672 columns, 80 to 8192
-// deep, operands out of the caches; the form picked is the fastest at the median, within 5 % of it for nine tenths; 128x256
-// was the fastest for one of them and is not looked at).
+// (us; fitted to timings of 921 products of shards like the library's, 128 to 32768 rows, 64 to 28672 columns, 80 to 8192
+// deep, operands out of the caches; 128x256 was the fastest for one of them and is not looked at.  Of 1274 others, drawn
+// afterwards, the form picked is the fastest at the median, within 5 % of it for nine tenths and within 17 % for 99 of 100).
 // Forms of 192 and 320 rows or columns are there for the last round: 16384 x 1280 x 2560 is 320 tiles of 256x256, the second
 // round a quarter full, or 256 of 256x320 (108 -> 79 us; 8192 x 2560 x 5120 206 -> 147; 8192 x 2688 x 7168, 352 tiles or 448 of
 // 256x192, 274 -> 227).  A pair of columns that must meet in a lane rules out those with wave tiles of 96 or 160 columns.
@@ -85,7 +85,10 @@ inline double gemm_form_time(const GemmForm& f, double tiles, int it, int epi) {
 // Contraction ranges for weight gradients that are launched together and have the chip to themselves: `tiles` tiles of
 // 256x256, `depth` deep, `floats` values in all.  A launch of 160 such tiles leaves 96 of 256 compute units idle for as
 // long as its contraction is deep; cut into ranges it is rounds of shorter tiles, for partial sums that are written and
-// read once each.  (13 + 1.2 us per 64 deep and tile, 5 TB/s for the sums.)
+// read once each.  (13 + 1.2 us per 64 deep and tile, 5 TB/s for the sums: coarser figures than GEMM_FORMS, of 256x256 tiles
+// alone.  Of ten blocks timed with 1 to 6 ranges the rule is within 1.3 % of the best for nine; 24000 tokens of a 1536-wide
+// shard, 114 tiles, take 1642 us with the one range that it gives and 1599 with two.  16384 tokens of a 512-wide block, 48 tiles:
+// 690 us with one range, 659 with the rule's five; 2.7B with 32768 tokens, 160 tiles, 2710 and 2672 with three.)
 constexpr int GEMM_MAX_SPLITS = 6;
 inline int gemm_wgrad_splits(int tiles, int depth, long floats) {
   const int it = (depth + 63) / 64;

@@ -14,7 +14,7 @@
 // 128-byte lines of a contraction-contiguous operand) travel HBM/L2 -> LDS with buffer_load ... lds into two rings
 // (three tiles of A, two of B; two of each where a tile is 320 wide); no VGPR staging, no ds_write.
 // What bounds it at large sizes is power: a 16x16x32 MFMA reads and writes half as many accumulator bytes per flop as
-// a 32x32x16 one (1.91 against 1.86 PFLOP/s at 0.53 against 0.54 pJ/flop above idle on N(0,1) x N(0,0.02) fragments with
+// a 32x32x16 one (1.89 against 1.83 PFLOP/s at 0.545 against 0.549 pJ/flop above idle on N(0,1) x N(0,0.02) fragments with
 // nothing else running, which domino_mfma_probe_shape measures), so every product here is made of those; a wave tile of
 // 128x128 reads 64 bytes of fragments per clock and compute unit at full rate where 128x64 reads 96.  All whole-tile forms
 // sum the contraction in the same order (32 elements per MFMA), so the bits do not depend on the tile shape; the dealt
