@@ -57,11 +57,16 @@ constexpr int GEMM_GROUP = 4;
 // Forms of 192 and 320 rows or columns are there for the last round: 16384 x 1280 x 2560 is 320 tiles of 256x256, the second
 // round a quarter full, or 256 of 256x320 (108 -> 79 us; 8192 x 2560 x 5120 206 -> 147; 8192 x 2688 x 7168, 352 tiles or 448 of
 // 256x192, 274 -> 227).  A pair of columns that must meet in a lane rules out those with wave tiles of 96 or 160 columns.
-struct GemmForm { int id, bm, bn; double fixed, lone, full; };
+// adds: what adding to the fp32 values that C holds takes beyond overwriting them, for 256x256 values.  12 or 13 is reading them
+// at the rate of memory; some forms measure twice that; 128x128 tiles pay less, one of the two workgroups of a compute unit
+// loading while the other multiplies.  (Four weight gradients in one launch, adding, 71 such blocks of 64 to 4096 tokens: the
+// form picked is 0.5 % above the fastest on the mean and 13 % at most, without this term 17 and 56 %.  192 tokens of a 6144-wide
+// shard 150 us in 192x256, 110 in 128x128; 512 of a 1536-wide one 31 in 256x128, 23 in 128x128.)
+struct GemmForm { int id, bm, bn; double fixed, lone, full, adds; };
 constexpr GemmForm GEMM_FORMS[] = {
-  {GEMM_TILE_256x256, 256, 256, 6.1, 1.17, 1.335}, {GEMM_TILE_256x320, 256, 320, 9.5, 1.46, 1.85}, {GEMM_TILE_320x256, 320, 256, 7.6, 1.49, 2.00},
-  {GEMM_TILE_256x192, 256, 192, 4.8, 0.86, 1.19}, {GEMM_TILE_192x256, 192, 256, 4.3, 0.89, 1.27}, {GEMM_TILE_256x128, 256, 128, 3.4, 0.57, 0.90},
-  {GEMM_TILE_128x128, 128, 128, 2.1, 0.39, 0.47}};
+  {GEMM_TILE_256x256, 256, 256, 6.1, 1.17, 1.335, 12}, {GEMM_TILE_256x320, 256, 320, 9.5, 1.46, 1.85, 12}, {GEMM_TILE_320x256, 320, 256, 7.6, 1.49, 2.00, 22},
+  {GEMM_TILE_256x192, 256, 192, 4.8, 0.86, 1.19, 13}, {GEMM_TILE_192x256, 192, 256, 4.3, 0.89, 1.27, 20}, {GEMM_TILE_256x128, 256, 128, 3.4, 0.57, 0.90, 24},
+  {GEMM_TILE_128x128, 128, 128, 2.1, 0.39, 0.47, 8}};
 // what the epilogue takes beyond storing bf16 sums, for 256x256 values: activations (vector ALUs), wider results
 inline double gemm_epilogue_time(int epi) {
   return epi == EPI_BIAS_GELU ? 5.9 : epi == EPI_SWIGLU ? 8.2 : epi == EPI_DGELU ? 8.9 : epi == EPI_DSWIGLU ? 10.6 :
@@ -72,8 +77,8 @@ inline bool gemm_form_takes(const GemmForm& f, int epi) {
   return (epi != EPI_SWIGLU && epi != EPI_ROPE) || (f.bn != 192 && f.bn != 320);
 }
 // tiles of contraction `it` x 64 deep; 128x128 tiles run two to a compute unit
-inline double gemm_form_time(const GemmForm& f, double tiles, int it, int epi) {
-  const double fixed = f.fixed + gemm_epilogue_time(epi) * f.bm * f.bn / 65536;
+inline double gemm_form_time(const GemmForm& f, double tiles, int it, int epi, bool adds = false) {
+  const double fixed = f.fixed + (gemm_epilogue_time(epi) + (adds ? f.adds : 0.0)) * f.bm * f.bn / 65536;
   if (f.id == GEMM_TILE_128x128) {
     const double rounds = floor(tiles / 512), rest = tiles - 512 * rounds, share = f.full * rest / 512;
     return 3 + rounds * 2 * (fixed + f.full * it) + (rest == 0 ? 0.0 : rest <= 256 ? fixed - 1.1 + 0.503 * (it < 40 ? it : 40) + (it < 40 ? 0.0 : 0.80 * (it - 40)) : 2 * (fixed + (f.lone > share ? f.lone : share) * it));
@@ -131,16 +136,17 @@ inline int gemm_pick_form(const GemmArgs* products, int n, int epi, int concurre
   };
   const int it = ((products[0].K + GEMM_BK - 1) / GEMM_BK + splits - 1) / splits;      // a group's products share the contraction
   const double extra = gemm_epilogue_time(epi);
+  const bool adds = epi == EPI_ACC_F32 && products[0].beta && splits == 1;      // (ranges write sums of their own)
   int best = GEMM_TILE_128x128;
   double best_cost = 1e30, best_alone = 1e30;
   for (const GemmForm& f : GEMM_FORMS) {
     if (!gemm_form_takes(f, epi)) continue;
-    const double tiles = tiles_of(f.bm, f.bn), alone = gemm_form_time(f, tiles, it, epi);
-    best_alone = alone < best_alone ? alone : best_alone;
+    const double tiles = tiles_of(f.bm, f.bn), over = gemm_form_time(f, tiles, it, epi), alone = adds ? gemm_form_time(f, tiles, it, epi, true) : over;
+    best_alone = over < best_alone ? over : best_alone;      // whether a contraction is dealt does not depend on what C holds either
     // a launch of few tiles is a long serial kernel on its stream, and the other launches in flight do not always fill
     // the chip beside it: it is charged for leaving more than three eighths of its share of the chip unused
     const double share = 160.0 / concurrency;
-    const double shared = 3 + (tiles < share ? share : tiles) / 256 * (f.fixed + extra * f.bm * f.bn / 65536 + f.full * it);
+    const double shared = 3 + (tiles < share ? share : tiles) / 256 * (f.fixed + (extra + (adds ? f.adds : 0.0)) * f.bm * f.bn / 65536 + f.full * it);
     const double cost = concurrency == 1 ? alone : concurrency == 2 ? 0.35 * alone + 0.65 * shared : shared;
     if (cost < best_cost * 0.999) { best_cost = cost; best = f.id; }
   }

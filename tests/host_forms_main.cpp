@@ -1,7 +1,7 @@
 // Which form the launchers pick for given sizes, from the rules in csrc/gemm.h and csrc/attention.h alone (no GPU, no
 // library).  Reads one question per line and answers each with one number:
-//   gemm <epilogue> <M> <N> <K> <concurrency> <beside>   GemmTile of one product (SwiGLU: N gate columns)
-//   joined <K> <concurrency> <beside> <ranges> <M N> x 4   GemmTile of four weight gradients in one launch
+//   gemm <epilogue> <M> <N> <K> <concurrency> <beside> [<adds>]   GemmTile of one product (SwiGLU: N gate columns)
+//   joined <K> <concurrency> <beside> <ranges> <M N> x 4 [<adds>]   GemmTile of four weight gradients in one launch
 //   output <M> <N> <K>                                    1: the block output in the product's epilogue, 0: a pass
 //   attention <backward> <batch> <seq> <heads>            1: 32 positions per workgroup, 0: 128
 //   ranges <tiles> <depth> <floats>                       contraction ranges of joined weight gradients
@@ -13,18 +13,18 @@
 
 int main() {
   char line[256], what[32];
-  long v[12];
+  long v[13] = {};
   while (std::fgets(line, sizeof(line), stdin)) {
-    const int n = std::sscanf(line, "%31s %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld", what, v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7,
-                              v + 8, v + 9, v + 10, v + 11);
-    if (n == 7 && !std::strcmp(what, "gemm")) {
+    const int n = std::sscanf(line, "%31s %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld", what, v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7,
+                              v + 8, v + 9, v + 10, v + 11, v + 12);
+    if ((n == 7 || n == 8) && !std::strcmp(what, "gemm")) {
       GemmArgs a{};
-      a.M = (int)v[1]; a.N = a.n_split = (int)v[2]; a.K = (int)v[3]; a.beside = (int)v[5];
+      a.M = (int)v[1]; a.N = a.n_split = (int)v[2]; a.K = (int)v[3]; a.beside = (int)v[5]; a.beta = n == 8 ? (int)v[6] : 0;
       std::printf("%d\n", gemm_pick_form(&a, 1, (int)v[0], (int)v[4]));
-    } else if (n == 13 && !std::strcmp(what, "joined")) {
+    } else if ((n == 13 || n == 14) && !std::strcmp(what, "joined")) {
       GemmArgs a[GEMM_GROUP] = {};
       for (int i = 0; i < GEMM_GROUP; ++i) {
-        a[i].M = (int)v[4 + 2 * i]; a[i].N = (int)v[5 + 2 * i]; a[i].K = (int)v[0]; a[i].beside = (int)v[2]; a[i].splits = (int)v[3];
+        a[i].M = (int)v[4 + 2 * i]; a[i].N = (int)v[5 + 2 * i]; a[i].K = (int)v[0]; a[i].beside = (int)v[2]; a[i].splits = (int)v[3]; a[i].beta = n == 14 ? (int)v[12] : 0;
       }
       std::printf("%d\n", gemm_pick_form(a, GEMM_GROUP, EPI_ACC_F32, (int)v[1]));
     } else if (n == 4 && !std::strcmp(what, "output")) {

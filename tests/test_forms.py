@@ -62,6 +62,8 @@ def test_shapes_of_the_gpu_tests_take_the_tile_they_are_listed_under(ask):
     for e, table in ((D.EPI_SWIGLU, F.BY_TILE_GATED), (EPI_ROPE, F.BY_TILE_ROPE)):
         for tile, shapes in table.items():
             assert ask([("gemm", e, *shape, 1, 0) for shape in shapes]) == [tile] * len(shapes), (e, tile)
+    for tile, shape in F.ADDING.items():
+        assert ask([("gemm", D.EPI_ACC_F32, *shape, 1, 0, 1)]) == [tile], (tile, shape)
     assert any(K == 64 for shapes in F.BY_TILE.values() for _, _, K in shapes)      # one operand tile
 
 
@@ -114,6 +116,23 @@ def test_a_block_sums_alike_alone_and_in_a_stack(ask):
     for c in (1, 2, 4):
         plain, out = (ask([("gemm", e, *x, c, 0) for x in shapes]) for e in (D.EPI_STORE, EPI_RESID))
         assert [x for x, f, g in zip(shapes, plain, out) if order(f) != order(g)] == []
+
+
+def test_weight_gradients_that_add_take_another_tile_and_the_same_order(ask):
+    """Adding to what the gradients hold costs the forms differently, so it may move a launch to another whole tile (192 tokens
+    of a 6144-wide shard, 256 of a 1536-wide one: back to 128x128), which sums alike.  It never decides whether the
+    contraction is dealt: with gradients that hold zeros, adding and overwriting stay the same bit for bit."""
+    four = lambda h, hl, fl: [fl, h, h, fl, hl, h, h, 3 * hl]
+    for K, sizes, over in ((192, (6144, 768, 3072), 7), (256, (1536, 384, 1536), 1)):
+        assert ask([("joined", K, 1, 0, 1, *four(*sizes), beta) for beta in (0, 1)]) == [over, 0], (K, sizes)
+    rng = random.Random(9)
+    order = lambda f: f if f in (TILE_64_DEALT, TILE_128_DEALT) else "whole"
+    shapes = [(rng.randrange(64, 8000), [rng.randrange(8, 600) * 8 for _ in range(8)], c) for _ in range(1000) for c in (1, 2, 3)]
+    over, adds = (ask([("joined", K, c, 0, 1, *mn, beta) for K, mn, c in shapes]) for beta in (0, 1))
+    assert [s for s, f, g in zip(shapes, over, adds) if order(f) != order(g)] == []
+    singles = [(rng.randrange(8, 900) * 8, rng.randrange(8, 900) * 8, rng.randrange(8, 900) * 8) for _ in range(2000)]
+    over, adds = (ask([("gemm", D.EPI_ACC_F32, *s, 1, 0, beta) for s in singles]) for beta in (0, 1))
+    assert [s for s, f, g in zip(singles, over, adds) if order(f) != order(g)] == []
 
 
 def test_whether_a_contraction_is_dealt_does_not_depend_on_the_streams(ask):

@@ -19,13 +19,16 @@ SHALLOW = [(200, 264, 72)]         # two operand tiles: dealt under GeLU', plain
 DEEP = [(1032, 2568, 4104), (1024, 2688, 4096)]
 # (M, ffn columns, K) of the gated and rotary products: dealt forms too
 GATED = [(72, 96, 520), (400, 352, 584), (1032, 1376, 4104)]
-# tiles of 192 and 320 rows or columns, products and (M, ffn columns, K): two operand tiles and more, ragged edges
+# tiles of 192 and 320 rows or columns, products and (M, ffn columns, K): two operand tiles and more, ragged edges (fp32 sums
+# that are added to what C holds take ADDING's)
 WIDE = [(1976, 5944, 72), (3408, 2352, 328), (8104, 2552, 136), (4048, 5112, 264), (4776, 3376, 72), (2888, 5784, 264)]
 WIDE_GATED = [(1160, 3392, 72), (2072, 3936, 200)]       # (the derivative takes 256x128 and 192x256 here; BY_TILE has it in all four)
 # one tile of 192 or 320 each under every epilogue it can take, by GemmTile: products (also the gated derivative), (M, ffn
 # columns, K) of the gated product, rotary products; the first of each row is one operand tile deep where such a shape takes it
 BY_TILE = {6: [(7016, 1552, 64), (7352, 1056, 264)], 7: [(7208, 1032, 64), (1040, 7208, 264)],
            8: [(2896, 6488, 136), (2944, 6432, 264)], 9: [(7192, 2208, 64), (6184, 2584, 264)]}
+# fp32 sums added to what C holds: 128x128, 256x256, and the tiles of 192 and 320 that the rule takes for them
+ADDING = {0: (264, 3384, 64), 2: (3080, 3928, 264), 6: (2312, 3360, 520), 8: (3352, 4768, 520), 9: (2832, 6888, 2056)}
 BY_TILE_GATED = {7: [(648, 5568, 64), (536, 6624, 264)], 9: [(2576, 3104, 64), (1576, 4736, 264)]}
 BY_TILE_ROPE = {7: [(1184, 6784, 64), (1032, 7424, 200)], 9: [(2336, 6656, 64), (2080, 7296, 264)]}
 # (hidden, ffn columns, local heads of 64, ranks, batch, seq) of blocks whose four weight gradients share a launch of such tiles
@@ -147,7 +150,15 @@ def test_tiles_of_192_and_320_sum_as_256x256_does(dom, M, N, K):
     gu, dgu = gpu((M, 2 * N)), torch.empty((M, 2 * N), device="cuda", dtype=torch.bfloat16)
     same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_NT, dom.EPI_DSWIGLU, t, A, K, Wt, K, dgu, 2 * N, M, N, K, aux=gu, ldaux=2 * N, n_split=N), dgu)
     F = torch.empty((M, N), device="cuda")
-    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_TN, dom.EPI_ACC_F32, t, At, M, W, N, F, N, M, N, K, beta=1), F)
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_TN, dom.EPI_ACC_F32, t, At, M, W, N, F, N, M, N, K), F)
+
+
+@pytest.mark.parametrize("M,N,K", ADDING.values())
+def test_tiles_add_fp32_sums_as_256x256_does(dom, M, N, K):
+    torch.manual_seed(M + N + K)
+    A, W, F = gpu((K, M)), gpu((K, N), 0.05), torch.empty((M, N), device="cuda")
+    same_bits_by_rule_and_in_256x256(lambda t: dom.domino_gemm(dom.GEMM_TN, dom.EPI_ACC_F32, t, A, M, W, N, F, N, M, N, K, beta=1), F)
+    assert close(F, A.float().t() @ W.float() + 7.0, 1e-4)
 
 
 @pytest.mark.parametrize("M,fl,K", [x for xs in BY_TILE_GATED.values() for x in xs])
