@@ -184,7 +184,7 @@ int validate(const domino_cfg* c, Layout* L) {
   l.dqkv = take(Mz * 3 * l.hl * 2);
   l.dot = take((size_t)l.b * l.nl * l.s * 4);
   {
-    const int nb = norm_bwd_slice_blocks(l.M, l.Ms);
+    const int nb = norm_bwd_slice_blocks((l.p + l.groups - 1) / l.groups, l.Ms, l.h);
     // b_o and b_down come out of the Norm2 backward kernel (one partial row per workgroup), the others from column-sum passes
     const int rows[NAREAS] = {nb, nb, nb, nb, COLSUM_PARTS, nb, COLSUM_PARTS, nb};
     const int width[NAREAS] = {l.h, l.h, l.h, l.h, 3 * l.hl, l.h, l.fl, l.h};

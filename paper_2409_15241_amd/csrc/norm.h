@@ -30,7 +30,7 @@ struct NormBwdArgs {
   const float* rstd;      // fp32 [rows]
   const void* dres;       // bf16 [rows, h] or null: gradient arriving over the residual branch
   void* dx;               // bf16 [rows, h] = dres + NormBwd(ga + gb)
-  // partial column sums: [slice_blocks, h] for each slice of slice_rows rows, one slice after the other
+  // partial column sums: slice_blocks rows of h for each slice of slice_rows rows; every workgroup of the launch leaves one row of each
   float* part_g;          // fp32
   float* part_b;          // fp32 (LayerNorm only)
   float* part_dres;       // fp32 or null: of dres (a bias gradient)
@@ -40,14 +40,14 @@ struct NormBwdArgs {
   int slice_blocks;       // workgroups (and partial rows) per slice; 0: norm_bwd_blocks(slice_rows)
 };
 
-// Workgroups of the backward for a slice of a block of `rows` rows (where the caller's memory allows their number to be
-// chosen; the single-kernel entry point's scratch holds norm_bwd_blocks).  Each walks its rows one after the other and leaves a
-// partial row per gradient vector: 16 rows keep that traffic below a tenth of the kernel's, fewer rows are spread down to 4
-// each while they fill 256 compute units once (812 x 1792: 64 workgroups 15.3 us, 203 11.3; 2048 x 5120: 128 31.1, 256 27.9).
-inline int norm_bwd_slice_blocks(int rows, int slice_rows) {
-  const int spread = (rows + 255) / 256, per = spread < 4 ? 4 : spread > NORM_BWD_ROWS ? NORM_BWD_ROWS : spread;
-  const int want = (slice_rows + per - 1) / per;
-  return want < NORM_BWD_MAX_BLOCKS ? want : NORM_BWD_MAX_BLOCKS;
+// Workgroups of the backward, per slice of a launch over `slices` slices (where the caller's memory allows their number to be
+// chosen; the single-kernel entry point's scratch holds norm_bwd_blocks): one per compute unit, more where a row has few
+// waves, so that about eight waves have their loads in flight.  Each leaves a partial row per gradient vector, which costs
+// traffic, so there are no more than that, and each has four rows or more (us, 256 / 512 / 768: 16384 x 2560, five waves, 69.8 / 72.5 /
+// 76; 8192 x 5120, ten, 69.3 / 75.8 / 83.7; 2048 x 5120 23.4 / 29.0 / 34.8; 4096 x 2048, four, 18.9 / 18.9 / 19.9; 8192 x 1024, two, 25.8 / 20.7 / 18.2).
+inline int norm_bwd_slice_blocks(int slices, int slice_rows, int h) {
+  const int waves = (h / 8 + 63) / 64, fill = 256 * (waves > 4 ? 1 : 8 / waves) / slices, want = (slice_rows + 3) / 4;
+  return fill < 1 ? 1 : want < fill ? want : fill;
 }
 int norm_bwd_blocks(int rows);              // 16 rows each until the block limit is reached
 hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st);

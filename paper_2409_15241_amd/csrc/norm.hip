@@ -4,12 +4,22 @@
 // instruction.  Statistics are fp32; wave reductions combined through LDS give the row sums.
 #include "norm.h"
 #include "common.h"
+#include <type_traits>
 
 namespace {
 
 DEV void unpack8(const u32x4 v, float* f) {
   f[0] = bf16_lo(v[0]); f[1] = bf16_hi(v[0]); f[2] = bf16_lo(v[1]); f[3] = bf16_hi(v[1]);
   f[4] = bf16_lo(v[2]); f[5] = bf16_hi(v[2]); f[6] = bf16_lo(v[3]); f[7] = bf16_hi(v[3]);
+}
+// ONCE: rows that nobody reads again soon go past the caches (see norm_streams)
+template <bool ONCE>
+DEV u32x4 load_row(const u32x4* p) {
+  if constexpr (ONCE) return __builtin_nontemporal_load(p); else return *p;
+}
+template <bool ONCE>
+DEV void store_row(u32x4* p, const u32x4 v) {
+  if constexpr (ONCE) __builtin_nontemporal_store(v, p); else *p = v;
 }
 DEV u32x4 pack8(const float* f) {
   u32x4 v = {pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])};
@@ -23,7 +33,7 @@ DEV u32x4 pack8(const float* f) {
 // of branching, and are masked out of the sums and stores); the two row sums cross the waves through LDS in wave
 // order.  Under 96 registers a lane: such waves fit beside the two 192-register waves that a 256x256 product
 // tile keeps on every SIMD.
-template <int NC, bool RMS>
+template <int NC, bool RMS, bool ONCE>
 __global__ __launch_bounds__(256, 5)
 void norm_fwd_kernel(const NormFwdArgs p) {
   __shared__ float red[2][4];
@@ -48,13 +58,13 @@ void norm_fwd_kernel(const NormFwdArgs p) {
   }
   u32x4 xs[NC];
 #pragma unroll
-  for (int i = 0; i < NC; ++i) xs[i] = x[cc[i]];
+  for (int i = 0; i < NC; ++i) xs[i] = fused ? load_row<ONCE>(x + cc[i]) : x[cc[i]];
   if (fused) {
     u32x4 t1[NC], t2[NC], t3[NC];
 #pragma unroll
     for (int i = 0; i < NC; ++i) t1[i] = a1 ? a1[cc[i]] : zero4;
 #pragma unroll
-    for (int i = 0; i < NC; ++i) t2[i] = a2 ? a2[cc[i]] : zero4;
+    for (int i = 0; i < NC; ++i) t2[i] = a2 ? load_row<ONCE>(a2 + cc[i]) : zero4;
 #pragma unroll
     for (int i = 0; i < NC; ++i) t3[i] = vec ? vec[cc[i]] : zero4;
 #pragma unroll
@@ -76,7 +86,7 @@ void norm_fwd_kernel(const NormFwdArgs p) {
       u32x4* o = reinterpret_cast<u32x4*>(static_cast<bf16_t*>(p.xsum) + ro);
 #pragma unroll
       for (int i = 0; i < NC; ++i)
-        if (live[i]) o[cc[i]] = xs[i];
+        if (live[i]) store_row<ONCE>(o + cc[i], xs[i]);
     }
   }
   const u32x4* gam = reinterpret_cast<const u32x4*>(p.gamma);
@@ -136,19 +146,20 @@ void norm_fwd_kernel(const NormFwdArgs p) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) f[e] += g[e];
     }
-    if (live[i]) y[cc[i]] = pack8(f);
+    if (live[i]) store_row<ONCE>(y + cc[i], pack8(f));
   }
 }
 
 // dx = dres + NormBwd(ga + gb); per-workgroup partial sums of d gamma / d beta.
-// A workgroup owns a contiguous range of rows and walks it R rows at a time; thread t owns the 8
-// columns of 16-byte chunk t in every row, so its share of the column sums (d gamma, d beta) is 16
-// registers and every load of an iteration (R rows x up to 4 tensors) is in flight at once.  The two
+// The launch's workgroups sweep the rows side by side, R rows each at a time; thread t owns the 8 columns of 16-byte chunk t in
+// every row, so its share of the column sums (d gamma, d beta) is 16 registers and every load of an iteration (R rows x up
+// to 4 tensors) is in flight at once.  Side by side the memory sees one front per tensor: with a range of rows to each workgroup
+// 16384 x 2560 took 88.1 us and 80.4 so (512 and 256 workgroups), 8192 x 4096 67.7 and 63.5, 8192 x 5120 95.8 and 88.0.  The two
 // row sums cross the waves through LDS: wave sums in a double-buffered table, one barrier per
 // iteration, added in wave order (fixed summation order).
-template <int NT, int R, bool RMS, bool SUMS>
+template <int NT, int R, bool RMS, bool SUMS, bool ONCE>
 __global__ __launch_bounds__(NT)
-void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block, int blocks_per_slice) {
+void norm_bwd_kernel(const NormBwdArgs p) {
   constexpr int NW = NT / 64;
   constexpr int RW = 2 * R < 4 ? 4 : 2 * R;     // row sums per wave and iteration, padded to whole 16-byte reads
   __shared__ __align__(16) float red[2][NW][RW];
@@ -165,9 +176,7 @@ void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block, int blocks_per_sli
 #pragma unroll
   for (int e = 0; e < 8; ++e) { dg[e] = 0.0f; db[e] = 0.0f; sres[e] = 0.0f; sdx[e] = 0.0f; }
 
-  // the rows of a workgroup lie in one slice, so the partial sums do not depend on how many slices a launch covers
-  const int slice = blockIdx.x / blocks_per_slice, block = blockIdx.x % blocks_per_slice;
-  const int s0 = slice * p.slice_rows, r0 = s0 + block * rows_per_block, r1 = min(s0 + p.slice_rows, r0 + rows_per_block);
+  const int r1 = p.rows, step = gridDim.x * R;
   const long part_at = (long)blockIdx.x * p.h + tid * 8;
   // the rows of iteration k+1 are requested before iteration k is worked on, so the memory pipeline stays
   // busy across the barrier and the arithmetic of an iteration
@@ -178,19 +187,19 @@ void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block, int blocks_per_sli
       const int row = rb + j;
       const bool ok = live && row < r1;
       const long at = (long)row * p.h + tid * 8;
-      w.xs[j] = ok ? *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.x) + at) : zero4;
+      w.xs[j] = ok ? load_row<ONCE>(reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.x) + at)) : zero4;
       w.gs[j] = ok ? *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.ga) + at) : zero4;
-      w.bs[j] = (ok && p.gb) ? *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.gb) + at) : zero4;
-      w.ds[j] = (ok && p.dres) ? *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.dres) + at) : zero4;
+      w.bs[j] = (ok && p.gb) ? load_row<ONCE>(reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.gb) + at)) : zero4;
+      w.ds[j] = (ok && p.dres) ? load_row<ONCE>(reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(p.dres) + at)) : zero4;
       w.mean[j] = (!RMS && row < r1) ? p.mean[row] : 0.0f;
       w.rstd[j] = row < r1 ? p.rstd[row] : 0.0f;
     }
   };
   Rows cur, nxt;
-  load_rows(r0, cur);
+  load_rows(blockIdx.x * R, cur);
   int buf = 0;
-  for (int rb = r0; rb < r1; rb += R, buf ^= 1) {
-    load_rows(rb + R, nxt);                     // rows past r1 load nothing
+  for (int rb = blockIdx.x * R; rb < r1; rb += step, buf ^= 1) {
+    load_rows(rb + step, nxt);                     // rows past r1 load nothing
     const u32x4 (&xs)[R] = cur.xs;
     const u32x4 (&gs)[R] = cur.gs;
     const u32x4 (&bs)[R] = cur.bs;
@@ -244,7 +253,7 @@ void norm_bwd_kernel(const NormBwdArgs p, int rows_per_block, int blocks_per_sli
           o[e] = rstd[j] * ((gv[e] + bv[e]) * gm[e] - c1 - (xv[e] - mean[j]) * rstd[j] * c2) + rv[e];
           if (SUMS) { sres[e] += rv[e]; sdx[e] += o[e]; }
         }
-        *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(p.dx) + (long)row * p.h + tid * 8) = pack8(o);
+        store_row<ONCE>(reinterpret_cast<u32x4*>(static_cast<bf16_t*>(p.dx) + (long)row * p.h + tid * 8), pack8(o));
       }
     }
     cur = nxt;
@@ -350,27 +359,33 @@ void colsum_partial_kernel(const bf16_t* __restrict__ g, long ld, int rows, int 
   o[1] = f32x4{acc[4], acc[5], acc[6], acc[7]};
 }
 
-template <bool RMS>
+// Whether a launch's rows outgrow the last-level cache (256 MB, shared with the products beside them): tensors of 32 MB and
+// more.  Then what is read once (x, the other ranks' sum, the incoming gradients but the one just written) and what is written
+// goes past the caches: backward 16384 x 2560 79.8 -> 69.8 us, 8192 x 4096 63.5 -> 53.6, 4096 x 5120 44.1 -> 39.6; forward with the residual
+// sum 73.3 -> 64.2, 58.7 -> 52.5, 38.8 -> 35.1.  Smaller ones are read again while they are still there: a step of 2 x 200
+// tokens of a 1024-wide block 126.5 us without and 129.6 with, 2048 tokens of 13B 664.7 and 673.6, 6018 of 2.7B 623.4 and 627.6.
+bool norm_streams(long rows, int h) { return rows * h >= 1L << 24; }
+
+template <bool RMS, bool ONCE>
 hipError_t fwd_dispatch(const NormFwdArgs& a, hipStream_t st) {
   const int nq = ((a.h >> 3) + 255) / 256;               // 16-byte chunks per thread
   const dim3 grid(a.rows), block(256);
-  if (nq <= 1) hipLaunchKernelGGL((norm_fwd_kernel<1, RMS>), grid, block, 0, st, a);
-  else if (nq <= 2) hipLaunchKernelGGL((norm_fwd_kernel<2, RMS>), grid, block, 0, st, a);
-  else if (nq <= 3) hipLaunchKernelGGL((norm_fwd_kernel<3, RMS>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((norm_fwd_kernel<4, RMS>), grid, block, 0, st, a);
+  if (nq <= 1) hipLaunchKernelGGL((norm_fwd_kernel<1, RMS, ONCE>), grid, block, 0, st, a);
+  else if (nq <= 2) hipLaunchKernelGGL((norm_fwd_kernel<2, RMS, ONCE>), grid, block, 0, st, a);
+  else if (nq <= 3) hipLaunchKernelGGL((norm_fwd_kernel<3, RMS, ONCE>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((norm_fwd_kernel<4, RMS, ONCE>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
-template <bool RMS, bool SUMS>
+template <bool RMS, bool SUMS, bool ONCE>
 hipError_t bwd_dispatch(const NormBwdArgs& a, hipStream_t st) {
   const int nt = (((a.h >> 3) + 63) / 64) * 64;           // one thread per 16-byte chunk of a row
-  const int nb = a.slice_blocks, rpb = (a.slice_rows + nb - 1) / nb;
-  const dim3 grid(nb * (a.rows / a.slice_rows)), block(nt);
+  const dim3 grid(a.slice_blocks * (a.rows / a.slice_rows)), block(nt);
   // two rows per iteration (four took 245 registers and left one workgroup per compute unit), one where the block has 16 waves
-  if (nt <= 256) hipLaunchKernelGGL((norm_bwd_kernel<256, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
-  else if (nt <= 512) hipLaunchKernelGGL((norm_bwd_kernel<512, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
-  else if (nt <= 768) hipLaunchKernelGGL((norm_bwd_kernel<768, 2, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
-  else hipLaunchKernelGGL((norm_bwd_kernel<1024, 1, RMS, SUMS>), grid, block, 0, st, a, rpb, nb);
+  if (nt <= 256) hipLaunchKernelGGL((norm_bwd_kernel<256, 2, RMS, SUMS, ONCE>), grid, block, 0, st, a);
+  else if (nt <= 512) hipLaunchKernelGGL((norm_bwd_kernel<512, 2, RMS, SUMS, ONCE>), grid, block, 0, st, a);
+  else if (nt <= 768) hipLaunchKernelGGL((norm_bwd_kernel<768, 2, RMS, SUMS, ONCE>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((norm_bwd_kernel<1024, 1, RMS, SUMS, ONCE>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
@@ -382,7 +397,8 @@ int norm_bwd_blocks(int rows) {
 }
 
 hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st) {
-  return a.rms ? fwd_dispatch<true>(a, st) : fwd_dispatch<false>(a, st);
+  if (norm_streams(a.rows, a.h)) return a.rms ? fwd_dispatch<true, true>(a, st) : fwd_dispatch<false, true>(a, st);
+  return a.rms ? fwd_dispatch<true, false>(a, st) : fwd_dispatch<false, false>(a, st);
 }
 
 hipError_t norm_bwd_launch(const NormBwdArgs& a0, hipStream_t st) {
@@ -391,8 +407,12 @@ hipError_t norm_bwd_launch(const NormBwdArgs& a0, hipStream_t st) {
   if (a.slice_blocks <= 0) a.slice_blocks = norm_bwd_blocks(a.slice_rows);
   if (a.rows % a.slice_rows) return hipErrorInvalidValue;
   const bool sums = a.part_dres && a.part_dx && a.dres;
-  if (a.rms) return sums ? bwd_dispatch<true, true>(a, st) : bwd_dispatch<true, false>(a, st);
-  return sums ? bwd_dispatch<false, true>(a, st) : bwd_dispatch<false, false>(a, st);
+  auto form = [&](auto once) {
+    constexpr bool ONCE = decltype(once)::value;
+    if (a.rms) return sums ? bwd_dispatch<true, true, ONCE>(a, st) : bwd_dispatch<true, false, ONCE>(a, st);
+    return sums ? bwd_dispatch<false, true, ONCE>(a, st) : bwd_dispatch<false, false, ONCE>(a, st);
+  };
+  return norm_streams(a.rows, a.h) ? form(std::true_type{}) : form(std::false_type{});
 }
 
 hipError_t colsum_finish_launch(const float* part, int nparts, int n, float* out, int accumulate, hipStream_t st) {
