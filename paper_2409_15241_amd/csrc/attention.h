@@ -19,12 +19,12 @@ struct AttnArgs {
 
 // Whether the form for few workgroups (32 positions each, see attention.hip) is the faster one, from the time of either on
 // an otherwise idle chip (us): the longest workgroup's chain against the split form's start, end and rounds of workgroups.
-// Forward / backward, heads of 128: 4 x 704 positions, one head 16.9 -> 12.3 / 30.7 -> 18.6; 812, seven heads 19.1 -> 14.4 /
-// 35.0 -> 24.4; 4096, two heads 80 -> 42 / 118 -> 67; the two forms meet at 6 x 512, four heads, forward (14.9 each) and at
-// 3 x 1024, four heads, backward (42.2 and 41.2).  Of 34 shapes with heads of 64, 80 and 128 the form taken is the slower one
-// by more than 5 % in the backward of 2 x 2048, four heads of 128 (75.5 for 70.1: the constants were fitted before the
-// 128-position backward of these heads ran its softmax under its MFMAs) and of 8 x 256, four heads of 64 and 80 (by 1 us), and
-// in the forward of 8 x 512, four heads (by 1 us) and 2 x 2048, five heads of 64 (31.7 for 29.9).
+// Forward / backward, heads of 128: 4 x 704 positions, one head 14.0 -> 12.1 / 30.7 -> 18.6; 812, seven heads 16.1 -> 14.6 /
+// 35.0 -> 24.4; 4096, two heads 60 -> 42 / 118 -> 67; the two forms meet at 3 x 1024, four heads, backward (42.2 and 41.2).
+// The constants were fitted before either 128-position form ran its softmax under its MFMAs, which moved where they
+// meet: forward, heads of 128, 4 x 512, five heads 13.0 in the form not taken, 14.2 in the one that is, 8 x 512, four heads 13.1 and 16.4,
+// 8 x 384, five heads 11.2 and 15.3, where 3 x 1024, four heads is right with 20.0 and 18.6; backward 2 x 2048, four heads 70.1 and 75.5.
+// The line stays: the forms sum in another order, and moving it would change the bits of every block in between for 1 to 5 us.
 inline bool attention_split_pays(const AttnArgs& a, bool backward) {
   const int wgs = (a.seq + 127) / 128 * a.heads * a.batch, steps = (a.seq + 63) / 64;
   if (wgs > 128) return false;

@@ -95,7 +95,6 @@ DEV void rope_back(f32x16 (&o)[Dims<D>::DT], int pos, int fh, float log2_base) {
     }
 }
 
-// ------------------------------------------------------------------------------------- forward
 // compile-time loop: f(std::integral_constant<int, I>) for I in [0, N)
 template <int I, int N, class F>
 DEV void static_for(F&& f) {
@@ -122,200 +121,6 @@ DEV bool ranked_item(int per_group, int groups, int& pos, int& group) {
   return true;
 }
 inline int ranked_grid(int per_group, int groups) { return ((per_group * groups + 7) / 8) * 8; }
-
-// One workgroup = 128 queries of one (batch element, head): 4 waves x 32 queries.  K and V tiles of 64
-// keys travel HBM/L2 -> LDS with buffer_load ... lds (double buffered, no VGPR staging): K as
-// contraction-contiguous [kv][32 d] sub-tiles, V as row-major [32 kv][d] sub-tiles read back with the
-// transposing LDS read in accumulator-row order, so P feeds P V straight from registers.
-template <int D>
-__global__ __launch_bounds__(256, 2)
-void attn_fwd_kernel(const AttnArgs p) {
-  using X = Dims<D>;
-  constexpr int DS = (D + 31) / 32;                 // 32-wide d sub-tiles of K
-  constexpr int K_BYTES = DS * 4096;                // [DS][64 kv][32 d]
-  constexpr int V_BYTES = 2 * 8192;                 // [2][32 kv][128 d]
-  constexpr int STAGE = K_BYTES + V_BYTES;
-  constexpr int NB = (X::KSTEPS + 3) / 4;           // batches of up to 4 contraction steps over d
-  extern __shared__ __align__(1024) uint8_t smem[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int fr = lane & 31, fh = lane >> 5;
-  const int s = p.seq;
-  const int nqb = (s + 127) / 128;
-  int pos, group;
-  if (!ranked_item(nqb, p.heads * p.batch, pos, group)) return;
-  const int qb = nqb - 1 - pos;                     // longest rows first
-  const int hh = group % p.heads, bi = group / p.heads;
-  const int qw0 = qb * 128 + wave * 32, qpos = qw0 + fr;
-  const long ld = p.ld;
-  const bf16_t* tok0 = static_cast<const bf16_t*>(p.qkv) + (long)bi * s * ld;
-  const int hl = p.heads * D;
-  const long view_bytes = ((long)(s - 1) * ld + D) * 2;
-  const buf_rsrc rsK = make_rsrc(tok0 + hl + hh * D, view_bytes);
-  const buf_rsrc rsV = make_rsrc(tok0 + 2 * hl + hh * D, view_bytes);
-
-  bf16x8 qf[X::KSTEPS];
-  load_row_frags<D>(tok0 + hh * D, ld, qpos, s, fh, qf);
-
-  DmaLoader<64, 4, false> ldK;
-  DmaLoader<128, 4, true> ldV;
-  ldK.init_kc((int)ld, 0, 1 << 30, wave, lane);       // rows past the sequence end fall outside the extent
-  ldV.init_ks((int)ld, IdentityCols{0, D}, wave, lane);
-  auto issue_tile = [&](int j) {
-    uint8_t* st = smem + (j & 1) * STAGE;
-    const int kv0 = j * 64;
-#pragma unroll
-    for (int c = 0; c < DS; ++c) ldK.issue(rsK, st + c * 4096, c * 32, D, wave, (uint32_t)kv0 * (uint32_t)ld * 2u);
-#pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2) ldV.issue(rsV, st + K_BYTES + h2 * 8192, kv0 + 32 * h2, 0, wave);
-  };
-
-  // per-lane LDS offsets: K fragment (row lane%32, chunk 2*step + lane/32) and V^T fragment rows d
-  const uint32_t offK0 = kc_frag_off(lane, 0), offK1 = kc_frag_off(lane, 1);
-  uint32_t offV[X::DT];
-  {
-    const int sl = lane & 15, nh = (lane >> 4) & 1;
-    const int kr = 4 * fh + (sl >> 2);
-#pragma unroll
-    for (int dt = 0; dt < X::DT; ++dt)
-      offV[dt] = (uint32_t)(kr * 256 + ((dt ^ (kr & 3)) << 6) + (16 * nh + 4 * (sl & 3)) * 2 + K_BYTES);
-  }
-
-  const int q_end = min(qb * 128 + 128, s);
-  const int ntiles = (q_end + 63) / 64;
-  f32x16 o[X::DT];
-#pragma unroll
-  for (int dt = 0; dt < X::DT; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) o[dt][v] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
-  const float sc = p.scale * LOG2E;
-  const uint32_t smem_base = lds_addr(smem);
-
-  issue_tile(0);
-  for (int j = 0; j < ntiles; ++j) {
-    wait_vmcnt<0>();                                  // tile j has landed (this wave's part)
-    __builtin_amdgcn_s_barrier();                     // ... everybody's part; the other stage is free
-    if (j + 1 < ntiles) issue_tile(j + 1);
-    const int kv0 = j * 64;
-    if (kv0 > qw0 + 31) continue;                     // every key of the tile is masked for this wave
-    const uint32_t st = smem_base + (j & 1) * STAGE;
-
-    // ---- S^T[kv, q] = K Q^T: batches of 4 contraction steps, next batch's reads in flight
-    f32x16 sT[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sT[t][v] = 0.0f;
-    u32x4 kf[2][4][2];
-    auto read_batch = [&](auto bb) {
-      constexpr int B = decltype(bb)::value;
-      static_for<0, 4>([&](auto kk) {
-        constexpr int KS = B * 4 + decltype(kk)::value;
-        if constexpr (KS < X::KSTEPS) {
-          const uint32_t a = st + ((KS & 1) ? offK1 : offK0);
-          kf[B & 1][decltype(kk)::value][0] = ds_read_b128_at<(KS >> 1) * 4096>(a);
-          kf[B & 1][decltype(kk)::value][1] = ds_read_b128_at<(KS >> 1) * 4096 + 2048>(a);
-        }
-      });
-    };
-    read_batch(std::integral_constant<int, 0>{});
-    static_for<0, NB>([&](auto bb) {
-      constexpr int B = decltype(bb)::value;
-      constexpr int NEXT = (B + 1 < NB) ? ((X::KSTEPS - 4 * (B + 1)) < 4 ? (X::KSTEPS - 4 * (B + 1)) : 4) * 2 : 0;
-      if constexpr (B + 1 < NB) read_batch(std::integral_constant<int, B + 1>{});
-      lds_wait<NEXT>();
-      static_for<0, 4>([&](auto kk) {
-        constexpr int KS = B * 4 + decltype(kk)::value;
-        if constexpr (KS < X::KSTEPS) {
-          tie(kf[B & 1][decltype(kk)::value][0]);
-          tie(kf[B & 1][decltype(kk)::value][1]);
-#pragma unroll
-          for (int t = 0; t < 2; ++t)
-            sT[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[B & 1][decltype(kk)::value][t]),
-                                                            qf[KS], sT[t], 0, 0, 0);
-        }
-      });
-    });
-
-    // ---- online softmax; a lane owns one query (both lane halves: the two key halves of each 8)
-    float mx = -INFINITY;
-    if (kv0 + 63 > qw0) {                             // tile touches the diagonal: mask keys after the query
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          if (kv0 + 32 * t + acc_row(v, fh) > qpos) sT[t][v] = -INFINITY;
-          mx = fmaxf(mx, sT[t][v]);
-        }
-    } else {
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[t][v]);
-    }
-    mx = fmaxf(mx, other_half(mx)) * sc;       // scores scaled to the log2 domain (sc > 0)
-    const float m_new = fmaxf(m, mx);                  // finite: key 0 is visible to every query
-    if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {   // rescale only when some query's maximum moved
-      const float alpha = exp2_raw(m - m_new);
-      l *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < X::DT; ++dt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
-      m = m_new;
-    }
-    float rs = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float e = exp2_raw(sT[t][v] * sc - m);
-        sT[t][v] = e;
-        rs += e;
-      }
-    l += rs;
-    bf16x8 pf[4];
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      const int t = s4 >> 1, u = s4 & 1;
-      u32x4 w = {pack_bf16(sT[t][8 * u + 0], sT[t][8 * u + 1]), pack_bf16(sT[t][8 * u + 2], sT[t][8 * u + 3]),
-                 pack_bf16(sT[t][8 * u + 4], sT[t][8 * u + 5]), pack_bf16(sT[t][8 * u + 6], sT[t][8 * u + 7])};
-      pf[s4] = __builtin_bit_cast(bf16x8, w);
-    }
-
-    // ---- O^T[d, q] += V^T P^T, one 32-row d tile at a time, next tile's reads in flight
-    u32x2 vf[2][4][2];
-    auto read_v = [&](auto dd) {
-      constexpr int DTI = decltype(dd)::value;
-      static_for<0, 4>([&](auto ss) {
-        constexpr int S4 = decltype(ss)::value;
-        constexpr int OFF = (S4 >> 1) * 8192 + (S4 & 1) * 4096;
-        vf[DTI & 1][S4][0] = ds_read_tr_at<OFF>(st + offV[DTI]);
-        vf[DTI & 1][S4][1] = ds_read_tr_at<OFF + 2048>(st + offV[DTI]);
-      });
-    };
-    read_v(std::integral_constant<int, 0>{});
-    static_for<0, X::DT>([&](auto dd) {
-      constexpr int DTI = decltype(dd)::value;
-      if constexpr (DTI + 1 < X::DT) read_v(std::integral_constant<int, DTI + 1>{});
-      lds_wait<(DTI + 1 < X::DT) ? 8 : 0>();
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) {
-        tie(vf[DTI & 1][s4][0]);
-        tie(vf[DTI & 1][s4][1]);
-        const u32x4 a = {vf[DTI & 1][s4][0][0], vf[DTI & 1][s4][0][1], vf[DTI & 1][s4][1][0], vf[DTI & 1][s4][1][1]};
-        o[DTI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pf[s4], o[DTI], 0, 0, 0);
-      }
-    });
-  }
-  l += other_half(l);
-  if (qpos < s) {
-    bf16_t* out = static_cast<bf16_t*>(p.ctx) + ((long)bi * s + qpos) * p.ld_ctx + hh * D;
-    store_transposed<D>(o, 1.0f / l, out, fh);
-    if (fh == 0) p.lse[((long)bi * p.heads + hh) * s + qpos] = (m + log2f(l)) * LN2;
-  }
-}
 
 // ------------------------------------------------------------------------------------- D = rowsum(dO * O)
 // One thread per (row, head), all its loads in flight at once; a workgroup of one wave, so that few rows still spread over
@@ -532,9 +337,10 @@ struct BwdSteps {
 };
 
 // an operand that stays in accumulation registers from here on
-DEV void keep_in_acc(bf16x8 (&f)[8]) {
+template <int N>
+DEV void keep_in_acc(bf16x8 (&f)[N]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) asm volatile("" : "+a"(f[i]));
+  for (int i = 0; i < N; ++i) asm volatile("" : "+a"(f[i]));
 }
 // behind the loop: the last sums are as many clocks away from their MFMA as a use needs, and no copy of them is made before
 template <int N>
@@ -627,6 +433,357 @@ DEV void bwd_tile(uint32_t rows_a, uint32_t rows_b, uint32_t off_rows, uint32_t 
     if constexpr (SOFTMAX) grads_step<STEP, PER>(half{}, grads);
     __builtin_amdgcn_sched_barrier(0);
   });
+}
+
+// the same for sums in vector registers
+template <int N>
+DEV void settle_v(f32x16 (&acc)[N]) {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 7\n\ts_nop 7");
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(acc[i]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// ------------------------------------------------------------------------------------- forward
+// One workgroup = 128 queries of one (batch element, head): 4 waves x 32 queries.  A tile of 64 keys is a chain of scores, softmax and
+// output, and the longest workgroup's tiles are the launch's time where the chip is not full many times over.  So a wave
+// works on two tiles at once: while the scores of tile j + 1 are formed the softmax of tile j ends, and while the output products
+// of tile j run that of tile j + 1 begins.  A step is two MFMAs with vector work dealt out behind each.
+// What bounds a wave alone is that it issues one instruction of any kind every 4 to 8 clocks (2^x 8, a dependent addition 8): some
+// 400 a tile, so LDS places are constants of the instructions (the loop is written for two tiles) and the products, the
+// waits and the powers are most of what is left.  With two workgroups on a compute unit it is the LDS: each wave reads all of K and V.
+// K and V tiles travel HBM/L2 -> LDS with buffer_load ... lds into two places each: K as contraction-contiguous [kv][32 d]
+// sub-tiles, V as row-major [32 kv][128 d] ones read back with the transposing LDS read in accumulator-row order, so P feeds P V
+// straight from registers.  MFMAs are inline assembly on vector registers only: with accumulation registers in use the compiler
+// halves the 256 that two waves per SIMD leave each.
+// (us, with each tile's three parts one after the other and so: heads of 128, 2 x 4096 positions, 4 heads 82 -> 63, 4 x 2048, 5 heads
+// 46 -> 39, 4 x 4096, 5 heads 104 -> 100, 44 x 448, 7 heads 52 -> 51; heads of 80, 8 x 2048, 4 heads 43 -> 37, 6 x 1003, 4 heads
+// 20.9 -> 17.6; heads of 64, 2 x 2048, 5 heads 32 -> 27, but 44 x 448, 7 heads 26 -> 27.5: three workgroups fitted a compute unit.
+// One wave per SIMD with deeper rings and Q and K in accumulation registers: 71, 41 and 122 for the first three.)
+template <int D>
+struct FwdSteps {
+  static constexpr int KS = Dims<D>::KSTEPS, NV = 2 * Dims<D>::DT;                   // steps of the scores and of the output, two MFMAs each
+  static constexpr int EARLY = D == 128 ? 10 : 8;                                    // pairs of probabilities (of 16) taken beside the output products
+  static constexpr int AK = D == 128 ? 2 : 3, AV = AK;                                               // steps ahead that fragments are read
+  // reads in flight that step `at` (scores 0 .. KS - 1, then output) may leave so: those of the steps behind it
+  static constexpr int reads(int at) { return at < KS ? 2 : at < KS + NV ? 4 : 0; }
+  static constexpr int issued(int at) { return at < KS ? at - AK : at - AV; }          // the step beside which `at`'s reads stand
+  static constexpr int behind(int at) {
+    int n = 0;
+    for (int k = at + 1; k < KS + NV; ++k) n += issued(k) < at ? reads(k) : 0;
+    return n;
+  }
+};
+// K fragment and Q in accumulation registers, scores in vector registers; ZERO: the first product of a sum.  The wait for the fragments
+// stands in the same statement.
+template <bool ZERO, int WAIT>
+DEV void fwd_score_mfma(const u32x4& k, bf16x8 q, f32x16& t) {
+  if constexpr (WAIT >= 0) {
+    if constexpr (ZERO) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(t) : "v"(k), "v"(q), "n"(WAIT));
+    else asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(t) : "v"(k), "v"(q), "n"(WAIT));
+  } else {
+    if constexpr (ZERO) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(t) : "v"(k), "v"(q));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(t) : "v"(k), "v"(q));
+  }
+}
+template <int WAIT>
+DEV void fwd_output_mfma(const u32x4& v, const u32x4& p, f32x16& o) {
+  if constexpr (WAIT >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(o) : "v"(v), "v"(p), "n"(WAIT));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(o) : "v"(v), "v"(p));
+}
+// a value is formed here, and not behind the branches that follow, or ahead of the loop
+template <class T>
+DEV void here(T& v) { asm volatile("" : "+v"(v)); }
+DEV void idle8() {
+  asm volatile("s_nop 7");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// both transposing reads of 16 keys into the halves of one fragment
+template <int OFF>
+DEV void read_v_frag(uint32_t addr, u32x2& a, u32x2& b) {
+  a = ds_read_tr_at<OFF>(addr);
+  b = ds_read_tr_at<OFF + 2048>(addr);
+}
+
+template <int D>
+DEV void attn_fwd_body(const AttnArgs& p, uint8_t* smem) {
+  using X = Dims<D>;
+  using S = FwdSteps<D>;
+  constexpr int DS = (D + 31) / 32;                 // 32-wide d sub-tiles of K
+  constexpr int K_BYTES = DS * 4096, V_BYTES = 2 * 8192;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 31, fh = lane >> 5;
+  const int s = p.seq;
+  const int nqb = (s + 127) / 128;
+  int pos, group;
+  if (!ranked_item(nqb, p.heads * p.batch, pos, group)) return;
+  const int qb = nqb - 1 - pos;                     // longest rows first
+  const int hh = group % p.heads, bi = group / p.heads;
+  const int qw0 = qb * 128 + wave * 32, qpos = qw0 + fr;
+  const long ld = p.ld;
+  const bf16_t* tok0 = static_cast<const bf16_t*>(p.qkv) + (long)bi * s * ld;
+  const int hl = p.heads * D;
+  const int ntiles = (min(qb * 128 + 128, s) + 63) / 64;
+  const int mine = min((qw0 + 31) / 64 + 1, ntiles);          // tiles that this wave's queries see; the others see at most one more
+
+  // loads: a wave's pieces of a tile.  The tile is advanced in the buffer resource, whose extent ends with the last tile or
+  // row that is needed: what lies beyond gives zeros.
+  DmaLoader<64, 4, false> ldK;
+  DmaLoader<128, 4, true> ldV;
+  ldK.init_kc((int)ld, 0, 1 << 30, wave, lane);
+  ldV.init_ks((int)ld, IdentityCols{0, D}, wave, lane);
+  uint32_t at_k[DS], at_v[4];
+#pragma unroll
+  for (int c = 0; c < DS; ++c) at_k[c] = c * 32 + ldK.kofs < D ? ldK.base[0] + c * 64 : BUF_OOB;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) at_v[i] = ldV.base[i & 1] + (uint32_t)((i >> 1) * 32) * (uint32_t)ld * 2u;
+  const int step = 64 * (int)ld * 2;
+  const char* next_k = reinterpret_cast<const char*>(tok0 + hl + hh * D);
+  const char* next_v = reinterpret_cast<const char*>(tok0 + 2 * hl + hh * D);
+  int left_k = ((min(ntiles * 64, s) - 1) * (int)ld + D) * 2, left_v = left_k;
+  auto load_k = [&](int c, buf_rsrc rs, int slot) { __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * K_BYTES + c * 4096 + wave * 1024), 16, at_k[c], 0, 0, 0); };
+  auto load_v = [&](int i, buf_rsrc rs, int slot) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + 2 * K_BYTES + slot * V_BYTES + (i >> 1) * 8192 + (wave * 2 + (i & 1)) * 1024), 16, at_v[i], 0, 0, 0);
+  };
+  auto advance_k = [&] { next_k += step; left_k = max(left_k - step, 0); };
+  auto advance_v = [&] { next_v += step; left_v = max(left_v - step, 0); };
+  auto fill_k = [&](int slot) {
+    const buf_rsrc rs = make_rsrc(next_k, left_k);
+#pragma unroll
+    for (int c = 0; c < DS; ++c) load_k(c, rs, slot);
+    advance_k();
+  };
+  auto fill_v = [&](int slot) {
+    const buf_rsrc rs = make_rsrc(next_v, left_v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_v(i, rs, slot);
+    advance_v();
+  };
+  bf16x8 qf[X::KSTEPS];
+  load_row_frags<D>(tok0 + hh * D, ld, qpos, s, fh, qf);
+  fill_k(0); fill_v(0); fill_k(1);
+
+  // per-lane LDS addresses: K fragment (row lane%32, chunk 2*step + lane/32) and V^T fragment rows d
+  const uint32_t lds = lds_addr(smem);
+  const uint32_t offK[2] = {lds + kc_frag_off(lane, 0), lds + kc_frag_off(lane, 1)};
+  uint32_t offV[X::DT];
+  {
+    const int sl = lane & 15, nh = (lane >> 4) & 1;
+    const int kr = 4 * fh + (sl >> 2);
+#pragma unroll
+    for (int dt = 0; dt < X::DT; ++dt) offV[dt] = lds + (uint32_t)(kr * 256 + ((dt ^ (kr & 3)) << 6) + (16 * nh + 4 * (sl & 3)) * 2);
+  }
+  f32x16 o[X::DT], sT[2][2];                        // sT[j & 1]: scores of tile j, then their powers
+#pragma unroll
+  for (int dt = 0; dt < X::DT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[dt][v] = 0.0f;
+  uint32_t pw[16];                                  // P, packed: pair w of the 32 scores
+  float m = -INFINITY, l = 0.0f, alpha = 1.0f, rs = 0.0f, mx = 0.0f;
+  uint64_t moved = 0;                               // queries whose maximum moved with the tile
+  const float sc = p.scale * LOG2E;
+
+  u32x4 kf[S::AK + 1][2];
+  u32x2 vf[S::AV + 1][2][2];
+  auto read_k = [&](auto gc, auto slot) {
+    constexpr int G = decltype(gc)::value, OFF = decltype(slot)::value * K_BYTES + (G >> 1) * 4096;
+    kf[G % (S::AK + 1)][0] = ds_read_b128_at<OFF>(offK[G & 1]);
+    kf[G % (S::AK + 1)][1] = ds_read_b128_at<OFF + 2048>(offK[G & 1]);
+  };
+  auto read_v = [&](auto hc, auto slot) {           // step h: d tile h / 2, 32 keys of half h % 2
+    constexpr int H = decltype(hc)::value, OFF = 2 * K_BYTES + decltype(slot)::value * V_BYTES + (H & 1) * 8192;
+    read_v_frag<OFF>(offV[H / 2], vf[H % (S::AV + 1)][0][0], vf[H % (S::AV + 1)][0][1]);
+    read_v_frag<OFF + 4096>(offV[H / 2], vf[H % (S::AV + 1)][1][0], vf[H % (S::AV + 1)][1][1]);
+  };
+  // reads that stand beside step `at`: K from place sk, V from place sv
+  auto reads_beside = [&](auto at, auto sk, auto sv) {
+    static_for<0, S::KS>([&](auto g) { if constexpr (S::issued(decltype(g)::value) == decltype(at)::value) read_k(g, sk); });
+    static_for<0, S::NV>([&](auto h) { if constexpr (S::issued(S::KS + decltype(h)::value) == decltype(at)::value) read_v(h, sv); });
+  };
+  auto score_step = [&](auto gc, auto&& beside, f32x16 (&t)[2], auto waits) {
+    constexpr int G = decltype(gc)::value;
+    u32x4 (&k)[2] = kf[G % (S::AK + 1)];
+    static_for<0, 2>([&](auto tc) {
+      constexpr int T = decltype(tc)::value;
+      fwd_score_mfma<G == 0, T == 0 ? decltype(waits)::value : -1>(k[T], qf[G], t[T]);
+      __builtin_amdgcn_sched_barrier(0);
+      beside(tc);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto output_step = [&](auto hc, auto&& beside, auto waits) {
+    constexpr int H = decltype(hc)::value;
+    u32x2 (&v)[2][2] = vf[H % (S::AV + 1)];
+    static_for<0, 2>([&](auto uc) {
+      constexpr int U = decltype(uc)::value, W = 8 * (H & 1) + 4 * U;
+      if constexpr (U == 0) wait_for<decltype(waits)::value>(v[0][0], v[0][1], v[1][0], v[1][1]);
+      const u32x4 a = {v[U][0][0], v[U][0][1], v[U][1][0], v[U][1][1]}, b = {pw[W], pw[W + 1], pw[W + 2], pw[W + 3]};
+      fwd_output_mfma<-1>(a, b, o[H / 2]);
+      __builtin_amdgcn_sched_barrier(0);
+      beside(uc);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // ---- online softmax; a lane owns one query (both lane halves: the two key halves of each 8)
+  auto maximum = [&](f32x16 (&t)[2], int j) {
+    if (j == mine - 1) {                            // the tile meets the diagonal: mask keys after the query
+      int last = qpos - j * 64;                     // (opaque: 32 comparisons of the last tile, kept from the start, would take 64 scalar registers)
+      here(last);
+#pragma unroll
+      for (int T = 0; T < 2; ++T)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (32 * T + acc_row(v, fh) > last) t[T][v] = -INFINITY;
+    }
+    mx = -INFINITY;
+#pragma unroll
+    for (int T = 0; T < 2; ++T)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, t[T][v]);
+  };
+  auto statistics = [&] {
+    mx = fmaxf(mx, other_half(mx)) * sc;            // scores scaled to the log2 domain (sc > 0)
+    const float m_new = fmaxf(m, mx);               // finite: key 0 is visible to every query
+    moved = __builtin_amdgcn_ballot_w64(m_new != m);           // rescale only when some query's maximum moved
+    if (moved) {
+      alpha = exp2_raw(m - m_new);
+      l *= alpha;
+      m = m_new;
+    }
+    rs = 0.0f;
+  };
+  auto rescale = [&] {
+    if (moved) {
+#pragma unroll
+      for (int dt = 0; dt < X::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
+    }
+  };
+  auto power = [&](f32x16 (&t)[2], auto wc) {       // pair w of the powers, in the place of their scores
+    constexpr int T = decltype(wc)::value / 8, V = decltype(wc)::value % 8 * 2;
+    float e0 = exp2_raw(t[T][V] * sc - m), e1 = exp2_raw(t[T][V + 1] * sc - m);
+    rs += e0;
+    rs += e1;
+    here(e0);
+    here(e1);
+    here(rs);
+    t[T][V] = e0;
+    t[T][V + 1] = e1;
+  };
+  auto pack = [&](f32x16 (&t)[2], auto wc) {
+    constexpr int W = decltype(wc)::value, T = W / 8, V = W % 8 * 2;
+    pw[W] = pack_bf16(t[T][V], t[T][V + 1]);
+    here(pw[W]);
+  };
+  // vector work of score step G of the tile after t's: the end of t's softmax
+  constexpr int LATE = 16 - S::EARLY;
+  auto beside_scores = [&](auto gc, auto half, f32x16 (&t)[2]) {
+    constexpr int G = decltype(gc)::value, H = 2 * G + decltype(half)::value, NH = 2 * S::KS;
+    if constexpr (H == 5) rescale();
+    static_for<S::EARLY * H / NH, S::EARLY * (H + 1) / NH>([&](auto w) { pack(t, w); });
+    static_for<S::EARLY + LATE * H / NH, S::EARLY + LATE * (H + 1) / NH>([&](auto w) { power(t, w); pack(t, w); });
+    if constexpr (H == NH - 1) { l += rs; here(l); }
+  };
+  // vector work of output step h: the beginning of the softmax of tile j
+  auto beside_output = [&](auto hc, auto half, f32x16 (&t)[2], int j) {
+    constexpr int H = decltype(hc)::value, Q = 2 * (H - 2) + decltype(half)::value, NQ = 2 * (S::NV - 2);
+    if constexpr (H == 1 && decltype(half)::value == 0) { idle8(); maximum(t, j); }
+    if constexpr (H == 1 && decltype(half)::value == 1) statistics();
+    if constexpr (H >= 2) static_for<S::EARLY * Q / NQ, S::EARLY * (Q + 1) / NQ>([&](auto w) { power(t, w); });
+  };
+
+  // scores of tile 0, and the beginning of its softmax
+  wait_vmcnt<4 + DS>();
+  __builtin_amdgcn_s_barrier();
+  static_for<0, S::AK>([&](auto g) { read_k(g, half0{}); });
+  static_for<0, S::KS>([&](auto gc) {
+    constexpr int G = decltype(gc)::value, NEXT = G + S::AK, LEFT = S::KS - 1 - G;
+    score_step(gc, [&](auto half) {
+      if constexpr (decltype(half)::value == 0 && NEXT < S::KS) read_k(std::integral_constant<int, (NEXT < S::KS ? NEXT : 0)>{}, half0{});
+    }, sT[0], std::integral_constant<int, 2 * (LEFT < S::AK - 1 ? LEFT : S::AK - 1)>{});
+  });
+  wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  idle8();
+  maximum(sT[0], 0);
+  statistics();
+  moved = 0;                                        // there is no output yet to rescale
+  static_for<0, S::EARLY>([&](auto w) { power(sT[0], w); });
+
+  auto both = [&](auto cur, int j) {                // scores of tile j + 1, output of tile j
+    constexpr int C = decltype(cur)::value;
+    using other = std::integral_constant<int, C ^ 1>;
+    f32x16 (&now)[2] = sT[C];
+    f32x16 (&nxt)[2] = sT[C ^ 1];
+    const buf_rsrc rk = make_rsrc(next_k, left_k), rv = make_rsrc(next_v, left_v);
+    static_for<-S::AK, 0>([&](auto at) { reads_beside(at, other{}, cur); });
+    static_for<0, S::KS>([&](auto gc) {
+      constexpr int G = decltype(gc)::value;
+      score_step(gc, [&](auto half) {
+        constexpr int Q = 2 * G + decltype(half)::value, N = 2 * S::KS, L = DS + 4;
+        if constexpr (decltype(half)::value == 0) { reads_beside(gc, other{}, cur); __builtin_amdgcn_sched_barrier(0); }
+        static_for<L * Q / N, L * (Q + 1) / N>([&](auto ic) {      // K of tile j + 2 in the place of tile j's, V of tile j + 1
+          constexpr int I = decltype(ic)::value;
+          if constexpr (I < DS) load_k(I, rk, C); else load_v(I - DS, rv, C ^ 1);
+        });
+        beside_scores(gc, half, now);
+      }, nxt, std::integral_constant<int, S::behind(G)>{});
+    });
+    advance_k();
+    advance_v();
+    static_for<0, S::NV>([&](auto hc) {
+      constexpr int H = decltype(hc)::value;
+      output_step(hc, [&](auto half) {
+        if constexpr (decltype(half)::value == 0) { reads_beside(std::integral_constant<int, S::KS + H>{}, other{}, cur); __builtin_amdgcn_sched_barrier(0); }
+        beside_output(hc, half, nxt, j + 1);
+      }, std::integral_constant<int, S::behind(S::KS + H)>{});
+    });
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+  };
+  int j = 0;
+  for (; j + 2 < mine; j += 2) {
+    both(half0{}, j);
+    both(half1{}, j + 1);
+  }
+  auto end = [&](auto cur) {                        // the last tile: the end of its softmax, its output
+    constexpr int C = decltype(cur)::value;
+    if (mine < ntiles) fill_v(C ^ 1);               // the tile that the other waves' queries still see
+    static_for<0, S::AV>([&](auto h) { read_v(h, cur); });
+    settle_v(o);
+    static_for<0, S::KS>([&](auto gc) { beside_scores(gc, half0{}, sT[C]); beside_scores(gc, half1{}, sT[C]); });
+    idle8();
+    static_for<0, S::NV>([&](auto hc) {
+      constexpr int H = decltype(hc)::value;
+      output_step(hc, [&](auto half) {
+        if constexpr (decltype(half)::value == 0 && H + S::AV < S::NV) read_v(std::integral_constant<int, H + S::AV < S::NV ? H + S::AV : 0>{}, cur);
+      }, std::integral_constant<int, (S::NV - 1 - H < S::AV - 1 ? S::NV - 1 - H : S::AV - 1) * 4>{});
+    });
+    settle_v(o);
+  };
+  if (j + 1 < mine) {
+    both(half0{}, j);
+    end(half1{});
+  } else {
+    end(half0{});
+  }
+  wait_vmcnt<0>();                                  // what was asked for ahead lands before the LDS is another workgroup's
+  if (mine < ntiles) __builtin_amdgcn_s_barrier();
+  l += other_half(l);
+  if (qpos < s) {
+    bf16_t* out = static_cast<bf16_t*>(p.ctx) + ((long)bi * s + qpos) * p.ld_ctx + hh * D;
+    store_transposed<D>(o, 1.0f / l, out, fh);
+    if (fh == 0) p.lse[((long)bi * p.heads + hh) * s + qpos] = (m + log2f(l)) * LN2;
+  }
+}
+template <int D>
+__global__ __launch_bounds__(256, 2)
+void attn_fwd_kernel(const AttnArgs p) {
+  extern __shared__ __align__(1024) uint8_t smem[];
+  attn_fwd_body<D>(p, smem);
 }
 
 // ------------------------------------------------------------------------------------- dQ pass
