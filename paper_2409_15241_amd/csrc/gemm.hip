@@ -12,7 +12,7 @@
 // Work decomposition: one workgroup of four waves (one per SIMD) per BM x BN tile of C, each wave owning a
 // WM x WN sub-tile as (WN/16) x (WM/16) MFMA accumulators.  Operand tiles of BK = 64 contraction elements (whole
 // 128-byte lines of a contraction-contiguous operand) travel HBM/L2 -> LDS with buffer_load ... lds into two rings
-// (three tiles of A, two of B; two of each where a tile is 320 wide); no VGPR staging, no ds_write.
+// (see Rings); no VGPR staging, no ds_write.
 // What bounds it at large sizes is power: a 16x16x32 MFMA reads and writes half as many accumulator bytes per flop as
 // a 32x32x16 one (1.89 against 1.83 PFLOP/s at 0.545 against 0.549 pJ/flop above idle on N(0,1) x N(0,0.02) fragments with
 // nothing else running, which domino_mfma_probe_shape measures), so every product here is made of those; a wave tile of
@@ -29,8 +29,17 @@
 namespace {
 
 constexpr int BK = GEMM_BK;
-constexpr int RING_B = 2;
-constexpr int ring_a(int BM, int BN) { return (3 * BM + RING_B * BN) * BK * 2 <= 160 * 1024 ? 3 : 2; }      // tiles of A in flight
+// Operand tiles in LDS at once, of A and of B (see the software pipeline of gemm_body).  Weights come from HBM, the activations
+// often from a cache that the kernel before has just written, and a place more is half to one and a half tiles more to
+// land in: 256x128 tiles work through theirs in 0.6 us, so they take all 160 KB, and in 192x256 the third place is B's, the
+// larger tile of the two.  (A just written, B out of the caches, {3, 2} and as here: 2048 x 2560 x 5120 in 256x128 NN 70 -> 66 us,
+// NT 74 -> 69, in 192x256 103 -> 92 and 97 -> 87, 2048 x 5120 x 2560 51.5 -> 48.2; all in the caches 60.6 -> 59.2, 80 -> 78.  256x256 with {2, 3}
+// and five places of each in 128x128 tiles, one workgroup to a compute unit, won here and lost there.)
+struct Rings { int a, b; };
+constexpr Rings rings(int BM, int BN) {
+  return BM == 256 && BN == 128 ? Rings{3, 4} : BM == 192 && BN == 256 ? Rings{2, 3} : (3 * BM + 2 * BN) * BK * 2 <= 160 * 1024 ? Rings{3, 2} : Rings{2, 2};
+}
+constexpr int ring_bytes(int BM, int BN) { return (rings(BM, BN).a * BM + rings(BM, BN).b * BN) * BK * 2; }
 
 // KS tile [64 k][R rows]: element (k, n) at byte 2 R k + 64 ((n >> 5) ^ ks_swz(k)) + 2 (n & 31).  A transposing read
 // covers 4 consecutive k x 16 n: the XOR, together with the row pitch, puts the 4 rows in 4 different 64-byte quarters of
@@ -355,7 +364,7 @@ DEV void mfma_vgpr(bf16x8 a, bf16x8 b, f32x4& c) { asm volatile("v_mfma_f32_16x1
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 DEV void gemm_body(const GemmArgs& p, const int lin) {
   constexpr int NW = (BM / WM) * (BN / WN);
-  constexpr int TM = WM / 16, TN = WN / 16, RING_A = ring_a(BM, BN);
+  constexpr int TM = WM / 16, TN = WN / 16, RING_A = rings(BM, BN).a, RING_B = rings(BM, BN).b;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   extern __shared__ __align__(1024) uint8_t smem[];
 
@@ -481,14 +490,17 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   using step0 = std::integral_constant<int, 0>;
   using step1 = std::integral_constant<int, 1>;
 
+  // X: the operand with more places, loaded during step 0 into the place of the tile before; Y: the other one, during step 1
+  constexpr bool X_IS_B = RING_B > RING_A, BOTH = RING_A == RING_B;
+
   // Software pipeline.  Tile kt's two MFMA steps: during step 0 the fragments of step 1 are read, during step 1 those
   // of tile kt+1's step 0.  The one barrier of a tile stands between the steps: by then every wave has read all of tile
-  // kt, whose two ring places are refilled from there on: with B of tile kt+2 during step 1, with A of tile kt+3 during
-  // the next tile's step 0.  So loads are spread over the whole tile, one every 8 MFMAs (a load occupies the address
-  // path for 16 clocks; bunched up behind the barrier they stall the MFMAs issued between them), each has at least a
-  // step to land, and the third place of the A ring keeps a tile in flight across the barrier.  Where the LDS has no third
-  // place (tiles of 320), both are loaded during step 1, A first, which comes from further away: one every 3 MFMAs (every 2
-  // measured 3 to 4 % slower); a step of such a tile is a quarter longer, which is what its loads have less to land in.
+  // kt, whose two ring places are refilled from there on: Y's during step 1 with tile kt+Y, X's during the next tile's
+  // step 0 with tile kt+X (X and Y for the number of places of each).  So loads are spread over the whole tile, in 256x256 one
+  // every 8 MFMAs (a load occupies the address path for 16 clocks; bunched up behind the barrier they stall the MFMAs issued
+  // between them), and with three and two places each has at least a step to land, with four and three three.  Where the LDS
+  // has two places of each only (tiles of 320), both are loaded during step 1, A first, which comes from further away: one every
+  // 3 MFMAs (every 2 measured 3 to 4 % slower); a step of such a tile is a quarter longer, which is what its loads have less to land in.
   // (8192^3, N(0,1) x N(0,0.02), NT / NN / TN: 1.52 / 1.53 / 1.48 PFLOP/s; with compiler-placed sums 1.51 / 1.49 / 1.43, and on
   // another board 1.48 / 1.45 / 1.43, where a ring of four 32-deep tiles, eight waves and 32x32x16 MFMAs made 1.20 / 1.26 /
   // 1.21 and two rings of two 1.42 / 1.39 / 1.40.)
@@ -507,8 +519,21 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
     for (int i = 0; i < IPB; ++i) ldB.issue(i, rs, in, ringB + slot * B_BYTES, wave);
     ldB.advance();
   };
-  fill_a(0); fill_b(0); fill_a(1); fill_b(1);
-  wait_vmcnt<IPA + IPB>();
+  // The loads in the order that the loop goes on with, the first tile's in front.  BEHIND: loads asked for behind those of tile
+  // kt+1 when the barrier of tile kt is reached; X(kt+1) was asked for 2 (X - 2) steps before that one, Y(kt+1) 2 Y - 3.
+  constexpr int X = X_IS_B ? RING_B : RING_A, Y = X_IS_B ? RING_A : RING_B, IPX = X_IS_B ? IPB : IPA, IPY = X_IS_B ? IPA : IPB;
+  auto fill_x = [&](int slot) { if constexpr (X_IS_B) fill_b(slot); else fill_a(slot); };
+  auto fill_y = [&](int slot) { if constexpr (X_IS_B) fill_a(slot); else fill_b(slot); };
+  constexpr int SINCE = 2 * Y - 3 < 2 * (X - 2) ? 2 * Y - 3 : 2 * (X - 2);
+  constexpr int BEHIND = BOTH ? 0 : (SINCE + 1) / 2 * IPX + SINCE / 2 * IPY;
+  if constexpr (BOTH) {
+    fill_x(0); fill_y(0); fill_x(1); fill_y(1);
+    wait_vmcnt<IPX + IPY>();
+  } else {
+    static_assert(X == Y + 1, "the order of the loads in front of the loop");
+    static_for<0, Y>([&](auto t) { fill_x(decltype(t)::value); fill_y(decltype(t)::value); });
+    wait_vmcnt<(Y - 1) * (IPX + IPY)>();
+  }
   __builtin_amdgcn_s_barrier();
   const uint32_t lds_a = lds_addr(smem), lds_b = lds_addr(ringB);
   static_for<0, READS>([&](auto r) { read_one(step0{}, r, lds_a, lds_b); });
@@ -520,49 +545,51 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
 
   constexpr int NM = TM * TN;                          // MFMAs per step
   int sa = 0, sb = 0;                                  // ring places of tile kt
-  int free_a = RING_A - 1;                             // ring place that tile kt-1 left to the A tile loaded in step 0
+  int free_x = X - 1;                                  // ring place that tile kt-1 left to the tile of X loaded in step 0
   for (int kt = 0; kt < nk; ++kt) {
     const uint32_t ta = lds_a + sa * A_BYTES, tb = lds_b + sb * B_BYTES;
-    const int sa_next = sa == RING_A - 1 ? 0 : sa + 1, sb_next = sb ^ 1;
+    const int sa_next = sa == RING_A - 1 ? 0 : sa + 1, sb_next = sb == RING_B - 1 ? 0 : sb + 1;
     const uint32_t ta_next = lds_a + sa_next * A_BYTES, tb_next = lds_b + sb_next * B_BYTES;
     tie_step(step0{});
     __builtin_amdgcn_sched_barrier(0);
     {
-      const buf_rsrc rs = ldA.rsrc();
-      const bool in = ldA.inside();
-      uint8_t* dst = smem + free_a * A_BYTES;
+      const buf_rsrc rs = X_IS_B ? ldB.rsrc() : ldA.rsrc();
+      const bool in = X_IS_B ? ldB.inside() : ldA.inside();
+      uint8_t* dst = X_IS_B ? ringB + free_x * B_BYTES : smem + free_x * A_BYTES;
       static_for<0, NM>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
         mfma_and_reads(step0{}, step1{}, mc, ta, tb);
-        constexpr int LE = NM / IPA;
-        if constexpr (RING_A == 3 && m % LE == LE / 2 && m / LE < IPA) ldA.issue(m / LE, rs, in, dst, wave);
+        constexpr int LE = NM / IPX;
+        if constexpr (!BOTH && m % LE == LE / 2 && m / LE < IPX) {
+          if constexpr (X_IS_B) ldB.issue(m / LE, rs, in, dst, wave); else ldA.issue(m / LE, rs, in, dst, wave);
+        }
         __builtin_amdgcn_sched_barrier(0);
       });
-      if (RING_A == 3) ldA.advance();
+      if constexpr (!BOTH) { if constexpr (X_IS_B) ldB.advance(); else ldA.advance(); }
     }
-    wait_vmcnt<RING_A == 3 ? IPA : 0>();               // tile kt+1 has landed (this wave's share); A of kt+2 may be in flight
+    wait_vmcnt<BEHIND>();                              // tile kt+1 has landed (this wave's share); later ones may be in flight
     tie_step(step1{});                                 // ... and this wave has read all of tile kt
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     {
-      const buf_rsrc rs = ldB.rsrc(), rsa = ldA.rsrc();
-      const bool in = ldB.inside(), ina = ldA.inside();
-      uint8_t *dst = ringB + sb * B_BYTES, *dsta = smem + sa * A_BYTES;
+      const buf_rsrc rsb = ldB.rsrc(), rsa = ldA.rsrc();
+      const bool inb = ldB.inside(), ina = ldA.inside();
+      uint8_t *dstb = ringB + sb * B_BYTES, *dsta = smem + sa * A_BYTES;
       static_for<0, NM>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
         mfma_and_reads(step1{}, step0{}, mc, ta_next, tb_next);
-        constexpr int LOADS = RING_A == 3 ? IPB : IPA + IPB, LE = RING_A == 3 ? NM / LOADS : NM * 3 / 4 / LOADS;
+        constexpr int LOADS = BOTH ? IPA + IPB : IPY, LE = BOTH ? NM * 3 / 4 / LOADS : NM / LOADS;
         if constexpr (m % LE == LE / 2 && m / LE < LOADS) {
-          constexpr int l = m / LE, a = RING_A == 3 ? 0 : IPA;
+          constexpr int l = m / LE, a = BOTH || X_IS_B ? IPA : 0;
           if constexpr (l < a) ldA.issue(l, rsa, ina, dsta, wave);
-          else ldB.issue(l - a, rs, in, dst, wave);
+          else ldB.issue(l - a, rsb, inb, dstb, wave);
         }
         __builtin_amdgcn_sched_barrier(0);
       });
-      ldB.advance();
-      if (RING_A == 2) ldA.advance();
+      if constexpr (BOTH || !X_IS_B) ldB.advance();
+      if constexpr (BOTH || X_IS_B) ldA.advance();
     }
-    free_a = sa;
+    free_x = X_IS_B ? sb : sa;
     sa = sa_next; sb = sb_next;
   }
   wait_vmcnt<0>();     // the zero-fill loads issued past the last tile must land before the LDS is released
@@ -811,7 +838,7 @@ bool plan_tiles(GemmArgs& a) {
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int NT = gemm_threads(BM, BN, WM, WN);
-  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : (ring_a(BM, BN) * BM + RING_B * BN) * BK * 2;
+  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : ring_bytes(BM, BN);
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
   if (n > 1 || products[0].splits > 1) {
     if constexpr (EPI == EPI_ACC_F32 && !(BM == 128 && BN == 256)) {      // (the rule, which alone forms groups, never picks 128x256)
