@@ -227,6 +227,7 @@ int begin_call(void* const* streams, int nstreams, int p) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev), "hipGetDevice");
   g_pool = &g_pools[dev];
+  t_tail.open = false;                       // (a call that failed half way may have left it)
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(static_cast<hipStream_t>(streams[0]), &cs), "hipStreamIsCapturing");
   g_capturing = cs != hipStreamCaptureStatusNone;
@@ -581,8 +582,9 @@ enum { WG_DOWN = 0, WG_UP, WG_OUT, WG_QKV, NWGRADS };
 
 // the weight gradients of the n matrices in `which` (and before them the column sums behind the biases of the same
 // products), on `st`: one launch for all of them (`parts`: memory for the sums of L.wsplits contraction ranges, or NULL
-// for one range); with cfg->wgrad_per_slice one per matrix and slice, in slice order
-int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, const int* which, int n, hipStream_t st, float* parts) {
+// for one range); with cfg->wgrad_per_slice one per matrix and slice, in slice order.  `tail`: a Norm1 backward is held back
+// for that one launch (HeldTail)
+int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, const int* which, int n, hipStream_t st, float* parts, bool tail) {
   const char* sv = static_cast<const char*>(B.saved);
   const domino_grads* G = B.G;
   struct { int cls; const void* A; long lda; const void* Bm; long ldb; float* C; int M, N; int bias; } const tab[NWGRADS] = {
@@ -611,6 +613,7 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
       a.beside = L.beside;
       if (parts) { a.splits = L.wsplits; a.split_ws = parts; }
       a.join = join ? 1 : 0;
+      a.tail = tail ? 1 : 0;
       LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
     }
   }
@@ -647,6 +650,13 @@ int vector_gradients(const Layout& L, const BwdLayer& B, int which, hipStream_t 
     LAUNCH(colsum_finish_jobs_launch(jobs, njobs, (i > 0 || B.accumulate) ? 1 : 0, st), "vector gradient reduction");
   }
   return DOMINO_OK;
+}
+
+// Whether the Norm1 backward and the bias gradients go into the weight gradients' launch where one stream carries them all: two
+// or three launches fewer, which pays the more the smaller the block is (figures at gemm_tail_kernel of gemm.hip); with 8M
+// values of an activation, the largest measured, it is 2 %.
+inline bool tail_joins(const Layout& L) {
+  return L.groups == 1 && !L.per_slice && L.wsplits == 1 && L.h <= HeldTail::MAX_H && (long)L.M * L.h <= 1L << 23;
 }
 
 // What the blocks of a stack hand on to each other: events behind the weight gradients of a block and the stream each ran
@@ -704,8 +714,8 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
   const bool in_place = !S.side && S.lanes == 1;
   // several contraction ranges where the launch follows the chain on its one stream: nothing else then uses their sums' memory
   float* const parts_ws = in_place && L.wsplits > 1 ? reinterpret_cast<float*>(at(ws, L.wpart)) : nullptr;
-  auto form = [&](std::initializer_list<int> which, hipStream_t st) -> int {
-    TRY(weight_gradients(L, gb, B, which.begin(), (int)which.size(), st, parts_ws));
+  auto form = [&](std::initializer_list<int> which, hipStream_t st, bool tail = false) -> int {
+    TRY(weight_gradients(L, gb, B, which.begin(), (int)which.size(), st, parts_ws, tail));
     if (own) {
       hipEvent_t ev;
       TRY(record(&ev, st));
@@ -724,17 +734,31 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
         if (two_above->on[m] != as_stream(S.streams[k])) TRY(wait(as_stream(S.streams[k]), two_above->wgrad[m]));
 
   auto norm_bwd = [&](const Rows& R, hipStream_t st, const void* ga, const void* gb2, const void* xin, const void* gamma, size_t mean,
-                      size_t rstd, const void* dres, void* out, int kg, int kb, int kres, int kdx) -> int {
+                      size_t rstd, const void* dres, void* out, int kg, int kb, int kres, int kdx, bool join = false) -> int {
     ProfScope ps(PC_NORM_BWD, st);
     NormBwdArgs a{};
     a.ga = ga; a.gb = gb2; a.x = xin; a.gamma = gamma; a.mean = rowf(mean, R); a.rstd = rowf(rstd, R); a.dres = dres; a.dx = out;
     a.part_g = B.red + L.area(kg, R.slice); a.part_b = B.red + L.area(kb, R.slice); a.rows = R.n; a.h = L.h; a.rms = rms;
     a.slice_rows = L.Ms;
     a.slice_blocks = L.area_rows[kg];
+    a.join = join ? 1 : 0;
     if (kres >= 0) { a.part_dres = B.red + L.area(kres, R.slice); a.part_dx = B.red + L.area(kdx, R.slice); }   // bias gradients of the two row-cut products
     LAUNCH(norm_bwd_launch(a, st), "norm backward");
     return DOMINO_OK;
   };
+
+  auto norm1 = [&](bool join) -> int {
+    // in a stack dx goes into the tensor that the block above took its dy from, and that block's down-projection weight
+    // gradient, enqueued a whole block ago, reads all of it
+    if (above && above->wgrad[WG_DOWN])
+      for (int k = 0; k < S.lanes; ++k)
+        if (above->on[WG_DOWN] != as_stream(S.streams[k])) TRY(wait(as_stream(S.streams[k]), above->wgrad[WG_DOWN]));
+    return each_group([&](const Rows& R, hipStream_t st) -> int {
+      return norm_bwd(R, st, at(B.dln1_partial, R.rh), B.dln1_others ? at(B.dln1_others, R.rh) : nullptr, at(B.x, R.rh), P->norm1_g,
+                      L.mean1, L.rstd1, dx1(R), at(B.dx, R.rh), AREA_G1, AREA_B1, -1, -1, join);
+    });
+  };
+  const bool joined_tail = in_place && (parts & DOMINO_BWD_ATTN) && (parts & DOMINO_BWD_NORM1) && tail_joins(L);
 
   if (parts & DOMINO_BWD_MLP) {
     if (S.side) {        // operands: the forward's, and dy, which in a stack the block above has just written
@@ -807,21 +831,12 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       return DOMINO_OK;
     }));
     if (in_place) {      // all of the call's weight gradients in one launch
-      if (parts & DOMINO_BWD_MLP) TRY(form({WG_DOWN, WG_UP, WG_OUT, WG_QKV}, S.lane(0)));
-      else TRY(form({WG_OUT, WG_QKV}, S.lane(0)));
+      if (joined_tail) TRY(norm1(true));
+      if (parts & DOMINO_BWD_MLP) TRY(form({WG_DOWN, WG_UP, WG_OUT, WG_QKV}, S.lane(0), joined_tail));
+      else TRY(form({WG_OUT, WG_QKV}, S.lane(0), joined_tail));
     }
   }
-  if (parts & DOMINO_BWD_NORM1) {
-    // in a stack dx goes into the tensor that the block above took its dy from, and that block's down-projection weight
-    // gradient, enqueued a whole block ago, reads all of it
-    if (above && above->wgrad[WG_DOWN])
-      for (int k = 0; k < S.lanes; ++k)
-        if (above->on[WG_DOWN] != as_stream(S.streams[k])) TRY(wait(as_stream(S.streams[k]), above->wgrad[WG_DOWN]));
-    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {
-      return norm_bwd(R, st, at(B.dln1_partial, R.rh), B.dln1_others ? at(B.dln1_others, R.rh) : nullptr, at(B.x, R.rh), P->norm1_g,
-                      L.mean1, L.rstd1, dx1(R), at(B.dx, R.rh), AREA_G1, AREA_B1, -1, -1);
-    }));
-  }
+  if ((parts & DOMINO_BWD_NORM1) && !joined_tail) TRY(norm1(false));
   if (S.side) {
     if (parts & DOMINO_BWD_NORM1) {
       TRY(behind_groups(side, own ? &own->dx : nullptr));

@@ -37,6 +37,7 @@ struct GemmArgs {
   int splits;            // joined weight gradients: contraction ranges, each summed into its own part of split_ws (0 or 1: one)
   float* split_ws;       // splits * (sum of M * N of the joined products) floats
   int join;              // EPI_ACC_F32: 1 = hold this product back, it is launched together with the next call's (see gemm_launch)
+  int tail;              // joined weight gradients: 1 = with what t_tail of norm.h holds for their stream; filled in by the launcher for the kernels
   int tiles_m, tiles_n;  // filled by the launcher
   int group_m;           // filled by the launcher: tile rows per band of the tile order
   long a_bytes, b_bytes; // extent of the A / B views in bytes, filled by the launcher

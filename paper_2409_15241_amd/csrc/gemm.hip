@@ -24,6 +24,7 @@
 #include "gemm.h"
 #include "host_once.h"
 #include "lds_dma.h"
+#include "norm_body.h"
 #include <type_traits>
 
 namespace {
@@ -778,8 +779,7 @@ void gemm_kernel(const GemmArgs p) {
 // Several weight gradients of one block in one launch: alone, each leaves part of the chip idle (the 13B shard's are 200,
 // 200, 60 and 160 tiles of 256x256 on 256 compute units), and a small block pays mostly for the launches.
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
-__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
-void gemm_group_kernel(const GemmGroup p) {
+DEV void gemm_group_body(const GemmGroup& p) {
   const int T1 = p.first[GEMM_GROUP], T = T1 * p.splits;
   int lin = tile_of_block(T);
   if (lin >= T) return;
@@ -799,6 +799,41 @@ void gemm_group_kernel(const GemmGroup p) {
   a.C = static_cast<float*>(a.C) + range * p.part_stride;
   if constexpr (BM == WM && BN == WN) gemm_split_body<BM, AKS, BKS, EPI>(a, lin - p.first[i]);
   else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(a, lin - p.first[i]);
+}
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
+void gemm_group_kernel(const GemmGroup p) {
+  gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI>(p);
+}
+
+// ... and with what else a small block's backward ends with: the Norm1 backward's workgroups behind the tiles, then those of
+// the bias gradients (four waves each, two to a workgroup of eight).  A dependent launch costs such a block some 4 us whatever it does, and
+// its products leave part of the chip idle (forward + backward, us, apart and joined: 256 tokens of a 256-wide block 82 and 73, 1024
+// of a 1024-wide one 128 and 117, 4096 of it 241 and 230, 8192 403 and 394, 400 of a Llama one 129 and 125; 256 of a 2048-wide one
+// 128 and 120, 2000 of it 228 and 216, 4000 355 and 348).
+struct GemmTail { HeldTail t; int tiles, norm_blocks, sum_items[COLSUM_MAX_HELD]; };      // workgroups of the tiles and of the norm; column blocks x ranges
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+__global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
+void gemm_tail_kernel(const GemmGroup p, const GemmTail tail) {
+  extern __shared__ __align__(1024) uint8_t smem[];
+  if ((int)blockIdx.x < tail.tiles) {
+    gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI>(p);
+    return;
+  }
+  const int at = blockIdx.x - tail.tiles;
+  float* const lds = reinterpret_cast<float*>(smem);
+  if (at < tail.norm_blocks) {
+    if (tail.t.norm.rms) norm_bwd_body<2, true, false, false>(tail.t.norm, at, tail.norm_blocks, lds);
+    else norm_bwd_body<2, false, false, false>(tail.t.norm, at, tail.norm_blocks, lds);
+    return;
+  }
+  const int wave = threadIdx.x >> 6, quad = wave >> 2;
+  int item = (at - tail.norm_blocks) * (gemm_threads(BM, BN, WM, WN) / 256) + quad, k = 0;
+  if (item >= tail.sum_items[0]) { item -= tail.sum_items[0]; k = 1; }
+  const bool any = item < tail.sum_items[k];
+  const ColsumPartial c = tail.t.sums[k];
+  colsum_partial_body(static_cast<const bf16_t*>(c.g), c.ld, any ? c.rows : 0, any ? c.n : 0, c.part, item / COLSUM_PARTS, item % COLSUM_PARTS,
+                      COLSUM_PARTS, wave & 3, lds + quad * (COLSUM_LDS / 4));
 }
 
 // The ranges' sums added in order (and to what the gradient held): HBM-bound, one 16-byte chunk of every range per thread.
@@ -872,6 +907,21 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
       }
       for (int i = n; i <= GEMM_GROUP; ++i) grp.first[i] = T;
       grp.part_stride = sum.part_stride = at;
+      if (products[0].tail) {
+        GemmTail tail{};
+        tail.t = t_tail;
+        t_tail.open = false;
+        tail.tiles = (int)grid(T).x;
+        tail.norm_blocks = tail.t.norm.slice_blocks * (tail.t.norm.rows / tail.t.norm.slice_rows);
+        for (int k = 0; k < tail.t.nsums; ++k) tail.sum_items[k] = (tail.t.sums[k].n / 8 + 63) / 64 * COLSUM_PARTS;
+        constexpr int QUADS = NT / 256;
+        const int sums = (tail.sum_items[0] + tail.sum_items[1] + QUADS - 1) / QUADS;
+        auto both = gemm_tail_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
+        static LdsLimitOnce tail_limit;
+        if (hipError_t e = tail_limit.ensure(reinterpret_cast<const void*>(both), LDS); e != hipSuccess) return e;
+        hipLaunchKernelGGL(both, dim3(tail.tiles + tail.norm_blocks + sums), dim3(NT), LDS, stream, grp, tail);
+        return hipGetLastError();
+      }
       hipLaunchKernelGGL(kern, grid(T * grp.splits), dim3(NT), LDS, stream, grp);
       if (hipError_t e = hipGetLastError(); e != hipSuccess || grp.splits == 1) return e;
       hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((at / 4 + 255) / 256)), dim3(256), 0, stream, sum);
@@ -930,6 +980,13 @@ hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hi
     a = g_held; n = g_nheld; g_nheld = 0;
   }
   if (tile_cfg < 0) tile_cfg = gemm_pick_form(a, n, epi, a->concurrency);
+  if (a0.tail) {      // what is held has to fit the launch: four waves or more a workgroup, one range, the kernel's form of the norm
+    const NormBwdArgs& norm = t_tail.norm;
+    if (!t_tail.open || t_tail.stream != stream || n < 2 || a->splits > 1 || norm.h > HeldTail::MAX_H || norm.part_dres || norm_streams(norm.rows, norm.h)) {
+      t_tail.open = false;
+      return hipErrorInvalidValue;
+    }
+  }
   if (layout == GEMM_NN) {
     switch (epi) {
       case EPI_STORE:     return launch_layout<false, true, EPI_STORE>(a, n, tile_cfg, stream);

@@ -38,7 +38,24 @@ struct NormBwdArgs {
   int rows, h, rms;
   int slice_rows;         // divides rows; 0: one slice of all rows
   int slice_blocks;       // workgroups (and partial rows) per slice; 0: norm_bwd_blocks(slice_rows)
+  int join;               // 1: held back for the weight gradients' launch (see HeldTail)
 };
+
+// What a small block's backward ends with, next to its weight gradients: the Norm1 backward and the bias gradients' first
+// stages.  None of them reads what another writes, so they can be one launch (GemmArgs::tail): a Norm1 backward with `join` is held
+// back (per thread) with the column sums that follow it on the same stream, until the weight gradients of that stream are
+// launched with `tail` set.
+struct ColsumPartial { const void* g; long ld; int rows, n; float* part; };
+constexpr int COLSUM_MAX_HELD = 2;
+struct HeldTail {
+  static constexpr int MAX_H = 2048;         // rows of four waves: the fewest that a workgroup of a product has
+  NormBwdArgs norm;
+  ColsumPartial sums[COLSUM_MAX_HELD];
+  int nsums;
+  hipStream_t stream;
+  bool open;
+};
+inline thread_local HeldTail t_tail{};
 
 // Workgroups of the backward, per slice of a launch over `slices` slices (where the caller's memory allows their number to be
 // chosen; the single-kernel entry point's scratch holds norm_bwd_blocks): one per compute unit, more where a row has few
@@ -49,6 +66,13 @@ inline int norm_bwd_slice_blocks(int slices, int slice_rows, int h) {
   const int waves = (h / 8 + 63) / 64, fill = 256 * (waves > 4 ? 1 : 8 / waves) / slices, want = (slice_rows + 3) / 4;
   return fill < 1 ? 1 : want < fill ? want : fill;
 }
+// Whether a launch's rows outgrow the last-level cache (256 MB, shared with the products beside them): tensors of 32 MB and
+// more.  Then what is read once (x, the other ranks' sum, the incoming gradients but the one just written) and what is written
+// goes past the caches: backward 16384 x 2560 79.8 -> 69.8 us, 8192 x 4096 63.5 -> 53.6, 4096 x 5120 44.1 -> 39.6; forward with the residual
+// sum 73.3 -> 64.2, 58.7 -> 52.5, 38.8 -> 35.1.  Smaller ones are read again while they are still there: a step of 2 x 200
+// tokens of a 1024-wide block 126.5 us without and 129.6 with, 2048 tokens of 13B 664.7 and 673.6, 6018 of 2.7B 623.4 and 627.6.
+inline bool norm_streams(long rows, int h) { return rows * h >= 1L << 24; }
+
 int norm_bwd_blocks(int rows);              // 16 rows each until the block limit is reached
 hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st);
 hipError_t norm_bwd_launch(const NormBwdArgs& a, hipStream_t st);
