@@ -33,5 +33,11 @@ inline bool attention_split_pays(const AttnArgs& a, bool backward) {
   return 4.5 + rounds * (1.5 + 1.1 * a.seq / 128) < 0.95 * (5 + 1.17 * steps);
 }
 
+// Whether that form's backward forms D = rowsum(dctx * ctx) itself, where a wave has two tiles of 32 queries or fewer: it saves a dependent launch
+// and costs 0.85 us a tile of a wave's chain (16-byte loads of 32 rows, which nothing else covers).  Backward with the launch and
+// without, us: 2 x 128 positions, two heads of 64 7.8 and 6.0, 2 x 200, two of 128 12.1 and 10.7, 4 x 256 12.4 and 11.5; 2 x 512, four heads
+// 15.3 and 16.3, 2 x 1024, two 20.7 and 25.4, 4096, two 62 and 90.
+inline bool attention_owns_d(int seq) { return seq <= 256; }
+
 hipError_t attention_fwd_launch(const AttnArgs& a, hipStream_t st);
 hipError_t attention_bwd_launch(const AttnArgs& a, hipStream_t st);

@@ -1249,7 +1249,18 @@ void attn_fwd_split_kernel(const AttnArgs p) {
   }
 }
 
-template <int D>
+// D = rowsum(dO * O) of 32 queries is the diagonal of dO O^T: with OWN_D the passes form it by the MFMAs that form dP, in the same order, so
+// that for a sequence of one position D equals dP bit for bit here too.  See attention_owns_d for where that pays.
+// Lane c, or the one 32 on, holds the diagonal's value c: lanes whose half is diag_half(c).
+DEV int diag_half(int c) { return (c >> 2) & 1; }
+DEV float diag(const f32x16& t, int c) {
+  float d = t[0];
+#pragma unroll
+  for (int v = 1; v < 16; ++v) d = 4 * (c >> 3) + (c & 3) == v ? t[v] : d;
+  return d;
+}
+
+template <int D, bool OWN_D>
 DEV void attn_bwd_dq_split_body(const AttnArgs& p, uint8_t* smem, int qb, int hh, int bi) {
   using X = Dims<D>;
   const int lane = threadIdx.x & 63;
@@ -1276,7 +1287,20 @@ DEV void attn_bwd_dq_split_body(const AttnArgs& p, uint8_t* smem, int qb, int hh
   load_row_frags<D>(static_cast<const bf16_t*>(p.dctx) + (long)bi * s * p.ld_ctx + hh * D, p.ld_ctx, qpos, s, fh, dof);
   const long stat = ((long)bi * p.heads + hh) * s + qpos;
   const float lse2 = qpos < s ? p.lse[stat] * LOG2E : INFINITY;
-  const float dq_dot = qpos < s ? p.dot[stat] : 0.0f;
+  float dq_dot;
+  if constexpr (!OWN_D) {
+    dq_dot = qpos < s ? p.dot[stat] : 0.0f;
+  } else {
+    bf16x8 of[X::KSTEPS];
+    load_row_frags<D>(static_cast<const bf16_t*>(p.ctx) + (long)bi * s * p.ld_ctx + hh * D, p.ld_ctx, qpos, s, fh, of);
+    f32x16 sums;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sums[v] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < X::KSTEPS; ++k) sums = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[k], dof[k], sums, 0, 0, 0);
+    const float mine_d = diag(sums, fr), other_d = other_half(mine_d);
+    dq_dot = fh == diag_half(fr) ? mine_d : other_d;
+  }
   const uint32_t offP = rm_plain_off(lane), offT = rm_trans_off(lane);
   const float sc = p.scale * LOG2E;
   f32x16 dq[X::DT];
@@ -1310,7 +1334,7 @@ DEV void attn_bwd_dq_split_body(const AttnArgs& p, uint8_t* smem, int qb, int hh
   }
 }
 
-template <int D>
+template <int D, bool OWN_D>
 DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int hh, int bi) {
   using X = Dims<D>;
   const int lane = threadIdx.x & 63;
@@ -1326,6 +1350,7 @@ DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int h
   const long stat0 = ((long)bi * p.heads + hh) * s;
   const buf_rsrc rsL = make_rsrc(p.lse + stat0, (long)s * 4);
   const buf_rsrc rsD = make_rsrc(p.dot + stat0, (long)s * 4);
+  const buf_rsrc rsC = make_rsrc(static_cast<const bf16_t*>(p.ctx) + (long)bi * s * ldc + hh * D, ((long)(s - 1) * ldc + D) * 2);
   uint8_t* const mine = smem + wave * SP_WAVE;
   SplitLoader ldq, ldo;
   ldq.init((int)ld, D, lane);
@@ -1335,8 +1360,9 @@ DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int h
     ldq.issue(rsQ, st, (uint32_t)(j * 32) * (uint32_t)ld * 2u);
     ldo.issue(rsO, st + SP_TILE, (uint32_t)(j * 32) * (uint32_t)ldc * 2u);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsL, LDS_PTR(st + 2 * SP_TILE), 4, (uint32_t)(j * 32 + lane) * 4u, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsD, LDS_PTR(st + 2 * SP_TILE + 256), 4, (uint32_t)(j * 32 + lane) * 4u, 0, 0, 0);
+    if constexpr (!OWN_D) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsD, LDS_PTR(st + 2 * SP_TILE + 256), 4, (uint32_t)(j * 32 + lane) * 4u, 0, 0, 0);
   };
+  const uint32_t o_off = (uint32_t)(fr * (int)ldc + fh * 8) * 2u;
   if (kb + wave < nq) issue(kb + wave, 0);
   bf16x8 kf[X::KSTEPS], vf[X::KSTEPS];
   load_row_frags<D>(tok0 + hl + hh * D, ld, kpos, s, fh, kf);
@@ -1348,7 +1374,22 @@ DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int h
   zero_acc<D>(dv);
   int stage = 0;
   for (int j = kb + wave; j < nq; j += 4, stage ^= 1) {
-    if (j + 4 < nq) { issue(j + 4, stage ^ 1); wait_vmcnt<18>(); } else { wait_vmcnt<0>(); }
+    // O of this tile straight into fragments, asked for in front of the next tile so that it can be waited for alone, and needed
+    // behind the scores
+    u32x4 of[OWN_D ? X::KSTEPS : 1];
+    if constexpr (OWN_D) {
+#pragma unroll
+      for (int k = 0; k < X::KSTEPS; ++k) of[k] = __builtin_amdgcn_raw_buffer_load_b128(rsC, o_off + (uint32_t)(j * 32) * (uint32_t)ldc * 2u + 32u * k, 0, 0);
+      issue(j + 4, stage ^ 1);                             // past the last one too: zeros, and one count of loads for the compiler's waits
+      asm volatile("" ::: "memory");                       // none of them is moved behind the wait
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vmcnt<X::KSTEPS + 17>();
+    } else if (j + 4 < nq) {
+      issue(j + 4, stage ^ 1);
+      wait_vmcnt<18>();
+    } else {
+      wait_vmcnt<0>();
+    }
     const uint32_t st = lds_addr(mine) + stage * SP_STAGE;
     {
       f32x16 sm, dpm;
@@ -1356,6 +1397,21 @@ DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int h
 #pragma unroll
       for (int v = 0; v < 16; ++v) dpm[v] = 0.0f;
       rm_mma_rows<D, 0>(st, st + SP_TILE, offP, kf, vf, sm, dpm);
+      if constexpr (OWN_D) {
+        f32x16 sums;                                         // dO O^T, its diagonal to where D is read from
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sums[v] = 0.0f;
+        u32x4 dof[X::KSTEPS];
+        static_for<0, X::KSTEPS>([&](auto kc) { constexpr int K = decltype(kc)::value; dof[K] = ds_read_b128_at<SP_TILE>(st + (offP ^ (K << 5))); });
+        lds_wait<0>();
+#pragma unroll
+        for (int k = 0; k < X::KSTEPS; ++k) {
+          tie(dof[k]);
+          sums = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dof[k]), __builtin_bit_cast(bf16x8, of[k]), sums, 0, 0, 0);
+        }
+        const float d = diag(sums, fr);
+        if (fh == diag_half(fr)) asm volatile("ds_write_b32 %0, %1 offset:%2" ::"v"(st + 4u * fr), "v"(d), "n"(2 * SP_TILE + 256) : "memory");
+      }
       dkv_probs(st + 2 * SP_TILE + (uint32_t)fh * 16u, sc, sm, dpm);
       bf16x8 pf[2], dsf[2];
       pack_acc(sm, pf);
@@ -1364,6 +1420,7 @@ DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int h
       rm_mma_cols<D, 0>(st, offT, dsf, dk);
     }
   }
+  if constexpr (OWN_D) wait_vmcnt<0>();                    // no load may land in what the sums go to
   put_acc(mine, dk, lane);
   put_acc(mine + X::DT * 4096, dv, lane);
   __syncthreads();
@@ -1379,7 +1436,7 @@ DEV void attn_bwd_dkv_split_body(const AttnArgs& p, uint8_t* smem, int kb, int h
   }
 }
 
-template <int D>
+template <int D, bool OWN_D>
 __global__ __launch_bounds__(256)
 void attn_bwd_split_kernel(const AttnArgs p) {
   static_assert(SP_WAVE >= 2 * Dims<D>::DT * 4096, "a wave's dK and dV sums fit its stages");
@@ -1388,8 +1445,8 @@ void attn_bwd_split_kernel(const AttnArgs p) {
   int pos, group;
   if (!ranked_item(2 * nb, p.heads * p.batch, pos, group)) return;
   const int hh = group % p.heads, bi = group / p.heads;
-  if (pos & 1) attn_bwd_dq_split_body<D>(p, smem, nb - 1 - (pos >> 1), hh, bi);
-  else attn_bwd_dkv_split_body<D>(p, smem, pos >> 1, hh, bi);
+  if (pos & 1) attn_bwd_dq_split_body<D, OWN_D>(p, smem, nb - 1 - (pos >> 1), hh, bi);
+  else attn_bwd_dkv_split_body<D, OWN_D>(p, smem, pos >> 1, hh, bi);
 }
 
 template <int D>
@@ -1410,20 +1467,25 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int D, bool OWN_D>
+hipError_t bwd_split_launch(const AttnArgs& a, hipStream_t st) {
+  constexpr int LDS = 4 * SP_WAVE;
+  static LdsLimitOnce lds_limit;
+  if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_bwd_split_kernel<D, OWN_D>), LDS); e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_bwd_split_kernel<D, OWN_D>), dim3(ranked_grid(2 * ((a.seq + 31) / 32), a.heads * a.batch)), dim3(256), LDS, st, a);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t bwd_launch(const AttnArgs& a, hipStream_t st) {
+  const bool split = attention_split_pays(a, true);
+  if (split && attention_owns_d(a.seq)) return bwd_split_launch<D, true>(a, st);
   const int rows = a.batch * a.seq;
   hipLaunchKernelGGL(attn_dot_kernel<D>, dim3((unsigned)(((long)rows * a.heads + 63) / 64)), dim3(64), 0, st,
                      static_cast<const bf16_t*>(a.ctx), static_cast<const bf16_t*>(a.dctx), a.ld_ctx, rows, a.seq, a.heads, a.dot);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (attention_split_pays(a, true)) {
-    constexpr int LDS = 4 * SP_WAVE;
-    static LdsLimitOnce lds_limit;
-    if ((e = lds_limit.ensure(reinterpret_cast<const void*>(attn_bwd_split_kernel<D>), LDS)) != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_bwd_split_kernel<D>, dim3(ranked_grid(2 * ((a.seq + 31) / 32), a.heads * a.batch)), dim3(256), LDS, st, a);
-    return hipGetLastError();
-  }
+  if (split) return bwd_split_launch<D, false>(a, st);
   constexpr int LDS = 2 * (2 * RM_TILE + 512);             // the larger of the two passes' needs
   static LdsLimitOnce lds_limit;
   if ((e = lds_limit.ensure(reinterpret_cast<const void*>(attn_bwd_kernel<D>), LDS)) != hipSuccess) return e;
