@@ -243,10 +243,14 @@ int begin_call(void* const* streams, int nstreams, int p) {
   return DOMINO_OK;
 }
 
+// The events order streams of one device and are never looked at from the host, so they go without the fence that would make
+// the work before them visible there (a program's own synchronisation has its own): a record then holds its stream up for 5 us and
+// not for 6 to 8 (forward + backward, us, with and without the fence: 13B with 2048 tokens 655 and 641, with 8192 2042 and 2028, in parts 2124 and
+// 2115; Llama-2 7B level).
 int next_sync_event(hipEvent_t* ev) {
   if (g_pool->used == g_pool->events.size()) {
     hipEvent_t e;
-    HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
+    HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence), "hipEventCreate");
     g_pool->events.push_back(e);
   }
   *ev = g_pool->events[g_pool->used++];
@@ -380,8 +384,9 @@ struct StreamPlan {
   void* const* streams;
   int ns, lanes;
   bool side;
-  StreamPlan(void* const* s, int n, const Layout& L, bool backward)
-      : streams(s), ns(n), lanes(L.groups < n ? L.groups : n), side(backward && L.beside && !g_capturing && n > lanes) {}
+  StreamPlan(void* const* s, int n, const Layout& L, int bwd_parts)
+      : streams(s), ns(n), lanes(L.groups < n ? L.groups : n),
+        side((bwd_parts & (DOMINO_BWD_MLP | DOMINO_BWD_ATTN)) && L.beside && !g_capturing && n > lanes) {}
   hipStream_t lane(int g) const { return as_stream(streams[g % lanes]); }
   hipStream_t side_stream() const { return as_stream(streams[lanes]); }
   int used() const { return lanes + (side ? 1 : 0); }
@@ -678,16 +683,24 @@ int wait(hipStream_t st, hipEvent_t ev) {
   return DOMINO_OK;
 }
 
+// Where the weight gradients run beside the chain, or the call is the Norm1 part alone, the streams meet on streams[0] before the last
+// reduction of the vector gradients and not behind it: an edge between streams is 10 to 14 us in which nothing else runs, and on
+// the side stream the reduction stood between two of them (forward + backward, us, both
+// with the events as they are: 13B with 2048 tokens 661 and 650, Llama-2 7B 1560 and 1538, the 13B block in parts 2170 and 2149).
+inline bool reduces_joined(const StreamPlan& S, int parts) {
+  return (parts & DOMINO_BWD_NORM1) && (S.side || !(parts & (DOMINO_BWD_MLP | DOMINO_BWD_ATTN)));
+}
+
 // Backward of one block: each step of the chain of input gradients for one row group after the other, every group on
 // its own stream; each input gradient is enqueued before the weight gradient of the same product (Sec. 4.1.2).  With a
 // side stream the weight and vector gradients run there, each behind an event of every group; without one they follow
 // on the groups' streams: one group forms them where their operands are complete, several first meet on streams[0] and
 // part again (the same join and fork that end one call and begin the next) and take the matrices in turn.
-// In a stack: `own` receives this block's events, `above` are those of the block above, `two_above` of the block that
+// `last`: no block follows in the call.  In a stack: `own` receives this block's events, `above` are those of the block above, `two_above` of the block that
 // used the same set of gradient tensors (NULL outside a stack or where there is no such block); `turn` deals the matrices
 // to the streams differently from block to block.
 int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& S, void* ws, const GradBufs& gb, const BwdLayer& B,
-                      int parts, int turn = 0, BlockEvents* own = nullptr, const BlockEvents* above = nullptr,
+                      int parts, bool last, int turn = 0, BlockEvents* own = nullptr, const BlockEvents* above = nullptr,
                       const BlockEvents* two_above = nullptr) {
   const domino_params* P = B.P;
   const void* saved = B.saved;
@@ -837,7 +850,10 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
     }
   }
   if ((parts & DOMINO_BWD_NORM1) && !joined_tail) TRY(norm1(false));
-  if (S.side) {
+  if (last && reduces_joined(S, parts)) {
+    TRY(join_streams(S, S.used()));
+    TRY(vector_gradients(L, B, mlp_vectors_early ? VEC_ATTN : VEC_ALL, S.lane(0)));
+  } else if (S.side) {
     if (parts & DOMINO_BWD_NORM1) {
       TRY(behind_groups(side, own ? &own->dx : nullptr));
       TRY(vector_gradients(L, B, mlp_vectors_early ? VEC_ATTN : VEC_ALL, side));
@@ -952,7 +968,7 @@ int domino_layer_fwd_parts(const domino_cfg* cfg, const domino_params* P,
   if (workspace_bytes < L.ws_total) return fail(DOMINO_ERR_WORKSPACE_TOO_SMALL, "workspace holds %zu bytes, %zu needed", workspace_bytes, L.ws_total);
   std::lock_guard<std::mutex> lock(g_mutex);
   TRY(begin_call(streams, nstreams, L.p));
-  const StreamPlan S(streams, nstreams, L, false);
+  const StreamPlan S(streams, nstreams, L, 0);
   note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
@@ -990,12 +1006,12 @@ int domino_layer_bwd_parts(const domino_cfg* cfg, const domino_params* P, const 
   std::lock_guard<std::mutex> lock(g_mutex);
   TRY(begin_call(streams, nstreams, L.p));
   B.red = reinterpret_cast<float*>(at(workspace, L.red));
-  const StreamPlan S(streams, nstreams, L, true);
+  const StreamPlan S(streams, nstreams, L, parts);
   note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
-  TRY(enqueue_bwd_block(L, cfg, S, workspace, grad_bufs(L, workspace), B, parts));
-  TRY(join_streams(S, S.used()));
+  TRY(enqueue_bwd_block(L, cfg, S, workspace, grad_bufs(L, workspace), B, parts, true));
+  if (!reduces_joined(S, parts)) TRY(join_streams(S, S.used()));
   return DOMINO_OK;
 }
 
@@ -1029,7 +1045,7 @@ int domino_stack_fwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   TRY(begin_call(streams, nstreams, L.p));
   // a row slice of block l+1 needs only the same row slice of block l (Sec. 3.2): the groups run through the
   // whole stack on their own streams and meet only at the end
-  const StreamPlan S(streams, nstreams, L, false);
+  const StreamPlan S(streams, nstreams, L, 0);
   note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
@@ -1070,7 +1086,7 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   if (g_capturing && merged && nlayers > 1)
     return fail(DOMINO_ERR_UNSUPPORTED, "streams[0] is being captured into a HIP graph: the backward of a stack of %d blocks with "
                 "p = %d > 2 row slices cannot be captured; capture one domino_layer_bwd call per block instead", nlayers, L.p);
-  const StreamPlan S(streams, nstreams, L, true);
+  const StreamPlan S(streams, nstreams, L, DOMINO_BWD_ALL);
   note_hw_queues(S.used());
   ConcurrencyScope conc(S.used(), L);
   TRY(fork_streams(S, S.used()));
@@ -1081,11 +1097,11 @@ int domino_stack_bwd(const domino_cfg* cfg, int nlayers, const domino_params* pa
   const bool several = S.used() > 1;       // one stream orders itself
   for (int l = nlayers - 1, k = 0; l >= 0; --l, ++k) {
     BlockEvents own;
-    TRY(enqueue_bwd_block(L, cfg, S, workspace, gb[k & 1], layers[l], DOMINO_BWD_ALL, k, several ? &own : nullptr,
+    TRY(enqueue_bwd_block(L, cfg, S, workspace, gb[k & 1], layers[l], DOMINO_BWD_ALL, l == 0, k, several ? &own : nullptr,
                           several && k > 0 ? &ev[(k & 1) ^ 1] : nullptr, several && k > 1 ? &ev[k & 1] : nullptr));
     ev[k & 1] = own;
   }
-  TRY(join_streams(S, S.used()));
+  if (!reduces_joined(S, DOMINO_BWD_ALL)) TRY(join_streams(S, S.used()));
   return DOMINO_OK;
 }
 
