@@ -685,8 +685,9 @@ int wait(hipStream_t st, hipEvent_t ev) {
 
 // Where the weight gradients run beside the chain, or the call is the Norm1 part alone, the streams meet on streams[0] before the last
 // reduction of the vector gradients and not behind it: an edge between streams is 10 to 14 us in which nothing else runs, and on
-// the side stream the reduction stood between two of them (forward + backward, us, both
-// with the events as they are: 13B with 2048 tokens 661 and 650, Llama-2 7B 1560 and 1538, the 13B block in parts 2170 and 2149).
+// the side stream the reduction stood between two of them (forward + backward,
+// us, before and now, together with what next_sync_event says: 13B with 2048 tokens 672 and 650, Llama-2 7B 1560 and 1538, the 13B block in
+// parts 2180 and 2149).
 inline bool reduces_joined(const StreamPlan& S, int parts) {
   return (parts & DOMINO_BWD_NORM1) && (S.side || !(parts & (DOMINO_BWD_MLP | DOMINO_BWD_ATTN)));
 }

@@ -185,8 +185,8 @@ struct EpiCols {
 // Stores ROWS rows of sums from LDS.  side() requests what the epilogue needs of the side tensors for the rows from m on
 // and is called one block of rows ahead of finish(), which reads the sums and stores: loads of global memory (1 to 2 us)
 // are in flight while the block before them is worked on.  Rows or columns outside the matrix read a safe address instead
-// of branching, their results are never stored.  PARTS: the sums of `parts` buffers part_bytes apart, added in their order.
-template <int BN, int WN, int EPI, int ROWS, bool PARTS, int ROW_BYTES = epi_row_bytes(WN)>
+// of branching, their results are never stored.  The sums of PARTS buffers PART_BYTES apart are added in their order.
+template <int BN, int WN, int EPI, int ROWS, int ROW_BYTES = epi_row_bytes(WN), int PARTS = 1, int PART_BYTES = 0>
 struct RowStore {
   static constexpr int ROWB = ROW_BYTES, NROWS = ROWS;
   static constexpr int RPI = 64 / (WN / 4);      // rows per read instruction
@@ -198,7 +198,6 @@ struct RowStore {
   };
   const GemmArgs& p;
   const EpiCols<BN, WN, EPI>& ec;
-  int parts, part_bytes;
 
   DEV bool inside(int m, int t, long& row) const {
     const int mr = m + t * RPI + ec.rrow;
@@ -227,9 +226,12 @@ struct RowStore {
     }
   }
   DEV f32x4 read(const uint8_t* buf, int at) const {
-    f32x4 v = *reinterpret_cast<const f32x4*>(buf + at);
-    if constexpr (PARTS)
-      for (int k = 1; k < parts; ++k) v += *reinterpret_cast<const f32x4*>(buf + k * part_bytes + at);
+    f32x4 part[PARTS];
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) part[k] = *reinterpret_cast<const f32x4*>(buf + k * PART_BYTES + at);
+    f32x4 v = part[0];
+#pragma unroll
+    for (int k = 1; k < PARTS; ++k) v += part[k];
     return v;
   }
   // buf: row m's sums
@@ -611,10 +613,10 @@ DEV void gemm_body(const GemmArgs& p, const int lin) {
   constexpr int CA = WN >= 128 ? 128 : 64, CB = WN - CA;
   const EpiCols<BN, CA, EPI> ec_a(p, tn, n0, wn0, lane);
   const EpiCols<BN, CB ? CB : CA, EPI> ec_b(p, tn, n0, wn0 + (CB ? CA : 0), lane);
-  using StoreA = RowStore<BN, CA, EPI, epi_block_rows(CA), false, ROWB>;
-  using StoreB = RowStore<BN, CB ? CB : CA, EPI, epi_block_rows(CB ? CB : CA), false, ROWB>;
-  const StoreA rs_a{p, ec_a, 1, 0};
-  const StoreB rs_b{p, ec_b, 1, 0};
+  using StoreA = RowStore<BN, CA, EPI, epi_block_rows(CA), ROWB>;
+  using StoreB = RowStore<BN, CB ? CB : CA, EPI, epi_block_rows(CB ? CB : CA), ROWB>;
+  const StoreA rs_a{p, ec_a};
+  const StoreB rs_b{p, ec_b};
   typename StoreA::Side side_a;
   typename StoreB::Side side_b;
   rs_a.side(side_a, m0 + wm0);
@@ -689,8 +691,16 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
 #pragma unroll
   for (int i = 0; i < (BKS ? T / 2 : 1); ++i) offB[i] = lds_b + (BKS ? ks_frag_off16<R>(lane, i) : kc_frag_off16(lane));
 
+  constexpr int ROWB = epi_row_bytes(R), MINE = S::ROWS / S::W;
   const int nk = (p.K + BK - 1) / BK;
   if (wave < nk) fill();
+  // what the epilogue reads besides the sums is asked for here where the registers hold it: it is then there with the first tiles
+  constexpr bool EARLY = R == 64;
+  const EpiCols<R, R, EPI> ec(p, tn, n0, 0, lane);
+  using Store = RowStore<R, R, EPI, MINE, ROWB, S::W, S::STAGE>;
+  const Store rs{p, ec};
+  typename Store::Side side;
+  if constexpr (EARLY) rs.side(side, m0 + wave * MINE);
   for (int kt = wave; kt < nk; kt += S::W) {
     u32x4 fa[2][AKS ? 1 : T], fb[2][BKS ? 1 : T];
     u32x2 ha[2][AKS ? T : 1][2], hb[2][BKS ? T : 1][2];
@@ -734,23 +744,18 @@ DEV void gemm_split_body(const GemmArgs& p, const int lin) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), acc[i][j], 0, 0, 0);
         }
   }
-  // the sums replace the wave's own operand tiles, 64 rows at a time; then every wave stores its share of these rows
-  constexpr int ROWB = epi_row_bytes(R), MINE = S::ROWS / S::W;
-  const EpiCols<R, R, EPI> ec(p, tn, n0, 0, lane);
-  const RowStore<R, R, EPI, MINE, true> rs{p, ec, min(nk, S::W), S::STAGE};
+  // the sums replace the wave's own operand tiles, 64 rows at a time; then every wave stores its share of these rows.  A wave
+  // without a tile (a short contraction) puts down its zeros, so that all the sums of a row are asked for at once
   static_for<0, R / S::ROWS>([&](auto bc) {
     constexpr int B = decltype(bc)::value;
     const int m = m0 + B * S::ROWS + wave * MINE;
-    typename RowStore<R, R, EPI, MINE, true>::Side side;
-    rs.side(side, m);
+    if constexpr (!EARLY) rs.side(side, m);
     if constexpr (B > 0) __syncthreads();                           // everybody has read the rows before
-    if (wave < nk) {
 #pragma unroll
-      for (int i = 0; i < T; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < S::ROWS / 16; ++j)
-          *reinterpret_cast<f32x4*>(stage + (16 * j + (lane & 15)) * ROWB + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][B * (S::ROWS / 16) + j];
-    }
+      for (int j = 0; j < S::ROWS / 16; ++j)
+        *reinterpret_cast<f32x4*>(stage + (16 * j + (lane & 15)) * ROWB + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][B * (S::ROWS / 16) + j];
     __syncthreads();
     rs.finish(side, smem + wave * MINE * ROWB, m);
   });
