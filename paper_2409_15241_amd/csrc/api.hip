@@ -585,9 +585,9 @@ inline bool merged_wgrads(const Layout& L) { return L.merged; }
 
 enum { WG_DOWN = 0, WG_UP, WG_OUT, WG_QKV, NWGRADS };
 
-// the weight gradients of the n matrices in `which` (and before them the column sums behind the biases of the same
-// products), on `st`: one launch for all of them (`parts`: memory for the sums of L.wsplits contraction ranges, or NULL
-// for one range); with cfg->wgrad_per_slice one per matrix and slice, in slice order.  `tail`: a Norm1 backward is held back
+// the weight gradients of the n matrices in `which` and the column sums behind the biases of the same
+// products, on `st`: one launch for all of them (`parts`: memory for the sums of L.wsplits contraction ranges, or NULL
+// for one range); with cfg->wgrad_per_slice one per matrix and slice, in slice order, behind one per column sum.  `tail`: a Norm1 backward is held back
 // for that one launch (HeldTail)
 int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, const int* which, int n, hipStream_t st, float* parts, bool tail) {
   const char* sv = static_cast<const char*>(B.saved);
@@ -597,6 +597,13 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
     {PC_WGRAD_UP, sv + L.ln2, L.h, gb.d_pre, L.upc, G->w_up, L.h, L.upc, AREA_BUP},
     {PC_WGRAD_OUT, sv + L.ctx, L.hl, gb.dx1, L.h, G->w_o, L.hl, L.h, -1},
     {PC_WGRAD_QKV, sv + L.ln1, L.h, gb.dqkv, 3 * L.hl, G->w_qkv, L.h, 3 * L.hl, AREA_BQKV}};
+  struct Close { ~Close() { t_tail.open = false; } } close;      // nothing stays held back, whatever fails
+  bool sums = false;
+  for (int m = 0; m < n; ++m) sums |= !L.llama && tab[which[m]].bias >= 0;
+  // with one row group the column sums are further workgroups of the weight gradients' launch (see gemm_tail_kernel of gemm.hip; with
+  // two, where the chip is full, a 13B block's step is 0.5 % faster with launches of their own, 2029 and 2038 us)
+  const bool held = tail || (sums && !L.per_slice && L.groups == 1);
+  if (held && !tail) t_tail = HeldTail{NormBwdArgs{}, {}, 0, st, true};
   for (int m = 0; m < n; ++m) {
     const auto& w = tab[which[m]];
     if (!L.llama && w.bias >= 0)
@@ -618,7 +625,7 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
       a.beside = L.beside;
       if (parts) { a.splits = L.wsplits; a.split_ws = parts; }
       a.join = join ? 1 : 0;
-      a.tail = tail ? 1 : 0;
+      a.tail = held ? 1 : 0;
       LAUNCH(gemm_launch(GEMM_TN, EPI_ACC_F32, a, -1, st), "weight gradient");
     }
   }

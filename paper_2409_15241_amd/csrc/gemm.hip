@@ -811,11 +811,12 @@ void gemm_group_kernel(const GemmGroup p) {
   gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI>(p);
 }
 
-// ... and with what else a small block's backward ends with: the Norm1 backward's workgroups behind the tiles, then those of
+// ... and with further workgroups behind the tiles: in a small block those of the Norm1 backward, then in any block those of
 // the bias gradients (four waves each, two to a workgroup of eight).  A dependent launch costs such a block some 4 us whatever it does, and
 // its products leave part of the chip idle (forward + backward, us, apart and joined: 256 tokens of a 256-wide block 82 and 73, 1024
 // of a 1024-wide one 128 and 117, 4096 of it 241 and 230, 8192 403 and 394, 400 of a Llama one 129 and 125; 256 of a 2048-wide one
-// 128 and 120, 2000 of it 228 and 216, 4000 355 and 348).
+// 128 and 120, 2000 of it 228 and 216, 4000 355 and 348; the bias gradients alone: 6018 tokens of the 2.7B shard, whose 224 tiles leave 32
+// compute units to them, 626 and 613, 16384 of it 1432 and 1420, 2048 of 13B 650 and 647).
 struct GemmTail { HeldTail t; int tiles, norm_blocks, sum_items[COLSUM_MAX_HELD]; };      // workgroups of the tiles and of the norm; column blocks x ranges
 template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
 __global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
@@ -880,7 +881,7 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int NT = gemm_threads(BM, BN, WM, WN);
   constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : ring_bytes(BM, BN);
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
-  if (n > 1 || products[0].splits > 1) {
+  if (n > 1 || products[0].splits > 1 || products[0].tail) {
     if constexpr (EPI == EPI_ACC_F32 && !(BM == 128 && BN == 256)) {      // (the rule, which alone forms groups, never picks 128x256)
       auto kern = gemm_group_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
       static LdsLimitOnce lds_limit;      // one per instantiation
@@ -916,8 +917,8 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
         GemmTail tail{};
         tail.t = t_tail;
         t_tail.open = false;
-        tail.tiles = (int)grid(T).x;
-        tail.norm_blocks = tail.t.norm.slice_blocks * (tail.t.norm.rows / tail.t.norm.slice_rows);
+        tail.tiles = (int)grid(T * grp.splits).x;
+        tail.norm_blocks = tail.t.norm.rows ? tail.t.norm.slice_blocks * (tail.t.norm.rows / tail.t.norm.slice_rows) : 0;
         for (int k = 0; k < tail.t.nsums; ++k) tail.sum_items[k] = (tail.t.sums[k].n / 8 + 63) / 64 * COLSUM_PARTS;
         constexpr int QUADS = NT / 256;
         const int sums = (tail.sum_items[0] + tail.sum_items[1] + QUADS - 1) / QUADS;
@@ -925,9 +926,9 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
         static LdsLimitOnce tail_limit;
         if (hipError_t e = tail_limit.ensure(reinterpret_cast<const void*>(both), LDS); e != hipSuccess) return e;
         hipLaunchKernelGGL(both, dim3(tail.tiles + tail.norm_blocks + sums), dim3(NT), LDS, stream, grp, tail);
-        return hipGetLastError();
+      } else {
+        hipLaunchKernelGGL(kern, grid(T * grp.splits), dim3(NT), LDS, stream, grp);
       }
-      hipLaunchKernelGGL(kern, grid(T * grp.splits), dim3(NT), LDS, stream, grp);
       if (hipError_t e = hipGetLastError(); e != hipSuccess || grp.splits == 1) return e;
       hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((at / 4 + 255) / 256)), dim3(256), 0, stream, sum);
       return hipGetLastError();
@@ -985,9 +986,10 @@ hipError_t gemm_launch(int layout, int epi, const GemmArgs& a0, int tile_cfg, hi
     a = g_held; n = g_nheld; g_nheld = 0;
   }
   if (tile_cfg < 0) tile_cfg = gemm_pick_form(a, n, epi, a->concurrency);
-  if (a0.tail) {      // what is held has to fit the launch: four waves or more a workgroup, one range, the kernel's form of the norm
+  if (a0.tail) {      // a norm that is held has to fit the launch: four waves or more a workgroup, one range, the kernel's form of it
     const NormBwdArgs& norm = t_tail.norm;
-    if (!t_tail.open || t_tail.stream != stream || n < 2 || a->splits > 1 || norm.h > HeldTail::MAX_H || norm.part_dres || norm_streams(norm.rows, norm.h)) {
+    const bool norm_fits = norm.rows == 0 || (a->splits <= 1 && norm.h <= HeldTail::MAX_H && !norm.part_dres && !norm_streams(norm.rows, norm.h));
+    if (!t_tail.open || t_tail.stream != stream || layout != GEMM_TN || !norm_fits) {
       t_tail.open = false;
       return hipErrorInvalidValue;
     }

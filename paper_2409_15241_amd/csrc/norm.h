@@ -41,10 +41,10 @@ struct NormBwdArgs {
   int join;               // 1: held back for the weight gradients' launch (see HeldTail)
 };
 
-// What a small block's backward ends with, next to its weight gradients: the Norm1 backward and the bias gradients' first
-// stages.  None of them reads what another writes, so they can be one launch (GemmArgs::tail): a Norm1 backward with `join` is held
-// back (per thread) with the column sums that follow it on the same stream, until the weight gradients of that stream are
-// launched with `tail` set.
+// What goes into the launch of weight gradients besides their tiles: the first stages of the bias gradients, and in a small block
+// the Norm1 backward that it ends with.  None of them reads what another writes, so they can be one launch (GemmArgs::tail): column sums
+// that follow on the same stream, behind a Norm1 backward with `join` or without one (norm.rows 0), are held back (per thread) until
+// the weight gradients of that stream are launched with `tail` set.
 struct ColsumPartial { const void* g; long ld; int rows, n; float* part; };
 constexpr int COLSUM_MAX_HELD = 2;
 struct HeldTail {
