@@ -447,9 +447,10 @@ Rows rows_of(const Layout& L, int g) {
 }
 
 // Forward of one block (Sec. 3.2, Eq. 3): each step of the block for one row group after the other, every group on its
-// own stream.  Of the two row-cut products (Sec. 3.3, Eq. 4), whose column pieces are written in place into the
-// full-width buffers, the MLP's pieces are one launch, and the out-projection's too when one group holds all rows: a
-// piece is a unit of reduction, and inside a call none is handed out.
+// own stream.  The column pieces of each of the two row-cut products (Sec. 3.3, Eq. 4), written in place into the
+// full-width buffers, are one launch: a piece is a unit of reduction, and inside a call none is handed out.  (With two groups the
+// out-projection's once were a launch each, 26 us of which a third filled and drained the chip: 13B 2062 us, 2045 in one, 30B
+// forward 1266 and 1256, Llama-2 13B 4181 and 4170, Llama-2 7B with 16 x 1024 tokens level.)
 // `norm1_done`: the block's Norm1 has already been written (by the block below, see `next`).
 // `next`: the block above in a stack; its Norm1 is then taken in the same pass that forms this block's output.
 int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& S, const FwdLayer& B,
@@ -507,15 +508,10 @@ int enqueue_fwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
       LAUNCH(attention_fwd_launch(a, st), "attention forward");
       return DOMINO_OK;
     }));
-    const int pieces = L.groups > 1 ? L.q : 1;
-    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F4: (XA) * B_j
-      for (int j = 0; j < pieces; ++j) {
-        ProfScope ps(PC_GEMM_OUT, st);
-        const int n = L.h / pieces;
-        const size_t cj = (size_t)j * n * 2;
-        GemmArgs a = gemm_args(ctx(R), L.hl, at(P->w_o, cj), L.h, at(B.attn_partial, R.rh + cj), L.h, R.n, n, L.hl);
-        LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "out-projection");
-      }
+    TRY(each_group([&](const Rows& R, hipStream_t st) -> int {  // F4: (XA) * B_j, all column pieces
+      ProfScope ps(PC_GEMM_OUT, st);
+      GemmArgs a = gemm_args(ctx(R), L.hl, P->w_o, L.h, at(B.attn_partial, R.rh), L.h, R.n, L.h, L.hl);
+      LAUNCH(gemm_launch(GEMM_NN, EPI_STORE, a, -1, st), "out-projection");
       return DOMINO_OK;
     }));                                                    // column synchronisation before Norm2: stream order
   }
