@@ -119,8 +119,9 @@ bool wgrads_beside(const Layout& l) {
 // queues that a process gets by default, and slices that meet on a queue run one after the other), and only pays in
 // wide blocks where a group's launches fill the chip on their own (two groups and one beside a side stream, us: Llama-2 7B
 // with 16384 tokens, 1024 tiles, 2571 and 2691; with 8192, 512 tiles, 1384 and 1415; with 4096, 256 tiles, 823 and 781; 13B with
-// 4096 tokens, 320 tiles, 1134 and 1062; with 2048, 765 and 653.  Level to 1 %: 13B with 8192 tokens, 640 tiles, 2035 and 2019,
-// 30B, 896 tiles, 3521 and 3542, Llama-2 13B with 16384, 1280 tiles, 4172 and 4234.)
+// 4096 tokens, 320 tiles, 1134 and 1062; with 2048, 765 and 653.  13B with 8192 tokens, 640 tiles, 2030 and 2061, four such
+// blocks in a stack 7980 and 8150, one in parts 2132 and 2078; 30B, 896 tiles, 3521 and 3542, forward 1242 and 1254; Llama-2 13B with 16384,
+// 1280 tiles, 4172 and 4234.)
 int row_groups(const Layout& l) { return l.p > 2 && wgrads_beside(l) && tiles256(l.M, l.h) >= 512 ? 2 : 1; }
 
 int validate(const domino_cfg* c, Layout* L) {
