@@ -320,8 +320,9 @@ int domino_mfma_probe(const void* a, const void* b, float* out, int blocks, int 
 
 /* While enabled, every step of a layer or stack call is bracketed by a pair of timing events on its own stream where it
  * is launched; nothing else about the call changes.  A step launched together with others is timed with them: the weight
- * gradients of several matrices in one launch are the class "wgrad_joined", those of one matrix their own class; the block
- * output is part of "gemm_down" where that product forms it, "residual_out" where it is a pass of its own (two row groups, and
+ * gradients of several matrices in one launch are the class "wgrad_joined", those of one matrix their own class; with one row
+ * group the first stage of the bias gradients of QKV and MLP-up ("colsum" elsewhere), and in a small block the Norm1 backward
+ * ("norm_bwd" elsewhere), are part of the launch of weight gradients that takes them along; the block output is part of "gemm_down" where that product forms it, "residual_out" where it is a pass of its own (two row groups, and
  * some sizes with one), and "norm_fwd" where it is formed together with the next block's Norm1.
  * domino_profile_read() synchronises the events and returns, for step class `cls` (0 .. domino_profile_classes()-1), the
  * summed elapsed milliseconds and the launch count since the last domino_profile_reset().  Costs two event records per

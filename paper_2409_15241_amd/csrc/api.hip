@@ -281,7 +281,7 @@ int prof_event(hipEvent_t* ev) {
 }
 
 // RAII bracket around the launches of one step on one stream; launches = false: the step only hands work over to a later
-// launch (GemmArgs::join, ColsumJobs::join), which has the bracket
+// launch (GemmArgs::join, ColsumJobs::join, HeldTail), which has the bracket
 struct ProfScope {
   int cls; hipStream_t st; hipEvent_t start{}, stop{}; bool live = false;
   ProfScope(int c, hipStream_t s, bool launches = true) : cls(c), st(s) {
@@ -600,13 +600,14 @@ int weight_gradients(const Layout& L, const GradBufs& gb, const BwdLayer& B, con
   // with one row group the column sums are further workgroups of the weight gradients' launch (see gemm_tail_kernel of gemm.hip; with
   // two, where the chip is full, a 13B block's step is 0.5 % faster with launches of their own, 2029 and 2038 us)
   const bool held = tail || (sums && !L.per_slice && L.groups == 1);
+  static_assert(COLSUM_MAX_HELD >= 2, "one group has a column sum for QKV and one for MLP-up, and both are held");
   if (held && !tail) t_tail = HeldTail{NormBwdArgs{}, {}, 0, st, true};
   for (int m = 0; m < n; ++m) {
     const auto& w = tab[which[m]];
     if (!L.llama && w.bias >= 0)
       for (int g = 0; g < L.groups; ++g) {
         const Rows R = rows_of(L, g);
-        ProfScope ps(PC_COLSUM, st);
+        ProfScope ps(PC_COLSUM, st, !held);
         LAUNCH(colsum_partial_launch(at(w.Bm, R.r0 * w.ldb * 2), w.ldb, R.n, w.N, B.red + L.area(w.bias, g), st), "bias gradient");
       }
   }
@@ -753,7 +754,7 @@ int enqueue_bwd_block(const Layout& L, const domino_cfg* cfg, const StreamPlan& 
 
   auto norm_bwd = [&](const Rows& R, hipStream_t st, const void* ga, const void* gb2, const void* xin, const void* gamma, size_t mean,
                       size_t rstd, const void* dres, void* out, int kg, int kb, int kres, int kdx, bool join = false) -> int {
-    ProfScope ps(PC_NORM_BWD, st);
+    ProfScope ps(PC_NORM_BWD, st, !join);
     NormBwdArgs a{};
     a.ga = ga; a.gb = gb2; a.x = xin; a.gamma = gamma; a.mean = rowf(mean, R); a.rstd = rowf(rstd, R); a.dres = dres; a.dx = out;
     a.part_g = B.red + L.area(kg, R.slice); a.part_b = B.red + L.area(kb, R.slice); a.rows = R.n; a.h = L.h; a.rms = rms;

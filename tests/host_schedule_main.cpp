@@ -11,7 +11,9 @@
 //   - the vector gradients sum partial rows that were written in this backward, and no launch writes over another's;
 //   - over the parts of one backward every gradient is formed exactly once, whatever pool each part is handed and whichever
 //     of them are captured or timed launch by launch;
-//   - timing a step launch by launch changes none of its launches, and times each under its own step's name;
+//   - timing a step launch by launch changes none of its launches, and times each under its own step's name, what is held
+//     back for a later launch with that launch;
+//   - no call returns with work still held back;
 //   - a captured call uses no event twice, and pools outside domino_capture_supported() are refused while capturing.
 // Nothing here touches a GPU.  Exit status 0 = every expectation held.
 #include <algorithm>
@@ -36,6 +38,7 @@
 // ------------------------------------------------------------------------------------------- the recorded schedule
 struct Region {                      // rows x cols elements of `esz` bytes, `ld` elements from row to row
   const char* base; long ld; long rows, cols; int esz; bool write;
+  enum Rows { PLAIN, NORM_SUMS, COLUMN_SUMS } partial = PLAIN;      // partial rows of vector gradients, and what leaves them
 };
 struct Op {
   enum Kind { LAUNCH, RECORD, WAIT } kind;
@@ -68,6 +71,11 @@ static std::string g_case;
 
 static Region reg(const void* p, long ld, long rows, long cols, int esz, bool write) {
   return Region{static_cast<const char*>(p), ld, rows, cols, esz, write};
+}
+static Region partial_rows(Region::Rows kind, const void* p, long rows, long cols) {
+  Region r = reg(p, cols, rows, cols, 4, true);
+  r.partial = kind;
+  return r;
 }
 static void launch(hipStream_t st, const char* what, std::vector<Region> r, std::vector<Op::Product> products = {}, bool vec = false) {
   Op o;
@@ -107,10 +115,30 @@ static const char* gemm_name(int layout, int epi) {
   if (layout == GEMM_NT) return epi == EPI_STORE ? "dgrad" : "dgrad+act'";
   return epi == EPI_STORE ? "gemm" : epi == EPI_ROPE ? "gemm+rope" : "gemm+act";
 }
+int norm_bwd_blocks(int rows) {
+  const int want = (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
+  return want < NORM_BWD_MAX_BLOCKS ? want : NORM_BWD_MAX_BLOCKS;
+}
+static std::vector<Region> norm_bwd_regions(const NormBwdArgs& a) {
+  // one partial row per workgroup: slice_blocks of them for each slice
+  const int slice_rows = a.slice_rows > 0 ? a.slice_rows : a.rows;
+  const long nb = (long)(a.slice_blocks > 0 ? a.slice_blocks : norm_bwd_blocks(slice_rows)) * (a.rows / slice_rows);
+  std::vector<Region> r = {reg(a.ga, a.h, a.rows, a.h, 2, false), reg(a.gb, a.h, a.rows, a.h, 2, false),
+                           reg(a.x, a.h, a.rows, a.h, 2, false), reg(a.dres, a.h, a.rows, a.h, 2, false),
+                           reg(a.mean, a.rows, 1, a.rows, 4, false), reg(a.rstd, a.rows, 1, a.rows, 4, false),
+                           reg(a.dx, a.h, a.rows, a.h, 2, true)};
+  for (float* part : {a.part_g, a.part_b, a.part_dres, a.part_dx}) r.push_back(partial_rows(Region::NORM_SUMS, part, nb, a.h));
+  return r;
+}
+static std::vector<Region> colsum_regions(const ColsumPartial& c) {
+  return {reg(c.g, c.ld, c.rows, c.n, 2, false), partial_rows(Region::COLUMN_SUMS, c.part, COLSUM_PARTS, c.n)};
+}
+
 // products held back by GemmArgs::join, and the stream of the first
 static std::vector<GemmArgs> g_held;
 static hipStream_t g_held_on;
 static long g_range_launches = 0;     // launches over several contraction ranges, in all cases
+static long g_norm_joins = 0, g_sum_joins = 0;      // Norm1 backwards and column sums launched with weight gradients, in all cases
 static hipError_t launch_weight_gradients(const std::vector<GemmArgs>& held, hipStream_t st) {
   std::vector<Region> r, sums;
   std::vector<Op::Product> products;
@@ -123,6 +151,20 @@ static hipError_t launch_weight_gradients(const std::vector<GemmArgs>& held, hip
     (splits > 1 ? sums : r).push_back(reg(a.C, a.ldc, a.M, a.N, 4, true));
     products.push_back({static_cast<float*>(a.C), static_cast<const char*>(a.A), a.K, a.beta});
     EXPECT(a.K == held[0].K && a.beta == held[0].beta && a.splits == held[0].splits, "products of one launch differ in depth, ranges or accumulation");
+    EXPECT(a.tail == held[0].tail, "products of one launch differ in what is launched with them");
+  }
+  if (held[0].tail) {                  // what t_tail holds: further workgroups of this launch
+    EXPECT(t_tail.open && t_tail.stream == st, "weight gradients are launched with work that is not held back for their stream");
+    const NormBwdArgs& norm = t_tail.norm;
+    if (norm.rows) {
+      EXPECT(splits == 1 && norm.h <= HeldTail::MAX_H && !norm.part_dres && !norm_streams(norm.rows, norm.h), "a norm is held back for a launch that does not take it");
+      for (const Region& x : norm_bwd_regions(norm)) r.push_back(x);
+      ++g_norm_joins;
+    }
+    EXPECT(norm.rows || t_tail.nsums, "nothing is held back for a launch");
+    for (int k = 0; k < t_tail.nsums; ++k, ++g_sum_joins)
+      for (const Region& x : colsum_regions(t_tail.sums[k])) r.push_back(x);
+    t_tail.open = false;
   }
   if (splits == 1) { launch(st, "wgrad", r, products); return hipSuccess; }
   ++g_range_launches;
@@ -169,10 +211,6 @@ hipError_t rope_launch(void* m, long ld, int rows, int, int col0, int nblocks, i
   launch(st, "rope", {reg(static_cast<char*>(m) + 2L * col0, ld, rows, (long)nblocks * heads * d, 2, true)});
   return hipSuccess;
 }
-int norm_bwd_blocks(int rows) {
-  const int want = (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS;
-  return want < NORM_BWD_MAX_BLOCKS ? want : NORM_BWD_MAX_BLOCKS;
-}
 hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st) {
   launch(st, "norm_fwd", {reg(a.x, a.h, a.rows, a.h, 2, false), reg(a.add1, a.h, a.rows, a.h, 2, false),
                           reg(a.add2, a.h, a.rows, a.h, 2, false), reg(a.xsum, a.h, a.rows, a.h, 2, true),
@@ -181,15 +219,12 @@ hipError_t norm_fwd_launch(const NormFwdArgs& a, hipStream_t st) {
   return hipSuccess;
 }
 hipError_t norm_bwd_launch(const NormBwdArgs& a, hipStream_t st) {
-  // one partial row per workgroup: slice_blocks of them for each slice
-  const int slice_rows = a.slice_rows > 0 ? a.slice_rows : a.rows;
-  const long nb = (long)(a.slice_blocks > 0 ? a.slice_blocks : norm_bwd_blocks(slice_rows)) * (a.rows / slice_rows);
-  launch(st, "norm_bwd", {reg(a.ga, a.h, a.rows, a.h, 2, false), reg(a.gb, a.h, a.rows, a.h, 2, false),
-                          reg(a.x, a.h, a.rows, a.h, 2, false), reg(a.dres, a.h, a.rows, a.h, 2, false),
-                          reg(a.mean, a.rows, 1, a.rows, 4, false), reg(a.rstd, a.rows, 1, a.rows, 4, false),
-                          reg(a.dx, a.h, a.rows, a.h, 2, true), reg(a.part_g, a.h, nb, a.h, 4, true),
-                          reg(a.part_b, a.h, nb, a.h, 4, true), reg(a.part_dres, a.h, nb, a.h, 4, true),
-                          reg(a.part_dx, a.h, nb, a.h, 4, true)});
+  if (a.join) {
+    EXPECT(!t_tail.open, "a norm is held back over another");
+    t_tail = HeldTail{a, {}, 0, st, true};
+    return hipSuccess;
+  }
+  launch(st, "norm_bwd", norm_bwd_regions(a));
   return hipSuccess;
 }
 hipError_t attention_fwd_launch(const AttnArgs& a, hipStream_t st) {
@@ -210,7 +245,12 @@ hipError_t attention_bwd_launch(const AttnArgs& a, hipStream_t st) {
   return hipSuccess;
 }
 hipError_t colsum_partial_launch(const void* g, long ld, int rows, int n, float* part, hipStream_t st) {
-  launch(st, "colsum_partial", {reg(g, ld, rows, n, 2, false), reg(part, n, COLSUM_PARTS, n, 4, true)});
+  const ColsumPartial c{g, ld, rows, n, part};
+  if (t_tail.open && t_tail.stream == st && t_tail.nsums < COLSUM_MAX_HELD) {
+    t_tail.sums[t_tail.nsums++] = c;
+    return hipSuccess;
+  }
+  launch(st, "colsum_partial", colsum_regions(c));
   return hipSuccess;
 }
 // jobs held back by ColsumJobs::join, and their stream
@@ -305,14 +345,13 @@ static void check_partial_rows(int first) {
   for (int i = first; i < (int)g_ops.size(); ++i) {
     const Op& o = g_ops[i];
     if (o.kind != Op::LAUNCH) continue;
-    if (o.what == "norm_bwd" || o.what == "colsum_partial")
-      for (const Region& r : o.regions)
-        if (r.write && r.esz == 4) {
-          const auto w = range(r);
-          for (const auto& v : written)
-            EXPECT(w.second <= v.first || v.second <= w.first, "launch %d (%s) writes over partial rows of another launch", i, o.what.c_str());
-          written.push_back(w);
-        }
+    for (const Region& r : o.regions)
+      if (r.partial != Region::PLAIN) {
+        const auto w = range(r);
+        for (const auto& v : written)
+          EXPECT(w.second <= v.first || v.second <= w.first, "launch %d (%s) writes over partial rows of another", i, o.what.c_str());
+        written.push_back(w);
+      }
     if (!o.vec_reduce) continue;
     for (const Region& r : o.regions) {
       if (r.write) continue;
@@ -330,6 +369,7 @@ static void check_partial_rows(int first) {
 // one library call = operations [first, end) of g_ops
 static void check_call(int first, hipStream_t s0, int p, bool capturing) {
   const int n = (int)g_ops.size();
+  EXPECT(!t_tail.open && g_held.empty() && g_jobs.empty(), "the call returns with work still held back");
   if (first == n) return;
   const Analysis A = analyse(g_ops, first);
   int origin = -1, last0 = -1;
@@ -610,12 +650,13 @@ static int run_mixed_parts(int arch, int p, int accumulate) {
         for (size_t r = 0; o.vec_reduce && r < o.regions.size(); ++r)
           if (o.regions[r].write && o.regions[r].base == reinterpret_cast<const char*>(vecs[v]))
             for (size_t k = r + 1; k < o.regions.size() && !o.regions[k].write; ++k) ++summed;
-      const bool by_group = v == 4 || v == 6;          // column sums: as many sets as launches that made them
+      const bool by_group = v == 4 || v == 6;          // column sums: as many sets as were made
       long want = p;
       if (by_group) {
         want = 0;
         for (const Op& o : g_ops)
-          if (o.what == "colsum_partial" && o.regions[0].cols == (v == 4 ? 3L * c.hidden / c.tp : (long)c.ffn / c.tp)) ++want;
+          for (const Region& r : o.regions)
+            if (r.partial == Region::COLUMN_SUMS && r.cols == (v == 4 ? 3L * c.hidden / c.tp : (long)c.ffn / c.tp)) ++want;
       }
       EXPECT(summed == want, "%s takes in %ld sets of partial rows of %ld over the three parts", names[v], summed, want);
     }
@@ -765,6 +806,7 @@ int main() {
       for (int p : {1, 2, 4, 8})
         for (int ns : {1, 2, 4}) { g_size = size; run_timed(arch, p, ns); ++cases; }
   EXPECT(g_range_launches > 0, "no case formed its weight gradients over several contraction ranges");
+  EXPECT(g_norm_joins > 0 && g_sum_joins > 0, "no case launched a Norm1 backward (%ld) or column sums (%ld) with its weight gradients", g_norm_joins, g_sum_joins);
   // the check must be able to fail: two launches on different fake streams that write one buffer, no event between them
   {
     g_case = "planted race";
@@ -796,7 +838,7 @@ int main() {
     // the check of partial rows must be able to fail, too: a reduction of four rows where three were written
     g_ops.clear();
     const int had = g_failures;
-    launch(a, "colsum_partial", {reg(buf, 16, 3, 16, 4, true)});
+    launch(a, "colsum_partial", {partial_rows(Region::COLUMN_SUMS, buf, 3, 16)});
     launch(a, "vector_gradients", {reg(buf + 2048, 16, 1, 16, 4, true), reg(buf, 16, 4, 16, 4, false)}, {}, true);
     std::printf("(the next FAILED line is the planted unwritten row being found)\n");
     check_partial_rows(0);
