@@ -5,7 +5,8 @@
 //   - every stream other than streams[0] enters a call by waiting for an event recorded in that call (under HIP graph
 //     capture this is how a stream joins the capture), and no wait refers to an event not yet recorded in the call;
 //   - any two launches that touch overlapping memory, at least one of them writing, are ordered by stream order or by
-//     a chain of events (the race check), over the buffers the launchers are handed;
+//     a chain of events (the race check), over the buffers the launchers are handed; where products, a norm and column sums
+//     share a launch, no two of these do;
 //   - the weight gradients of a matrix, and the reductions of the vector gradients, are one launch over all rows, or
 //     enqueued in slice order and ordered one after the other (the fixed accumulation order);
 //   - the vector gradients sum partial rows that were written in this backward, and no launch writes over another's;
@@ -39,6 +40,7 @@
 struct Region {                      // rows x cols elements of `esz` bytes, `ld` elements from row to row
   const char* base; long ld; long rows, cols; int esz; bool write;
   enum Rows { PLAIN, NORM_SUMS, COLUMN_SUMS } partial = PLAIN;      // partial rows of vector gradients, and what leaves them
+  int job = 0;                       // which of the products, norms and sums that share a launch touches it: these run side by side
 };
 struct Op {
   enum Kind { LAUNCH, RECORD, WAIT } kind;
@@ -145,10 +147,13 @@ static hipError_t launch_weight_gradients(const std::vector<GemmArgs>& held, hip
   const int splits = held[0].splits > 1 ? held[0].splits : 1;
   long floats = 0;
   for (const GemmArgs& a : held) floats += (long)a.M * a.N;
+  int job = 0;
+  auto touch = [&](std::vector<Region>& to, Region x) { x.job = job; to.push_back(x); };
   for (const GemmArgs& a : held) {
-    r.push_back(reg(a.A, a.lda, a.K, a.M, 2, false));
-    r.push_back(reg(a.B, a.ldb, a.K, a.N, 2, false));
-    (splits > 1 ? sums : r).push_back(reg(a.C, a.ldc, a.M, a.N, 4, true));
+    ++job;
+    touch(r, reg(a.A, a.lda, a.K, a.M, 2, false));
+    touch(r, reg(a.B, a.ldb, a.K, a.N, 2, false));
+    touch(splits > 1 ? sums : r, reg(a.C, a.ldc, a.M, a.N, 4, true));
     products.push_back({static_cast<float*>(a.C), static_cast<const char*>(a.A), a.K, a.beta});
     EXPECT(a.K == held[0].K && a.beta == held[0].beta && a.splits == held[0].splits, "products of one launch differ in depth, ranges or accumulation");
     EXPECT(a.tail == held[0].tail, "products of one launch differ in what is launched with them");
@@ -158,12 +163,15 @@ static hipError_t launch_weight_gradients(const std::vector<GemmArgs>& held, hip
     const NormBwdArgs& norm = t_tail.norm;
     if (norm.rows) {
       EXPECT(splits == 1 && norm.h <= HeldTail::MAX_H && !norm.part_dres && !norm_streams(norm.rows, norm.h), "a norm is held back for a launch that does not take it");
-      for (const Region& x : norm_bwd_regions(norm)) r.push_back(x);
+      ++job;
+      for (const Region& x : norm_bwd_regions(norm)) touch(r, x);
       ++g_norm_joins;
     }
     EXPECT(norm.rows || t_tail.nsums, "nothing is held back for a launch");
-    for (int k = 0; k < t_tail.nsums; ++k, ++g_sum_joins)
-      for (const Region& x : colsum_regions(t_tail.sums[k])) r.push_back(x);
+    for (int k = 0; k < t_tail.nsums; ++k, ++g_sum_joins) {
+      ++job;
+      for (const Region& x : colsum_regions(t_tail.sums[k])) touch(r, x);
+    }
     t_tail.open = false;
   }
   if (splits == 1) { launch(st, "wgrad", r, products); return hipSuccess; }
@@ -409,6 +417,13 @@ static void check_call(int first, hipStream_t s0, int p, bool capturing) {
           }
     next_pair:;
     }
+  for (int i : L) {                  // ... and inside a launch, between the jobs that share it
+    const std::vector<Region>& r = g_ops[i].regions;
+    bool clash = false;
+    for (size_t x = 0; x < r.size(); ++x)
+      for (size_t y = x + 1; y < r.size(); ++y) clash |= r[x].job != r[y].job && (r[x].write || r[y].write) && overlap(r[x], r[y]);
+    EXPECT(!clash, "two jobs of launch %d (%s) touch the same memory", i, g_ops[i].what.c_str());
+  }
   // fixed accumulation order: per matrix, and for the vector gradients, enqueue order = slice order, each ordered after the one before
   std::map<const void*, std::vector<int>> per_matrix, per_vector;     // keyed by the gradient tensor (one set per block of a stack)
   for (int i : L) {
@@ -835,6 +850,16 @@ int main() {
     (void)hipEventRecord(e, b);
     (void)hipStreamWaitEvent(a, e, 0);
     check_call(0, a, 1, false);
+    // two jobs of one launch, the second writing a row that the first reads
+    g_ops.clear();
+    const int jobs_before = g_failures;
+    Region second = reg(buf + 2 * 64 * 2, 64, 1, 64, 2, true);
+    second.job = 1;
+    launch(a, "wgrad", {reg(buf, 64, 8, 64, 2, false), second});
+    std::printf("(the next FAILED line is the planted clash inside a launch being found)\n");
+    check_call(0, a, 1, false);
+    if (g_failures == jobs_before + 1) g_failures = jobs_before;
+    else { std::printf("the race check did not find the planted clash inside a launch\n"); ++g_failures; }
     // the check of partial rows must be able to fail, too: a reduction of four rows where three were written
     g_ops.clear();
     const int had = g_failures;

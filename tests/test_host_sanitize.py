@@ -73,5 +73,6 @@ def test_every_schedule_the_library_enqueues_is_ordered_and_race_free(tmp_path, 
     r = subprocess.run([exe], capture_output=True, text=True, env=ENV, timeout=300)
     out = r.stdout + r.stderr
     assert r.returncode == 0 and "host schedule driver: ok" in r.stdout, out[-4000:]
-    assert "planted race" in r.stdout and "planted unwritten row" in r.stdout       # the checks showed that they can fail
+    for planted in ("planted race", "planted clash inside a launch", "planted unwritten row"):      # the checks showed that they can fail
+        assert planted in r.stdout
     assert "runtime error" not in out and "AddressSanitizer" not in out, out[-3000:]
