@@ -39,5 +39,12 @@ inline bool attention_split_pays(const AttnArgs& a, bool backward) {
 // 15.3 and 16.3, 2 x 1024, two 20.7 and 25.4, 4096, two 62 and 90.
 inline bool attention_owns_d(int seq) { return seq <= 256; }
 
+// How the 128-position forward walks a view of K or V: `left` bytes from a tile's first row to the end of the last row needed, tiles
+// of 64 rows of `ld` values.  A matrix is smaller than 2 GiB, 64 rows of it need not be (few rows of more than 2^24 values): such a tile
+// is the last, whatever its size.  No sum or difference here leaves 31 bits.
+constexpr int attention_view_bytes(int rows, int ld, int head_dim) { return ((rows - 1) * ld + head_dim) * 2; }
+constexpr int attention_tile_bytes(long ld) { return ld < 1L << 24 ? (int)(64 * ld * 2) : 0x7fffffff; }
+constexpr int attention_left_behind(int left, int tile_bytes) { return left > tile_bytes ? left - tile_bytes : 0; }
+
 hipError_t attention_fwd_launch(const AttnArgs& a, hipStream_t st);
 hipError_t attention_bwd_launch(const AttnArgs& a, hipStream_t st);

@@ -539,16 +539,16 @@ DEV void attn_fwd_body(const AttnArgs& p, uint8_t* smem) {
   for (int c = 0; c < DS; ++c) at_k[c] = c * 32 + ldK.kofs < D ? ldK.base[0] + c * 64 : BUF_OOB;
 #pragma unroll
   for (int i = 0; i < 4; ++i) at_v[i] = ldV.base[i & 1] + (uint32_t)((i >> 1) * 32) * (uint32_t)ld * 2u;
-  const int step = 64 * (int)ld * 2;
+  const int step = attention_tile_bytes(ld);
   const char* next_k = reinterpret_cast<const char*>(tok0 + hl + hh * D);
   const char* next_v = reinterpret_cast<const char*>(tok0 + 2 * hl + hh * D);
-  int left_k = ((min(ntiles * 64, s) - 1) * (int)ld + D) * 2, left_v = left_k;
+  int left_k = attention_view_bytes(min(ntiles * 64, s), (int)ld, D), left_v = left_k;
   auto load_k = [&](int c, buf_rsrc rs, int slot) { __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * K_BYTES + c * 4096 + wave * 1024), 16, at_k[c], 0, 0, 0); };
   auto load_v = [&](int i, buf_rsrc rs, int slot) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + 2 * K_BYTES + slot * V_BYTES + (i >> 1) * 8192 + (wave * 2 + (i & 1)) * 1024), 16, at_v[i], 0, 0, 0);
   };
-  auto advance_k = [&] { next_k += step; left_k = max(left_k - step, 0); };
-  auto advance_v = [&] { next_v += step; left_v = max(left_v - step, 0); };
+  auto advance_k = [&] { next_k += step; left_k = attention_left_behind(left_k, step); };
+  auto advance_v = [&] { next_v += step; left_v = attention_left_behind(left_v, step); };
   auto fill_k = [&](int slot) {
     const buf_rsrc rs = make_rsrc(next_k, left_k);
 #pragma unroll

@@ -4,6 +4,9 @@
 //   joined <K> <concurrency> <beside> <ranges> <M N> x 4 [<adds>]   GemmTile of four weight gradients in one launch
 //   output <M> <N> <K>                                    1: the block output in the product's epilogue, 0: a pass
 //   attention <backward> <batch> <seq> <heads>            1: 32 positions per workgroup, 0: 128
+//   walk <seq> <ld> <head_dim> <tiles>                    the furthest byte of a [seq, ld] matrix that the attention forward's views of
+//                                                         one head and that many tiles (and the two asked for ahead) reach, or -1 where
+//                                                         a view is before the matrix
 //   ranges <tiles> <depth> <floats>                       contraction ranges of joined weight gradients
 #include <cstdio>
 #include <cstring>
@@ -33,6 +36,16 @@ int main() {
       AttnArgs a{};
       a.batch = (int)v[1]; a.seq = (int)v[2]; a.heads = (int)v[3];
       std::printf("%d\n", attention_split_pays(a, v[0] != 0) ? 1 : 0);
+    } else if (n == 5 && !std::strcmp(what, "walk")) {
+      const int tile = attention_tile_bytes(v[1]), rows = (int)(v[3] * 64 < v[0] ? v[3] * 64 : v[0]);
+      long at = 0, furthest = 0;
+      int left = attention_view_bytes(rows, (int)v[1], (int)v[2]);
+      bool before = false;
+      for (long k = 0; k < v[3] + 2; ++k, at += tile, left = attention_left_behind(left, tile)) {
+        if (left > 0) furthest = at + left > furthest ? at + left : furthest;
+        before |= left > 0 && at < 0;
+      }
+      std::printf("%ld\n", before ? -1L : furthest);
     } else if (n == 4 && !std::strcmp(what, "ranges")) {
       std::printf("%d\n", gemm_wgrad_splits((int)v[0], (int)v[1], v[2]));
     } else {

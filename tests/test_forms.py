@@ -150,3 +150,15 @@ def test_whether_a_contraction_is_dealt_does_not_depend_on_the_streams(ask):
         assert not dealt(ask([("gemm", e, M, N, K, 1, 1)])[0])
         taken += dealt(forms[0])
     assert 30 < taken < 270
+
+
+def test_views_of_the_attention_forward_stay_inside_the_matrix(ask):
+    """Any row pitch that the entry point takes (a matrix under 2 GiB), also one so wide that 64 rows of it are more than
+    31 bits of bytes: no view begins before the matrix or ends behind the last row that is needed."""
+    shapes = []
+    for ld in (384, 3072, 24576, (1 << 24) - 8, 1 << 24, (1 << 24) + 8, 3 << 23, (1 << 25) + 8, (1 << 26) + 64, (1 << 29) - 8):
+        most = ((1 << 30) - 1) // ld
+        shapes += [(seq, ld, d) for seq in {1, 2, 3, 63, 64, 65, 200, most} if 1 <= seq <= most for d in (64, 80, 128)]
+    reach = ask([("walk", seq, ld, d, (seq + 63) // 64) for seq, ld, d in shapes])
+    for (seq, ld, d), end in zip(shapes, reach):
+        assert end == ((seq - 1) * ld + d) * 2, (seq, ld, d)

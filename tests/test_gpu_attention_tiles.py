@@ -59,3 +59,16 @@ def test_keys_behind_a_query_do_not_reach_it(dom, d, bad):
         ctx2, lse2 = forward(dom, spoiled.reshape(b * s, -1), b, s, nh, d)
         assert torch.equal(ctx2.reshape(b, s, -1)[:, :first], ctx.reshape(b, s, -1)[:, :first])
         assert torch.equal(lse2[:, :, :first], lse[:, :, :first])
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("s,ld", [(1, (1 << 24) + 8), (5, (1 << 24) + 8), (3, (1 << 25) + 64), (7, 1 << 24)])
+def test_rows_so_wide_that_a_tile_of_them_is_over_2_gib(dom, d, s, ld):
+    """64 rows of such a matrix are more than 31 bits of bytes, the few that it has are not: same bits as from a narrow one."""
+    qkv = draw(1, s, 1, d)
+    ctx, lse = forward(dom, qkv, 1, s, 1, d)
+    wide = torch.full((s, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:, :3 * d] = qkv
+    ctx2, lse2 = torch.zeros_like(ctx), torch.zeros_like(lse)
+    dom.domino_attention_fwd(wide, ld, 1, s, 1, d, ctx2, lse2)
+    assert torch.equal(ctx2, ctx) and torch.equal(lse2, lse)
