@@ -33,7 +33,23 @@ inline bool attention_split_pays(const AttnArgs& a, bool backward) {
   return 4.5 + rounds * (1.5 + 1.1 * a.seq / 128) < 0.95 * (5 + 1.17 * steps);
 }
 
-// Whether that form's backward forms D = rowsum(dctx * ctx) itself, where a wave has two tiles of 32 queries or fewer: it saves a dependent launch
+// Whether the 128-position forward takes each tile's scores, softmax and output one after the other (attn_fwd_serial_kernel) and not two
+// tiles at once (attn_fwd_kernel); both give the same bits.  Two at once needs 204 registers for heads of 64, so that a compute unit takes
+// two workgroups where it takes three of the serial form: of 512 < n <= 768 workgroups the last wait for a second round, and in
+// several rounds three that alternate hide a tile's chain as well as two tiles a wave (us, two at once / serial: 256 positions x 308 heads
+// 14.1 / 11.8, 64 x 640 7.5 / 5.8, 1024 x 256 62.0 / 55.1, 4096 x 64 171 / 166; up to 512 workgroups 4096 x 8 48.9 / 59.7, 704 x 64
+// 12.3 / 13.9, but of few tiles, two workgroups to a compute unit, 256 x 256 9.7 / 8.9, 192 x 160 7.0 / 6.8; of 769 to 1024, two rounds either way, 192 x 400 12.3 / 13.4, 1024 x 128 28.4 / 29.5, but 512 x 200 19.1 / 17.3).  Heads of
+// 80 and 128 take two workgroups in either form, and one tile leaves nothing to overlap (64 positions: 256 heads of 64 4.4 / 4.2, of 80
+// 4.9 / 4.7, 512 of 128 8.3 / 7.8); heads of 128 of two tiles, two workgroups to some compute units, 128 x 308 11.5 / 10.8, 100 x 400
+// 10.7 / 10.1, but x 256 level and x 160 6.9 / 7.2.
+inline bool attention_fwd_serial(const AttnArgs& a) {
+  const long wgs = (long)((a.seq + 127) / 128) * a.heads * a.batch;
+  if (a.seq <= 64) return true;
+  if (a.head_dim == 64) return wgs > 512 ? wgs <= 768 || wgs > 1024 : wgs > 256 && a.seq <= 256;
+  return a.head_dim == 128 && a.seq <= 128 && wgs > 256 && wgs <= 512;
+}
+
+// Whether the backward of the form for few workgroups forms D = rowsum(dctx * ctx) itself, where a wave has two tiles of 32 queries or fewer: it saves a dependent launch
 // and costs 0.85 us a tile of a wave's chain (16-byte loads of 32 rows, which nothing else covers).  Backward with the launch and
 // without, us: 2 x 128 positions, two heads of 64 7.8 and 6.0, 2 x 200, two of 128 12.1 and 10.7, 4 x 256 12.4 and 11.5; 2 x 512, four heads
 // 15.3 and 16.3, 2 x 1024, two 20.7 and 25.4, 4096, two 62 and 90.

@@ -459,7 +459,7 @@ DEV void settle_v(f32x16 (&acc)[N]) {
 // halves the 256 that two waves per SIMD leave each.
 // (us, with each tile's three parts one after the other and so: heads of 128, 2 x 4096 positions, 4 heads 82 -> 63, 4 x 2048, 5 heads
 // 46 -> 39, 4 x 4096, 5 heads 104 -> 100, 44 x 448, 7 heads 52 -> 51; heads of 80, 8 x 2048, 4 heads 43 -> 37, 6 x 1003, 4 heads
-// 20.9 -> 17.6; heads of 64, 2 x 2048, 5 heads 32 -> 27, but 44 x 448, 7 heads 26 -> 27.5: three workgroups fitted a compute unit.
+// 20.9 -> 17.6; heads of 64, 2 x 2048, 5 heads 32 -> 27.  44 x 448, 7 heads of 64 would take 27.5 for 26 and keep the serial form below.
 // One wave per SIMD with deeper rings and Q and K in accumulation registers: 71, 41 and 122 for the first three.)
 template <int D>
 struct FwdSteps {
@@ -784,6 +784,200 @@ __global__ __launch_bounds__(256, 2)
 void attn_fwd_kernel(const AttnArgs p) {
   extern __shared__ __align__(1024) uint8_t smem[];
   attn_fwd_body<D>(p, smem);
+}
+
+// The same sums with the three parts of a tile one after the other: 120 registers and 48 KB of LDS for heads of 64, so that three
+// workgroups share a compute unit, and nothing in front of the first tile's scores that a lone tile does not need.  What bounds a
+// wave is that chain; attention_fwd_serial (attention.h) says where it is the faster one all the same, with both sides measured.  K and
+// V in two places of 64 keys each, loaded together a tile ahead.
+template <int D>
+__global__ __launch_bounds__(256, 2)
+void attn_fwd_serial_kernel(const AttnArgs p) {
+  using X = Dims<D>;
+  constexpr int DS = (D + 31) / 32;                 // 32-wide d sub-tiles of K
+  constexpr int K_BYTES = DS * 4096;                // [DS][64 kv][32 d]
+  constexpr int V_BYTES = 2 * 8192;                 // [2][32 kv][128 d]
+  constexpr int STAGE = K_BYTES + V_BYTES;
+  constexpr int NB = (X::KSTEPS + 3) / 4;           // batches of up to 4 contraction steps over d
+  extern __shared__ __align__(1024) uint8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 31, fh = lane >> 5;
+  const int s = p.seq;
+  const int nqb = (s + 127) / 128;
+  int pos, group;
+  if (!ranked_item(nqb, p.heads * p.batch, pos, group)) return;
+  const int qb = nqb - 1 - pos;                     // longest rows first
+  const int hh = group % p.heads, bi = group / p.heads;
+  const int qw0 = qb * 128 + wave * 32, qpos = qw0 + fr;
+  const long ld = p.ld;
+  const bf16_t* tok0 = static_cast<const bf16_t*>(p.qkv) + (long)bi * s * ld;
+  const int hl = p.heads * D;
+  const long view_bytes = ((long)(s - 1) * ld + D) * 2;
+  const buf_rsrc rsK = make_rsrc(tok0 + hl + hh * D, view_bytes);
+  const buf_rsrc rsV = make_rsrc(tok0 + 2 * hl + hh * D, view_bytes);
+
+  bf16x8 qf[X::KSTEPS];
+  load_row_frags<D>(tok0 + hh * D, ld, qpos, s, fh, qf);
+
+  DmaLoader<64, 4, false> ldK;
+  DmaLoader<128, 4, true> ldV;
+  ldK.init_kc((int)ld, 0, 1 << 30, wave, lane);       // rows past the sequence end fall outside the extent
+  ldV.init_ks((int)ld, IdentityCols{0, D}, wave, lane);
+  auto issue_tile = [&](int j) {
+    uint8_t* st = smem + (j & 1) * STAGE;
+    const int kv0 = j * 64;
+#pragma unroll
+    for (int c = 0; c < DS; ++c) ldK.issue(rsK, st + c * 4096, c * 32, D, wave, (uint32_t)kv0 * (uint32_t)ld * 2u);
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) ldV.issue(rsV, st + K_BYTES + h2 * 8192, kv0 + 32 * h2, 0, wave);
+  };
+
+  // per-lane LDS offsets: K fragment (row lane%32, chunk 2*step + lane/32) and V^T fragment rows d
+  const uint32_t offK0 = kc_frag_off(lane, 0), offK1 = kc_frag_off(lane, 1);
+  uint32_t offV[X::DT];
+  {
+    const int sl = lane & 15, nh = (lane >> 4) & 1;
+    const int kr = 4 * fh + (sl >> 2);
+#pragma unroll
+    for (int dt = 0; dt < X::DT; ++dt)
+      offV[dt] = (uint32_t)(kr * 256 + ((dt ^ (kr & 3)) << 6) + (16 * nh + 4 * (sl & 3)) * 2 + K_BYTES);
+  }
+
+  const int q_end = min(qb * 128 + 128, s);
+  const int ntiles = (q_end + 63) / 64;
+  f32x16 o[X::DT];
+#pragma unroll
+  for (int dt = 0; dt < X::DT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[dt][v] = 0.0f;
+  float m = -INFINITY, l = 0.0f;
+  const float sc = p.scale * LOG2E;
+  const uint32_t smem_base = lds_addr(smem);
+
+  issue_tile(0);
+  for (int j = 0; j < ntiles; ++j) {
+    wait_vmcnt<0>();                                  // tile j has landed (this wave's part)
+    __builtin_amdgcn_s_barrier();                     // ... everybody's part; the other stage is free
+    if (j + 1 < ntiles) issue_tile(j + 1);
+    const int kv0 = j * 64;
+    if (kv0 > qw0 + 31) continue;                     // every key of the tile is masked for this wave
+    const uint32_t st = smem_base + (j & 1) * STAGE;
+
+    // ---- S^T[kv, q] = K Q^T: batches of 4 contraction steps, next batch's reads in flight
+    f32x16 sT[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sT[t][v] = 0.0f;
+    u32x4 kf[2][4][2];
+    auto read_batch = [&](auto bb) {
+      constexpr int B = decltype(bb)::value;
+      static_for<0, 4>([&](auto kk) {
+        constexpr int KS = B * 4 + decltype(kk)::value;
+        if constexpr (KS < X::KSTEPS) {
+          const uint32_t a = st + ((KS & 1) ? offK1 : offK0);
+          kf[B & 1][decltype(kk)::value][0] = ds_read_b128_at<(KS >> 1) * 4096>(a);
+          kf[B & 1][decltype(kk)::value][1] = ds_read_b128_at<(KS >> 1) * 4096 + 2048>(a);
+        }
+      });
+    };
+    read_batch(std::integral_constant<int, 0>{});
+    static_for<0, NB>([&](auto bb) {
+      constexpr int B = decltype(bb)::value;
+      constexpr int NEXT = (B + 1 < NB) ? ((X::KSTEPS - 4 * (B + 1)) < 4 ? (X::KSTEPS - 4 * (B + 1)) : 4) * 2 : 0;
+      if constexpr (B + 1 < NB) read_batch(std::integral_constant<int, B + 1>{});
+      lds_wait<NEXT>();
+      static_for<0, 4>([&](auto kk) {
+        constexpr int KS = B * 4 + decltype(kk)::value;
+        if constexpr (KS < X::KSTEPS) {
+          tie(kf[B & 1][decltype(kk)::value][0]);
+          tie(kf[B & 1][decltype(kk)::value][1]);
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            sT[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[B & 1][decltype(kk)::value][t]),
+                                                            qf[KS], sT[t], 0, 0, 0);
+        }
+      });
+    });
+
+    // ---- online softmax; a lane owns one query (both lane halves: the two key halves of each 8)
+    float mx = -INFINITY;
+    if (kv0 + 63 > qw0) {                             // tile touches the diagonal: mask keys after the query
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          if (kv0 + 32 * t + acc_row(v, fh) > qpos) sT[t][v] = -INFINITY;
+          mx = fmaxf(mx, sT[t][v]);
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[t][v]);
+    }
+    mx = fmaxf(mx, other_half(mx)) * sc;       // scores scaled to the log2 domain (sc > 0)
+    const float m_new = fmaxf(m, mx);                  // finite: key 0 is visible to every query
+    if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {   // rescale only when some query's maximum moved
+      const float alpha = exp2_raw(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < X::DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
+      m = m_new;
+    }
+    float rs = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float e = exp2_raw(sT[t][v] * sc - m);
+        sT[t][v] = e;
+        rs += e;
+      }
+    l += rs;
+    bf16x8 pf[4];
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) {
+      const int t = s4 >> 1, u = s4 & 1;
+      u32x4 w = {pack_bf16(sT[t][8 * u + 0], sT[t][8 * u + 1]), pack_bf16(sT[t][8 * u + 2], sT[t][8 * u + 3]),
+                 pack_bf16(sT[t][8 * u + 4], sT[t][8 * u + 5]), pack_bf16(sT[t][8 * u + 6], sT[t][8 * u + 7])};
+      pf[s4] = __builtin_bit_cast(bf16x8, w);
+    }
+
+    // ---- O^T[d, q] += V^T P^T, one 32-row d tile at a time, next tile's reads in flight
+    u32x2 vf[2][4][2];
+    auto read_v = [&](auto dd) {
+      constexpr int DTI = decltype(dd)::value;
+      static_for<0, 4>([&](auto ss) {
+        constexpr int S4 = decltype(ss)::value;
+        constexpr int OFF = (S4 >> 1) * 8192 + (S4 & 1) * 4096;
+        vf[DTI & 1][S4][0] = ds_read_tr_at<OFF>(st + offV[DTI]);
+        vf[DTI & 1][S4][1] = ds_read_tr_at<OFF + 2048>(st + offV[DTI]);
+      });
+    };
+    read_v(std::integral_constant<int, 0>{});
+    static_for<0, X::DT>([&](auto dd) {
+      constexpr int DTI = decltype(dd)::value;
+      if constexpr (DTI + 1 < X::DT) read_v(std::integral_constant<int, DTI + 1>{});
+      lds_wait<(DTI + 1 < X::DT) ? 8 : 0>();
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) {
+        tie(vf[DTI & 1][s4][0]);
+        tie(vf[DTI & 1][s4][1]);
+        const u32x4 a = {vf[DTI & 1][s4][0][0], vf[DTI & 1][s4][0][1], vf[DTI & 1][s4][1][0], vf[DTI & 1][s4][1][1]};
+        o[DTI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pf[s4], o[DTI], 0, 0, 0);
+      }
+    });
+  }
+  l += other_half(l);
+  if (qpos < s) {
+    bf16_t* out = static_cast<bf16_t*>(p.ctx) + ((long)bi * s + qpos) * p.ld_ctx + hh * D;
+    store_transposed<D>(o, 1.0f / l, out, fh);
+    if (fh == 0) p.lse[((long)bi * p.heads + hh) * s + qpos] = (m + log2f(l)) * LN2;
+  }
 }
 
 // ------------------------------------------------------------------------------------- dQ pass
@@ -1459,11 +1653,17 @@ hipError_t fwd_launch(const AttnArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(attn_fwd_split_kernel<D>, dim3(ranked_grid((a.seq + 31) / 32, a.heads * a.batch)), dim3(256), LDS, st, a);
     return hipGetLastError();
   }
-  constexpr int LDS = 2 * (((D + 31) / 32) * 4096 + 2 * 8192);
+  constexpr int LDS = 2 * (((D + 31) / 32) * 4096 + 2 * 8192);      // both forms
+  const dim3 grid(ranked_grid((a.seq + 127) / 128, a.heads * a.batch));
+  if (attention_fwd_serial(a)) {
+    static LdsLimitOnce lds_limit;
+    if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_serial_kernel<D>), LDS); e != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_fwd_serial_kernel<D>, grid, dim3(256), LDS, st, a);
+    return hipGetLastError();
+  }
   static LdsLimitOnce lds_limit;
-  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_kernel<D>), LDS);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_fwd_kernel<D>, dim3(ranked_grid((a.seq + 127) / 128, a.heads * a.batch)), dim3(256), LDS, st, a);
+  if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(attn_fwd_kernel<D>), LDS); e != hipSuccess) return e;
+  hipLaunchKernelGGL(attn_fwd_kernel<D>, grid, dim3(256), LDS, st, a);
   return hipGetLastError();
 }
 

@@ -55,13 +55,14 @@ struct IdentityCols {
 };
 
 // Where the loads of one operand tile read.  R rows, NW waves in the workgroup; each wave owns IPW of the tile's R/16 one-KiB
-// pieces; later tiles are reached through the buffer resource.
+// pieces; later tiles are reached through the buffer resource, or by an offset (issue).
 template <int R, int NW, bool KS>
 struct DmaLoader {
   static_assert(R % (16 * NW) == 0, "tile pieces must divide over the waves");
   static constexpr int IPW = R / 16 / NW;
   uint32_t base[IPW];   // byte offset of the lane's chunk at k0 = 0, or BUF_OOB
   int kofs;             // KC: contraction offset of the lane's chunk inside the tile (K-tail test)
+  uint32_t ld2;         // KS: bytes per memory row
 
   // KC: memory [row][k]; rows row0.. clipped at row_end.
   DEV void init_kc(int ld, int row0, int row_end, int wave, int lane) {
@@ -77,6 +78,7 @@ struct DmaLoader {
   // Contraction indices past the operand's last memory row fall outside the buffer extent by themselves.
   template <class ColMap>
   DEV void init_ks(int ld, const ColMap& cols, int wave, int lane) {
+    ld2 = (uint32_t)ld * 2u;
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
       const int P = (wave * IPW + i) * 1024 + lane * 16;
@@ -84,6 +86,16 @@ struct DmaLoader {
       const int g = (w >> 6) ^ (k & 3), sub = (w >> 4) & 3;
       const int c = cols(g * 32 + sub * 8);
       base[i] = c >= 0 ? (uint32_t)(k * ld + c) * 2u : BUF_OOB;
+    }
+  }
+  // extra: a wave-uniform byte offset (e.g. a row offset of a KC operand)
+  DEV void issue(buf_rsrc rs, uint8_t* tile, int k0, int k_end, int wave, uint32_t extra = 0) const {
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      uint32_t off;
+      if (KS) off = base[i] + (uint32_t)k0 * ld2 + extra;
+      else off = (k0 + kofs < k_end) ? base[i] + (uint32_t)k0 * 2u + extra : BUF_OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(tile + (wave * IPW + i) * 1024), 16, off, 0, 0, 0);
     }
   }
 };

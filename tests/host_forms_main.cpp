@@ -4,6 +4,7 @@
 //   joined <K> <concurrency> <beside> <ranges> <M N> x 4 [<adds>]   GemmTile of four weight gradients in one launch
 //   output <M> <N> <K>                                    1: the block output in the product's epilogue, 0: a pass
 //   attention <backward> <batch> <seq> <heads>            1: 32 positions per workgroup, 0: 128
+//   serial <head_dim> <batch> <seq> <heads>               1: the 128-position forward takes a tile's parts one after the other
 //   walk <seq> <ld> <head_dim> <tiles>                    the furthest byte of a [seq, ld] matrix that the attention forward's views of
 //                                                         one head and that many tiles (and the two asked for ahead) reach, or -1 where
 //                                                         a view is before the matrix
@@ -36,6 +37,10 @@ int main() {
       AttnArgs a{};
       a.batch = (int)v[1]; a.seq = (int)v[2]; a.heads = (int)v[3];
       std::printf("%d\n", attention_split_pays(a, v[0] != 0) ? 1 : 0);
+    } else if (n == 5 && !std::strcmp(what, "serial")) {
+      AttnArgs a{};
+      a.head_dim = (int)v[0]; a.batch = (int)v[1]; a.seq = (int)v[2]; a.heads = (int)v[3];
+      std::printf("%d\n", attention_fwd_serial(a) ? 1 : 0);
     } else if (n == 5 && !std::strcmp(what, "walk")) {
       const int tile = attention_tile_bytes(v[1]), rows = (int)(v[3] * 64 < v[0] ? v[3] * 64 : v[0]);
       long at = 0, furthest = 0;

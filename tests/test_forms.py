@@ -152,6 +152,17 @@ def test_whether_a_contraction_is_dealt_does_not_depend_on_the_streams(ask):
     assert 30 < taken < 270
 
 
+def test_shapes_of_the_gpu_test_take_both_orders_of_a_tile(ask):
+    """... of the 128-position attention forward, in whole and cut down to the batch elements that they are compared with."""
+    import test_gpu_attention_serial as S
+    for d, b, s, nh, few in S.SHAPES:
+        assert ask([("attention", 0, b, s, nh), ("serial", d, b, s, nh)]) == [0, 1], (d, b, s, nh)
+        if few:
+            assert ask([("attention", 0, few, s, nh), ("serial", d, few, s, nh)]) == [0, 0], (d, few, s, nh)
+    for d, b, s, nh in ((64, 128, 512, 1), (64, 256, 128, 1), (64, 104, 257, 1), (64, 8, 4096, 1), (64, 128, 1024, 1), (80, 640, 65, 1), (128, 256, 128, 1), (128, 513, 128, 1), (128, 400, 129, 1)):
+        assert ask([("serial", d, b, s, nh)]) == [0], (d, b, s, nh)
+
+
 def test_views_of_the_attention_forward_stay_inside_the_matrix(ask):
     """Any row pitch that the entry point takes (a matrix under 2 GiB), also one so wide that 64 rows of it are more than
     31 bits of bytes: no view begins before the matrix or ends behind the last row that is needed."""
