@@ -32,15 +32,18 @@ namespace {
 constexpr int BK = GEMM_BK;
 // Operand tiles in LDS at once, of A and of B (see the software pipeline of gemm_body).  Weights come from HBM, the activations
 // often from a cache that the kernel before has just written, and a place more is half to one and a half tiles more to
-// land in: 256x128 tiles work through theirs in 0.6 us, so they take all 160 KB, and in 192x256 the third place is B's, the
-// larger tile of the two.  (A just written, B out of the caches, {3, 2} and as here: 2048 x 2560 x 5120 in 256x128 NN 70 -> 66 us,
-// NT 74 -> 69, in 192x256 103 -> 92 and 97 -> 87, 2048 x 5120 x 2560 51.5 -> 48.2; all in the caches 60.6 -> 59.2, 80 -> 78.  256x256 with {2, 3}
-// and five places of each in 128x128 tiles, one workgroup to a compute unit, won here and lost there.)
+// land in: 256x128 tiles work through theirs in 0.6 us, so along a deep contraction they take all 160 KB, and in 192x256 the third place
+// is B's, the larger tile of the two.  (A just written, B out of the caches, {3, 2} and as here: 2048 x 2560 x 5120 in 256x128 NN 70 -> 66 us,
+// NT 74 -> 69, 3000 x 2000 x 2560 NN 37.6 -> 35.9, in 192x256 103 -> 92 and 97 -> 87, 2048 x 5120 x 2560 51.5 -> 48.2.  256x256 with {2, 3}
+// and five places of each in 128x128 tiles, one workgroup to a compute unit, won here and lost there.)  DEEP: a third tile of both in front
+// of the loop costs every 256x128 tile 0.2 to 0.5 us, which a shallow contraction does not win back (ring_pays; {3, 2} and {3, 4},
+// 3000 x 2000 x 200 NT 9.8 and 10.4 us, x 640 13.0 and 13.5, x 1280 19.2 and 19.5, with B out of the caches 22.2 and 21.7).
 struct Rings { int a, b; };
-constexpr Rings rings(int BM, int BN) {
-  return BM == 256 && BN == 128 ? Rings{3, 4} : BM == 192 && BN == 256 ? Rings{2, 3} : (3 * BM + 2 * BN) * BK * 2 <= 160 * 1024 ? Rings{3, 2} : Rings{2, 2};
+constexpr Rings rings(int BM, int BN, bool DEEP) {
+  return BM == 256 && BN == 128 && DEEP ? Rings{3, 4} : BM == 192 && BN == 256 ? Rings{2, 3} : (3 * BM + 2 * BN) * BK * 2 <= 160 * 1024 ? Rings{3, 2} : Rings{2, 2};
 }
-constexpr int ring_bytes(int BM, int BN) { return (rings(BM, BN).a * BM + rings(BM, BN).b * BN) * BK * 2; }
+constexpr int ring_bytes(int BM, int BN, bool DEEP) { return (rings(BM, BN, DEEP).a * BM + rings(BM, BN, DEEP).b * BN) * BK * 2; }
+inline bool ring_pays(const GemmArgs& a) { return a.K / (a.splits > 1 ? a.splits : 1) >= 2048; }
 
 // KS tile [64 k][R rows]: element (k, n) at byte 2 R k + 64 ((n >> 5) ^ ks_swz(k)) + 2 (n & 31).  A transposing read
 // covers 4 consecutive k x 16 n: the XOR, together with the row pitch, puts the 4 rows in 4 different 64-byte quarters of
@@ -364,10 +367,10 @@ constexpr int IN_AGPRS = 64;
 DEV void mfma_agpr(bf16x8 a, bf16x8 b, f32x4& c) { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b)); }
 DEV void mfma_vgpr(bf16x8 a, bf16x8 b, f32x4& c) { asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b)); }
 
-template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI, bool DEEP>
 DEV void gemm_body(const GemmArgs& p, const int lin) {
   constexpr int NW = (BM / WM) * (BN / WN);
-  constexpr int TM = WM / 16, TN = WN / 16, RING_A = rings(BM, BN).a, RING_B = rings(BM, BN).b;
+  constexpr int TM = WM / 16, TN = WN / 16, RING_A = rings(BM, BN, DEEP).a, RING_B = rings(BM, BN, DEEP).b;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   extern __shared__ __align__(1024) uint8_t smem[];
 
@@ -772,18 +775,18 @@ DEV int tile_of_block(int T) {
 // wave tile = tile: the contraction is dealt over the waves (gemm_split_body)
 constexpr int gemm_threads(int BM, int BN, int WM, int WN) { return BM == WM && BN == WN ? (BM == 64 ? Split<64>::W : Split<128>::W) * 64 : (BM / WM) * (BN / WN) * 64; }
 
-template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI, bool DEEP>
 __global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
 void gemm_kernel(const GemmArgs p) {
   const int T = p.tiles_m * p.tiles_n, lin = tile_of_block(T);
   if (lin >= T) return;
   if constexpr (BM == WM && BN == WN) gemm_split_body<BM, AKS, BKS, EPI>(p, lin);
-  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(p, lin);
+  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>(p, lin);
 }
 
 // Several weight gradients of one block in one launch: alone, each leaves part of the chip idle (the 13B shard's are 200,
 // 200, 60 and 160 tiles of 256x256 on 256 compute units), and a small block pays mostly for the launches.
-template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI, bool DEEP>
 DEV void gemm_group_body(const GemmGroup& p) {
   const int T1 = p.first[GEMM_GROUP], T = T1 * p.splits;
   int lin = tile_of_block(T);
@@ -803,12 +806,12 @@ DEV void gemm_group_body(const GemmGroup& p) {
   a.K = min(a.K - (int)k0, p.k_per);
   a.C = static_cast<float*>(a.C) + range * p.part_stride;
   if constexpr (BM == WM && BN == WN) gemm_split_body<BM, AKS, BKS, EPI>(a, lin - p.first[i]);
-  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI>(a, lin - p.first[i]);
+  else gemm_body<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>(a, lin - p.first[i]);
 }
-template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI, bool DEEP>
 __global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
 void gemm_group_kernel(const GemmGroup p) {
-  gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI>(p);
+  gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>(p);
 }
 
 // ... and with further workgroups behind the tiles: in a small block those of the Norm1 backward, then in any block those of
@@ -818,12 +821,12 @@ void gemm_group_kernel(const GemmGroup p) {
 // 128 and 120, 2000 of it 228 and 216, 4000 355 and 348; the bias gradients alone: 6018 tokens of the 2.7B shard, whose 224 tiles leave 32
 // compute units to them, 626 and 613, 16384 of it 1432 and 1420, 2048 of 13B 650 and 647).
 struct GemmTail { HeldTail t; int tiles, norm_blocks, sum_items[COLSUM_MAX_HELD]; };      // workgroups of the tiles and of the norm; column blocks x ranges
-template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI, bool DEEP>
 __global__ __launch_bounds__(gemm_threads(BM, BN, WM, WN), BM * BN == 128 * 128 && BM != WM ? 2 : 1)
 void gemm_tail_kernel(const GemmGroup p, const GemmTail tail) {
   extern __shared__ __align__(1024) uint8_t smem[];
   if ((int)blockIdx.x < tail.tiles) {
-    gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI>(p);
+    gemm_group_body<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>(p);
     return;
   }
   const int at = blockIdx.x - tail.tiles;
@@ -876,14 +879,14 @@ bool plan_tiles(GemmArgs& a) {
   return a.a_bytes < (1L << 31) && a.b_bytes < (1L << 31);
 }
 
-template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AKS, bool BKS, int EPI, bool DEEP>
 hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   constexpr int NT = gemm_threads(BM, BN, WM, WN);
-  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : ring_bytes(BM, BN);
+  constexpr int LDS = BM == WM && BN == WN ? Split<BM == 64 ? 64 : 128>::W * Split<BM == 64 ? 64 : 128>::STAGE : ring_bytes(BM, BN, DEEP);
   auto grid = [](int T) { return dim3(T < 16 ? T : 8 * ((T + 7) / 8)); };
   if (n > 1 || products[0].splits > 1 || products[0].tail) {
     if constexpr (EPI == EPI_ACC_F32 && !(BM == 128 && BN == 256)) {      // (the rule, which alone forms groups, never picks 128x256)
-      auto kern = gemm_group_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
+      auto kern = gemm_group_kernel<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>;
       static LdsLimitOnce lds_limit;      // one per instantiation
       if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
       GemmGroup grp{};
@@ -922,7 +925,7 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
         for (int k = 0; k < tail.t.nsums; ++k) tail.sum_items[k] = (tail.t.sums[k].n / 8 + 63) / 64 * COLSUM_PARTS;
         constexpr int QUADS = NT / 256;
         const int sums = (tail.sum_items[0] + tail.sum_items[1] + QUADS - 1) / QUADS;
-        auto both = gemm_tail_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
+        auto both = gemm_tail_kernel<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>;
         static LdsLimitOnce tail_limit;
         if (hipError_t e = tail_limit.ensure(reinterpret_cast<const void*>(both), LDS); e != hipSuccess) return e;
         hipLaunchKernelGGL(both, dim3(tail.tiles + tail.norm_blocks + sums), dim3(NT), LDS, stream, grp, tail);
@@ -937,7 +940,7 @@ hipError_t launch_cfg(const GemmArgs* products, int n, hipStream_t stream) {
   }
   GemmArgs a = products[0];
   if (!plan_tiles<BM, BN, AKS, BKS, EPI>(a)) return hipErrorInvalidValue;
-  auto kern = gemm_kernel<BM, BN, WM, WN, AKS, BKS, EPI>;
+  auto kern = gemm_kernel<BM, BN, WM, WN, AKS, BKS, EPI, DEEP>;
   static LdsLimitOnce lds_limit;      // one per instantiation
   if (hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(kern), LDS); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, grid(a.tiles_m * a.tiles_n), dim3(NT), LDS, stream, a);
@@ -948,17 +951,19 @@ template <bool AKS, bool BKS, int EPI>
 hipError_t launch_layout(const GemmArgs* a, int n, int tile_cfg, hipStream_t stream) {
   constexpr bool PAIRED = EPI == EPI_SWIGLU || EPI == EPI_ROPE;      // column pairs 32 apart inside every 64 of a wave tile
   switch (tile_cfg) {
-    case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI>(a, n, stream);
-    case GEMM_TILE_256x128: return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_256x256: return launch_cfg<256, 256, 128, 128, AKS, BKS, EPI, false>(a, n, stream);
+    case GEMM_TILE_256x128:
+      if (ring_pays(a[0])) return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI, true>(a, n, stream);
+      return launch_cfg<256, 128, 128, 64, AKS, BKS, EPI, false>(a, n, stream);
     // by number only, through the single-kernel entry points, which offer no block output
-    case GEMM_TILE_128x256: if constexpr (EPI != EPI_RESID) return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
-    case GEMM_TILE_256x192: if constexpr (!PAIRED) return launch_cfg<256, 192, 128, 96, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
-    case GEMM_TILE_256x320: if constexpr (!PAIRED && EPI != EPI_RESID) return launch_cfg<256, 320, 128, 160, AKS, BKS, EPI>(a, n, stream); return hipErrorInvalidValue;
-    case GEMM_TILE_192x256: return launch_cfg<192, 256, 96, 128, AKS, BKS, EPI>(a, n, stream);
-    case GEMM_TILE_320x256: return launch_cfg<320, 256, 160, 128, AKS, BKS, EPI>(a, n, stream);
-    case GEMM_TILE_64x64:   return launch_cfg<64, 64, 64, 64, AKS, BKS, EPI>(a, n, stream);
-    case GEMM_TILE_128x128_DEALT: return launch_cfg<128, 128, 128, 128, AKS, BKS, EPI>(a, n, stream);
-    default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI>(a, n, stream);
+    case GEMM_TILE_128x256: if constexpr (EPI != EPI_RESID) return launch_cfg<128, 256, 64, 128, AKS, BKS, EPI, false>(a, n, stream); return hipErrorInvalidValue;
+    case GEMM_TILE_256x192: if constexpr (!PAIRED) return launch_cfg<256, 192, 128, 96, AKS, BKS, EPI, false>(a, n, stream); return hipErrorInvalidValue;
+    case GEMM_TILE_256x320: if constexpr (!PAIRED && EPI != EPI_RESID) return launch_cfg<256, 320, 128, 160, AKS, BKS, EPI, false>(a, n, stream); return hipErrorInvalidValue;
+    case GEMM_TILE_192x256: return launch_cfg<192, 256, 96, 128, AKS, BKS, EPI, false>(a, n, stream);
+    case GEMM_TILE_320x256: return launch_cfg<320, 256, 160, 128, AKS, BKS, EPI, false>(a, n, stream);
+    case GEMM_TILE_64x64:   return launch_cfg<64, 64, 64, 64, AKS, BKS, EPI, false>(a, n, stream);
+    case GEMM_TILE_128x128_DEALT: return launch_cfg<128, 128, 128, 128, AKS, BKS, EPI, false>(a, n, stream);
+    default:                return launch_cfg<128, 128, 64, 64, AKS, BKS, EPI, false>(a, n, stream);
   }
 }
 

@@ -26,3 +26,11 @@ def test_every_depth_around_the_ring(dom, tile, M, N, K):
         torch.cuda.synchronize()
         assert close(got[1], A.float() @ W.float())
         assert torch.equal(*got), layout
+
+
+# the longer rings of 256x128 tiles begin at a contraction of 2048: the line itself, one step under it, and behind it every remainder of
+# tiles over the places of either operand
+@pytest.mark.parametrize("K", [2040, 2048, 2056, 2112, 2184, 2240, 2312, 2368, 2440, 2496, 2568])
+@pytest.mark.parametrize("M,N", [(264, 200), (512, 128)])
+def test_deep_contractions(dom, M, N, K):
+    test_every_depth_around_the_ring(dom, TILE_256x128, M, N, K)
