@@ -1443,8 +1443,8 @@ void attn_fwd_split_kernel(const AttnArgs p) {
   }
 }
 
-// D = rowsum(dO * O) of 32 queries is the diagonal of dO O^T: with OWN_D the passes form it by the MFMAs that form dP, in the same order, so
-// that for a sequence of one position D equals dP bit for bit here too.  See attention_owns_d for where that pays.
+// D = rowsum(dO * O) of 32 queries is the diagonal of dO O^T: with OWN_D the passes form it by the MFMAs that form dP, in the same order.
+// See attention_owns_d for where that pays.
 // Lane c, or the one 32 on, holds the diagonal's value c: lanes whose half is diag_half(c).
 DEV int diag_half(int c) { return (c >> 2) & 1; }
 DEV float diag(const f32x16& t, int c) {

@@ -101,6 +101,22 @@ def test_ranges_of_the_gpu_test(ask):
         assert ask([("ranges", tiles, 16 * seq, h * (4 * h + 2 * f))])[0] > 1
 
 
+def test_shapes_of_the_other_gpu_tests_take_the_forms_that_these_name(ask):
+    import test_gpu_attention_own_d as A
+    import test_gpu_joined_sums as J
+    import test_gpu_operand_rings as R
+    for shapes, few in ((A.OWN, 1), (A.PASS[:-1], 0), (A.PASS[-1:], 1)):
+        assert [ask([("attention", 1, *x)])[0] for x in shapes] == [few] * len(shapes)
+    assert all(s <= 256 for _, s, _ in A.OWN) and A.PASS[-1][1] == 257         # attention_owns_d
+    assert set(ask([("gemm", e, *R.TILES_192x256, K, 1, 0) for e in (D.EPI_STORE, D.EPI_ACC_F32) for K in R.DEPTHS])) == {7}
+    ranges = []
+    for h, _, tp, f, b, s, _ in J.BLOCKS:
+        shapes = [(f // tp, h), (h, f // tp), (h // tp, h), (h, 3 * h // tp)]
+        tiles = sum(-(-m // 256) * -(-n // 256) for m, n in shapes)
+        ranges += ask([("ranges", tiles, b * s, sum(m * n for m, n in shapes))]) if tiles <= 200 else [1]      # beside the chain: one
+    assert ranges == [5, 1, 1, 1]
+
+
 # (hidden, ffn columns, batch, seq) of blocks whose MLP-down product was dealt with the block output in its epilogue and not
 # without: 4 x 66 tokens of the Llama-2 7B shard, 16 x 257 of the smallest GPT block
 ORDER_OF_BLOCK_OUTPUT = [(4096, 1376, 4, 66), (256, 512, 16, 257), (256, 48, 1, 233)]

@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 # (hidden, heads, ranks, ffn, batch, seq, p): contraction ranges; whole tiles behind the chain, ragged; weight gradients beside the
 # chain, one row group (one matrix a launch) and two (two sums a launch)
-BLOCKS = [(512, 8, 1, 2048, 4, 2048, 1), (2560, 32, 8, 10240, 2, 501, 2), (5120, 40, 8, 20480, 2, 777, 2), (4096, 32, 8, 16384, 4, 2048, 4)]
+BLOCKS = [(512, 8, 1, 2048, 16, 1024, 1), (2560, 32, 8, 10240, 2, 501, 2), (5120, 40, 8, 20480, 2, 777, 2), (4096, 32, 8, 16384, 4, 2048, 4)]
 
 
 @pytest.mark.parametrize("hidden,heads,tp,ffn,batch,seq,p", BLOCKS)

@@ -11,9 +11,13 @@ torch = pytest.importorskip("torch")
 TILE_256x128, TILE_256x256 = 1, 2
 
 
-# 1 to 9 operand tiles of 64, ragged in the last; (M, N): a full tile and ragged edges; 192x256 tiles by the rule
-@pytest.mark.parametrize("K", [8, 64, 72, 128, 192, 200, 256, 320, 328, 456, 520, 576])
-@pytest.mark.parametrize("tile,M,N", [(TILE_256x128, 264, 200), (TILE_256x128, 512, 128), (-1, 7208, 1032)])
+# 1 to 9 operand tiles of 64, ragged in the last; (M, N): a full tile and ragged edges; 192x256 tiles by the rule at every depth
+DEPTHS = [8, 64, 72, 128, 192, 200, 256, 320, 328, 456, 520, 576]
+TILES_192x256 = (4408, 1800)
+
+
+@pytest.mark.parametrize("K", DEPTHS)
+@pytest.mark.parametrize("tile,M,N", [(TILE_256x128, 264, 200), (TILE_256x128, 512, 128), (-1, *TILES_192x256)])
 def test_every_depth_around_the_ring(dom, tile, M, N, K):
     torch.manual_seed(M + K)
     A, W = gpu((M, K)), gpu((K, N), 0.05)

@@ -221,3 +221,21 @@ def test_captured_parts_of_a_wide_block_beside_an_eager_one(wide):
         b.forward()                                 # eager work of the same pool between the replays
         b.backward()
         b.sync()
+
+
+@pytest.mark.parametrize("nstreams", [1, 2, 4])
+def test_a_captured_norm1_part_of_a_wide_block_behind_eager_ones(wide, nstreams):
+    """The Norm1 part alone, whose two groups meet before the last reduction, replayed from a graph."""
+    from paper_2409_15241_amd import domino as D
+    b, ref = wide
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=b.streams[0]):
+        bwd_part(D, b, D.BWD_NORM1, nstreams=nstreams)
+    for _ in range(3):
+        start(b, False)
+        bwd_part(D, b, D.BWD_MLP)
+        bwd_part(D, b, D.BWD_ATTN)
+        with torch.cuda.stream(b.streams[0]):
+            graph.replay()
+        b.sync()
+        check(b, ref[False])
