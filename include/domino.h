@@ -14,7 +14,9 @@
  *     no device memory.  Activations are bf16, row-major [tokens, features] with tokens = batch*seq
  *     (batch-major); weight matrices are bf16 row-major [in, out]; gradients of parameters are fp32.
  *   - Streams are hipStream_t handles passed as void*.  Calls only enqueue work and return; on
- *     return, everything is ordered before later work submitted to streams[0].  No host sync.
+ *     return, everything is ordered before later work submitted to streams[0].  No host sync.  The edges between a call's own
+ *     streams carry no system fence: the host and other devices may look at the results behind an operation of the caller's
+ *     on streams[0] that has one (an event recorded without hipEventDisableSystemFence, a synchronisation, a copy).
  *   - Return value: DOMINO_OK or a negative DOMINO_ERR_*; domino_last_error() gives the text.
  *     Arguments are validated before any GPU call, so invalid calls fail the same way on a host
  *     without a GPU.  The library never throws and never aborts.  DOMINO_ERR_HIP can come back in the
@@ -103,15 +105,15 @@ int domino_saved_slot(const domino_cfg* cfg, const char* name, size_t* offset, s
  * MLP-up with fused activation, the down-projection's pieces into mlp_partial; finally
  * y = x1 + mlp_partial + mlp_others + b_down.
  * A call hands out no single piece, so pieces share launches: all row slices are one row group, or two where p > 2 and
- * the block is wide enough that a half's launches fill the chip, and the column pieces of a product are one launch
- * (those of the out-projection one each where there are two groups).
+ * the block is wide enough that a half's launches fill the chip, and the column pieces of a product are one launch a group.
  *   attn_others, mlp_others: [b,s,h] or NULL (= zeros): sum of the other ranks' partials.
  *   attn_partial, mlp_partial: out [b,s,h]: what the two forward all-reduces would consume.
  *   y: out [b,s,h] or NULL.   saved: out, domino_saved_bytes().   workspace: scratch.
  *   streams[0..nstreams-1]: row group g runs on streams[g % m], m = min(nstreams, groups).  The backward puts weight and
  *   vector gradients on streams[m], beside the chain of input gradients, attention and norms, where the pool has that
  *   stream, streams[0] is not being captured and the block is large enough for it to pay; otherwise they follow on the
- *   groups' streams.  No other stream is used: three at most.  Which block gets what follows from cfg alone.
+ *   groups' streams.  The last reduction of the vector gradients follows on streams[0] where a call's streams meet before it (behind
+ *   weight gradients beside the chain, except between the blocks of a stack, and in the Norm1 part alone).  No other stream is used: three at most.  Which block gets what follows from cfg alone.
  *   Streams overlap only on distinct hardware queues: create the pool once; HIP's default of four queues
  *   (GPU_MAX_HW_QUEUES, read when the runtime starts) is enough (domino_last_warning() tells when it is set too low).
  *   streams[0] may be under HIP graph capture (the other streams join the capture through the call's own

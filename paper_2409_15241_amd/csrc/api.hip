@@ -245,7 +245,8 @@ int begin_call(void* const* streams, int nstreams, int p) {
 }
 
 // The events order streams of one device and are never looked at from the host, so they go without the fence that would make
-// the work before them visible there (a program's own synchronisation has its own): a record then holds its stream up for 5 us and
+// the work before them visible there and to other devices (a program's own event, synchronisation or copy behind the call on streams[0]
+// has its own): a record then holds its stream up for 5 us and
 // not for 6 to 8 (forward + backward, us, with and without the fence: 13B with 2048 tokens 655 and 641, with 8192 2042 and 2028, in parts 2124 and
 // 2115; Llama-2 7B level).
 int next_sync_event(hipEvent_t* ev) {
@@ -663,8 +664,10 @@ int vector_gradients(const Layout& L, const BwdLayer& B, int which, hipStream_t 
 }
 
 // Whether the Norm1 backward and the bias gradients go into the weight gradients' launch where one stream carries them all: two
-// or three launches fewer, which pays the more the smaller the block is (figures at gemm_tail_kernel of gemm.hip); with 8M
-// values of an activation, the largest measured, it is 2 %.
+// or three launches fewer, which pays the more the smaller the block is (figures at gemm_tail_kernel of gemm.hip).  The Norm1
+// backward apart and joined at the line, us: 4096 tokens of a 2048-wide block 348 and 342, 8192 of a 1024-wide one 300.5 and
+// 302.8.  Beyond it the two go on like that (2048-wide, 6144 tokens 486 and 473, 8000 559 and 548; 1024-wide, 12288 tokens 435 and 438; 1536-wide,
+// 5120 422 and 426, 10240 675 and 673).
 inline bool tail_joins(const Layout& L) {
   return L.groups == 1 && !L.per_slice && L.wsplits == 1 && L.h <= HeldTail::MAX_H && (long)L.M * L.h <= 1L << 23;
 }
@@ -690,9 +693,8 @@ int wait(hipStream_t st, hipEvent_t ev) {
 
 // Where the weight gradients run beside the chain, or the call is the Norm1 part alone, the streams meet on streams[0] before the last
 // reduction of the vector gradients and not behind it: an edge between streams is 10 to 14 us in which nothing else runs, and on
-// the side stream the reduction stood between two of them (forward + backward,
-// us, before and now, together with what next_sync_event says: 13B with 2048 tokens 672 and 650, Llama-2 7B 1560 and 1538, the 13B block in
-// parts 2180 and 2149).
+// the side stream the reduction stood between two of them (forward + backward, us, both with the events as next_sync_event makes them:
+// 13B with 2048 tokens 661 and 650, Llama-2 7B 1560 and 1538, the 13B block in parts 2170 and 2149).
 inline bool reduces_joined(const StreamPlan& S, int parts) {
   return (parts & DOMINO_BWD_NORM1) && (S.side || !(parts & (DOMINO_BWD_MLP | DOMINO_BWD_ATTN)));
 }

@@ -24,7 +24,7 @@ struct AttnArgs {
 // The constants were fitted before either 128-position form ran its softmax under its MFMAs, which moved where they
 // meet: forward, heads of 128, 4 x 512, five heads 13.0 in the form not taken, 14.2 in the one that is, 8 x 512, four heads 13.1 and 16.4,
 // 8 x 384, five heads 11.2 and 15.3, where 3 x 1024, four heads is right with 20.0 and 18.6; backward 2 x 2048, four heads 70.1 and 75.5.
-// The line stays: the forms sum in another order, and moving it would change the bits of every block in between for 1 to 5 us.
+// They have not been fitted again since.
 inline bool attention_split_pays(const AttnArgs& a, bool backward) {
   const int wgs = (a.seq + 127) / 128 * a.heads * a.batch, steps = (a.seq + 63) / 64;
   if (wgs > 128) return false;

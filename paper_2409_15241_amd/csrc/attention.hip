@@ -337,10 +337,9 @@ struct BwdSteps {
 };
 
 // an operand that stays in accumulation registers from here on
-template <int N>
-DEV void keep_in_acc(bf16x8 (&f)[N]) {
+DEV void keep_in_acc(bf16x8 (&f)[8]) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) asm volatile("" : "+a"(f[i]));
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+a"(f[i]));
 }
 // behind the loop: the last sums are as many clocks away from their MFMA as a use needs, and no copy of them is made before
 template <int N>
@@ -475,8 +474,7 @@ struct FwdSteps {
     return n;
   }
 };
-// K fragment and Q in accumulation registers, scores in vector registers; ZERO: the first product of a sum.  The wait for the fragments
-// stands in the same statement.
+// All in vector registers; ZERO: the first product of a sum.  The wait for the fragments stands in the same statement.
 template <bool ZERO, int WAIT>
 DEV void fwd_score_mfma(const u32x4& k, bf16x8 q, f32x16& t) {
   if constexpr (WAIT >= 0) {
@@ -487,11 +485,7 @@ DEV void fwd_score_mfma(const u32x4& k, bf16x8 q, f32x16& t) {
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(t) : "v"(k), "v"(q));
   }
 }
-template <int WAIT>
-DEV void fwd_output_mfma(const u32x4& v, const u32x4& p, f32x16& o) {
-  if constexpr (WAIT >= 0) asm volatile("s_waitcnt lgkmcnt(%3)\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(o) : "v"(v), "v"(p), "n"(WAIT));
-  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(o) : "v"(v), "v"(p));
-}
+DEV void fwd_output_mfma(const u32x4& v, const u32x4& p, f32x16& o) { asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(o) : "v"(v), "v"(p)); }
 // a value is formed here, and not behind the branches that follow, or ahead of the loop
 template <class T>
 DEV void here(T& v) { asm volatile("" : "+v"(v)); }
@@ -620,7 +614,7 @@ DEV void attn_fwd_body(const AttnArgs& p, uint8_t* smem) {
       constexpr int U = decltype(uc)::value, W = 8 * (H & 1) + 4 * U;
       if constexpr (U == 0) wait_for<decltype(waits)::value>(v[0][0], v[0][1], v[1][0], v[1][1]);
       const u32x4 a = {v[U][0][0], v[U][0][1], v[U][1][0], v[U][1][1]}, b = {pw[W], pw[W + 1], pw[W + 2], pw[W + 3]};
-      fwd_output_mfma<-1>(a, b, o[H / 2]);
+      fwd_output_mfma(a, b, o[H / 2]);
       __builtin_amdgcn_sched_barrier(0);
       beside(uc);
       __builtin_amdgcn_sched_barrier(0);

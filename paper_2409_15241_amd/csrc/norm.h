@@ -71,6 +71,8 @@ inline int norm_bwd_slice_blocks(int slices, int slice_rows, int h) {
 // goes past the caches: backward 16384 x 2560 79.8 -> 69.8 us, 8192 x 4096 63.5 -> 53.6, 4096 x 5120 44.1 -> 39.6; forward with the residual
 // sum 73.3 -> 64.2, 58.7 -> 52.5, 38.8 -> 35.1.  Smaller ones are read again while they are still there: a step of 2 x 200
 // tokens of a 1024-wide block 126.5 us without and 129.6 with, 2048 tokens of 13B 664.7 and 673.6, 6018 of 2.7B 623.4 and 627.6.
+// Between 2^24 and 2^25 values the two sides meet (steps and forwards, without / with: 2048-wide 8192 tokens 551 / 559 and 208 / 203,
+// 14336 tokens 882 / 871 and 321 / 325; 4096-wide 4096 tokens 754 / 761, 6144 1061 / 1055; 2560-wide 8192 tokens 734 / 738 and 274 / 268).
 inline bool norm_streams(long rows, int h) { return rows * h >= 1L << 24; }
 
 int norm_bwd_blocks(int rows);              // 16 rows each until the block limit is reached
