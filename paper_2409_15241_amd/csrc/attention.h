@@ -41,7 +41,8 @@ inline bool attention_split_pays(const AttnArgs& a, bool backward) {
 // 12.3 / 13.9, but of few tiles, two workgroups to a compute unit, 256 x 256 9.7 / 8.9, 192 x 160 7.0 / 6.8; of 769 to 1024, two rounds either way, 192 x 400 12.3 / 13.4, 1024 x 128 28.4 / 29.5, but 512 x 200 19.1 / 17.3).  Heads of
 // 80 and 128 take two workgroups in either form, and one tile leaves nothing to overlap (64 positions: 256 heads of 64 4.4 / 4.2, of 80
 // 4.9 / 4.7, 512 of 128 8.3 / 7.8); heads of 128 of two tiles, two workgroups to some compute units, 128 x 308 11.5 / 10.8, 100 x 400
-// 10.7 / 10.1, but x 256 level and x 160 6.9 / 7.2.
+// 10.7 / 10.1, but x 256 level and x 160 6.9 / 7.2.  All with the operands in the caches, as the QKV product in front leaves them; out
+// of them heads of 128 of two tiles would be the other way round, 128 x 308 16.1 / 17.4.
 inline bool attention_fwd_serial(const AttnArgs& a) {
   const long wgs = (long)((a.seq + 127) / 128) * a.heads * a.batch;
   if (a.seq <= 64) return true;
