@@ -112,8 +112,9 @@ int domino_saved_slot(const domino_cfg* cfg, const char* name, size_t* offset, s
  *   streams[0..nstreams-1]: row group g runs on streams[g % m], m = min(nstreams, groups).  The backward puts weight and
  *   vector gradients on streams[m], beside the chain of input gradients, attention and norms, where the pool has that
  *   stream, streams[0] is not being captured and the block is large enough for it to pay; otherwise they follow on the
- *   groups' streams.  The last reduction of the vector gradients follows on streams[0] where a call's streams meet before it (behind
- *   weight gradients beside the chain, except between the blocks of a stack, and in the Norm1 part alone).  No other stream is used: three at most.  Which block gets what follows from cfg alone.
+ *   groups' streams.  The last reduction of the vector gradients follows on streams[0] where a call's streams meet before
+ *   it (behind weight gradients beside the chain, except between the blocks of a stack, and in the Norm1 part alone).  No
+ *   other stream is used: three at most.  Which block gets what follows from cfg alone.
  *   Streams overlap only on distinct hardware queues: create the pool once; HIP's default of four queues
  *   (GPU_MAX_HW_QUEUES, read when the runtime starts) is enough (domino_last_warning() tells when it is set too low).
  *   streams[0] may be under HIP graph capture (the other streams join the capture through the call's own
